@@ -87,6 +87,7 @@ struct ConvStep {
     void *dst;
     int64_t dst_stream_stride;
     int64_t dst_row0, dst_slot0;
+    int dst_ring;                // > 0: the next layer keeps its input rows in a ring of that many slots, slot = (dst_slot0 + o - dst_row0) mod dst_ring
     int to_output;
     int64_t out_cap;
     const void *w;               // [k_h][k_w][c_in][c_out]
@@ -116,6 +117,7 @@ struct PoolStep {
     void *dst;
     int64_t dst_stream_stride;
     int64_t dst_row0, dst_slot0;
+    int dst_ring;                // as in ConvStep
     int to_output;
     int64_t out_cap;
     unsigned long long *stats;
@@ -215,63 +217,60 @@ template <int NSTEP> struct CascadeArgsT {
 };
 using CascadeArgs = CascadeArgsT<kCasStepMax>;
 
-// One arriving row of a 3x3 / stride 1 / same-padded conv layer on the matrix cores.
-// Tap ky of input row y lands on output row o = y + 1 - ky.
-enum { kEmitNone = 0,      // row not final: back to the rolling buffer
-       kEmitDirect,        // final: activate and emit
-       kEmitHold,          // final, even row of a pool pair: becomes the pool's held row
-       kEmitPoolHeld,      // final, odd row of a pool pair: max with the held row, emit pooled row
-       kEmitPoolReg,       // final, odd row whose even partner became final in the same launch
-       kEmitKeep };        // not final, and the step's second input row follows at once: stays in the accumulators
-enum { kMfmaTile64x64 = 0, kMfmaTile128x32, kMfmaTile32x64, kMfmaTile32x32, kMfmaTile64x32 };
+// Output rows of one conv layer on the matrix cores (k_conv3x3_mfma.hip).  A layer keeps the rows of its
+// input that some output row still needs, as events, in a ring; an output row of c is formed in
+// registers once its last input row has arrived, activated and emitted.
+constexpr int kRowCells = 8;           // 16-byte cells per position that a chunk of input channels holds
+constexpr int kRowLaunchRows = 16;     // arriving rows one launch takes at most (longer pushes are several launches)
 
-struct MfmaTap {
-    int valid;             // output row exists
-    int fresh;             // first touched by this input row: starts from the bias
-    int emit;              // kEmit*
-    int store_held;        // kEmitHold: write the held row (not needed when its partner follows at once)
-    int ring_slot;
-    int64_t dst_slot;      // row slot in the destination (pooled row slot for the pool cases)
-};
+enum { kRowTake = 0,                   // no convolution: rows of the caller go into the ring and are counted
+       kRowSmall1, kRowSmall2,         // a wave does 16 positions x 16 channels of 1 / 2 output rows
+       kRowWide1, kRowWide2 };         // a wave does 32 positions x 32 channels of 1 / 2 output rows
 
-struct MfmaStep {
-    int w, c_in, c_out, c_out_pad;
-    unsigned c_in_rcp;                 // ceil(2^32 / c_in): k / c_in = umulhi(k, c_in_rcp) for the k in use
-    unsigned chunks_rcp;               // the same for the 16-byte cells per position (0: fewer channels than a cell)
+struct RowStep {
+    int form;                          // kRow*
+    int tiles;                         // workgroups per stream
+    int w, h;                          // positions per row, rows per sample (input and output alike)
+    int c_in, c_out;
+    int cells;                         // 16-byte cells per position (0: one to four channels)
+    int y0, n_rows;                    // first output row (index in the sample) and how many; kRowTake: input rows
+    int slot0;                         // ring slot of input row y0 - 1 (kRowTake: of row y0), whether that row exists or not
+    int ring_rows;                     // slots of the ring
+    int y_new;                         // input rows from this one on are in the caller's buffer, the others in the ring
+    int y_save;                        // kRowTake: rows from this one on go into the ring
+    int x_lo, x_hi;                    // kRowTake: columns of the row that are given (a pixel segment)
+    int wc_log;                        // log2 of the waves of a workgroup that lie side by side along the channels
+    int n_xt, n_cg;                    // position tiles of a row, channel groups
+    unsigned xt_rcp, cg_rcp;           // ceil(2^32 / n) of those (0 for one)
+    int nb[2];                         // blocks of 64 cells per row of the stretch in a full / in the last chunk
+    unsigned nb_rcp[2], cc_rcp[2];     // ceil(65536 / nb), ceil(65536 / cells per position) of those chunks
     int act, shr, clamp_hi;
-    int layer, pool_layer, n_layers;   // pool_layer < 0: no fused pool
-    int taps_y;                        // taps of this input row that land inside the output (for the counters)
-    int x_lo, x_hi;                    // columns of the input row that are given (a pixel segment); the rest reads as zero
-    int skip_clear_tiles;              // tiles no given column reaches have nothing to do (no row starts or ends)
-    int tile;                          // kMfmaTile*
-    MfmaTap t[3];
-    int dbl;                           // the step takes a second input row straight after the first (batch launches only):
-    int taps_y2;                       //   its taps_y, its tap rows (rows y and y+1 arrive in the accumulators), its place
-    MfmaTap t2[3];
-    int64_t in_row_off2;
-    const void *in;                    // input rows
-    int64_t in_stream_stride, in_row_off;   // elements
-    int in_by_position;
-    void *ring;  int64_t ring_stream_stride;
-    void *held;  int64_t held_stream_stride;
-    void *dst;   int64_t dst_stream_stride;
+    int pool;                          // 1: 2x2 max-pool behind the layer
+    int pool_from;                     // output rows before this one have been counted as the pool's events already
+    int pool_emit;                     // 0: only count the pool's events, emit nothing
     int to_output;
+    int dst_slot0, dst_rows;           // slot of the first emitted row, slots of the destination
+    int layer, pool_layer, next_layer, next_c_out, n_layers;     // next_layer: the layer whose events the emitted rows are (-1: it counts them itself)
+    int ev_limit;                      // a row's stretch of 32 positions with at most this many events goes the event path (0: never; at most half the list's length)
+    int in_stride, new_stride;         // elements per stream of the ring / of the caller's buffer
+    const void *in_ring, *in_new;
+    void *dst;
+    int64_t dst_stride;
     const void *wfrag;                 // fragment-ordered weights
     const void *w_ev;                  // int8 nets: weights for the event path, [kx][c_in][c_out_pad] words of the three ky taps
-    int ev_limit;                      // a tile with at most this many events (its halo included) goes the event path (0: never)
     const void *bias;
     unsigned long long *stats;
-    unsigned long long *issued;        // [stream][layer]: multiply-adds issued by the matrix instructions (zeros inside live steps included)
+    unsigned long long *issued;        // [stream][layer] multiply-adds issued by the matrix instructions, or null
 };
 
 // Steps of several layers for one launch of the matrix-core kernel.
-constexpr int kMfmaBatchMax = 8;
-struct MfmaBatch {
+constexpr int kRowUnits = 8;           // conv layers one launch can hold
+constexpr int kRowBatchMax = kRowUnits + 1;
+struct RowBatch {
     int n;
-    int tile;                          // kMfmaTile* (not 128x32), the same for every step
-    MfmaStep st[kMfmaBatchMax];
+    RowStep st[kRowBatchMax];
 };
-static_assert(sizeof(MfmaBatch) + sizeof(StreamSel) <= 4096, "a launch's arguments must fit the kernel-argument segment");
+static_assert(sizeof(RowBatch) + sizeof(StreamSel) <= 4096, "a launch's arguments must fit the kernel-argument segment");
 
 struct CopyOut {
     const void *src;             // output area [stream][out_cap][row_elems]

@@ -60,22 +60,18 @@ size_t cascade1d_weight_index(int c_in, int c_out, int ci, int co, int ky);
 int cascade1d_slot_off(int S, int rho);   // accumulator slot 0 relative to floor((y0 + p) / S)
 hipError_t launch_cascade1d(const CascadeArgs &a, const StreamSel &sel, const LaunchCtx &lc);
 
-// Matrix-core kernel for 3x3 / stride 1 / same-padded conv layers (bf16 and int8 nets).
+// Matrix-core kernel for 3x3 / stride 1 / same-padded conv layers.
 int conv3x3_mfma_vl(int prec);
 bool conv3x3_mfma_eligible(int prec, const Geom &g);
-int conv3x3_mfma_tile(const Geom &g, int n_streams);
 // Packs weights [k_h][k_w][c_in][c_out] into fragment order; returns the size (out may be null).
 size_t conv3x3_mfma_pack(int prec, const Geom &g, const void *w_khkwcico, void *out);
 // Where in that packing the event-path weights of an int8 layer begin (0: the layer has none), and the
-// most events (tile and halo) the event path takes.
+// most events per 32 positions of a row's stretch the event path takes.
 size_t conv3x3_mfma_event_weights(int prec, const Geom &g);
 int conv3x3_mfma_event_cap();
-// Tiles of one stream's row of w positions x c_out channels in a launch of that tile shape, and how many
-// workgroups of such a launch one compute unit holds at once (by the registers the kernel is built for).
-int conv3x3_mfma_tiles(int tile, int w, int c_out);
-int conv3x3_mfma_batch_resident(int prec, int tile);
-hipError_t launch_conv3x3_mfma(int prec, const MfmaStep &a, const StreamSel &sel, const LaunchCtx &lc);
-hipError_t launch_conv3x3_mfma_batch(int prec, const MfmaBatch &b, const StreamSel &sel, const LaunchCtx &lc);
+// Fills in how the workgroups of a step of a.n_rows rows lie (a.n_rows and a.ev_limit are set).
+void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, RowStep &a);
+hipError_t launch_conv3x3_mfma_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc);
 
 // Plain kernels that show what the machine delivers (copy, multiply-add chains, matrix-instruction
 // chains): bytes the compute kinds write for a launch of `blocks` workgroups, operations such a

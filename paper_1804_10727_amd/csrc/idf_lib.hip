@@ -77,6 +77,30 @@ struct StreamHost {
     int64_t head_base = 0;    // first of the rows they average (start of the current sample)
     int x_next = 0;           // columns of the current row received (pixel segments)
     int64_t eager_rows = 0;   // eager emission: input rows of the sample last presented that the levels have seen
+    int64_t sample = 0;       // whole samples received since open/reset
+    uint32_t early = 0;       // layer-by-layer pushes: matrix-core units whose waiting pool row has been counted (bit per unit)
+};
+
+// A convolution on the matrix cores, with the pool fused behind it if there is one.  Its input rows lie in a
+// ring of ring_rows rows per stream, row y of sample k in slot (k * rows per sample + y) mod ring_rows.
+struct RowUnit {
+    int l = 0, lp = 0;        // the layer, and the layer whose rows leave the unit
+    bool pool = false, last = false;
+    int next = -1;            // the unit that takes those rows (-1: the output area, or a layer of another kind)
+    int ring_rows = 0;
+    size_t ring_off = 0;
+    int64_t ring_stride = 0;
+};
+
+// How far a stream has come in a net whose layers run side by side: per unit the input rows that have
+// arrived and the rows of c that have been formed, both counted over samples since open/reset.
+struct RowProg {
+    int64_t in[kRowUnits + 1] = {}, out[kRowUnits + 1] = {};
+    uint32_t early = 0;       // units whose waiting pool row has been counted (bit per unit)
+    bool same(const RowProg &o, int n) const
+    {
+        return early == o.early && memcmp(in, o.in, sizeof(int64_t) * n) == 0 && memcmp(out, o.out, sizeof(int64_t) * n) == 0;
+    }
 };
 
 struct ProfRec {
@@ -135,19 +159,15 @@ struct idf_streams {
     int cas_parity = 0;
     size_t cas_transit_off = 0;
     int64_t cas_transit_stride = 0;
-    // 2-D nets served by the matrix-core kernel throughout: one launch per arriving row holds a
-    // step of every conv layer, each on a row that was complete before the launch.  Per conv
-    // layer ("unit") the rows waiting for it, and where in the ring of hand-over rows they lie.
-    struct StgRow { int64_t y; int slot; };
+    // Layers on the matrix-core kernel.  Where it serves the whole net (stg2d) one launch per push holds a step
+    // of every unit that has rows to form, each on rows that were complete before the launch.
+    std::vector<RowUnit> units;
+    std::vector<int> unit_of;                   // layer -> unit (-1: none)
     bool stg2d = false;
+    bool prog_same = true;                      // all streams stand at prog_all (else each at its own)
+    RowProg prog_all;
+    std::vector<RowProg> prog;
     std::vector<std::pair<int, int>> push_members;   // (position, id) of the streams of the push being checked
-    std::vector<int> stg_unit;                  // conv layer of unit k
-    std::vector<std::deque<StgRow>> stg_fifo;
-    std::vector<int64_t> stg_seq;               // rows emitted by unit k so far
-    int64_t stg_out_next = 0;                   // output slot of the next completed row
-    int stg_tile = kMfmaTile64x64;              // tile shape of the staged launches
-    int stg_slots = 4;                          // rows of a hand-over ring (kStgSlots, twice that where a step may take two rows)
-    bool stg_pairs = false;                     // pushes of several rows go through the layers two rows per launch
     // eager emission: per stream and level (0 = input) rows of state, announced values and deltas in a
     // workspace of its own -- rings of the rows that can still change or be looked at (nets without
     // biases) or whole maps
@@ -207,6 +227,8 @@ struct Layout {
     std::vector<size_t> w_off, b_off, wm_off, ring_off, held_off, transit_off;
     std::vector<int64_t> ring_stride, held_stride, transit_stride;
     std::vector<int> transit_cap;
+    std::vector<int> mfma;           // per layer: 1 = matrix-core conv kernel, 2 = pool fused into the conv before it
+    std::vector<RowUnit> units;
     size_t out_off = 0, stats_off = 0, issued_off = 0, head_off = 0, total = 0;
     int64_t out_stride = 0;
     bool cascade1d = false;          // the whole-net 1-D kernel serves this stream set
@@ -216,12 +238,10 @@ struct Layout {
     idf_sizes sizes{};
 };
 
-// Staged layers (one launch per arriving row, layer l a launch behind layer l-1): rows a layer has
-// completed wait for the next layer's step in a small ring per layer and stream.  The host never
-// leaves more than kStgWait rows waiting per layer when a call returns; a launch reads one slot,
-// leaves at most kStgWait - 1 waiting and writes at most two new rows, hence kStgSlots.
+// Staged layers (one launch per push, layer l a launch behind layer l-1), rows pushed one at a time: a layer
+// takes its rows in pairs, so besides the K_h rows its output rows still need at most two rows wait for it
+// when a call returns.  Pushes of several rows leave up to the rows one launch completes, and one more.
 constexpr int kStgWait = 2;
-constexpr int kStgSlots = 4;
 
 // The layers run strictly depth-first within each call (nothing waits between layers across
 // calls) when the staged modes are switched off.
@@ -241,7 +261,20 @@ bool net_all_mfma(const idf_net &net)
             return false;
         }
     }
-    return units >= 1 && units <= kMfmaBatchMax;
+    return units >= 1 && units <= kRowUnits;
+}
+
+// Which layers run on the matrix-core kernel: 1 = a convolution, 2 = a pool fused into the one before it.
+std::vector<int> mfma_layers(const idf_net &net)
+{
+    std::vector<int> m(net.g.size(), 0);
+    if (getenv("IDF_NO_MFMA")) return m;
+    for (size_t l = 0; l < net.g.size(); ++l) {
+        if (net.wm_img[l].empty()) continue;
+        m[l] = 1;
+        if (l + 1 < net.g.size() && net.g[l + 1].kind == IDF_MAXPOOL && net.g[l + 1].k_w == 2) m[l + 1] = 2;
+    }
+    return m;
 }
 
 int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout &L)
@@ -253,15 +286,19 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     L.ring_off.assign(n, 0); L.held_off.assign(n, 0); L.transit_off.assign(n, 0);
     L.ring_stride.assign(n, 0); L.held_stride.assign(n, 0); L.transit_stride.assign(n, 0);
     L.transit_cap.assign(n, 0);
+    // rows a layer completes in one push at most, and in one launch of the staged mode (which takes
+    // kRowLaunchRows arriving rows at most)
+    std::vector<int> launch_cap(n, 0);
     {
-        int cap = max_seg;
+        int cap = max_seg, lcap = std::min(max_seg, kRowLaunchRows);
         for (int l = 0; l < n; ++l) {
-            cap = std::max(1, max_emit(net.g[l], cap));
-            L.transit_cap[l] = cap;
+            L.transit_cap[l] = cap = std::max(1, max_emit(net.g[l], cap));
+            launch_cap[l] = lcap = std::max(1, max_emit(net.g[l], lcap));
         }
     }
     L.cascade1d = cascade1d_eligible(net.precision, net.g.data(), n, L.transit_cap.data(), max_seg);
     const bool all_mfma = net_all_mfma(net);
+    L.mfma = mfma_layers(net);
     for (int l = 0; l < n; ++l) {
         if (net.g[l].kind != IDF_CONV) continue;
         // the 1-D cascade reads its own packing, taps zero-padded to kCasKMax
@@ -274,30 +311,42 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     L.sizes.weights_bytes = off;
     size_t state_per_stream = 0, transit_per_stream = 0, handover_per_stream = 0;
     const bool staged_rows = all_mfma && !strict_rows();
-    int cap = max_seg;
     for (int l = 0; l < n; ++l) {
         const Geom &g = net.g[l];
+        // The retained state of a layer is K_h rows: of c, or, on the matrix cores, of the events of its input that
+        // some row of c has yet to take in (they lie in the ring the layer before writes them to).
         if (g.kind == IDF_CONV) {
             L.ring_stride[l] = (int64_t)g.k_h * g.w_out * g.c_out;
-            L.ring_off[l] = off; off = align_up(off + (size_t)L.ring_stride[l] * 4 * B);
+            if (!L.mfma[l]) { L.ring_off[l] = off; off = align_up(off + (size_t)L.ring_stride[l] * 4 * B); }
             state_per_stream += (size_t)L.ring_stride[l] * 4;
         } else {
             L.held_stride[l] = (int64_t)g.w_in * g.c_out;
-            L.held_off[l] = off; off = align_up(off + (size_t)L.held_stride[l] * eb * B);
+            if (!L.mfma[l]) { L.held_off[l] = off; off = align_up(off + (size_t)L.held_stride[l] * eb * B); }
             state_per_stream += (size_t)L.held_stride[l] * eb;
         }
-        cap = L.transit_cap[l];
+        if (L.mfma[l] == 1) {
+            RowUnit u;
+            u.l = l; u.pool = l + 1 < n && L.mfma[l + 1] == 2; u.lp = u.pool ? l + 1 : l; u.last = u.lp == n - 1;
+            if (!u.last && L.mfma[u.lp + 1] == 1) u.next = (int)L.units.size() + 1;
+            // rows arriving with a launch while the ones before them are being read, and the rows still needed
+            const int cap = l == 0 ? max_seg : L.transit_cap[l - 1], lcap = l == 0 ? std::min(max_seg, kRowLaunchRows) : launch_cap[l - 1];
+            u.ring_rows = l == 0 ? lcap + 6 : std::max(2 * lcap + 4, cap + 4);
+            u.ring_stride = (int64_t)u.ring_rows * g.w_in * g.c_in;
+            u.ring_off = off; off = align_up(off + (size_t)u.ring_stride * eb * B);
+            if (l > 0) {
+                L.transit_off[l - 1] = u.ring_off; L.transit_stride[l - 1] = u.ring_stride;
+                // rows that can wait for the layer when a call returns
+                if (staged_rows) handover_per_stream += (size_t)(max_seg == 1 ? kStgWait : lcap + 1) * g.w_in * g.c_in * eb;
+            }
+            transit_per_stream += (size_t)u.ring_stride * eb;
+            L.units.push_back(u);
+        }
         // (the 1-D cascade passes rows on inside LDS; a conv layer's rows go straight into a fused pool)
-        const bool into_fused_pool = all_mfma && !getenv("IDF_NO_MFMA") && l + 1 < n && net.g[l + 1].kind == IDF_MAXPOOL;
-        if (l < n - 1 && !L.cascade1d && !into_fused_pool) {
-            // room for the hand-over ring when the layers are staged across pushes
-            // (a step that takes two rows can complete three and reads two more meanwhile: twice the slots)
-            const int rows = all_mfma ? std::max(cap, max_seg >= 2 ? 2 * kStgSlots : kStgSlots) : cap;
-            L.transit_stride[l] = (int64_t)rows * g.w_out * g.c_out;
+        const bool into_fused_pool = l + 1 < n && L.mfma[l + 1] == 2, into_ring = l + 1 < n && L.mfma[l + 1] == 1;
+        if (l < n - 1 && !L.cascade1d && !into_fused_pool && !into_ring) {
+            L.transit_stride[l] = (int64_t)L.transit_cap[l] * g.w_out * g.c_out;
             L.transit_off[l] = off; off = align_up(off + (size_t)L.transit_stride[l] * eb * B);
             transit_per_stream += (size_t)L.transit_stride[l] * eb;
-            // rows that can wait for the next conv layer when a call returns
-            if (staged_rows) handover_per_stream += (size_t)kStgWait * g.w_out * g.c_out * eb;
         }
     }
     if (out_cap <= 0) {
@@ -692,194 +741,347 @@ int enqueue_cascade1d(idf_streams *s, const StreamSel &sel, const void *dev_rows
     return worst >= kCasStepMax ? cascade_flush(s) : IDF_OK;
 }
 
-// The matrix-core step of conv layer l (with the pool fused behind it, if any) for input row y:
-// everything but where the input row lies and where emitted rows go.  rows_out[ky] = index, in
-// the layer whose rows leave the step, of the row tap ky emits, or -1.
-void make_mfma_step(idf_streams *s, int l, int64_t y, int n_streams, MfmaStep &a, int64_t rows_out[3], double &bytes)
+// ---- layers on the matrix cores -------------------------------------------------------------------
+// Rows counted over samples: sample * rows per sample + row.
+
+// Rows of c of a layer that can be formed once `in` input rows have arrived.
+int64_t rows_ready(const Geom &g, int64_t in) { return in / g.h_in * g.h_out + rows_final(g, in % g.h_in); }
+// First input row that row o of c needs.
+int64_t first_needed(const Geom &g, int64_t o)
+{
+    return o / g.h_out * g.h_in + std::max<int64_t>(0, o % g.h_out * g.s_h - g.p_h);
+}
+int mod_rows(int64_t y, int64_t n) { return (int)((y % n + n) % n); }
+
+// How many rows leave a unit that forms rows [o, o + n) of c (all of one sample).
+int64_t rows_leaving(const idf_net &net, const RowUnit &u, int64_t o, int64_t n)
+{
+    if (!u.pool) return n;
+    const int h = net.g[u.l].h_out, hp = net.g[u.lp].h_out;
+    const int64_t y = o % h;
+    return std::min<int64_t>((y + n) / 2, hp) - std::min<int64_t>(y / 2, hp);
+}
+// The first of them, counted over samples.
+int64_t leaving_index(const idf_net &net, const RowUnit &u, int64_t o)
+{
+    if (!u.pool) return o;
+    const int h = net.g[u.l].h_out;
+    return o / h * net.g[u.lp].h_out + o % h / 2;
+}
+
+// The step that forms rows [o, o + n) of c of unit k: everything but where rows that are new in this
+// launch lie (y_new) and, for a layer of another kind or the output area behind it, the destination.
+void row_step(idf_streams *s, int k, int64_t o, int64_t n, int n_streams, bool counted, RowStep &a, double &bytes)
 {
     const idf_net &net = *s->net;
-    const int n = (int)net.g.size();
-    const int eb = ev_bytes(net.precision);
-    const Geom &g = net.g[l];
-    const bool pool = l + 1 < n && s->mfma[l + 1] == 2;
-    const int lp = pool ? l + 1 : l;
-    const bool last_out = lp == n - 1;
-    const Geom &gp = net.g[lp];
-    a = MfmaStep{};
-    a.w = g.w_out; a.c_in = g.c_in; a.c_out = g.c_out; a.c_out_pad = (g.c_out + 63) / 64 * 64;
-    a.c_in_rcp = (unsigned)((0x100000000ull + g.c_in - 1) / g.c_in);
-    {
-        const int chunks = g.c_in / conv3x3_mfma_vl(net.precision);
-        a.chunks_rcp = chunks > 1 ? (unsigned)((0x100000000ull + chunks - 1) / chunks) : 0u;
-    }
+    const RowUnit &u = s->units[k];
+    const Geom &g = net.g[u.l];
+    const int eb = ev_bytes(net.precision), nl = (int)net.g.size();
+    a = RowStep{};
+    a.w = g.w_in; a.h = g.h_in; a.c_in = g.c_in; a.c_out = g.c_out;
+    a.y0 = (int)(o % g.h_out); a.n_rows = (int)n;
+    a.ring_rows = u.ring_rows;
+    a.slot0 = mod_rows(o / g.h_out * g.h_in + a.y0 - g.p_h, u.ring_rows);
+    a.y_new = 1 << 30;
     a.act = g.act; a.shr = g.shr; a.clamp_hi = g.clamp_hi;
-    a.layer = l; a.pool_layer = pool ? l + 1 : -1; a.n_layers = n;
-    a.tile = conv3x3_mfma_tile(g, n_streams);
-    const bool part = l == 0 && s->part.on;
-    a.x_lo = part ? s->part.x_lo : 0; a.x_hi = part ? s->part.x_hi : g.w_in;
-    const bool first_part = !part || s->part.first, last_part = !part || s->part.last;
-    a.skip_clear_tiles = !first_part && !last_part;
-    const int64_t fin_after = rows_final(g, y + 1);
-    int taps_y = 0;
-    for (int ky = 0; ky < 3; ++ky) {
-        MfmaTap &t = a.t[ky];
-        rows_out[ky] = -1;
-        const int64_t o = y + 1 - ky;
-        t.valid = o >= 0 && o < g.h_out;
-        if (!t.valid) continue;
-        ++taps_y;
-        t.fresh = first_part && std::max<int64_t>(0, o - 1) >= y;     // later segments of the row continue it
-        t.ring_slot = (int)(o % 3);
-        const bool fin = last_part && o < fin_after;                  // nothing is final before the row is whole
-        if (!fin) { t.emit = kEmitNone; continue; }
-        int64_t row = o;                                // row index in the leaving layer
-        if (!pool) t.emit = kEmitDirect;
-        else if (o % 2 == 0) {
-            t.emit = kEmitHold;
-            t.store_held = (o / 2 < gp.h_out) && !(o + 1 < fin_after);
-            continue;
-        } else {
-            t.emit = (o - 1 >= rows_final(g, y)) ? kEmitPoolReg : kEmitPoolHeld;
-            row = o / 2;
-            if (row >= gp.h_out) { t.emit = kEmitHold; t.store_held = 0; continue; }
-        }
-        rows_out[ky] = row;
+    a.pool = u.pool; a.pool_layer = u.pool ? u.lp : -1; a.pool_emit = 1; a.pool_from = a.y0 + (counted ? 1 : 0);
+    a.layer = u.l; a.n_layers = nl;
+    a.next_layer = -1;
+    if (u.next >= 0) { a.next_layer = s->units[u.next].l; a.next_c_out = net.g[a.next_layer].c_out; }
+    a.in_ring = s->ws + u.ring_off; a.in_stride = (int)u.ring_stride;
+    a.to_output = u.last;
+    if (u.last) {
+        a.dst = s->ws + s->out_off; a.dst_stride = s->out_stride; a.dst_rows = (int)s->out_cap;
+    } else {
+        a.dst = s->ws + s->transit_off[u.lp]; a.dst_stride = s->transit_stride[u.lp];
+        a.dst_rows = u.next >= 0 ? s->units[u.next].ring_rows : s->transit_cap[u.lp];
     }
-    a.taps_y = taps_y;
-    a.ring = s->ws + s->ring_off[l]; a.ring_stream_stride = s->ring_stride[l];
-    a.held = pool ? s->ws + s->held_off[l + 1] : nullptr;
-    a.held_stream_stride = pool ? s->held_stride[l + 1] : 0;
-    a.dst = last_out ? (void *)(s->ws + s->out_off) : (void *)(s->ws + s->transit_off[lp]);
-    a.dst_stream_stride = last_out ? s->out_stride : s->transit_stride[lp];
-    a.to_output = last_out;
-    a.wfrag = s->ws + s->wm_off[l];
+    if (u.last || u.next >= 0) a.dst_slot0 = mod_rows(leaving_index(net, u, o), a.dst_rows);
+    a.wfrag = s->ws + s->wm_off[u.l];
     if (const size_t ev_at = conv3x3_mfma_event_weights(net.precision, g)) {
-        // Up to how many events a tile goes the event path, once the caller has switched it on: a first
-        // layer of a few channels whenever the list holds them, elsewhere ev_per_step events per K-step
-        // that the contraction would take.
-        a.w_ev = s->ws + s->wm_off[l] + ev_at;
-        const int vl = conv3x3_mfma_vl(net.precision);
-        const int steps = (3 * g.c_in + 2 * vl - 1) / (2 * vl);
+        // Up to how many events the stretch of a row goes the event path, once the caller has switched it on: a
+        // first layer of a few channels whenever the list holds them, elsewhere ev_per_step events per 32
+        // elements of the contraction.
+        a.w_ev = s->ws + s->wm_off[u.l] + ev_at;
+        const int vl = conv3x3_mfma_vl(net.precision), steps = (3 * g.c_in + 2 * vl - 1) / (2 * vl);
         // (layers of more than 16 input channels never take it: their share of the weights would crowd
-        // the LDS of every workgroup of the launch for tiles too sparse to exist in practice)
+        // the LDS of every workgroup of the launch for stretches too sparse to exist in practice)
         a.ev_limit = s->ev_per_step == 0 || g.c_in > 16 ? 0
                      : g.c_in < vl ? conv3x3_mfma_event_cap() : std::min(conv3x3_mfma_event_cap(), steps * s->ev_per_step);
     }
-    a.bias = net.b_img[l].empty() ? nullptr : s->ws + s->b_off[l];
+    a.bias = net.b_img[u.l].empty() ? nullptr : s->ws + s->b_off[u.l];
     a.stats = (unsigned long long *)(s->ws + s->stats_off);
     a.issued = s->count_issued ? (unsigned long long *)(s->ws + s->issued_off) : nullptr;
-    ConvStep c{};
-    c.g = g; c.y0 = y; c.cnt = 1; c.o_lo = rows_final(g, y); c.o_fin = fin_after;
-    c.o_hi = std::max(rows_touched(g, y + 1), c.o_fin);
-    c.in_by_position = l == 0; c.to_output = !pool && last_out; c.bias = a.bias;
-    bytes = conv_step_bytes(net, c, n_streams);
-    if (pool) bytes += n_streams * (double)g.w_out * g.c_out * eb;      // the held row, written or read
+    conv3x3_mfma_shape(net.precision, g, n_streams, a);
+    // Bytes the step has to move: the input rows the rows of c need (their events), the rows that leave, weights once.
+    // Rows handed from layer to layer on their way out are not counted: the method does not require them to leave the chip.
+    const int64_t i_lo = std::max<int64_t>(0, a.y0 - g.p_h), i_hi = std::min<int64_t>(g.h_in, a.y0 + n - g.p_h + g.k_h - 1);
+    bytes += n_streams * ((double)(i_hi - i_lo) * g.w_in * g.c_in * eb +
+                          (u.last ? (double)rows_leaving(net, u, o, n) * net.out_w * net.out_c * 4 : 0.0)) +
+             (double)g.k_h * g.k_w * g.c_in * g.c_out * w_bytes(net.precision) + (a.bias ? g.c_out * 4.0 : 0.0);
 }
 
-// One launch for all streams: every conv layer that has a row waiting takes one step, layer 0 on
-// row j of the pushed segment (j < 0: no new row, the layers only move on).  What a step emits
-// waits for the next layer's step in a later launch.
-int stg_tick(idf_streams *s, const void *dev_rows, int n_rows, int j, int64_t r, bool pairs = false)
+// Rows [y, y + n) of a sample (counted over samples: from `at`) go into the ring of the unit that serves layer l and
+// are counted as its events; save: from which of them on (index in the sample) they are needed later.
+void take_step(idf_streams *s, int k, int64_t at, int64_t n, const void *dev_rows, int row_of_buffer, int n_rows, int64_t save_at, RowStep &a)
 {
     const idf_net &net = *s->net;
-    const int nu = (int)s->stg_unit.size();
-    StreamSel all{};
-    all.n = s->B; all.base = 0; all.pos0 = 0;
-    MfmaBatch b{};
-    b.tile = s->stg_tile;
-    double bytes_total = 0;
-    for (int k = nu - 1; k >= 0; --k) {         // deeper first: they take only rows that were there before
-        const int l = s->stg_unit[k];
-        const Geom &g = net.g[l];
-        // the row the unit takes, and with pairs the one after it if that is there too (same sample)
-        int64_t y, y2 = -1;
-        int slot = 0, slot2 = 0;
-        if (k == 0) {
-            if (j < 0) continue;
-            y = r + j;
-            if (pairs && j + 1 < n_rows) y2 = y + 1;
-        } else {
-            std::deque<idf_streams::StgRow> &f = s->stg_fifo[k];
-            if (f.empty()) continue;
-            y = f.front().y; slot = f.front().slot;
-            f.pop_front();
-            if (pairs && !f.empty() && f.front().y == y + 1) { y2 = y + 1; slot2 = f.front().slot; f.pop_front(); }
-        }
-        MfmaStep a;
-        int64_t rows_out[2][3];
-        double bytes = 0;
-        make_mfma_step(s, l, y, s->B, a, rows_out[0], bytes);
-        const int lp = l - 1;                     // the layer whose rows this one reads: conv or fused pool before it
-        if (k == 0) {
-            a.in = dev_rows; a.in_stream_stride = (int64_t)n_rows * net.in_w * net.in_c; a.in_by_position = 1;
-            a.in_row_off = (int64_t)j * g.w_in * g.c_in;
-            a.in_row_off2 = (int64_t)(j + 1) * g.w_in * g.c_in;
-            if (s->part.on) { a.in_stream_stride = (int64_t)(s->part.x_hi - s->part.x_lo) * net.in_c; a.in_row_off = -(int64_t)s->part.x_lo * net.in_c; }
-        } else {
-            a.in = s->ws + s->transit_off[lp]; a.in_stream_stride = s->transit_stride[lp]; a.in_by_position = 0;
-            a.in_row_off = (int64_t)slot * g.w_in * g.c_in;
-            a.in_row_off2 = (int64_t)slot2 * g.w_in * g.c_in;
-        }
-        if (y2 >= 0) {
-            // The second row's step, folded into the first: rows y and y+1 of c stay in the accumulators in between,
-            // and a pool pair that the two rows complete between them keeps its even row in registers.
-            MfmaStep a2;
-            double bytes2 = 0;
-            make_mfma_step(s, l, y2, s->B, a2, rows_out[1], bytes2);
-            a.dbl = 1; a.taps_y2 = a2.taps_y;
-            for (int ky = 0; ky < 3; ++ky) a.t2[ky] = a2.t[ky];
-            for (int ky = 0; ky < 2; ++ky)
-                if (a.t[ky].valid && a.t[ky].emit == kEmitNone) a.t[ky].emit = kEmitKeep;
-            if (a.t[2].valid && a.t[2].emit == kEmitHold && a.t2[2].valid && a.t2[2].emit == kEmitPoolHeld) {
-                a.t[2].store_held = 0; a.t2[2].emit = kEmitPoolReg;
-            }
-            // what the pair has to move by the method: the two rows of c between the two input rows neither leave
-            // the chip nor come back (two rows written and two read fewer than two steps)
-            bytes += bytes2 - (double)s->B * 4.0 * g.w_out * g.c_out * 4.0;
-        }
-        for (int sub = 0; sub < (y2 >= 0 ? 2 : 1); ++sub) {
-            MfmaTap *t = sub ? a.t2 : a.t;
-            for (int ky = 2; ky >= 0; --ky) {     // increasing row index
-                if (rows_out[sub][ky] < 0) continue;
-                if (k == nu - 1) {
-                    t[ky].dst_slot = s->stg_out_next;
-                    s->stg_out_next = (s->stg_out_next + 1) % s->out_cap;
-                } else {
-                    const int wslot = (int)(s->stg_seq[k]++ % s->stg_slots);
-                    t[ky].dst_slot = wslot;
-                    s->stg_fifo[k + 1].push_back({rows_out[sub][ky], wslot});
-                }
-            }
-        }
-        b.st[b.n++] = a;
-        bytes_total += bytes;
+    const RowUnit &u = s->units[k];
+    const Geom &g = net.g[u.l];
+    const int vl = conv3x3_mfma_vl(net.precision);
+    a = RowStep{};
+    a.form = kRowTake; a.tiles = (int)n;
+    a.w = g.w_in; a.h = g.h_in; a.c_in = g.c_in; a.c_out = g.c_out;
+    a.cells = g.c_in % vl == 0 && g.c_in >= vl ? g.c_in / vl : 0;
+    a.y0 = (int)(at % g.h_in); a.n_rows = (int)n;
+    a.ring_rows = u.ring_rows; a.slot0 = mod_rows(at, u.ring_rows);
+    a.in_ring = s->ws + u.ring_off; a.in_stride = (int)u.ring_stride;
+    a.x_lo = 0; a.x_hi = g.w_in;
+    a.layer = u.l; a.n_layers = (int)net.g.size();
+    a.stats = (unsigned long long *)(s->ws + s->stats_off);
+    if (!dev_rows) return;                         // rows a layer of another kind has put into the ring: only counted
+    a.in_new = dev_rows;
+    a.y_new = a.y0 - row_of_buffer;
+    a.y_save = a.y0 + (int)std::max<int64_t>(0, save_at - at);
+    a.new_stride = n_rows * net.in_w * net.in_c;
+    if (s->part.on) {                              // a pixel segment: one row's columns [x_lo, x_hi)
+        a.x_lo = s->part.x_lo; a.x_hi = s->part.x_hi; a.y_save = a.y0; a.y_new = a.y0;
+        a.new_stride = (a.x_hi - a.x_lo) * net.in_c;
     }
-    if (b.n == 0) return IDF_OK;
-    // Dispatch order of the steps within the launch: deepest layer first (its workgroups run longest).
-    // When the launch holds more workgroups than the chip takes at once, the others follow shallowest
-    // first: the short workgroups of the first layers then finish early and hand their places to what
-    // did not fit.  (Measured: 4 % faster on the VGG-style workload, whose launches are 1.25 rounds;
-    // 15 % slower on the small-image workload, whose launches fit at once: hence the condition.)
-    if (b.n >= 3 && s->cus > 0) {
-        long wgs = 0;
-        for (int k = 0; k < b.n; ++k) wgs += (long)conv3x3_mfma_tiles(b.tile, b.st[k].w, b.st[k].c_out) * s->B;
-        if (wgs > (long)s->cus * conv3x3_mfma_batch_resident(net.precision, b.tile)) std::reverse(b.st + 1, b.st + b.n);
-    }
-    hipError_t e = launch_conv3x3_mfma_batch(net.precision, b, all, launch_ctx(s, kKindConvMfma, bytes_total, -1));
-    return e == hipSuccess ? IDF_OK : dev_fail(e, "staged mfma conv launch");
 }
 
-bool stg_pending(const idf_streams *s, size_t more_than)
+int launch_rows(idf_streams *s, const RowBatch &b, const StreamSel &sel, double bytes, int layer)
 {
-    for (const auto &f : s->stg_fifo) if (f.size() > more_than) return true;
+    if (b.n == 0) return IDF_OK;
+    hipError_t e = launch_conv3x3_mfma_rows(s->net->precision, b, sel, launch_ctx(s, kKindConvMfma, bytes, layer));
+    return e == hipSuccess ? IDF_OK : dev_fail(e, "mfma conv launch");
+}
+
+// One launch for streams that all stand at p: every unit forms the rows it has the input for -- in pairs,
+// which share their weights and two of four input rows; a single row only where the sample ends or, with
+// flush, where a caller wants everything out -- the first unit from the n_new rows of the caller's buffer
+// too.  What a unit emits waits for the next unit's step in a later launch.  Returns false, with nothing
+// launched and p unchanged, when the ring of the first unit has no room for the new rows yet, or when
+// there is nothing to do.
+bool row_plan(idf_streams *s, RowProg &p, int n_streams, const void *dev_rows, int row0, int n_rows, int n_new, bool flush, RowBatch &b, double &bytes)
+{
+    const idf_net &net = *s->net;
+    const int nu = (int)s->units.size();
+    RowProg q = p;
+    b.n = 0;
+    const bool part = s->part.on && n_new > 0;
+    if (n_new > 0) b.n = 1;                        // place for the step that takes them
+    for (int k = nu - 1; k >= 0; --k) {            // deepest first: its workgroups run longest
+        const RowUnit &u = s->units[k];
+        const Geom &g = net.g[u.l];
+        const int64_t have = p.in[k] + (k == 0 && !part ? n_new : 0);
+        const int64_t o = p.out[k], sample_end = (o / g.h_out + 1) * g.h_out;
+        int64_t n = std::min(rows_ready(g, have), sample_end) - o;
+        if (o + n < sample_end && (u.pool || !flush)) n &= ~(int64_t)1;
+        if (u.next >= 0) {                         // room in the ring of the unit behind (as it stands before the launch)
+            const RowUnit &v = s->units[u.next];
+            const int64_t room = v.ring_rows - (p.in[u.next] - first_needed(net.g[v.l], p.out[u.next]));
+            while (n > 0 && rows_leaving(net, u, o, n) > room) n -= n % 2 ? 1 : 2;
+        }
+        if (n <= 0) continue;
+        if (b.n >= kRowBatchMax) continue;
+        row_step(s, k, o, n, n_streams, (q.early >> k) & 1u, b.st[b.n], bytes);
+        if (k == 0 && n_new > 0 && !part && p.in[0] / g.h_in == o / g.h_out) {      // (else the new rows are of the next sample)
+            b.st[b.n].in_new = (const char *)dev_rows + (int64_t)row0 * net.in_w * net.in_c * ev_bytes(net.precision);
+            b.st[b.n].new_stride = n_rows * net.in_w * net.in_c;
+            b.st[b.n].y_new = (int)(p.in[0] % g.h_in);
+        }
+        ++b.n;
+        q.early &= ~(1u << k);
+        q.out[k] = o + n;
+        if (u.next >= 0) q.in[u.next] += rows_leaving(net, u, o, n);
+    }
+    if (n_new > 0) {
+        q.in[0] += n_new;
+        const int64_t keep = first_needed(net.g[0], q.out[0]);
+        // rows still needed, and those this launch reads while it writes the new ones
+        if (q.in[0] - std::min(keep, first_needed(net.g[0], p.out[0])) > s->units[0].ring_rows) return false;
+        take_step(s, 0, p.in[0], n_new, dev_rows, row0, n_rows, keep, b.st[0]);
+        // last in dispatch order: the shortest
+        std::rotate(b.st, b.st + 1, b.st + b.n);
+        bytes += (double)n_streams * n_new * net.in_w * net.in_c * ev_bytes(net.precision);
+    }
+    if (b.n == 0) return false;
+    p = q;
+    return true;
+}
+
+// Streams that stand at p receive n_rows rows (dev_rows), or (dev_rows null) everything on its way is brought through.
+int row_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *dev_rows, int n_rows)
+{
+    RowBatch b;
+    int done = 0;
+    for (int guard = 0;; ++guard) {
+        double bytes = 0;
+        const int n_new = dev_rows ? (int)std::min<int64_t>({n_rows - done, kRowLaunchRows, s->net->in_h - p.in[0] % s->net->in_h}) : 0;
+        if (dev_rows && done == n_rows) return IDF_OK;
+        bool go = row_plan(s, p, sel.n, dev_rows, done, n_rows, n_new, !dev_rows, b, bytes);
+        if (go) done += n_new;
+        else if (dev_rows) go = row_plan(s, p, sel.n, nullptr, 0, 0, 0, guard > 64, b, bytes);
+        if (!go) return dev_rows ? fail(IDF_ESTATE, "internal: rows between layers do not move on") : IDF_OK;
+        int rc = launch_rows(s, b, sel, bytes, -1);
+        if (rc != IDF_OK) return rc;
+    }
+}
+
+void prog_split(idf_streams *s)
+{
+    if (!s->prog_same) return;
+    std::fill(s->prog.begin(), s->prog.end(), s->prog_all);
+    s->prog_same = false;
+}
+void prog_join(idf_streams *s)
+{
+    const int nu = (int)s->units.size();
+    for (size_t i = 1; i < s->prog.size(); ++i)
+        if (!s->prog[i].same(s->prog[0], nu)) return;
+    s->prog_all = s->prog[0];
+    s->prog_same = true;
+}
+
+// Calls f(selection, progress) for the members (position, id), those that stand at the same place together.
+template <class F> int for_each_prog(idf_streams *s, const std::vector<std::pair<int, int>> &members, F &&f)
+{
+    const int nu = (int)s->units.size();
+    if (s->prog_same) {
+        if ((int)members.size() == s->B && members[0] == std::make_pair(0, 0) && members.back() == std::make_pair(s->B - 1, s->B - 1)) {
+            bool straight = true;
+            for (int i = 0; i < s->B && straight; ++i) straight = members[i].second == i;
+            if (straight) {
+                StreamSel all{};
+                all.n = s->B; all.base = 0; all.pos0 = 0;
+                return f(all, s->prog_all);
+            }
+        }
+        prog_split(s);
+    }
+    std::vector<char> taken(members.size(), 0);
+    std::vector<std::pair<int, int>> group;
+    for (size_t i = 0; i < members.size(); ++i) {
+        if (taken[i]) continue;
+        const RowProg at = s->prog[members[i].second];
+        group.clear();
+        for (size_t j = i; j < members.size(); ++j)
+            if (!taken[j] && s->prog[members[j].second].same(at, nu)) { taken[j] = 1; group.push_back(members[j]); }
+        RowProg moved = at;
+        int rc = for_each_selection(group, [&](const StreamSel &sel) {
+            moved = at;
+            return f(sel, moved);
+        });
+        if (rc != IDF_OK) return rc;
+        for (const auto &m : group) s->prog[m.second] = moved;
+    }
+    if ((int)members.size() == s->B) prog_join(s);
+    return IDF_OK;
+}
+
+std::vector<std::pair<int, int>> all_members(const idf_streams *s)
+{
+    std::vector<std::pair<int, int>> m(s->B);
+    for (int i = 0; i < s->B; ++i) m[i] = {i, i};
+    return m;
+}
+
+bool row_pending(const idf_streams *s, const RowProg &p)
+{
+    for (size_t k = 0; k < s->units.size(); ++k) {
+        const RowUnit &u = s->units[k];
+        const Geom &g = s->net->g[u.l];
+        const int64_t o = p.out[k], end = (o / g.h_out + 1) * g.h_out;
+        int64_t n = std::min(rows_ready(g, p.in[k]), end) - o;
+        if (o + n < end && u.pool) n &= ~(int64_t)1;
+        if (n > 0) return true;
+    }
     return false;
 }
 
 int stg_drain(idf_streams *s)
 {
-    while (s->stg2d && stg_pending(s, 0)) {
-        int rc = stg_tick(s, nullptr, 0, -1, 0);
-        if (rc != IDF_OK) return rc;
+    if (!s->stg2d) return IDF_OK;
+    if (s->prog_same) {
+        if (!row_pending(s, s->prog_all)) return IDF_OK;
+        StreamSel all{};
+        all.n = s->B; all.base = 0; all.pos0 = 0;
+        return row_run(s, all, s->prog_all, nullptr, 0);
+    }
+    bool any = false;
+    for (const RowProg &p : s->prog) any = any || row_pending(s, p);
+    if (!any) return IDF_OK;
+    return for_each_prog(s, all_members(s), [&](const StreamSel &sel, RowProg &p) { return row_run(s, sel, p, nullptr, 0); });
+}
+
+// Where a stream that has received `in` rows stands once nothing is on its way.
+RowProg prog_at(const idf_streams *s, int64_t in, bool counted)
+{
+    RowProg p;
+    const idf_net &net = *s->net;
+    p.in[0] = in;
+    for (size_t k = 0; k < s->units.size(); ++k) {
+        const RowUnit &u = s->units[k];
+        const Geom &g = net.g[u.l];
+        int64_t o = rows_ready(g, p.in[k]);
+        if (u.pool && (o % g.h_out) % 2) { --o; if (counted) p.early |= 1u << k; }
+        p.out[k] = o;
+        if (u.next >= 0) p.in[u.next] = leaving_index(net, u, o / g.h_out * g.h_out) + (u.pool ? o % g.h_out / 2 : o % g.h_out);
+    }
+    return p;
+}
+
+// A row of c in front of a pool whose partner has not arrived is formed with the pair.  Counters show it as
+// delivered to the pool from the moment it is final: here it is formed once more, only to be counted.
+int count_waiting_rows(idf_streams *s)
+{
+    const idf_net &net = *s->net;
+    bool pool = false;
+    for (const RowUnit &u : s->units) pool = pool || u.pool;
+    if (!pool || s->eager.on) return IDF_OK;
+    auto count = [&](const StreamSel &sel, const RowProg &p, uint32_t &early) -> int {
+        RowBatch b;
+        b.n = 0;
+        double bytes = 0;
+        for (size_t k = 0; k < s->units.size(); ++k) {
+            const RowUnit &u = s->units[k];
+            const Geom &g = net.g[u.l];
+            if (!u.pool || ((early >> k) & 1u) || rows_ready(g, p.in[k]) <= p.out[k]) continue;
+            row_step(s, (int)k, p.out[k], 1, sel.n, false, b.st[b.n], bytes);
+            b.st[b.n].pool_emit = 0; b.st[b.n].issued = nullptr;
+            early |= 1u << k;
+            if (++b.n == kRowBatchMax) { int rc = launch_rows(s, b, sel, bytes, -1); if (rc != IDF_OK) return rc; b.n = 0; }
+        }
+        return launch_rows(s, b, sel, bytes, -1);
+    };
+    if (s->stg2d)
+        return for_each_prog(s, all_members(s), [&](const StreamSel &sel, RowProg &p) { return count(sel, p, p.early); });
+    for (int id = 0; id < s->B; ++id) {
+        StreamHost &h = s->h[id];
+        StreamSel sel{};
+        sel.n = 1; sel.base = id;
+        // nets with layers of other kinds run layer by layer: where unit k stands follows from the rows received
+        int64_t y = h.r;
+        for (size_t l = 0; l < net.g.size(); ++l) {
+            const Geom &g = net.g[l];
+            const int k = s->unit_of[l];
+            if (k >= 0) {
+                int64_t o = rows_final(g, y);
+                if (s->units[k].pool && o % 2 && o < g.h_out) --o;
+                RowBatch b;
+                double bytes = 0;
+                if (s->units[k].pool && rows_final(g, y) > o && !((h.early >> k) & 1u)) {
+                    b.n = 1;
+                    row_step(s, k, h.sample * g.h_out + o, 1, 1, false, b.st[0], bytes);
+                    b.st[0].pool_emit = 0; b.st[0].issued = nullptr;
+                    h.early |= 1u << k;
+                    int rc = launch_rows(s, b, sel, bytes, (int)l);
+                    if (rc != IDF_OK) return rc;
+                }
+            }
+            y = rows_final(g, y);
+        }
     }
     return IDF_OK;
 }
@@ -892,29 +1094,12 @@ int pipeline_drain(idf_streams *s)
     return rc != IDF_OK ? rc : stg_drain(s);
 }
 
+// Layer by layer, for nets that hold layers of several kinds: streams that all stand at row r of their
+// sample (`sample` whole samples before it) receive n_rows rows.
 int enqueue_cascade(idf_streams *s, const StreamSel &sel, const void *dev_rows, int n_rows, int64_t r,
-                    int64_t out_slot0)
+                    int64_t out_slot0, int64_t sample, uint32_t early)
 {
     if (s->use_cascade1d) return enqueue_cascade1d(s, sel, dev_rows, n_rows, r, out_slot0);
-    if (s->stg2d) {
-        if (sel.base == 0 && sel.pos0 == 0 && sel.n == s->B) {
-            if (!stg_pending(s, 0)) s->stg_out_next = out_slot0;
-            // A push of several rows goes through two rows per launch (every unit that finds two rows waiting takes both
-            // in one step); a push of one row, and the ticks that only move the layers on, take one.
-            const bool pairs = s->stg_pairs && !s->part.on && s->ev_per_step == 0;
-            for (int j = 0; j < n_rows;) {
-                const bool two = pairs && j + 1 < n_rows;
-                int rc = stg_tick(s, dev_rows, n_rows, j, r, two);
-                // the hand-over rings hold kStgSlots rows: never let more than kStgWait wait
-                while (rc == IDF_OK && stg_pending(s, kStgWait)) rc = stg_tick(s, nullptr, 0, -1, 0);
-                if (rc != IDF_OK) return rc;
-                j += two ? 2 : 1;
-            }
-            return IDF_OK;
-        }
-        int rc = stg_drain(s);                     // some streams only: finish what is on its way, then layer by layer
-        if (rc != IDF_OK) return rc;
-    }
     const idf_net &net = *s->net;
     const int n = (int)net.g.size();
     const int eb = ev_bytes(net.precision);
@@ -934,37 +1119,56 @@ int enqueue_cascade(idf_streams *s, const StreamSel &sel, const void *dev_rows, 
         if (!last && o_fin - o_lo > s->transit_cap[l])
             return fail(IDF_ESTATE, "internal: layer %d would emit %lld rows, room for %d", l,
                         (long long)(o_fin - o_lo), s->transit_cap[l]);
+        // the layer behind keeps its input rows in a ring: where this layer's rows go in it
+        const int dst_ring = !last && s->unit_of[l + 1] >= 0 ? s->units[s->unit_of[l + 1]].ring_rows : 0;
+        const int64_t ring_slot0 = dst_ring ? mod_rows(sample * g.h_out + o_lo, dst_ring) : 0;
         if (g.kind == IDF_CONV && s->mfma[l] == 1) {
-            // one launch per arriving row; a pool that follows is done in the epilogue
-            const bool pool = l + 1 < n && s->mfma[l + 1] == 2;
-            const int lp = pool ? l + 1 : l;                        // layer whose rows leave this step
-            const bool last_out = lp == n - 1;
+            // the rows that arrive are counted (and, when they are the caller's, kept); all rows of c they complete are formed,
+            // a pool that follows taking them in pairs
+            const int k = s->unit_of[l];
+            const RowUnit &u = s->units[k];
+            const int lp = u.lp;
             const Geom &gp = net.g[lp];
-            const int64_t e_lo = pool ? rows_final(gp, o_lo) : o_lo, e_fin = pool ? rows_final(gp, o_fin) : o_fin;
-            void *edst = last_out ? (void *)(s->ws + s->out_off) : (void *)(s->ws + s->transit_off[lp]);
-            const int64_t edst_stride = last_out ? s->out_stride : s->transit_stride[lp];
-            if (!last_out && e_fin - e_lo > s->transit_cap[lp])
-                return fail(IDF_ESTATE, "internal: layer %d would emit %lld rows, room for %d", lp,
-                            (long long)(e_fin - e_lo), s->transit_cap[lp]);
-            for (int64_t y = y0; y < y0 + cnt; ++y) {
-                MfmaStep a;
-                int64_t rows_out[3];
-                double bytes = 0;
-                make_mfma_step(s, l, y, sel.n, a, rows_out, bytes);
-                for (int ky = 0; ky < 3; ++ky) {
-                    if (rows_out[ky] < 0) continue;
-                    a.t[ky].dst_slot = rows_out[ky] - e_lo;
-                    if (last_out) a.t[ky].dst_slot = (out_slot0 + a.t[ky].dst_slot) % s->out_cap;
-                }
-                a.in = in; a.in_stream_stride = in_stride; a.in_by_position = by_pos;
-                a.in_row_off = (y - in_row0) * (int64_t)g.w_in * g.c_in;
-                if (l == 0 && s->part.on) { a.in_stream_stride = (int64_t)(s->part.x_hi - s->part.x_lo) * net.in_c; a.in_row_off = -(int64_t)s->part.x_lo * net.in_c; }
-                hipError_t e = launch_conv3x3_mfma(net.precision, a, sel, launch_ctx(s, kKindConvMfma, bytes, l));
-                if (e != hipSuccess) return dev_fail(e, "mfma conv launch");
+            const int64_t e_lo = u.pool ? rows_final(gp, o_lo) : o_lo, e_fin = u.pool ? rows_final(gp, o_fin) : o_fin;
+            const int64_t c_lo = u.pool && o_lo < g.h_out ? o_lo & ~(int64_t)1 : o_lo;
+            const int64_t c_fin = u.pool && o_fin < g.h_out ? o_fin & ~(int64_t)1 : o_fin;
+            RowBatch b;
+            b.n = 0;
+            double bytes = 0;
+            const bool own_rows = l == 0, part = own_rows && s->part.on;
+            const bool counts_itself = own_rows || s->mfma[l - 1] == 0;
+            if (c_fin > c_lo && !part) {
+                RowStep &a = b.st[b.n++];
+                row_step(s, k, sample * g.h_out + c_lo, c_fin - c_lo, sel.n, (early >> k) & 1u, a, bytes);
+                if (own_rows) { a.in_new = dev_rows; a.new_stride = (int)in_stride; a.y_new = (int)y0; }
+                if (!u.last && u.next < 0) a.dst_slot0 = 0;
+                if (u.last) a.dst_slot0 = (int)out_slot0;
             }
-            in = edst; in_stride = edst_stride; in_row0 = e_lo; by_pos = 0;
+            int rc = IDF_OK;
+            if (own_rows && b.n > 0 && y0 + cnt - first_needed(g, c_lo) > u.ring_rows) {
+                // more rows than the ring has slots: those that are read from it go out before new ones are written to it
+                rc = launch_rows(s, b, sel, bytes, l);
+                if (rc != IDF_OK) return rc;
+                b.n = 0; bytes = 0;
+            }
+            if (counts_itself)
+                take_step(s, k, sample * g.h_in + y0, cnt, own_rows ? dev_rows : nullptr, 0, n_rows,
+                          sample * g.h_in + (c_fin < g.h_out ? first_needed(g, c_fin) : g.h_in), b.st[b.n++]);
+            rc = launch_rows(s, b, sel, bytes, l);
+            if (rc != IDF_OK) return rc;
+            if (c_fin > c_lo && part) {           // the row is whole only with the segment just taken: formed from the ring
+                b.n = 1;
+                bytes = 0;
+                row_step(s, k, sample * g.h_out + c_lo, c_fin - c_lo, sel.n, (early >> k) & 1u, b.st[0], bytes);
+                if (!u.last && u.next < 0) b.st[0].dst_slot0 = 0;
+                if (u.last) b.st[0].dst_slot0 = (int)out_slot0;
+                rc = launch_rows(s, b, sel, bytes, l);
+                if (rc != IDF_OK) return rc;
+            }
+            in = u.last ? (void *)(s->ws + s->out_off) : (void *)(s->ws + s->transit_off[lp]);
+            in_stride = u.last ? s->out_stride : s->transit_stride[lp]; in_row0 = e_lo; by_pos = 0;
             y0 = e_lo; cnt = e_fin - e_lo;
-            if (pool) ++l;
+            if (u.pool) ++l;
             continue;
         } else if (g.kind == IDF_CONV) {
             const int max_rows = conv_generic_max_rows(g.c_out);
@@ -982,7 +1186,8 @@ int enqueue_cascade(idf_streams *s, const StreamSel &sel, const void *dev_rows, 
                 a.ring_rows = g.k_h;
                 a.in = in; a.in_stream_stride = in_stride; a.in_row0 = in_row0; a.in_by_position = by_pos;
                 a.ring = s->ws + s->ring_off[l]; a.ring_stream_stride = s->ring_stride[l];
-                a.dst = dst; a.dst_stream_stride = dst_stride; a.dst_row0 = o_lo; a.dst_slot0 = out_slot0;
+                a.dst = dst; a.dst_stream_stride = dst_stride; a.dst_row0 = o_lo; a.dst_slot0 = last ? out_slot0 : ring_slot0;
+                a.dst_ring = dst_ring;
                 a.to_output = last; a.out_cap = s->out_cap;
                 a.w = s->ws + s->w_off[l];
                 a.bias = net.b_img[l].empty() ? nullptr : s->ws + s->b_off[l];
@@ -1004,7 +1209,8 @@ int enqueue_cascade(idf_streams *s, const StreamSel &sel, const void *dev_rows, 
             a.hold_new = (y_last % 2 == 0) && (g.h_out == 0 || y_last / 2 < g.h_out);
             a.in = in; a.in_stream_stride = in_stride; a.in_row0 = in_row0; a.in_by_position = by_pos;
             a.held = s->ws + s->held_off[l]; a.held_stream_stride = s->held_stride[l];
-            a.dst = dst; a.dst_stream_stride = dst_stride; a.dst_row0 = o_lo; a.dst_slot0 = out_slot0;
+            a.dst = dst; a.dst_stream_stride = dst_stride; a.dst_row0 = o_lo; a.dst_slot0 = last ? out_slot0 : ring_slot0;
+            a.dst_ring = dst_ring;
             a.to_output = last; a.out_cap = s->out_cap;
             a.stats = stats; a.n_layers = n;
             const double row_in = (double)g.w_in * g.c_out * eb, row_out = (double)g.w_out * g.c_out;
@@ -1019,6 +1225,34 @@ int enqueue_cascade(idf_streams *s, const StreamSel &sel, const void *dev_rows, 
     return IDF_OK;
 }
 
+// Units that have a row waiting for its partner in front of a pool after `rows` rows of the sample (layer-by-layer nets).
+uint32_t early_at(const idf_streams *s, int64_t rows)
+{
+    uint32_t m = 0;
+    for (size_t l = 0; l < s->net->g.size(); ++l) {
+        const Geom &g = s->net->g[l];
+        rows = rows_final(g, rows);
+        const int k = s->unit_of[l];
+        if (k >= 0 && s->units[k].pool && rows % 2 && rows < g.h_out) m |= 1u << k;
+    }
+    return m;
+}
+
+// Which of those units' waiting rows, counted before a push, still wait after it.
+uint32_t early_after(const idf_streams *s, uint32_t early, int64_t before, int64_t rows)
+{
+    const idf_net &net = *s->net;
+    int64_t a = before, b = rows;
+    for (size_t l = 0; l < net.g.size(); ++l) {
+        const Geom &g = net.g[l];
+        const int k = s->unit_of[l];
+        a = rows_final(g, a); b = rows_final(g, b);
+        if (k >= 0 && s->units[k].pool && a / 2 != b / 2) early &= ~(1u << k);
+        if (k >= 0 && s->units[k].pool && b >= g.h_out) early &= ~(1u << k);
+    }
+    return early;
+}
+
 // One stream's pieces of the workspace, in the order they are laid out in a snapshot.
 template <class F> void for_each_state_piece(const idf_streams *s, int id, F &&f)
 {
@@ -1026,9 +1260,11 @@ template <class F> void for_each_state_piece(const idf_streams *s, int id, F &&f
     const int n = (int)net.g.size();
     const int eb = ev_bytes(net.precision);
     for (int l = 0; l < n; ++l) {
+        if (s->mfma[l]) continue;
         if (net.g[l].kind == IDF_CONV) f(s->ring_off[l] + (size_t)id * s->ring_stride[l] * 4, (size_t)s->ring_stride[l] * 4);
         else f(s->held_off[l] + (size_t)id * s->held_stride[l] * eb, (size_t)s->held_stride[l] * eb);
     }
+    for (const RowUnit &u : s->units) f(u.ring_off + (size_t)id * u.ring_stride * eb, (size_t)u.ring_stride * eb);
     f(s->stats_off + (size_t)id * n * 2 * sizeof(unsigned long long), (size_t)n * 2 * sizeof(unsigned long long));
     f(s->issued_off + (size_t)id * n * sizeof(unsigned long long), (size_t)n * sizeof(unsigned long long));
     f(s->head_off + (size_t)id * net.out_c * sizeof(double), (size_t)net.out_c * sizeof(double));
@@ -1568,29 +1804,11 @@ int open_on(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
         if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) s->cus = 0;
     }
     if (L.cascade1d) { plan_cascade_stages(s); cascade_layers(s); }
-    s->mfma.assign(net->g.size(), 0);
-    if (!getenv("IDF_NO_MFMA")) {
-        for (size_t l = 0; l < net->g.size(); ++l) {
-            if (net->wm_img[l].empty()) continue;
-            s->mfma[l] = 1;
-            if (l + 1 < net->g.size() && net->g[l + 1].kind == IDF_MAXPOOL && net->g[l + 1].k_w == 2) s->mfma[l + 1] = 2;
-        }
-    }
+    s->mfma = L.mfma; s->units = L.units;
+    s->unit_of.assign(net->g.size(), -1);
+    for (size_t k = 0; k < s->units.size(); ++k) s->unit_of[s->units[k].l] = (int)k;
     s->stg2d = !strict_rows() && net_all_mfma(*net);
-    if (s->stg2d) {
-        for (size_t l = 0; l < net->g.size(); ++l)
-            if (net->g[l].kind == IDF_CONV) s->stg_unit.push_back((int)l);
-        s->stg_fifo.assign(s->stg_unit.size(), {});
-        // One tile shape for all layers of a launch: 32 positions (measured faster than 64 on every
-        // workload: rows of 224 or 112 positions waste less, and the smaller workgroups of a
-        // launch overlap better), 32 channels when some layer has no more.
-        int c_min = 1 << 30;
-        for (int l : s->stg_unit) c_min = std::min(c_min, net->g[l].c_out);
-        s->stg_tile = c_min > 32 ? kMfmaTile32x64 : kMfmaTile32x32;
-        s->stg_seq.assign(s->stg_unit.size(), 0);
-        s->stg_slots = max_seg_rows >= 2 ? 2 * kStgSlots : kStgSlots;
-        s->stg_pairs = max_seg_rows >= 2 && !getenv("IDF_NO_ROW_PAIRS");
-    }
+    if (s->stg2d) s->prog.assign(n_streams, RowProg{});
     s->h.assign(n_streams, StreamHost{});
     s->stamp.assign(n_streams, 0);
     hipError_t e = launch_fill_zero(s->ws, L.sizes.weights_bytes, s->st);     // zero padding of the weights
@@ -1641,9 +1859,16 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
     // map, and what depends on the row number only is worked out once per distinct value.
     std::vector<std::pair<int, int>> &members = s->push_members;
     members.clear();
-    std::pair<int64_t, int64_t> key0{0, 0};
+    // (nets with layers on the matrix cores keep rows in rings by their number since open: streams there
+    // go together only if they stand in the same sample too)
+    typedef std::tuple<int64_t, int64_t, int64_t, uint32_t> Key;
+    const bool by_sample = !s->units.empty() && !s->stg2d;
+    Key key0{0, 0, 0, 0};
     bool one_group = true;
     int64_t memo_r = -1, memo_fresh = 0;
+    auto key_of = [&](const StreamHost &h) {
+        return Key{h.r, s->stg2d ? 0 : h.out_written % s->out_cap, by_sample ? h.sample : 0, by_sample ? h.early : 0};
+    };
     for (int i = 0; i < n_ids; ++i) {
         const int id = stream_ids ? stream_ids[i] : i;
         const StreamHost &h = s->h[id];
@@ -1657,27 +1882,27 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
         if (h.out_written - h.out_read + fresh > s->out_cap)
             return fail(IDF_ESTATE, "stream %d: output area full (%lld rows waiting, %lld more would complete, room for %lld)",
                         id, (long long)(h.out_written - h.out_read), (long long)fresh, (long long)s->out_cap);
-        const std::pair<int64_t, int64_t> key{h.r, h.out_written % s->out_cap};
+        const Key key = key_of(h);
         if (i == 0) key0 = key;
         else if (key != key0) one_group = false;
         members.push_back({i, id});
     }
-    if (one_group) {
-        rc = for_each_selection(members, [&](const StreamSel &sel) {
-            return enqueue_cascade(s, sel, dev_rows, n_rows, key0.first, key0.second);
+    auto deliver = [&](const Key &key, const std::vector<std::pair<int, int>> &group) {
+        return for_each_selection(group, [&](const StreamSel &sel) {
+            return enqueue_cascade(s, sel, dev_rows, n_rows, std::get<0>(key), std::get<1>(key), std::get<2>(key), std::get<3>(key));
         });
+    };
+    if (s->stg2d) {
+        rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return row_run(s, sel, p, dev_rows, n_rows); });
+        if (rc != IDF_OK) return rc;
+    } else if (one_group) {
+        rc = deliver(key0, members);
         if (rc != IDF_OK) return rc;
     } else {
-        std::map<std::pair<int64_t, int64_t>, std::vector<std::pair<int, int>>> groups;
-        for (const auto &m : members) {
-            const StreamHost &h = s->h[m.second];
-            groups[{h.r, h.out_written % s->out_cap}].push_back(m);
-        }
+        std::map<Key, std::vector<std::pair<int, int>>> groups;
+        for (const auto &m : members) groups[key_of(s->h[m.second])].push_back(m);
         for (auto &kv : groups) {
-            const int64_t r = kv.first.first, slot0 = kv.first.second;
-            rc = for_each_selection(kv.second, [&](const StreamSel &sel) {
-                return enqueue_cascade(s, sel, dev_rows, n_rows, r, slot0);
-            });
+            rc = deliver(kv.first, kv.second);
             if (rc != IDF_OK) return rc;
         }
     }
@@ -1687,9 +1912,10 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
         StreamHost &h = s->h[id];
         if (h.r != memo_r) { memo_r = h.r; memo_fresh = output_rows_of_push(net, h.r, n_rows); }
         h.out_written += memo_fresh;
+        if (by_sample && h.early) h.early = early_after(s, h.early, h.r, h.r + n_rows);
         h.r += n_rows;
         h.x_next = 0;
-        if (net.in_h > 0 && h.r == net.in_h) h.r = 0;      // next sample
+        if (net.in_h > 0 && h.r == net.in_h) { h.r = 0; ++h.sample; }      // next sample
     }
     return IDF_OK;
 }
@@ -1722,7 +1948,7 @@ int idf_push_pixels(idf_streams *s, const int32_t *stream_ids, int n_ids, const 
     for (int i = 0; i < n_ids; ++i) {
         const int id = stream_ids ? stream_ids[i] : i;
         if (net.in_h > 0 && s->h[id].r >= net.in_h) { s->part = idf_streams::Part{}; return fail(IDF_ESTATE, "stream %d: sample complete", id); }
-        groups[s->h[id].r].push_back({i, id});
+        groups[first_mfma ? s->h[id].sample * net.in_h + s->h[id].r : s->h[id].r].push_back({i, id});
     }
     for (auto &kv : groups) {
         const int64_t r = kv.first;
@@ -1748,14 +1974,11 @@ int idf_push_pixels(idf_streams *s, const int32_t *stream_ids, int n_ids, const 
                 hipError_t e = launch_conv_generic(net.precision, c, sel, launch_ctx(s, kKindConvGeneric, conv_step_bytes(net, c, sel.n), 0));
                 return e == hipSuccess ? (int)IDF_OK : dev_fail(e, "pixel segment launch");
             }
-            MfmaStep a;
-            int64_t rows_out[3];
-            double bytes = 0;
-            make_mfma_step(s, 0, r, sel.n, a, rows_out, bytes);
-            a.in = dev_pixels; a.in_stream_stride = (int64_t)n_px * net.in_c; a.in_by_position = 1;
-            a.in_row_off = -(int64_t)x0 * net.in_c;
-            hipError_t e = launch_conv3x3_mfma(net.precision, a, sel, launch_ctx(s, kKindConvMfma, bytes, 0));
-            return e == hipSuccess ? IDF_OK : dev_fail(e, "pixel segment launch");
+            // the matrix-core kernel forms its rows of c when the row is whole: the pixels wait in the layer's ring
+            RowBatch b;
+            b.n = 1;
+            take_step(s, 0, kv.first, 1, dev_pixels, 0, 1, kv.first, b.st[0]);
+            return launch_rows(s, b, sel, (double)sel.n * n_px * net.in_c * ev_bytes(net.precision), 0);
         });
         if (rc != IDF_OK) break;
     }
@@ -1822,7 +2045,9 @@ int idf_reset_streams(idf_streams *s, const int32_t *stream_ids, int n_ids)
                                  (size_t)s->net->out_c * sizeof(double), s->st);
         if (e != hipSuccess) return dev_fail(e, "reset_streams");
         s->h[id] = StreamHost{};
+        if (s->stg2d) { prog_split(s); s->prog[id] = RowProg{}; }
     }
+    if (s->stg2d) prog_join(s);
     return IDF_OK;
 }
 
@@ -1833,6 +2058,7 @@ int idf_get_stats(idf_streams *s, int stream_id, uint64_t *events_in, uint64_t *
     const int n = (int)s->net->g.size();
     std::vector<unsigned long long> buf((size_t)n * 2);
     if (int rc = pipeline_drain(s)) return rc;
+    if (int rc = count_waiting_rows(s)) return rc;
     hipError_t e = hipStreamSynchronize(s->st);
     if (e == hipSuccess)
         e = hipMemcpy(buf.data(), s->ws + s->stats_off + (size_t)stream_id * n * 2 * sizeof(unsigned long long),
@@ -1932,6 +2158,8 @@ int idf_snapshot(idf_streams *s, int stream_id, void *dev_buf, idf_stream_pos *p
     if (s->h[stream_id].x_next != 0) return fail(IDF_ESTATE, "stream %d: a row is half presented", stream_id);
     int rc = pipeline_drain(s);
     if (rc != IDF_OK) return rc;
+    rc = count_waiting_rows(s);
+    if (rc != IDF_OK) return rc;
     const int32_t id32 = stream_id;
     rc = head_catch_up(s, &id32, 1);
     if (rc != IDF_OK) return rc;
@@ -1973,6 +2201,11 @@ int idf_restore(idf_streams *s, int stream_id, const void *dev_buf, const idf_st
     if (e != hipSuccess) return dev_fail(e, "restore");
     h.r = pos->rows_pushed; h.out_written = h.out_read = pos->out_rows; h.x_next = 0;
     h.head_done = pos->out_rows; h.head_base = pos->out_rows - pos->head_rows;
+    // the ring slots of the rows that came back follow from how many rows the stream has received; what waits in
+    // front of a pool was counted when the snapshot was taken
+    h.sample = net.out_h > 0 ? pos->out_rows / net.out_h : 0;
+    h.early = early_at(s, h.r);
+    if (s->stg2d) { prog_split(s); s->prog[stream_id] = prog_at(s, h.sample * net.in_h + h.r, true); prog_join(s); }
     return IDF_OK;
 }
 

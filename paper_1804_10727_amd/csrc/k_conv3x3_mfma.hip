@@ -1,91 +1,96 @@
-// Matrix-core event propagation for one arriving row of a 3x3, stride 1, same-padded conv layer
-// (bfloat16 events and weights -> float32 state, int8 -> int32, or float32 throughout).
+// Matrix-core event propagation for rows of a 3x3, stride 1, same-padded conv layer (bfloat16 events
+// and weights -> float32 sums, int8 -> int32, or float32 throughout).
 //
-// For one input row y the update of Sec. 3 (c += w * dh for every event dh of the row) is,
-// for each of the three output rows o = y+1-ky the row can influence, a contraction
-//     D_ky[x_out][c_out] = sum_{kx, c_in} X[x_out - 1 + kx][c_in] * W[ky][kx][c_in][c_out]
-// over the flattened index k = kx * C_in + c_in, for which the operand A[x_out][k] is simply
-// the row read as one long vector starting at position x_out - 1.
+// The events of an arriving row are not delivered one row at a time into a retained row of c: they
+// wait, in their own compact type, in a ring of the layer's input rows until the last row that an
+// output row needs has arrived.  Then all events of its three input rows are delivered at once (the
+// order of delivery does not matter to the sum, Sec. 3) and c lives in registers from its bias to
+// its activation:
+//     c[o][x][c_out] = bias + sum_{ky, kx, c_in} X[o - 1 + ky][x - 1 + kx][c_in] * W[ky][kx][c_in][c_out].
+// A layer keeps K_h rows of events instead of K_h rows of four-byte sums, and a step reads rows and
+// writes one row where it used to read two rows of c, add to three and write two back: on the
+// VGG-style workload a launch of one row per stream moved 73 MB and took 20 us that way.
 //
-// A workgroup owns a tile of x_out positions and a chunk of output channels for all three ky.
-//   * The needed stretch of the input row goes to LDS once.  While it is loaded, every 16-byte
-//     cell (position, channel chunk) that holds a non-zero sets a bit; from these bits each wave
-//     ballots the list of K-steps whose A fragment is not entirely zero and then visits only
-//     those: a stretch of the row without events costs no weight fetch and no matrix
-//     instruction (zero values are not events, Sec. 1).
-//   * Weights come straight from global memory in the fragment layout (packed once on the host).
-//   * The retained rows of c (rows y-1 and y of the rolling buffer) are fetched at the start,
-//     straight into the accumulators; row y+1 starts there from the bias.  Epilogue: the row that is now final (y-1; also y
-//     when y is the last row of the sample) is activated, rounded to the event type and emitted
-//     -- through a fused 2x2 max-pool when one follows -- and forgotten; the others go back to
-//     the rolling buffer.
+// A workgroup of four waves owns a stretch of positions and a group of output channels, for one output
+// row or two.  Two rows share everything that is fetched: each weight serves both, and each of the
+// two middle input rows is read from LDS once for both.
+//   * Input channels are taken in chunks of eight 16-byte cells.  The stretch of the input rows
+//     goes to LDS chunk by chunk, the next chunk's loads under the current one's arithmetic.  On the way
+//     every cell that holds a non-zero sets a bit (a wave ballot, one word per wave): K-steps of a row
+//     without events cost no matrix instruction, a chunk without events not even a weight fetch (zero
+//     values are not events, Sec. 1).
+//   * Operands are swapped: the matrix instruction's rows are output channels, its columns positions.
+//     With the channels of a pair of tiles interleaved in the weight packing a lane then holds eight
+//     neighbouring channels of one position, i.e. 16 bytes of a bfloat16 row: rows go straight from the
+//     accumulators to memory, and the 2x2 max-pool is a maximum of two accumulators and one lane
+//     exchange.
+//   * The order of the sum is the same whatever a launch holds (chunk, K-step, tap row), so results do
+//     not depend on how rows were grouped.
 #include "idf.h"
 #include "idf_kernels.h"
 #include <algorithm>
+#include <cstddef>
+#include <type_traits>
 
 namespace idf {
+
+// every lambda of the kernel works on the accumulators or the arguments: called instead of inlined, those would live in memory
+#define IDF_INLINE __attribute__((always_inline))
 
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(16))) int i32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(2))) int i32x2;
 
+// A step's arguments, read where the launch put them (the kernel-argument segment): taken as an ordinary
+// by-value argument, a block this large that is read in this many places is first copied to scratch memory.
+typedef const __attribute__((address_space(4))) RowStep ArgStep;
+
+constexpr int kWaves = 4, kThreads = 64 * kWaves;
+
+// Per event type: VL elements per 16-byte cell, EB bytes per element, kInst matrix instructions of
+// 16 x 16 per K-step of four cells, pack4: four activated sums as EB words of events.
 struct TraitsBf16 {
     static constexpr bool kEvents = false;
-    static constexpr int kOcc = 3;           // waves per SIMD the batch kernel is compiled for (168 registers)
-    static constexpr int kDepth = 3;         // K-steps whose operands are in flight: three waves hide more than six steps did for two
-    static constexpr int VL = 8;             // elements per 16-byte lane fragment
-    static constexpr int EB = 2;             // bytes per element
-    using acc_t = f32x16; using st_t = float; using ev_t = uint16_t;
-    static __device__ __forceinline__ acc_t mfma(const i32x4 &a, const i32x4 &b, const acc_t &c)
+    static constexpr int VL = 8, EB = 2, kInst = 1;
+    using acc_t = f32x4; using st_t = float; using ev_t = uint16_t;
+    static __device__ __forceinline__ acc_t mfma(const i32x4 &w, const i32x4 &x, const acc_t &c, int)
     {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
     }
-    static __device__ __forceinline__ bool cell_nonzero(const i32x4 &v)
-    {   // bf16 zero is +0 or -0
-        return ((v.x | v.y | v.z | v.w) & 0x7fff7fff) != 0;
-    }
-    static __device__ __forceinline__ int count_nonzero(const i32x4 &v)
+    static __device__ __forceinline__ int or_of(const i32x4 &v) { return (v.x | v.y | v.z | v.w) & 0x7fff7fff; }      // zero is +0 or -0
+    static __device__ __forceinline__ int nonzero(uint32_t w)
     {   // adding 0x7fff to the 15 magnitude bits of a half carries into its top bit unless they are all zero
-        int n = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) n += __builtin_popcount((((uint32_t)v[i] & 0x7fff7fffu) + 0x7fff7fffu) & 0x80008000u);
-        return n;
+        return __builtin_popcount(((w & 0x7fff7fffu) + 0x7fff7fffu) & 0x80008000u);
     }
     static __device__ __forceinline__ st_t activate(st_t c, int act, int, int) { return act == IDF_ACT_NONE ? c : fmaxf(c, 0.f); }
-    static __device__ __forceinline__ ev_t to_ev(st_t h)
-    {
-        return __builtin_bit_cast(ev_t, (__bf16)h);     // round to nearest, ties to even (one conversion instruction here)
+    static __device__ __forceinline__ void pack4(const st_t *v, uint32_t *out)
+    {   // round to nearest, ties to even (the conversion instruction)
+        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            bf16x2 p;
+            p.x = (__bf16)v[2 * i]; p.y = (__bf16)v[2 * i + 1];
+            out[i] = __builtin_bit_cast(uint32_t, p);
+        }
     }
-    static __device__ __forceinline__ st_t ev_val(ev_t v) { return __uint_as_float((uint32_t)v << 16); }
     static __device__ __forceinline__ bool ev_nonzero(ev_t v) { return (v & 0x7fffu) != 0; }
-    static __device__ __forceinline__ uint32_t bits(ev_t v) { return v; }
-    static __device__ __forceinline__ ev_t from_bits(uint32_t u) { return (ev_t)u; }
 };
 
 struct TraitsI8 {
-    static constexpr bool kEvents = true;    // sparse tiles take the event-list path on the vector units
-    static constexpr int kOcc = 2;           // three gain nothing where a launch is one short round of workgroups
-    static constexpr int kDepth = 3;           // measured against 4 and 6 on the event workload
-    static constexpr int VL = 16;
-    static constexpr int EB = 1;
-    using acc_t = i32x16; using st_t = int32_t; using ev_t = int8_t;
-    static __device__ __forceinline__ acc_t mfma(const i32x4 &a, const i32x4 &b, const acc_t &c)
+    static constexpr bool kEvents = true;    // sparse stretches can take the event-list path on the vector units
+    static constexpr int VL = 16, EB = 1, kInst = 1;
+    using acc_t = i32x4; using st_t = int32_t; using ev_t = int8_t;
+    static __device__ __forceinline__ acc_t mfma(const i32x4 &w, const i32x4 &x, const acc_t &c, int)
     {
-        return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_i32_16x16x64_i8(w, x, c, 0, 0, 0);
     }
-    static __device__ __forceinline__ bool cell_nonzero(const i32x4 &v) { return (v.x | v.y | v.z | v.w) != 0; }
-    static __device__ __forceinline__ int count_nonzero(const i32x4 &v)
-    {
-        int n = 0;          // per byte: the low seven bits carry into the top bit, or the top bit is set already
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t u = (uint32_t)v[i];
-            n += __builtin_popcount((((u & 0x7f7f7f7fu) + 0x7f7f7f7fu) | u) & 0x80808080u);
-        }
-        return n;
+    static __device__ __forceinline__ int or_of(const i32x4 &v) { return v.x | v.y | v.z | v.w; }
+    static __device__ __forceinline__ int nonzero(uint32_t u)
+    {   // per byte: the low seven bits carry into the top bit, or the top bit is set already
+        return __builtin_popcount((((u & 0x7f7f7f7fu) + 0x7f7f7f7fu) | u) & 0x80808080u);
     }
     static __device__ __forceinline__ st_t activate(st_t c, int act, int shr, int hi)
     {
@@ -94,782 +99,708 @@ struct TraitsI8 {
         if (act == IDF_ACT_RELU_SHR_CLAMP) { r >>= shr; r = r > hi ? hi : r; }
         return r;
     }
-    static __device__ __forceinline__ ev_t to_ev(st_t h) { return (ev_t)h; }
-    static __device__ __forceinline__ st_t ev_val(ev_t v) { return v; }
+    static __device__ __forceinline__ void pack4(const st_t *v, uint32_t *out)
+    {
+        out[0] = (uint32_t)(uint8_t)v[0] | (uint32_t)(uint8_t)v[1] << 8 | (uint32_t)(uint8_t)v[2] << 16 | (uint32_t)v[3] << 24;
+    }
     static __device__ __forceinline__ bool ev_nonzero(ev_t v) { return v != 0; }
-    static __device__ __forceinline__ uint32_t bits(ev_t v) { return (uint32_t)(uint8_t)v; }
-    static __device__ __forceinline__ ev_t from_bits(uint32_t u) { return (ev_t)(uint8_t)u; }
 };
 
-// float32 events, weights and state: the 16-byte fragment of a lane holds four k, served by four
-// 32x32x2 matrix instructions (instruction i pairs element i of the two half-waves' fragments;
-// which two k share an instruction does not matter to the sum).
+// float32: a cell holds four k, served by four 16x16x4 instructions (instruction i takes element i of
+// every lane's cell; which four k share an instruction does not matter to the sum).
 struct TraitsF32 {
     static constexpr bool kEvents = false;
-    static constexpr int kOcc = 2;
-    static constexpr int kDepth = 3;         // a step is twelve long matrix instructions here: little to hide
-    static constexpr int VL = 4;
-    static constexpr int EB = 4;
-    using acc_t = f32x16; using st_t = float; using ev_t = float;
-    static __device__ __forceinline__ acc_t mfma(const i32x4 &a, const i32x4 &b, acc_t c)
+    static constexpr int VL = 4, EB = 4, kInst = 4;
+    using acc_t = f32x4; using st_t = float; using ev_t = float;
+    static __device__ __forceinline__ acc_t mfma(const i32x4 &w, const i32x4 &x, const acc_t &c, int i)
     {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            c = __builtin_amdgcn_mfma_f32_32x32x2f32(__int_as_float(a[i]), __int_as_float(b[i]), c, 0, 0, 0);
-        return c;
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__int_as_float(w[i]), __int_as_float(x[i]), c, 0, 0, 0);
     }
-    static __device__ __forceinline__ bool cell_nonzero(const i32x4 &v)
-    {   // zero is +0 or -0
-        return ((v.x | v.y | v.z | v.w) & 0x7fffffff) != 0;
-    }
-    static __device__ __forceinline__ int count_nonzero(const i32x4 &v)
-    {
-        int n = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) n += (v[i] & 0x7fffffff) != 0;
-        return n;
-    }
+    static __device__ __forceinline__ int or_of(const i32x4 &v) { return (v.x | v.y | v.z | v.w) & 0x7fffffff; }      // zero is +0 or -0
+    static __device__ __forceinline__ int nonzero(uint32_t w) { return (w & 0x7fffffffu) != 0; }
     static __device__ __forceinline__ st_t activate(st_t c, int act, int, int) { return act == IDF_ACT_NONE ? c : fmaxf(c, 0.f); }
-    static __device__ __forceinline__ ev_t to_ev(st_t h) { return h; }
-    static __device__ __forceinline__ st_t ev_val(ev_t v) { return v; }
+    static __device__ __forceinline__ void pack4(const st_t *v, uint32_t *out)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = __float_as_uint(v[i]);
+    }
     static __device__ __forceinline__ bool ev_nonzero(ev_t v) { return v != 0.f; }
-    static __device__ __forceinline__ uint32_t bits(ev_t v) { return __float_as_uint(v); }
-    static __device__ __forceinline__ ev_t from_bits(uint32_t u) { return __uint_as_float(u); }
 };
 
-// A 4-byte cell at a byte offset from a base every lane shares.
+// A value at a byte offset from a base every lane shares: "scalar base + lane offset", no 64-bit
+// arithmetic per lane.
 template <class P> __device__ __forceinline__ P *at4(P *base, uint32_t byte_off)
 {
-    return (P *)((const char *)base + byte_off);      // plain pointer arithmetic: the address space stays known
+    return (P *)((const char *)base + byte_off);
 }
 
-constexpr int kMaxPos = 128 + 2;                 // positions of the widest tile plus halo
-constexpr int kEvCap = 256;                      // events (tile and halo) the event path takes at most
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// LDS the event path needs behind the stretch / staging area: offsets and counts per position, the
-// packed event list, and the sums it hands to the accumulators.
-// and the tile's share of the layer's weights (three words per input channel and output channel).
-constexpr size_t event_lds_bytes(int mt, int nc, int c_in) { return (size_t)(2 * (mt + 4) + kEvCap + 3 * mt * nc + 3 * c_in * nc) * 4; }
-constexpr int kNzWords = (kMaxPos + 31) / 32 + 1;
-
-// DBL: a step may take two consecutive input rows (MfmaStep::dbl): the second is worked on by the
-// same workgroup straight after the first, with the two rows of c that the first leaves unfinished
-// staying in the accumulators (they move up by one tap row) instead of going to the rolling buffer
-// and back -- every sum is formed in the same order as by two steps, so the values are the same.
-template <class T, int WM, int WN, bool COUNT, bool EV, bool DBL = false>
-__device__ __forceinline__ void conv3x3_row(const MfmaStep &a, const StreamSel &sel, const int bx, const int si,
-                                            const uint32_t a_at, const uint32_t sel_at)
+// Sum over the wave's lanes, in every lane: shifts and broadcasts inside the vector units, no LDS.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
 {
-    using acc_t = typename T::acc_t; using st_t = typename T::st_t; using ev_t = typename T::ev_t;
-    constexpr int VL = T::VL, EB = T::EB, KI = 2 * VL;
-    constexpr int MT = 32 * WM, NC = 32 * WN, NT = 64 * WM * WN;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    __shared__ uint32_t nz[64][kNzWords];          // per channel chunk: positions with a non-zero cell
-    __shared__ unsigned long long red[2][WM * WN];
-    __shared__ unsigned int red_ev[WM * WN];       // events of the tile and its halo, per wave (event path)
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);       // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);       // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);       // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);       // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);      // lane 15 of a row to the next row
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);      // lane 31 to the upper half
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
 
-    // Every argument the kernel uses is asked for here, in one batch of scalar loads with one
-    // wait: left to first use, the loads end up behind conditions and cost one memory round
-    // trip each, one after the other.
-    // Before that batch, one word of every 64-byte line of this step's arguments (they lie a_at
-    // bytes into the kernel-argument segment, the stream selection sel_at bytes) is asked for and
-    // never looked at: the compiler fetches some arguments again later rather than keep them in
-    // registers, and a launch's argument segment is new memory to every scalar cache -- with the
-    // lines all requested in the first round, those later fetches find them there instead of
-    // paying one miss after the other.  (The register the words land in stays reserved until the
-    // batch's own wait has passed: nothing else may be written to it while they are in flight.)
-    uint32_t line_touch;
-    {
-        typedef const __attribute__((address_space(4))) char *karg_ptr;
-        const karg_ptr ka = (karg_ptr)__builtin_amdgcn_kernarg_segment_ptr() + a_at;
-        const karg_ptr ks = (karg_ptr)__builtin_amdgcn_kernarg_segment_ptr() + sel_at;
-        static_assert(sizeof(MfmaStep) > 0x180 && sizeof(MfmaStep) <= 0x1c0, "one request per 64-byte line of a step's arguments");
-        asm volatile("s_load_dword %0, %1, 0x0\n\ts_load_dword %0, %1, 0x40\n\ts_load_dword %0, %1, 0x80\n\t"
-                     "s_load_dword %0, %1, 0xc0\n\ts_load_dword %0, %1, 0x100\n\ts_load_dword %0, %1, 0x140\n\t"
-                     "s_load_dword %0, %1, 0x180\n\ts_load_dword %0, %1, %3\n\ts_load_dword %0, %2, 0x0"
-                     : "=&s"(line_touch)
-                     : "s"(ka), "s"(ks), "n"(sizeof(MfmaStep) - 4));
-    }
-    asm volatile("" ::"s"(a.w), "s"(a.c_in), "s"(a.c_out), "s"(a.c_out_pad), "s"(a.c_in_rcp), "s"(a.chunks_rcp), "s"(a.act), "s"(a.shr),
-                 "s"(a.clamp_hi), "s"(a.x_lo), "s"(a.x_hi), "s"(a.skip_clear_tiles), "s"(a.layer), "s"(a.pool_layer), "s"(a.n_layers), "s"(a.taps_y), "s"(a.in_by_position),
-                 "s"(a.to_output), "s"(a.in), "s"(a.in_stream_stride), "s"(a.in_row_off), "s"(a.ring),
-                 "s"(a.ring_stream_stride), "s"(a.held), "s"(a.held_stream_stride), "s"(a.dst), "s"(a.dst_stream_stride),
-                 "s"(a.wfrag), "s"(a.bias), "s"(a.stats));
-    asm volatile("" ::"s"(a.t[0].valid), "s"(a.t[0].fresh), "s"(a.t[0].emit), "s"(a.t[0].store_held), "s"(a.t[0].ring_slot),
-                 "s"(a.t[0].dst_slot), "s"(a.t[1].valid), "s"(a.t[1].fresh), "s"(a.t[1].emit), "s"(a.t[1].store_held),
-                 "s"(a.t[1].ring_slot), "s"(a.t[1].dst_slot), "s"(a.t[2].valid), "s"(a.t[2].fresh), "s"(a.t[2].emit),
-                 "s"(a.t[2].store_held), "s"(a.t[2].ring_slot), "s"(a.t[2].dst_slot), "s"(sel.n), "s"(sel.base), "s"(sel.pos0));
-    asm volatile("" ::"s"(line_touch));
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % WM, wn = wave / WM;
+// The value of the neighbouring lane (lane ^ 1).
+template <class V> __device__ __forceinline__ V neighbour(V v)
+{
+    return __builtin_bit_cast(V, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
+}
+
+__device__ __forceinline__ int taps_of(int v, int n) { return 3 - (v == 0) - (v == n - 1); }      // of a 3-tap axis with one position of padding
+
+// ---- rows of the caller: into the ring, and counted as the first layer's events --------------------
+template <class T> __device__ __forceinline__ void take_row(ArgStep &a, const StreamSel &sel, const int tile, const int si)
+{
+    using ev_t = typename T::ev_t;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int stream = sel_stream(sel, si);
-    const int n_co_chunks = (a.c_out + NC - 1) / NC;
-    const int x_tile = bx / n_co_chunks, co_chunk = bx - x_tile * n_co_chunks;
-    const int x0 = x_tile * MT, co0 = co_chunk * NC;
-    if (x0 >= a.w) return;                         // a launch of several steps is as deep as its largest
-    // a pixel segment in the middle of a row: tiles it cannot reach are left alone
-    if (a.skip_clear_tiles && (x0 + MT < a.x_lo || x0 > a.x_hi)) return;
-    const int W = a.w, C_in = a.c_in, C_out = a.c_out;
-    const int chunks = C_in / VL;                  // 16-byte cells per position
-    const int xs_stride = C_in * EB + 16;          // bytes per position in LDS (padded against bank conflicts)
-
-    // Order of the global loads: the hardware counts outstanding loads in issue order, so what
-    // is needed first is requested first -- the row stretch, then the retained state -- and
-    // waiting for the stretch leaves the state in flight.  The first weights are asked for only
-    // once the stretch has left its registers, and the pool's held row only in the epilogue:
-    // with fewer values alive at once, more waves fit a SIMD, which hides more than the earlier
-    // requests did.
-    const int row_lane = (lane >> 5) * 4;          // D layout: row = 8*i + (lane/32)*4 + j, col = lane%32
-    const int xo_base = x0 + wm * 32 + row_lane;
-    const int co = co0 + wn * 32 + (lane & 31);
-    const bool co_ok = co < C_out;
-    // Addresses are clamped into the row instead of predicated per lane: the loads then sit in
-    // straight-line code; lanes outside the tile simply never store.
-    const int co_c = co_ok ? co : C_out - 1;
-    const bool small_c = C_in < VL;                // first layers: 1..4 input channels
-    const int64_t in_idx = a.in_by_position ? (int64_t)(sel.pos0 + si) : (int64_t)stream;
-    const unsigned char *in_base = (const unsigned char *)a.in + in_idx * a.in_stream_stride * EB;
-    acc_t acc[3];
-    ev_t hprev[16];                                   // activations of an even row of a pool pair whose partner follows in this launch
+    const int y = a.y0 + tile, row_elems = a.w * a.c_in;
+    const int slot = (a.slot0 + tile) % a.ring_rows;
+    ev_t *ring = (ev_t *)a.in_ring + (int64_t)stream * a.in_stride + (int64_t)slot * row_elems;
+    const ev_t *src = a.in_new ? (const ev_t *)a.in_new + (int64_t)(sel.pos0 + si) * a.new_stride + (int64_t)(y - a.y_new) * row_elems
+                               : ring + a.x_lo * a.c_in;
+    const bool save = a.in_new && y >= a.y_save;
+    const int n = (a.x_hi - a.x_lo) * a.c_in;
+    ev_t *dst = ring + a.x_lo * a.c_in;
+    uint32_t ev = 0, tx = 0;
+    if (a.cells > 0) {
+        for (int i = tid; i < n / T::VL; i += kThreads) {
+            const i32x4 v = reinterpret_cast<const i32x4 *>(src)[i];
+            if (save) reinterpret_cast<i32x4 *>(dst)[i] = v;
+            uint32_t k = 0;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) hprev[q] = 0;
-    const int n_sub = DBL ? (a.dbl ? 2 : 1) : 1;
-#pragma unroll
-    for (int sub = 0; sub < (DBL ? 2 : 1); ++sub) {           // two copies of the body: each is straight-line code for the compiler
-    if (sub >= n_sub) break;
-    const bool second = DBL && sub > 0;
-    auto tap = [&](int ky) -> const MfmaTap & { return second ? a.t2[ky] : a.t[ky]; };
-    const unsigned char *in_row = in_base + (second ? a.in_row_off2 : a.in_row_off) * EB;
-    if (second) lds_barrier();                     // the first row's stretch, bits and staged rows are done with
-    for (int i = tid; i < chunks * kNzWords; i += NT) nz[i / kNzWords][i % kNzWords] = 0;
-
-    // ---- (1) input row stretch [x0-1, x0+MT+1): first batch of 16-byte cells ------------------
-    constexpr int kBatch = 9;                      // cells per lane per batch (one batch for C_in <= 256 at 64 positions)
-    const int cells = small_c ? 0 : (MT + 2) * chunks;
-    i32x4 tv[kBatch];
-    auto tile_issue = [&](int base) {
-#pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-            if (base + b * NT >= cells) break;         // the same for every lane: narrow layers ask for less
-            int i = base + b * NT + tid;
-            i = i < cells ? i : cells - 1;
-            const int p = a.chunks_rcp ? (int)__umulhi((unsigned)i, a.chunks_rcp) : i, c = i - p * chunks;   // i / chunks
-            int x = x0 - 1 + p;
-            x = x < a.x_lo ? a.x_lo : (x >= a.x_hi ? a.x_hi - 1 : x);
-            tv[b] = *at4(reinterpret_cast<const i32x4 *>(in_row), (uint32_t)((x * C_in + c * VL) * EB));
-        }
-    };
-    if (cells > 0) tile_issue(0);
-
-    // ---- (2) retained rows of c, the bias ------------------------------------------------------
-    // This lane's 16 cells of a row [W][C_out]: element offsets (clamped into the row, so loads
-    // need no predicate) and which of them exist.  A wave whose cells all exist -- every wave
-    // when W is a multiple of 32 and C_out a multiple of the chunk -- stores without predicates.
-    // (kept as 32-bit byte offsets of 4-byte cells: with the row's base in scalar registers an
-    // access is then "scalar base + lane offset", no 64-bit arithmetic per cell)
-    uint32_t roff[16];
-    unsigned int vmask = 0;
-    auto cell_offsets = [&](int xo_first) {
-        vmask = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int xo = xo_first + 8 * i + j;
-                roff[i * 4 + j] = (uint32_t)(((xo < W ? xo : W - 1) * C_out + co_c) * 4);
-                vmask |= (co_ok && xo < W) ? 1u << (i * 4 + j) : 0u;
-            }
-    };
-    cell_offsets(xo_base);
-    const bool wave_full = __ballot(vmask != 0xffffu) == 0ull;
-    const st_t bias_v = a.bias ? ((const st_t *)a.bias)[co_c] : (st_t)0;
-    st_t *ring = (st_t *)a.ring + (int64_t)stream * a.ring_stream_stride;
-    // They are loaded straight into the accumulators (a row touched for the first time starts
-    // from the bias there): the contraction then adds on top and the epilogue has nothing to add.
-    if (!second) {
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky) {
-            const st_t start = a.t[ky].valid ? bias_v : (st_t)0;
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[ky][q] = start;
-            if (a.t[ky].valid && !a.t[ky].fresh) {
-                const st_t *rrow = ring + (int64_t)a.t[ky].ring_slot * W * C_out;
-#pragma unroll
-                for (int q = 0; q < 16; ++q) acc[ky][q] = *at4(rrow, roff[q]);
-            }
+            for (int q = 0; q < 4; ++q) k += T::nonzero((uint32_t)v[q]);
+            ev += k; tx += k * taps_of(a.x_lo + i / a.cells, a.w);
         }
     } else {
-        // rows y and y+1 are in the accumulators already: one tap row up; row y+2 starts from the bias
-        acc[2] = acc[1];
-        acc[1] = acc[0];
-        const st_t start = a.t2[0].valid ? bias_v : (st_t)0;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[0][q] = start;
+        for (int i = tid; i < n; i += kThreads) {
+            const ev_t v = src[i];
+            if (save) dst[i] = v;
+            if (T::ev_nonzero(v)) { ev += 1; tx += taps_of(a.x_lo + i / a.c_in, a.w); }
+        }
     }
-    ev_t *held = (ev_t *)a.held + (int64_t)stream * a.held_stream_stride;
+    if (!a.stats) return;
+    ev = wave_sum(ev); tx = wave_sum(tx);
+    if (lane == 0 && ev) {
+        unsigned long long *d = a.stats + ((int64_t)stream * a.n_layers + a.layer) * 2;
+        atomicAdd(d, (unsigned long long)ev);
+        atomicAdd(d + 1, (unsigned long long)tx * (unsigned long long)(taps_of(y, a.h) * a.c_out));
+    }
+}
 
-    // ---- (3) weight fragments: addressing -------------------------------------------------------
-    const int KT = 3 * C_in;
-    const int steps = (KT + KI - 1) / KI;
-    const int hlf = lane >> 5, r = wm * 32 + (lane & 31);
-    // weights: the three ky planes as scalar bases, this lane's fragment as a 32-bit byte offset
-    const uint32_t w_lane = (uint32_t)((hlf * a.c_out_pad + co0 + wn * 32 + (lane & 31)) * 16);
-    const uint32_t w_step = (uint32_t)(2 * a.c_out_pad * 16);       // bytes per K-step
-    const i32x4 *w_plane[3];
+constexpr int kLoads = 5;                        // cells of a chunk each lane has in flight
+constexpr int kEvCap = 512;                      // events (stretch and halo) of a row the event path takes at most: 256 per 32 positions
+// LDS of the event path behind the stretch: offsets and counts per position, the packed event list, the
+// sums it hands to the accumulators, and the tile's share of the layer's weights.
+constexpr size_t event_lds_bytes(int rows, int xt, int nc, int c_in) { return (size_t)(2 * (xt + 4) + kEvCap + rows * xt * nc + 3 * c_in * nc) * 4; }
+
+// MC tiles of 16 channels x NP tiles of 16 positions x NR output rows per wave.
+template <class T, int MC, int NP, int NR, bool EV>
+__device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, const int tile, const int si)
+{
+    using acc_t = typename T::acc_t; using st_t = typename T::st_t; using ev_t = typename T::ev_t;
+    constexpr int VL = T::VL, EB = T::EB;
+    constexpr int R = NR + 2;                      // input rows
+    constexpr int NW = 3 * MC;                     // weight fragments of a K-step
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ uint32_t occ[2][kWaves];            // per chunk parity and wave: for each input row a byte, bit c: cell c holds an event somewhere
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+    const int m = lane & 15, g = lane >> 4;        // position within a tile; group of channels / of k
+    const int stream = sel_stream(sel, si);
+    const int rest = a.cg_rcp ? (int)__umulhi((unsigned)tile, a.cg_rcp) : tile, cg = tile - rest * a.n_cg;
+    const int rg = a.xt_rcp ? (int)__umulhi((unsigned)rest, a.xt_rcp) : rest, xt = rest - rg * a.n_xt;
+    const int y = a.y0 + rg * NR;                  // first output row
+    const int rows = a.n_rows - rg * NR < NR ? a.n_rows - rg * NR : NR;
+    const int W = a.w, H = a.h, C_in = a.c_in, C_out = a.c_out;
+    const int wc = wave & ((1 << a.wc_log) - 1), wp = wave >> a.wc_log;
+    const int XT = (16 * NP * kWaves) >> a.wc_log;
+    const int x0 = xt * XT;
+    const bool single = C_out == 16;               // one tile of channels; else tiles come in interleaved pairs
+    const int n_blk = (C_out + 31) >> 5;
+    const int ct0 = ((cg << a.wc_log) + wc) * MC;  // first channel tile of this wave
+    const int xw = x0 + wp * 16 * NP;              // first position of this wave
+    const bool active = ct0 < (single ? 1 : 2 * n_blk) && xw < W;
+    const int np_on = (W - xw + 15) >> 4;          // position tiles of this wave that exist
+    // this lane's channels: co0 .. co0 + 4 * MC - 1
+    const int co0 = single ? g * 4 : (ct0 >> 1) * 32 + g * 8 + (MC == 1 ? (ct0 & 1) * 4 : 0);
+    const bool co_ok = co0 < C_out;
+    const bool small_c = a.cells == 0;
+
+    // ---- input rows ---------------------------------------------------------------------------------
+    auto row_there = [&](int r) IDF_INLINE { const int yi = y - 1 + r; return yi >= 0 && yi < H && r < rows + 2; };
+    auto row_ptr = [&](int r) IDF_INLINE -> const unsigned char * {
+        const int yi = y - 1 + r;
+        if (yi >= a.y_new) return (const unsigned char *)a.in_new + ((int64_t)(sel.pos0 + si) * a.new_stride + (int64_t)(yi - a.y_new) * W * C_in) * EB;
+        int slot = a.slot0 + rg * NR + r;
+        if (slot >= a.ring_rows) slot -= a.ring_rows;
+        return (const unsigned char *)a.in_ring + ((int64_t)stream * a.in_stride + (int64_t)slot * W * C_in) * EB;
+    };
+    const int n_chunks = small_c ? 1 : (a.cells + kRowCells - 1) / kRowCells;
+    const int npos = XT + 2;
+    // few channels: the stretch is kept as the windows the positions see, [row][position][3 * C_in values, padded to cells]
+    const int wcells = small_c ? (3 * C_in + VL - 1) / VL : 0;
+    const int wstride = (wcells | 1) * 16;
+    auto cells_of = [&](int ch) IDF_INLINE { return ch + 1 < n_chunks ? kRowCells : a.cells - ch * kRowCells; };
+    auto stride_of = [&](int cc) IDF_INLINE { return (cc | 1) * 16; };          // bytes per position: an odd number of 16-byte cells, no bank conflicts
+
+    i32x4 tv[kLoads];
+    // one chunk's cells in blocks of 64 per input row, dealt to the waves: block `item` of the chunk -> (row, cells)
+    auto chunk_cell = [&](int item, int ch, int cc, int &r, int &p, int &c) IDF_INLINE {
+        const int last = ch + 1 < n_chunks ? 0 : 1;
+        r = (int)(((unsigned)item * a.nb_rcp[last]) >> 16);
+        const int i = (item - r * a.nb[last]) * 64 + lane;
+        p = (int)(((unsigned)i * a.cc_rcp[last]) >> 16);
+        c = i - p * cc;
+    };
+    auto chunk_load = [&](int ch, int it0) IDF_INLINE {
+        const int cc = cells_of(ch), items = R * a.nb[ch + 1 < n_chunks ? 0 : 1];
 #pragma unroll
-    for (int ky = 0; ky < 3; ++ky)
-        w_plane[ky] = reinterpret_cast<const i32x4 *>((const unsigned char *)a.wfrag + (int64_t)ky * steps * w_step);
-    constexpr int kDepth = T::kDepth;                                // K-steps in flight
-    i32x4 aq[kDepth], bq[kDepth][3];
-    auto fetch_b = [&](int d, int sn) {
-        const uint32_t off = w_lane + (uint32_t)sn * w_step;
-        bq[d][0] = *at4(w_plane[0], off);
-        bq[d][1] = *at4(w_plane[1], off);
-        bq[d][2] = *at4(w_plane[2], off);
+        for (int b = 0; b < kLoads; ++b) {
+            const int item = (it0 + b) * kWaves + wave;
+            if (item >= items) break;
+            int r, p, c;
+            chunk_cell(item, ch, cc, r, p, c);
+            if (!row_there(r)) continue;
+            int x = x0 - 1 + p;
+            x = x < 0 ? 0 : (x >= W ? W - 1 : x);
+            tv[b] = *at4(reinterpret_cast<const i32x4 *>(row_ptr(r)), (uint32_t)((x * C_in + (ch * kRowCells + c) * VL) * EB));
+        }
+    };
+    uint32_t my_occ = 0;
+    auto chunk_store = [&](int ch, int it0, unsigned char *buf) IDF_INLINE {
+        const int cc = cells_of(ch), items = R * a.nb[ch + 1 < n_chunks ? 0 : 1], stride = stride_of(cc);
+#pragma unroll
+        for (int b = 0; b < kLoads; ++b) {
+            const int item = (it0 + b) * kWaves + wave;
+            if (item >= items) break;
+            int r, p, c;
+            chunk_cell(item, ch, cc, r, p, c);
+            if (!row_there(r)) continue;
+            const int x = x0 - 1 + p;
+            i32x4 v = tv[b];
+            if (x < 0 || x >= W) v = i32x4{0, 0, 0, 0};
+            if (p < npos) *reinterpret_cast<i32x4 *>(buf + (r * npos + p) * stride + c * 16) = v;
+            // which cells of the row hold an event anywhere in the stretch
+            unsigned long long bal = __ballot(p < npos && T::or_of(v) != 0);
+            uint32_t bits = (uint32_t)(bal | bal >> 32);
+            if (cc == 8 || cc == 4 || cc == 2 || cc == 1) {
+                bits |= bits >> 16;
+                bits |= bits >> 8;
+                if (cc <= 4) bits |= bits >> 4;
+                if (cc <= 2) bits |= bits >> 2;
+                if (cc <= 1) bits |= bits >> 1;
+                bits &= (1u << cc) - 1u;
+            } else {
+                bits = bits ? 0xffu : 0u;
+            }
+            my_occ |= bits << (8 * r);
+        }
     };
 
-    // ---- stretch -> LDS, with occupancy bits and the counters ---------------------------------
-    lds_barrier();                               // occupancy bits are cleared
-    {
-        const bool count = co_chunk == 0 && a.stats;
-        const bool weigh = EV && a.ev_limit > 0;   // the tile's events decide which way it goes
-        unsigned int ev = 0, taps = 0;               // per lane: a few cells
-        unsigned int ev_all = 0;                     // halo included
-        if (!small_c) {
-            for (int base = 0; base < cells; base += NT * kBatch) {
-                if (base > 0) tile_issue(base);
+    // ---- weights -------------------------------------------------------------------------------------
+    // [K-step][block of 32 channels][ky][tile of the pair][lane][16 bytes]  (one tile of channels: [K-step][ky][lane][16])
+    const uint32_t w_kstep = single ? 3 * 1024 : (uint32_t)n_blk * 6144;
+    const uint32_t w_ky = single ? 1024 : 2048;
+    const unsigned char *wp_next = (const unsigned char *)a.wfrag + (active && !single ? (ct0 >> 1) * 6144 + (MC == 1 ? (ct0 & 1) * 1024 : 0) : 0);
+    const uint32_t w_lane = (uint32_t)lane * 16;
+    auto fetch_w = [&](i32x4 (&w)[NW]) IDF_INLINE {
 #pragma unroll
-                for (int b = 0; b < kBatch; ++b) {
-                    const int i = base + b * NT + tid;
-                    if (i >= cells) continue;
-                    const int p = a.chunks_rcp ? (int)__umulhi((unsigned)i, a.chunks_rcp) : i, c = i - p * chunks;
-                    const int x = x0 - 1 + p;
-                    if (x < a.x_lo || x >= a.x_hi) tv[b] = i32x4{0, 0, 0, 0};
-                    *reinterpret_cast<i32x4 *>(smem + p * xs_stride + c * 16) = tv[b];
-                    if (T::cell_nonzero(tv[b])) {
-                        atomicOr(&nz[c][p >> 5], 1u << (p & 31));
-                        if (weigh || (count && p >= 1 && p <= MT)) {
-                            const int n = T::count_nonzero(tv[b]);
-                            ev_all += n;
-                            if (count && p >= 1 && p <= MT) {
-                                ev += n;
-                                taps += n * (3 - (x == 0) - (x == W - 1));
-                            }
-                        }
-                    }
+        for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+            for (int mc = 0; mc < MC; ++mc)
+                w[ky * MC + mc] = *at4(reinterpret_cast<const i32x4 *>(wp_next), w_lane + (MC == 2 ? ky * 2048 + mc * 1024 : ky * w_ky));
+    };
+    int ks_left = small_c ? 1 : 0;                 // K-steps whose weights have not been asked for
+    if (!small_c)
+        for (int ch = 0; ch < n_chunks; ++ch) ks_left += (3 * cells_of(ch) + 3) >> 2;
+    auto advance_w = [&](int n) IDF_INLINE { ks_left -= n; if (ks_left > 0) wp_next += (size_t)n * w_kstep; };     // past the end the last one is simply fetched again
+
+    // ---- the first stretch, and what can be asked for while it is on its way ---------------------------
+    acc_t acc[NR][MC][NP];
+    i32x4 wa[NW], wb[NW];
+    if (!small_c) {
+        const int iters = (R * a.nb[n_chunks > 1 ? 0 : 1] + kWaves - 1) / kWaves;
+        chunk_load(0, 0);
+        if (active) fetch_w(wa);
+        advance_w(1);
+        for (int it = 0; it < iters; it += kLoads) {
+            if (it > 0) chunk_load(0, it);
+            chunk_store(0, it, smem);
+        }
+        if (lane == 0) occ[0][wave] = my_occ;
+    } else {
+        // a lane gathers whole windows: up to twelve values next to each other in the row
+        const int xt_log = 6 + (NP == 2) - a.wc_log;           // XT = 1 << xt_log
+        if (active) fetch_w(wa);
+        advance_w(1);
+        for (int i = tid; i < R * XT; i += kThreads) {
+            const int r = i >> xt_log, p = i & (XT - 1);
+            const ev_t *row = nullptr;
+            bool there = false;
+#pragma unroll
+            for (int rr = 0; rr < R; ++rr)
+                if (r == rr) { there = row_there(rr); row = there ? reinterpret_cast<const ev_t *>(row_ptr(rr)) : nullptr; }
+            ev_t val[3][4];
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                for (int ci = 0; ci < 4; ++ci) {
+                    const int x = x0 - 1 + p + kx;
+                    val[kx][ci] = 0;
+                    if (ci < C_in && there && x >= 0 && x < W) val[kx][ci] = row[x * C_in + ci];
                 }
-            }
-        } else {
-            // the stretch is kept as one flat vector: A[x_out][k] is element (x_out - x0) * C_in + k of it
-            const ev_t *in_e = reinterpret_cast<const ev_t *>(in_row);
-            ev_t *xs_e = reinterpret_cast<ev_t *>(smem);
-            const int elems = (MT + 2) * C_in;
-            for (int i = tid; i < elems; i += NT) {
-                const int p = i / C_in;
-                const int x = x0 - 1 + p;
-                ev_t v = 0;
-                if (x >= a.x_lo && x < a.x_hi) v = *at4(in_e, (uint32_t)((x * C_in + (i - p * C_in)) * EB));
-                xs_e[i] = v;
-                if (T::ev_nonzero(v)) {
-                    ev_all += 1;
-                    if (count && p >= 1 && p <= MT) {
-                        ev += 1;
-                        taps += 3 - (x == 0) - (x == W - 1);
-                    }
-                }
-            }
-        }
-        if (count) {
-            for (int off = 32; off > 0; off >>= 1) { ev += __shfl_down(ev, off); taps += __shfl_down(taps, off); }
-            if (lane == 0) { red[0][wave] = ev; red[1][wave] = taps; }
-        }
-        if (weigh) {
-            for (int off = 32; off > 0; off >>= 1) ev_all += __shfl_down(ev_all, off);
-            if (lane == 0) red_ev[wave] = ev_all;
-        }
-        if (!small_c && tid == 0) *reinterpret_cast<i32x4 *>(smem + C_in * EB) = i32x4{0, 0, 0, 0};      // the padding behind position 0: a cell of zeros
-        lds_barrier();
-        if (count && tid == 0) {
-            unsigned long long e = 0, t = 0;
-            for (int wv = 0; wv < WM * WN; ++wv) { e += red[0][wv]; t += red[1][wv]; }
-            unsigned long long *dst = a.stats + ((int64_t)stream * a.n_layers + a.layer) * 2;
-            if (e) atomicAdd(dst, e);
-            if (t) atomicAdd(dst + 1, t * (unsigned long long)((second ? a.taps_y2 : a.taps_y) * C_out));
+            unsigned char *win = smem + i * wstride;
+            for (int k = 0; k < wcells; ++k) *reinterpret_cast<i32x4 *>(win + k * 16) = i32x4{0, 0, 0, 0};
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                for (int ci = 0; ci < 4; ++ci)
+                    if (ci < C_in) reinterpret_cast<ev_t *>(win)[kx * C_in + ci] = val[kx][ci];
         }
     }
-
-    // weights of the first K-steps, before it is known which steps are live
+    {
+        acc_t start[MC];
 #pragma unroll
-    for (int d = 0; d < kDepth; ++d) fetch_b(d, d < steps ? d : steps - 1);
+        for (int mc = 0; mc < MC; ++mc) {
+            start[mc] = acc_t{0, 0, 0, 0};
+            if (a.bias) start[mc] = *reinterpret_cast<const acc_t *>((const st_t *)a.bias + (co_ok ? co0 : 0) + mc * 4);
+        }
+#pragma unroll
+        for (int j = 0; j < NR; ++j)
+#pragma unroll
+            for (int mc = 0; mc < MC; ++mc)
+#pragma unroll
+                for (int np = 0; np < NP; ++np) acc[j][mc][np] = start[mc];
+    }
+    lds_barrier();
+    uint32_t n_mfma = 0;                           // tiles of 16 x 16 x one K-step issued
 
-    // ---- sparse tiles: the event-list path ------------------------------------------------------
-    // Zero values are not events (Sec. 1): where a tile and its halo hold few of them, the update is
-    // done event by event on the vector units instead of as a contraction that multiplies the zeros.
-    //   1. Every position's non-zero values are counted (one lane per position), an exclusive prefix
-    //      sum over the positions gives each its place in a packed list, and the events (channel,
-    //      value) are written there position by position: a compressed row.
-    //   2. If the list is short enough (the host's cost model says up to how many events the vector
-    //      units are the faster way), lanes = output channels take the tile's output positions in
-    //      turn; for a position the events of its three input positions lie one after the other in
-    //      the list; each event costs one weight word (the three ky taps of its (kx, channel) for
-    //      this lane's output channel) and three multiply-adds.  The sums go to the matrix path's
-    //      accumulators through LDS, and everything after is common.
-    bool use_events = false;
-    if constexpr (EV) {
+    // ---- sparse stretches: the event-list path ---------------------------------------------------------
+    // Where a row's stretch (halo included) holds few events they are packed into a list -- counts per
+    // position, an exclusive prefix sum, then (channel, value) words position by position -- and visited one by
+    // one on the vector units: lanes = (position group, output channel), one weight word and one multiply-add
+    // per event, output row and output channel.  The sums join the accumulators through LDS.
+    uint32_t rows_done = 0;                        // input rows the list has taken care of (bit per row)
+    if constexpr (EV && T::kEvents) {
         if (a.ev_limit > 0) {
-            const size_t front = (size_t)(MT + 2) * (small_c ? C_in * EB : xs_stride), stg = (size_t)MT * NC * EB;
-            int32_t *ev_cnt = reinterpret_cast<int32_t *>(smem + (((front > stg ? front : stg) + 15) & ~(size_t)15));
-            int32_t *ev_off = ev_cnt + (MT + 4);
-            uint32_t *ev_list = reinterpret_cast<uint32_t *>(ev_off + (MT + 4));
-            int32_t *dsum = reinterpret_cast<int32_t *>(ev_list + kEvCap);
-            uint32_t *wlds = reinterpret_cast<uint32_t *>(dsum + 3 * MT * NC);      // [kx][c_in][NC]
-            const ev_t *xs_flat = reinterpret_cast<const ev_t *>(smem);
-            // visits every non-zero value of stretch position p in channel order
-            auto for_events = [&](int p, auto &&f) {
-                if (small_c) {
-                    for (int ci = 0; ci < C_in; ++ci) {
-                        const ev_t v = xs_flat[p * C_in + ci];
-                        if (T::ev_nonzero(v)) f(ci, v);
-                    }
-                } else {
-                    for (int c = 0; c < chunks; ++c) {
-                        if (!(nz[c][p >> 5] >> (p & 31) & 1u)) continue;
-                        const ev_t *cell = reinterpret_cast<const ev_t *>(smem + p * xs_stride + c * 16);
-                        for (int e = 0; e < VL; ++e)
-                            if (T::ev_nonzero(cell[e])) f(c * VL + e, cell[e]);
-                    }
+            const int cc = a.cells, nc = 16 * MC << a.wc_log, stride = stride_of(cc);
+            const size_t front = small_c ? (size_t)R * XT * wstride : (size_t)R * npos * stride;
+            int32_t *ev_cnt = reinterpret_cast<int32_t *>(smem + ((front + 15) & ~(size_t)15));
+            int32_t *ev_off = ev_cnt + (XT + 4);
+            uint32_t *ev_list = reinterpret_cast<uint32_t *>(ev_off + (XT + 4));
+            int32_t *dsum = reinterpret_cast<int32_t *>(ev_list + kEvCap);          // [output row][position][channel]
+            uint32_t *wlds = reinterpret_cast<uint32_t *>(dsum + NR * XT * nc);          // [kx][c_in][channel]
+            const int cop = (C_out + 63) & ~63;
+            {
+                const uint32_t *wsrc = reinterpret_cast<const uint32_t *>(a.w_ev) + cg * nc;
+                for (int i = tid; i < 3 * C_in * nc; i += kThreads) {
+                    const int k = i / nc, c = i - k * nc;
+                    wlds[i] = cg * nc + c < cop ? wsrc[(size_t)k * cop + c] : 0u;
                 }
+                for (int i = tid; i < NR * XT * nc; i += kThreads) dsum[i] = 0;
+            }
+            // value ci of stretch position p (p = 0: x0 - 1) of input row r
+            auto value = [&](int r, int p, int ci) IDF_INLINE -> ev_t {
+                if (!small_c) return reinterpret_cast<const ev_t *>(smem + (r * npos + p) * stride)[ci];
+                const int q = p == 0 ? 0 : p == XT + 1 ? XT - 1 : p - 1, kx = p == 0 ? 0 : p == XT + 1 ? 2 : 1;
+                return reinterpret_cast<const ev_t *>(smem + (r * XT + q) * wstride)[kx * C_in + ci];
             };
-            unsigned int n_ev = 0;
-            for (int wv = 0; wv < WM * WN; ++wv) n_ev += red_ev[wv];
-            use_events = n_ev <= (unsigned)a.ev_limit && n_ev <= (unsigned)kEvCap;
-            if (use_events && n_ev > 0) {
-                // the tile's share of the weights, asked for first: on its way while the list is made
-                {
-                    const uint32_t *wsrc = reinterpret_cast<const uint32_t *>(a.w_ev) + co0;
-                    for (int i = tid; i < 3 * C_in * NC; i += NT) {
-                        const int row = i / NC, col = i - row * NC;
-                        wlds[i] = wsrc[(size_t)row * a.c_out_pad + col];
-                    }
-                }
-                int my_cnt = 0;
-                if (tid < MT + 2) {
-                    for_events(tid, [&](int, ev_t) { ++my_cnt; });
-                    ev_cnt[tid] = my_cnt;
+            unsigned long long visits = 0;
+            for (int r = 0; r < R; ++r) {
+                if (!row_there(r)) { rows_done |= 1u << r; continue; }
+                if (tid < XT + 2) {
+                    int n = 0;
+                    for (int ci = 0; ci < C_in; ++ci) n += T::ev_nonzero(value(r, tid, ci));
+                    ev_cnt[tid] = n;
                 }
                 lds_barrier();
-                if (tid <= MT + 2) {                 // exclusive prefix: where position tid's events begin (entry MT+2: the total)
+                if (tid <= XT + 2) {
                     int o = 0;
                     for (int q = 0; q < tid; ++q) o += ev_cnt[q];
                     ev_off[tid] = o;
                 }
                 lds_barrier();
-            }
-            if (use_events && n_ev > 0) {
-                if (tid < MT + 2) {
-                    int at = ev_off[tid];
-                    for_events(tid, [&](int ci, ev_t v) { ev_list[at++] = ((uint32_t)ci << 8) | (T::bits(v) & 0xffu); });
-                }
-                lds_barrier();
-                constexpr int PG = NT / NC;              // output positions worked on side by side
-                const int co_l = tid % NC, pg = tid / NC;
-                const uint32_t *wev = wlds + co_l;
-                unsigned long long visits = 0;
-                for (int r = pg; r < MT; r += PG) {
-                    const int i0 = ev_off[r], i1 = ev_off[r + 1], i2 = ev_off[r + 2], i3 = ev_off[r + 3];
-                    int32_t d0 = 0, d1 = 0, d2 = 0;
-                    for (int idx = i0; idx < i3; idx += 4) {
-                        uint32_t wv[4];
-                        int32_t vv[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {        // the four weight words are asked for before the first is used
-                            const int id = idx + u;
-                            const bool ok = id < i3;
-                            const uint32_t e = ev_list[ok ? id : i0];
-                            const int kx = (id >= i1) + (id >= i2);
-                            const int ci = (int)(e >> 8);
-                            vv[u] = ok ? (int32_t)(int8_t)(e & 0xffu) : 0;
-                            wv[u] = wev[(ok ? kx * C_in + ci : 0) * NC];
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            d0 += vv[u] * (int32_t)(int8_t)(wv[u] & 0xffu);
-                            d1 += vv[u] * (int32_t)(int8_t)((wv[u] >> 8) & 0xffu);
-                            d2 += vv[u] * (int32_t)(int8_t)((wv[u] >> 16) & 0xffu);
+                const int n_ev = uni(ev_off[XT + 2]);
+                if (n_ev <= (XT > 32 ? 2 : 1) * a.ev_limit) {
+                    rows_done |= 1u << r;
+                    if (tid < XT + 2) {
+                        int at = ev_off[tid];
+                        for (int ci = 0; ci < C_in; ++ci) {
+                            const ev_t v = value(r, tid, ci);
+                            if (T::ev_nonzero(v)) ev_list[at++] = ((uint32_t)ci << 8) | (uint32_t)(uint8_t)v;
                         }
                     }
-                    dsum[(0 * MT + r) * NC + co_l] = d0;
-                    dsum[(1 * MT + r) * NC + co_l] = d1;
-                    dsum[(2 * MT + r) * NC + co_l] = d2;
-                    visits += (unsigned long long)(i3 - i0);
+                    lds_barrier();
+                    const int col = tid & (nc - 1), pg = tid / nc, n_pg = kThreads / nc;
+                    for (int p = pg; p < XT && x0 + p < W; p += n_pg) {
+                        const int i1 = ev_off[p + 1], i2 = ev_off[p + 2], i3 = ev_off[p + 3];
+                        int32_t d[NR] = {};
+                        for (int i = ev_off[p]; i < i3; ++i) {
+                            const uint32_t e = ev_list[i];
+                            const int kx = (i >= i1) + (i >= i2);
+                            const uint32_t w = wlds[(kx * C_in + (int)(e >> 8)) * nc + col];
+#pragma unroll
+                            for (int j = 0; j < NR; ++j)
+                                if (r - j >= 0 && r - j <= 2) d[j] += (int32_t)(int8_t)(e & 0xffu) * (int32_t)(int8_t)((w >> (8 * (r - j))) & 0xffu);
+                        }
+#pragma unroll
+                        for (int j = 0; j < NR; ++j)
+                            if (r - j >= 0 && r - j <= 2 && j < rows) {
+                                dsum[(j * XT + p) * nc + col] += d[j];
+                                if (col == 0) visits += (unsigned long long)(i3 - ev_off[p]);
+                            }
+                    }
                 }
-                if (COUNT && a.issued && co_l == 0 && visits)
-                    atomicAdd(a.issued + (int64_t)stream * a.n_layers + a.layer, visits * (3ull * NC));
                 lds_barrier();
-                const int dcol = wn * 32 + (lane & 31), drow = wm * 32 + row_lane;
+            }
+            if (a.issued && visits)
+                atomicAdd(a.issued + (int64_t)stream * a.n_layers + a.layer, visits * (unsigned long long)nc);
+            if (active) {
+                const int cl = co0 - cg * nc;
 #pragma unroll
-                for (int ky = 0; ky < 3; ++ky)
+                for (int j = 0; j < NR; ++j)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
+                    for (int mc = 0; mc < MC; ++mc)
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            acc[ky][i * 4 + j] += (st_t)dsum[(ky * MT + drow + 8 * i + j) * NC + dcol];
+                        for (int np = 0; np < NP; ++np)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) acc[j][mc][np][i] += dsum[(j * XT + wp * 16 * NP + np * 16 + m) * nc + cl + mc * 4 + i];
             }
         }
     }
 
-    // ---- which K-steps have anything in them for this wave's 32 positions -------------------
-    unsigned long long live;
-    if (!use_events) {
-        bool occ = small_c && lane < steps;          // few channels: every step is visited
-        if (!small_c && lane < steps) {
+    // ---- contraction -------------------------------------------------------------------------------------
+    // All matrix instructions of input row r's fragment of one K-step: tap row ky = r - j of output row j.
+    auto deliver = [&](const i32x4 (&w)[NW], const i32x4 (&x)[NP], int r, int n_on) IDF_INLINE {
 #pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2) {
-                const int k0 = lane * KI + h2 * VL;
-                if (k0 < KT) {
-                    const int kx = k0 / C_in, c = (k0 - kx * C_in) / VL;
-                    const int start = wm * 32 + kx;               // first tile position of the window
-                    const uint32_t lo = nz[c][start >> 5], hi = nz[c][(start >> 5) + 1];
-                    const uint32_t win = (uint32_t)((((unsigned long long)hi << 32) | lo) >> (start & 31));
-                    occ |= win != 0;
-                }
+        for (int j = 0; j < NR; ++j) {
+            const int ky = r - j;
+            if (ky < 0 || ky > 2) continue;
+#pragma unroll
+            for (int e = 0; e < T::kInst; ++e)
+#pragma unroll
+                for (int mc = 0; mc < MC; ++mc)
+#pragma unroll
+                    for (int np = 0; np < NP; ++np)
+                        if (np < n_on) acc[j][mc][np] = T::mfma(w[ky * MC + mc], x[np], acc[j][mc][np], e);
+        }
+    };
+    auto taps_used = [&](int r) IDF_INLINE { int n = 0; for (int j = 0; j < NR; ++j) n += r - j >= 0 && r - j <= 2 && j < rows; return n; };
+
+    // One chunk of CC cells per position (CC = 0: any number, known at run time only).  wa holds the weights
+    // of its first K-step on entry and those of the next chunk's first on exit.
+    auto compute = [&](auto cc_tag, auto check_tag, const unsigned char *buf, int cc_rt, uint32_t bits) IDF_INLINE {
+        constexpr int CC = decltype(cc_tag)::value;
+        constexpr bool CHECK = decltype(check_tag)::value;
+        const int cc = CC ? CC : cc_rt, stride = stride_of(cc);
+        const int S = (3 * cc + 3) >> 2;
+        const uint32_t pos = (uint32_t)((wp * 16 * NP + m) * stride);
+        const uint32_t row_pitch = (uint32_t)(npos * stride);
+        auto one = [&](int s, const i32x4 (&w)[NW]) IDF_INLINE {
+            // this lane's cell of the K-step: q = 4 s + g of the 3 * cc cells of its window (past the end the last one
+            // again: the weights there are zero)
+            uint32_t off;
+            if (CC == 8) off = pos + (uint32_t)((s >> 1) * stride + (s & 1) * 64 + g * 16);
+            else if (CC == 4) off = pos + (uint32_t)(s * stride + g * 16);
+            else {
+                int q = 4 * s + g;
+                q = q < 3 * cc ? q : 3 * cc - 1;
+                const int kx = CC == 2 ? q >> 1 : CC == 1 ? q : (q >= cc) + (q >= 2 * cc);
+                off = pos + (uint32_t)(kx * stride + (q - kx * cc) * 16);
+            }
+            const uint32_t part = CC == 8 ? ((s & 1) ? 0xf0u : 0x0fu) : 0xffu;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (CHECK && !((bits >> (8 * r)) & part)) continue;          // no event in these cells of the row: nothing to do
+                i32x4 x[NP];
+#pragma unroll
+                for (int np = 0; np < NP; ++np)
+                    if (!CHECK || np < np_on) x[np] = *reinterpret_cast<const i32x4 *>(buf + off + r * row_pitch + np * 16 * stride);
+                deliver(w, x, r, CHECK ? np_on : NP);
+                n_mfma += (uint32_t)(taps_used(r) * MC * (CHECK && np_on < NP ? np_on : NP));
+            }
+        };
+        if constexpr (CC == 8) {
+#pragma unroll
+            for (int s = 0; s < 6; s += 2) {
+                fetch_w(wb); advance_w(1);
+                one(s, wa);
+                fetch_w(wa); advance_w(1);
+                one(s + 1, wb);
+            }
+        } else if constexpr (CC == 2) {
+            fetch_w(wb); advance_w(1);
+            one(0, wa);
+            fetch_w(wa); advance_w(1);
+            one(1, wb);
+        } else if constexpr (CC == 4 || CC == 1) {
+            // an odd number of K-steps: only ever the layer's last chunk, nothing follows
+            if (CC == 1) { one(0, wa); return; }
+            fetch_w(wb); advance_w(1);
+            one(0, wa);
+            fetch_w(wa); advance_w(1);
+            one(1, wb);
+            one(2, wa);
+        } else {
+            for (int s = 0; s < S; ++s) {
+                fetch_w(wb); advance_w(1);
+                one(s, wa);
+#pragma unroll
+                for (int q = 0; q < NW; ++q) wa[q] = wb[q];
             }
         }
-        live = __ballot(occ);
-        // what the matrix instructions of this wave will multiply, zeros inside a live step included
-        if (COUNT && a.issued && lane == 0 && live)
-            atomicAdd(a.issued + (int64_t)stream * a.n_layers + a.layer,
-                      (unsigned long long)__builtin_popcountll(live) * (3ull * 32 * 32 * KI));
-    }
-
-    else live = 0;
-
-    // ---- contraction over the live K-steps ----------------------------------------------------
-    if (use_events) {
-        // done above, event by event
-    } else if (small_c) {
-        // first layers: K = 3*C_in <= 12, one or two steps (all prefetched); the fragment is gathered
-        // element by element
-        const ev_t *xs_e = reinterpret_cast<const ev_t *>(smem) + r * C_in;
+    };
+    if (small_c) {
+        // one K-step per tap row, always visited
+        if (active) {
 #pragma unroll
-        for (int sn = 0; sn < (12 + KI - 1) / KI; ++sn) {
-            if (sn >= steps) break;
-            const int k0 = sn * KI + hlf * VL;
-            ev_t e[VL];
+            for (int r = 0; r < R; ++r) {
+                if (EV && ((rows_done >> r) & 1u)) continue;
+                if (r >= rows + 2) continue;
+                i32x4 x[NP];
 #pragma unroll
-            for (int q = 0; q < VL; ++q) e[q] = k0 + q < KT ? xs_e[k0 + q] : (ev_t)0;
-            i32x4 av;
-            __builtin_memcpy(&av, e, 16);
-            acc[0] = T::mfma(av, bq[sn][0], acc[0]);
-            acc[1] = T::mfma(av, bq[sn][1], acc[1]);
-            acc[2] = T::mfma(av, bq[sn][2], acc[2]);
+                for (int np = 0; np < NP; ++np)
+                    x[np] = *reinterpret_cast<const i32x4 *>(smem + (r * XT + wp * 16 * NP + np * 16 + m) * wstride + (g < wcells ? g : wcells - 1) * 16);
+                deliver(wa, x, r, np_on);
+                n_mfma += (uint32_t)(taps_used(r) * MC * (np_on < NP ? np_on : NP));
+            }
         }
     } else {
-        // Software pipeline over the live steps, kDepth steps deep.  Every slot issues its loads
-        // unconditionally (past the end the last live step is simply fetched again), so the
-        // loop body is straight-line code and each slot waits for exactly its own operands.
-        const int n_live = __builtin_popcountll(live);
-        int s_last = 0;
-        bool any_left = true;
-        auto next_step = [&]() {
-            const int f = __builtin_ffsll((long long)live);           // 0 when nothing is left
-            any_left = f != 0;
-            const int sn = f ? f - 1 : s_last;
-            s_last = sn;
-            live &= live - 1;
-            return sn;
-        };
-        auto fetch_a = [&](int d, int sn) {
-            const int k0 = sn * KI + hlf * VL;
-            const int kx = (int)__umulhi((unsigned)k0, a.c_in_rcp);   // k0 / C_in
-            const int ci = k0 - kx * C_in;
-            // half a step of padding at the end of K, and slots past the last live step: these read the cell of zeros
-            // behind position 0 (no select after the read, so nothing waits for it before the slot's turn comes)
-            const bool ok = any_left && k0 < KT;
-            aq[d] = *reinterpret_cast<const i32x4 *>(smem + (ok ? (r + kx) * xs_stride + ci * EB : C_in * EB));
-        };
-        if (n_live > 0) {
-            int sn0[kDepth];
-            bool guessed = true;
+        const int buf_bytes = R * npos * stride_of(n_chunks > 1 ? kRowCells : a.cells);
+        constexpr uint32_t kFull = R == 4 ? 0x11111111u : 0x00111111u, kFullRow = R == 4 ? 0x01010101u : 0x00010101u;
+        for (int ch = 0; ch < n_chunks; ++ch) {
+            const unsigned char *buf = smem + (ch & 1) * buf_bytes;
+            const int cc = cells_of(ch);
+            uint32_t bits = 0;
 #pragma unroll
-            for (int d = 0; d < kDepth; ++d) {
-                sn0[d] = next_step();
-                fetch_a(d, sn0[d]);
-                guessed &= sn0[d] == (d < steps ? d : steps - 1);
+            for (int w = 0; w < kWaves; ++w) bits |= occ[ch & 1][w];
+            bits = (uint32_t)uni((int)bits);
+            if (EV) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) if ((rows_done >> r) & 1u) bits &= ~(0xffu << (8 * r));
             }
-            // a wrong guess: all slots again, in slot order -- whichever way the loop is entered, the youngest requests
-            // are then slot 0's, 1's, ... in turn, and each slot's wait inside the loop can leave the others in flight
-            if (!guessed) {
-#pragma unroll
-                for (int d = 0; d < kDepth; ++d) fetch_b(d, sn0[d]);
-            }
-            for (int it = 0; it < n_live; it += kDepth) {
-#pragma unroll
-                for (int d = 0; d < kDepth; ++d) {
-                    // no branch around these: past the last live step the slot multiplies zeros, and the loop body stays
-                    // one straight line in which every slot's wait leaves the younger slots' requests in flight
-                    acc[0] = T::mfma(aq[d], bq[d][0], acc[0]);
-                    acc[1] = T::mfma(aq[d], bq[d][1], acc[1]);
-                    acc[2] = T::mfma(aq[d], bq[d][2], acc[2]);
-                    const int sn = next_step();
-                    fetch_a(d, sn);
-                    fetch_b(d, sn);
-                    __builtin_amdgcn_sched_barrier(0);      // the slots stay in this order: requests go out right behind their slot's matrix instructions
+            if (ch + 1 < n_chunks) chunk_load(ch + 1, 0);
+            if (active) {
+                const uint32_t nib = (bits | bits >> 1 | bits >> 2 | bits >> 3) & 0x11111111u, byt = (nib | nib >> 4) & 0x01010101u;
+                const bool all = np_on >= NP && (cc == 8 ? nib == kFull : byt == kFullRow);
+                if (bits == 0) {                    // nothing but zeros: no weights either
+                    advance_w(((3 * cc + 3) >> 2) - 1);
+                    if (ch + 1 < n_chunks) fetch_w(wa);
+                    advance_w(1);
+                } else if (cc == 8) {
+                    if (all) compute(std::integral_constant<int, 8>{}, std::false_type{}, buf, cc, bits); else compute(std::integral_constant<int, 8>{}, std::true_type{}, buf, cc, bits);
+                } else if (cc == 4) {
+                    if (all) compute(std::integral_constant<int, 4>{}, std::false_type{}, buf, cc, bits); else compute(std::integral_constant<int, 4>{}, std::true_type{}, buf, cc, bits);
+                } else if (cc == 2) {
+                    compute(std::integral_constant<int, 2>{}, std::true_type{}, buf, cc, bits);
+                } else if (cc == 1) {
+                    compute(std::integral_constant<int, 1>{}, std::true_type{}, buf, cc, bits);
+                } else {
+                    compute(std::integral_constant<int, 0>{}, std::true_type{}, buf, cc, bits);
                 }
             }
+            if (ch + 1 < n_chunks) {
+                my_occ = 0;
+                chunk_store(ch + 1, 0, smem + ((ch + 1) & 1) * buf_bytes);
+                if (lane == 0) occ[(ch + 1) & 1][wave] = my_occ;
+                lds_barrier();
+            }
         }
     }
+    if (!active) return;
 
-    // ---- epilogue -----------------------------------------------------------------------------
-    // Rows of c go back to the ring straight from the accumulator layout (32 lanes x 4 bytes = one
-    // full 128-byte line per row of the tile).  Event-type rows (1 or 2 bytes per value) would be
-    // partial-line writes from that layout, so they are staged in LDS as [position][channel] and
-    // leave as 16-byte chunks that tile whole lines.
-    if (T::kOcc > 2) {
-        // The offsets are worked out again rather than kept: sixteen registers held across the
-        // contraction would be spilled to memory by every lane at three waves per SIMD.  (The
-        // empty statement hides from the compiler that it has seen this value before.)
-        int xo_again = xo_base;
-        asm volatile("" : "+v"(xo_again));
-        cell_offsets(xo_again);
-    }
-    ev_t *stage = reinterpret_cast<ev_t *>(smem);
-    bool stage_free = false;                          // the stretch in LDS may still be read by slower waves
-    auto flush = [&](ev_t *grow, int row_w, int p0, int npos) {
-        // grow: the row [x][C_out] in global memory; positions p0 .. p0+npos-1 of it are staged
-        lds_barrier();
-        constexpr int kPer = 16 / EB;                 // channels per 16-byte chunk
-        constexpr int kCpp = NC / kPer;               // chunks per position
-        for (int i = tid; i < npos * kCpp; i += NT) {
-            const int p = i / kCpp, k = i - p * kCpp;
-            const int x = p0 + p, cch = co0 + k * kPer;
-            if (x < row_w && cch < C_out)
-                *at4(reinterpret_cast<i32x4 *>(grow), (uint32_t)((x * C_out + cch) * EB)) =
-                    *reinterpret_cast<const i32x4 *>(stage + p * NC + k * kPer);
+    // ---- the rows are final: activate, emit, count ---------------------------------------------------------
+    constexpr int NV = 4 * MC;                     // neighbouring channels a lane holds
+    uint32_t next = 0, pooled = 0;                 // events for the next layer (high half: their taps), events the pool receives
+    auto emit = [&](const uint32_t (&e)[MC * EB], int row_w, int x, int slot) IDF_INLINE {
+        unsigned char *d = (unsigned char *)a.dst + ((int64_t)stream * a.dst_stride + (int64_t)slot * row_w * C_out) * EB;
+        const uint32_t off = (uint32_t)((x * C_out + co0) * EB);
+        if constexpr (MC * EB == 1) *at4(reinterpret_cast<uint32_t *>(d), off) = e[0];
+        else if constexpr (MC * EB == 2) *at4(reinterpret_cast<i32x2 *>(d), off) = i32x2{(int)e[0], (int)e[1]};
+        else {
+#pragma unroll
+            for (int q = 0; q < MC * EB / 4; ++q)
+                *at4(reinterpret_cast<i32x4 *>(d), off + q * 16) = i32x4{(int)e[4 * q], (int)e[4 * q + 1], (int)e[4 * q + 2], (int)e[4 * q + 3]};
         }
-        lds_barrier();
     };
-    const int col = wn * 32 + (lane & 31);            // channel within the chunk
-    const int prow = wm * 32 + row_lane;              // first of this lane's positions within the tile
-    uint32_t heldv[16];                               // the pool's held row: one register each, nothing to pack
-    {
-        const bool need = tap(2).valid && tap(2).emit == kEmitPoolHeld;   // only row y-1 can pair with the held row
+    auto emit_out = [&](const st_t (&v)[NV], int row_w, int x, int slot) IDF_INLINE {        // last layer: 4-byte values, not rounded to the event type
+        st_t *d = (st_t *)a.dst + (int64_t)stream * a.dst_stride + (int64_t)slot * row_w * C_out;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            heldv[q] = 0;
-            if (need) heldv[q] = T::bits(*at4(held, roff[q] / (4 / EB)));
-        }
-    }
+        for (int q = 0; q < MC; ++q)
+            *at4(reinterpret_cast<acc_t *>(d), (uint32_t)((x * C_out + co0 + q * 4) * 4)) = acc_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+    };
+    auto count = [&](const uint32_t (&e)[MC * EB]) IDF_INLINE {
+        uint32_t n = 0;
 #pragma unroll
-    for (int kk = 0; kk < 3; ++kk) {
-        const int ky = 2 - kk;                        // row y-1 first
-        const MfmaTap &t = tap(ky);
-        if (!t.valid) continue;
-        if (DBL && t.emit == kEmitKeep) continue;     // stays in the accumulators for the second row
-        st_t c[16];
+        for (int q = 0; q < MC * EB; ++q) n += (uint32_t)T::nonzero(e[q]);
+        return n;
+    };
+    auto slot_of = [&](int i) IDF_INLINE { int s = a.dst_slot0 + i; return s >= a.dst_rows ? s - a.dst_rows : s; };
 #pragma unroll
-        for (int q = 0; q < 16; ++q) c[q] = acc[ky][q];
-        if (t.emit == kEmitNone) {
-            st_t *rrow = ring + (int64_t)t.ring_slot * W * C_out;
-            if (wave_full) {
+    for (int np = 0; np < NP; ++np) {
+        const int x = xw + np * 16 + m;
+        const bool ok = x < W && co_ok;
+        if (!a.pool) {
 #pragma unroll
-                for (int q = 0; q < 16; ++q) *at4(rrow, roff[q]) = c[q];
-            } else {
+            for (int j = 0; j < NR; ++j) {
+                if (j >= rows) break;
+                st_t v[NV];
 #pragma unroll
-                for (int q = 0; q < 16; ++q)
-                    if (vmask >> q & 1u) *at4(rrow, roff[q]) = c[q];
-            }
-            continue;
-        }
-        ev_t e[16];
+                for (int q = 0; q < NV; ++q) v[q] = T::activate(acc[j][q >> 2][np][q & 3], a.act, a.shr, a.clamp_hi);
+                if (!ok) continue;
+                if (a.to_output) {
+                    emit_out(v, W, x, slot_of(rg * NR + j));
+                } else {
+                    uint32_t e[MC * EB];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) e[q] = T::to_ev(T::activate(c[q], a.act, a.shr, a.clamp_hi));
-        if (a.pool_layer >= 0 && a.stats) {          // what the fused pool receives counts as its events
-            unsigned int n = 0;
-#pragma unroll
-            for (int q = 0; q < 16; ++q) n += ((vmask >> q & 1u) && T::ev_nonzero(e[q])) ? 1u : 0u;
-            for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off);
-            if (lane == 0 && n)
-                atomicAdd(a.stats + ((int64_t)stream * a.n_layers + a.pool_layer) * 2, (unsigned long long)n);
-        }
-        if (t.emit == kEmitDirect && a.to_output) {
-            // last layer: 4-byte values, not rounded to the event type
-            st_t *orow = (st_t *)a.dst + (int64_t)stream * a.dst_stream_stride + t.dst_slot * W * C_out;
-#pragma unroll
-            for (int q = 0; q < 16; ++q)
-                if (wave_full || (vmask >> q & 1u)) *at4(orow, roff[q]) = T::activate(c[q], a.act, a.shr, a.clamp_hi);
-        } else if (t.emit == kEmitDirect || (t.emit == kEmitHold && t.store_held)) {
-            if (!stage_free) { lds_barrier(); stage_free = true; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) stage[(prow + 8 * i + j) * NC + col] = e[i * 4 + j];
-            ev_t *grow = t.emit == kEmitHold
-                             ? held
-                             : (ev_t *)a.dst + (int64_t)stream * a.dst_stream_stride + t.dst_slot * W * C_out;
-            flush(grow, W, x0, MT);
-        }
-        if (t.emit == kEmitHold) {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) hprev[q] = e[q];
-        } else if (t.emit == kEmitPoolHeld || t.emit == kEmitPoolReg) {
-            // 2x2 max: this row and the even row of the pair, positions 2j and 2j+1 (both in this lane)
-            const int Wp = W / 2;
-            if (!stage_free && !a.to_output) { lds_barrier(); stage_free = true; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int jj = 0; jj < 2; ++jj) {
-                    st_t m = T::ev_val(e[i * 4 + 2 * jj]);
-                    const st_t m1 = T::ev_val(e[i * 4 + 2 * jj + 1]);
-                    m = m1 > m ? m1 : m;
-                    st_t e0, e1;
-                    if (t.emit == kEmitPoolHeld) {
-                        e0 = T::ev_val(T::from_bits(heldv[i * 4 + 2 * jj]));
-                        e1 = T::ev_val(T::from_bits(heldv[i * 4 + 2 * jj + 1]));
-                    } else {
-                        e0 = T::ev_val(hprev[i * 4 + 2 * jj]);
-                        e1 = T::ev_val(hprev[i * 4 + 2 * jj + 1]);
-                    }
-                    m = e0 > m ? e0 : m;
-                    m = e1 > m ? e1 : m;
-                    const int pl = ((prow + 8 * i) >> 1) + jj;        // pooled position within the tile
-                    if (a.to_output) {
-                        const int xp = (x0 >> 1) + pl;
-                        if (co_ok && xp < Wp)
-                            ((st_t *)a.dst)[(int64_t)stream * a.dst_stream_stride + (t.dst_slot * Wp + xp) * C_out + co] = m;
-                    } else {
-                        stage[pl * NC + col] = T::to_ev(m);
+                    for (int q = 0; q < MC; ++q) T::pack4(v + 4 * q, e + q * EB);
+                    emit(e, W, x, slot_of(rg * NR + j));
+                    if (a.next_layer >= 0) {
+                        const uint32_t n = count(e);
+                        next += n + ((n * (uint32_t)(taps_of(x, W) * taps_of(y + j, H))) << 16);
                     }
                 }
-            if (!a.to_output)
-                flush((ev_t *)a.dst + (int64_t)stream * a.dst_stream_stride + t.dst_slot * Wp * C_out, Wp, x0 >> 1, MT / 2);
-        }
-    }
-    }   // rows of the step
-}
-
-template <class T, int WM, int WN, bool COUNT, bool EV>
-__global__ void __launch_bounds__(64 * WM * WN, 2) k_conv3x3_mfma(const MfmaStep a, const StreamSel sel)
-{
-    // tile by tile, the streams of a tile side by side
-    conv3x3_row<T, WM, WN, COUNT, EV>(a, sel, blockIdx.z, blockIdx.x, 0, (uint32_t)sizeof(MfmaStep));
-}
-
-// Several layers' steps in one launch (each on a row that was complete before the launch).  The grid
-// is (stream, tile, step): a workgroup knows its step from its own index, so its arguments arrive in
-// one round of scalar loads (a table of first tiles per step cost a second, dependent round: about
-// half a microsecond before the first row request of every workgroup).  Steps with fewer tiles than
-// the launch's largest leave a few workgroups that return at once.  One tile shape for all steps.
-// In dispatch order the streams of a tile lie side by side, then the tiles of a step, then the steps
-// with the deepest (longest) first.  Consecutive workgroups go to the eight XCDs in turn: with a
-// multiple of eight streams a stream always meets the same XCD, so its row stretch is fetched into one
-// L2 for all its channel chunks, a weight fragment is fetched once per XCD and used by that XCD's
-// streams close in time, and every step is spread evenly.  (Stream by stream with the tiles inside was
-// measured 8 % slower on the VGG-style workload; one contiguous eighth of the order per XCD slower
-// still: the steps differ too much in length.)
-// (the form that can take two rows per step keeps a pool's even row in registers across the second
-// row's contraction: compiled for two waves per SIMD)
-template <class T, int WM, int WN, bool COUNT, bool EV, bool DBL = false>
-__global__ void __launch_bounds__(64 * WM * WN, DBL ? 2 : T::kOcc) k_conv3x3_mfma_batch(const MfmaBatch b, const StreamSel sel)
-{
-    conv3x3_row<T, WM, WN, COUNT, EV, DBL>(b.st[blockIdx.z], sel, blockIdx.y, blockIdx.x,
-                                           (uint32_t)(offsetof(MfmaBatch, st) + blockIdx.z * sizeof(MfmaStep)), (uint32_t)sizeof(MfmaBatch));
-}
-
-template <class T, int WM, int WN>
-hipError_t launch_batch_shape(const MfmaBatch &b, const StreamSel &sel, const LaunchCtx &lc)
-{
-    constexpr int MT = 32 * WM, NC = 32 * WN;
-    size_t lds = 0;
-    int tiles_max = 0;
-    for (int k = 0; k < b.n; ++k) {
-        const MfmaStep &a = b.st[k];
-        tiles_max = std::max(tiles_max, ((a.w + MT - 1) / MT) * ((a.c_out + NC - 1) / NC));
-        lds = std::max(lds, (size_t)(MT + 2) * (a.c_in * T::EB + 16));
-        lds = std::max(lds, (size_t)MT * NC * T::EB);
-    }
-    if (b.n < 1 || tiles_max < 1 || tiles_max > 65535) return hipErrorInvalidValue;      // tiles are the grid's y extent
-    const dim3 grid(sel.n, tiles_max, b.n), block(64 * WM * WN);
-    if constexpr (T::kEvents) {
-        // room for the event path behind a step's stretch / staging area, or no event path for that step; the kernel
-        // that carries the event path is a separate one, so a launch without it pays nothing for it
-        MfmaBatch bb = b;
-        const size_t base = (lds + 15) & ~(size_t)15;
-        bool any = false;
-        for (int k = 0; k < bb.n; ++k) {
-            if (bb.st[k].ev_limit <= 0) continue;
-            const size_t need = base + event_lds_bytes(MT, NC, bb.st[k].c_in);
-            if (need <= 64 * 1024) { lds = std::max(lds, need); any = true; }
-            else bb.st[k].ev_limit = 0;
-        }
-        if (any) {
-            if (b.st[0].issued) return launch(k_conv3x3_mfma_batch<T, WM, WN, true, true>, grid, block, lds, lc, bb, sel);
-            return launch(k_conv3x3_mfma_batch<T, WM, WN, false, true>, grid, block, lds, lc, bb, sel);
-        }
-    }
-    bool two_rows = false;                        // some step takes two input rows: the kernel that can
-    for (int k = 0; k < b.n; ++k) two_rows = two_rows || b.st[k].dbl;
-    if (two_rows) {
-        if constexpr (WM == 1) {                  // (the launches that pair rows use tiles of 32 positions only)
-            if (b.st[0].issued) return launch(k_conv3x3_mfma_batch<T, WM, WN, true, false, true>, grid, block, lds, lc, b, sel);
-            return launch(k_conv3x3_mfma_batch<T, WM, WN, false, false, true>, grid, block, lds, lc, b, sel);
+            }
         } else {
-            return hipErrorInvalidValue;
+            // 2x2 max over the two rows and the neighbouring position; rounding does not change the order of values
+            st_t v[NV];
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                if (j >= rows) break;
+                st_t u[NV];
+#pragma unroll
+                for (int q = 0; q < NV; ++q) u[q] = T::activate(acc[j][q >> 2][np][q & 3], a.act, a.shr, a.clamp_hi);
+                if (y + j >= a.pool_from && ok) {
+                    uint32_t e[MC * EB];
+#pragma unroll
+                    for (int q = 0; q < MC; ++q) T::pack4(u + 4 * q, e + q * EB);
+                    pooled += count(e);
+                }
+#pragma unroll
+                for (int q = 0; q < NV; ++q) v[q] = j == 0 ? u[q] : (u[q] > v[q] ? u[q] : v[q]);
+            }
+            if (NR == 2 && rows == 2 && a.pool_emit) {
+#pragma unroll
+                for (int q = 0; q < NV; ++q) { const st_t o = neighbour(v[q]); v[q] = o > v[q] ? o : v[q]; }
+                const int Wp = W >> 1, xp = x >> 1, yp = y >> 1;
+                if (ok && !(m & 1) && xp < Wp) {
+                    if (a.to_output) {
+                        // (a pool as the last layer: float32 nets only, whose events are the values)
+                        emit_out(v, Wp, xp, slot_of(rg));
+                    } else {
+                        uint32_t e[MC * EB];
+#pragma unroll
+                        for (int q = 0; q < MC; ++q) T::pack4(v + 4 * q, e + q * EB);
+                        emit(e, Wp, xp, slot_of(rg));
+                        if (a.next_layer >= 0) {
+                            const uint32_t n = count(e);
+                            next += n + ((n * (uint32_t)(taps_of(xp, Wp) * taps_of(yp, H >> 1))) << 16);
+                        }
+                    }
+                }
+            }
         }
     }
-    // the variant that adds up what it issues is a kernel of its own: the one that is timed carries none of it
-    if (b.st[0].issued) return launch(k_conv3x3_mfma_batch<T, WM, WN, true, false>, grid, block, lds, lc, b, sel);
-    return launch(k_conv3x3_mfma_batch<T, WM, WN, false, false>, grid, block, lds, lc, b, sel);
-}
-
-template <class T>
-hipError_t launch_batch(const MfmaBatch &b, const StreamSel &sel, const LaunchCtx &lc)
-{
-    switch (b.tile) {
-    case kMfmaTile64x64: return launch_batch_shape<T, 2, 2>(b, sel, lc);
-    case kMfmaTile64x32: return launch_batch_shape<T, 2, 1>(b, sel, lc);
-    case kMfmaTile32x64: return launch_batch_shape<T, 1, 2>(b, sel, lc);
-    case kMfmaTile32x32: return launch_batch_shape<T, 1, 1>(b, sel, lc);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-template <class T, int WM, int WN>
-hipError_t launch_one(const MfmaStep &a, const StreamSel &sel, const LaunchCtx &lc)
-{
-    constexpr int MT = 32 * WM, NC = 32 * WN;
-    const int x_tiles = (a.w + MT - 1) / MT, co_chunks = (a.c_out + NC - 1) / NC;
-    size_t lds = (size_t)(MT + 2) * (a.c_in * T::EB + 16);
-    const size_t stage = (size_t)MT * NC * T::EB;       // the epilogue reuses the space to stage emitted rows
-    if (lds < stage) lds = stage;
-    if (x_tiles * co_chunks > 65535) return hipErrorInvalidValue;      // tiles are the grid's z extent
-    const dim3 grid(sel.n, 1, x_tiles * co_chunks), block(64 * WM * WN);
-    if constexpr (T::kEvents) {
-        const size_t with_events = ((lds + 15) & ~(size_t)15) + event_lds_bytes(MT, NC, a.c_in);
-        if (a.ev_limit > 0 && with_events <= 64 * 1024) {
-            if (a.issued) return launch(k_conv3x3_mfma<T, WM, WN, true, true>, grid, block, with_events, lc, a, sel);
-            return launch(k_conv3x3_mfma<T, WM, WN, false, true>, grid, block, with_events, lc, a, sel);
+    if (a.stats) {
+        if (a.next_layer >= 0) {
+            next = wave_sum(next);
+            if (lane == 0 && next) {
+                unsigned long long *d = a.stats + ((int64_t)stream * a.n_layers + a.next_layer) * 2;
+                atomicAdd(d, (unsigned long long)(next & 0xffffu));
+                atomicAdd(d + 1, (unsigned long long)(next >> 16) * (unsigned long long)a.next_c_out);
+            }
+        }
+        if (a.pool) {
+            pooled = wave_sum(pooled);
+            if (lane == 0 && pooled) atomicAdd(a.stats + ((int64_t)stream * a.n_layers + a.pool_layer) * 2, (unsigned long long)pooled);
         }
     }
-    if (a.issued) return launch(k_conv3x3_mfma<T, WM, WN, true, false>, grid, block, lds, lc, a, sel);
-    return launch(k_conv3x3_mfma<T, WM, WN, false, false>, grid, block, lds, lc, a, sel);
+    // what the matrix instructions of this wave multiplied, zeros inside a live K-step included
+    if (a.issued && lane == 0 && n_mfma)
+        atomicAdd(a.issued + (int64_t)stream * a.n_layers + a.layer, (unsigned long long)n_mfma * (256ull * 4 * VL));
 }
 
-template <class T> hipError_t launch_prec(const MfmaStep &a, const StreamSel &sel, const LaunchCtx &lc)
+// Several layers' steps in one launch (each on rows that were complete before the launch).  The grid is
+// (stream, tile, step): a workgroup knows its step from its own index, so its arguments arrive in one
+// round of scalar loads.  Steps with fewer tiles than the launch's largest leave workgroups that return
+// at once.  In dispatch order the streams of a tile lie side by side, then the tiles of a step, then the
+// steps with the deepest (longest) first.  Consecutive workgroups go to the eight XCDs in turn: with a
+// multiple of eight streams a stream always meets the same XCD, so its rows stay in one L2 from the layer
+// that emits them to the layer that reads them.
+template <class T, bool EV, bool WIDE>
+__global__ void __launch_bounds__(kThreads, 2) k_conv3x3_mfma_rows(const RowBatch b, const StreamSel sel)
 {
-    switch (a.tile) {
-    case kMfmaTile64x64: return launch_one<T, 2, 2>(a, sel, lc);
-    case kMfmaTile128x32: return launch_one<T, 4, 1>(a, sel, lc);
-    case kMfmaTile32x64: return launch_one<T, 1, 2>(a, sel, lc);
-    case kMfmaTile32x32: return launch_one<T, 1, 1>(a, sel, lc);
-    default: return hipErrorInvalidValue;
+    (void)b;                                      // the first argument: it begins the segment
+    ArgStep &a = *((ArgStep *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(RowBatch, st)) + blockIdx.z);
+    const int tile = blockIdx.y, si = blockIdx.x;
+    if (tile >= a.tiles) return;
+    switch (a.form) {
+    case kRowTake: take_row<T>(a, sel, tile, si); break;
+    case kRowSmall1: conv_rows<T, 1, 1, 1, EV>(a, sel, tile, si); break;
+    case kRowSmall2: conv_rows<T, 1, 1, 2, EV>(a, sel, tile, si); break;
+    case kRowWide1: if constexpr (WIDE) conv_rows<T, 2, 2, 1, false>(a, sel, tile, si); break;
+    case kRowWide2: if constexpr (WIDE) conv_rows<T, 2, 2, 2, false>(a, sel, tile, si); break;
+    default: break;
     }
+}
+
+int form_np(int form) { return form >= kRowWide1 ? 2 : 1; }
+int form_rows(int form) { return form == kRowSmall2 || form == kRowWide2 ? 2 : 1; }
+
+size_t step_lds(int prec, const RowStep &a)
+{
+    if (a.form == kRowTake) return 0;
+    const int xt = (16 * form_np(a.form) * kWaves) >> a.wc_log, rows = form_rows(a.form) + 2;
+    if (a.cells == 0) {
+        const int wcells = (3 * a.c_in + conv3x3_mfma_vl(prec) - 1) / conv3x3_mfma_vl(prec);
+        return (size_t)rows * xt * (wcells | 1) * 16;
+    }
+    const int cc = std::min(a.cells, kRowCells);
+    return (size_t)rows * (xt + 2) * (cc | 1) * 16 * (a.cells > kRowCells ? 2 : 1);
+}
+
+template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc)
+{
+    size_t lds = 0;
+    int tiles = 0;
+    bool events = false, wide = false;
+    for (int k = 0; k < b.n; ++k) {
+        const RowStep &a = b.st[k];
+        tiles = std::max(tiles, a.tiles);
+        wide = wide || a.form >= kRowWide1;
+        size_t need = step_lds(prec, a);
+        if (a.ev_limit > 0) {
+            events = true;
+            need = ((need + 15) & ~(size_t)15) + event_lds_bytes(form_rows(a.form), (16 * kWaves) >> a.wc_log, 16 << a.wc_log, a.c_in);
+        }
+        lds = std::max(lds, need);
+    }
+    if (b.n < 1 || tiles < 1 || tiles > 65535 || lds > 160 * 1024 - 256) return hipErrorInvalidValue;      // tiles are the grid's y extent
+    const dim3 grid(sel.n, tiles, b.n), block(kThreads);
+    auto go = [&](auto kernel) {
+        static hipError_t prepared = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
+        if (prepared != hipSuccess) return prepared;
+        return launch(kernel, grid, block, lds, lc, b, sel);
+    };
+    if constexpr (T::kEvents)
+        if (events) return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, true, false>);
+    if constexpr (!std::is_same<T, TraitsF32>::value)
+        if (wide) return go(k_conv3x3_mfma_rows<T, false, true>);
+    return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, false, false>);
 }
 
 }  // namespace
 
-// Elements of the event type per 16-byte fragment.
+// Elements of the event type per 16-byte cell.
 int conv3x3_mfma_vl(int prec) { return prec == IDF_PREC_F32 ? 4 : prec == IDF_PREC_BF16 ? 8 : 16; }
 
 bool conv3x3_mfma_eligible(int prec, const Geom &g)
@@ -884,46 +815,67 @@ bool conv3x3_mfma_eligible(int prec, const Geom &g)
     return true;
 }
 
-int conv3x3_mfma_tile(const Geom &g, int n_streams)
+// K-steps (of four cells) per tap row: every chunk of eight cells per position is six, the rest rounds up.
+static int row_ksteps(int prec, const Geom &g)
 {
-    // wide tiles reuse each weight fragment for more positions; narrow ones give more workgroups
-    if (g.c_out <= 32) return g.w_out > 64 ? kMfmaTile128x32 : kMfmaTile32x32;
-    const long wg64 = (long)((g.w_out + 63) / 64) * ((g.c_out + 63) / 64) * n_streams;
-    if (g.w_out <= 32 || (wg64 < 256 && g.w_out % 64 != 0 && g.w_out % 64 <= 32)) return kMfmaTile32x64;
-    return kMfmaTile64x64;
+    const int vl = conv3x3_mfma_vl(prec);
+    if (g.c_in % vl != 0 || g.c_in < vl) return 1;
+    const int cells = g.c_in / vl;
+    return cells / kRowCells * 6 + (3 * (cells % kRowCells) + 3) / 4;
 }
 
-namespace {
-void tile_shape(int tile, int &wm, int &wn)
+// Shape of a step of n_rows output rows for n_streams streams: which tiles a wave takes, how the waves of a
+// workgroup lie, and the numbers that follow from that.
+void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, RowStep &a)
 {
-    wm = tile == kMfmaTile64x64 || tile == kMfmaTile64x32 ? 2 : tile == kMfmaTile128x32 ? 4 : 1;
-    wn = tile == kMfmaTile64x64 || tile == kMfmaTile32x64 ? 2 : 1;
+    const int vl = conv3x3_mfma_vl(prec);
+    a.cells = g.c_in % vl == 0 && g.c_in >= vl ? g.c_in / vl : 0;
+    const int n_ct = g.c_out == 16 ? 1 : 2 * ((g.c_out + 31) / 32);
+    const bool chunks = a.cells > kRowCells;
+    const int pairs = a.n_rows >= 2 ? (a.n_rows + 1) / 2 : 1;
+    // Wide tiles use each weight fragment and each cell twice as often and pay where they still give
+    // every SIMD most of a wave; float32 stays narrow, its matrix instructions being sixteen times longer.
+    bool wide = prec != IDF_PREC_F32 && a.ev_limit == 0 && g.c_out > 16 && (long)n_streams * ((g.w_out + 31) / 32) * (n_ct / 2) * pairs >= 768;
+    auto waves_log = [&](int tiles) { return tiles >= 4 ? 2 : tiles >= 2 ? 1 : 0; };
+    if (wide) {
+        a.wc_log = waves_log(n_ct / 2);
+        // a stretch of at most 32 positions while chunks follow one another (their loads are held in registers),
+        // of at most 64 where a position has eight cells
+        const int xt = 128 >> a.wc_log;
+        if ((chunks && xt > 32) || (a.cells > 4 && xt > 64)) wide = false;
+    }
+    if (!wide) {
+        a.wc_log = waves_log(n_ct);
+        if (chunks && a.wc_log < 1) a.wc_log = 1;
+    }
+    a.form = wide ? (a.n_rows >= 2 ? kRowWide2 : kRowWide1) : (a.n_rows >= 2 ? kRowSmall2 : kRowSmall1);
+    const int mc = a.form >= kRowWide1 ? 2 : 1, xt = (16 * form_np(a.form) * kWaves) >> a.wc_log;
+    auto rcp32 = [](int n) { return n > 1 ? (unsigned)((0x100000000ull + n - 1) / n) : 0u; };
+    auto rcp16 = [](int n) { return (unsigned)((65536 + n - 1) / n); };
+    a.n_xt = (g.w_out + xt - 1) / xt;
+    a.n_cg = (n_ct + (mc << a.wc_log) - 1) / (mc << a.wc_log);
+    a.xt_rcp = rcp32(a.n_xt); a.cg_rcp = rcp32(a.n_cg);
+    a.tiles = (a.n_rows + form_rows(a.form) - 1) / form_rows(a.form) * a.n_xt * a.n_cg;
+    const int cc[2] = {kRowCells, a.cells == 0 ? 1 : (a.cells - 1) % kRowCells + 1};
+    for (int k = 0; k < 2; ++k) {
+        a.nb[k] = ((xt + 2) * cc[k] + 63) / 64;
+        a.nb_rcp[k] = rcp16(a.nb[k]); a.cc_rcp[k] = rcp16(cc[k]);
+    }
 }
-}  // namespace
 
-int conv3x3_mfma_tiles(int tile, int w, int c_out)
-{
-    int wm, wn;
-    tile_shape(tile, wm, wn);
-    return ((w + 32 * wm - 1) / (32 * wm)) * ((c_out + 32 * wn - 1) / (32 * wn));
-}
-
-int conv3x3_mfma_batch_resident(int prec, int tile)
-{
-    int wm, wn;
-    tile_shape(tile, wm, wn);
-    const int per_simd = prec == IDF_PREC_BF16 ? TraitsBf16::kOcc : prec == IDF_PREC_I8 ? TraitsI8::kOcc : TraitsF32::kOcc;
-    return std::max(1, 4 * per_simd / (wm * wn));
-}
-
-// Weights [k_h][k_w][c_in][c_out] -> fragment order [ky][k/VL][c_out_pad][VL] with k = kx*c_in + ci,
-// zero padded to whole K-steps and to a multiple of 64 output channels.
+// Weights [k_h][k_w][c_in][c_out] -> fragment order, zero padded to whole K-steps and channel pairs:
+//   [K-step][block of 32 channels][ky][tile t of 2][lane][16 bytes], lane = 16 g + m holding cell 4 s + g of the
+//   K-step for row m of the tile, which is channel 32 * block + (m / 4) * 8 + t * 4 + m % 4;
+//   16 output channels: [K-step][ky][lane][16 bytes], row m = channel m.
+// K-steps run chunk by chunk (eight cells per position), inside a chunk over the cells kx * (cells) + c; with one to
+// four input channels there is one K-step whose elements are k = kx * c_in + ci.
 size_t conv3x3_mfma_pack(int prec, const Geom &g, const void *w_khkwcico, void *out)
 {
     const int vl = conv3x3_mfma_vl(prec), eb = 16 / vl;
-    const int KT = 3 * g.c_in, steps = (KT + 2 * vl - 1) / (2 * vl), kc = 2 * steps;
+    const int ksteps = row_ksteps(prec, g), n_blk = (g.c_out + 31) / 32;
+    const bool single = g.c_out == 16;
+    const size_t per_step = single ? 3 * 1024 : (size_t)n_blk * 6144, frag_bytes = per_step * ksteps;
     const int cop = (g.c_out + 63) / 64 * 64;
-    const size_t frag_bytes = (size_t)3 * kc * cop * 16;
     // int8: behind the fragments the same weights for the event path, [kx][c_in][cop] words holding the taps ky = 0, 1, 2 of
     // (kx, c_in, c_out) in their three low bytes
     const size_t bytes = frag_bytes + (prec == IDF_PREC_I8 ? (size_t)3 * g.c_in * cop * 4 : 0);
@@ -931,47 +883,48 @@ size_t conv3x3_mfma_pack(int prec, const Geom &g, const void *w_khkwcico, void *
     unsigned char *o = (unsigned char *)out;
     const unsigned char *src = (const unsigned char *)w_khkwcico;
     for (size_t i = 0; i < bytes; ++i) o[i] = 0;
-    if (prec == IDF_PREC_I8)
-        for (int ky = 0; ky < 3; ++ky)
-            for (int kx = 0; kx < 3; ++kx)
-                for (int ci = 0; ci < g.c_in; ++ci)
-                    for (int co = 0; co < g.c_out; ++co)
-                        o[frag_bytes + (((size_t)kx * g.c_in + ci) * cop + co) * 4 + ky] = src[(((size_t)ky * 3 + kx) * g.c_in + ci) * g.c_out + co];
+    const int cells = g.c_in % vl == 0 && g.c_in >= vl ? g.c_in / vl : 0;
     for (int ky = 0; ky < 3; ++ky)
-        for (int k = 0; k < KT; ++k) {
-            const int kx = k / g.c_in, ci = k % g.c_in;
-            for (int co = 0; co < g.c_out; ++co) {
-                const size_t s_idx = (((size_t)ky * 3 + kx) * g.c_in + ci) * g.c_out + co;
-                const size_t d_idx = (((size_t)ky * kc + k / vl) * cop + co) * vl + k % vl;
-                for (int b = 0; b < eb; ++b) o[d_idx * eb + b] = src[s_idx * eb + b];
+        for (int kx = 0; kx < 3; ++kx)
+            for (int ci = 0; ci < g.c_in; ++ci) {
+                int step, grp, elem;
+                if (cells == 0) {
+                    const int k = kx * g.c_in + ci;
+                    step = 0; grp = k / vl; elem = k % vl;
+                } else {
+                    const int cell = ci / vl, ch = cell / kRowCells, cc = std::min(kRowCells, cells - ch * kRowCells);
+                    const int q = kx * cc + cell % kRowCells;
+                    step = ch * 6 + q / 4; grp = q % 4; elem = ci % vl;
+                }
+                for (int co = 0; co < g.c_out; ++co) {
+                    const size_t s_idx = (((size_t)ky * 3 + kx) * g.c_in + ci) * g.c_out + co;
+                    size_t d;
+                    if (single) {
+                        d = step * per_step + (size_t)ky * 1024 + (size_t)(grp * 16 + co) * 16;
+                    } else {
+                        const int in = co % 32, t = in % 8 / 4, m = in / 8 * 4 + in % 4;
+                        d = step * per_step + (size_t)(co / 32) * 6144 + (size_t)(ky * 2 + t) * 1024 + (size_t)(grp * 16 + m) * 16;
+                    }
+                    for (int b = 0; b < eb; ++b) o[d + (size_t)elem * eb + b] = src[s_idx * eb + b];
+                    if (prec == IDF_PREC_I8) o[frag_bytes + (((size_t)kx * g.c_in + ci) * cop + co) * 4 + ky] = src[s_idx];
+                }
             }
-        }
     return bytes;
 }
 
 size_t conv3x3_mfma_event_weights(int prec, const Geom &g)
 {
     if (prec != IDF_PREC_I8) return 0;
-    const int vl = conv3x3_mfma_vl(prec);
-    const int KT = 3 * g.c_in, steps = (KT + 2 * vl - 1) / (2 * vl);
-    return (size_t)3 * 2 * steps * ((g.c_out + 63) / 64 * 64) * 16;
+    return (g.c_out == 16 ? 3 * 1024 : (size_t)((g.c_out + 31) / 32) * 6144) * row_ksteps(prec, g);
 }
 
-int conv3x3_mfma_event_cap() { return kEvCap; }
+int conv3x3_mfma_event_cap() { return kEvCap / 2; }
 
-hipError_t launch_conv3x3_mfma_batch(int prec, const MfmaBatch &b, const StreamSel &sel, const LaunchCtx &lc)
+hipError_t launch_conv3x3_mfma_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc)
 {
-    if (prec == IDF_PREC_F32) return launch_batch<TraitsF32>(b, sel, lc);
-    if (prec == IDF_PREC_BF16) return launch_batch<TraitsBf16>(b, sel, lc);
-    if (prec == IDF_PREC_I8) return launch_batch<TraitsI8>(b, sel, lc);
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_conv3x3_mfma(int prec, const MfmaStep &a, const StreamSel &sel, const LaunchCtx &lc)
-{
-    if (prec == IDF_PREC_F32) return launch_prec<TraitsF32>(a, sel, lc);
-    if (prec == IDF_PREC_BF16) return launch_prec<TraitsBf16>(a, sel, lc);
-    if (prec == IDF_PREC_I8) return launch_prec<TraitsI8>(a, sel, lc);
+    if (prec == IDF_PREC_F32) return launch_rows<TraitsF32>(prec, b, sel, lc);
+    if (prec == IDF_PREC_BF16) return launch_rows<TraitsBf16>(prec, b, sel, lc);
+    if (prec == IDF_PREC_I8) return launch_rows<TraitsI8>(prec, b, sel, lc);
     return hipErrorInvalidValue;
 }
 

@@ -208,7 +208,9 @@ __global__ void __launch_bounds__(kGenThreads) k_conv_generic(const ConvStep a, 
                 if (slot >= a.out_cap) slot -= a.out_cap;
                 ((out_t *)a.dst)[(int64_t)stream * a.dst_stream_stride + slot * row_out + xo * g.c_out + co] = (out_t)h;
             } else {
-                ((ev_t *)a.dst)[(int64_t)stream * a.dst_stream_stride + (dst_rel0 + oi) * row_out + xo * g.c_out + co] = T::to_ev(h);
+                int64_t slot = dst_rel0 + oi;
+                if (a.dst_ring > 0) { slot += a.dst_slot0; if (slot >= a.dst_ring) slot -= a.dst_ring; }
+                ((ev_t *)a.dst)[(int64_t)stream * a.dst_stream_stride + slot * row_out + xo * g.c_out + co] = T::to_ev(h);
             }
         } else {
             ring[((slot_lo + oi) % a.ring_rows) * row_out + xo * g.c_out + co] = c;
@@ -296,7 +298,9 @@ __global__ void __launch_bounds__(kGenThreads) k_pool_generic(const PoolStep a, 
             if (slot >= a.out_cap) slot -= a.out_cap;
             ((out_t *)a.dst)[(int64_t)stream * a.dst_stream_stride + slot * row_out + ox * C + c] = (out_t)m;
         } else {
-            ((ev_t *)a.dst)[(int64_t)stream * a.dst_stream_stride + (dst_rel0 + oi) * row_out + ox * C + c] = T::to_ev(m);
+            int64_t slot = dst_rel0 + oi;
+            if (a.dst_ring > 0) { slot += a.dst_slot0; if (slot >= a.dst_ring) slot -= a.dst_ring; }
+            ((ev_t *)a.dst)[(int64_t)stream * a.dst_stream_stride + slot * row_out + ox * C + c] = T::to_ev(m);
         }
     }
     // The thread that consumed the old held values of its window is the one that replaces them.
