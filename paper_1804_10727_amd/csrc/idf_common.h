@@ -225,7 +225,7 @@ constexpr int kRowLaunchRows = 16;     // arriving rows one launch takes at most
 
 enum { kRowTake = 0,                   // no convolution: rows of the caller go into the ring and are counted
        kRowSmall1, kRowSmall2,         // a wave does 16 positions x 16 channels of 1 / 2 output rows
-       kRowWide1, kRowWide2 };         // a wave does 32 positions x 32 channels of 1 / 2 output rows
+       kRowWide2 };                    // a wave does 32 positions x 32 channels of 2 output rows
 
 struct RowStep {
     int form;                          // kRow*

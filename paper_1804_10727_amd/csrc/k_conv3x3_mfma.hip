@@ -229,7 +229,6 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     const int ct0 = ((cg << a.wc_log) + wc) * MC;  // first channel tile of this wave
     const int xw = x0 + wp * 16 * NP;              // first position of this wave
     const bool active = ct0 < (single ? 1 : 2 * n_blk) && xw < W;
-    const int np_on = (W - xw + 15) >> 4;          // position tiles of this wave that exist
     // this lane's channels: co0 .. co0 + 4 * MC - 1
     const int co0 = single ? g * 4 : (ct0 >> 1) * 32 + g * 8 + (MC == 1 ? (ct0 & 1) * 4 : 0);
     const bool co_ok = co0 < C_out;
@@ -254,10 +253,10 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 
     i32x4 tv[kLoads];
     // one chunk's cells in blocks of 64 per input row, dealt to the waves: block `item` of the chunk -> (row, cells)
-    auto chunk_cell = [&](int item, int ch, int cc, int &r, int &p, int &c) IDF_INLINE {
+    auto chunk_cell = [&](int item, int ch, int cc, int ln, int &r, int &p, int &c) IDF_INLINE {
         const int last = ch + 1 < n_chunks ? 0 : 1;
         r = (int)(((unsigned)item * a.nb_rcp[last]) >> 16);
-        const int i = (item - r * a.nb[last]) * 64 + lane;
+        const int i = (item - r * a.nb[last]) * 64 + ln;
         p = (int)(((unsigned)i * a.cc_rcp[last]) >> 16);
         c = i - p * cc;
     };
@@ -268,7 +267,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             const int item = (it0 + b) * kWaves + wave;
             if (item >= items) break;
             int r, p, c;
-            chunk_cell(item, ch, cc, r, p, c);
+            chunk_cell(item, ch, cc, lane, r, p, c);
             if (!row_there(r)) continue;
             int x = x0 - 1 + p;
             x = x < 0 ? 0 : (x >= W ? W - 1 : x);
@@ -278,16 +277,17 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     uint32_t my_occ = 0;
     auto chunk_store = [&](int ch, int it0, unsigned char *buf) IDF_INLINE {
         const int cc = cells_of(ch), items = R * a.nb[ch + 1 < n_chunks ? 0 : 1], stride = stride_of(cc);
+        int ln = lane;                             // (places are worked out again rather than held in registers from the load on:
+        asm volatile("" : "+v"(ln));               //  the empty statement hides that this is the same value)
 #pragma unroll
         for (int b = 0; b < kLoads; ++b) {
             const int item = (it0 + b) * kWaves + wave;
             if (item >= items) break;
             int r, p, c;
-            chunk_cell(item, ch, cc, r, p, c);
-            if (!row_there(r)) continue;
+            chunk_cell(item, ch, cc, ln, r, p, c);
             const int x = x0 - 1 + p;
             i32x4 v = tv[b];
-            if (x < 0 || x >= W) v = i32x4{0, 0, 0, 0};
+            if (x < 0 || x >= W || !row_there(r)) v = i32x4{0, 0, 0, 0};
             if (p < npos) *reinterpret_cast<i32x4 *>(buf + (r * npos + p) * stride + c * 16) = v;
             // which cells of the row hold an event anywhere in the stretch
             unsigned long long bal = __ballot(p < npos && T::or_of(v) != 0);
@@ -382,7 +382,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
                 for (int np = 0; np < NP; ++np) acc[j][mc][np] = start[mc];
     }
     lds_barrier();
-    uint32_t n_mfma = 0;                           // tiles of 16 x 16 x one K-step issued
+    uint32_t n_mfma = 0, n_ksteps = 0;             // tiles of 16 x 16 x one K-step issued; K-steps issued
 
     // ---- sparse stretches: the event-list path ---------------------------------------------------------
     // Where a row's stretch (halo included) holds few events they are packed into a list -- counts per
@@ -461,7 +461,12 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
                     }
                 }
                 lds_barrier();
+                // a row that has been delivered reads as zero from here on
+                if (!small_c && ((rows_done >> r) & 1u))
+                    for (int i = tid; i < npos * cc; i += kThreads)
+                        *reinterpret_cast<i32x4 *>(smem + (r * npos + i / cc) * stride + i % cc * 16) = i32x4{0, 0, 0, 0};
             }
+            lds_barrier();
             if (a.issued && visits)
                 atomicAdd(a.issued + (int64_t)stream * a.n_layers + a.layer, visits * (unsigned long long)nc);
             if (active) {
@@ -480,85 +485,63 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 
     // ---- contraction -------------------------------------------------------------------------------------
     // All matrix instructions of input row r's fragment of one K-step: tap row ky = r - j of output row j.
-    auto deliver = [&](const i32x4 (&w)[NW], const i32x4 (&x)[NP], int r, int n_on) IDF_INLINE {
+    auto deliver = [&](const i32x4 (&w)[NW], const i32x4 (&x)[NP], int r) IDF_INLINE {
 #pragma unroll
-        for (int j = 0; j < NR; ++j) {
-            const int ky = r - j;
-            if (ky < 0 || ky > 2) continue;
+        for (int e = 0; e < T::kInst; ++e)
 #pragma unroll
-            for (int e = 0; e < T::kInst; ++e)
+            for (int j = 0; j < NR; ++j) {
+                const int ky = r - j;
+                if (ky < 0 || ky > 2) continue;
 #pragma unroll
                 for (int mc = 0; mc < MC; ++mc)
 #pragma unroll
-                    for (int np = 0; np < NP; ++np)
-                        if (np < n_on) acc[j][mc][np] = T::mfma(w[ky * MC + mc], x[np], acc[j][mc][np], e);
-        }
-    };
-    auto taps_used = [&](int r) IDF_INLINE { int n = 0; for (int j = 0; j < NR; ++j) n += r - j >= 0 && r - j <= 2 && j < rows; return n; };
-
-    // One chunk of CC cells per position (CC = 0: any number, known at run time only).  wa holds the weights
-    // of its first K-step on entry and those of the next chunk's first on exit.
-    auto compute = [&](auto cc_tag, auto check_tag, const unsigned char *buf, int cc_rt, uint32_t bits) IDF_INLINE {
-        constexpr int CC = decltype(cc_tag)::value;
-        constexpr bool CHECK = decltype(check_tag)::value;
-        const int cc = CC ? CC : cc_rt, stride = stride_of(cc);
-        const int S = (3 * cc + 3) >> 2;
-        const uint32_t pos = (uint32_t)((wp * 16 * NP + m) * stride);
-        const uint32_t row_pitch = (uint32_t)(npos * stride);
-        auto one = [&](int s, const i32x4 (&w)[NW]) IDF_INLINE {
-            // this lane's cell of the K-step: q = 4 s + g of the 3 * cc cells of its window (past the end the last one
-            // again: the weights there are zero)
-            uint32_t off;
-            if (CC == 8) off = pos + (uint32_t)((s >> 1) * stride + (s & 1) * 64 + g * 16);
-            else if (CC == 4) off = pos + (uint32_t)(s * stride + g * 16);
-            else {
-                int q = 4 * s + g;
-                q = q < 3 * cc ? q : 3 * cc - 1;
-                const int kx = CC == 2 ? q >> 1 : CC == 1 ? q : (q >= cc) + (q >= 2 * cc);
-                off = pos + (uint32_t)(kx * stride + (q - kx * cc) * 16);
+                    for (int np = 0; np < NP; ++np) acc[j][mc][np] = T::mfma(w[ky * MC + mc], x[np], acc[j][mc][np], e);
             }
-            const uint32_t part = CC == 8 ? ((s & 1) ? 0xf0u : 0x0fu) : 0xffu;
+    };
+
+    // One K-step with its weights in w: row by row, a row's cells asked for while the row before is multiplied.
+    // off: this lane's cell of the step in the first input row.
+    auto kstep = [&](const i32x4 (&w)[NW], const unsigned char *buf, uint32_t off, uint32_t row_pitch, int np_pitch) IDF_INLINE {
+        i32x4 x[2][NP];
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                if (CHECK && !((bits >> (8 * r)) & part)) continue;          // no event in these cells of the row: nothing to do
-                i32x4 x[NP];
+        for (int np = 0; np < NP; ++np) x[0][np] = *reinterpret_cast<const i32x4 *>(buf + off + np * np_pitch);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r + 1 < R) {
 #pragma unroll
                 for (int np = 0; np < NP; ++np)
-                    if (!CHECK || np < np_on) x[np] = *reinterpret_cast<const i32x4 *>(buf + off + r * row_pitch + np * 16 * stride);
-                deliver(w, x, r, CHECK ? np_on : NP);
-                n_mfma += (uint32_t)(taps_used(r) * MC * (CHECK && np_on < NP ? np_on : NP));
+                    x[(r + 1) & 1][np] = *reinterpret_cast<const i32x4 *>(buf + off + (r + 1) * row_pitch + np * np_pitch);
             }
+            deliver(w, x[r & 1], r);
+        }
+        ++n_ksteps;
+    };
+    // The K-steps of one chunk, `live` saying which of them hold events (bit per K-step).  wa holds the weights of the
+    // first one on entry and, if another chunk follows (this one then has an even number), those of its first one on exit.
+    auto chunk = [&](const unsigned char *buf, int cc, uint32_t live) IDF_INLINE {
+        const int stride = stride_of(cc), np_pitch = 16 * stride, S = (3 * cc + 3) >> 2;
+        const uint32_t row_pitch = (uint32_t)(npos * stride);
+        const uint32_t pos = (uint32_t)((wp * 16 * NP + m) * stride);
+        auto at = [&](int st) IDF_INLINE {
+            // this lane's cell: number 4 st + g of the 3 * cc cells of its window (past the end the last one again:
+            // the weights there are zero)
+            int q = 4 * st + g;
+            q = q < 3 * cc ? q : 3 * cc - 1;
+            const int kx = (q >= cc) + (q >= 2 * cc);
+            return pos + (uint32_t)(kx * stride + (q - kx * cc) * 16);
         };
-        if constexpr (CC == 8) {
-#pragma unroll
-            for (int s = 0; s < 6; s += 2) {
-                fetch_w(wb); advance_w(1);
-                one(s, wa);
-                fetch_w(wa); advance_w(1);
-                one(s + 1, wb);
-            }
-        } else if constexpr (CC == 2) {
+#pragma unroll 1
+        for (int st = 0; st < S; st += 2) {
             fetch_w(wb); advance_w(1);
-            one(0, wa);
+            if (live & 1u) kstep(wa, buf, at(st), row_pitch, np_pitch);
+            __builtin_amdgcn_sched_barrier(0);     // K-steps stay apart: nothing of a later one is held in registers early
             fetch_w(wa); advance_w(1);
-            one(1, wb);
-        } else if constexpr (CC == 4 || CC == 1) {
-            // an odd number of K-steps: only ever the layer's last chunk, nothing follows
-            if (CC == 1) { one(0, wa); return; }
-            fetch_w(wb); advance_w(1);
-            one(0, wa);
-            fetch_w(wa); advance_w(1);
-            one(1, wb);
-            one(2, wa);
-        } else {
-            for (int s = 0; s < S; ++s) {
-                fetch_w(wb); advance_w(1);
-                one(s, wa);
-#pragma unroll
-                for (int q = 0; q < NW; ++q) wa[q] = wb[q];
-            }
+            if (live & 2u) kstep(wb, buf, at(st + 1), row_pitch, np_pitch);
+            __builtin_amdgcn_sched_barrier(0);
+            live >>= 2;
         }
     };
+
     if (small_c) {
         // one K-step per tap row, always visited
         if (active) {
@@ -570,13 +553,13 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 #pragma unroll
                 for (int np = 0; np < NP; ++np)
                     x[np] = *reinterpret_cast<const i32x4 *>(smem + (r * XT + wp * 16 * NP + np * 16 + m) * wstride + (g < wcells ? g : wcells - 1) * 16);
-                deliver(wa, x, r, np_on);
-                n_mfma += (uint32_t)(taps_used(r) * MC * (np_on < NP ? np_on : NP));
+                deliver(wa, x, r);
+                n_mfma += (uint32_t)(((r <= 2) + (NR == 2 && r >= 1 && rows == 2)) * MC * NP);
             }
         }
     } else {
         const int buf_bytes = R * npos * stride_of(n_chunks > 1 ? kRowCells : a.cells);
-        constexpr uint32_t kFull = R == 4 ? 0x11111111u : 0x00111111u, kFullRow = R == 4 ? 0x01010101u : 0x00010101u;
+#pragma unroll 1
         for (int ch = 0; ch < n_chunks; ++ch) {
             const unsigned char *buf = smem + (ch & 1) * buf_bytes;
             const int cc = cells_of(ch);
@@ -590,23 +573,10 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             }
             if (ch + 1 < n_chunks) chunk_load(ch + 1, 0);
             if (active) {
-                const uint32_t nib = (bits | bits >> 1 | bits >> 2 | bits >> 3) & 0x11111111u, byt = (nib | nib >> 4) & 0x01010101u;
-                const bool all = np_on >= NP && (cc == 8 ? nib == kFull : byt == kFullRow);
-                if (bits == 0) {                    // nothing but zeros: no weights either
-                    advance_w(((3 * cc + 3) >> 2) - 1);
-                    if (ch + 1 < n_chunks) fetch_w(wa);
-                    advance_w(1);
-                } else if (cc == 8) {
-                    if (all) compute(std::integral_constant<int, 8>{}, std::false_type{}, buf, cc, bits); else compute(std::integral_constant<int, 8>{}, std::true_type{}, buf, cc, bits);
-                } else if (cc == 4) {
-                    if (all) compute(std::integral_constant<int, 4>{}, std::false_type{}, buf, cc, bits); else compute(std::integral_constant<int, 4>{}, std::true_type{}, buf, cc, bits);
-                } else if (cc == 2) {
-                    compute(std::integral_constant<int, 2>{}, std::true_type{}, buf, cc, bits);
-                } else if (cc == 1) {
-                    compute(std::integral_constant<int, 1>{}, std::true_type{}, buf, cc, bits);
-                } else {
-                    compute(std::integral_constant<int, 0>{}, std::true_type{}, buf, cc, bits);
-                }
+                // K-steps with events: of a full chunk the even ones take cells 0-3 of a tap column, the odd ones cells 4-7
+                uint32_t live = bits ? (1u << ((3 * cc + 3) >> 2)) - 1u : 0u;
+                if (cc == kRowCells) live &= ((bits & 0x0f0f0f0fu) ? 0x15u : 0u) | ((bits & 0xf0f0f0f0u) ? 0x2au : 0u);
+                if (live || ch + 1 < n_chunks) chunk(buf, cc, live);
             }
             if (ch + 1 < n_chunks) {
                 my_occ = 0;
@@ -725,6 +695,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         }
     }
     // what the matrix instructions of this wave multiplied, zeros inside a live K-step included
+    n_mfma += n_ksteps * (uint32_t)(3 * rows * MC * NP);
     if (a.issued && lane == 0 && n_mfma)
         atomicAdd(a.issued + (int64_t)stream * a.n_layers + a.layer, (unsigned long long)n_mfma * (256ull * 4 * VL));
 }
@@ -747,14 +718,13 @@ __global__ void __launch_bounds__(kThreads, 2) k_conv3x3_mfma_rows(const RowBatc
     case kRowTake: take_row<T>(a, sel, tile, si); break;
     case kRowSmall1: conv_rows<T, 1, 1, 1, EV>(a, sel, tile, si); break;
     case kRowSmall2: conv_rows<T, 1, 1, 2, EV>(a, sel, tile, si); break;
-    case kRowWide1: if constexpr (WIDE) conv_rows<T, 2, 2, 1, false>(a, sel, tile, si); break;
     case kRowWide2: if constexpr (WIDE) conv_rows<T, 2, 2, 2, false>(a, sel, tile, si); break;
     default: break;
     }
 }
 
-int form_np(int form) { return form >= kRowWide1 ? 2 : 1; }
-int form_rows(int form) { return form == kRowSmall2 || form == kRowWide2 ? 2 : 1; }
+int form_np(int form) { return form == kRowWide2 ? 2 : 1; }
+int form_rows(int form) { return form == kRowSmall1 ? 1 : 2; }
 
 size_t step_lds(int prec, const RowStep &a)
 {
@@ -776,7 +746,7 @@ template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const Str
     for (int k = 0; k < b.n; ++k) {
         const RowStep &a = b.st[k];
         tiles = std::max(tiles, a.tiles);
-        wide = wide || a.form >= kRowWide1;
+        wide = wide || a.form == kRowWide2;
         size_t need = step_lds(prec, a);
         if (a.ev_limit > 0) {
             events = true;
@@ -835,7 +805,7 @@ void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, RowStep &a)
     const int pairs = a.n_rows >= 2 ? (a.n_rows + 1) / 2 : 1;
     // Wide tiles use each weight fragment and each cell twice as often and pay where they still give
     // every SIMD most of a wave; float32 stays narrow, its matrix instructions being sixteen times longer.
-    bool wide = prec != IDF_PREC_F32 && a.ev_limit == 0 && g.c_out > 16 && (long)n_streams * ((g.w_out + 31) / 32) * (n_ct / 2) * pairs >= 768;
+    bool wide = prec != IDF_PREC_F32 && a.ev_limit == 0 && a.n_rows >= 2 && g.c_out > 16 && (long)n_streams * ((g.w_out + 31) / 32) * (n_ct / 2) * pairs >= 768;
     auto waves_log = [&](int tiles) { return tiles >= 4 ? 2 : tiles >= 2 ? 1 : 0; };
     if (wide) {
         a.wc_log = waves_log(n_ct / 2);
@@ -848,8 +818,8 @@ void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, RowStep &a)
         a.wc_log = waves_log(n_ct);
         if (chunks && a.wc_log < 1) a.wc_log = 1;
     }
-    a.form = wide ? (a.n_rows >= 2 ? kRowWide2 : kRowWide1) : (a.n_rows >= 2 ? kRowSmall2 : kRowSmall1);
-    const int mc = a.form >= kRowWide1 ? 2 : 1, xt = (16 * form_np(a.form) * kWaves) >> a.wc_log;
+    a.form = wide ? kRowWide2 : a.n_rows >= 2 ? kRowSmall2 : kRowSmall1;
+    const int mc = a.form == kRowWide2 ? 2 : 1, xt = (16 * form_np(a.form) * kWaves) >> a.wc_log;
     auto rcp32 = [](int n) { return n > 1 ? (unsigned)((0x100000000ull + n - 1) / n) : 0u; };
     auto rcp16 = [](int n) { return (unsigned)((65536 + n - 1) / n); };
     a.n_xt = (g.w_out + xt - 1) / xt;
