@@ -225,7 +225,7 @@ constexpr int kRowLaunchRows = 16;     // arriving rows one launch takes at most
 
 enum { kRowTake = 0,                   // no convolution: rows of the caller go into the ring and are counted
        kRowSmall1, kRowSmall2,         // a wave does 16 positions x 16 channels of 1 / 2 output rows
-       kRowWide2 };                    // a wave does 32 positions x 32 channels of 2 output rows
+       kRowWide2, kRowWider2 };        // a wave does 32 / 64 positions x 32 channels of 2 output rows
 
 struct RowStep {
     int form;                          // kRow*
@@ -243,7 +243,8 @@ struct RowStep {
     int n_xt, n_cg;                    // position tiles of a row, channel groups
     unsigned xt_rcp, cg_rcp;           // ceil(2^32 / n) of those (0 for one)
     int nb[2];                         // blocks of 64 cells per row of the stretch in a full / in the last chunk
-    unsigned nb_rcp[2], cc_rcp[2];     // ceil(65536 / nb), ceil(65536 / cells per position) of those chunks
+    int row_pos[2];                    // positions those blocks cover: what a row of the stretch takes in LDS
+    unsigned cc_rcp[2];                // ceil(65536 / cells per position) of those chunks
     int act, shr, clamp_hi;
     int pool;                          // 1: 2x2 max-pool behind the layer
     int pool_from;                     // output rows before this one have been counted as the pool's events already

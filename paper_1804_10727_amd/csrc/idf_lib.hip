@@ -871,13 +871,23 @@ bool row_plan(idf_streams *s, RowProg &p, int n_streams, const void *dev_rows, i
     b.n = 0;
     const bool part = s->part.on && n_new > 0;
     if (n_new > 0) b.n = 1;                        // place for the step that takes them
+    int busy = 0;                                  // first unit with rows it can form (without one: past the last)
+    for (busy = 0; busy < nu; ++busy) {
+        const RowUnit &u = s->units[busy];
+        const Geom &g = net.g[u.l];
+        const int64_t end = (p.out[busy] / g.h_out + 1) * g.h_out;
+        int64_t n = std::min(rows_ready(g, p.in[busy]), end) - p.out[busy];
+        if (p.out[busy] + n < end && u.pool) n &= ~(int64_t)1;
+        if (n > 0) break;
+    }
     for (int k = nu - 1; k >= 0; --k) {            // deepest first: its workgroups run longest
         const RowUnit &u = s->units[k];
         const Geom &g = net.g[u.l];
         const int64_t have = p.in[k] + (k == 0 && !part ? n_new : 0);
         const int64_t o = p.out[k], sample_end = (o / g.h_out + 1) * g.h_out;
         int64_t n = std::min(rows_ready(g, have), sample_end) - o;
-        if (o + n < sample_end && (u.pool || !flush)) n &= ~(int64_t)1;
+        // (a single row goes alone only when no unit before this one has anything left that could complete the pair)
+        if (o + n < sample_end && (u.pool || !flush || k > busy)) n &= ~(int64_t)1;
         if (u.next >= 0) {                         // room in the ring of the unit behind (as it stands before the launch)
             const RowUnit &v = s->units[u.next];
             const int64_t room = v.ring_rows - (p.in[u.next] - first_needed(net.g[v.l], p.out[u.next]));

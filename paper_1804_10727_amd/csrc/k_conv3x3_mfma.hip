@@ -196,7 +196,6 @@ template <class T> __device__ __forceinline__ void take_row(ArgStep &a, const St
     }
 }
 
-constexpr int kLoads = 5;                        // cells of a chunk each lane has in flight
 constexpr int kEvCap = 512;                      // events (stretch and halo) of a row the event path takes at most: 256 per 32 positions
 // LDS of the event path behind the stretch: offsets and counts per position, the packed event list, the
 // sums it hands to the accumulators, and the tile's share of the layer's weights.
@@ -210,8 +209,9 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     constexpr int VL = T::VL, EB = T::EB;
     constexpr int R = NR + 2;                      // input rows
     constexpr int NW = 3 * MC;                     // weight fragments of a K-step
+    constexpr int kLoads = NP == 4 ? 9 : 5;        // cells of a chunk each lane has in flight
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    __shared__ uint32_t occ[2][kWaves];            // per chunk parity and wave: for each input row a byte, bit c: cell c holds an event somewhere
+    __shared__ uint32_t occ[2][kWaves];            // per chunk parity and wave: a byte for the wave's input row, bit c: cell c holds an event somewhere
 
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     const int m = lane & 15, g = lane >> 4;        // position within a tile; group of channels / of k
@@ -234,76 +234,80 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     const bool co_ok = co0 < C_out;
     const bool small_c = a.cells == 0;
 
-    // ---- input rows ---------------------------------------------------------------------------------
+    // ---- input rows: wave r of the workgroup brings in input row r ------------------------------------
     auto row_there = [&](int r) IDF_INLINE { const int yi = y - 1 + r; return yi >= 0 && yi < H && r < rows + 2; };
-    auto row_ptr = [&](int r) IDF_INLINE -> const unsigned char * {
-        const int yi = y - 1 + r;
-        if (yi >= a.y_new) return (const unsigned char *)a.in_new + ((int64_t)(sel.pos0 + si) * a.new_stride + (int64_t)(yi - a.y_new) * W * C_in) * EB;
-        int slot = a.slot0 + rg * NR + r;
-        if (slot >= a.ring_rows) slot -= a.ring_rows;
-        return (const unsigned char *)a.in_ring + ((int64_t)stream * a.in_stride + (int64_t)slot * W * C_in) * EB;
-    };
+    const bool there = wave < R && row_there(wave);
+    const unsigned char *my_row = nullptr;         // the same in every lane
+    if (there) {
+        const int yi = y - 1 + wave;
+        if (yi >= a.y_new) {
+            my_row = (const unsigned char *)a.in_new + ((int64_t)(sel.pos0 + si) * a.new_stride + (int64_t)(yi - a.y_new) * W * C_in) * EB;
+        } else {
+            int slot = a.slot0 + rg * NR + wave;
+            if (slot >= a.ring_rows) slot -= a.ring_rows;
+            my_row = (const unsigned char *)a.in_ring + ((int64_t)stream * a.in_stride + (int64_t)slot * W * C_in) * EB;
+        }
+    }
     const int n_chunks = small_c ? 1 : (a.cells + kRowCells - 1) / kRowCells;
-    const int npos = XT + 2;
     // few channels: the stretch is kept as the windows the positions see, [row][position][3 * C_in values, padded to cells]
     const int wcells = small_c ? (3 * C_in + VL - 1) / VL : 0;
     const int wstride = (wcells | 1) * 16;
     auto cells_of = [&](int ch) IDF_INLINE { return ch + 1 < n_chunks ? kRowCells : a.cells - ch * kRowCells; };
     auto stride_of = [&](int cc) IDF_INLINE { return (cc | 1) * 16; };          // bytes per position: an odd number of 16-byte cells, no bank conflicts
+    // A row of the stretch in LDS holds what whole blocks of 64 cells bring, a few positions more than needed: no lane has to sit out
+    auto pitch_of = [&](int ch) IDF_INLINE { return ch + 1 < n_chunks ? a.row_pos[0] : a.row_pos[1]; };       // positions
+    const bool edge = x0 == 0 || x0 + XT >= W;
 
     i32x4 tv[kLoads];
-    // one chunk's cells in blocks of 64 per input row, dealt to the waves: block `item` of the chunk -> (row, cells)
-    auto chunk_cell = [&](int item, int ch, int cc, int ln, int &r, int &p, int &c) IDF_INLINE {
-        const int last = ch + 1 < n_chunks ? 0 : 1;
-        r = (int)(((unsigned)item * a.nb_rcp[last]) >> 16);
-        const int i = (item - r * a.nb[last]) * 64 + ln;
-        p = (int)(((unsigned)i * a.cc_rcp[last]) >> 16);
+    auto cell_of = [&](int i, int ch, int cc, int &p, int &c) IDF_INLINE {
+        p = (int)(((unsigned)i * a.cc_rcp[ch + 1 < n_chunks ? 0 : 1]) >> 16);
         c = i - p * cc;
     };
-    auto chunk_load = [&](int ch, int it0) IDF_INLINE {
-        const int cc = cells_of(ch), items = R * a.nb[ch + 1 < n_chunks ? 0 : 1];
+    auto chunk_load = [&](int ch, int b0) IDF_INLINE {
+        if (!there) return;
+        const int cc = cells_of(ch), nb = a.nb[ch + 1 < n_chunks ? 0 : 1], pos_bytes = C_in * EB;
+        const unsigned char *base = my_row + ch * (kRowCells * 16);
+        int p, c;
+        cell_of(b0 * 64 + lane, ch, cc, p, c);
 #pragma unroll
         for (int b = 0; b < kLoads; ++b) {
-            const int item = (it0 + b) * kWaves + wave;
-            if (item >= items) break;
-            int r, p, c;
-            chunk_cell(item, ch, cc, lane, r, p, c);
-            if (!row_there(r)) continue;
+            if (b0 + b >= nb) break;
             int x = x0 - 1 + p;
             x = x < 0 ? 0 : (x >= W ? W - 1 : x);
-            tv[b] = *at4(reinterpret_cast<const i32x4 *>(row_ptr(r)), (uint32_t)((x * C_in + (ch * kRowCells + c) * VL) * EB));
+            tv[b] = *at4(reinterpret_cast<const i32x4 *>(base), (uint32_t)(x * pos_bytes + c * 16));
+            if (64 % cc == 0) p += 64 / cc; else cell_of((b0 + b + 1) * 64 + lane, ch, cc, p, c);
         }
     };
-    uint32_t my_occ = 0;
-    auto chunk_store = [&](int ch, int it0, unsigned char *buf) IDF_INLINE {
-        const int cc = cells_of(ch), items = R * a.nb[ch + 1 < n_chunks ? 0 : 1], stride = stride_of(cc);
+    int my_or = 0;                                 // all values of this lane's cells, or-ed
+    auto chunk_store = [&](int ch, int b0, unsigned char *buf) IDF_INLINE {
+        if (wave >= R) return;
+        const int cc = cells_of(ch), nb = a.nb[ch + 1 < n_chunks ? 0 : 1], stride = stride_of(cc);
+        unsigned char *row = buf + wave * pitch_of(ch) * stride;
         int ln = lane;                             // (places are worked out again rather than held in registers from the load on:
         asm volatile("" : "+v"(ln));               //  the empty statement hides that this is the same value)
+        int p, c;
+        cell_of(b0 * 64 + ln, ch, cc, p, c);
 #pragma unroll
         for (int b = 0; b < kLoads; ++b) {
-            const int item = (it0 + b) * kWaves + wave;
-            if (item >= items) break;
-            int r, p, c;
-            chunk_cell(item, ch, cc, ln, r, p, c);
-            const int x = x0 - 1 + p;
-            i32x4 v = tv[b];
-            if (x < 0 || x >= W || !row_there(r)) v = i32x4{0, 0, 0, 0};
-            if (p < npos) *reinterpret_cast<i32x4 *>(buf + (r * npos + p) * stride + c * 16) = v;
-            // which cells of the row hold an event anywhere in the stretch
-            unsigned long long bal = __ballot(p < npos && T::or_of(v) != 0);
-            uint32_t bits = (uint32_t)(bal | bal >> 32);
-            if (cc == 8 || cc == 4 || cc == 2 || cc == 1) {
-                bits |= bits >> 16;
-                bits |= bits >> 8;
-                if (cc <= 4) bits |= bits >> 4;
-                if (cc <= 2) bits |= bits >> 2;
-                if (cc <= 1) bits |= bits >> 1;
-                bits &= (1u << cc) - 1u;
-            } else {
-                bits = bits ? 0xffu : 0u;
+            if (b0 + b >= nb) break;
+            i32x4 v = there ? tv[b] : i32x4{0, 0, 0, 0};
+            if (edge) {
+                const int x = x0 - 1 + p;
+                if (x < 0 || x >= W) v = i32x4{0, 0, 0, 0};
             }
-            my_occ |= bits << (8 * r);
+            *reinterpret_cast<i32x4 *>(row + p * stride + c * 16) = v;
+            my_or |= T::or_of(v);
+            if (64 % cc == 0) p += 64 / cc; else cell_of((b0 + b + 1) * 64 + ln, ch, cc, p, c);
         }
+    };
+    // what chunk ch holds of this wave's row: bit c set when cell c holds an event somewhere in the stretch (fewer than eight
+    // cells: all bits or none)
+    auto occupied = [&](int cc) IDF_INLINE {
+        const unsigned long long bal = __ballot(my_or != 0);
+        uint32_t bits = (uint32_t)(bal | bal >> 32);
+        bits |= bits >> 16;
+        bits |= bits >> 8;
+        return wave < R ? (cc == kRowCells ? bits & 0xffu : bits ? 0xffu : 0u) << (8 * wave) : 0u;
     };
 
     // ---- weights -------------------------------------------------------------------------------------
@@ -328,43 +332,49 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     acc_t acc[NR][MC][NP];
     i32x4 wa[NW], wb[NW];
     if (!small_c) {
-        const int iters = (R * a.nb[n_chunks > 1 ? 0 : 1] + kWaves - 1) / kWaves;
         chunk_load(0, 0);
         if (active) fetch_w(wa);
         advance_w(1);
-        for (int it = 0; it < iters; it += kLoads) {
-            if (it > 0) chunk_load(0, it);
-            chunk_store(0, it, smem);
+        const int nb = a.nb[n_chunks > 1 ? 0 : 1];
+        for (int b0 = 0; b0 < nb; b0 += kLoads) {
+            if (b0 > 0) chunk_load(0, b0);
+            chunk_store(0, b0, smem);
         }
-        if (lane == 0) occ[0][wave] = my_occ;
+        const uint32_t o = occupied(cells_of(0));
+        if (lane == 0) occ[0][wave] = o;
     } else {
-        // a lane gathers whole windows: up to twelve values next to each other in the row
-        const int xt_log = 6 + (NP == 2) - a.wc_log;           // XT = 1 << xt_log
+        // a lane gathers whole windows: three times C_in values next to each other in the row
         if (active) fetch_w(wa);
         advance_w(1);
-        for (int i = tid; i < R * XT; i += kThreads) {
-            const int r = i >> xt_log, p = i & (XT - 1);
-            const ev_t *row = nullptr;
-            bool there = false;
+        auto windows = [&](auto n_tag) IDF_INLINE {
+            constexpr int C = decltype(n_tag)::value, WC = (3 * C + VL - 1) / VL;
+            if (wave >= R) return;
+            for (int p = lane; p < XT; p += 64) {
+                ev_t val[WC * VL];
 #pragma unroll
-            for (int rr = 0; rr < R; ++rr)
-                if (r == rr) { there = row_there(rr); row = there ? reinterpret_cast<const ev_t *>(row_ptr(rr)) : nullptr; }
-            ev_t val[3][4];
+                for (int k = 0; k < WC * VL; ++k) val[k] = 0;
+                if (there) {
 #pragma unroll
-            for (int kx = 0; kx < 3; ++kx)
+                    for (int kx = 0; kx < 3; ++kx) {
+                        const int x = x0 - 1 + p + kx, xc = x < 0 ? 0 : (x >= W ? W - 1 : x);
 #pragma unroll
-                for (int ci = 0; ci < 4; ++ci) {
-                    const int x = x0 - 1 + p + kx;
-                    val[kx][ci] = 0;
-                    if (ci < C_in && there && x >= 0 && x < W) val[kx][ci] = row[x * C_in + ci];
+                        for (int ci = 0; ci < C; ++ci) {
+                            const ev_t v = *at4(reinterpret_cast<const ev_t *>(my_row), (uint32_t)((xc * C + ci) * EB));
+                            val[kx * C + ci] = x == xc ? v : (ev_t)0;
+                        }
+                    }
                 }
-            unsigned char *win = smem + i * wstride;
-            for (int k = 0; k < wcells; ++k) *reinterpret_cast<i32x4 *>(win + k * 16) = i32x4{0, 0, 0, 0};
+                i32x4 w[WC];
+                __builtin_memcpy(w, val, sizeof(w));
 #pragma unroll
-            for (int kx = 0; kx < 3; ++kx)
-#pragma unroll
-                for (int ci = 0; ci < 4; ++ci)
-                    if (ci < C_in) reinterpret_cast<ev_t *>(win)[kx * C_in + ci] = val[kx][ci];
+                for (int k = 0; k < WC; ++k) *reinterpret_cast<i32x4 *>(smem + (wave * XT + p) * wstride + k * 16) = w[k];
+            }
+        };
+        switch (C_in) {
+        case 1: windows(std::integral_constant<int, 1>{}); break;
+        case 2: windows(std::integral_constant<int, 2>{}); break;
+        case 3: windows(std::integral_constant<int, 3>{}); break;
+        default: windows(std::integral_constant<int, 4>{}); break;
         }
     }
     {
@@ -392,8 +402,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     uint32_t rows_done = 0;                        // input rows the list has taken care of (bit per row)
     if constexpr (EV && T::kEvents) {
         if (a.ev_limit > 0) {
-            const int cc = a.cells, nc = 16 * MC << a.wc_log, stride = stride_of(cc);
-            const size_t front = small_c ? (size_t)R * XT * wstride : (size_t)R * npos * stride;
+            const int cc = a.cells, nc = 16 * MC << a.wc_log, stride = stride_of(cc), pitch = a.row_pos[1];
+            const size_t front = small_c ? (size_t)R * XT * wstride : (size_t)R * pitch * stride;
             int32_t *ev_cnt = reinterpret_cast<int32_t *>(smem + ((front + 15) & ~(size_t)15));
             int32_t *ev_off = ev_cnt + (XT + 4);
             uint32_t *ev_list = reinterpret_cast<uint32_t *>(ev_off + (XT + 4));
@@ -410,7 +420,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             }
             // value ci of stretch position p (p = 0: x0 - 1) of input row r
             auto value = [&](int r, int p, int ci) IDF_INLINE -> ev_t {
-                if (!small_c) return reinterpret_cast<const ev_t *>(smem + (r * npos + p) * stride)[ci];
+                if (!small_c) return reinterpret_cast<const ev_t *>(smem + (r * pitch + p) * stride)[ci];
                 const int q = p == 0 ? 0 : p == XT + 1 ? XT - 1 : p - 1, kx = p == 0 ? 0 : p == XT + 1 ? 2 : 1;
                 return reinterpret_cast<const ev_t *>(smem + (r * XT + q) * wstride)[kx * C_in + ci];
             };
@@ -463,8 +473,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
                 lds_barrier();
                 // a row that has been delivered reads as zero from here on
                 if (!small_c && ((rows_done >> r) & 1u))
-                    for (int i = tid; i < npos * cc; i += kThreads)
-                        *reinterpret_cast<i32x4 *>(smem + (r * npos + i / cc) * stride + i % cc * 16) = i32x4{0, 0, 0, 0};
+                    for (int i = tid; i < (XT + 2) * cc; i += kThreads)
+                        *reinterpret_cast<i32x4 *>(smem + (r * pitch + i / cc) * stride + i % cc * 16) = i32x4{0, 0, 0, 0};
             }
             lds_barrier();
             if (a.issued && visits)
@@ -518,9 +528,9 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     };
     // The K-steps of one chunk, `live` saying which of them hold events (bit per K-step).  wa holds the weights of the
     // first one on entry and, if another chunk follows (this one then has an even number), those of its first one on exit.
-    auto chunk = [&](const unsigned char *buf, int cc, uint32_t live) IDF_INLINE {
+    auto chunk = [&](const unsigned char *buf, int cc, int pitch, uint32_t live) IDF_INLINE {
         const int stride = stride_of(cc), np_pitch = 16 * stride, S = (3 * cc + 3) >> 2;
-        const uint32_t row_pitch = (uint32_t)(npos * stride);
+        const uint32_t row_pitch = (uint32_t)(pitch * stride);
         const uint32_t pos = (uint32_t)((wp * 16 * NP + m) * stride);
         auto at = [&](int st) IDF_INLINE {
             // this lane's cell: number 4 st + g of the 3 * cc cells of its window (past the end the last one again:
@@ -558,7 +568,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             }
         }
     } else {
-        const int buf_bytes = R * npos * stride_of(n_chunks > 1 ? kRowCells : a.cells);
+        const int buf_bytes = R * (n_chunks > 1 ? a.row_pos[0] * stride_of(kRowCells) : a.row_pos[1] * stride_of(a.cells));
 #pragma unroll 1
         for (int ch = 0; ch < n_chunks; ++ch) {
             const unsigned char *buf = smem + (ch & 1) * buf_bytes;
@@ -576,12 +586,13 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
                 // K-steps with events: of a full chunk the even ones take cells 0-3 of a tap column, the odd ones cells 4-7
                 uint32_t live = bits ? (1u << ((3 * cc + 3) >> 2)) - 1u : 0u;
                 if (cc == kRowCells) live &= ((bits & 0x0f0f0f0fu) ? 0x15u : 0u) | ((bits & 0xf0f0f0f0u) ? 0x2au : 0u);
-                if (live || ch + 1 < n_chunks) chunk(buf, cc, live);
+                if (live || ch + 1 < n_chunks) chunk(buf, cc, pitch_of(ch), live);
             }
             if (ch + 1 < n_chunks) {
-                my_occ = 0;
+                my_or = 0;
                 chunk_store(ch + 1, 0, smem + ((ch + 1) & 1) * buf_bytes);
-                if (lane == 0) occ[(ch + 1) & 1][wave] = my_occ;
+                const uint32_t o = occupied(cells_of(ch + 1));
+                if (lane == 0) occ[(ch + 1) & 1][wave] = o;
                 lds_barrier();
             }
         }
@@ -707,7 +718,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 // steps with the deepest (longest) first.  Consecutive workgroups go to the eight XCDs in turn: with a
 // multiple of eight streams a stream always meets the same XCD, so its rows stay in one L2 from the layer
 // that emits them to the layer that reads them.
-template <class T, bool EV, bool WIDE>
+template <class T, bool EV, int WIDE>
 __global__ void __launch_bounds__(kThreads, 2) k_conv3x3_mfma_rows(const RowBatch b, const StreamSel sel)
 {
     (void)b;                                      // the first argument: it begins the segment
@@ -718,12 +729,13 @@ __global__ void __launch_bounds__(kThreads, 2) k_conv3x3_mfma_rows(const RowBatc
     case kRowTake: take_row<T>(a, sel, tile, si); break;
     case kRowSmall1: conv_rows<T, 1, 1, 1, EV>(a, sel, tile, si); break;
     case kRowSmall2: conv_rows<T, 1, 1, 2, EV>(a, sel, tile, si); break;
-    case kRowWide2: if constexpr (WIDE) conv_rows<T, 2, 2, 2, false>(a, sel, tile, si); break;
+    case kRowWide2: if constexpr (WIDE == 1) conv_rows<T, 2, 2, 2, false>(a, sel, tile, si); break;
+    case kRowWider2: if constexpr (WIDE == 2) conv_rows<T, 2, 4, 2, false>(a, sel, tile, si); break;
     default: break;
     }
 }
 
-int form_np(int form) { return form == kRowWide2 ? 2 : 1; }
+int form_np(int form) { return form == kRowWide2 ? 2 : form == kRowWider2 ? 4 : 1; }
 int form_rows(int form) { return form == kRowSmall1 ? 1 : 2; }
 
 size_t step_lds(int prec, const RowStep &a)
@@ -734,19 +746,23 @@ size_t step_lds(int prec, const RowStep &a)
         const int wcells = (3 * a.c_in + conv3x3_mfma_vl(prec) - 1) / conv3x3_mfma_vl(prec);
         return (size_t)rows * xt * (wcells | 1) * 16;
     }
-    const int cc = std::min(a.cells, kRowCells);
-    return (size_t)rows * (xt + 2) * (cc | 1) * 16 * (a.cells > kRowCells ? 2 : 1);
+    if (a.cells <= kRowCells) return (size_t)rows * a.row_pos[1] * (a.cells | 1) * 16;
+    return (size_t)rows * std::max(a.row_pos[0] * (kRowCells | 1), a.row_pos[1] * (((a.cells - 1) % kRowCells + 1) | 1)) * 16 * 2;
 }
 
 template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc)
 {
     size_t lds = 0;
     int tiles = 0;
-    bool events = false, wide = false;
+    bool events = false;
+    int wide = 0;
     for (int k = 0; k < b.n; ++k) {
         const RowStep &a = b.st[k];
         tiles = std::max(tiles, a.tiles);
-        wide = wide || a.form == kRowWide2;
+        if (a.form == kRowWide2 || a.form == kRowWider2) {
+            if (wide && wide != (a.form == kRowWide2 ? 1 : 2)) return hipErrorInvalidValue;
+            wide = a.form == kRowWide2 ? 1 : 2;
+        }
         size_t need = step_lds(prec, a);
         if (a.ev_limit > 0) {
             events = true;
@@ -762,10 +778,10 @@ template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const Str
         return launch(kernel, grid, block, lds, lc, b, sel);
     };
     if constexpr (T::kEvents)
-        if (events) return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, true, false>);
+        if (events) return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, true, 0>);
     if constexpr (!std::is_same<T, TraitsF32>::value)
-        if (wide) return go(k_conv3x3_mfma_rows<T, false, true>);
-    return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, false, false>);
+        if (wide) return wide == 1 ? go(k_conv3x3_mfma_rows<T, false, 1>) : go(k_conv3x3_mfma_rows<T, false, 2>);
+    return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, false, 0>);
 }
 
 }  // namespace
@@ -829,7 +845,8 @@ void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, RowStep &a)
     const int cc[2] = {kRowCells, a.cells == 0 ? 1 : (a.cells - 1) % kRowCells + 1};
     for (int k = 0; k < 2; ++k) {
         a.nb[k] = ((xt + 2) * cc[k] + 63) / 64;
-        a.nb_rcp[k] = rcp16(a.nb[k]); a.cc_rcp[k] = rcp16(cc[k]);
+        a.row_pos[k] = (a.nb[k] * 64 + cc[k] - 1) / cc[k];
+        a.cc_rcp[k] = rcp16(cc[k]);
     }
 }
 
