@@ -156,6 +156,12 @@ template <class V> __device__ __forceinline__ V neighbour(V v)
 
 __device__ __forceinline__ int taps_of(int v, int n) { return 3 - (v == 0) - (v == n - 1); }      // of a 3-tap axis with one position of padding
 
+// 16-byte cells from one position to the next in LDS.  The lanes of a fragment read 16 positions x 4 consecutive
+// cells; one cycle serves eight positions of one cell and the other eight of the next, so that an even distance that
+// is no multiple of four keeps all sixteen on banks of their own (measured: 222 bytes per clock and CU at 10 cells,
+// 123 at 9, 63 at 8).
+__host__ __device__ inline int cell_stride(int cells) { return cells <= 2 ? cells : cells <= 6 ? 6 : 10; }
+
 // ---- rows of the caller: into the ring, and counted as the first layer's events --------------------
 template <class T> __device__ __forceinline__ void take_row(ArgStep &a, const StreamSel &sel, const int tile, const int si)
 {
@@ -251,9 +257,9 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     const int n_chunks = small_c ? 1 : (a.cells + kRowCells - 1) / kRowCells;
     // few channels: the stretch is kept as the windows the positions see, [row][position][3 * C_in values, padded to cells]
     const int wcells = small_c ? (3 * C_in + VL - 1) / VL : 0;
-    const int wstride = (wcells | 1) * 16;
+    const int wstride = cell_stride(wcells) * 16;
     auto cells_of = [&](int ch) IDF_INLINE { return ch + 1 < n_chunks ? kRowCells : a.cells - ch * kRowCells; };
-    auto stride_of = [&](int cc) IDF_INLINE { return (cc | 1) * 16; };          // bytes per position: an odd number of 16-byte cells, no bank conflicts
+    auto stride_of = [&](int cc) IDF_INLINE { return cell_stride(cc) * 16; };   // bytes per position
     // A row of the stretch in LDS holds what whole blocks of 64 cells bring, a few positions more than needed: no lane has to sit out
     auto pitch_of = [&](int ch) IDF_INLINE { return ch + 1 < n_chunks ? a.row_pos[0] : a.row_pos[1]; };       // positions
     const bool edge = x0 == 0 || x0 + XT >= W;
@@ -744,10 +750,10 @@ size_t step_lds(int prec, const RowStep &a)
     const int xt = (16 * form_np(a.form) * kWaves) >> a.wc_log, rows = form_rows(a.form) + 2;
     if (a.cells == 0) {
         const int wcells = (3 * a.c_in + conv3x3_mfma_vl(prec) - 1) / conv3x3_mfma_vl(prec);
-        return (size_t)rows * xt * (wcells | 1) * 16;
+        return (size_t)rows * xt * cell_stride(wcells) * 16;
     }
-    if (a.cells <= kRowCells) return (size_t)rows * a.row_pos[1] * (a.cells | 1) * 16;
-    return (size_t)rows * std::max(a.row_pos[0] * (kRowCells | 1), a.row_pos[1] * (((a.cells - 1) % kRowCells + 1) | 1)) * 16 * 2;
+    if (a.cells <= kRowCells) return (size_t)rows * a.row_pos[1] * cell_stride(a.cells) * 16;
+    return (size_t)rows * std::max(a.row_pos[0] * cell_stride(kRowCells), a.row_pos[1] * cell_stride((a.cells - 1) % kRowCells + 1)) * 16 * 2;
 }
 
 template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc)
