@@ -220,12 +220,11 @@ using CascadeArgs = CascadeArgsT<kCasStepMax>;
 // Output rows of one conv layer on the matrix cores (k_conv3x3_mfma.hip).  A layer keeps the rows of its
 // input that some output row still needs, as events, in a ring; an output row of c is formed in
 // registers once its last input row has arrived, activated and emitted.
-constexpr int kRowCells = 8;           // 16-byte cells per position that a chunk of input channels holds
 constexpr int kRowLaunchRows = 16;     // arriving rows one launch takes at most (longer pushes are several launches)
 
 enum { kRowTake = 0,                   // no convolution: rows of the caller go into the ring and are counted
        kRowSmall1, kRowSmall2,         // a wave does 16 positions x 16 channels of 1 / 2 output rows
-       kRowWide2, kRowWider2 };        // a wave does 32 / 64 positions x 32 channels of 2 output rows
+       kRowWide2 };                    // a wave does 32 positions x 32 channels of 2 output rows
 
 struct RowStep {
     int form;                          // kRow*
@@ -242,9 +241,8 @@ struct RowStep {
     int wc_log;                        // log2 of the waves of a workgroup that lie side by side along the channels
     int n_xt, n_cg;                    // position tiles of a row, channel groups
     unsigned xt_rcp, cg_rcp;           // ceil(2^32 / n) of those (0 for one)
-    int nb[2];                         // blocks of 64 cells per row of the stretch in a full / in the last chunk
-    int row_pos[2];                    // positions those blocks cover: what a row of the stretch takes in LDS
-    unsigned cc_rcp[2];                // ceil(65536 / cells per position) of those chunks
+    int nb, row_pos;                   // blocks of 64 cells per row of a stretch; positions those cover: what a row takes in LDS
+    unsigned cells_rcp;                // ceil(65536 / cells)
     int act, shr, clamp_hi;
     int pool;                          // 1: 2x2 max-pool behind the layer
     int pool_from;                     // output rows before this one have been counted as the pool's events already

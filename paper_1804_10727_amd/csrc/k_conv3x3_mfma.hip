@@ -14,17 +14,16 @@
 // A workgroup of four waves owns a stretch of positions and a group of output channels, for one output
 // row or two.  Two rows share everything that is fetched: each weight serves both, and each of the
 // two middle input rows is read from LDS once for both.
-//   * Input channels are taken in chunks of eight 16-byte cells.  The stretch of the input rows
-//     goes to LDS chunk by chunk, the next chunk's loads under the current one's arithmetic.  On the way
-//     every cell that holds a non-zero sets a bit (a wave ballot, one word per wave): K-steps of a row
-//     without events cost no matrix instruction, a chunk without events not even a weight fetch (zero
+//   * The stretch of the input rows goes to LDS at once, a wave per row.  On the way every 16-byte cell
+//     (channels of a position) that holds a non-zero sets a bit (a wave ballot, one word per row): K-steps
+//     without events cost no matrix instruction, a stretch without events not even a weight fetch (zero
 //     values are not events, Sec. 1).
 //   * Operands are swapped: the matrix instruction's rows are output channels, its columns positions.
 //     With the channels of a pair of tiles interleaved in the weight packing a lane then holds eight
 //     neighbouring channels of one position, i.e. 16 bytes of a bfloat16 row: rows go straight from the
 //     accumulators to memory, and the 2x2 max-pool is a maximum of two accumulators and one lane
 //     exchange.
-//   * The order of the sum is the same whatever a launch holds (chunk, K-step, tap row), so results do
+//   * The order of the sum is the same whatever a launch holds (K-step, tap row), so results do
 //     not depend on how rows were grouped.
 #include "idf.h"
 #include "idf_kernels.h"
@@ -160,7 +159,7 @@ __device__ __forceinline__ int taps_of(int v, int n) { return 3 - (v == 0) - (v 
 // cells; one cycle serves eight positions of one cell and the other eight of the next, so that an even distance that
 // is no multiple of four keeps all sixteen on banks of their own (measured: 222 bytes per clock and CU at 10 cells,
 // 123 at 9, 63 at 8).
-__host__ __device__ inline int cell_stride(int cells) { return cells <= 2 ? cells : cells <= 6 ? 6 : 10; }
+__host__ __device__ inline int cell_stride(int cells) { return cells == 1 ? 1 : (cells + 1) / 4 * 4 + 2; }
 
 // ---- rows of the caller: into the ring, and counted as the first layer's events --------------------
 template <class T> __device__ __forceinline__ void take_row(ArgStep &a, const StreamSel &sel, const int tile, const int si)
@@ -215,9 +214,9 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     constexpr int VL = T::VL, EB = T::EB;
     constexpr int R = NR + 2;                      // input rows
     constexpr int NW = 3 * MC;                     // weight fragments of a K-step
-    constexpr int kLoads = NP == 4 ? 9 : 5;        // cells of a chunk each lane has in flight
+    constexpr int kLoads = NP == 2 ? 17 : 9;       // cells each lane has in flight: a row of 32 positions (16) and halo x 32 cells at once
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    __shared__ uint32_t occ[2][kWaves];            // per chunk parity and wave: a byte for the wave's input row, bit c: cell c holds an event somewhere
+    __shared__ unsigned long long occ[kWaves];     // per input row, bit c: cell c holds an event somewhere in the stretch
 
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     const int m = lane & 15, g = lane >> 4;        // position within a tile; group of channels / of k
@@ -254,66 +253,14 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             my_row = (const unsigned char *)a.in_ring + ((int64_t)stream * a.in_stride + (int64_t)slot * W * C_in) * EB;
         }
     }
-    const int n_chunks = small_c ? 1 : (a.cells + kRowCells - 1) / kRowCells;
     // few channels: the stretch is kept as the windows the positions see, [row][position][3 * C_in values, padded to cells]
     const int wcells = small_c ? (3 * C_in + VL - 1) / VL : 0;
     const int wstride = cell_stride(wcells) * 16;
-    auto cells_of = [&](int ch) IDF_INLINE { return ch + 1 < n_chunks ? kRowCells : a.cells - ch * kRowCells; };
-    auto stride_of = [&](int cc) IDF_INLINE { return cell_stride(cc) * 16; };   // bytes per position
-    // A row of the stretch in LDS holds what whole blocks of 64 cells bring, a few positions more than needed: no lane has to sit out
-    auto pitch_of = [&](int ch) IDF_INLINE { return ch + 1 < n_chunks ? a.row_pos[0] : a.row_pos[1]; };       // positions
+    const int cells = a.cells, stride = cell_stride(cells) * 16;      // 16-byte cells per position; bytes from one position to the next
     const bool edge = x0 == 0 || x0 + XT >= W;
-
-    i32x4 tv[kLoads];
-    auto cell_of = [&](int i, int ch, int cc, int &p, int &c) IDF_INLINE {
-        p = (int)(((unsigned)i * a.cc_rcp[ch + 1 < n_chunks ? 0 : 1]) >> 16);
-        c = i - p * cc;
-    };
-    auto chunk_load = [&](int ch, int b0) IDF_INLINE {
-        if (!there) return;
-        const int cc = cells_of(ch), nb = a.nb[ch + 1 < n_chunks ? 0 : 1], pos_bytes = C_in * EB;
-        const unsigned char *base = my_row + ch * (kRowCells * 16);
-        int p, c;
-        cell_of(b0 * 64 + lane, ch, cc, p, c);
-#pragma unroll
-        for (int b = 0; b < kLoads; ++b) {
-            if (b0 + b >= nb) break;
-            int x = x0 - 1 + p;
-            x = x < 0 ? 0 : (x >= W ? W - 1 : x);
-            tv[b] = *at4(reinterpret_cast<const i32x4 *>(base), (uint32_t)(x * pos_bytes + c * 16));
-            if (64 % cc == 0) p += 64 / cc; else cell_of((b0 + b + 1) * 64 + lane, ch, cc, p, c);
-        }
-    };
-    int my_or = 0;                                 // all values of this lane's cells, or-ed
-    auto chunk_store = [&](int ch, int b0, unsigned char *buf) IDF_INLINE {
-        if (wave >= R) return;
-        const int cc = cells_of(ch), nb = a.nb[ch + 1 < n_chunks ? 0 : 1], stride = stride_of(cc);
-        unsigned char *row = buf + wave * pitch_of(ch) * stride;
-        int ln = lane;                             // (places are worked out again rather than held in registers from the load on:
-        asm volatile("" : "+v"(ln));               //  the empty statement hides that this is the same value)
-        int p, c;
-        cell_of(b0 * 64 + ln, ch, cc, p, c);
-#pragma unroll
-        for (int b = 0; b < kLoads; ++b) {
-            if (b0 + b >= nb) break;
-            i32x4 v = there ? tv[b] : i32x4{0, 0, 0, 0};
-            if (edge) {
-                const int x = x0 - 1 + p;
-                if (x < 0 || x >= W) v = i32x4{0, 0, 0, 0};
-            }
-            *reinterpret_cast<i32x4 *>(row + p * stride + c * 16) = v;
-            my_or |= T::or_of(v);
-            if (64 % cc == 0) p += 64 / cc; else cell_of((b0 + b + 1) * 64 + ln, ch, cc, p, c);
-        }
-    };
-    // what chunk ch holds of this wave's row: bit c set when cell c holds an event somewhere in the stretch (fewer than eight
-    // cells: all bits or none)
-    auto occupied = [&](int cc) IDF_INLINE {
-        const unsigned long long bal = __ballot(my_or != 0);
-        uint32_t bits = (uint32_t)(bal | bal >> 32);
-        bits |= bits >> 16;
-        bits |= bits >> 8;
-        return wave < R ? (cc == kRowCells ? bits & 0xffu : bits ? 0xffu : 0u) << (8 * wave) : 0u;
+    auto cell_of = [&](int i, int &p, int &c) IDF_INLINE {
+        p = (int)(((unsigned)i * a.cells_rcp) >> 16);
+        c = i - p * cells;
     };
 
     // ---- weights -------------------------------------------------------------------------------------
@@ -329,29 +276,67 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             for (int mc = 0; mc < MC; ++mc)
                 w[ky * MC + mc] = *at4(reinterpret_cast<const i32x4 *>(wp_next), w_lane + (MC == 2 ? ky * 2048 + mc * 1024 : ky * w_ky));
     };
-    int ks_left = small_c ? 1 : 0;                 // K-steps whose weights have not been asked for
-    if (!small_c)
-        for (int ch = 0; ch < n_chunks; ++ch) ks_left += (3 * cells_of(ch) + 3) >> 2;
-    auto advance_w = [&](int n) IDF_INLINE { ks_left -= n; if (ks_left > 0) wp_next += (size_t)n * w_kstep; };     // past the end the last one is simply fetched again
+    const int n_ksteps = small_c ? 1 : (3 * cells + 3) >> 2;
+    int ks_left = n_ksteps;                        // K-steps whose weights have not been asked for
+    auto advance_w = [&]() IDF_INLINE { if (--ks_left > 0) wp_next += w_kstep; };         // past the end the last one is simply fetched again
 
     // ---- the first stretch, and what can be asked for while it is on its way ---------------------------
     acc_t acc[NR][MC][NP];
     i32x4 wa[NW], wb[NW];
     if (!small_c) {
-        chunk_load(0, 0);
-        if (active) fetch_w(wa);
-        advance_w(1);
-        const int nb = a.nb[n_chunks > 1 ? 0 : 1];
+        // The whole stretch at once, in blocks of 64 cells: everything this wave needs from memory is on its way together
+        // (the registers it lands in are those of the accumulators and fragments later).  A row in LDS is as long as whole
+        // blocks, so that no lane has to sit out.
+        const int nb = a.nb, pos_bytes = C_in * EB;
+        unsigned char *row = smem + wave * a.row_pos * stride;
+        unsigned long long mask = 0;               // bit c: cell c holds an event somewhere in the stretch
         for (int b0 = 0; b0 < nb; b0 += kLoads) {
-            if (b0 > 0) chunk_load(0, b0);
-            chunk_store(0, b0, smem);
+            i32x4 tv[kLoads];
+            int p, c;
+            if (there) {
+                cell_of(b0 * 64 + lane, p, c);
+#pragma unroll
+                for (int b = 0; b < kLoads; ++b) {
+                    if (b0 + b >= nb) break;
+                    int x = x0 - 1 + p;
+                    x = x < 0 ? 0 : (x >= W ? W - 1 : x);
+                    tv[b] = *at4(reinterpret_cast<const i32x4 *>(my_row), (uint32_t)(x * pos_bytes + c * 16));
+                    if (64 % cells == 0) p += 64 / cells; else cell_of((b0 + b + 1) * 64 + lane, p, c);
+                }
+            }
+            if (b0 == 0) {
+                if (active) fetch_w(wa);
+                advance_w();
+            }
+            if (wave < R) {
+                int ln = lane, any = 0;            // (places are worked out again rather than held in registers from the load on:
+                asm volatile("" : "+v"(ln));       //  the empty statement hides that this is the same value)
+                cell_of(b0 * 64 + ln, p, c);
+#pragma unroll
+                for (int b = 0; b < kLoads; ++b) {
+                    if (b0 + b >= nb) break;
+                    i32x4 v = there ? tv[b] : i32x4{0, 0, 0, 0};
+                    if (edge) {
+                        const int x = x0 - 1 + p;
+                        if (x < 0 || x >= W) v = i32x4{0, 0, 0, 0};
+                    }
+                    *reinterpret_cast<i32x4 *>(row + p * stride + c * 16) = v;
+                    any |= T::or_of(v);
+                    if (64 % cells == 0) p += 64 / cells; else cell_of((b0 + b + 1) * 64 + ln, p, c);
+                }
+                unsigned long long bal = __ballot(any != 0);
+                if (64 % cells == 0) {             // a lane has had one and the same cell throughout
+                    for (int w = 32; w >= cells; w >>= 1) bal |= bal >> w;
+                } else {
+                    bal = bal ? ~0ull : 0ull;
+                }
+                mask |= bal;
+            }
         }
-        const uint32_t o = occupied(cells_of(0));
-        if (lane == 0) occ[0][wave] = o;
+        if (lane == 0) occ[wave] = mask;
     } else {
         // a lane gathers whole windows: three times C_in values next to each other in the row
         if (active) fetch_w(wa);
-        advance_w(1);
         auto windows = [&](auto n_tag) IDF_INLINE {
             constexpr int C = decltype(n_tag)::value, WC = (3 * C + VL - 1) / VL;
             if (wave >= R) return;
@@ -398,7 +383,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
                 for (int np = 0; np < NP; ++np) acc[j][mc][np] = start[mc];
     }
     lds_barrier();
-    uint32_t n_mfma = 0, n_ksteps = 0;             // tiles of 16 x 16 x one K-step issued; K-steps issued
+    uint32_t n_mfma = 0, n_done = 0;               // tiles of 16 x 16 x one K-step issued; K-steps issued
 
     // ---- sparse stretches: the event-list path ---------------------------------------------------------
     // Where a row's stretch (halo included) holds few events they are packed into a list -- counts per
@@ -408,7 +393,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     uint32_t rows_done = 0;                        // input rows the list has taken care of (bit per row)
     if constexpr (EV && T::kEvents) {
         if (a.ev_limit > 0) {
-            const int cc = a.cells, nc = 16 * MC << a.wc_log, stride = stride_of(cc), pitch = a.row_pos[1];
+            const int nc = 16 * MC << a.wc_log, pitch = a.row_pos;
             const size_t front = small_c ? (size_t)R * XT * wstride : (size_t)R * pitch * stride;
             int32_t *ev_cnt = reinterpret_cast<int32_t *>(smem + ((front + 15) & ~(size_t)15));
             int32_t *ev_off = ev_cnt + (XT + 4);
@@ -479,8 +464,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
                 lds_barrier();
                 // a row that has been delivered reads as zero from here on
                 if (!small_c && ((rows_done >> r) & 1u))
-                    for (int i = tid; i < (XT + 2) * cc; i += kThreads)
-                        *reinterpret_cast<i32x4 *>(smem + (r * pitch + i / cc) * stride + i % cc * 16) = i32x4{0, 0, 0, 0};
+                    for (int i = tid; i < (XT + 2) * cells; i += kThreads)
+                        *reinterpret_cast<i32x4 *>(smem + (r * pitch + i / cells) * stride + i % cells * 16) = i32x4{0, 0, 0, 0};
             }
             lds_barrier();
             if (a.issued && visits)
@@ -530,34 +515,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             }
             deliver(w, x[r & 1], r);
         }
-        ++n_ksteps;
+        ++n_done;
     };
-    // The K-steps of one chunk, `live` saying which of them hold events (bit per K-step).  wa holds the weights of the
-    // first one on entry and, if another chunk follows (this one then has an even number), those of its first one on exit.
-    auto chunk = [&](const unsigned char *buf, int cc, int pitch, uint32_t live) IDF_INLINE {
-        const int stride = stride_of(cc), np_pitch = 16 * stride, S = (3 * cc + 3) >> 2;
-        const uint32_t row_pitch = (uint32_t)(pitch * stride);
-        const uint32_t pos = (uint32_t)((wp * 16 * NP + m) * stride);
-        auto at = [&](int st) IDF_INLINE {
-            // this lane's cell: number 4 st + g of the 3 * cc cells of its window (past the end the last one again:
-            // the weights there are zero)
-            int q = 4 * st + g;
-            q = q < 3 * cc ? q : 3 * cc - 1;
-            const int kx = (q >= cc) + (q >= 2 * cc);
-            return pos + (uint32_t)(kx * stride + (q - kx * cc) * 16);
-        };
-#pragma unroll 1
-        for (int st = 0; st < S; st += 2) {
-            fetch_w(wb); advance_w(1);
-            if (live & 1u) kstep(wa, buf, at(st), row_pitch, np_pitch);
-            __builtin_amdgcn_sched_barrier(0);     // K-steps stay apart: nothing of a later one is held in registers early
-            fetch_w(wa); advance_w(1);
-            if (live & 2u) kstep(wb, buf, at(st + 1), row_pitch, np_pitch);
-            __builtin_amdgcn_sched_barrier(0);
-            live >>= 2;
-        }
-    };
-
     if (small_c) {
         // one K-step per tap row, always visited
         if (active) {
@@ -573,35 +532,41 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
                 n_mfma += (uint32_t)(((r <= 2) + (NR == 2 && r >= 1 && rows == 2)) * MC * NP);
             }
         }
-    } else {
-        const int buf_bytes = R * (n_chunks > 1 ? a.row_pos[0] * stride_of(kRowCells) : a.row_pos[1] * stride_of(a.cells));
+    } else if (active) {
+        // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column (past the
+        // end the last one again: the weights there are zero)
+        unsigned long long mask = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w)
+            if (w < R && !(EV && ((rows_done >> w) & 1u))) mask |= occ[w];
+        mask = (unsigned long long)(uint32_t)uni((int)(mask >> 32)) << 32 | (uint32_t)uni((int)mask);
+        const bool by_cells = (cells & 3) == 0;    // every K-step lies in one tap column: its four cells have bits of their own
+        unsigned long long left = mask;
+        int col_left = by_cells ? cells >> 2 : 1 << 30;       // K-steps to the end of the tap column
+        auto live = [&]() IDF_INLINE { return by_cells ? ((uint32_t)left & 0xfu) != 0 : mask != 0; };
+        auto next = [&]() IDF_INLINE {
+            left >>= 4;
+            if (--col_left == 0) { left = mask; col_left = cells >> 2; }
+        };
+        const uint32_t row_pitch = (uint32_t)(a.row_pos * stride), pos = (uint32_t)((wp * 16 * NP + m) * stride);
+        auto at = [&](int st) IDF_INLINE {
+            int q = 4 * st + g;
+            q = q < 3 * cells ? q : 3 * cells - 1;
+            const int kx = (q >= cells) + (q >= 2 * cells);
+            return pos + (uint32_t)(kx * stride + (q - kx * cells) * 16);
+        };
+        if (mask)
 #pragma unroll 1
-        for (int ch = 0; ch < n_chunks; ++ch) {
-            const unsigned char *buf = smem + (ch & 1) * buf_bytes;
-            const int cc = cells_of(ch);
-            uint32_t bits = 0;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) bits |= occ[ch & 1][w];
-            bits = (uint32_t)uni((int)bits);
-            if (EV) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) if ((rows_done >> r) & 1u) bits &= ~(0xffu << (8 * r));
+            for (int st = 0; st < n_ksteps; st += 2) {
+                fetch_w(wb); advance_w();
+                if (live()) kstep(wa, smem, at(st), row_pitch, 16 * stride);
+                __builtin_amdgcn_sched_barrier(0); // K-steps stay apart: nothing of a later one is held in registers early
+                next();
+                fetch_w(wa); advance_w();
+                if (live() && st + 1 < n_ksteps) kstep(wb, smem, at(st + 1), row_pitch, 16 * stride);
+                __builtin_amdgcn_sched_barrier(0);
+                next();
             }
-            if (ch + 1 < n_chunks) chunk_load(ch + 1, 0);
-            if (active) {
-                // K-steps with events: of a full chunk the even ones take cells 0-3 of a tap column, the odd ones cells 4-7
-                uint32_t live = bits ? (1u << ((3 * cc + 3) >> 2)) - 1u : 0u;
-                if (cc == kRowCells) live &= ((bits & 0x0f0f0f0fu) ? 0x15u : 0u) | ((bits & 0xf0f0f0f0u) ? 0x2au : 0u);
-                if (live || ch + 1 < n_chunks) chunk(buf, cc, pitch_of(ch), live);
-            }
-            if (ch + 1 < n_chunks) {
-                my_or = 0;
-                chunk_store(ch + 1, 0, smem + ((ch + 1) & 1) * buf_bytes);
-                const uint32_t o = occupied(cells_of(ch + 1));
-                if (lane == 0) occ[(ch + 1) & 1][wave] = o;
-                lds_barrier();
-            }
-        }
     }
     if (!active) return;
 
@@ -712,7 +677,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         }
     }
     // what the matrix instructions of this wave multiplied, zeros inside a live K-step included
-    n_mfma += n_ksteps * (uint32_t)(3 * rows * MC * NP);
+    n_mfma += n_done * (uint32_t)(3 * rows * MC * NP);
     if (a.issued && lane == 0 && n_mfma)
         atomicAdd(a.issued + (int64_t)stream * a.n_layers + a.layer, (unsigned long long)n_mfma * (256ull * 4 * VL));
 }
@@ -724,8 +689,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 // steps with the deepest (longest) first.  Consecutive workgroups go to the eight XCDs in turn: with a
 // multiple of eight streams a stream always meets the same XCD, so its rows stay in one L2 from the layer
 // that emits them to the layer that reads them.
-template <class T, bool EV, int WIDE>
-__global__ void __launch_bounds__(kThreads, 2) k_conv3x3_mfma_rows(const RowBatch b, const StreamSel sel)
+template <class T, bool EV, bool WIDE>
+__global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatch b, const StreamSel sel)
 {
     (void)b;                                      // the first argument: it begins the segment
     ArgStep &a = *((ArgStep *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(RowBatch, st)) + blockIdx.z);
@@ -735,13 +700,12 @@ __global__ void __launch_bounds__(kThreads, 2) k_conv3x3_mfma_rows(const RowBatc
     case kRowTake: take_row<T>(a, sel, tile, si); break;
     case kRowSmall1: conv_rows<T, 1, 1, 1, EV>(a, sel, tile, si); break;
     case kRowSmall2: conv_rows<T, 1, 1, 2, EV>(a, sel, tile, si); break;
-    case kRowWide2: if constexpr (WIDE == 1) conv_rows<T, 2, 2, 2, false>(a, sel, tile, si); break;
-    case kRowWider2: if constexpr (WIDE == 2) conv_rows<T, 2, 4, 2, false>(a, sel, tile, si); break;
+    case kRowWide2: if constexpr (WIDE) conv_rows<T, 2, 2, 2, false>(a, sel, tile, si); break;
     default: break;
     }
 }
 
-int form_np(int form) { return form == kRowWide2 ? 2 : form == kRowWider2 ? 4 : 1; }
+int form_np(int form) { return form == kRowWide2 ? 2 : 1; }
 int form_rows(int form) { return form == kRowSmall1 ? 1 : 2; }
 
 size_t step_lds(int prec, const RowStep &a)
@@ -752,23 +716,18 @@ size_t step_lds(int prec, const RowStep &a)
         const int wcells = (3 * a.c_in + conv3x3_mfma_vl(prec) - 1) / conv3x3_mfma_vl(prec);
         return (size_t)rows * xt * cell_stride(wcells) * 16;
     }
-    if (a.cells <= kRowCells) return (size_t)rows * a.row_pos[1] * cell_stride(a.cells) * 16;
-    return (size_t)rows * std::max(a.row_pos[0] * cell_stride(kRowCells), a.row_pos[1] * cell_stride((a.cells - 1) % kRowCells + 1)) * 16 * 2;
+    return (size_t)rows * a.row_pos * cell_stride(a.cells) * 16;
 }
 
 template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc)
 {
     size_t lds = 0;
     int tiles = 0;
-    bool events = false;
-    int wide = 0;
+    bool events = false, wide = false;
     for (int k = 0; k < b.n; ++k) {
         const RowStep &a = b.st[k];
         tiles = std::max(tiles, a.tiles);
-        if (a.form == kRowWide2 || a.form == kRowWider2) {
-            if (wide && wide != (a.form == kRowWide2 ? 1 : 2)) return hipErrorInvalidValue;
-            wide = a.form == kRowWide2 ? 1 : 2;
-        }
+        wide = wide || a.form == kRowWide2;
         size_t need = step_lds(prec, a);
         if (a.ev_limit > 0) {
             events = true;
@@ -784,10 +743,10 @@ template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const Str
         return launch(kernel, grid, block, lds, lc, b, sel);
     };
     if constexpr (T::kEvents)
-        if (events) return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, true, 0>);
+        if (events) return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, true, false>);
     if constexpr (!std::is_same<T, TraitsF32>::value)
-        if (wide) return wide == 1 ? go(k_conv3x3_mfma_rows<T, false, 1>) : go(k_conv3x3_mfma_rows<T, false, 2>);
-    return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, false, 0>);
+        if (wide) return go(k_conv3x3_mfma_rows<T, false, true>);
+    return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, false, false>);
 }
 
 }  // namespace
@@ -807,13 +766,12 @@ bool conv3x3_mfma_eligible(int prec, const Geom &g)
     return true;
 }
 
-// K-steps (of four cells) per tap row: every chunk of eight cells per position is six, the rest rounds up.
+// K-steps (of four cells) per tap row.
 static int row_ksteps(int prec, const Geom &g)
 {
     const int vl = conv3x3_mfma_vl(prec);
     if (g.c_in % vl != 0 || g.c_in < vl) return 1;
-    const int cells = g.c_in / vl;
-    return cells / kRowCells * 6 + (3 * (cells % kRowCells) + 3) / 4;
+    return (3 * (g.c_in / vl) + 3) / 4;
 }
 
 // Shape of a step of n_rows output rows for n_streams streams: which tiles a wave takes, how the waves of a
@@ -823,45 +781,33 @@ void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, RowStep &a)
     const int vl = conv3x3_mfma_vl(prec);
     a.cells = g.c_in % vl == 0 && g.c_in >= vl ? g.c_in / vl : 0;
     const int n_ct = g.c_out == 16 ? 1 : 2 * ((g.c_out + 31) / 32);
-    const bool chunks = a.cells > kRowCells;
     const int pairs = a.n_rows >= 2 ? (a.n_rows + 1) / 2 : 1;
     // Wide tiles use each weight fragment and each cell twice as often and pay where they still give
     // every SIMD most of a wave; float32 stays narrow, its matrix instructions being sixteen times longer.
-    bool wide = prec != IDF_PREC_F32 && a.ev_limit == 0 && a.n_rows >= 2 && g.c_out > 16 && (long)n_streams * ((g.w_out + 31) / 32) * (n_ct / 2) * pairs >= 768;
+    const bool wide = prec != IDF_PREC_F32 && a.ev_limit == 0 && a.n_rows >= 2 && g.c_out > 16 && (long)n_streams * ((g.w_out + 31) / 32) * (n_ct / 2) * pairs >= 768;
     auto waves_log = [&](int tiles) { return tiles >= 4 ? 2 : tiles >= 2 ? 1 : 0; };
-    if (wide) {
-        a.wc_log = waves_log(n_ct / 2);
-        // a stretch of at most 32 positions while chunks follow one another (their loads are held in registers),
-        // of at most 64 where a position has eight cells
-        const int xt = 128 >> a.wc_log;
-        if ((chunks && xt > 32) || (a.cells > 4 && xt > 64)) wide = false;
-    }
-    if (!wide) {
-        a.wc_log = waves_log(n_ct);
-        if (chunks && a.wc_log < 1) a.wc_log = 1;
-    }
+    a.wc_log = waves_log(wide ? n_ct / 2 : n_ct);
+    // a stretch short enough for two workgroups to share a CU's LDS, where channels can take the waves instead of positions
+    while (a.wc_log < 2 && (((wide ? 128 : 64) >> a.wc_log) + 2) * cell_stride(std::max(a.cells, 1)) * 4 * 16 > 76 * 1024) ++a.wc_log;
     a.form = wide ? kRowWide2 : a.n_rows >= 2 ? kRowSmall2 : kRowSmall1;
     const int mc = a.form == kRowWide2 ? 2 : 1, xt = (16 * form_np(a.form) * kWaves) >> a.wc_log;
     auto rcp32 = [](int n) { return n > 1 ? (unsigned)((0x100000000ull + n - 1) / n) : 0u; };
-    auto rcp16 = [](int n) { return (unsigned)((65536 + n - 1) / n); };
     a.n_xt = (g.w_out + xt - 1) / xt;
     a.n_cg = (n_ct + (mc << a.wc_log) - 1) / (mc << a.wc_log);
     a.xt_rcp = rcp32(a.n_xt); a.cg_rcp = rcp32(a.n_cg);
     a.tiles = (a.n_rows + form_rows(a.form) - 1) / form_rows(a.form) * a.n_xt * a.n_cg;
-    const int cc[2] = {kRowCells, a.cells == 0 ? 1 : (a.cells - 1) % kRowCells + 1};
-    for (int k = 0; k < 2; ++k) {
-        a.nb[k] = ((xt + 2) * cc[k] + 63) / 64;
-        a.row_pos[k] = (a.nb[k] * 64 + cc[k] - 1) / cc[k];
-        a.cc_rcp[k] = rcp16(cc[k]);
-    }
+    const int cells = std::max(a.cells, 1);
+    a.nb = ((xt + 2) * cells + 63) / 64;
+    a.row_pos = (a.nb * 64 + cells - 1) / cells;
+    a.cells_rcp = (unsigned)((65536 + cells - 1) / cells);
 }
 
 // Weights [k_h][k_w][c_in][c_out] -> fragment order, zero padded to whole K-steps and channel pairs:
 //   [K-step][block of 32 channels][ky][tile t of 2][lane][16 bytes], lane = 16 g + m holding cell 4 s + g of the
 //   K-step for row m of the tile, which is channel 32 * block + (m / 4) * 8 + t * 4 + m % 4;
 //   16 output channels: [K-step][ky][lane][16 bytes], row m = channel m.
-// K-steps run chunk by chunk (eight cells per position), inside a chunk over the cells kx * (cells) + c; with one to
-// four input channels there is one K-step whose elements are k = kx * c_in + ci.
+// K-steps run over the cells kx * (cells per position) + c; with one to four input channels there is one K-step whose
+// elements are k = kx * c_in + ci.
 size_t conv3x3_mfma_pack(int prec, const Geom &g, const void *w_khkwcico, void *out)
 {
     const int vl = conv3x3_mfma_vl(prec), eb = 16 / vl;
@@ -885,9 +831,8 @@ size_t conv3x3_mfma_pack(int prec, const Geom &g, const void *w_khkwcico, void *
                     const int k = kx * g.c_in + ci;
                     step = 0; grp = k / vl; elem = k % vl;
                 } else {
-                    const int cell = ci / vl, ch = cell / kRowCells, cc = std::min(kRowCells, cells - ch * kRowCells);
-                    const int q = kx * cc + cell % kRowCells;
-                    step = ch * 6 + q / 4; grp = q % 4; elem = ci % vl;
+                    const int q = kx * cells + ci / vl;
+                    step = q / 4; grp = q % 4; elem = ci % vl;
                 }
                 for (int co = 0; co < g.c_out; ++co) {
                     const size_t s_idx = (((size_t)ky * 3 + kx) * g.c_in + ci) * g.c_out + co;
