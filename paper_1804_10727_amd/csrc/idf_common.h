@@ -308,6 +308,42 @@ struct EagerStep {
     unsigned long long *stats;
 };
 
+// Eager emission of a segment through a whole net in one launch (k_eager_pass.hip): its layers in order.
+constexpr int kPassMax = 16;     // conv layers at most
+constexpr int kPassGroups = 4;   // groups of four rows of a layer that a band reaches at most
+struct EagerPassStep {           // a conv layer and the 2x2 pool behind it, if there is one
+    int layer, n_layers;
+    int n_in;                    // delta rows that arrive
+    int row0, n_groups;          // first row of the first group; groups
+    int band0;                   // row row0 - 1, counted from the band's first
+    uint32_t rows_in;            // bit i: row row0 - 1 + i is in the band
+    uint32_t rows_on, rows_old;  // bit i: row row0 + i of the layer is reached / has a state already
+    int w, c_in, c_out;
+    int act, shr, clamp_hi;
+    int emit;                    // differences are passed on
+    int out_first;               // place of row row0 (pool: of row row0 / 2) among the rows passed on (may be negative)
+    int pool, out_w;             // out_w: positions of the rows passed on
+    uint32_t pool_on;            // bit i: pooled row row0 / 2 + i is looked at
+    uint32_t c_off[4 * kPassGroups], pool_off[2 * kPassGroups];   // bytes from a stream's first row kept to the one that holds each row
+    int64_t c_stride, ann_stride, pool_ann_stride;     // elements per stream
+    void *c, *ann, *pool_ann;    // ann: kept whole, or null: whoever wants them takes f of the state
+    const void *w_frag;
+    // set with the layout
+    unsigned ct_rcp, xt_rcp;
+    int n_xt, n_ct, cells, win_cells, n_ksteps;
+    int lds_in, lds_out, in_pitch, in_stride, out_pitch, out_stride, out_rows;
+};
+struct EagerPass {
+    int n, n_layers;
+    int ann0_rows, ann0_slot;    // level 0
+    int lds;                     // bytes (set with the layout)
+    const void *in;              // pushed rows [position][rows][w][c], event type
+    int64_t in_stride, ann0_stride;
+    void *ann0;
+    unsigned long long *stats;
+    EagerPassStep st[kPassMax];
+};
+
 // Averaging output units: rows [first_slot, first_slot + n_rows) of the output ring are added to
 // the per-channel sums of each selected stream.
 struct HeadAcc {

@@ -174,6 +174,7 @@ struct idf_streams {
     struct Eager {
         bool on = false;
         bool ring = false;
+        bool one_launch = false;                  // a segment can go through the net in one launch (k_eager_pass.hip)
         char *ws = nullptr;
         std::vector<int64_t> row_elems;           // per level: W*C of one row
         std::vector<int> rows;                    // per level: rows the level has (H)
@@ -1351,6 +1352,109 @@ size_t eager_layout(const idf_net &net, int B, int max_seg, idf_streams::Eager *
     return off;
 }
 
+// The input rows [a, a + n_rows) through all layers in one launch; false where the bands are too large for it.
+bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int64_t a, const std::vector<int64_t> &lo,
+                     const std::vector<int64_t> &hi, const std::vector<int64_t> &seen_hi, EagerPass &P, double &bytes)
+{
+    const idf_net &net = *s->net;
+    const int n = (int)net.g.size();
+    const idf_streams::Eager &E = s->eager;
+    P.n = 0;
+    P.n_layers = n;
+    P.in = dev_rows; P.in_stride = (int64_t)n_rows * net.in_w * net.in_c;
+    P.ann0 = E.ws + E.ann_off[0]; P.ann0_rows = E.ann_rows[0]; P.ann0_slot = (int)(a % E.ann_rows[0]);
+    P.ann0_stride = (int64_t)E.ann_rows[0] * E.row_elems[0];
+    P.stats = (unsigned long long *)(s->ws + s->stats_off);
+    bytes = 0;
+    for (int l = 0; l < n && hi[l] > lo[l] && hi[l + 1] > lo[l + 1];) {
+        const Geom &g = net.g[l];
+        const int lv = l + 1;
+        if (P.n == kPassMax) return false;
+        EagerPassStep &L = P.st[P.n++];
+        L = EagerPassStep{};
+        L.layer = l; L.n_layers = n;
+        L.n_in = (int)(hi[l] - lo[l]);
+        L.row0 = (int)(lo[lv] & ~(int64_t)1);              // (no window of a pool lies in two groups)
+        L.n_groups = (int)((hi[lv] - L.row0 + 3) / 4);
+        if (L.n_groups > kPassGroups) return false;
+        L.band0 = L.row0 - 1 - (int)lo[l];
+        L.w = g.w_out; L.c_in = g.c_in; L.c_out = g.c_out; L.act = g.act; L.shr = g.shr; L.clamp_hi = g.clamp_hi;
+        const uint32_t row_bytes = (uint32_t)E.row_elems[lv] * 4;
+        L.c = E.ws + E.c_off[lv]; L.c_stride = (int64_t)E.cd_rows[lv] * E.row_elems[lv];
+        for (int i = 0; i < 4 * L.n_groups + 2; ++i) {
+            const int y = L.row0 + i;
+            if (y - 1 >= lo[l] && y - 1 < hi[l]) L.rows_in |= 1u << i;
+            if (i == 4 * L.n_groups) { if (y >= lo[l] && y < hi[l]) L.rows_in |= 2u << i; break; }
+            if (y >= lo[lv] && y < hi[lv]) L.rows_on |= 1u << i;
+            if (y < std::min(seen_hi[lv], hi[lv])) L.rows_old |= 1u << i;
+            L.c_off[i] = (uint32_t)(y % E.cd_rows[lv]) * row_bytes;
+        }
+        L.ann = lv < n ? nullptr : E.ws + E.ann_off[lv];
+        L.ann_stride = (int64_t)E.ann_rows[lv] * E.row_elems[lv];
+        L.w_frag = s->ws + s->wm_off[l];
+        L.out_w = g.w_out;
+        L.out_first = L.row0 - (int)lo[lv];
+        bytes += (double)(hi[lv] - lo[lv]) * E.row_elems[lv] * (L.ann ? 12.0 : 8.0);
+        ++l;
+        if (l < n && net.g[l].kind == IDF_MAXPOOL) {
+            const int pv = l + 1;
+            L.pool = 1; L.out_w = net.g[l].w_out;
+            L.out_first = L.row0 / 2 - (int)lo[pv];
+            L.pool_ann = E.ws + E.ann_off[pv]; L.pool_ann_stride = (int64_t)E.ann_rows[pv] * E.row_elems[pv];
+            for (int i = 0; i < 2 * L.n_groups; ++i) {
+                const int o = L.row0 / 2 + i;
+                if (o >= lo[pv] && o < hi[pv]) L.pool_on |= 1u << i;
+                L.pool_off[i] = (uint32_t)(o % E.ann_rows[pv]) * (uint32_t)E.row_elems[pv] * 4;
+            }
+            bytes += (double)(hi[pv] - lo[pv]) * E.row_elems[pv] * 4.0;
+            ++l;
+        }
+        L.emit = l < n && hi[l] > lo[l] && hi[l + 1] > lo[l + 1];
+    }
+    return P.n > 0 && eager_pass_shape(net.precision, P);
+}
+
+// A net whose segments one launch takes through all layers: 3x3 conv layers the matrix cores serve and a 2x2 pool
+// behind any of them; no biases (rings, every row starts from zero); differences that fit the operands -- a bfloat16
+// net's do not, and an int8 net must clamp what it passes on.  The switches that choose between the kernels for single
+// layers choose those.
+bool eager_one_launch(const idf_streams *s)
+{
+    const idf_net &net = *s->net;
+    const bool ring = s->eager.ring;
+    const int n = (int)net.g.size();
+    if (!ring || net.precision == IDF_PREC_BF16 || n > 2 * kPassMax) return false;
+    for (const char *e : {"IDF_EAGER_PLAIN", "IDF_EAGER_TILED", "IDF_EAGER_POS", "IDF_NO_MFMA"})
+        if (getenv(e)) return false;
+    for (int l = 0; l < n; ++l) {
+        const Geom &g = net.g[l];
+        if (g.kind == IDF_MAXPOOL) {
+            if (l == 0 || net.g[l - 1].kind != IDF_CONV || g.k_w != 2 || g.s_w != 2) return false;
+            continue;
+        }
+        if (net.wm_img[l].empty() || (l > 0 && g.c_in < 16)) return false;
+        if (net.precision == IDF_PREC_I8 && l + 1 < n && g.act != IDF_ACT_RELU_SHR_CLAMP) return false;
+    }
+    // every segment of this opening has to go this way: announced values of conv layers are then nowhere kept but in the state
+    std::vector<int64_t> lo, hi, seen_lo, seen_hi;
+    EagerPass P;
+    double bytes;
+    for (int64_t a = 0; a < net.in_h; ++a) {
+        const int64_t b = std::min<int64_t>(a + s->max_seg, net.in_h);
+        eager_bands(net, a, b, false, lo, hi);
+        eager_bands(net, 0, a, false, seen_lo, seen_hi);
+        if (!eager_pass_plan(s, nullptr, (int)(b - a), a, lo, hi, seen_hi, P, bytes)) return false;
+        // One workgroup per stream: at float32 it does 160 multiply-adds per ns, where a launch per layer takes some 14 us
+        // for each layer as long as the streams are few (one stream of 32-32-64-64 channels: 57 us against about 70 at
+        // 64 positions, 108 against 73 at 128; with 64 streams the two are even there).  The quantised nets are ahead
+        // at any size that fits (one stream of 224 positions: 62 us against 158).
+        double macs = 0;
+        for (int k = 0; k < P.n; ++k) macs += 9.0 * P.st[k].n_in * 16 * P.st[k].n_xt * P.st[k].c_in * P.st[k].c_out;
+        if (net.precision == IDF_PREC_F32 && s->B < 64 && macs > 160e3 * 14 * n) return false;
+    }
+    return true;
+}
+
 // One pass of eager emission for a selection of streams: the input rows [a, b) (pushed rows, or
 // none when only the biases announce themselves) and, layer by layer, the band of rows they reach.
 int eager_pass(idf_streams *s, const StreamSel &sel, const void *dev_rows, int n_rows, int64_t a, int64_t b, bool init_bias)
@@ -1363,6 +1467,13 @@ int eager_pass(idf_streams *s, const StreamSel &sel, const void *dev_rows, int n
     eager_bands(net, a, b, init_bias, lo, hi);
     eager_bands(net, 0, a, false, seen_lo, seen_hi);          // seen_hi[lv]: rows of level lv reached before this pass
     const int round_bf16 = net.precision == IDF_PREC_BF16;
+    if (E.one_launch && dev_rows && !init_bias) {
+        EagerPass P;
+        double bytes = 0;
+        if (!eager_pass_plan(s, dev_rows, n_rows, a, lo, hi, seen_hi, P, bytes)) return fail(IDF_ESTATE, "internal: a segment does not fit one launch");
+        hipError_t e = launch_eager_pass(net.precision, P, sel, launch_ctx(s, kKindEager, bytes * sel.n, 0));
+        return e == hipSuccess ? (int)IDF_OK : dev_fail(e, "eager launch");
+    }
     auto fresh_from = [&](int lv) { return E.ring ? (int)seen_hi[lv] : (int)E.rows[lv]; };    // whole maps are cleared when a sample begins
     if (dev_rows) {
         EagerStep st{};
@@ -2239,6 +2350,7 @@ int idf_enable_eager(idf_streams *s, void *dev_workspace, size_t workspace_bytes
         if (h.r != 0 || h.out_written != 0 || h.x_next != 0) return fail(IDF_ESTATE, "eager emission must be enabled before the first push");
     eager_layout(*s->net, s->B, s->max_seg, &s->eager);
     s->eager.ws = (char *)dev_workspace;
+    s->eager.one_launch = eager_one_launch(s);
     s->eager.on = true;
     return IDF_OK;
 }
@@ -2272,10 +2384,12 @@ int idf_read_announced(idf_streams *s, int level, const int32_t *stream_ids, int
     int rc = check_ids(s, stream_ids, n_ids);
     if (rc != IDF_OK) return rc;
     const size_t bytes = (size_t)s->eager.rows[level] * s->eager.row_elems[level] * 4;
-    for (int i = 0; i < n_ids; ++i) {
+    // streams lie side by side, as they do in the output: one copy per run of ids
+    for (int i = 0, run; i < n_ids; i += run) {
         const int id = stream_ids ? stream_ids[i] : i;
+        for (run = 1; i + run < n_ids && (stream_ids ? stream_ids[i + run] : i + run) == id + run; ++run) {}
         hipError_t e = hipMemcpyAsync((char *)dev_out + (size_t)i * bytes, s->eager.ws + s->eager.ann_off[level] + (size_t)id * bytes,
-                                      bytes, hipMemcpyDeviceToDevice, s->st);
+                                      bytes * run, hipMemcpyDeviceToDevice, s->st);
         if (e != hipSuccess) return dev_fail(e, "read_announced");
     }
     return IDF_OK;
@@ -2303,6 +2417,12 @@ int idf_read_announced_rows(idf_streams *s, int level, const int32_t *stream_ids
         const int64_t first = whole ? 0 : std::max<int64_t>(0, reached - E.ann_rows[level]);
         const int64_t cnt = std::min<int64_t>(reached - first, max_rows);
         first_row[i] = first; n_rows[i] = (int32_t)cnt;
+        if (E.one_launch && level > 0 && level < n && s->net->g[level - 1].kind == IDF_CONV) {      // not kept: f of the state
+            hipError_t e = launch_eager_announced(s->net->precision, s->net->g[level - 1], s->eager.ws + E.c_off[level] + (size_t)id * E.cd_rows[level] * row_bytes,
+                                                  E.cd_rows[level], first, (int)cnt, (char *)dev_out + (size_t)i * max_rows * row_bytes, s->st);
+            if (e != hipSuccess) return dev_fail(e, "read_announced_rows");
+            continue;
+        }
         const char *src = s->eager.ws + E.ann_off[level] + (size_t)id * E.ann_rows[level] * row_bytes;
         for (int64_t r = first; r < first + cnt; ++r) {         // (a ring wraps: row by row)
             hipError_t e = hipMemcpyAsync((char *)dev_out + ((size_t)i * max_rows + (size_t)(r - first)) * row_bytes,

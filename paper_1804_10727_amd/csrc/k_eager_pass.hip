@@ -1,0 +1,382 @@
+// Eager emission of one segment through a whole net of 3x3 / stride 1 / same-padded conv layers and 2x2
+// max-pools in one launch: a workgroup takes one stream from the pushed rows to the output.
+//
+// A segment's events are a band of a few rows per layer, so layer by layer the work is small and the time
+// went into launches, into memory round trips between them and into finding the events: the 8 conv layers
+// of the int8 network at 8 streams of 112 x 112 took 8 launches of 20 us.  Here
+//   * the differences announced by a layer stay in LDS for the next one, which multiplies all of them on
+//     the matrix cores (float32 as 16x16x4, int8 as 16x16x64: differences of values in 0..127 are int8
+//     again, and exact).  A wave takes 16 channels x 16 positions of four rows of the layer (the first
+//     of them even, so that no window of a pool is divided), and of those only what the band reaches;
+//   * what a cell had announced is f of the state it had, so only the state is read; a pool's windows are
+//     maxima of two rows in registers and one exchange of lanes;
+//   * between layers there is one barrier over LDS; the stores of state and announced values are not waited for.
+// What bounds it is the chain: every layer is a memory round trip for its weights, a few dozen matrix
+// instructions and about a hundred others per wave, one after the other.  Hence sixteen waves with small shares
+// (eight waves with all the rows of a band each took 1.3 times as long), one copy of the code for every layer,
+// which then stays in the instruction cache, and weights and state on their way before the barrier.
+// Measured per pushed row, layer by layer before: int8, 8 streams of 112 x 112, 38 us (170); float32, 256 streams of
+// 32 x 32, 35 us (112), of which 18 us are matrix instructions.
+#include <algorithm>
+#include <type_traits>
+
+#include "idf.h"
+#include "idf_kernels.h"
+#include "mfma_tile.h"
+
+namespace idf {
+
+namespace {
+
+typedef const __attribute__((address_space(4))) EagerPassStep PassStep;
+typedef const __attribute__((address_space(4))) EagerPass PassArgs;
+
+constexpr int kPassWaves = 16, kPassThreads = 64 * kPassWaves;
+constexpr int kQueue = 3;                        // K-steps whose weights are on their way
+
+extern __shared__ __attribute__((aligned(16))) unsigned char pass_smem[];
+
+// ---- the pushed rows: announced values, events, and the first layer's delta band ---------------------
+template <class T> __device__ __forceinline__ void pass_input(PassArgs &a, PassStep &L, int stream, int pos, uint32_t *events)
+{
+    using ev_t = typename T::ev_t; using st_t = typename T::st_t;
+    const int tid = threadIdx.x, W = L.w, C = L.c_in, n_rows = L.n_in, row_elems = W * C;
+    const ev_t *src = (const ev_t *)a.in + (int64_t)pos * a.in_stride;
+    st_t *ann = (st_t *)a.ann0 + (int64_t)stream * a.ann0_stride;
+    unsigned char *out = pass_smem + L.lds_in;
+    const int XP = 16 * L.n_xt + 2;
+    uint32_t ev = 0;
+    int slot = a.ann0_slot;
+    for (int r = 0; r < n_rows; ++r) {
+        for (int i = tid; i < row_elems; i += kPassThreads) {
+            const ev_t v = src[r * row_elems + i];
+            ann[(int64_t)slot * row_elems + i] = (st_t)v;
+            ev += T::ev_nonzero(v);
+        }
+        slot = slot + 1 == a.ann0_rows ? 0 : slot + 1;
+    }
+    if (L.cells > 0) {                             // whole cells: [row][position, one of halo in front][channel]
+        const int cells = L.cells, n = XP * cells;
+        for (int r = 0; r < n_rows; ++r)
+            for (int i = tid; i < n; i += kPassThreads) {
+                const int p = i / cells, c = i - p * cells, x = p - 1;
+                i32x4 v = {0, 0, 0, 0};
+                if (x >= 0 && x < W) v = reinterpret_cast<const i32x4 *>(src)[(r * W + x) * cells + c];
+                *reinterpret_cast<i32x4 *>(out + r * L.in_pitch + p * L.in_stride + c * 16) = v;
+            }
+    } else {                                       // few channels: the windows the positions see, 3 * C values padded to cells
+        auto windows = [&](auto n_tag) IDF_INLINE {
+            constexpr int NC = decltype(n_tag)::value, WC = (3 * NC + T::VL - 1) / T::VL;
+            const int XT = 16 * L.n_xt;
+            // (a wave takes whole rows: the waves are many and a row is short)
+            for (int r = tid >> 6; r < n_rows; r += kPassWaves)
+              for (int p = tid & 63; p < XT; p += 64) {
+                ev_t val[WC * T::VL];
+#pragma unroll
+                for (int k = 0; k < WC * T::VL; ++k) val[k] = 0;
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx) {
+                    const int x = p - 1 + kx, xc = x < 0 ? 0 : (x >= W ? W - 1 : x);
+#pragma unroll
+                    for (int ci = 0; ci < NC; ++ci) {
+                        const ev_t v = src[(r * W + xc) * NC + ci];
+                        val[kx * NC + ci] = x == xc ? v : (ev_t)0;
+                    }
+                }
+                i32x4 w[WC];
+                __builtin_memcpy(w, val, sizeof(w));
+#pragma unroll
+                for (int k = 0; k < WC; ++k) *reinterpret_cast<i32x4 *>(out + r * L.in_pitch + p * L.in_stride + k * 16) = w[k];
+            }
+        };
+        switch (C) {
+        case 1: windows(std::integral_constant<int, 1>{}); break;
+        case 2: windows(std::integral_constant<int, 2>{}); break;
+        case 3: windows(std::integral_constant<int, 3>{}); break;
+        default: windows(std::integral_constant<int, 4>{}); break;
+        }
+    }
+    ev = wave_sum(ev);
+    if ((tid & 63) == 0 && ev) atomicAdd(events, ev);
+}
+
+// ---- one conv layer, and the 2x2 max-pool behind it ------------------------------------------------------
+template <class T> struct Activation {
+    using st_t = typename T::st_t;
+    st_t lo, hi;
+    int shr;
+    bool none;
+    __device__ __forceinline__ explicit Activation(PassStep &L)
+    {
+        none = L.act == IDF_ACT_NONE;
+        lo = 0; hi = 0; shr = 0;
+        if constexpr (T::EB == 1) {                // one shift and two bounds serve all three kinds
+            lo = none ? INT32_MIN : 0;
+            hi = L.act == IDF_ACT_RELU_SHR_CLAMP ? L.clamp_hi : INT32_MAX;
+            shr = L.act == IDF_ACT_RELU_SHR_CLAMP ? L.shr : 0;
+        }
+    }
+    __device__ __forceinline__ st_t operator()(st_t c) const
+    {
+        if constexpr (T::EB == 1) return min(max(c >> shr, lo), hi);
+        else return none ? c : fmaxf(c, 0.f);
+    }
+};
+
+template <class T> __device__ __forceinline__ void pass_conv(PassStep &L, int stream, uint32_t *events)
+{
+    using acc_t = typename T::acc_t; using st_t = typename T::st_t;
+    const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6), m = lane & 15, g = lane >> 4;
+    const int W = L.w, C_out = L.c_out, n_ct = L.n_ct, n_xt = L.n_xt, tasks = n_ct * n_xt * L.n_groups;
+    const bool single = C_out == 16;
+    const uint32_t w_kstep = single ? 3 * 1024 : (uint32_t)((C_out + 31) >> 5) * 6144, w_ky = single ? 1024 : 2048;
+    st_t *c_map = (st_t *)L.c + (int64_t)stream * L.c_stride;
+
+    acc_t old[4];                                  // states as they were
+    i32x4 wq[kQueue][3];
+    const unsigned char *w_next = nullptr;
+    int ks_left = 0, xt = 0, gi = 0, x = 0, co0 = 0;
+    uint32_t cell = 0;                             // this lane's first channel, bytes into a row
+    uint32_t c_off[4];
+    bool here = false;
+    auto fetch_w = [&](i32x4 (&w)[3]) IDF_INLINE {
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) w[ky] = *at4(reinterpret_cast<const i32x4 *>(w_next), (uint32_t)(lane * 16 + ky * w_ky));
+        if (--ks_left > 0) w_next += w_kstep;
+    };
+    // everything a task needs from memory is asked for before its cells are
+    auto begin = [&](int t) IDF_INLINE {
+        const int rest = L.ct_rcp ? (int)__umulhi((unsigned)t, L.ct_rcp) : t, ct = t - rest * n_ct;
+        gi = L.xt_rcp ? (int)__umulhi((unsigned)rest, L.xt_rcp) : rest;
+        xt = rest - gi * n_xt;
+        x = xt * 16 + m;
+        co0 = single ? g * 4 : (ct >> 1) * 32 + g * 8 + (ct & 1) * 4;
+        here = x < W && co0 < C_out;
+        cell = here ? (uint32_t)(x * C_out + co0) * 4 : 0;
+        w_next = (const unsigned char *)L.w_frag + (single ? 0 : (ct >> 1) * 6144 + (ct & 1) * 1024);
+        ks_left = L.n_ksteps;
+#pragma unroll
+        for (int d = 0; d < kQueue; ++d) fetch_w(wq[d]);        // past the end the last one again
+        // (rows without a state are read like the others: their places exist)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            c_off[j] = L.c_off[gi * 4 + j];
+            old[j] = *at4(reinterpret_cast<const acc_t *>((const char *)c_map + c_off[j]), cell);
+        }
+    };
+    int t = wave;
+    if (t < tasks) begin(t);
+    lds_barrier();                                 // the band is there, and nobody reads what this layer overwrites any more
+    const Activation<T> act(L);
+    if (L.emit) {
+        // what is passed on has zeros in front of each row, and behind it as far as no lane of the tiles reaches
+        const int cells_out = L.out_stride >> 4, end = L.out_pitch / L.out_stride, done = L.pool ? L.out_w : 16 * n_xt;
+        for (int r = wave; r < L.out_rows; r += kPassWaves) {
+            unsigned char *row = pass_smem + L.lds_out + r * L.out_pitch;
+            for (int c = lane; c < cells_out; c += 64) {
+                *reinterpret_cast<i32x4 *>(row + c * 16) = i32x4{0, 0, 0, 0};
+                for (int p = done + 1; p < end; ++p) *reinterpret_cast<i32x4 *>(row + p * L.out_stride + c * 16) = i32x4{0, 0, 0, 0};
+            }
+        }
+    }
+    uint32_t ev = 0, ev_pool = 0;
+    for (; t < tasks;) {
+        acc_t acc[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] = acc_t{0, 0, 0, 0};
+        {
+            const int cells = L.cells, n_ksteps = L.n_ksteps, in_stride = L.in_stride, win_cells = L.win_cells;
+            const uint32_t rows_in = L.rows_in >> (4 * gi);    // bit r: row r - 1 of the four (-1 .. 4) is in the band
+            // where the six rows lie (those outside the band: somewhere inside)
+            const unsigned char *row[6];
+#pragma unroll
+            for (int r = 0; r < 6; ++r) {
+                int b = L.band0 + 4 * gi + r;
+                b = b < 0 ? 0 : (b >= L.n_in ? L.n_in - 1 : b);
+                row[r] = pass_smem + L.lds_in + b * L.in_pitch + (xt * 16 + m) * in_stride;
+            }
+            auto kstep = [&](const i32x4 (&w)[3], uint32_t off) IDF_INLINE {
+                i32x4 xv[6];
+#pragma unroll
+                for (int r = 0; r < 6; ++r) xv[r] = *reinterpret_cast<const i32x4 *>(row[r] + off);
+#pragma unroll
+                for (int r = 0; r < 6; ++r) {
+                    if (!((rows_in >> r) & 1u)) continue;
+#pragma unroll
+                    for (int e = 0; e < T::kInst; ++e)
+#pragma unroll
+                        for (int ky = 0; ky < 3; ++ky)
+                            if (r - ky >= 0 && r - ky < 4) acc[r - ky] = T::mfma(w[ky], xv[r], acc[r - ky], e);
+                }
+            };
+            // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column (past the end the
+            // last one again: the weights there are zero); few channels: the cells of the gathered window
+            auto at = [&](int st) IDF_INLINE {
+                int q = 4 * st + g;
+                if (cells == 0) return (uint32_t)(q < win_cells ? q : win_cells - 1) * 16;
+                q = q < 3 * cells ? q : 3 * cells - 1;
+                const int kx = (q >= cells) + (q >= 2 * cells);
+                return (uint32_t)(kx * in_stride + (q - kx * cells) * 16);
+            };
+#pragma unroll 1
+            for (int st = 0; st < n_ksteps; st += kQueue) {
+#pragma unroll
+                for (int d = 0; d < kQueue; ++d) {
+                    if (st + d >= n_ksteps) continue;
+                    kstep(wq[d], at(st + d));
+                    if (st + d + kQueue < n_ksteps) fetch_w(wq[d]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+        // the state moves on; what is announced is f of it, less f of what it was
+        const uint32_t on = L.rows_on >> (4 * gi), had = L.rows_old >> (4 * gi);
+        unsigned char *out = pass_smem + L.lds_out + L.out_first * L.out_pitch + co0 * T::EB;
+        const bool out_ok = L.emit && co0 < C_out;
+        auto count = [&](const st_t (&d)[4], uint32_t &n) IDF_INLINE {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) n += (uint32_t)__builtin_popcountll(__ballot(d[i] != 0));
+        };
+        auto pass_on = [&](const st_t (&d)[4], unsigned char *to) IDF_INLINE {
+            uint32_t e[T::EB];
+            T::pack4(d, e);
+            if constexpr (T::EB == 1) *reinterpret_cast<uint32_t *>(to) = e[0];
+            else *reinterpret_cast<i32x4 *>(to) = i32x4{(int)e[0], (int)e[1], (int)e[2], (int)e[3]};
+        };
+        char *ann = L.ann ? (char *)L.ann + ((int64_t)stream * L.ann_stride + (int64_t)(L.row0 + 4 * gi) * W * C_out) * 4 : nullptr;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            acc_t h_new, h_old = {0, 0, 0, 0};
+            if ((had >> j) & 1u) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { acc[j][i] += old[j][i]; h_old[i] = act(old[j][i]); }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) h_new[i] = act(acc[j][i]);
+            if ((on >> j) & 1u) {
+                st_t d[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) d[i] = h_new[i] - h_old[i];
+                if (!here) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) d[i] = 0;
+                } else {
+                    *at4(reinterpret_cast<acc_t *>((char *)c_map + c_off[j]), cell) = acc[j];
+                    if (ann) *at4(reinterpret_cast<acc_t *>(ann + (int64_t)(j * W * C_out) * 4), cell) = h_new;
+                }
+                if (L.layer + 1 < L.n_layers) count(d, ev);
+                if (!L.pool && out_ok) pass_on(d, out + (4 * gi + j) * L.out_pitch + (x + 1) * L.out_stride);
+            }
+            // rows that have not been reached announce zero (and have nothing in acc or old)
+            acc[j] = h_new; old[j] = h_old;
+        }
+        if (L.pool) {
+            const bool mine = (x & 1) == 0 && (x >> 1) < L.out_w && co0 < C_out;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                if (!((L.pool_on >> (2 * gi + p)) & 1u)) continue;
+                acc_t n;
+                st_t d[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const st_t nn = acc[2 * p][i] > acc[2 * p + 1][i] ? acc[2 * p][i] : acc[2 * p + 1][i];
+                    const st_t oo = old[2 * p][i] > old[2 * p + 1][i] ? old[2 * p][i] : old[2 * p + 1][i];
+                    const st_t nx = neighbour(nn), ox = neighbour(oo);
+                    n[i] = nn > nx ? nn : nx;
+                    d[i] = mine ? n[i] - (oo > ox ? oo : ox) : (st_t)0;
+                }
+                count(d, ev_pool);
+                if (mine) *at4(reinterpret_cast<acc_t *>((char *)L.pool_ann + (int64_t)stream * L.pool_ann_stride * 4 + L.pool_off[2 * gi + p]),
+                               (uint32_t)((x >> 1) * C_out + co0) * 4) = n;
+                if (L.emit && mine) pass_on(d, out + (2 * gi + p) * L.out_pitch + ((x >> 1) + 1) * L.out_stride);
+            }
+        }
+        t += kPassWaves;
+        if (t < tasks) begin(t);
+    }
+    if (lane == 0) {
+        if (ev) atomicAdd(events, ev);
+        if (ev_pool) atomicAdd(events + 1, ev_pool);
+    }
+}
+
+template <class T>
+__global__ void __launch_bounds__(kPassThreads, 4) k_eager_pass(const EagerPass args, const StreamSel sel)
+{
+    // the arguments are read where the launch put them, a step at a time (by value they would be copied to scratch memory)
+    PassArgs &a = *(PassArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    __shared__ uint32_t events[2 * kPassMax + 2];      // per level
+    const int tid = threadIdx.x, stream = sel_stream(sel, blockIdx.x);
+    if (tid < 2 * kPassMax + 2) events[tid] = 0;
+    lds_barrier();
+    pass_input<T>(a, a.st[0], stream, sel.pos0 + (int)blockIdx.x, &events[0]);
+    const int n = a.n;
+#pragma unroll 1
+    for (int k = 0; k < n; ++k) {
+        PassStep &L = a.st[k];
+        pass_conv<T>(L, stream, &events[L.layer + 1]);
+    }
+    lds_barrier();
+    if (tid < a.n_layers && events[tid]) atomicAdd(a.stats + ((int64_t)stream * a.n_layers + tid) * 2, (unsigned long long)events[tid]);
+}
+
+template <class T>
+__global__ void __launch_bounds__(256) k_eager_announced(const typename T::st_t *c, int c_rows, int64_t first, int64_t row, int act, int shr, int hi, typename T::st_t *out)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < row) out[blockIdx.y * row + i] = T::activate(c[(first + blockIdx.y) % c_rows * row + i], act, shr, hi);
+}
+
+}  // namespace
+
+// Lays the bands out in LDS; false where they do not fit.
+bool eager_pass_shape(int prec, EagerPass &a)
+{
+    const int vl = conv3x3_mfma_vl(prec), eb = 16 / vl;
+    size_t lds = 0, size[kPassMax + 1] = {};
+    auto rcp32 = [](int n) { return n > 1 ? (unsigned)((0x100000000ull + n - 1) / n) : 0u; };
+    for (int k = 0; k < a.n; ++k) {
+        EagerPassStep &L = a.st[k];
+        L.n_xt = (L.w + 15) / 16;
+        L.n_ct = L.c_out == 16 ? 1 : 2 * ((L.c_out + 31) / 32);
+        L.xt_rcp = rcp32(L.n_xt); L.ct_rcp = rcp32(L.n_ct);
+        L.cells = L.c_in % vl == 0 ? L.c_in / vl : 0;
+        L.win_cells = L.cells ? 0 : (3 * L.c_in + vl - 1) / vl;
+        L.n_ksteps = L.cells ? (3 * L.cells + 3) / 4 : 1;
+        L.in_stride = cell_stride(L.cells ? L.c_in * eb / 16 : L.win_cells) * 16;
+        L.in_pitch = (16 * L.n_xt + 2) * L.in_stride;
+        size[k] = (size_t)L.n_in * L.in_pitch;
+        if (k > 0) { a.st[k - 1].out_stride = L.in_stride; a.st[k - 1].out_pitch = L.in_pitch; a.st[k - 1].out_rows = L.n_in; }
+    }
+    for (int k = 0; k < a.n; ++k) lds = std::max(lds, size[k] + size[k + 1]);
+    if (lds > 160 * 1024 - 512) return false;
+    for (int k = 0; k < a.n; ++k) {                // bands lie alternately at the bottom and at the top
+        a.st[k].lds_in = k & 1 ? (int)(lds - size[k]) : 0;
+        a.st[k].lds_out = k & 1 ? 0 : (int)(lds - size[k + 1]);
+    }
+    a.lds = (int)lds;
+    return true;
+}
+
+hipError_t launch_eager_pass(int prec, const EagerPass &a, const StreamSel &sel, const LaunchCtx &lc)
+{
+    auto go = [&](auto kernel) {
+        static hipError_t prepared = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 512);
+        if (prepared != hipSuccess) return prepared;
+        return launch(kernel, dim3(sel.n), dim3(kPassThreads), (size_t)a.lds, lc, a, sel);
+    };
+    return prec == IDF_PREC_I8 ? go(k_eager_pass<TraitsI8>) : go(k_eager_pass<TraitsF32>);
+}
+
+hipError_t launch_eager_announced(int prec, const Geom &g, const void *c, int c_rows, int64_t first, int n, void *out, hipStream_t st)
+{
+    if (n <= 0) return hipSuccess;
+    const int64_t row = (int64_t)g.w_out * g.c_out;
+    const dim3 grid((unsigned)((row + 255) / 256), (unsigned)n), block(256);
+    LaunchCtx lc;
+    lc.st = st;
+    if (prec == IDF_PREC_I8) return launch(k_eager_announced<TraitsI8>, grid, block, 0, lc, (const int32_t *)c, c_rows, first, row, g.act, g.shr, g.clamp_hi, (int32_t *)out);
+    return launch(k_eager_announced<TraitsF32>, grid, block, 0, lc, (const float *)c, c_rows, first, row, g.act, g.shr, g.clamp_hi, (float *)out);
+}
+
+}  // namespace idf
