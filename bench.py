@@ -37,7 +37,7 @@ KERNEL_PEAK = {
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
-KERNEL_SYMBOL = {"cascade1d": "k_cascade1d", "conv3x3_mfma": "k_conv3x3_mfma", "conv_generic": "k_conv_generic"}
+KERNEL_SYMBOL = {"cascade1d": "k_conv_gather", "conv3x3_mfma": "k_conv3x3_mfma", "conv_generic": "k_conv_generic"}
 
 
 def sources_digest():

@@ -124,99 +124,6 @@ struct PoolStep {
     int n_layers;
 };
 
-// Whole-net cascade for 1-D nets (one launch per push).
-constexpr int kCasThreads = 256;     // four waves: two workgroups share a CU
-constexpr int kCasKMax = 9;        // kernel height at most
-constexpr int kCasRowsMax = 16;    // rows a layer receives per push at most
-constexpr int kCasMaxLayers = 8;
-constexpr int kCasSlotsMax = kCasRowsMax + kCasKMax - 1;   // output rows a layer touches per push at most
-constexpr int kCasAhead = 4;       // input channels whose weights are in flight per lane
-
-// Lanes of the cascade's workgroup take the output channels (padded to a power of two) and
-// split the input channels round-robin over the kCasThreads / pad groups that result; every
-// lane runs the same number of steps, a multiple of kCasAhead, and the weight packing is
-// zero padded to the input channels those steps reach.
-IDF_HD int cascade1d_steps(int c_in, int c_out)
-{
-    int cp = 1;
-    while (cp < c_out) cp *= 2;
-    const int n_grp = kCasThreads / cp;
-    const int n_q = (c_in + n_grp - 1) / n_grp;
-    return (n_q + kCasAhead - 1) / kCasAhead * kCasAhead;
-}
-IDF_HD int cascade1d_cin_pad(int c_in, int c_out)
-{
-    int cp = 1;
-    while (cp < c_out) cp *= 2;
-    return kCasThreads / cp * cascade1d_steps(c_in, c_out);
-}
-
-// What a cascade launch needs to know of a layer whatever the segment.
-struct CascadeLayer {
-    int cp_log;              // log2 of c_out rounded up to a power of two
-    int c_in, c_out, k_h, s_h, act;
-    int steps;               // cascade1d_steps(c_in, c_out)
-    int ring_floats;         // k_h * c_out
-    int rcp_k;               // ceil(65536 / k_h): (v * rcp_k) >> 16 == v / k_h for the small v that occur
-    const void *w;           // cascade packing, see cascade1d_weight_index
-    const void *bias;
-    void *ring;              // this launch's first stream is at ring + stream * ring_stride floats
-    int64_t ring_stride;
-};
-
-// One step of one layer, in small integers: the new input rows of one pushed segment or of
-// several consecutive ones taken together.  Accumulator slot t stands for output row o_base + t.
-struct CascadeStep {
-    signed char cnt;             // new input rows (0: the layer does not fire)
-    signed char t_lo, t_fin, t_hi;   // slots [t_lo, t_hi) are live; those below t_fin become final
-    signed char d0;              // first input row of slot 0 minus the first new row
-    signed char at_start;        // 1: the first new row is row 0 of the sample
-    signed char rho;             // (first new row + padding) mod stride
-    signed char slot0;           // ring slot of accumulator slot 0 (slot of t is (slot0 + t) mod k_h)
-    signed char seg0, seg_rows;  // first layer of stage 0: the new rows are seg_rows rows each of the pushed segments seg0, seg0 + 1, ...
-    short fma_per_channel;       // multiply-adds a lane issues for one input channel that holds an event (all rows, all taps)
-    short in_off, out_off;       // rows: where a stage's first layer finds its rows in the hand-over buffer of the stage before,
-                                 // and where its last layer puts the rows it hands over (both counted from the launch's first row)
-    unsigned char taps4[kCasRowsMax / 2];   // per new row, four bits each: kernel taps landing inside the output
-};
-IDF_HD int cascade_taps(const CascadeStep &s, int j) { return (s.taps4[j >> 1] >> ((j & 1) * 4)) & 15; }
-
-// The layers can be dealt to up to kCasMaxStages groups of workgroups (blockIdx.y) that run side
-// by side in one launch, stage s working on the segments pushed s launches earlier: its first
-// layer reads what stage s-1 wrote in the launch before (double-buffered by launch parity).
-// A launch can take several segments of every stream at once (segments pushed in step and held
-// back until there are enough of them): a stage then takes as many consecutive ones together as
-// fit the rows one step can take, and runs the resulting steps one after the other with its
-// layers' rolling buffers staying in LDS in between.
-constexpr int kCasMaxStages = 8;
-constexpr int kCasSegMax = 16;       // pushed segments one launch can take
-constexpr int kCasStepMax = 8;       // steps a stage runs in one launch
-
-// (NSTEP: steps of room in the block; a launch of one step per stage passes the short form, whose fields lie where the long one's do)
-template <int NSTEP> struct CascadeArgsT {
-    int n_layers;
-    int n_stages;
-    int stage_lo[kCasMaxStages + 1];     // stage s runs layers [stage_lo[s], stage_lo[s+1])
-    int stage_steps[kCasMaxStages];      // steps stage s runs in this launch (0: nothing has reached it)
-    int steps_max;                       // the largest of them
-    int transit_wr;                      // parity of the hand-over buffers written by this launch
-    int per;                             // filled by the launcher: streams side by side in blockIdx.x
-    CascadeLayer layer[kCasMaxLayers];
-    CascadeLayer first[kCasMaxStages];   // filled by the launcher: first[s] = layer[stage_lo[s]], first_step[s] = step[0][stage_lo[s]],
-    CascadeStep first_step[kCasMaxStages];   // so that a workgroup finds them from its stage alone, in its first round of loads
-    const void *in[kCasSegMax];          // stage 0: pushed segment q as [position][rows][c0]
-    int in_stream_stride[kCasSegMax];    // elements
-    void *transit;                       // hand-over rows [boundary][parity][stream][row][channel]
-    int64_t transit_stream_stride, transit_buf_stride;   // floats
-    void *out;                           // output area [stream][out_cap][c_out]
-    int64_t out_stride, out_cap;
-    int64_t out_slot0[kCasStepMax];      // of the steps the last stage runs
-    unsigned long long *stats;
-    unsigned long long *issued;          // [stream][layer]: multiply-adds issued (all rows of every channel that holds an event)
-    CascadeStep step[NSTEP][kCasMaxLayers];   // step[m][l]: step m of layer l's stage (last in the block)
-};
-using CascadeArgs = CascadeArgsT<kCasStepMax>;
-
 // Output rows of one conv layer on the matrix cores (k_conv3x3_mfma.hip).  A layer keeps the rows of its
 // input that some output row still needs, as events, in a ring; an output row of c is formed in
 // registers once its last input row has arrived, activated and emitted.
@@ -306,6 +213,50 @@ struct EagerStep {
     int64_t c_stride, ann_stride, dlt_stride;   // elements per stream
     const void *w, *bias;
     unsigned long long *stats;
+};
+
+// Steps of the gathering matrix-core kernel (k_conv_gather.hip): rows of one layer to form, or the caller's rows to take in.
+constexpr int kGatherMax = 9;        // steps of a launch
+constexpr int kGatherSegs = 16;      // buffers of the caller a launch can take rows from
+constexpr int kBatchRows = 256;      // and rows
+struct GatherStep {
+    // (in the order a workgroup needs them: a scalar load brings 64 bytes)
+    int tiles, take;             // workgroups (set by the launcher); 1: the caller's rows are taken in
+    int n_ct, n_pt, spt_log;     // tiles of channels; of positions per stream or group of streams; streams per tile (log2)
+    unsigned ct_rcp;
+    int n_rows, y0;              // output rows (take: input rows): how many, first within its sample
+    int n_ks, cells;             // K-steps; cells of 16 bytes per position (channels padded)
+    unsigned cells_rcp;
+    int slot0, ring_rows;        // ring slot of the first row of the first window (take: of row y0); rows of the ring
+    int k_h, s_h_log;
+
+    int64_t ring_stride, dst_stride;       // elements per stream
+    void *ring, *dst;
+    const void *w_frag, *bias;
+    int h_in, p_h;
+    int dst_slot0, dst_rows;
+
+    int c_in, c_out, dst_cells, to_output;
+    int act, shr, clamp_hi, layer;
+    // the layer behind, whose events the emitted values are
+    int next_layer, next_c_out, nk_h, ns_h_log, np_h, nh_out;
+    int h_out, flat;             // flat: one position per row and kernel column (1-D)
+    // rows of many positions
+    int k_w, s_w_log, p_w, w_in, w_out, nk_w, ns_w_log, np_w, nw_out;
+    unsigned kw_rcp, wout_rcp;
+};
+struct GatherHead {
+    int end[8];                  // workgroups of the steps up to and with step i (the last step's own end is not needed)
+    int n, n_layers;
+    int sb_log, n_sb, n_sb8;     // streams in blocks of 1 << sb_log, each of which stays on an XCD (n_sb == 0: not)
+    unsigned sb_rcp;
+    int n_in, seg_rows, in_stride;     // the caller's buffers: how many, rows each brings; elements per stream
+    unsigned long long *stats, *issued;
+    const void *in[kGatherSegs];
+};
+template <int NS> struct GatherBatch {
+    GatherHead head;
+    GatherStep st[NS];
 };
 
 // Eager emission of a segment through a whole net in one launch (k_eager_pass.hip): its layers in order.

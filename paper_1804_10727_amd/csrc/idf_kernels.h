@@ -59,12 +59,8 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st);
 hipError_t launch_copy_out(const CopyOut &a, const StreamSel &sel, int64_t first_slot, int n_rows,
                            const LaunchCtx &lc);
 
-// Whole-net cascade for 1-D float32 nets: can it serve this net (rows_cap[l] = most rows layer
-// l emits per push)?
-bool cascade1d_eligible(int prec, const Geom *g, int n_layers, const int *rows_cap, int max_seg_rows);
-size_t cascade1d_weight_index(int c_in, int c_out, int ci, int co, int ky);
-int cascade1d_slot_off(int S, int rho);   // accumulator slot 0 relative to floor((y0 + p) / S)
-hipError_t launch_cascade1d(const CascadeArgs &a, const StreamSel &sel, const LaunchCtx &lc);
+// Does the gathering kernel take the whole of this 1-D net?
+bool cascade1d_eligible(int prec, const Geom *g, int n_layers, int max_seg_rows);
 
 // Matrix-core kernel for 3x3 / stride 1 / same-padded conv layers.
 int conv3x3_mfma_vl(int prec);
@@ -78,6 +74,13 @@ int conv3x3_mfma_event_cap();
 // Fills in how the workgroups of a step of a.n_rows rows lie (a.n_rows and a.ev_limit are set).
 void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, RowStep &a);
 hipError_t launch_conv3x3_mfma_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc);
+
+// Matrix-core kernel that gathers its windows from memory: any kernel size, strides 1, 2, 4 .., any padding.
+void conv_gather_layer(int prec, const Geom &g, GatherStep &a);
+void conv_gather_shape(bool first, GatherStep &a);
+size_t conv_gather_pack(int prec, const Geom &g, const void *w_khkwcico, void *out);
+// chain: the steps one after the other (a workgroup per stream), else all side by side.
+hipError_t launch_conv_gather(int prec, const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc);
 
 // Plain kernels that show what the machine delivers (copy, multiply-add chains, matrix-instruction
 // chains): bytes the compute kinds write for a launch of `blocks` workgroups, operations such a

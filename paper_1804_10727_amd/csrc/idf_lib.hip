@@ -88,6 +88,7 @@ struct RowUnit {
     bool pool = false, last = false;
     int next = -1;            // the unit that takes those rows (-1: the output area, or a layer of another kind)
     int ring_rows = 0;
+    int ring_room = 0, row_elems = 0;      // gathering kernel: rows the ring has memory for (ring_rows of them are in use); elements of a row
     size_t ring_off = 0;
     int64_t ring_stride = 0;
 };
@@ -113,7 +114,7 @@ struct idf_streams {
     int static_dev = -1;             // >= 0: the workspace is that device's static array (given back at close)
     int cus = 0;                     // compute units of the device the streams were opened on
     int ev_per_step = 0;             // int8 event path (idf_set_event_path): events a tile may hold per K-step of its contraction and still go that way; 0: off
-    bool use_cascade1d = false;      // whole-net kernel for 1-D nets instead of one launch per layer
+    bool use_cascade1d = false;      // 1-D net: its layers are units of the gathering kernel
     bool prof_on = false;
     std::vector<ProfRec> prof;
     std::vector<hipEvent_t> ev_pool;
@@ -134,31 +135,12 @@ struct idf_streams {
     char *head_units_ws = nullptr;   // caller's buffer: weights [unit][map], bias [unit], values [stream][unit]
     bool head_units_bias = false;
     int64_t out_stride = 0;
-    std::vector<std::vector<float>> cas_w;      // cascade packing of the weights (kept until the upload has run)
-    // 1-D cascade, layers dealt to stages that run side by side, stage k on the segments of the
-    // launch k launches earlier: the launches still on their way, newest first.  A launch holds
-    // one segment of every stream, or up to cas_batch of them when pushes in step are held back
-    // (idf_set_push_batching); cas_pending are the segments waiting for their launch.
-    struct CasSeg {
-        int64_t y0[kCasMaxLayers + 1];       // per layer: first of the rows the segment brings it (entry n_layers: first output row)
-        int cnt[kCasMaxLayers + 1];          // and how many
-        int64_t out_slot0 = 0; const void *dev_rows = nullptr; int n_rows = 0;
-    };
-    struct CasGroup {                                                            // n = 0: none
-        int n = 0; double bytes = 0; CasSeg seg[kCasSegMax];
-        void take(const CasGroup &o) { n = o.n; bytes = o.bytes; for (int q = 0; q < o.n; ++q) seg[q] = o.seg[q]; }
-    };
-    int cas_stages = 1;
-    int cas_lo[kCasMaxStages + 1] = {};
-    CasGroup cas_ring[kCasMaxStages];        // the launches on their way: the one k launches back is hist(k - 1)
-    int cas_head = 0;
-    CasGroup &hist(int k) { return cas_ring[(cas_head + k) % kCasMaxStages]; }
-    CasGroup cas_pending;
-    int cas_batch = 1;
-    CascadeLayer cas_layer[kCasMaxLayers];
-    int cas_parity = 0;
-    size_t cas_transit_off = 0;
-    int64_t cas_transit_stride = 0;
+    std::vector<std::vector<unsigned char>> gather_w;      // packed weights of the gathering kernel (kept until the upload has run)
+    std::vector<GatherStep> gather;             // per unit: what a step of it holds whatever the rows
+    // pushes of all streams in step that wait for their launch (idf_set_push_batching)
+    int batch = 1, batch_rows = 0;              // pushes per launch; rows a launch takes at most as the rings lie now
+    int held = 0, held_rows = 0;                // waiting buffers, and the rows each of them brings
+    const void *held_buf[kGatherSegs];
     // Layers on the matrix-core kernel.  Where it serves the whole net (stg2d) one launch per push holds a step
     // of every unit that has rows to form, each on rows that were complete before the launch.
     std::vector<RowUnit> units;
@@ -232,10 +214,7 @@ struct Layout {
     std::vector<RowUnit> units;
     size_t out_off = 0, stats_off = 0, issued_off = 0, head_off = 0, total = 0;
     int64_t out_stride = 0;
-    bool cascade1d = false;          // the whole-net 1-D kernel serves this stream set
-    size_t cas_transit_off = 0;      // hand-over rows between the cascade's stages
-    int64_t cas_transit_stride = 0;  // floats per stream in one hand-over buffer
-    int cas_boundaries = 0;          // stage boundaries the block has room for
+    bool cascade1d = false;          // the gathering kernel serves this 1-D net
     idf_sizes sizes{};
 };
 
@@ -297,14 +276,13 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
             launch_cap[l] = lcap = std::max(1, max_emit(net.g[l], lcap));
         }
     }
-    L.cascade1d = cascade1d_eligible(net.precision, net.g.data(), n, L.transit_cap.data(), max_seg);
+    L.cascade1d = cascade1d_eligible(net.precision, net.g.data(), n, max_seg);
     const bool all_mfma = net_all_mfma(net);
     L.mfma = mfma_layers(net);
     for (int l = 0; l < n; ++l) {
         if (net.g[l].kind != IDF_CONV) continue;
-        // the 1-D cascade reads its own packing, taps zero-padded to kCasKMax
-        size_t wsz = net.w_img[l].size();
-        if (L.cascade1d) wsz = (size_t)cascade1d_cin_pad(net.g[l].c_in, net.g[l].c_out) * net.g[l].c_out * kCasKMax * 4;
+        // (the gathering kernel reads a packing of its own)
+        const size_t wsz = L.cascade1d ? conv_gather_pack(net.precision, net.g[l], nullptr, nullptr) : net.w_img[l].size();
         L.w_off[l] = off; off = align_up(off + wsz);
         L.b_off[l] = off; off = align_up(off + net.b_img[l].size());
         L.wm_off[l] = off; off = align_up(off + net.wm_img[l].size());
@@ -318,7 +296,7 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
         // some row of c has yet to take in (they lie in the ring the layer before writes them to).
         if (g.kind == IDF_CONV) {
             L.ring_stride[l] = (int64_t)g.k_h * g.w_out * g.c_out;
-            if (!L.mfma[l]) { L.ring_off[l] = off; off = align_up(off + (size_t)L.ring_stride[l] * 4 * B); }
+            if (!L.mfma[l] && !L.cascade1d) { L.ring_off[l] = off; off = align_up(off + (size_t)L.ring_stride[l] * 4 * B); }
             state_per_stream += (size_t)L.ring_stride[l] * 4;
         } else {
             L.held_stride[l] = (int64_t)g.w_in * g.c_out;
@@ -363,21 +341,25 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     L.issued_off = off; off = align_up(off + (size_t)B * n * sizeof(unsigned long long));
     L.head_off = off; off = align_up(off + (size_t)B * net.out_c * 2 * sizeof(double));   // sums, means
     if (L.cascade1d) {
-        // Rows passed from one stage to the next, double-buffered by launch parity: room for a
-        // boundary behind every layer but the last, each as large as the largest hand-over.
-        int64_t most = 0;
-        for (int l = 0; l < n - 1; ++l) {
-            most = std::max<int64_t>(most, (int64_t)L.transit_cap[l] * net.g[l].c_out);
-            // what is alive between two pushes if every layer is a stage of its own
-            if (!strict_cascade()) handover_per_stream += (size_t)L.transit_cap[l] * net.g[l].c_out * 4;
+        // every layer's input lies in a ring: the rows some output row still needs, those of a launch while those of the one
+        // before are being read -- of up to kGatherSegs pushes, where they are held back
+        int big = std::min(kGatherSegs * max_seg, kBatchRows), small = max_seg;
+        for (int l = 0; l < n; ++l) {
+            const Geom &g = net.g[l];
+            RowUnit u;
+            u.l = u.lp = l; u.last = l == n - 1; u.next = l + 1 < n ? l + 1 : -1;
+            u.ring_rows = 2 * small + g.k_h + g.s_h;
+            u.ring_room = 2 * big + g.k_h + g.s_h;
+            const int vl = conv3x3_mfma_vl(net.precision);
+            u.row_elems = g.w_in * ((g.c_in + vl - 1) / vl * vl);
+            u.ring_stride = (int64_t)u.ring_rows * u.row_elems;
+            u.ring_off = off; off = align_up(off + (size_t)u.ring_room * u.row_elems * eb * B);
+            transit_per_stream += (size_t)u.ring_room * u.row_elems * eb;
+            // what is alive between two pushes
+            if (l < n - 1 && !strict_cascade()) handover_per_stream += (size_t)L.transit_cap[l] * g.c_out * 4;
+            L.units.push_back(u);
+            big = std::max(1, max_emit(g, big)); small = std::max(1, max_emit(g, small));
         }
-        L.cas_boundaries = std::min(kCasMaxStages, n) - 1;
-        L.cas_transit_stride = (most + 63) / 64 * 64;          // of one segment; a launch can hold kCasSegMax of them
-        L.cas_transit_off = off;
-        off = align_up(off + (size_t)L.cas_boundaries * 2 * B * kCasSegMax * L.cas_transit_stride * 4);
-        transit_per_stream = (size_t)L.cas_boundaries * 2 * kCasSegMax * L.cas_transit_stride * 4;
-        // (a launch of held-back segments hands over the rows of all of them: kCasSegMax times the
-        // rows of one; with a launch per push only the first of these is ever in use)
     }
     L.total = off;
     L.sizes.workspace_bytes = off;
@@ -475,282 +457,18 @@ double conv_step_bytes(const idf_net &net, const ConvStep &a, int n_streams)
     return per_stream * n_streams + weights;
 }
 
-// Deals the cascade's layers to stages.  A stage costs a fixed part and a part per layer that
-// grows with the layer's steps; the split with the cheapest slowest stage wins, as long as all
-// workgroups of a launch (streams x stages) are resident at once, two to a compute unit.
-void plan_cascade_stages(idf_streams *s)
-{
-    const idf_net &net = *s->net;
-    const int n = (int)net.g.size();
-    int cus = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        cus = 0;
-    int max_stages = std::min({kCasMaxStages, n, std::max(1, 2 * cus / std::max(1, s->B))});      // two workgroups fit a CU
-    if (const char *e = getenv("IDF_CASCADE_STAGES")) max_stages = std::max(1, std::min(max_stages, atoi(e)));
-    if (strict_cascade()) max_stages = 1;
-    std::vector<double> cost(n);
-    for (int l = 0; l < n; ++l) cost[l] = 2.5 + 0.2 * cascade1d_steps(net.g[l].c_in, net.g[l].c_out);
-    const double fixed = 4.0;
-    // Contiguous groups of layers, at most max_stages of them, the slowest as fast as possible
-    // (on a tie, fewer stages): best[k][i] = cost of the slowest of k stages over layers [0, i).
-    std::vector<std::vector<double>> best(max_stages + 1, std::vector<double>(n + 1, 1e30));
-    std::vector<std::vector<int>> cut(max_stages + 1, std::vector<int>(n + 1, 0));
-    best[0][0] = 0;
-    for (int k = 1; k <= max_stages; ++k)
-        for (int i = k; i <= n; ++i) {
-            double t = fixed;
-            for (int j = i - 1; j >= k - 1; --j) {         // the last stage is layers [j, i)
-                t += cost[j];
-                const double w = std::max(best[k - 1][j], t);
-                if (w < best[k][i]) { best[k][i] = w; cut[k][i] = j; }
-            }
-        }
-    int best_n = 1;
-    for (int k = 2; k <= max_stages; ++k)
-        if (best[k][n] + 0.3 * k < best[best_n][n] + 0.3 * best_n) best_n = k;
-    int best_lo[kCasMaxStages + 1];
-    for (int k = 0; k <= kCasMaxStages; ++k) best_lo[k] = n;
-    for (int k = best_n, i = n; k >= 1; --k) { i = cut[k][i]; best_lo[k - 1] = i; }
-    s->cas_stages = best_n;
-    for (int k = 0; k <= kCasMaxStages; ++k) s->cas_lo[k] = best_lo[k];
-}
-
-// What a cascade launch needs to know of every layer whatever the segment.
-void cascade_layers(idf_streams *s)
-{
-    const idf_net &net = *s->net;
-    for (int l = 0; l < (int)net.g.size() && l < kCasMaxLayers; ++l) {
-        const Geom &g = net.g[l];
-        CascadeLayer &L = s->cas_layer[l];
-        L = CascadeLayer{};
-        L.c_in = g.c_in; L.c_out = g.c_out; L.k_h = g.k_h; L.s_h = g.s_h; L.act = g.act;
-        L.steps = cascade1d_steps(g.c_in, g.c_out);
-        L.ring_floats = g.k_h * g.c_out;
-        L.rcp_k = (65536 + g.k_h - 1) / g.k_h;
-        L.w = s->ws + s->w_off[l];
-        L.bias = net.b_img[l].empty() ? nullptr : s->ws + s->b_off[l];
-        L.ring = s->ws + s->ring_off[l];
-        L.ring_stride = s->ring_stride[l];
-        L.cp_log = 0;
-        while ((1 << L.cp_log) < g.c_out) ++L.cp_log;
-    }
-}
-
-// Which rows a segment of n_rows rows arriving at row r brings to every layer.
-void cascade_propagate(idf_streams *s, int n_rows, int64_t r, int n_streams, idf_streams::CasSeg &p, double &bytes)
-{
-    const idf_net &net = *s->net;
-    const int n = (int)net.g.size();
-    int64_t y0 = r, cnt = n_rows;
-    for (int l = 0; l < n; ++l) {
-        const Geom &g = net.g[l];
-        p.y0[l] = y0; p.cnt[l] = (int)cnt;
-        if (cnt > 0) {
-            ConvStep c{};
-            c.g = g; c.y0 = y0; c.cnt = (int)cnt; c.o_lo = rows_final(g, y0); c.o_fin = rows_final(g, y0 + cnt);
-            c.o_hi = std::max(rows_touched(g, y0 + cnt), c.o_fin);
-            c.in_by_position = l == 0; c.to_output = l == n - 1; c.bias = s->cas_layer[l].bias;
-            bytes += conv_step_bytes(net, c, n_streams);
-            y0 = c.o_lo; cnt = c.o_fin - c.o_lo;
-        }
-    }
-    p.y0[n] = y0; p.cnt[n] = (int)cnt;
-}
-
-// The step of layer l for input rows [y0, y0 + cnt).
-int cascade_step(const idf_net &net, int l, int64_t y0, int64_t cnt, CascadeStep &L)
-{
-    const Geom &g = net.g[l];
-    L = CascadeStep{};
-    if (cnt <= 0) return IDF_OK;
-    const int64_t o_lo = rows_final(g, y0), o_fin = rows_final(g, y0 + cnt);
-    const int64_t o_hi = std::max(rows_touched(g, y0 + cnt), o_fin);
-    const int64_t y0p = y0 + g.p_h;
-    const int rho = (int)(y0p % g.s_h);
-    const int64_t o_base = y0p / g.s_h + cascade1d_slot_off(g.s_h, rho);
-    {   // what a lane issues per channel that holds an event: the kernel's variant for 4, 8 or 16
-        // new rows computes all of them, all nine tap positions that land on an output row
-        // (the cascade takes strides 1 and 2 only: parity by mask, no division in what runs with every push)
-        const int nin = cnt <= 4 ? 4 : cnt <= 8 ? 8 : 16, par = g.s_h - 1;
-        int f = 0;
-        for (int j = 0; j < nin; ++j)
-            for (int ky = 0; ky < kCasKMax; ++ky)
-                if (((rho + j - ky) & par) == 0) ++f;
-        L.fma_per_channel = (short)f;
-    }
-    const int64_t t_lo = o_lo - o_base, t_fin = o_fin - o_base, t_hi = o_hi - o_base;
-    const int64_t d0 = o_base * g.s_h - g.p_h - y0;
-    if (cnt > kCasRowsMax || t_lo < 0 || t_hi > kCasSlotsMax || d0 < -127 || d0 > 127)
-        return fail(IDF_ESTATE, "internal: cascade schedule of layer %d out of range", l);
-    L.cnt = (signed char)cnt; L.rho = (signed char)rho;
-    L.t_lo = (signed char)t_lo; L.t_fin = (signed char)t_fin; L.t_hi = (signed char)t_hi;
-    L.slot0 = (signed char)(((o_base % g.k_h) + g.k_h) % g.k_h);
-    L.d0 = (signed char)d0;
-    L.at_start = y0 == 0;
-    for (int j = 0; j < cnt && j < kCasRowsMax; ++j) {
-        int t = 0;
-        const int64_t v = y0 + j + g.p_h, par = g.s_h - 1, sh = g.s_h - 1;      // stride 1 or 2: u % s = u & par, u / s = u >> sh
-        for (int ky = 0; ky < g.k_h; ++ky) {
-            const int64_t u = v - ky;
-            if (u < 0 || (u & par) != 0) continue;
-            if (g.h_out > 0 && (u >> sh) >= g.h_out) continue;
-            ++t;
-        }
-        L.taps4[j >> 1] |= (unsigned char)(t << ((j & 1) * 4));
-    }
-    return IDF_OK;
-}
-
-// How a stage whose first layer is l0 takes the segments of a launch: consecutive segments
-// together while their rows fit one step (stage 0 gathers the rows of several pushed segments
-// itself: those must bring the same number of rows each).  first[m] = first segment of step m.
-int cascade_steps_of(const idf_streams::CasGroup &g, int l0, bool merge, int first[kCasSegMax + 1])
-{
-    int m = 0, q = 0;
-    while (q < g.n) {
-        int rows = g.seg[q].cnt[l0], e = q + 1;
-        while (merge && e < g.n && rows + g.seg[e].cnt[l0] <= kCasRowsMax &&
-               (l0 > 0 || g.seg[e].n_rows == g.seg[q].n_rows))
-            rows += g.seg[e++].cnt[l0];
-        first[m++] = q;
-        q = e;
-    }
-    first[m] = g.n;
-    return m;
-}
-
-// One launch: stage 0 takes the new segments (none: the stages only move on), stage k those of
-// the launch k launches earlier.  staged == false: all layers in one stage, nothing may be on its way.
-int cascade_launch(idf_streams *s, const StreamSel &sel, const idf_streams::CasGroup *fresh, bool staged)
-{
-    const idf_net &net = *s->net;
-    const int n = (int)net.g.size();
-    CascadeArgs a{};
-    a.n_layers = n;
-    a.n_stages = staged ? s->cas_stages : 1;
-    for (int k = 0; k <= kCasMaxStages; ++k) a.stage_lo[k] = staged ? s->cas_lo[k] : (k == 0 ? 0 : n);
-    a.transit_wr = s->cas_parity;
-    for (int l = 0; l < n; ++l) a.layer[l] = s->cas_layer[l];
-    for (int k = 0; k < a.n_stages; ++k) {
-        const idf_streams::CasGroup *src = k == 0 ? fresh : (s->hist(k - 1).n > 0 ? &s->hist(k - 1) : nullptr);
-        if (!src) continue;
-        const int l0 = a.stage_lo[k], l1 = a.stage_lo[k + 1];
-        int first[kCasSegMax + 1];
-        const int n_steps = cascade_steps_of(*src, l0, src->n > 1, first);
-        if (n_steps > kCasStepMax) return fail(IDF_ESTATE, "internal: %d steps in one cascade launch", n_steps);
-        a.stage_steps[k] = n_steps;
-        a.steps_max = std::max(a.steps_max, n_steps);
-        int in_rows = 0, out_rows = 0;                  // rows of the launch before this step: into the stage, out of it
-        for (int m = 0; m < n_steps; ++m) {
-            const int q0 = first[m], q1 = first[m + 1];
-            int64_t y0 = 0, cnt = 0;
-            for (int q = q0; q < q1; ++q) {
-                if (cnt == 0) y0 = src->seg[q].y0[l0];          // (where a segment brings the layer no row, its y0 says nothing)
-                cnt += src->seg[q].cnt[l0];
-            }
-            for (int l = l0; l < l1; ++l) {
-                CascadeStep &st = a.step[m][l];
-                int rc = cascade_step(net, l, y0, cnt, st);
-                if (rc != IDF_OK) return rc;
-                if (l == l0) { st.in_off = (short)in_rows; st.seg0 = (signed char)q0; st.seg_rows = (signed char)src->seg[q0].n_rows; }
-                if (l == l1 - 1) st.out_off = (short)out_rows;
-                const int64_t o_lo = cnt > 0 ? rows_final(net.g[l], y0) : y0, o_fin = cnt > 0 ? rows_final(net.g[l], y0 + cnt) : y0;
-                if (cnt <= 0) break;
-                y0 = o_lo; cnt = o_fin - o_lo;
-            }
-            for (int q = q0; q < q1; ++q) { in_rows += src->seg[q].cnt[l0]; out_rows += src->seg[q].cnt[l1]; }
-            if (k == a.n_stages - 1) a.out_slot0[m] = src->seg[q0].out_slot0;
-        }
-    }
-    for (int q = 0; fresh && q < fresh->n; ++q) {
-        a.in[q] = fresh->seg[q].dev_rows;
-        a.in_stream_stride[q] = fresh->seg[q].n_rows * net.in_c;
-    }
-    a.transit = s->ws + s->cas_transit_off;
-    a.transit_stream_stride = (int64_t)kCasSegMax * s->cas_transit_stride;
-    a.transit_buf_stride = a.transit_stream_stride * s->B;
-    a.out = s->ws + s->out_off; a.out_stride = s->out_stride; a.out_cap = s->out_cap;
-    a.stats = (unsigned long long *)(s->ws + s->stats_off);
-    a.issued = s->count_issued ? (unsigned long long *)(s->ws + s->issued_off) : nullptr;
-    hipError_t e = launch_cascade1d(a, sel, launch_ctx(s, kKindCascade1d, fresh ? fresh->bytes : 0.0));
-    if (e != hipSuccess) return dev_fail(e, "cascade launch");
-    if (staged) {
-        // every launch on its way is one launch older now; the new one takes the place of the oldest
-        s->cas_head = (s->cas_head + kCasMaxStages - 1) % kCasMaxStages;
-        if (fresh) s->hist(0).take(*fresh); else s->hist(0).n = 0;
-        for (int k = s->cas_stages - 1; k < kCasMaxStages; ++k) s->hist(k).n = 0;   // left the last stage
-        s->cas_parity ^= 1;
-    }
-    return IDF_OK;
-}
-
-// Segments held back (pushes in step, idf_set_push_batching) get their launch.
-int cascade_flush(idf_streams *s)
-{
-    if (s->cas_pending.n == 0) return IDF_OK;
-    StreamSel all{};
-    all.n = s->B; all.base = 0; all.pos0 = 0;
-    int rc = cascade_launch(s, all, &s->cas_pending, s->cas_stages > 1);
-    s->cas_pending.n = 0; s->cas_pending.bytes = 0;
-    return rc;
-}
-
-// Runs the segments still held back or on their way through the remaining stages.
-int cascade_drain(idf_streams *s)
-{
-    if (!s->use_cascade1d) return IDF_OK;
-    int rc = cascade_flush(s);
-    if (rc != IDF_OK) return rc;
-    StreamSel all{};
-    all.n = s->B; all.base = 0; all.pos0 = 0;
-    for (;;) {
-        bool pending = false;
-        for (int k = 0; k < kCasMaxStages - 1; ++k) pending |= s->hist(k).n > 0;
-        if (!pending) return IDF_OK;
-        rc = cascade_launch(s, all, nullptr, true);
-        if (rc != IDF_OK) return rc;
-    }
-}
-
-// Enqueue everything one group of streams (all at row r, n new rows) needs.
-int enqueue_cascade1d(idf_streams *s, const StreamSel &sel, const void *dev_rows, int n_rows, int64_t r,
-                      int64_t out_slot0)
-{
-    // All streams in step: the segment joins those of its launch (stages hold segments of all streams
-    // together; held-back segments are segments of all streams).  Any other push first lets everything
-    // finish and then runs through all layers at once.
-    const bool in_step = sel.base == 0 && sel.pos0 == 0 && sel.n == s->B && (s->cas_stages > 1 || s->cas_batch > 1);
-    if (!in_step) {
-        int rc = cascade_drain(s);
-        if (rc != IDF_OK) return rc;
-        idf_streams::CasGroup g;
-        g.n = 1;
-        cascade_propagate(s, n_rows, r, sel.n, g.seg[0], g.bytes);
-        g.seg[0].out_slot0 = out_slot0; g.seg[0].dev_rows = dev_rows; g.seg[0].n_rows = n_rows;
-        return cascade_launch(s, sel, &g, false);
-    }
-    idf_streams::CasGroup &p = s->cas_pending;
-    idf_streams::CasSeg &seg = p.seg[p.n];
-    cascade_propagate(s, n_rows, r, sel.n, seg, p.bytes);
-    seg.out_slot0 = out_slot0; seg.dev_rows = dev_rows; seg.n_rows = n_rows;
-    ++p.n;
-    // the launch is due when enough segments are held back, or when one more could need more steps
-    // than a stage runs in one launch (every stage merges at least as well as the one that merges nothing)
-    if (p.n >= s->cas_batch || p.n >= kCasSegMax) return cascade_flush(s);
-    int first[kCasSegMax + 1], worst = 0;
-    for (int l = 0; l < (int)s->net->g.size(); ++l) worst = std::max(worst, cascade_steps_of(p, l, true, first));
-    return worst >= kCasStepMax ? cascade_flush(s) : IDF_OK;
-}
-
 // ---- layers on the matrix cores -------------------------------------------------------------------
 // Rows counted over samples: sample * rows per sample + row.
 
 // Rows of c of a layer that can be formed once `in` input rows have arrived.
-int64_t rows_ready(const Geom &g, int64_t in) { return in / g.h_in * g.h_out + rows_final(g, in % g.h_in); }
+// (a signal without end is one sample)
+int64_t rows_ready(const Geom &g, int64_t in) { return g.h_in > 0 ? in / g.h_in * g.h_out + rows_final(g, in % g.h_in) : rows_final(g, in); }
+int64_t row_in_sample(const Geom &g, int64_t o) { return g.h_out > 0 ? o % g.h_out : o; }
+int64_t sample_end(const Geom &g, int64_t o) { return g.h_out > 0 ? (o / g.h_out + 1) * g.h_out : INT64_MAX; }
 // First input row that row o of c needs.
 int64_t first_needed(const Geom &g, int64_t o)
 {
-    return o / g.h_out * g.h_in + std::max<int64_t>(0, o % g.h_out * g.s_h - g.p_h);
+    return (g.h_out > 0 ? o / g.h_out * g.h_in : 0) + std::max<int64_t>(0, row_in_sample(g, o) * g.s_h - g.p_h);
 }
 int mod_rows(int64_t y, int64_t n) { return (int)((y % n + n) % n); }
 
@@ -940,6 +658,139 @@ int row_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *dev_ro
     }
 }
 
+// ---- layers on the gathering kernel (k_conv_gather.hip) ---------------------------------------------------
+// A signal without end: what a step says of where its rows lie in the sample matters near the beginning only.
+int64_t near_start(int64_t y) { return y < 8192 ? y : 4096 + (y & 4095); }
+
+// The step that forms rows [o, o + n) of unit k.
+void gather_step(const idf_streams *s, int k, int64_t o, int64_t n, int n_streams, GatherStep &a, double &bytes)
+{
+    const idf_net &net = *s->net;
+    const RowUnit &u = s->units[k];
+    const Geom &g = net.g[u.l];
+    a = s->gather[k];
+    const int64_t y = row_in_sample(g, o);
+    a.y0 = (int)(g.h_out > 0 ? y : near_start(y)); a.n_rows = (int)n;
+    a.slot0 = mod_rows((g.h_out > 0 ? o / g.h_out * g.h_in : 0) + y * g.s_h - g.p_h, u.ring_rows);
+    a.ring_rows = u.ring_rows;
+    a.dst_rows = u.last ? (int)s->out_cap : s->units[u.next].ring_rows;
+    a.dst_slot0 = mod_rows(o, a.dst_rows);
+    conv_gather_shape(k == 0, a);
+    const double eb = ev_bytes(net.precision);
+    bytes += n_streams * ((double)((n - 1) * g.s_h + g.k_h) * g.w_in * g.c_in * eb + (u.last ? (double)n * net.out_w * net.out_c * 4 : 0.0)) +
+             (double)g.k_h * g.k_w * g.c_in * g.c_out * w_bytes(net.precision) + (a.bias ? g.c_out * 4.0 : 0.0);
+}
+
+// One launch for streams that all stand at p; as row_plan, without pairs.  chain: the layers one after the other, each on
+// what the ones before it emit in this launch.
+bool gather_plan(const idf_streams *s, RowProg &p, int n_streams, int n_new, bool chain, GatherHead &h, GatherStep *st, double &bytes)
+{
+    const idf_net &net = *s->net;
+    const int nu = (int)s->units.size();
+    RowProg q = p;
+    h.n = 0;
+    auto take = [&]() {
+        GatherStep &a = st[h.n++];
+        const RowUnit &u = s->units[0];
+        const Geom &g = net.g[u.l];
+        a = s->gather[0];
+        a.take = 1;
+        const int64_t y = g.h_in > 0 ? p.in[0] % g.h_in : near_start(p.in[0]);
+        a.y0 = (int)y; a.n_rows = n_new; a.ring_rows = u.ring_rows; a.slot0 = mod_rows(p.in[0], u.ring_rows);
+            conv_gather_shape(true, a);
+        bytes += (double)n_streams * n_new * net.in_w * net.in_c * ev_bytes(net.precision);
+    };
+    if (chain && n_new > 0) { take(); q.in[0] += n_new; }
+    for (int i = 0; i < nu; ++i) {
+        const int k = chain ? i : nu - 1 - i;              // (side by side: the deepest first, their tiles run longest)
+        const RowUnit &u = s->units[k];
+        const Geom &g = net.g[u.l];
+        const int64_t o = q.out[k], in = chain ? q.in[k] : p.in[k];
+        int64_t n = std::min(rows_ready(g, in), sample_end(g, o)) - o;
+        if (u.next >= 0) {                         // room in the ring of the unit behind (as it stands before the step)
+            const RowUnit &v = s->units[u.next];
+            n = std::min<int64_t>(n, v.ring_rows - ((chain ? q.in[u.next] : p.in[u.next]) - first_needed(net.g[v.l], chain ? q.out[u.next] : p.out[u.next])));
+        }
+        if (n <= 0) continue;
+        GatherStep &a = st[h.n++];
+        gather_step(s, k, o, n, n_streams, a, bytes);
+        q.out[k] = o + n;
+        if (u.next >= 0) q.in[u.next] += n;
+    }
+    if (n_new > 0) {
+        if (!chain) { take(); q.in[0] += n_new; }
+        // rows still needed, and those this launch reads while it writes the new ones
+        const int64_t keep = std::min(first_needed(net.g[0], q.out[0]), first_needed(net.g[0], p.out[0]));
+        if (q.in[0] - keep > s->units[0].ring_rows) return false;
+    }
+    if (h.n == 0) return false;
+    p = q;
+    return true;
+}
+
+// Streams that stand at p receive the rows of n_seg buffers of seg_rows rows each (0: none), which belong to one sample;
+// out: everything on its way is brought through.
+int gather_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *const *bufs, int n_seg, int seg_rows, bool out)
+{
+    const idf_net &net = *s->net;
+    GatherHead h;
+    GatherStep st[kGatherMax];
+    h.n_layers = (int)net.g.size();
+    h.stats = (unsigned long long *)(s->ws + s->stats_off);
+    h.issued = s->count_issued ? (unsigned long long *)(s->ws + s->issued_off) : nullptr;
+    h.n_in = n_seg; h.seg_rows = seg_rows; h.in_stride = seg_rows * net.in_w * net.in_c;
+    for (int i = 0; i < n_seg; ++i) h.in[i] = bufs[i];
+    // What is on its way goes through in one launch, a workgroup per stream and one layer after the other, unless that is more
+    // than a tile or two per layer and stream: a launch per layer, on the whole chip, is faster then (37 audio streams with 256
+    // samples each on their way: 40 us against 370).
+    int64_t most = n_seg * seg_rows;               // rows of one layer that wait
+    for (size_t k = 0; k < s->units.size(); ++k) most = std::max(most, rows_ready(net.g[s->units[k].l], p.in[k]) - p.out[k]);
+    const bool chain = out && (strict_cascade() || most <= 32);
+    for (bool fresh = n_seg > 0; fresh || out;) {
+        double bytes = 0;
+        bool took = fresh && gather_plan(s, p, sel.n, n_seg * seg_rows, chain, h, st, bytes);
+        if (!took) {
+            bytes = 0;
+            if (!gather_plan(s, p, sel.n, 0, chain, h, st, bytes)) {
+                if (fresh) return fail(IDF_ESTATE, "internal: rows between layers do not move on");
+                break;
+            }
+        }
+        if (took) fresh = false;
+        hipError_t e = launch_conv_gather(net.precision, h, st, sel, chain, launch_ctx(s, kKindCascade1d, bytes));
+        if (e != hipSuccess) return dev_fail(e, "gather launch");
+    }
+    return IDF_OK;
+}
+
+// Pushes that were held back get their launch.
+int gather_flush(idf_streams *s)
+{
+    if (s->held == 0) return IDF_OK;
+    StreamSel all{};
+    all.n = s->B; all.base = 0; all.pos0 = 0;
+    const int n = s->held;
+    s->held = 0;
+    return gather_run(s, all, s->prog_all, s->held_buf, n, s->held_rows, strict_cascade());
+}
+
+// How many rows of the rings are in use: as many as k pushes per launch need.  Only while no row lies in them.
+void gather_rings(idf_streams *s, int k)
+{
+    for (const RowProg &p : s->prog) if ((s->prog_same ? s->prog_all : p).in[0] > 0) return;
+    int rows = s->batch_rows = std::min(k * s->max_seg, kBatchRows);
+    for (RowUnit &u : s->units) {
+        const Geom &g = s->net->g[u.l];
+        u.ring_rows = std::min(u.ring_room, 2 * rows + g.k_h + g.s_h);
+        u.ring_stride = (int64_t)u.ring_rows * u.row_elems;        // (close together: a few pages hold the rings of all streams)
+        rows = std::max(1, max_emit(g, rows));
+    }
+    for (size_t k = 0; k < s->units.size(); ++k) {
+        s->gather[k].ring_stride = s->units[k].ring_stride;
+        if (!s->units[k].last) s->gather[k].dst_stride = s->units[k + 1].ring_stride;
+    }
+}
+
 void prog_split(idf_streams *s)
 {
     if (!s->prog_same) return;
@@ -1003,9 +854,9 @@ bool row_pending(const idf_streams *s, const RowProg &p)
     for (size_t k = 0; k < s->units.size(); ++k) {
         const RowUnit &u = s->units[k];
         const Geom &g = s->net->g[u.l];
-        const int64_t o = p.out[k], end = (o / g.h_out + 1) * g.h_out;
+        const int64_t o = p.out[k], end = sample_end(g, o);
         int64_t n = std::min(rows_ready(g, p.in[k]), end) - o;
-        if (o + n < end && u.pool) n &= ~(int64_t)1;
+        if (u.pool && o + n < end) n &= ~(int64_t)1;
         if (n > 0) return true;
     }
     return false;
@@ -1014,16 +865,17 @@ bool row_pending(const idf_streams *s, const RowProg &p)
 int stg_drain(idf_streams *s)
 {
     if (!s->stg2d) return IDF_OK;
+    auto through = [&](const StreamSel &sel, RowProg &p) { return s->use_cascade1d ? gather_run(s, sel, p, nullptr, 0, 1, true) : row_run(s, sel, p, nullptr, 0); };
     if (s->prog_same) {
         if (!row_pending(s, s->prog_all)) return IDF_OK;
         StreamSel all{};
         all.n = s->B; all.base = 0; all.pos0 = 0;
-        return row_run(s, all, s->prog_all, nullptr, 0);
+        return through(all, s->prog_all);
     }
     bool any = false;
     for (const RowProg &p : s->prog) any = any || row_pending(s, p);
     if (!any) return IDF_OK;
-    return for_each_prog(s, all_members(s), [&](const StreamSel &sel, RowProg &p) { return row_run(s, sel, p, nullptr, 0); });
+    return for_each_prog(s, all_members(s), through);
 }
 
 // Where a stream that has received `in` rows stands once nothing is on its way.
@@ -1038,7 +890,8 @@ RowProg prog_at(const idf_streams *s, int64_t in, bool counted)
         int64_t o = rows_ready(g, p.in[k]);
         if (u.pool && (o % g.h_out) % 2) { --o; if (counted) p.early |= 1u << k; }
         p.out[k] = o;
-        if (u.next >= 0) p.in[u.next] = leaving_index(net, u, o / g.h_out * g.h_out) + (u.pool ? o % g.h_out / 2 : o % g.h_out);
+        if (u.next >= 0 && g.h_out == 0) p.in[u.next] = o;
+        else if (u.next >= 0) p.in[u.next] = leaving_index(net, u, o / g.h_out * g.h_out) + (u.pool ? o % g.h_out / 2 : o % g.h_out);
     }
     return p;
 }
@@ -1101,7 +954,7 @@ int count_waiting_rows(idf_streams *s)
 // that of every pushed row having gone through every layer it can influence.
 int pipeline_drain(idf_streams *s)
 {
-    int rc = cascade_drain(s);
+    int rc = gather_flush(s);
     return rc != IDF_OK ? rc : stg_drain(s);
 }
 
@@ -1110,7 +963,6 @@ int pipeline_drain(idf_streams *s)
 int enqueue_cascade(idf_streams *s, const StreamSel &sel, const void *dev_rows, int n_rows, int64_t r,
                     int64_t out_slot0, int64_t sample, uint32_t early)
 {
-    if (s->use_cascade1d) return enqueue_cascade1d(s, sel, dev_rows, n_rows, r, out_slot0);
     const idf_net &net = *s->net;
     const int n = (int)net.g.size();
     const int eb = ev_bytes(net.precision);
@@ -1265,17 +1117,29 @@ uint32_t early_after(const idf_streams *s, uint32_t early, int64_t before, int64
 }
 
 // One stream's pieces of the workspace, in the order they are laid out in a snapshot.
-template <class F> void for_each_state_piece(const idf_streams *s, int id, F &&f)
+template <class F> void for_each_state_piece(const idf_streams *s, int id, int64_t rows_in, F &&f)
 {
     const idf_net &net = *s->net;
     const int n = (int)net.g.size();
     const int eb = ev_bytes(net.precision);
     for (int l = 0; l < n; ++l) {
-        if (s->mfma[l]) continue;
+        if (s->mfma[l] || s->use_cascade1d) continue;
         if (net.g[l].kind == IDF_CONV) f(s->ring_off[l] + (size_t)id * s->ring_stride[l] * 4, (size_t)s->ring_stride[l] * 4);
         else f(s->held_off[l] + (size_t)id * s->held_stride[l] * eb, (size_t)s->held_stride[l] * eb);
     }
-    for (const RowUnit &u : s->units) f(u.ring_off + (size_t)id * u.ring_stride * eb, (size_t)u.ring_stride * eb);
+    if (s->use_cascade1d) {
+        // row by row, the K_h newest of every layer: how many rows of a ring are in use differs between openings
+        const RowProg p = prog_at(s, rows_in, false);
+        for (size_t k = 0; k < s->units.size(); ++k) {
+            const RowUnit &u = s->units[k];
+            const Geom &g = net.g[u.l];
+            const size_t row = (size_t)u.row_elems * eb;
+            for (int i = 0; i < g.k_h; ++i)
+                f(u.ring_off + (size_t)id * u.ring_stride * eb + mod_rows(p.in[k] - g.k_h + i, u.ring_rows) * row, row);
+        }
+    } else {
+        for (const RowUnit &u : s->units) f(u.ring_off + (size_t)id * u.ring_stride * eb, (size_t)u.ring_stride * eb);
+    }
     f(s->stats_off + (size_t)id * n * 2 * sizeof(unsigned long long), (size_t)n * 2 * sizeof(unsigned long long));
     f(s->issued_off + (size_t)id * n * sizeof(unsigned long long), (size_t)n * sizeof(unsigned long long));
     f(s->head_off + (size_t)id * net.out_c * sizeof(double), (size_t)net.out_c * sizeof(double));
@@ -1918,33 +1782,52 @@ int open_on(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
     s->out_off = L.out_off; s->stats_off = L.stats_off; s->issued_off = L.issued_off; s->out_stride = L.out_stride; s->sizes = L.sizes;
     s->use_cascade1d = L.cascade1d;
     s->head_off = L.head_off;
-    s->cas_transit_off = L.cas_transit_off;
-    s->cas_transit_stride = L.cas_transit_stride;
     {
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) s->cus = 0;
     }
-    if (L.cascade1d) { plan_cascade_stages(s); cascade_layers(s); }
     s->mfma = L.mfma; s->units = L.units;
     s->unit_of.assign(net->g.size(), -1);
     for (size_t k = 0; k < s->units.size(); ++k) s->unit_of[s->units[k].l] = (int)k;
-    s->stg2d = !strict_rows() && net_all_mfma(*net);
+    s->stg2d = L.cascade1d || (!strict_rows() && net_all_mfma(*net));
     if (s->stg2d) s->prog.assign(n_streams, RowProg{});
+    if (L.cascade1d) {
+        s->batch_rows = max_seg_rows;
+        for (size_t k = 0; k < s->units.size(); ++k) {
+            const RowUnit &u = s->units[k];
+            const Geom &g = net->g[u.l];
+            GatherStep a{};
+            conv_gather_layer(net->precision, g, a);
+            a.layer = u.l; a.next_layer = -1;
+            a.ring = s->ws + u.ring_off; a.ring_stride = u.ring_stride;
+            a.to_output = u.last;
+            if (u.last) {
+                a.dst = s->ws + s->out_off; a.dst_stride = s->out_stride;
+            } else {
+                const RowUnit &v = s->units[u.next];
+                const Geom &gn = net->g[v.l];
+                a.dst = s->ws + v.ring_off; a.dst_stride = v.ring_stride;
+                GatherStep b{};
+                conv_gather_layer(net->precision, gn, b);
+                a.dst_cells = b.cells;
+                a.next_layer = v.l; a.next_c_out = gn.c_out; a.nk_h = b.k_h; a.nk_w = b.k_w; a.ns_h_log = b.s_h_log; a.ns_w_log = b.s_w_log;
+                a.np_h = b.p_h; a.np_w = b.p_w; a.nh_out = b.h_out; a.nw_out = b.w_out;
+            }
+            a.w_frag = s->ws + s->w_off[u.l];
+            a.bias = net->b_img[u.l].empty() ? nullptr : s->ws + s->b_off[u.l];
+            s->gather.push_back(a);
+        }
+    }
     s->h.assign(n_streams, StreamHost{});
     s->stamp.assign(n_streams, 0);
     hipError_t e = launch_fill_zero(s->ws, L.sizes.weights_bytes, s->st);     // zero padding of the weights
     for (size_t l = 0; l < net->g.size() && e == hipSuccess; ++l) {
         if (net->g[l].kind != IDF_CONV) continue;
         if (L.cascade1d) {
-            const Geom &g = net->g[l];
-            const float *src = (const float *)net->w_img[l].data();      // [k_h][1][c_in][c_out]
-            s->cas_w.emplace_back((size_t)cascade1d_cin_pad(g.c_in, g.c_out) * g.c_out * kCasKMax, 0.f);
-            std::vector<float> &img = s->cas_w.back();
-            for (int ky = 0; ky < g.k_h; ++ky)
-                for (int ci = 0; ci < g.c_in; ++ci)
-                    for (int co = 0; co < g.c_out; ++co)
-                        img[cascade1d_weight_index(g.c_in, g.c_out, ci, co, ky)] = src[((size_t)ky * g.c_in + ci) * g.c_out + co];
-            e = hipMemcpyAsync(s->ws + s->w_off[l], img.data(), img.size() * 4, hipMemcpyHostToDevice, s->st);
+            s->gather_w.emplace_back(conv_gather_pack(net->precision, net->g[l], nullptr, nullptr));
+            std::vector<unsigned char> &img = s->gather_w.back();
+            conv_gather_pack(net->precision, net->g[l], net->w_img[l].data(), img.data());
+            e = hipMemcpyAsync(s->ws + s->w_off[l], img.data(), img.size(), hipMemcpyHostToDevice, s->st);
         } else {
             e = hipMemcpyAsync(s->ws + s->w_off[l], net->w_img[l].data(), net->w_img[l].size(), hipMemcpyHostToDevice, s->st);
         }
@@ -2013,7 +1896,23 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
             return enqueue_cascade(s, sel, dev_rows, n_rows, std::get<0>(key), std::get<1>(key), std::get<2>(key), std::get<3>(key));
         });
     };
-    if (s->stg2d) {
+    if (s->use_cascade1d) {
+        const bool in_step = s->prog_same && n_ids == s->B && (!stream_ids || members.back().second == s->B - 1);
+        bool straight = in_step;
+        for (int i = 0; straight && stream_ids && i < n_ids; ++i) straight = stream_ids[i] == i;
+        if (straight && s->batch > 1) {
+            // held back until there are enough of them; a launch takes buffers of one size and of one sample
+            if (s->held > 0 && (s->held_rows != n_rows || s->h[0].r == 0 || (s->held + 1) * n_rows > s->batch_rows)) rc = gather_flush(s);
+            if (rc != IDF_OK) return rc;
+            s->held_buf[s->held++] = dev_rows; s->held_rows = n_rows;
+            if (s->held >= s->batch || (s->held + 1) * n_rows > s->batch_rows) rc = gather_flush(s);
+        } else {
+            rc = gather_flush(s);
+            if (rc == IDF_OK)
+                rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, strict_cascade()); });
+        }
+        if (rc != IDF_OK) return rc;
+    } else if (s->stg2d) {
         rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return row_run(s, sel, p, dev_rows, n_rows); });
         if (rc != IDF_OK) return rc;
     } else if (one_group) {
@@ -2244,12 +2143,13 @@ int idf_get_issued_macs(idf_streams *s, int stream_id, uint64_t *macs_issued)
 int idf_set_push_batching(idf_streams *s, int k)
 {
     if (!s) return fail(IDF_EINVAL, "null argument");
-    if (k < 1 || k > kCasSegMax) return fail(IDF_EINVAL, "pushes per launch %d outside [1, %d]", k, kCasSegMax);
+    if (k < 1 || k > kGatherSegs) return fail(IDF_EINVAL, "pushes per launch %d outside [1, %d]", k, kGatherSegs);
     if (!s->use_cascade1d) return fail(IDF_EUNSUPPORTED, "holding back pushes is built for nets served by the 1-D cascade");
     if (s->eager.on) return fail(IDF_EUNSUPPORTED, "eager emission delivers every segment at once");
     int rc = pipeline_drain(s);                  // what is held back was pushed under the old setting
     if (rc != IDF_OK) return rc;
-    s->cas_batch = k;
+    s->batch = k;
+    gather_rings(s, k);
     return IDF_OK;
 }
 
@@ -2265,7 +2165,7 @@ int idf_snapshot_bytes(const idf_streams *s, size_t *bytes)
 {
     if (!s || !bytes) return fail(IDF_EINVAL, "null argument");
     size_t total = 0;
-    for_each_state_piece(s, 0, [&](size_t, size_t n) { total += align_up(n, 16); });
+    for_each_state_piece(s, 0, 0, [&](size_t, size_t n) { total += align_up(n, 16); });
     *bytes = total;
     return IDF_OK;
 }
@@ -2289,7 +2189,7 @@ int idf_snapshot(idf_streams *s, int stream_id, void *dev_buf, idf_stream_pos *p
                                                  (long long)(h.out_written - h.out_read));
     size_t at = 0;
     hipError_t e = hipSuccess;
-    for_each_state_piece(s, stream_id, [&](size_t off, size_t n) {
+    for_each_state_piece(s, stream_id, h.sample * s->net->in_h + h.r, [&](size_t off, size_t n) {
         if (e == hipSuccess && n) e = hipMemcpyAsync((char *)dev_buf + at, s->ws + off, n, hipMemcpyDeviceToDevice, s->st);
         at += align_up(n, 16);
     });
@@ -2315,7 +2215,7 @@ int idf_restore(idf_streams *s, int stream_id, const void *dev_buf, const idf_st
                                                  (long long)(h.out_written - h.out_read));
     size_t at = 0;
     hipError_t e = hipSuccess;
-    for_each_state_piece(s, stream_id, [&](size_t off, size_t n) {
+    for_each_state_piece(s, stream_id, (net.out_h > 0 ? pos->out_rows / net.out_h : 0) * net.in_h + pos->rows_pushed, [&](size_t off, size_t n) {
         if (e == hipSuccess && n) e = hipMemcpyAsync(s->ws + off, (const char *)dev_buf + at, n, hipMemcpyDeviceToDevice, s->st);
         at += align_up(n, 16);
     });

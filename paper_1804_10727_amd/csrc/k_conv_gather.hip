@@ -1,0 +1,470 @@
+// Output rows of a convolution of any kernel size, stride and padding on the matrix cores: every lane
+// gathers the cells of its own window from memory.
+//
+// A layer keeps the rows of its input that some output row still needs, as events, in a ring; an output
+// row is formed in registers once its last input row has arrived, activated and emitted into the ring of
+// the next layer.  A launch holds a step for every layer that has rows to form, all on rows that
+// were complete before it, and one that puts the caller's new rows into the first ring.
+//
+// The work is a matrix product: the columns of the instruction are output positions -- of one stream, or, where
+// a stream has few, of 2, 4, 8 or 16 streams side by side, so that a layer that completes four rows of a
+// 1-D signal per push still fills its tiles -- its rows 16 output channels, and the contraction runs over
+// the window's cells of 16 bytes, (ky, kx, cell of channels).  What a launch costs is latency, not
+// arithmetic: the windows of 64 audio streams are 64 tiles for each of the deep layers.  So a tile goes
+// to four waves, a quarter of the contraction each, which ask for everything they need (at most nine
+// K-steps at a time) before they use any of it; their sums are added in a fixed order.  Results do not depend
+// on how rows or streams were grouped.  K-steps whose 16 positions hold no event are skipped.
+//
+//   k_conv_gather_rows    a workgroup per tile, all steps side by side;
+//   k_conv_gather_chain   a workgroup of four such teams per stream, the steps one after the other: rows that
+//                         are to come out at once go through all layers in one launch.
+#include <algorithm>
+#include <cstring>
+
+#include "idf.h"
+#include "idf_kernels.h"
+#include "mfma_tile.h"
+
+namespace idf {
+
+namespace {
+
+typedef const __attribute__((address_space(4))) GatherStep Step;
+typedef const __attribute__((address_space(4))) GatherHead Head;
+
+constexpr int kTeam = 4;                         // waves that share a tile
+constexpr int kChunk = 9;                        // K-steps a wave has in flight
+
+// Taps of an axis that position v lands on inside an output of n positions (n == 0: unbounded).
+__device__ __forceinline__ int taps_axis(int v, int k, int s_log, int p, int n)
+{
+    int hi = (v + p) >> s_log;
+    int lo = (v + p - k + (1 << s_log)) >> s_log;
+    lo = lo < 0 ? 0 : lo;
+    if (n > 0 && hi >= n) hi = n - 1;
+    return hi >= lo ? hi - lo + 1 : 0;
+}
+
+// ---- the caller's rows: into the ring, channels padded to whole cells, and counted as the first layer's events ----
+template <class T> __device__ __forceinline__ void take_rows(Head &h, Step &a, const StreamSel &sel, int si, int tid, int threads)
+{
+    using ev_t = typename T::ev_t;
+    const int stream = sel_stream(sel, si), lane = tid & 63;
+    const int w_in = a.w_in, c_in = a.c_in, cells = a.cells, n_rows = a.n_rows, seg_rows = h.seg_rows;
+    const int row_elems = w_in * c_in, row_cells = w_in * cells;
+    unsigned char *ring = (unsigned char *)a.ring + (int64_t)stream * a.ring_stride * T::EB;
+    uint32_t ev = 0, taps = 0;
+    for (int i = tid; i < n_rows * row_cells; i += threads) {
+        const int r = row_cells == 1 ? i : i / row_cells, xc = i - r * row_cells, x = cells == 1 ? xc : xc / cells, c = (xc - x * cells) * T::VL;
+        const int seg = h.n_in == 1 ? 0 : r / seg_rows;
+        // (the pointer of a lane's own buffer: from the arguments, by a vector load)
+        const ev_t *src = (const ev_t *)((const __attribute__((address_space(4))) uint64_t *)h.in)[seg] +
+                          (int64_t)(sel.pos0 + si) * h.in_stride + (r - seg * seg_rows) * row_elems + x * c_in + c;
+        ev_t v[T::VL];
+        uint32_t n = 0;
+#pragma unroll
+        for (int e = 0; e < T::VL; ++e) v[e] = c + e < c_in ? src[e] : (ev_t)0;
+#pragma unroll
+        for (int e = 0; e < T::VL; ++e) n += T::ev_nonzero(v[e]);
+        i32x4 cell;
+        __builtin_memcpy(&cell, v, 16);
+        int slot = a.slot0 + r;
+        slot = slot >= a.ring_rows ? slot - a.ring_rows : slot;
+        *at4(reinterpret_cast<i32x4 *>(ring), (uint32_t)(slot * row_cells + xc) * 16) = cell;
+        ev += n;
+        taps += n * (uint32_t)(taps_axis(a.y0 + r, a.k_h, a.s_h_log, a.p_h, a.h_out) * (a.flat ? 1 : taps_axis(x, a.k_w, a.s_w_log, a.p_w, a.w_out)));
+    }
+    if (!h.stats) return;
+    ev = wave_sum(ev); taps = wave_sum(taps);
+    if (lane == 0 && ev) {
+        unsigned long long *d = h.stats + ((int64_t)stream * h.n_layers + a.layer) * 2;
+        atomicAdd(d, (unsigned long long)ev);
+        atomicAdd(d + 1, (unsigned long long)taps * (unsigned long long)a.c_out);
+    }
+}
+
+// ---- one tile: 16 positions x 16 channels, by a team of four waves ---------------------------------------
+// share: LDS for the sums of three waves; barrier: where the team's waves meet.
+template <class T, bool COUNT, class Barrier>
+__device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel, int si0, int pt, int ct, int spt_log, bool on, int kq,
+                                          typename T::acc_t *share, Barrier &&barrier)
+{
+    using acc_t = typename T::acc_t; using st_t = typename T::st_t;
+    constexpr int VL = T::VL, EB = T::EB;
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    // everything the loads need to know, asked for in one batch (left to first use: one wait after the other)
+    const int n_rows = a.n_rows, y0 = a.y0, n_ks = a.n_ks, cells = a.cells, slot0 = a.slot0, ring_rows = a.ring_rows, k_h = a.k_h, s_h_log = a.s_h_log;
+    const unsigned cells_rcp = a.cells_rcp;
+    const int64_t ring_stride = a.ring_stride;
+    const void *ring_p = a.ring, *w_frag = a.w_frag;
+    const int h_in = a.h_in, p_h = a.p_h, n_ct = a.n_ct, flat = a.flat, w_out = a.w_out;
+    asm volatile("" ::"s"(n_rows), "s"(y0), "s"(n_ks), "s"(cells), "s"(slot0), "s"(ring_rows), "s"(k_h), "s"(s_h_log), "s"(cells_rcp),
+                 "s"(ring_stride), "s"(ring_p), "s"(w_frag), "s"(h_in), "s"(p_h), "s"(n_ct), "s"(flat), "s"(w_out));
+    const int per_log = 4 - spt_log;               // positions per stream in the tile
+    const int si = si0 + (m >> per_log), pl = m & ((1 << per_log) - 1);
+    const bool stream_ok = on && si < sel.n;
+    const int stream = sel_stream(sel, stream_ok ? si : 0);
+    const unsigned char *ring = (const unsigned char *)ring_p + (int64_t)stream * ring_stride * EB;
+    const uint32_t lane16 = (uint32_t)lane * 16, w_step = (uint32_t)n_ct * 1024;
+    // this wave's K-steps
+    const int each = (n_ks + kTeam - 1) / kTeam, ks0 = kq * each, ks1 = ks0 + each < n_ks ? ks0 + each : n_ks;
+    const unsigned char *wf0 = (const unsigned char *)w_frag + ct * 1024 + ks0 * w_step;
+    const int p = (pt << per_log) + pl;
+    int o = p, x = 0;
+    if (!flat) { o = w_out == 1 ? p : (int)__umulhi((unsigned)p, a.wout_rcp); x = p - o * w_out; }
+    const bool valid = stream_ok && o < n_rows;
+    o = valid ? o : 0;
+    acc_t acc = {0, 0, 0, 0};
+    if (on) {
+        const int y_in = ((y0 + o) << s_h_log) - p_h;          // the window's first row
+        unsigned slot_o = (unsigned)(slot0 + (o << s_h_log));
+        slot_o = min(slot_o, slot_o - (unsigned)ring_rows);
+        unsigned long long issued = 0;
+        auto contract = [&](const i32x4 (&xv)[kChunk], const i32x4 (&wv)[kChunk], int kb) IDF_INLINE {
+#pragma unroll
+            for (int i = 0; i < kChunk; ++i) {
+                if (kb + i >= ks1) continue;
+                if (__ballot(T::or_of(xv[i]) != 0) == 0ull) continue;
+#pragma unroll
+                for (int e = 0; e < T::kInst; ++e) acc = T::mfma(wv[i], xv[i], acc, e);
+                if (COUNT) {
+                    const int n_cells = k_h * (flat ? 1 : a.k_w) * cells;
+                    for (int u = 0; u < 4; ++u) {
+                        const int q = 4 * (kb + i) + u, c = q % cells;
+                        if (q < n_cells) issued += (a.c_in - c * VL < VL ? a.c_in - c * VL : VL);
+                    }
+                }
+            }
+        };
+        if (flat) {
+            const int q_last = k_h * cells - 1;
+            // (a window that reaches over an end of the signal: its cells there are zero)
+            const bool edge = __ballot(valid && (y_in < 0 || y_in + k_h > h_in)) != 0ull;
+#pragma unroll 1
+            for (int kb = ks0; kb < ks1; kb += kChunk) {
+                i32x4 xv[kChunk], wv[kChunk];
+                const unsigned char *wf = wf0 + (kb - ks0) * w_step;
+#pragma unroll
+                for (int i = 0; i < kChunk; ++i) {
+                    if (kb + i >= ks1) continue;
+                    wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf), (uint32_t)i * w_step + lane16);
+                    int q = 4 * (kb + i) + g;
+                    q = q < q_last ? q : q_last;               // (past the end the weights are zero)
+                    const unsigned ky = __umul24((unsigned)q, cells_rcp) >> 16;
+                    unsigned slot = slot_o + ky;
+                    slot = min(slot, slot - (unsigned)ring_rows);
+                    xv[i] = *at4(reinterpret_cast<const i32x4 *>(ring), (__umul24(slot, (unsigned)cells) + (unsigned)q - __umul24(ky, (unsigned)cells)) * 16);
+                }
+                if (edge) {
+#pragma unroll
+                    for (int i = 0; i < kChunk; ++i) {
+                        if (kb + i >= ks1) continue;
+                        int q = 4 * (kb + i) + g;
+                        q = q < q_last ? q : q_last;
+                        const int y = y_in + (int)(__umul24((unsigned)q, cells_rcp) >> 16);
+                        if (y < 0 || y >= h_in) xv[i] = i32x4{0, 0, 0, 0};
+                    }
+                }
+                if (!valid) {
+#pragma unroll
+                    for (int i = 0; i < kChunk; ++i) if (kb + i < ks1) xv[i] = i32x4{0, 0, 0, 0};
+                }
+                contract(xv, wv, kb);
+            }
+        } else {
+            const int k_w = a.k_w, w_in = a.w_in, x_in = (x << a.s_w_log) - a.p_w, q_last = k_h * k_w * cells - 1;
+            const unsigned kw_rcp = a.kw_rcp;
+#pragma unroll 1
+            for (int kb = ks0; kb < ks1; kb += kChunk) {
+                i32x4 xv[kChunk], wv[kChunk];
+                const unsigned char *wf = wf0 + (kb - ks0) * w_step;
+                uint32_t there = 0;
+#pragma unroll
+                for (int i = 0; i < kChunk; ++i) {
+                    if (kb + i >= ks1) continue;
+                    wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf), (uint32_t)i * w_step + lane16);
+                    int q = 4 * (kb + i) + g;
+                    q = q < q_last ? q : q_last;
+                    const unsigned tap = __umul24((unsigned)q, cells_rcp) >> 16, ky = __umul24(tap, kw_rcp) >> 16;
+                    const int c = q - (int)__umul24(tap, (unsigned)cells), xx = x_in + (int)(tap - __umul24(ky, (unsigned)k_w)), y = y_in + (int)ky;
+                    const bool ok = valid && (unsigned)y < (unsigned)h_in && (unsigned)xx < (unsigned)w_in;
+                    there |= ok ? 1u << i : 0u;
+                    unsigned slot = slot_o + ky;
+                    slot = min(slot, slot - (unsigned)ring_rows);
+                    slot = min(slot, slot - (unsigned)ring_rows);
+                    const uint32_t off = ok ? (__umul24(__umul24(slot, (unsigned)w_in) + (unsigned)xx, (unsigned)cells) + (unsigned)c) * 16 : 0u;
+                    xv[i] = *at4(reinterpret_cast<const i32x4 *>(ring), off);
+                }
+#pragma unroll
+                for (int i = 0; i < kChunk; ++i)
+                    if (kb + i < ks1 && !((there >> i) & 1u)) xv[i] = i32x4{0, 0, 0, 0};
+                contract(xv, wv, kb);
+            }
+        }
+        if (COUNT && h.issued && g == 0 && pl == 0 && si < sel.n && issued) {
+            const int co_n = a.c_out - ct * 16 < 16 ? a.c_out - ct * 16 : 16;
+            atomicAdd(h.issued + (int64_t)sel_stream(sel, si) * h.n_layers + a.layer, (issued * (unsigned long long)co_n) << per_log);
+        }
+        if (kq > 0) share[(kq - 1) * 64 + lane] = acc;
+    }
+    // (likewise for what comes after the contraction)
+    const int act = a.act, shr = a.shr, clamp_hi = a.clamp_hi, c_out = a.c_out, dst_cells = a.dst_cells, dst_slot0 = a.dst_slot0, dst_rows = a.dst_rows;
+    const int64_t dst_stride = a.dst_stride;
+    void *dst = a.dst;
+    const st_t *bias = (const st_t *)a.bias;
+    const int next_layer = a.next_layer, nk_h = a.nk_h, ns_h_log = a.ns_h_log, np_h = a.np_h, nh_out = a.nh_out, next_c_out = a.next_c_out, to_output = a.to_output;
+    unsigned long long *stats = h.stats;
+    const int n_layers = h.n_layers;
+    asm volatile("" ::"s"(act), "s"(shr), "s"(clamp_hi), "s"(c_out), "s"(dst_cells), "s"(dst_slot0), "s"(dst_rows), "s"(dst_stride), "s"(dst), "s"(bias),
+                 "s"(next_layer), "s"(nk_h), "s"(ns_h_log), "s"(np_h), "s"(nh_out), "s"(next_c_out), "s"(to_output), "s"(stats), "s"(n_layers));
+    barrier();
+    if (!on || kq > 0) return;
+
+    const int co0 = ct * 16 + g * 4;
+    st_t hv[4];
+    {
+        acc_t part[kTeam - 1];
+#pragma unroll
+        for (int w = 0; w < kTeam - 1; ++w) part[w] = share[w * 64 + lane];
+        st_t c[4] = {0, 0, 0, 0};
+        if (bias) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c[i] = bias[co0 + i < c_out ? co0 + i : c_out - 1];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            c[i] += acc[i];
+#pragma unroll
+            for (int w = 0; w < kTeam - 1; ++w) c[i] += part[w][i];
+            hv[i] = co0 + i < c_out ? T::activate(c[i], act, shr, clamp_hi) : (st_t)0;
+        }
+    }
+    int slot = dst_slot0 + o;
+    slot = slot >= dst_rows ? slot - dst_rows : slot;
+    const int at = flat ? slot : slot * w_out + x;
+    if (to_output) {                               // 4-byte values, not rounded to the event type
+        st_t *d = (st_t *)dst + (int64_t)stream * dst_stride + (int64_t)at * c_out + co0;
+        if (valid) {
+            if (c_out % 4 == 0) {
+                if (co0 < c_out) *reinterpret_cast<acc_t *>(d) = acc_t{hv[0], hv[1], hv[2], hv[3]};
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (co0 + i < c_out) d[i] = hv[i];
+            }
+        }
+        return;
+    }
+    uint32_t e[EB], nz = 0;
+    T::pack4(hv, e);
+    if (valid && co0 < dst_cells * VL) {
+        unsigned char *d = (unsigned char *)dst + ((int64_t)stream * dst_stride + (int64_t)at * dst_cells * VL + co0) * EB;
+        if constexpr (EB == 1) *reinterpret_cast<uint32_t *>(d) = e[0];
+        else if constexpr (EB == 2) *reinterpret_cast<i32x2 *>(d) = i32x2{(int)e[0], (int)e[1]};
+        else *reinterpret_cast<i32x4 *>(d) = i32x4{(int)e[0], (int)e[1], (int)e[2], (int)e[3]};
+#pragma unroll
+        for (int i = 0; i < EB; ++i) nz += (uint32_t)T::nonzero(e[i]);
+    }
+    if (!stats || next_layer < 0) return;
+    // events of the next layer and the taps they reach
+    uint32_t ev_all = nz;
+    uint32_t taps_all = nz * (uint32_t)(taps_axis(y0 + o, nk_h, ns_h_log, np_h, nh_out) * (flat ? 1 : taps_axis(x, a.nk_w, a.ns_w_log, a.np_w, a.nw_out)));
+    // per stream: over the four groups of channels, then over the stream's positions
+    ev_all += __shfl_xor(ev_all, 16); taps_all += __shfl_xor(taps_all, 16);
+    ev_all += __shfl_xor(ev_all, 32); taps_all += __shfl_xor(taps_all, 32);
+    for (int w = 1; w < (1 << per_log); w <<= 1) { ev_all += __shfl_xor(ev_all, w); taps_all += __shfl_xor(taps_all, w); }
+    if (g == 0 && pl == 0 && ev_all) {
+        unsigned long long *d = stats + ((int64_t)stream * n_layers + next_layer) * 2;
+        atomicAdd(d, (unsigned long long)ev_all);
+        atomicAdd(d + 1, (unsigned long long)taps_all * (unsigned long long)next_c_out);
+    }
+}
+
+template <class T, int NS, bool COUNT>
+__global__ void __launch_bounds__(64 * kTeam) k_conv_gather_rows(const GatherBatch<NS> args, const StreamSel sel)
+{
+    typedef const __attribute__((address_space(4))) GatherBatch<NS> Batch;
+    Batch &b = *(Batch *)__builtin_amdgcn_kernarg_segment_ptr();
+    __shared__ typename T::acc_t share[(kTeam - 1) * 64];
+    // The steps' tiles follow each other without gaps: workgroups go to the compute units in turn, and with an empty one here
+    // and there some units got the tiles of three layers and others none (12.7 us per launch of 64 audio streams instead of 7).
+    int k = 0, tile = blockIdx.x;
+    {
+        int end[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) end[i] = b.head.end[i];
+        asm volatile("" ::"s"(end[0]), "s"(end[1]), "s"(end[2]), "s"(end[3]), "s"(end[4]), "s"(end[5]), "s"(end[6]), "s"(end[7]));
+        int first = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) if ((int)blockIdx.x >= end[i]) { k = i + 1; first = end[i]; }
+        tile -= first;
+    }
+    Step &a = b.st[k];
+    {   // first round of scalar loads, with one wait
+        const int take = a.take, n_ct = a.n_ct, n_pt = a.n_pt, spt_log = a.spt_log, base = sel.base, pos0 = sel.pos0;
+        const int n_sb = b.head.n_sb, n_sb8 = b.head.n_sb8, sb_log = b.head.sb_log, n_sel = sel.n;
+        const unsigned sb_rcp = b.head.sb_rcp;
+        asm volatile("" ::"s"(take), "s"(n_ct), "s"(n_pt), "s"(spt_log), "s"(base), "s"(pos0), "s"(n_sb), "s"(n_sb8), "s"(sb_log), "s"(n_sel), "s"(sb_rcp));
+    }
+    const int take = a.take, spt_log = a.spt_log;
+    int sg, rest;                                  // group of streams; tile of positions and channels
+    if (b.head.n_sb > 0) {
+        // workgroups go to the XCDs in turn: a block of streams meets one and the same in every layer, whose L2 then has the
+        // rows that the layer before has just written
+        const int inner = (int)__umulhi((unsigned)tile, b.head.sb_rcp), sb = tile - inner * b.head.n_sb8, subs = b.head.sb_log - spt_log;
+        if (sb >= b.head.n_sb) return;
+        sg = (sb << subs) + (inner & ((1 << subs) - 1));
+        rest = inner >> subs;
+        if ((sg << spt_log) >= sel.n) return;
+    } else {
+        const int per = a.n_ct * a.n_pt;
+        sg = take ? tile : (int)((unsigned)tile / (unsigned)per);
+        rest = take ? 0 : tile - sg * per;
+    }
+    if (take) { take_rows<T>(b.head, a, sel, sg, threadIdx.x, 64 * kTeam); return; }
+    const int pt = a.ct_rcp ? (int)__umulhi((unsigned)rest, a.ct_rcp) : rest, ct = rest - pt * a.n_ct;
+    conv_tile<T, COUNT>(b.head, a, sel, sg << spt_log, pt, ct, spt_log, true, uni(threadIdx.x >> 6), share, [] { lds_barrier(); });
+}
+
+template <class T, int NS, bool COUNT>
+__global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherBatch<NS> args, const StreamSel sel)
+{
+    typedef const __attribute__((address_space(4))) GatherBatch<NS> Batch;
+    Batch &b = *(Batch *)__builtin_amdgcn_kernarg_segment_ptr();
+    __shared__ typename T::acc_t share[4][(kTeam - 1) * 64];
+    const int team = uni(threadIdx.x >> 8), kq = uni((threadIdx.x >> 6) & 3), si = blockIdx.x;
+    for (int k = 0; k < b.head.n; ++k) {
+        Step &a = b.st[k];
+        if (a.take) {
+            take_rows<T>(b.head, a, sel, si, threadIdx.x, 256 * kTeam);
+        } else {
+            const int tasks = a.n_ct * ((a.n_rows * a.w_out + 15) >> 4);
+            for (int t0 = 0; t0 < tasks; t0 += 4) {
+                const int t = t0 + team, pt = a.ct_rcp ? (int)__umulhi((unsigned)t, a.ct_rcp) : t, ct = t - pt * a.n_ct;
+                conv_tile<T, COUNT>(b.head, a, sel, si, pt, ct, 0, t < tasks, kq, share[team], [] { lds_barrier(); });
+                lds_barrier();                     // the sums have been read
+            }
+        }
+        __syncthreads();                           // what this step stored is there for the next
+    }
+}
+
+// Positions of a step's tiles that belong to one stream.
+int streams_per_tile_log(int positions, bool first)
+{
+    // (a first layer has few channels and its rows are many: its tiles stay with one stream)
+    int l = 0;
+    while (!first && l < 4 && (positions << (l + 1)) <= 16) ++l;
+    return l;
+}
+
+template <class T, int NS> hipError_t launch_ns(const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc)
+{
+    GatherBatch<NS> b;
+    b.head = h;
+    // streams in blocks that no tile crosses, if there is one for every XCD
+    b.head.sb_log = 2;
+    for (int k = 0; k < h.n; ++k) b.head.sb_log = std::max(b.head.sb_log, st[k].spt_log);
+    b.head.n_sb = (sel.n + (1 << b.head.sb_log) - 1) >> b.head.sb_log;
+    b.head.n_sb8 = (b.head.n_sb + 7) / 8 * 8;
+    if (b.head.n_sb * 5 < b.head.n_sb8 * 4) b.head.n_sb = 0;               // (blocks for at least four XCDs in five, in every round)
+    b.head.sb_rcp = b.head.n_sb ? (unsigned)((0x100000000ull + b.head.n_sb8 - 1) / b.head.n_sb8) : 0u;
+    int64_t tiles = 0;
+    for (int k = 0; k < 8; ++k) b.head.end[k] = INT32_MAX;
+    for (int k = 0; k < h.n; ++k) {
+        b.st[k] = st[k];
+        GatherStep &a = b.st[k];
+        const int groups = b.head.n_sb > 0 ? b.head.n_sb8 << (b.head.sb_log - a.spt_log) : (sel.n + (1 << a.spt_log) - 1) >> a.spt_log;
+        a.tiles = groups * (a.take ? 1 : a.n_ct * a.n_pt);
+        tiles += b.st[k].tiles;
+        if (k < 8 && k + 1 < h.n) b.head.end[k] = (int)tiles;
+    }
+    if (chain) {
+        const dim3 grid(sel.n), block(256 * kTeam);
+        return h.issued ? launch(k_conv_gather_chain<T, NS, true>, grid, block, 0, lc, b, sel) : launch(k_conv_gather_chain<T, NS, false>, grid, block, 0, lc, b, sel);
+    }
+    if (tiles < 1 || tiles > INT32_MAX / (64 * kTeam)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)tiles), block(64 * kTeam);
+    return h.issued ? launch(k_conv_gather_rows<T, NS, true>, grid, block, 0, lc, b, sel) : launch(k_conv_gather_rows<T, NS, false>, grid, block, 0, lc, b, sel);
+}
+
+template <class T> hipError_t launch_t(const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc)
+{
+    // (the short block for the usual few steps: a third of the bytes to hand over)
+    return h.n <= 4 ? launch_ns<T, 4>(h, st, sel, chain, lc) : launch_ns<T, kGatherMax>(h, st, sel, chain, lc);
+}
+
+}  // namespace
+
+// How the tiles of a step lie (n_rows and the layer's shape are set).
+void conv_gather_shape(bool first, GatherStep &a)
+{
+    auto rcp32 = [](int n) { return n > 1 ? (unsigned)((0x100000000ull + n - 1) / n) : 0u; };
+    if (a.take) { a.spt_log = 0; a.n_pt = 1; return; }
+    const int positions = a.n_rows * a.w_out;
+    a.spt_log = streams_per_tile_log(positions, first);
+    a.n_pt = (positions + (16 >> a.spt_log) - 1) / (16 >> a.spt_log);
+    a.ct_rcp = rcp32(a.n_ct);
+}
+
+// The 1-D nets that go through units of this kernel from end to end, with pushes of all streams side by side.
+bool cascade1d_eligible(int prec, const Geom *g, int n_layers, int max_seg_rows)
+{
+    if (prec != IDF_PREC_F32 || n_layers > kRowUnits || max_seg_rows > 16) return false;
+    for (int l = 0; l < n_layers; ++l) {
+        if (g[l].kind != IDF_CONV || g[l].w_in != 1 || g[l].w_out != 1 || g[l].k_w != 1) return false;
+        if (g[l].c_in > 64 || g[l].c_out > 64 || g[l].k_h > 9 || g[l].s_h > 2 || g[l].k_h < g[l].s_h) return false;
+        if (g[l].act != IDF_ACT_NONE && g[l].act != IDF_ACT_RELU) return false;
+    }
+    return true;
+}
+
+// What a step needs to know of its layer whatever the rows.
+void conv_gather_layer(int prec, const Geom &g, GatherStep &a)
+{
+    const int vl = conv3x3_mfma_vl(prec);
+    auto log2i = [](int n) { int l = 0; while ((1 << l) < n) ++l; return l; };
+    a.flat = g.w_in == 1 && g.w_out == 1 && g.k_w == 1 && g.p_w == 0;
+    a.c_in = g.c_in; a.c_out = g.c_out; a.cells = (g.c_in + vl - 1) / vl;
+    a.k_h = g.k_h; a.k_w = g.k_w; a.s_h_log = log2i(g.s_h); a.s_w_log = log2i(g.s_w); a.p_h = g.p_h; a.p_w = g.p_w;
+    a.h_in = g.h_in > 0 ? g.h_in : INT32_MAX; a.w_in = g.w_in; a.h_out = g.h_out; a.w_out = g.w_out;
+    a.act = g.act; a.shr = g.shr; a.clamp_hi = g.clamp_hi;
+    a.n_ct = (g.c_out + 15) / 16;
+    a.n_ks = (g.k_h * g.k_w * a.cells + 3) / 4;
+    a.cells_rcp = (unsigned)((65536 + a.cells - 1) / a.cells);
+    a.kw_rcp = (unsigned)((65536 + g.k_w - 1) / g.k_w);
+    a.wout_rcp = (unsigned)((0x100000000ull + g.w_out - 1) / g.w_out);
+}
+
+// Weights [k_h][k_w][c_in][c_out] -> [K-step][tile of 16 channels][lane][16 bytes], lane = 16 g + m holding cell 4 s + g of the
+// K-step, counted (ky, kx, cell of channels), for channel m of the tile; zero padded.
+size_t conv_gather_pack(int prec, const Geom &g, const void *w_khkwcico, void *out)
+{
+    const int vl = conv3x3_mfma_vl(prec), eb = 16 / vl, cells = (g.c_in + vl - 1) / vl, n_ct = (g.c_out + 15) / 16;
+    const int n_ks = (g.k_h * g.k_w * cells + 3) / 4;
+    const size_t bytes = (size_t)n_ks * n_ct * 1024;
+    if (!out) return bytes;
+    unsigned char *o = (unsigned char *)out;
+    const unsigned char *src = (const unsigned char *)w_khkwcico;
+    memset(o, 0, bytes);
+    for (int tap = 0; tap < g.k_h * g.k_w; ++tap)
+        for (int ci = 0; ci < g.c_in; ++ci) {
+            const int q = tap * cells + ci / vl;
+            for (int co = 0; co < g.c_out; ++co)
+                memcpy(o + ((size_t)(q / 4) * n_ct + co / 16) * 1024 + (size_t)((q % 4) * 16 + co % 16) * 16 + (size_t)(ci % vl) * eb,
+                       src + (((size_t)tap * g.c_in + ci) * g.c_out + co) * eb, eb);
+        }
+    return bytes;
+}
+
+hipError_t launch_conv_gather(int prec, const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc)
+{
+    if (h.n < 1 || h.n > kGatherMax) return hipErrorInvalidValue;
+    switch (prec) {
+    case IDF_PREC_F32: return launch_t<TraitsF32>(h, st, sel, chain, lc);
+    case IDF_PREC_BF16: return launch_t<TraitsBf16>(h, st, sel, chain, lc);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace idf
