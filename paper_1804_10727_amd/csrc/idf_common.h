@@ -221,7 +221,7 @@ constexpr int kGatherSegs = 16;      // buffers of the caller a launch can take 
 constexpr int kBatchRows = 256;      // and rows
 struct GatherStep {
     // (in the order a workgroup needs them: a scalar load brings 64 bytes)
-    int tiles, take;             // workgroups (set by the launcher); 1: the caller's rows are taken in
+    int tiles, take;             // workgroups (set by the launcher); 1: the caller's rows are taken in, 2: a max-pool
     int n_ct, n_pt, spt_log;     // tiles of channels; of positions per stream or group of streams; streams per tile (log2)
     unsigned ct_rcp;
     int n_rows, y0;              // output rows (take: input rows): how many, first within its sample
@@ -234,7 +234,7 @@ struct GatherStep {
     void *ring, *dst;
     const void *w_frag, *bias;
     int h_in, p_h;
-    int dst_slot0, dst_rows;
+    int dst_slot0, dst_rows;     // ring slot of the first row that leaves, rows of that ring (take: first column given, columns given)
 
     int c_in, c_out, dst_cells, to_output;
     int act, shr, clamp_hi, layer;

@@ -34,10 +34,10 @@ __device__ __forceinline__ void lds_barrier()
 #endif
 }
 
-enum KernelKind { kKindConvGeneric = 0, kKindPoolGeneric, kKindCopyOut, kKindCascade1d, kKindConvMfma, kKindHead, kKindEager, kKindCount };
+enum KernelKind { kKindConvGeneric = 0, kKindPoolGeneric, kKindCopyOut, kKindCascade1d, kKindConvMfma, kKindHead, kKindEager, kKindConvGather, kKindCount };
 inline const char *kind_name(int k)
 {
-    static const char *names[kKindCount] = {"conv_generic", "pool_generic", "copy_out", "cascade1d", "conv3x3_mfma", "head_accumulate", "eager"};
+    static const char *names[kKindCount] = {"conv_generic", "pool_generic", "copy_out", "cascade1d", "conv3x3_mfma", "head_accumulate", "eager", "conv_gather"};
     return k >= 0 && k < kKindCount ? names[k] : "?";
 }
 
@@ -77,6 +77,8 @@ hipError_t launch_conv3x3_mfma_rows(int prec, const RowBatch &b, const StreamSel
 
 // Matrix-core kernel that gathers its windows from memory: any kernel size, strides 1, 2, 4 .., any padding.
 void conv_gather_layer(int prec, const Geom &g, GatherStep &a);
+bool conv_gather_takes(int prec, const Geom &g, int ring_rows);
+double conv_gather_traffic(int prec, const Geom &g, int n_streams, int rows);
 void conv_gather_shape(bool first, GatherStep &a);
 size_t conv_gather_pack(int prec, const Geom &g, const void *w_khkwcico, void *out);
 // chain: the steps one after the other (a workgroup per stream), else all side by side.

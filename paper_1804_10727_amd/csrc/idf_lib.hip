@@ -64,6 +64,7 @@ struct idf_net {
     std::vector<std::vector<unsigned char>> w_img, b_img;
     // per conv layer the matrix-core kernel can serve: weights in its fragment order (else empty)
     std::vector<std::vector<unsigned char>> wm_img;
+    bool finite = true;              // no weight is infinite or NaN
     int out_w = 0, out_c = 0;
     int64_t out_h = 0;
     int open_count = 0;
@@ -114,7 +115,8 @@ struct idf_streams {
     int static_dev = -1;             // >= 0: the workspace is that device's static array (given back at close)
     int cus = 0;                     // compute units of the device the streams were opened on
     int ev_per_step = 0;             // int8 event path (idf_set_event_path): events a tile may hold per K-step of its contraction and still go that way; 0: off
-    bool use_cascade1d = false;      // 1-D net: its layers are units of the gathering kernel
+    bool use_gather = false;         // the layers are units of the gathering kernel
+    bool use_cascade1d = false;      // such a net, 1-D
     bool prof_on = false;
     std::vector<ProfRec> prof;
     std::vector<hipEvent_t> ev_pool;
@@ -124,7 +126,7 @@ struct idf_streams {
     hipStream_t st = nullptr;
     char *ws = nullptr;
     size_t ws_bytes = 0;
-    std::vector<size_t> w_off, b_off, wm_off, ring_off, held_off, transit_off;
+    std::vector<size_t> w_off, b_off, wm_off, wg_off, ring_off, held_off, transit_off;
     std::vector<int> mfma;           // per layer: 1 = matrix-core conv kernel, 2 = pool fused into the conv before it
     std::vector<int64_t> ring_stride, held_stride, transit_stride;   // elements per stream
     std::vector<int> transit_cap;                                    // rows per stream
@@ -207,14 +209,15 @@ int max_emit(const Geom &g, int cap_in)
 }
 
 struct Layout {
-    std::vector<size_t> w_off, b_off, wm_off, ring_off, held_off, transit_off;
+    std::vector<size_t> w_off, b_off, wm_off, wg_off, ring_off, held_off, transit_off;
     std::vector<int64_t> ring_stride, held_stride, transit_stride;
     std::vector<int> transit_cap;
     std::vector<int> mfma;           // per layer: 1 = matrix-core conv kernel, 2 = pool fused into the conv before it
     std::vector<RowUnit> units;
     size_t out_off = 0, stats_off = 0, issued_off = 0, head_off = 0, total = 0;
     int64_t out_stride = 0;
-    bool cascade1d = false;          // the gathering kernel serves this 1-D net
+    bool gather = false;             // the gathering kernel serves this net
+    bool cascade1d = false;          // and it is 1-D
     idf_sizes sizes{};
 };
 
@@ -222,6 +225,12 @@ struct Layout {
 // takes its rows in pairs, so besides the K_h rows its output rows still need at most two rows wait for it
 // when a call returns.  Pushes of several rows leave up to the rows one launch completes, and one more.
 constexpr int kStgWait = 2;
+
+// Bytes a 3x3 layer's step on the gathering kernel may fetch from the caches; beyond, the net's 3x3 layers stay on the kernel
+// made for them.  Measured, 32 rows through a strided layer and two 3x3 layers, here against layer by layer: 4 MB per layer and
+// step 183 us against 497, 132 MB 598 against 832, 264 MB 925 against 1165 (float32); 528 MB 1570 against 1823 (bfloat16);
+// 1060 MB 2977 against 2847 (float32).
+constexpr double kGatherTraffic = 300e6;
 
 // The layers run strictly depth-first within each call (nothing waits between layers across
 // calls) when the staged modes are switched off.
@@ -257,12 +266,35 @@ std::vector<int> mfma_layers(const idf_net &net)
     return m;
 }
 
+// Rows the ring in front of layer l has on the gathering kernel when at most `rows` rows arrive with a launch: those some
+// output row still needs, and those of a launch while those of the one before are being read.
+int gather_ring(const Geom &g, int rows) { return 2 * rows + g.k_h + g.s_h; }
+
+// Nets of several kinds of layers that go through the gathering kernel, all layers side by side in one launch per push.
+// Layer by layer each kind has launches of its own, which is what such a net spends its time on until the layers are large.
+// Then 3x3 layers are better off on the kernel made for them, which reads each weight and cell far less often.
+bool gather_net(const idf_net &net, int B, int max_seg)
+{
+    const int n = (int)net.g.size();
+    if (strict_rows() || net_all_mfma(net) || !net.finite || n > kRowUnits || max_seg > 16) return false;
+    if (!net.wm_img[0].empty()) return false;       // a 3x3 layer in front has the largest map, on the kernel made for it
+    int rows = max_seg;
+    for (int l = 0; l < n; ++l) {
+        const Geom &g = net.g[l];
+        if (g.kind == IDF_MAXPOOL && (l == 0 || l == n - 1)) return false;
+        if (!conv_gather_takes(net.precision, g, gather_ring(g, rows))) return false;
+        rows = std::max(1, max_emit(g, rows));
+        if (!net.wm_img[l].empty() && conv_gather_traffic(net.precision, g, B, rows) > kGatherTraffic) return false;
+    }
+    return true;
+}
+
 int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout &L)
 {
     const int n = (int)net.g.size();
     const int eb = ev_bytes(net.precision);
     size_t off = 0;
-    L.w_off.assign(n, 0); L.b_off.assign(n, 0); L.wm_off.assign(n, 0);
+    L.w_off.assign(n, 0); L.b_off.assign(n, 0); L.wm_off.assign(n, 0); L.wg_off.assign(n, 0);
     L.ring_off.assign(n, 0); L.held_off.assign(n, 0); L.transit_off.assign(n, 0);
     L.ring_stride.assign(n, 0); L.held_stride.assign(n, 0); L.transit_stride.assign(n, 0);
     L.transit_cap.assign(n, 0);
@@ -278,12 +310,12 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     }
     L.cascade1d = cascade1d_eligible(net.precision, net.g.data(), n, max_seg);
     const bool all_mfma = net_all_mfma(net);
-    L.mfma = mfma_layers(net);
+    L.gather = L.cascade1d || gather_net(net, B, max_seg);
+    L.mfma = L.gather ? std::vector<int>(n, 0) : mfma_layers(net);
     for (int l = 0; l < n; ++l) {
         if (net.g[l].kind != IDF_CONV) continue;
-        // (the gathering kernel reads a packing of its own)
-        const size_t wsz = L.cascade1d ? conv_gather_pack(net.precision, net.g[l], nullptr, nullptr) : net.w_img[l].size();
-        L.w_off[l] = off; off = align_up(off + wsz);
+        L.w_off[l] = off; off = align_up(off + net.w_img[l].size());
+        if (L.gather) { L.wg_off[l] = off; off = align_up(off + conv_gather_pack(net.precision, net.g[l], nullptr, nullptr)); }
         L.b_off[l] = off; off = align_up(off + net.b_img[l].size());
         L.wm_off[l] = off; off = align_up(off + net.wm_img[l].size());
     }
@@ -296,11 +328,11 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
         // some row of c has yet to take in (they lie in the ring the layer before writes them to).
         if (g.kind == IDF_CONV) {
             L.ring_stride[l] = (int64_t)g.k_h * g.w_out * g.c_out;
-            if (!L.mfma[l] && !L.cascade1d) { L.ring_off[l] = off; off = align_up(off + (size_t)L.ring_stride[l] * 4 * B); }
+            if (!L.mfma[l] && !L.gather) { L.ring_off[l] = off; off = align_up(off + (size_t)L.ring_stride[l] * 4 * B); }
             state_per_stream += (size_t)L.ring_stride[l] * 4;
         } else {
             L.held_stride[l] = (int64_t)g.w_in * g.c_out;
-            if (!L.mfma[l]) { L.held_off[l] = off; off = align_up(off + (size_t)L.held_stride[l] * eb * B); }
+            if (!L.mfma[l] && !L.gather) { L.held_off[l] = off; off = align_up(off + (size_t)L.held_stride[l] * eb * B); }
             state_per_stream += (size_t)L.held_stride[l] * eb;
         }
         if (L.mfma[l] == 1) {
@@ -320,9 +352,9 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
             transit_per_stream += (size_t)u.ring_stride * eb;
             L.units.push_back(u);
         }
-        // (the 1-D cascade passes rows on inside LDS; a conv layer's rows go straight into a fused pool)
+        // (a conv layer's rows go straight into a fused pool, or into the ring of the layer behind)
         const bool into_fused_pool = l + 1 < n && L.mfma[l + 1] == 2, into_ring = l + 1 < n && L.mfma[l + 1] == 1;
-        if (l < n - 1 && !L.cascade1d && !into_fused_pool && !into_ring) {
+        if (l < n - 1 && !L.gather && !into_fused_pool && !into_ring) {
             L.transit_stride[l] = (int64_t)L.transit_cap[l] * g.w_out * g.c_out;
             L.transit_off[l] = off; off = align_up(off + (size_t)L.transit_stride[l] * eb * B);
             transit_per_stream += (size_t)L.transit_stride[l] * eb;
@@ -340,23 +372,22 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     L.stats_off = off; off = align_up(off + (size_t)B * n * 2 * sizeof(unsigned long long));
     L.issued_off = off; off = align_up(off + (size_t)B * n * sizeof(unsigned long long));
     L.head_off = off; off = align_up(off + (size_t)B * net.out_c * 2 * sizeof(double));   // sums, means
-    if (L.cascade1d) {
-        // every layer's input lies in a ring: the rows some output row still needs, those of a launch while those of the one
-        // before are being read -- of up to kGatherSegs pushes, where they are held back
-        int big = std::min(kGatherSegs * max_seg, kBatchRows), small = max_seg;
+    if (L.gather) {
+        // every layer's input lies in a ring, with room (1-D) for the rows of up to kGatherSegs pushes, where they are held back
+        int big = L.cascade1d ? std::min(kGatherSegs * max_seg, kBatchRows) : max_seg, small = max_seg;
         for (int l = 0; l < n; ++l) {
             const Geom &g = net.g[l];
             RowUnit u;
             u.l = u.lp = l; u.last = l == n - 1; u.next = l + 1 < n ? l + 1 : -1;
-            u.ring_rows = 2 * small + g.k_h + g.s_h;
-            u.ring_room = 2 * big + g.k_h + g.s_h;
+            u.ring_rows = gather_ring(g, small);
+            u.ring_room = gather_ring(g, big);
             const int vl = conv3x3_mfma_vl(net.precision);
             u.row_elems = g.w_in * ((g.c_in + vl - 1) / vl * vl);
             u.ring_stride = (int64_t)u.ring_rows * u.row_elems;
             u.ring_off = off; off = align_up(off + (size_t)u.ring_room * u.row_elems * eb * B);
             transit_per_stream += (size_t)u.ring_room * u.row_elems * eb;
             // what is alive between two pushes
-            if (l < n - 1 && !strict_cascade()) handover_per_stream += (size_t)L.transit_cap[l] * g.c_out * 4;
+            if (l < n - 1 && !(L.cascade1d && strict_cascade())) handover_per_stream += (size_t)L.transit_cap[l] * g.w_out * g.c_out * eb;
             L.units.push_back(u);
             big = std::max(1, max_emit(g, big)); small = std::max(1, max_emit(g, small));
         }
@@ -678,7 +709,20 @@ void gather_step(const idf_streams *s, int k, int64_t o, int64_t n, int n_stream
     conv_gather_shape(k == 0, a);
     const double eb = ev_bytes(net.precision);
     bytes += n_streams * ((double)((n - 1) * g.s_h + g.k_h) * g.w_in * g.c_in * eb + (u.last ? (double)n * net.out_w * net.out_c * 4 : 0.0)) +
-             (double)g.k_h * g.k_w * g.c_in * g.c_out * w_bytes(net.precision) + (a.bias ? g.c_out * 4.0 : 0.0);
+             (g.kind == IDF_CONV ? (double)g.k_h * g.k_w * g.c_in * g.c_out * w_bytes(net.precision) + (a.bias ? g.c_out * 4.0 : 0.0) : 0.0);
+}
+
+// The step that takes n rows of the caller, the first of which is row `at` counted over samples: columns [x_lo, x_hi).
+void gather_take(const idf_streams *s, int64_t at, int n, int x_lo, int x_hi, GatherStep &a)
+{
+    const RowUnit &u = s->units[0];
+    const Geom &g = s->net->g[u.l];
+    a = s->gather[0];
+    a.take = 1;
+    a.y0 = (int)(g.h_in > 0 ? at % g.h_in : near_start(at));
+    a.n_rows = n; a.ring_rows = u.ring_rows; a.slot0 = mod_rows(at, u.ring_rows);
+    a.dst_slot0 = x_lo; a.dst_rows = x_hi - x_lo;
+    conv_gather_shape(true, a);
 }
 
 // One launch for streams that all stand at p; as row_plan, without pairs.  chain: the layers one after the other, each on
@@ -690,14 +734,7 @@ bool gather_plan(const idf_streams *s, RowProg &p, int n_streams, int n_new, boo
     RowProg q = p;
     h.n = 0;
     auto take = [&]() {
-        GatherStep &a = st[h.n++];
-        const RowUnit &u = s->units[0];
-        const Geom &g = net.g[u.l];
-        a = s->gather[0];
-        a.take = 1;
-        const int64_t y = g.h_in > 0 ? p.in[0] % g.h_in : near_start(p.in[0]);
-        a.y0 = (int)y; a.n_rows = n_new; a.ring_rows = u.ring_rows; a.slot0 = mod_rows(p.in[0], u.ring_rows);
-            conv_gather_shape(true, a);
+        gather_take(s, p.in[0], n_new, s->part.on ? s->part.x_lo : 0, s->part.on ? s->part.x_hi : net.in_w, st[h.n++]);
         bytes += (double)n_streams * n_new * net.in_w * net.in_c * ev_bytes(net.precision);
     };
     if (chain && n_new > 0) { take(); q.in[0] += n_new; }
@@ -738,14 +775,17 @@ int gather_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *con
     h.n_layers = (int)net.g.size();
     h.stats = (unsigned long long *)(s->ws + s->stats_off);
     h.issued = s->count_issued ? (unsigned long long *)(s->ws + s->issued_off) : nullptr;
-    h.n_in = n_seg; h.seg_rows = seg_rows; h.in_stride = seg_rows * net.in_w * net.in_c;
+    h.n_in = n_seg; h.seg_rows = seg_rows; h.in_stride = seg_rows * (s->part.on ? s->part.x_hi - s->part.x_lo : net.in_w) * net.in_c;
     for (int i = 0; i < n_seg; ++i) h.in[i] = bufs[i];
     // What is on its way goes through in one launch, a workgroup per stream and one layer after the other, unless that is more
     // than a tile or two per layer and stream: a launch per layer, on the whole chip, is faster then (37 audio streams with 256
     // samples each on their way: 40 us against 370).
-    int64_t most = n_seg * seg_rows;               // rows of one layer that wait
-    for (size_t k = 0; k < s->units.size(); ++k) most = std::max(most, rows_ready(net.g[s->units[k].l], p.in[k]) - p.out[k]);
-    const bool chain = out && (strict_cascade() || most <= 32);
+    int64_t most = n_seg * seg_rows;               // positions of one layer that wait
+    for (size_t k = 0; k < s->units.size(); ++k) {
+        const Geom &g = net.g[s->units[k].l];
+        most = std::max(most, (rows_ready(g, p.in[k]) - p.out[k]) * g.w_out);
+    }
+    const bool chain = out && ((s->use_cascade1d && strict_cascade()) || most <= 32);
     for (bool fresh = n_seg > 0; fresh || out;) {
         double bytes = 0;
         bool took = fresh && gather_plan(s, p, sel.n, n_seg * seg_rows, chain, h, st, bytes);
@@ -757,7 +797,7 @@ int gather_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *con
             }
         }
         if (took) fresh = false;
-        hipError_t e = launch_conv_gather(net.precision, h, st, sel, chain, launch_ctx(s, kKindCascade1d, bytes));
+        hipError_t e = launch_conv_gather(net.precision, h, st, sel, chain, launch_ctx(s, s->use_cascade1d ? kKindCascade1d : kKindConvGather, bytes));
         if (e != hipSuccess) return dev_fail(e, "gather launch");
     }
     return IDF_OK;
@@ -865,7 +905,7 @@ bool row_pending(const idf_streams *s, const RowProg &p)
 int stg_drain(idf_streams *s)
 {
     if (!s->stg2d) return IDF_OK;
-    auto through = [&](const StreamSel &sel, RowProg &p) { return s->use_cascade1d ? gather_run(s, sel, p, nullptr, 0, 1, true) : row_run(s, sel, p, nullptr, 0); };
+    auto through = [&](const StreamSel &sel, RowProg &p) { return s->use_gather ? gather_run(s, sel, p, nullptr, 0, 1, true) : row_run(s, sel, p, nullptr, 0); };
     if (s->prog_same) {
         if (!row_pending(s, s->prog_all)) return IDF_OK;
         StreamSel all{};
@@ -1123,11 +1163,11 @@ template <class F> void for_each_state_piece(const idf_streams *s, int id, int64
     const int n = (int)net.g.size();
     const int eb = ev_bytes(net.precision);
     for (int l = 0; l < n; ++l) {
-        if (s->mfma[l] || s->use_cascade1d) continue;
+        if (s->mfma[l] || s->use_gather) continue;
         if (net.g[l].kind == IDF_CONV) f(s->ring_off[l] + (size_t)id * s->ring_stride[l] * 4, (size_t)s->ring_stride[l] * 4);
         else f(s->held_off[l] + (size_t)id * s->held_stride[l] * eb, (size_t)s->held_stride[l] * eb);
     }
-    if (s->use_cascade1d) {
+    if (s->use_gather) {
         // row by row, the K_h newest of every layer: how many rows of a ring are in use differs between openings
         const RowProg p = prog_at(s, rows_in, false);
         for (size_t k = 0; k < s->units.size(); ++k) {
@@ -1559,6 +1599,13 @@ int idf_create_net(const idf_net_desc *d, const void *const *weights, const void
                 size_t d_idx = (((size_t)ky * L.k_w + kx) * L.c_in + ci) * L.c_out + co;
                 memcpy(&img[d_idx * wb], src + s_idx * wb, wb);
             }
+            auto not_finite = [&](size_t i) {
+                if (wb == 1) return false;
+                uint32_t v = 0;
+                memcpy((unsigned char *)&v + 4 - wb, &img[i * wb], wb);
+                return (v & 0x7f800000u) == 0x7f800000u;
+            };
+            for (size_t i = 0; i * wb < img.size() && net->finite; ++i) net->finite = !not_finite(i);
             if (conv3x3_mfma_eligible(d->precision, g)) {
                 net->wm_img.back().resize(conv3x3_mfma_pack(d->precision, g, nullptr, nullptr));
                 conv3x3_mfma_pack(d->precision, g, img.data(), net->wm_img.back().data());
@@ -1776,11 +1823,11 @@ int open_on(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
     s->net = net; s->B = n_streams; s->max_seg = max_seg_rows;
     s->out_cap = out_cap_rows > 0 ? out_cap_rows : net->out_h;
     s->st = (hipStream_t)hip_stream; s->ws = (char *)dev_workspace; s->ws_bytes = workspace_bytes;
-    s->w_off = L.w_off; s->b_off = L.b_off; s->wm_off = L.wm_off; s->ring_off = L.ring_off; s->held_off = L.held_off;
+    s->w_off = L.w_off; s->b_off = L.b_off; s->wm_off = L.wm_off; s->wg_off = L.wg_off; s->ring_off = L.ring_off; s->held_off = L.held_off;
     s->transit_off = L.transit_off; s->ring_stride = L.ring_stride; s->held_stride = L.held_stride;
     s->transit_stride = L.transit_stride; s->transit_cap = L.transit_cap;
     s->out_off = L.out_off; s->stats_off = L.stats_off; s->issued_off = L.issued_off; s->out_stride = L.out_stride; s->sizes = L.sizes;
-    s->use_cascade1d = L.cascade1d;
+    s->use_gather = L.gather; s->use_cascade1d = L.cascade1d;
     s->head_off = L.head_off;
     {
         int dev = 0;
@@ -1789,9 +1836,9 @@ int open_on(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
     s->mfma = L.mfma; s->units = L.units;
     s->unit_of.assign(net->g.size(), -1);
     for (size_t k = 0; k < s->units.size(); ++k) s->unit_of[s->units[k].l] = (int)k;
-    s->stg2d = L.cascade1d || (!strict_rows() && net_all_mfma(*net));
+    s->stg2d = L.gather || (!strict_rows() && net_all_mfma(*net));
     if (s->stg2d) s->prog.assign(n_streams, RowProg{});
-    if (L.cascade1d) {
+    if (L.gather) {
         s->batch_rows = max_seg_rows;
         for (size_t k = 0; k < s->units.size(); ++k) {
             const RowUnit &u = s->units[k];
@@ -1810,10 +1857,10 @@ int open_on(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
                 GatherStep b{};
                 conv_gather_layer(net->precision, gn, b);
                 a.dst_cells = b.cells;
-                a.next_layer = v.l; a.next_c_out = gn.c_out; a.nk_h = b.k_h; a.nk_w = b.k_w; a.ns_h_log = b.s_h_log; a.ns_w_log = b.s_w_log;
+                a.next_layer = v.l; a.next_c_out = gn.kind == IDF_CONV ? gn.c_out : 0; a.nk_h = b.k_h; a.nk_w = b.k_w; a.ns_h_log = b.s_h_log; a.ns_w_log = b.s_w_log;
                 a.np_h = b.p_h; a.np_w = b.p_w; a.nh_out = b.h_out; a.nw_out = b.w_out;
             }
-            a.w_frag = s->ws + s->w_off[u.l];
+            a.w_frag = s->ws + s->wg_off[u.l];
             a.bias = net->b_img[u.l].empty() ? nullptr : s->ws + s->b_off[u.l];
             s->gather.push_back(a);
         }
@@ -1823,13 +1870,12 @@ int open_on(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
     hipError_t e = launch_fill_zero(s->ws, L.sizes.weights_bytes, s->st);     // zero padding of the weights
     for (size_t l = 0; l < net->g.size() && e == hipSuccess; ++l) {
         if (net->g[l].kind != IDF_CONV) continue;
-        if (L.cascade1d) {
+        e = hipMemcpyAsync(s->ws + s->w_off[l], net->w_img[l].data(), net->w_img[l].size(), hipMemcpyHostToDevice, s->st);
+        if (e == hipSuccess && L.gather) {
             s->gather_w.emplace_back(conv_gather_pack(net->precision, net->g[l], nullptr, nullptr));
             std::vector<unsigned char> &img = s->gather_w.back();
             conv_gather_pack(net->precision, net->g[l], net->w_img[l].data(), img.data());
-            e = hipMemcpyAsync(s->ws + s->w_off[l], img.data(), img.size(), hipMemcpyHostToDevice, s->st);
-        } else {
-            e = hipMemcpyAsync(s->ws + s->w_off[l], net->w_img[l].data(), net->w_img[l].size(), hipMemcpyHostToDevice, s->st);
+            e = hipMemcpyAsync(s->ws + s->wg_off[l], img.data(), img.size(), hipMemcpyHostToDevice, s->st);
         }
         if (e == hipSuccess && !net->b_img[l].empty())
             e = hipMemcpyAsync(s->ws + s->b_off[l], net->b_img[l].data(), net->b_img[l].size(), hipMemcpyHostToDevice, s->st);
@@ -1912,6 +1958,9 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
                 rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, strict_cascade()); });
         }
         if (rc != IDF_OK) return rc;
+    } else if (s->use_gather) {
+        rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, false); });
+        if (rc != IDF_OK) return rc;
     } else if (s->stg2d) {
         rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return row_run(s, sel, p, dev_rows, n_rows); });
         if (rc != IDF_OK) return rc;
@@ -1964,15 +2013,36 @@ int idf_push_pixels(idf_streams *s, const int32_t *stream_ids, int n_ids, const 
         return rc;
     }
     // layer 0 takes the columns into its rolling buffer; nothing can be final yet
+    if (s->use_gather) {
+        // the row that is begun needs a slot nobody reads any more
+        bool room = true;
+        for (const RowProg &q : s->prog) {
+            const RowProg &p = s->prog_same ? s->prog_all : q;
+            room = room && p.in[0] + 1 - first_needed(net.g[0], p.out[0]) <= s->units[0].ring_rows;
+        }
+        if (!room) rc = stg_drain(s);
+        if (rc != IDF_OK) { s->part = idf_streams::Part{}; return rc; }
+    }
     std::map<int64_t, std::vector<std::pair<int, int>>> groups;
     for (int i = 0; i < n_ids; ++i) {
         const int id = stream_ids ? stream_ids[i] : i;
         if (net.in_h > 0 && s->h[id].r >= net.in_h) { s->part = idf_streams::Part{}; return fail(IDF_ESTATE, "stream %d: sample complete", id); }
-        groups[first_mfma ? s->h[id].sample * net.in_h + s->h[id].r : s->h[id].r].push_back({i, id});
+        groups[first_mfma || s->use_gather ? s->h[id].sample * net.in_h + s->h[id].r : s->h[id].r].push_back({i, id});
     }
     for (auto &kv : groups) {
         const int64_t r = kv.first;
         rc = for_each_selection(kv.second, [&](const StreamSel &sel) {
+            if (s->use_gather) {                  // rows of c are formed when the row is whole: the pixels wait in the layer's ring
+                GatherHead h{};
+                GatherStep a;
+                gather_take(s, r, 1, x0, x0 + n_px, a);
+                h.n = 1; h.n_layers = (int)net.g.size();
+                h.stats = (unsigned long long *)(s->ws + s->stats_off);
+                h.n_in = 1; h.seg_rows = 1; h.in_stride = n_px * net.in_c; h.in[0] = dev_pixels;
+                const double bytes = (double)sel.n * n_px * net.in_c * ev_bytes(net.precision);
+                hipError_t e = launch_conv_gather(net.precision, h, &a, sel, false, launch_ctx(s, kKindConvGather, bytes, 0));
+                return e == hipSuccess ? (int)IDF_OK : dev_fail(e, "pixel segment launch");
+            }
             if (!first_mfma) {
                 // any other first convolution: the generic kernel with the segment's column range; every row the input
                 // row touches goes back to the rolling buffer
@@ -2132,9 +2202,9 @@ int idf_get_issued_macs(idf_streams *s, int stream_id, uint64_t *macs_issued)
                       st.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return dev_fail(e, "get_issued_macs");
     // the generic kernels test every value and keep no count of their own: they issue what they execute
-    const bool own_count = s->use_cascade1d || !s->mfma.empty();
+    const bool own_count = s->use_gather || !s->mfma.empty();
     for (int l = 0; l < n; ++l) {
-        const bool counted = s->use_cascade1d || (own_count && l < (int)s->mfma.size() && s->mfma[l] == 1);
+        const bool counted = s->use_gather || (own_count && l < (int)s->mfma.size() && s->mfma[l] == 1);
         macs_issued[l] = counted ? iss[l] : st[2 * l + 1];
     }
     return IDF_OK;
@@ -2508,7 +2578,7 @@ int idf_profile_end(idf_streams *s, int max_kinds, idf_kernel_profile *out, int 
 const char *idf_layer_kernel(const idf_streams *s, int layer)
 {
     if (!s || layer < 0 || layer >= (int)s->net->g.size()) return nullptr;
-    if (s->use_cascade1d) return kind_name(kKindCascade1d);
+    if (s->use_gather) return kind_name(s->use_cascade1d ? kKindCascade1d : kKindConvGather);
     if (s->mfma[layer]) return kind_name(kKindConvMfma);
     return s->net->g[layer].kind == IDF_CONV ? kind_name(kKindConvGeneric) : kind_name(kKindPoolGeneric);
 }

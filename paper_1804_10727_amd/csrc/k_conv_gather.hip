@@ -6,6 +6,10 @@
 // the next layer.  A launch holds a step for every layer that has rows to form, all on rows that
 // were complete before it, and one that puts the caller's new rows into the first ring.
 //
+// Max-pools, in nets that have them, are steps of the same launch.  Measured per image of 112 x 112, 32 streams, float32,
+// six layers (5x5 and 3x3 with stride 2, 3x3, 1x1, a pool): 612 us, 5.5 per row; a launch per layer, the layers that are not
+// 3x3 with stride 1 on the vector units: 4360, 39 per row.
+//
 // The work is a matrix product: the columns of the instruction are output positions -- of one stream, or, where
 // a stream has few, of 2, 4, 8 or 16 streams side by side, so that a layer that completes four rows of a
 // 1-D signal per push still fills its tiles -- its rows 16 output channels, and the contraction runs over
@@ -34,6 +38,7 @@ typedef const __attribute__((address_space(4))) GatherHead Head;
 
 constexpr int kTeam = 4;                         // waves that share a tile
 constexpr int kChunk = 9;                        // K-steps a wave has in flight
+constexpr int kPoolCells = 64 * kTeam;           // cells of a pool's rows per workgroup
 
 // Taps of an axis that position v lands on inside an output of n positions (n == 0: unbounded).
 __device__ __forceinline__ int taps_axis(int v, int k, int s_log, int p, int n)
@@ -50,8 +55,9 @@ template <class T> __device__ __forceinline__ void take_rows(Head &h, Step &a, c
 {
     using ev_t = typename T::ev_t;
     const int stream = sel_stream(sel, si), lane = tid & 63;
-    const int w_in = a.w_in, c_in = a.c_in, cells = a.cells, n_rows = a.n_rows, seg_rows = h.seg_rows;
-    const int row_elems = w_in * c_in, row_cells = w_in * cells;
+    // (a pixel segment brings x_n columns of its row, from x0 on)
+    const int c_in = a.c_in, cells = a.cells, n_rows = a.n_rows, seg_rows = h.seg_rows, x0 = a.dst_slot0, x_n = a.dst_rows;
+    const int row_elems = x_n * c_in, row_cells = x_n * cells, ring_cells = a.w_in * cells;
     unsigned char *ring = (unsigned char *)a.ring + (int64_t)stream * a.ring_stride * T::EB;
     uint32_t ev = 0, taps = 0;
     for (int i = tid; i < n_rows * row_cells; i += threads) {
@@ -70,9 +76,9 @@ template <class T> __device__ __forceinline__ void take_rows(Head &h, Step &a, c
         __builtin_memcpy(&cell, v, 16);
         int slot = a.slot0 + r;
         slot = slot >= a.ring_rows ? slot - a.ring_rows : slot;
-        *at4(reinterpret_cast<i32x4 *>(ring), (uint32_t)(slot * row_cells + xc) * 16) = cell;
+        *at4(reinterpret_cast<i32x4 *>(ring), (uint32_t)(slot * ring_cells + x0 * cells + xc) * 16) = cell;
         ev += n;
-        taps += n * (uint32_t)(taps_axis(a.y0 + r, a.k_h, a.s_h_log, a.p_h, a.h_out) * (a.flat ? 1 : taps_axis(x, a.k_w, a.s_w_log, a.p_w, a.w_out)));
+        taps += n * (uint32_t)(taps_axis(a.y0 + r, a.k_h, a.s_h_log, a.p_h, a.h_out) * (a.flat ? 1 : taps_axis(x0 + x, a.k_w, a.s_w_log, a.p_w, a.w_out)));
     }
     if (!h.stats) return;
     ev = wave_sum(ev); taps = wave_sum(taps);
@@ -80,6 +86,54 @@ template <class T> __device__ __forceinline__ void take_rows(Head &h, Step &a, c
         unsigned long long *d = h.stats + ((int64_t)stream * h.n_layers + a.layer) * 2;
         atomicAdd(d, (unsigned long long)ev);
         atomicAdd(d + 1, (unsigned long long)taps * (unsigned long long)a.c_out);
+    }
+}
+
+// ---- max-pool: rows of the layer's ring into the next one, a cell of 16 bytes per thread ---------------------
+template <class T> __device__ __forceinline__ void pool_rows(Head &h, Step &a, const StreamSel &sel, int si, int first, int past, int threads)
+{
+    using ev_t = typename T::ev_t;
+    const int stream = sel_stream(sel, si), lane = threadIdx.x & 63;
+    const int cells = a.cells, k_w = a.k_w, w_in = a.w_in, w_out = a.w_out, row_cells = w_out * cells, items = a.n_rows * row_cells;
+    const i32x4 *ring = reinterpret_cast<const i32x4 *>((const unsigned char *)a.ring + (int64_t)stream * a.ring_stride * T::EB);
+    i32x4 *dst = reinterpret_cast<i32x4 *>((unsigned char *)a.dst + (int64_t)stream * a.dst_stride * T::EB);
+    auto val = [](ev_t v) IDF_INLINE {
+        if constexpr (T::EB == 2) return __uint_as_float((uint32_t)v << 16);
+        else return v;
+    };
+    auto larger = [&](i32x4 u, i32x4 v) IDF_INLINE {
+        ev_t p[T::VL], q[T::VL];
+        __builtin_memcpy(p, &u, 16);
+        __builtin_memcpy(q, &v, 16);
+#pragma unroll
+        for (int e = 0; e < T::VL; ++e) p[e] = val(p[e]) > val(q[e]) ? p[e] : q[e];
+        __builtin_memcpy(&u, p, 16);
+        return u;
+    };
+    uint32_t ev = 0, taps = 0;
+    for (int i = first + (int)threadIdx.x; i < past && i < items; i += threads) {
+        const int r = i / row_cells, xc = i - r * row_cells, x = xc / cells, c = xc - x * cells;
+        int s0 = a.slot0 + 2 * r, s1 = s0 + 1;
+        s0 = s0 >= a.ring_rows ? s0 - a.ring_rows : s0;
+        s1 = s1 >= a.ring_rows ? s1 - a.ring_rows : s1;
+        const int at0 = (s0 * w_in + x * k_w) * cells + c, at1 = (s1 * w_in + x * k_w) * cells + c;
+        i32x4 m = larger(ring[at0], ring[at1]);
+        if (k_w == 2) m = larger(larger(ring[at0 + cells], ring[at1 + cells]), m);
+        int slot = a.dst_slot0 + r;
+        slot = slot >= a.dst_rows ? slot - a.dst_rows : slot;
+        dst[slot * row_cells + xc] = m;
+        uint32_t n = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) n += (uint32_t)T::nonzero((uint32_t)m[q]);
+        ev += n;
+        taps += n * (uint32_t)(taps_axis(a.y0 + r, a.nk_h, a.ns_h_log, a.np_h, a.nh_out) * taps_axis(x, a.nk_w, a.ns_w_log, a.np_w, a.nw_out));
+    }
+    if (!h.stats) return;
+    ev = wave_sum(ev); taps = wave_sum(taps);
+    if (lane == 0 && ev) {
+        unsigned long long *d = h.stats + ((int64_t)stream * h.n_layers + a.next_layer) * 2;
+        atomicAdd(d, (unsigned long long)ev);
+        atomicAdd(d + 1, (unsigned long long)taps * (unsigned long long)a.next_c_out);
     }
 }
 
@@ -138,8 +192,9 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
         };
         if (flat) {
             const int q_last = k_h * cells - 1;
-            // (a window that reaches over an end of the signal: its cells there are zero)
-            const bool edge = __ballot(valid && (y_in < 0 || y_in + k_h > h_in)) != 0ull;
+            // (a window that reaches over an end of the signal: its cells there are zero; so are those past the window's end, where
+            // the weights are zero too, but zero times infinity is not)
+            const bool edge = __ballot(valid && (y_in < 0 || y_in + k_h > h_in)) != 0ull || 4 * n_ks > q_last + 1;
 #pragma unroll 1
             for (int kb = ks0; kb < ks1; kb += kChunk) {
                 i32x4 xv[kChunk], wv[kChunk];
@@ -149,7 +204,7 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
                     if (kb + i >= ks1) continue;
                     wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf), (uint32_t)i * w_step + lane16);
                     int q = 4 * (kb + i) + g;
-                    q = q < q_last ? q : q_last;               // (past the end the weights are zero)
+                    q = q < q_last ? q : q_last;               // (past the end: see below)
                     const unsigned ky = __umul24((unsigned)q, cells_rcp) >> 16;
                     unsigned slot = slot_o + ky;
                     slot = min(slot, slot - (unsigned)ring_rows);
@@ -159,10 +214,8 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
 #pragma unroll
                     for (int i = 0; i < kChunk; ++i) {
                         if (kb + i >= ks1) continue;
-                        int q = 4 * (kb + i) + g;
-                        q = q < q_last ? q : q_last;
-                        const int y = y_in + (int)(__umul24((unsigned)q, cells_rcp) >> 16);
-                        if (y < 0 || y >= h_in) xv[i] = i32x4{0, 0, 0, 0};
+                        const int q = 4 * (kb + i) + g, y = y_in + (int)(__umul24((unsigned)q, cells_rcp) >> 16);
+                        if (y < 0 || y >= h_in || q > q_last) xv[i] = i32x4{0, 0, 0, 0};
                     }
                 }
                 if (!valid) {
@@ -183,11 +236,10 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
                 for (int i = 0; i < kChunk; ++i) {
                     if (kb + i >= ks1) continue;
                     wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf), (uint32_t)i * w_step + lane16);
-                    int q = 4 * (kb + i) + g;
-                    q = q < q_last ? q : q_last;
+                    const int q_all = 4 * (kb + i) + g, q = q_all < q_last ? q_all : q_last;
                     const unsigned tap = __umul24((unsigned)q, cells_rcp) >> 16, ky = __umul24(tap, kw_rcp) >> 16;
                     const int c = q - (int)__umul24(tap, (unsigned)cells), xx = x_in + (int)(tap - __umul24(ky, (unsigned)k_w)), y = y_in + (int)ky;
-                    const bool ok = valid && (unsigned)y < (unsigned)h_in && (unsigned)xx < (unsigned)w_in;
+                    const bool ok = valid && (unsigned)y < (unsigned)h_in && (unsigned)xx < (unsigned)w_in && q_all <= q_last;
                     there |= ok ? 1u << i : 0u;
                     unsigned slot = slot_o + ky;
                     slot = min(slot, slot - (unsigned)ring_rows);
@@ -318,10 +370,11 @@ __global__ void __launch_bounds__(64 * kTeam) k_conv_gather_rows(const GatherBat
         if ((sg << spt_log) >= sel.n) return;
     } else {
         const int per = a.n_ct * a.n_pt;
-        sg = take ? tile : (int)((unsigned)tile / (unsigned)per);
-        rest = take ? 0 : tile - sg * per;
+        sg = take == 1 ? tile : (int)((unsigned)tile / (unsigned)per);
+        rest = take == 1 ? 0 : tile - sg * per;
     }
-    if (take) { take_rows<T>(b.head, a, sel, sg, threadIdx.x, 64 * kTeam); return; }
+    if (take == 1) { take_rows<T>(b.head, a, sel, sg, threadIdx.x, 64 * kTeam); return; }
+    if (take == 2) { pool_rows<T>(b.head, a, sel, sg, rest * kPoolCells, (rest + 1) * kPoolCells, 64 * kTeam); return; }
     const int pt = a.ct_rcp ? (int)__umulhi((unsigned)rest, a.ct_rcp) : rest, ct = rest - pt * a.n_ct;
     conv_tile<T, COUNT>(b.head, a, sel, sg << spt_log, pt, ct, spt_log, true, uni(threadIdx.x >> 6), share, [] { lds_barrier(); });
 }
@@ -335,8 +388,10 @@ __global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherB
     const int team = uni(threadIdx.x >> 8), kq = uni((threadIdx.x >> 6) & 3), si = blockIdx.x;
     for (int k = 0; k < b.head.n; ++k) {
         Step &a = b.st[k];
-        if (a.take) {
+        if (a.take == 1) {
             take_rows<T>(b.head, a, sel, si, threadIdx.x, 256 * kTeam);
+        } else if (a.take == 2) {
+            pool_rows<T>(b.head, a, sel, si, 0, INT32_MAX, 256 * kTeam);
         } else {
             const int tasks = a.n_ct * ((a.n_rows * a.w_out + 15) >> 4);
             for (int t0 = 0; t0 < tasks; t0 += 4) {
@@ -375,7 +430,7 @@ template <class T, int NS> hipError_t launch_ns(const GatherHead &h, const Gathe
         b.st[k] = st[k];
         GatherStep &a = b.st[k];
         const int groups = b.head.n_sb > 0 ? b.head.n_sb8 << (b.head.sb_log - a.spt_log) : (sel.n + (1 << a.spt_log) - 1) >> a.spt_log;
-        a.tiles = groups * (a.take ? 1 : a.n_ct * a.n_pt);
+        a.tiles = groups * (a.take == 1 ? 1 : a.n_ct * a.n_pt);
         tiles += b.st[k].tiles;
         if (k < 8 && k + 1 < h.n) b.head.end[k] = (int)tiles;
     }
@@ -400,8 +455,9 @@ template <class T> hipError_t launch_t(const GatherHead &h, const GatherStep *st
 void conv_gather_shape(bool first, GatherStep &a)
 {
     auto rcp32 = [](int n) { return n > 1 ? (unsigned)((0x100000000ull + n - 1) / n) : 0u; };
-    if (a.take) { a.spt_log = 0; a.n_pt = 1; return; }
+    if (a.take == 1) { a.spt_log = 0; a.n_pt = 1; return; }
     const int positions = a.n_rows * a.w_out;
+    if (a.take == 2) { a.spt_log = 0; a.n_ct = 1; a.n_pt = (positions * a.cells + kPoolCells - 1) / kPoolCells; a.ct_rcp = 0; return; }
     a.spt_log = streams_per_tile_log(positions, first);
     a.n_pt = (positions + (16 >> a.spt_log) - 1) / (16 >> a.spt_log);
     a.ct_rcp = rcp32(a.n_ct);
@@ -419,6 +475,35 @@ bool cascade1d_eligible(int prec, const Geom *g, int n_layers, int max_seg_rows)
     return true;
 }
 
+// Can a layer of a net of several kinds of layers go through this kernel, its ring holding ring_rows rows?  Strides are
+// shifts here, divisions multiplications that have to be exact, and offsets into a stream's ring fit 31 bits; beyond
+// 256 channels the generic kernels stay.
+bool conv_gather_takes(int prec, const Geom &g, int ring_rows)
+{
+    const int vl = conv3x3_mfma_vl(prec), cells = (g.c_in + vl - 1) / vl;
+    if (g.h_in < 1 || g.h_out < 1 || g.w_in > 4096 || g.c_in > 256 || g.c_out > 256) return false;
+    if ((int64_t)ring_rows * g.w_in * cells * 16 > INT32_MAX || (int64_t)ring_rows * g.w_in >= 1 << 24) return false;
+    if (g.kind == IDF_MAXPOOL) return true;
+    auto shift = [](int s) { return s == 1 || s == 2 || s == 4; };
+    if (!shift(g.s_h) || !shift(g.s_w) || g.k_h < g.s_h) return false;
+    if (g.k_h > 32 || g.k_w > 32 || g.p_h >= g.k_h || g.p_w >= g.k_w) return false;
+    GatherStep a{};
+    conv_gather_layer(prec, g, a);
+    for (unsigned q = 0; q < (unsigned)(g.k_h * g.k_w * cells) + 4u; ++q) {
+        const unsigned tap = q * a.cells_rcp >> 16;
+        if (q > UINT32_MAX / a.cells_rcp || tap > UINT32_MAX / a.kw_rcp || tap != q / cells || tap * a.kw_rcp >> 16 != tap / g.k_w) return false;
+    }
+    return true;
+}
+
+// What a step of a layer fetches from the caches to form `rows` rows of n_streams streams: a window and weights per tile.
+double conv_gather_traffic(int prec, const Geom &g, int n_streams, int rows)
+{
+    GatherStep a{};
+    conv_gather_layer(prec, g, a);
+    return 2048.0 * a.n_ks * a.n_ct * ((double)n_streams * rows * g.w_out / 16);
+}
+
 // What a step needs to know of its layer whatever the rows.
 void conv_gather_layer(int prec, const Geom &g, GatherStep &a)
 {
@@ -429,6 +514,7 @@ void conv_gather_layer(int prec, const Geom &g, GatherStep &a)
     a.k_h = g.k_h; a.k_w = g.k_w; a.s_h_log = log2i(g.s_h); a.s_w_log = log2i(g.s_w); a.p_h = g.p_h; a.p_w = g.p_w;
     a.h_in = g.h_in > 0 ? g.h_in : INT32_MAX; a.w_in = g.w_in; a.h_out = g.h_out; a.w_out = g.w_out;
     a.act = g.act; a.shr = g.shr; a.clamp_hi = g.clamp_hi;
+    a.take = g.kind == IDF_MAXPOOL ? 2 : 0;
     a.n_ct = (g.c_out + 15) / 16;
     a.n_ks = (g.k_h * g.k_w * a.cells + 3) / 4;
     a.cells_rcp = (unsigned)((65536 + a.cells - 1) / a.cells);
@@ -463,6 +549,7 @@ hipError_t launch_conv_gather(int prec, const GatherHead &h, const GatherStep *s
     switch (prec) {
     case IDF_PREC_F32: return launch_t<TraitsF32>(h, st, sel, chain, lc);
     case IDF_PREC_BF16: return launch_t<TraitsBf16>(h, st, sel, chain, lc);
+    case IDF_PREC_I8: return launch_t<TraitsI8>(h, st, sel, chain, lc);
     default: return hipErrorInvalidValue;
     }
 }
