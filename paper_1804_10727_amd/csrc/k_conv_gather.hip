@@ -168,7 +168,8 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
     if (!flat) { o = w_out == 1 ? p : (int)__umulhi((unsigned)p, a.wout_rcp); x = p - o * w_out; }
     const bool valid = stream_ok && o < n_rows;
     o = valid ? o : 0;
-    acc_t acc = {0, 0, 0, 0};
+    // A K-step's instructions have sums of their own: none waits for the one before, and the chains that round are a quarter as long.
+    acc_t sums[T::kInst] = {}, acc = {0, 0, 0, 0};
     if (on) {
         const int y_in = ((y0 + o) << s_h_log) - p_h;          // the window's first row
         unsigned slot_o = (unsigned)(slot0 + (o << s_h_log));
@@ -180,7 +181,7 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
                 if (kb + i >= ks1) continue;
                 if (__ballot(T::or_of(xv[i]) != 0) == 0ull) continue;
 #pragma unroll
-                for (int e = 0; e < T::kInst; ++e) acc = T::mfma(wv[i], xv[i], acc, e);
+                for (int e = 0; e < T::kInst; ++e) sums[e] = T::mfma(wv[i], xv[i], sums[e], e);
                 if (COUNT) {
                     const int n_cells = k_h * (flat ? 1 : a.k_w) * cells;
                     for (int u = 0; u < 4; ++u) {
@@ -257,6 +258,8 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
             const int co_n = a.c_out - ct * 16 < 16 ? a.c_out - ct * 16 : 16;
             atomicAdd(h.issued + (int64_t)sel_stream(sel, si) * h.n_layers + a.layer, (issued * (unsigned long long)co_n) << per_log);
         }
+        if constexpr (T::kInst == 4) acc = (sums[0] + sums[1]) + (sums[2] + sums[3]);
+        else acc = sums[0];
         if (kq > 0) share[(kq - 1) * 64 + lane] = acc;
     }
     // (likewise for what comes after the contraction)
@@ -283,11 +286,10 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
 #pragma unroll
             for (int i = 0; i < 4; ++i) c[i] = bias[co0 + i < c_out ? co0 + i : c_out - 1];
         }
+        acc = (acc + part[0]) + (part[1] + part[2]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             c[i] += acc[i];
-#pragma unroll
-            for (int w = 0; w < kTeam - 1; ++w) c[i] += part[w][i];
             hv[i] = co0 + i < c_out ? T::activate(c[i], act, shr, clamp_hi) : (st_t)0;
         }
     }
@@ -333,7 +335,7 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
 }
 
 template <class T, int NS, bool COUNT>
-__global__ void __launch_bounds__(64 * kTeam) k_conv_gather_rows(const GatherBatch<NS> args, const StreamSel sel)
+__global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows(const GatherBatch<NS> args, const StreamSel sel)
 {
     typedef const __attribute__((address_space(4))) GatherBatch<NS> Batch;
     Batch &b = *(Batch *)__builtin_amdgcn_kernarg_segment_ptr();
