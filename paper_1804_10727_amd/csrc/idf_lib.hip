@@ -289,7 +289,9 @@ bool gather_net(const idf_net &net, int B, int max_seg)
     return true;
 }
 
-int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout &L)
+// by_kind: a net of several kinds of layers goes layer by layer, which takes less memory (rows of c instead of twice the rows a
+// launch brings).
+int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout &L, bool by_kind = false)
 {
     const int n = (int)net.g.size();
     const int eb = ev_bytes(net.precision);
@@ -310,7 +312,7 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     }
     L.cascade1d = cascade1d_eligible(net.precision, net.g.data(), n, max_seg);
     const bool all_mfma = net_all_mfma(net);
-    L.gather = L.cascade1d || gather_net(net, B, max_seg);
+    L.gather = L.cascade1d || (!by_kind && gather_net(net, B, max_seg));
     L.mfma = L.gather ? std::vector<int>(n, 0) : mfma_layers(net);
     for (int l = 0; l < n; ++l) {
         if (net.g[l].kind != IDF_CONV) continue;
@@ -1759,6 +1761,10 @@ int idf_open_streams_static(idf_net *net, int n_streams, int max_seg_rows, int64
     if (n_streams < 1 || max_seg_rows < 1) return fail(IDF_EINVAL, "n_streams and max_seg_rows must be >= 1");
     Layout L;
     int rc = make_layout(*net, n_streams, max_seg_rows, out_cap_rows, L);
+    if (rc == IDF_OK && L.total > kStaticScratchBytes && L.gather && !L.cascade1d) {
+        L = Layout{};
+        rc = make_layout(*net, n_streams, max_seg_rows, out_cap_rows, L, true);
+    }
     if (rc != IDF_OK) return rc;
     if (L.total > kStaticScratchBytes)
         return fail(IDF_ENOMEM, "these streams need a workspace of %zu bytes, the static one holds %zu: fewer streams, "

@@ -163,3 +163,27 @@ def test_a_stream_of_several_kinds_of_layers_resumes_in_another_slot(prec):
         assert got.shape == want.shape and rel_err(got, want) <= (0 if prec == "i8" else TOL["f32"])
         st.close()
     net.destroy()
+
+
+def test_a_static_workspace_too_small_for_the_rings_still_holds_the_streams():
+    """A net of several kinds of layers whose rings do not fit the library's own workspace goes layer by layer in it."""
+    import paper_1804_10727_amd as idf
+    from paper_1804_10727_amd.binding import input_tensor
+    h, w, c0, layers = _NETS[3]
+    streams = 300                                                # 60 MiB with rings, 25 without
+    layers, weights, biases, x = _image("f32", 2, h, w, c0, layers, seed=8)
+    wl = wl_mod._finish("gather2d", "f32", h, w, c0, layers, weights, biases, np.repeat(x, streams // 2, axis=0), 1)
+    net = idf.net_from_workload(wl)
+    outs = []
+    for static in (True, False):
+        st = idf.Streams(net, streams, max_seg_rows=1, static_workspace=static)
+        assert (set(st.layer_kernels()) == {"conv_gather"}) == (not static)
+        xd = input_tensor(wl)
+        for r in range(h):
+            st.push_segment(xd[:, r:r + 1].contiguous())
+        outs.append(st.read_outputs(int(st.sizes.out_h))[0].cpu().numpy())
+        st.close()
+    net.destroy()
+    for o in outs:
+        for b in (0, streams - 1):
+            assert rel_err(o[b], oracle_dense(wl, b)) <= TOL["f32"]
