@@ -83,11 +83,13 @@ typedef struct {
     size_t weights_bytes;            /* of which: packed weights and biases (shared by all streams) */
     size_t state_bytes_per_stream;   /* of which, per stream: the retained state -- the rolling rows of
                                         c of every conv layer and the held row of every pool.  This is
-                                        the footprint the paper bounds; it does not depend on in_h.  */
+                                        the footprint the paper bounds; it does not depend on in_h.
+                                        (Layers on the matrix cores keep rows of their input instead;
+                                        the rings they lie in count as transit.)                     */
     size_t handover_bytes_per_stream;/* of which, per stream: rows a layer has completed that may wait, when a
                                         call returns, for the next layer's step in a later call.  Only the
-                                        staged modes have such rows (the default for nets served by the
-                                        1-D cascade or throughout by the matrix-core kernel: layer l then
+                                        staged modes have such rows (the default for nets served throughout
+                                        by the matrix-core kernels: layer l then
                                         runs behind layer l-1 by one launch); 0 when the layers run strictly
                                         depth-first within every call (environment IDF_CASCADE_STAGES=1,
                                         IDF_NO_ROW_STAGES=1).  Independent of in_h as well.              */
@@ -206,17 +208,13 @@ int idf_open_streams_static(idf_net *net, int n_streams, int max_seg_rows, int64
  *   1 <= n_rows <= max_seg_rows.
  * Zero values are not events: they cause no arithmetic (Sec. 1).  Completed rows of the last
  * layer are appended to the stream's output area.
- * For 1-D nets the deeper layers of a segment may be enqueued only with the next pushes (layers
- * run in stages side by side, each stage on the segment one push older); idf_read_outputs,
+ * For nets whose layers run side by side (1-D nets; 2-D nets served throughout by the matrix-core
+ * kernels) a push is one launch for every group of streams that stand at the same place, and each
+ * layer takes what was complete before the launch: the deeper layers of a segment may be enqueued
+ * only with the next pushes.  A 3x3 layer forms its rows in pairs where it can.  idf_read_outputs,
  * idf_get_stats, idf_reset_streams, idf_close_streams and idf_profile_end first enqueue whatever
  * is still on its way, so what they return is always the result of every pushed row having gone
  * through every layer it can influence.  The last segment's dev_rows is read by the push itself.
- * For 2-D nets served throughout by the matrix-core kernel a push of all streams in step is one
- * launch per row -- or, when the push brings several rows (streams opened with max_seg_rows >= 2),
- * one launch per two rows: a layer that finds two rows waiting takes both in one step and keeps
- * the rows of c between them on chip instead of writing them to its rolling buffer and reading
- * them back; values and counters are those of a launch per row, bit for bit (environment
- * IDF_NO_ROW_PAIRS=1 switches it off).
  * IDF_EINVAL: bad id, duplicate id, n_rows out of range.  IDF_ESTATE: the rows would run past row
  * in_h-1 of the current sample, or the completed output rows would not fit the output area
  * (read first). */
