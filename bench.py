@@ -40,6 +40,11 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 KERNEL_SYMBOL = {"cascade1d": "k_conv_gather", "conv3x3_mfma": "k_conv3x3_mfma", "conv_generic": "k_conv_generic"}
 
 
+def counts_issued(kernel):
+    """Is this the gathering kernel's variant that also counts issued multiply-adds?"""
+    return "k_conv_gather" in kernel and "true>" in kernel
+
+
 def sources_digest():
     """Digest of the kernel and host sources: counter readings are only quoted for the code they were taken on."""
     import glob
@@ -129,7 +134,7 @@ def trace_summary(stats_csv, bench_log):
             if eager else
             f"  python3 $R/bench.py --config {cfg_no} --trace-summary $OUT/prof_cfg{cfg_no}/cfg{cfg_no}_kernel_stats.csv $OUT/prof_cfg{cfg_no}.log"), "",
            f"bench.py in that run: steps={bench['steps']} warmup={bench['warmup']} (+1 step bracketed by HIP events per launch, "
-           f"+1 step on the kernel variants that count issued multiply-adds, named <..., true>); ms_per_step={bench['ms_per_step']:.3f}", "",
+           f"+1 step that counts issued multiply-adds, on the gathering kernel with variants named <..., true>); ms_per_step={bench['ms_per_step']:.3f}", "",
            "Kernel statistics (kernel_stats.csv), all launches of the process:",
            f"  {'kernel':<52} {'calls':>7} {'total ms':>10} {'avg us':>9} {'min us':>8} {'max us':>8} {'%':>6}"]
     sym = KERNEL_SYMBOL.get(rf["kernel"], rf["kernel"])
@@ -140,7 +145,7 @@ def trace_summary(stats_csv, bench_log):
         short = short if len(short) <= 52 else short[:49] + "..."
         out.append(f"  {short:<52} {int(r['Calls']):>7} {int(r['TotalDurationNs']) / 1e6:>10.3f} {float(r['AverageNs']) / 1e3:>9.2f} "
                    f"{int(r['MinNs']) / 1e3:>8.2f} {int(r['MaxNs']) / 1e3:>8.2f} {float(r['Percentage']):>6.2f}")
-        if sym in name and "true>" not in short and (dom is None or int(r["TotalDurationNs"]) > int(dom["TotalDurationNs"])):
+        if sym in name and not counts_issued(name) and (dom is None or int(r["TotalDurationNs"]) > int(dom["TotalDurationNs"])):
             dom = r
     assert dom, f"no {sym} kernel in the trace"
     avg_s = float(dom["AverageNs"]) * 1e-9
@@ -173,7 +178,7 @@ def utilisation_from_counters(dirs):
         for f in glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True):
             for row in csv.DictReader(open(f)):
                 k = row["Kernel_Name"]
-                if not any(sym in k for sym in KERNEL_SYMBOL.values()) or "true>" in k.replace("(anonymous namespace)::", ""):
+                if not any(sym in k for sym in KERNEL_SYMBOL.values()) or counts_issued(k):
                     continue
                 key = (k.replace("(anonymous namespace)::", "").replace("void ", "", 1).split("(")[0].replace("idf::", ""), row["Counter_Name"])
                 tot[key] = tot.get(key, 0.0) + float(row["Counter_Value"]); cnt[key] = cnt.get(key, 0) + 1
