@@ -334,6 +334,26 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
     }
 }
 
+// A launch's arguments on their way to the scalar cache, a few of their lines by each wave of the workgroup: met one after the
+// other, each line would be a trip to memory of its own.  Workgroups behind the first round find them there.  us, nobody asking /
+// the first 256 / the first 512 / all: 64 audio streams 6090 / 5980 / 5785 / 5732; 37 streams with 16 pushes per launch 742 / 738 /
+// 738 / 762; 32 images through six layers 606 / 583 / 551 / 615; one live stream 36.3, asking 32.2.
+constexpr int kFirst = 512;
+template <int BYTES, int WAVES> __device__ __forceinline__ void request_arguments(const void __attribute__((address_space(4))) *args)
+{
+    typedef const __attribute__((address_space(4))) int Word;
+    constexpr int N = (BYTES / 64 + WAVES - 1) / WAVES;
+    const int wave = uni(threadIdx.x >> 6);
+    int w[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const int at = (wave + q * WAVES) * 64;
+        w[q] = ((Word *)args)[(at < BYTES ? at : 0) / 4];
+    }
+#pragma unroll
+    for (int q = 0; q < N; ++q) asm volatile("" ::"s"(w[q]));
+}
+
 template <class T, int NS, bool COUNT>
 __global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows(const GatherBatch<NS> args, const StreamSel sel)
 {
@@ -343,6 +363,7 @@ __global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows(const Gather
     // The steps' tiles follow each other without gaps: workgroups go to the compute units in turn, and with an empty one here
     // and there some units got the tiles of three layers and others none (12.7 us per launch of 64 audio streams instead of 7).
     int k = 0, tile = blockIdx.x;
+    if (blockIdx.x < kFirst) request_arguments<sizeof(Batch), kTeam>(&b);
     {
         int end[8];
 #pragma unroll
@@ -387,6 +408,7 @@ __global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherB
     typedef const __attribute__((address_space(4))) GatherBatch<NS> Batch;
     Batch &b = *(Batch *)__builtin_amdgcn_kernarg_segment_ptr();
     __shared__ typename T::acc_t share[4][(kTeam - 1) * 64];
+    request_arguments<sizeof(Batch), 4 * kTeam>(&b);
     const int team = uni(threadIdx.x >> 8), kq = uni((threadIdx.x >> 6) & 3), si = blockIdx.x;
     for (int k = 0; k < b.head.n; ++k) {
         Step &a = b.st[k];
