@@ -576,6 +576,7 @@ __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatc
     (void)b;                                      // the first argument: it begins the segment
     ArgStep &a = *((ArgStep *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(RowBatch, st)) + blockIdx.z);
     const int tile = blockIdx.y, si = blockIdx.x;
+    request_arguments<sizeof(RowStep), kWaves>(&a);
     if (tile >= a.tiles) return;
     switch (a.form) {
     case kRowTake: take_row<T>(a, sel, tile, si); break;

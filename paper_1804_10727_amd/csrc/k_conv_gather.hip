@@ -334,26 +334,10 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
     }
 }
 
-// A launch's arguments on their way to the scalar cache, a few of their lines by each wave of the workgroup: met one after the
-// other, each line would be a trip to memory of its own.  Workgroups behind the first round find them there.  us, nobody asking /
+// Workgroups that request the launch's arguments; those behind the first round find them in the scalar cache.  us, nobody asking /
 // the first 256 / the first 512 / all: 64 audio streams 6090 / 5980 / 5785 / 5732; 37 streams with 16 pushes per launch 742 / 738 /
 // 738 / 762; 32 images through six layers 606 / 583 / 551 / 615; one live stream 36.3, asking 32.2.
 constexpr int kFirst = 512;
-template <int BYTES, int WAVES> __device__ __forceinline__ void request_arguments(const void __attribute__((address_space(4))) *args)
-{
-    typedef const __attribute__((address_space(4))) int Word;
-    constexpr int N = (BYTES / 64 + WAVES - 1) / WAVES;
-    const int wave = uni(threadIdx.x >> 6);
-    int w[N];
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-        const int at = (wave + q * WAVES) * 64;
-        w[q] = ((Word *)args)[(at < BYTES ? at : 0) / 4];
-    }
-#pragma unroll
-    for (int q = 0; q < N; ++q) asm volatile("" ::"s"(w[q]));
-}
-
 template <class T, int NS, bool COUNT>
 __global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows(const GatherBatch<NS> args, const StreamSel sel)
 {

@@ -122,6 +122,23 @@ template <class V> __device__ __forceinline__ V neighbour(V v)
     return __builtin_bit_cast(V, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
 }
 
+// Arguments of a launch on their way to the scalar cache, a few of their 64-byte lines by each wave of the workgroup: met one
+// after the other, each line would be a trip to memory of its own.
+template <int BYTES, int WAVES> __device__ __forceinline__ void request_arguments(const void __attribute__((address_space(4))) *args)
+{
+    typedef const __attribute__((address_space(4))) int Word;
+    constexpr int N = (BYTES / 64 + WAVES - 1) / WAVES;
+    const int wave = uni(threadIdx.x >> 6);
+    int w[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const int at = (wave + q * WAVES) * 64;
+        w[q] = ((Word *)args)[(at < BYTES ? at : 0) / 4];
+    }
+#pragma unroll
+    for (int q = 0; q < N; ++q) asm volatile("" ::"s"(w[q]));
+}
+
 __device__ __forceinline__ int taps_of(int v, int n) { return 3 - (v == 0) - (v == n - 1); }      // of a 3-tap axis with one position of padding
 
 // 16-byte cells from one position to the next in LDS.  The lanes of a fragment read 16 positions x 4 consecutive
