@@ -7,7 +7,7 @@
 // were complete before it, and one that puts the caller's new rows into the first ring.
 //
 // Max-pools, in nets that have them, are steps of the same launch.  Measured per image of 112 x 112, 32 streams, float32,
-// six layers (5x5 and 3x3 with stride 2, 3x3, 1x1, a pool): 612 us, 5.5 per row; a launch per layer, the layers that are not
+// six layers (5x5 and 3x3 with stride 2, 3x3, 1x1, a pool): 551 us, 4.9 per row; a launch per layer, the layers that are not
 // 3x3 with stride 1 on the vector units: 4360, 39 per row.
 //
 // The work is a matrix product: the columns of the instruction are output positions -- of one stream, or, where

@@ -15,7 +15,7 @@
 // instructions and about a hundred others per wave, one after the other.  Hence sixteen waves with small shares
 // (eight waves with all the rows of a band each took 1.3 times as long), one copy of the code for every layer,
 // which then stays in the instruction cache, and weights and state on their way before the barrier.
-// Measured per pushed row, layer by layer before: int8, 8 streams of 112 x 112, 38 us (170); float32, 256 streams of
+// Measured per pushed row, layer by layer before: int8, 8 streams of 112 x 112, 37 us (170); float32, 256 streams of
 // 32 x 32, 35 us (112), of which 18 us are matrix instructions.
 #include <algorithm>
 #include <type_traits>
