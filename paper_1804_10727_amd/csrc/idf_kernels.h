@@ -71,8 +71,9 @@ size_t conv3x3_mfma_pack(int prec, const Geom &g, const void *w_khkwcico, void *
 // most events per 32 positions of a row's stretch the event path takes.
 size_t conv3x3_mfma_event_weights(int prec, const Geom &g);
 int conv3x3_mfma_event_cap();
-// Fills in how the workgroups of a step of a.n_rows rows lie (a.n_rows and a.ev_limit are set).
-void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, RowStep &a);
+// Fills in how the workgroups of a step of a.n_rows rows lie (a.n_rows and a.ev_limit are set).  narrow: the step may share a
+// launch with one that takes the event path.
+void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, bool narrow, RowStep &a);
 hipError_t launch_conv3x3_mfma_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc);
 
 // Matrix-core kernel that gathers its windows from memory: any kernel size, strides 1, 2, 4 .., any padding.

@@ -564,7 +564,7 @@ void row_step(idf_streams *s, int k, int64_t o, int64_t n, int n_streams, bool c
     a.bias = net.b_img[u.l].empty() ? nullptr : s->ws + s->b_off[u.l];
     a.stats = (unsigned long long *)(s->ws + s->stats_off);
     a.issued = s->count_issued ? (unsigned long long *)(s->ws + s->issued_off) : nullptr;
-    conv3x3_mfma_shape(net.precision, g, n_streams, a);
+    conv3x3_mfma_shape(net.precision, g, n_streams, s->ev_per_step > 0, a);
     // Bytes the step has to move: the input rows the rows of c need (their events), the rows that leave, weights once.
     // Rows handed from layer to layer on their way out are not counted: the method does not require them to leave the chip.
     const int64_t i_lo = std::max<int64_t>(0, a.y0 - g.p_h), i_hi = std::min<int64_t>(g.h_in, a.y0 + n - g.p_h + g.k_h - 1);

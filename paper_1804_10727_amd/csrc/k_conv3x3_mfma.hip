@@ -660,15 +660,16 @@ static int row_ksteps(int prec, const Geom &g)
 
 // Shape of a step of n_rows output rows for n_streams streams: which tiles a wave takes, how the waves of a
 // workgroup lie, and the numbers that follow from that.
-void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, RowStep &a)
+void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, bool narrow, RowStep &a)
 {
     const int vl = conv3x3_mfma_vl(prec);
     a.cells = g.c_in % vl == 0 && g.c_in >= vl ? g.c_in / vl : 0;
     const int n_ct = g.c_out == 16 ? 1 : 2 * ((g.c_out + 31) / 32);
     const int pairs = a.n_rows >= 2 ? (a.n_rows + 1) / 2 : 1;
     // Wide tiles use each weight fragment and each cell twice as often and pay where they still give
-    // every SIMD most of a wave; float32 stays narrow, its matrix instructions being sixteen times longer.
-    const bool wide = prec != IDF_PREC_F32 && a.ev_limit == 0 && a.n_rows >= 2 && g.c_out > 16 && (long)n_streams * ((g.w_out + 31) / 32) * (n_ct / 2) * pairs >= 768;
+    // every SIMD most of a wave; float32 stays narrow, its matrix instructions being sixteen times longer.  So do all steps next
+    // to one on the event path: one kernel with both wants more registers than three waves per SIMD leave (20 bytes of scratch).
+    const bool wide = prec != IDF_PREC_F32 && !narrow && a.ev_limit == 0 && a.n_rows >= 2 && g.c_out > 16 && (long)n_streams * ((g.w_out + 31) / 32) * (n_ct / 2) * pairs >= 768;
     auto waves_log = [&](int tiles) { return tiles >= 4 ? 2 : tiles >= 2 ? 1 : 0; };
     a.wc_log = waves_log(wide ? n_ct / 2 : n_ct);
     // a stretch short enough for two workgroups to share a CU's LDS, where channels can take the waves instead of positions

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import workloads as wl_mod
+from workloads import conv
 from helpers import check_stream, gpu_run
 
 pytestmark = pytest.mark.gpu
@@ -121,3 +122,18 @@ def test_cascade_issues_all_rows_of_channels_with_events():
     zero = dict(wl); zero["x"] = np.zeros_like(wl["x"])
     issued, _, _ = _counts(zero)
     assert all(int(i.sum()) == 0 for i in issued)
+
+
+def test_event_path_next_to_layers_of_wide_tiles():
+    """With this many streams the last layer alone would take wide tiles while the first two are on the event path."""
+    rng = np.random.default_rng(5)
+    q = dict(act="relu_shr_clamp", shr=4, clamp_hi=15)
+    layers = [conv(1, 16, 3, 3, p_h=1, p_w=1, **q), conv(16, 32, 3, 3, p_h=1, p_w=1, **q), conv(32, 32, 3, 3, p_h=1, p_w=1)]
+    x = rng.integers(1, 16, size=(192, 6, 112, 1)).astype(np.int8)
+    x[rng.random(x.shape) < 0.8] = 0
+    wl = dict(name="i8_wide", precision="i8", in_h=6, in_w=112, in_c=1, layers=layers, biases=[None] * 3, x=x, seg_rows=1, streams=192,
+              weights=[rng.integers(-8, 8, size=(L["c_out"], L["c_in"], 3, 3)).astype(np.int8) for L in layers])
+    out = gpu_run(wl, events_per_kstep=8)
+    assert np.array_equal(out, gpu_run(wl))
+    for b in (0, 63, 191):
+        check_stream(wl, out[b], b)
