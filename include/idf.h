@@ -25,7 +25,8 @@
  *     1-D signals use in_w = 1, k_w = 1; the streaming axis is always "row".
  *   - Every function returns IDF_OK (0) or a negative IDF_E* code and never
  *     throws or aborts; idf_last_error() gives the text for the calling thread.
- *     On any error nothing has been enqueued.
+ *     On any error nothing has been enqueued, except IDF_EDEVICE from a push of several launches
+ *     when one behind the first could not be enqueued: idf_rows_pushed says how many rows went in.
  *   - A handle must not be used from two threads at once.
  */
 #ifndef IDF_H

@@ -680,14 +680,17 @@ int row_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *dev_ro
     int done = 0;
     for (int guard = 0;; ++guard) {
         double bytes = 0;
+        RowProg q = p;                             // (p moves on once the launch is enqueued)
         const int n_new = dev_rows ? (int)std::min<int64_t>({n_rows - done, kRowLaunchRows, s->net->in_h - p.in[0] % s->net->in_h}) : 0;
         if (dev_rows && done == n_rows) return IDF_OK;
-        bool go = row_plan(s, p, sel.n, dev_rows, done, n_rows, n_new, !dev_rows, b, bytes);
-        if (go) done += n_new;
-        else if (dev_rows) go = row_plan(s, p, sel.n, nullptr, 0, 0, 0, guard > 64, b, bytes);
+        bool go = row_plan(s, q, sel.n, dev_rows, done, n_rows, n_new, !dev_rows, b, bytes);
+        const bool took = go && n_new > 0;
+        if (!go && dev_rows) go = row_plan(s, q, sel.n, nullptr, 0, 0, 0, guard > 64, b, bytes);
         if (!go) return dev_rows ? fail(IDF_ESTATE, "internal: rows between layers do not move on") : IDF_OK;
         int rc = launch_rows(s, b, sel, bytes, -1);
         if (rc != IDF_OK) return rc;
+        p = q;
+        if (took) done += n_new;
     }
 }
 
@@ -790,17 +793,19 @@ int gather_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *con
     const bool chain = out && ((s->use_cascade1d && strict_cascade()) || most <= 32);
     for (bool fresh = n_seg > 0; fresh || out;) {
         double bytes = 0;
-        bool took = fresh && gather_plan(s, p, sel.n, n_seg * seg_rows, chain, h, st, bytes);
+        RowProg q = p;                             // (p moves on once the launch is enqueued)
+        const bool took = fresh && gather_plan(s, q, sel.n, n_seg * seg_rows, chain, h, st, bytes);
         if (!took) {
             bytes = 0;
-            if (!gather_plan(s, p, sel.n, 0, chain, h, st, bytes)) {
+            if (!gather_plan(s, q, sel.n, 0, chain, h, st, bytes)) {
                 if (fresh) return fail(IDF_ESTATE, "internal: rows between layers do not move on");
                 break;
             }
         }
-        if (took) fresh = false;
         hipError_t e = launch_conv_gather(net.precision, h, st, sel, chain, launch_ctx(s, s->use_cascade1d ? kKindCascade1d : kKindConvGather, bytes));
         if (e != hipSuccess) return dev_fail(e, "gather launch");
+        p = q;
+        if (took) fresh = false;
     }
     return IDF_OK;
 }
@@ -811,9 +816,10 @@ int gather_flush(idf_streams *s)
     if (s->held == 0) return IDF_OK;
     StreamSel all{};
     all.n = s->B; all.base = 0; all.pos0 = 0;
-    const int n = s->held;
-    s->held = 0;
-    return gather_run(s, all, s->prog_all, s->held_buf, n, s->held_rows, strict_cascade());
+    const int64_t before = s->prog_all.in[0];
+    int rc = gather_run(s, all, s->prog_all, s->held_buf, s->held, s->held_rows, strict_cascade());
+    if (s->prog_all.in[0] != before) s->held = 0;
+    return rc;
 }
 
 // How many rows of the rings are in use: as many as k pushes per launch need.  Only while no row lies in them.
@@ -872,13 +878,13 @@ template <class F> int for_each_prog(idf_streams *s, const std::vector<std::pair
         group.clear();
         for (size_t j = i; j < members.size(); ++j)
             if (!taken[j] && s->prog[members[j].second].same(at, nu)) { taken[j] = 1; group.push_back(members[j]); }
-        RowProg moved = at;
         int rc = for_each_selection(group, [&](const StreamSel &sel) {
-            moved = at;
-            return f(sel, moved);
+            RowProg moved = at;
+            int rc1 = f(sel, moved);
+            for (int k = 0; k < sel.n; ++k) s->prog[sel_stream(sel, k)] = moved;
+            return rc1;
         });
         if (rc != IDF_OK) return rc;
-        for (const auto &m : group) s->prog[m.second] = moved;
     }
     if ((int)members.size() == s->B) prog_join(s);
     return IDF_OK;
@@ -946,10 +952,11 @@ int count_waiting_rows(idf_streams *s)
     bool pool = false;
     for (const RowUnit &u : s->units) pool = pool || u.pool;
     if (!pool || s->eager.on) return IDF_OK;
-    auto count = [&](const StreamSel &sel, const RowProg &p, uint32_t &early) -> int {
+    auto count = [&](const StreamSel &sel, RowProg &p) -> int {
         RowBatch b;
         b.n = 0;
         double bytes = 0;
+        uint32_t early = p.early;
         for (size_t k = 0; k < s->units.size(); ++k) {
             const RowUnit &u = s->units[k];
             const Geom &g = net.g[u.l];
@@ -957,12 +964,13 @@ int count_waiting_rows(idf_streams *s)
             row_step(s, (int)k, p.out[k], 1, sel.n, false, b.st[b.n], bytes);
             b.st[b.n].pool_emit = 0; b.st[b.n].issued = nullptr;
             early |= 1u << k;
-            if (++b.n == kRowBatchMax) { int rc = launch_rows(s, b, sel, bytes, -1); if (rc != IDF_OK) return rc; b.n = 0; }
+            ++b.n;                                 // (units are at most kRowUnits: one launch)
         }
-        return launch_rows(s, b, sel, bytes, -1);
+        int rc = launch_rows(s, b, sel, bytes, -1);
+        if (rc == IDF_OK) p.early = early;
+        return rc;
     };
-    if (s->stg2d)
-        return for_each_prog(s, all_members(s), [&](const StreamSel &sel, RowProg &p) { return count(sel, p, p.early); });
+    if (s->stg2d) return for_each_prog(s, all_members(s), count);
     for (int id = 0; id < s->B; ++id) {
         StreamHost &h = s->h[id];
         StreamSel sel{};
@@ -981,9 +989,9 @@ int count_waiting_rows(idf_streams *s)
                     b.n = 1;
                     row_step(s, k, h.sample * g.h_out + o, 1, 1, false, b.st[0], bytes);
                     b.st[0].pool_emit = 0; b.st[0].issued = nullptr;
-                    h.early |= 1u << k;
                     int rc = launch_rows(s, b, sel, bytes, (int)l);
                     if (rc != IDF_OK) return rc;
+                    h.early |= 1u << k;
                 }
             }
             y = rows_final(g, y);
@@ -1943,6 +1951,25 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
         else if (key != key0) one_group = false;
         members.push_back({i, id});
     }
+    // rows of the push that a stream has taken in: the host's count moves on
+    auto account = [&](StreamHost &h, int n) {
+        if (h.r != memo_r) { memo_r = h.r; memo_fresh = output_rows_of_push(net, h.r, n); }
+        h.out_written += memo_fresh;
+        if (by_sample && h.early) h.early = early_after(s, h.early, h.r, h.r + n);
+        h.r += n;
+        h.x_next = 0;
+        if (net.in_h > 0 && h.r == net.in_h) { h.r = 0; ++h.sample; }      // next sample
+    };
+    // A launch failed.  Layers side by side: what the launches before it took in has been taken in.
+    auto give_up = [&](int rc) {
+        for (const auto &m : members) {
+            StreamHost &h = s->h[m.second];
+            const int64_t in = (s->prog_same ? s->prog_all : s->prog[m.second]).in[0] - (h.sample * net.in_h + h.r);
+            memo_r = -1;
+            if (in > 0) account(h, (int)in);
+        }
+        return rc;
+    };
     auto deliver = [&](const Key &key, const std::vector<std::pair<int, int>> &group) {
         return for_each_selection(group, [&](const StreamSel &sel) {
             return enqueue_cascade(s, sel, dev_rows, n_rows, std::get<0>(key), std::get<1>(key), std::get<2>(key), std::get<3>(key));
@@ -1958,18 +1985,19 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
             if (rc != IDF_OK) return rc;
             s->held_buf[s->held++] = dev_rows; s->held_rows = n_rows;
             if (s->held >= s->batch || (s->held + 1) * n_rows > s->batch_rows) rc = gather_flush(s);
+            if (rc != IDF_OK && s->held > 0) --s->held;                      // (those before it still wait)
         } else {
             rc = gather_flush(s);
-            if (rc == IDF_OK)
-                rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, strict_cascade()); });
+            if (rc != IDF_OK) return rc;
+            rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, strict_cascade()); });
         }
-        if (rc != IDF_OK) return rc;
+        if (rc != IDF_OK) return give_up(rc);
     } else if (s->use_gather) {
         rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, false); });
-        if (rc != IDF_OK) return rc;
+        if (rc != IDF_OK) return give_up(rc);
     } else if (s->stg2d) {
         rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return row_run(s, sel, p, dev_rows, n_rows); });
-        if (rc != IDF_OK) return rc;
+        if (rc != IDF_OK) return give_up(rc);
     } else if (one_group) {
         rc = deliver(key0, members);
         if (rc != IDF_OK) return rc;
@@ -1982,16 +2010,7 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
         }
     }
     memo_r = -1;
-    for (int i = 0; i < n_ids; ++i) {
-        const int id = stream_ids ? stream_ids[i] : i;
-        StreamHost &h = s->h[id];
-        if (h.r != memo_r) { memo_r = h.r; memo_fresh = output_rows_of_push(net, h.r, n_rows); }
-        h.out_written += memo_fresh;
-        if (by_sample && h.early) h.early = early_after(s, h.early, h.r, h.r + n_rows);
-        h.r += n_rows;
-        h.x_next = 0;
-        if (net.in_h > 0 && h.r == net.in_h) { h.r = 0; ++h.sample; }      // next sample
-    }
+    for (int i = 0; i < n_ids; ++i) account(s->h[stream_ids ? stream_ids[i] : i], n_rows);
     return IDF_OK;
 }
 

@@ -43,3 +43,46 @@ def event_path(rt, streams, seg):
 @pytest.mark.parametrize("streams,seg", [(192, 1), (256, 2), (64, 8), (1, 16)])
 def test_event_path_next_to_wide_layers(runtime, streams, seg):
     host_runtime.run(runtime, "test_host_schedule", "event_path", streams, seg)
+
+
+# ---- a launch that cannot be enqueued ---------------------------------------------------------------------------
+def failed_launch(rt, net_args, streams, seg, fail_at, apart):
+    """Every push is tried with a failing launch; what it says it has taken in is not pushed again."""
+    import ctypes as C
+    from paper_1804_10727_amd import IdfError
+    h = net_args[1]
+    net = chain(*net_args)
+    st = host_runtime.Streams(net, streams, seg)
+
+    def rows(i):
+        r = C.c_int64()
+        st.check(st.L.idf_rows_pushed(st.h, i, C.byref(r)))
+        return r.value
+    rt.host_begin()
+    for ids in [[i] for i in range(streams)] if apart else [None]:
+        of, r, failures = (ids or [0])[0], 0, 0
+        while True:
+            rt.host_fail_in(fail_at)
+            before = r
+            try:
+                st.push(min(seg, h - r), ids)
+            except IdfError as e:
+                assert e.code == -4
+                failures += 1
+            rt.host_fail_in(-1)
+            r = rows(of)
+            if r == before:                            # nothing went in: at least the next push has to go well
+                st.push(1, ids)
+                r = rows(of)
+            if r == 0:                                 # the sample is complete
+                break
+        assert failures > 0
+    assert (st.read(h) == int(net.query_sizes(1, seg).out_h)).all()
+    assert rt.host_error() == b"", rt.host_error()
+    st.close()
+
+
+@pytest.mark.parametrize("fail_at", [0, 1, 2])
+@pytest.mark.parametrize("apart", [False, True])
+def test_rows_go_in_once_when_a_launch_fails(runtime, fail_at, apart):
+    host_runtime.run(runtime, "test_host_schedule", "failed_launch", ("f32", 64, 20, [3, 32, 32, 64, 64], (1,)), 3, 40, fail_at, apart)
