@@ -95,6 +95,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     constexpr int VL = T::VL, EB = T::EB;
     constexpr int R = NR + 2;                      // input rows
     constexpr int NW = 3 * MC;                     // weight fragments of a K-step
+    constexpr bool kFloat = std::is_same<st_t, float>::value;     // zero times infinity is not zero
     constexpr int kLoads = NP == 2 ? 17 : 9;       // cells each lane has in flight: a row of 32 positions (16) and halo x 32 cells at once
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ unsigned long long occ[kWaves];     // per input row, bit c: cell c holds an event somewhere in the stretch
@@ -215,6 +216,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             }
         }
         if (lane == 0) occ[wave] = mask;
+        // a cell of zeros behind the stretch, in every row, for the lanes past the window's end
+        if (kFloat && (cells & 3) && wave < R && lane == 0) *reinterpret_cast<i32x4 *>(row + (XT + 2) * stride) = i32x4{0, 0, 0, 0};
     } else {
         // a lane gathers whole windows: three times C_in values next to each other in the row
         if (active) fetch_w(wa);
@@ -382,8 +385,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     };
 
     // One K-step with its weights in w: row by row, a row's cells asked for while the row before is multiplied.
-    // off: this lane's cell of the step in the first input row.
-    auto kstep = [&](const i32x4 (&w)[NW], const unsigned char *buf, uint32_t off, uint32_t row_pitch, int np_pitch) IDF_INLINE {
+    // off: this lane's cell of the step in the first input row; np_pitch: from there to the next tile of positions.
+    auto kstep = [&](const i32x4 (&w)[NW], const unsigned char *buf, uint32_t off, uint32_t row_pitch, uint32_t np_pitch) IDF_INLINE {
         i32x4 x[2][NP];
 #pragma unroll
         for (int np = 0; np < NP; ++np) x[0][np] = *reinterpret_cast<const i32x4 *>(buf + off + np * np_pitch);
@@ -409,13 +412,18 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 #pragma unroll
                 for (int np = 0; np < NP; ++np)
                     x[np] = *reinterpret_cast<const i32x4 *>(smem + (r * XT + wp * 16 * NP + np * 16 + m) * wstride + (g < wcells ? g : wcells - 1) * 16);
+                if (kFloat && g >= wcells) {       // (past the window: the weights are zero, what was read may be infinite)
+#pragma unroll
+                    for (int np = 0; np < NP; ++np) x[np] = i32x4{0, 0, 0, 0};
+                }
                 deliver(wa, x, r);
                 n_mfma += (uint32_t)(((r <= 2) + (NR == 2 && r >= 1 && rows == 2)) * MC * NP);
             }
         }
     } else if (active) {
-        // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column (past the
-        // end the last one again: the weights there are zero)
+        // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column.  Past the end the
+        // weights are zero; a lane there reads a cell of zeros (float32, bfloat16: the last cell again may be infinite) or the
+        // last cell again.
         unsigned long long mask = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w)
@@ -430,21 +438,24 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             if (--col_left == 0) { left = mask; col_left = cells >> 2; }
         };
         const uint32_t row_pitch = (uint32_t)(a.row_pos * stride), pos = (uint32_t)((wp * 16 * NP + m) * stride);
+        const uint32_t tile = (uint32_t)(16 * stride), zeros = (uint32_t)((XT + 2) * stride);
+        auto past = [&](int st) IDF_INLINE { return kFloat && 4 * st + g >= 3 * cells; };
         auto at = [&](int st) IDF_INLINE {
             int q = 4 * st + g;
             q = q < 3 * cells ? q : 3 * cells - 1;
             const int kx = (q >= cells) + (q >= 2 * cells);
-            return pos + (uint32_t)(kx * stride + (q - kx * cells) * 16);
+            const uint32_t off = pos + (uint32_t)(kx * stride + (q - kx * cells) * 16);
+            return past(st) ? zeros : off;
         };
         if (mask)
 #pragma unroll 1
             for (int st = 0; st < n_ksteps; st += 2) {
                 fetch_w(wb); advance_w();
-                if (live()) kstep(wa, smem, at(st), row_pitch, 16 * stride);
+                if (live()) kstep(wa, smem, at(st), row_pitch, past(st) ? 0 : tile);
                 __builtin_amdgcn_sched_barrier(0); // K-steps stay apart: nothing of a later one is held in registers early
                 next();
                 fetch_w(wa); advance_w();
-                if (live() && st + 1 < n_ksteps) kstep(wb, smem, at(st + 1), row_pitch, 16 * stride);
+                if (live() && st + 1 < n_ksteps) kstep(wb, smem, at(st + 1), row_pitch, past(st + 1) ? 0 : tile);
                 __builtin_amdgcn_sched_barrier(0);
                 next();
             }
