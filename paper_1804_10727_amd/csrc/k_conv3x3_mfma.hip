@@ -87,15 +87,15 @@ constexpr int kEvCap = 512;                      // events (stretch and halo) of
 // sums it hands to the accumulators, and the tile's share of the layer's weights.
 constexpr size_t event_lds_bytes(int rows, int xt, int nc, int c_in) { return (size_t)(2 * (xt + 4) + kEvCap + rows * xt * nc + 3 * c_in * nc) * 4; }
 
-// MC tiles of 16 channels x NP tiles of 16 positions x NR output rows per wave.
-template <class T, int MC, int NP, int NR, bool EV>
+// MC tiles of 16 channels x NP tiles of 16 positions x NR output rows per wave.  PAD: positions may be padded (see pad_cells).
+template <class T, int MC, int NP, int NR, bool EV, bool PAD>
 __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, const int tile, const int si)
 {
     using acc_t = typename T::acc_t; using st_t = typename T::st_t; using ev_t = typename T::ev_t;
     constexpr int VL = T::VL, EB = T::EB;
     constexpr int R = NR + 2;                      // input rows
     constexpr int NW = 3 * MC;                     // weight fragments of a K-step
-    constexpr bool kFloat = std::is_same<st_t, float>::value;     // zero times infinity is not zero
+    constexpr bool kFloat = std::is_same<st_t, float>::value;
     constexpr int kLoads = NP == 2 ? 17 : 9;       // cells each lane has in flight: a row of 32 positions (16) and halo x 32 cells at once
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ unsigned long long occ[kWaves];     // per input row, bit c: cell c holds an event somewhere in the stretch
@@ -136,9 +136,9 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         }
     }
     // few channels: the stretch is kept as the windows the positions see, [row][position][3 * C_in values, padded to cells]
-    const int wcells = small_c ? (3 * C_in + VL - 1) / VL : 0;
+    const int wcells = small_c ? window_cells(C_in, VL, kFloat) : 0;
     const int wstride = cell_stride(wcells) * 16;
-    const int cells = a.cells, stride = cell_stride(cells) * 16;      // 16-byte cells per position; bytes from one position to the next
+    const int cells = a.cells, pad = PAD ? pad_cells(cells) : 0, stride = cell_stride(cells + pad) * 16;      // 16-byte cells per position; bytes from one position to the next
     const bool edge = x0 == 0 || x0 + XT >= W;
     auto cell_of = [&](int i, int &p, int &c) IDF_INLINE {
         p = (int)(((unsigned)i * a.cells_rcp) >> 16);
@@ -216,13 +216,14 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             }
         }
         if (lane == 0) occ[wave] = mask;
-        // a cell of zeros behind the stretch, in every row, for the lanes past the window's end
-        if (kFloat && (cells & 3) && wave < R && lane == 0) *reinterpret_cast<i32x4 *>(row + (XT + 2) * stride) = i32x4{0, 0, 0, 0};
+        if (PAD && pad && wave < R)
+            for (int p = lane; p < XT + 2; p += 64)
+                for (int c = 0; c < pad; ++c) *reinterpret_cast<i32x4 *>(row + p * stride + (cells + c) * 16) = i32x4{0, 0, 0, 0};
     } else {
         // a lane gathers whole windows: three times C_in values next to each other in the row
         if (active) fetch_w(wa);
         auto windows = [&](auto n_tag) IDF_INLINE {
-            constexpr int C = decltype(n_tag)::value, WC = (3 * C + VL - 1) / VL;
+            constexpr int C = decltype(n_tag)::value, WC = kFloat ? 4 : (3 * C + VL - 1) / VL;
             if (wave >= R) return;
             for (int p = lane; p < XT; p += 64) {
                 ev_t val[WC * VL];
@@ -385,8 +386,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     };
 
     // One K-step with its weights in w: row by row, a row's cells asked for while the row before is multiplied.
-    // off: this lane's cell of the step in the first input row; np_pitch: from there to the next tile of positions.
-    auto kstep = [&](const i32x4 (&w)[NW], const unsigned char *buf, uint32_t off, uint32_t row_pitch, uint32_t np_pitch) IDF_INLINE {
+    // off: this lane's cell of the step in the first input row.
+    auto kstep = [&](const i32x4 (&w)[NW], const unsigned char *buf, uint32_t off, uint32_t row_pitch, int np_pitch) IDF_INLINE {
         i32x4 x[2][NP];
 #pragma unroll
         for (int np = 0; np < NP; ++np) x[0][np] = *reinterpret_cast<const i32x4 *>(buf + off + np * np_pitch);
@@ -411,19 +412,14 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
                 i32x4 x[NP];
 #pragma unroll
                 for (int np = 0; np < NP; ++np)
-                    x[np] = *reinterpret_cast<const i32x4 *>(smem + (r * XT + wp * 16 * NP + np * 16 + m) * wstride + (g < wcells ? g : wcells - 1) * 16);
-                if (kFloat && g >= wcells) {       // (past the window: the weights are zero, what was read may be infinite)
-#pragma unroll
-                    for (int np = 0; np < NP; ++np) x[np] = i32x4{0, 0, 0, 0};
-                }
+                    x[np] = *reinterpret_cast<const i32x4 *>(smem + (r * XT + wp * 16 * NP + np * 16 + m) * wstride + (kFloat || g < wcells ? g : wcells - 1) * 16);
                 deliver(wa, x, r);
                 n_mfma += (uint32_t)(((r <= 2) + (NR == 2 && r >= 1 && rows == 2)) * MC * NP);
             }
         }
     } else if (active) {
         // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column.  Past the end the
-        // weights are zero; a lane there reads a cell of zeros (float32, bfloat16: the last cell again may be infinite) or the
-        // last cell again.
+        // weights are zero: the last one again, or the zeros behind it.
         unsigned long long mask = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w)
@@ -438,24 +434,21 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             if (--col_left == 0) { left = mask; col_left = cells >> 2; }
         };
         const uint32_t row_pitch = (uint32_t)(a.row_pos * stride), pos = (uint32_t)((wp * 16 * NP + m) * stride);
-        const uint32_t tile = (uint32_t)(16 * stride), zeros = (uint32_t)((XT + 2) * stride);
-        auto past = [&](int st) IDF_INLINE { return kFloat && 4 * st + g >= 3 * cells; };
         auto at = [&](int st) IDF_INLINE {
             int q = 4 * st + g;
-            q = q < 3 * cells ? q : 3 * cells - 1;
+            if (!PAD) q = q < 3 * cells ? q : 3 * cells - 1;
             const int kx = (q >= cells) + (q >= 2 * cells);
-            const uint32_t off = pos + (uint32_t)(kx * stride + (q - kx * cells) * 16);
-            return past(st) ? zeros : off;
+            return pos + (uint32_t)(kx * stride + (q - kx * cells) * 16);
         };
         if (mask)
 #pragma unroll 1
             for (int st = 0; st < n_ksteps; st += 2) {
                 fetch_w(wb); advance_w();
-                if (live()) kstep(wa, smem, at(st), row_pitch, past(st) ? 0 : tile);
+                if (live()) kstep(wa, smem, at(st), row_pitch, 16 * stride);
                 __builtin_amdgcn_sched_barrier(0); // K-steps stay apart: nothing of a later one is held in registers early
                 next();
                 fetch_w(wa); advance_w();
-                if (live() && st + 1 < n_ksteps) kstep(wb, smem, at(st + 1), row_pitch, past(st + 1) ? 0 : tile);
+                if (live() && st + 1 < n_ksteps) kstep(wb, smem, at(st + 1), row_pitch, 16 * stride);
                 __builtin_amdgcn_sched_barrier(0);
                 next();
             }
@@ -581,7 +574,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 // steps with the deepest (longest) first.  Consecutive workgroups go to the eight XCDs in turn: with a
 // multiple of eight streams a stream always meets the same XCD, so its rows stay in one L2 from the layer
 // that emits them to the layer that reads them.
-template <class T, bool EV, bool WIDE>
+template <class T, bool EV, bool WIDE, bool PAD>
 __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatch b, const StreamSel sel)
 {
     (void)b;                                      // the first argument: it begins the segment
@@ -593,9 +586,9 @@ __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatc
     if (tile >= a.tiles) return;
     switch (a.form) {
     case kRowTake: take_row<T>(a, sel, tile, si); break;
-    case kRowSmall1: conv_rows<T, 1, 1, 1, EV>(a, sel, tile, si); break;
-    case kRowSmall2: conv_rows<T, 1, 1, 2, EV>(a, sel, tile, si); break;
-    case kRowWide2: if constexpr (WIDE) conv_rows<T, 2, 2, 2, false>(a, sel, tile, si); break;
+    case kRowSmall1: conv_rows<T, 1, 1, 1, EV, PAD>(a, sel, tile, si); break;
+    case kRowSmall2: conv_rows<T, 1, 1, 2, EV, PAD>(a, sel, tile, si); break;
+    case kRowWide2: if constexpr (WIDE) conv_rows<T, 2, 2, 2, false, PAD>(a, sel, tile, si); break;
     default: break;
     }
 }
@@ -603,26 +596,26 @@ __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatc
 int form_np(int form) { return form == kRowWide2 ? 2 : 1; }
 int form_rows(int form) { return form == kRowSmall1 ? 1 : 2; }
 
+int position_stride(int prec, int cells) { return cell_stride(cells + (prec != IDF_PREC_I8 ? pad_cells(cells) : 0)); }
+
 size_t step_lds(int prec, const RowStep &a)
 {
     if (a.form == kRowTake) return 0;
     const int xt = (16 * form_np(a.form) * kWaves) >> a.wc_log, rows = form_rows(a.form) + 2;
-    if (a.cells == 0) {
-        const int wcells = (3 * a.c_in + conv3x3_mfma_vl(prec) - 1) / conv3x3_mfma_vl(prec);
-        return (size_t)rows * xt * cell_stride(wcells) * 16;
-    }
-    return (size_t)rows * a.row_pos * cell_stride(a.cells) * 16;
+    if (a.cells == 0) return (size_t)rows * xt * cell_stride(window_cells(a.c_in, conv3x3_mfma_vl(prec), prec != IDF_PREC_I8)) * 16;
+    return (size_t)rows * a.row_pos * position_stride(prec, a.cells) * 16;
 }
 
 template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc)
 {
     size_t lds = 0;
     int tiles = 0;
-    bool events = false, wide = false;
+    bool events = false, wide = false, pad = false;
     for (int k = 0; k < b.n; ++k) {
         const RowStep &a = b.st[k];
         tiles = std::max(tiles, a.tiles);
         wide = wide || a.form == kRowWide2;
+        pad = pad || (prec != IDF_PREC_I8 && a.form != kRowTake && (a.cells & 3));
         size_t need = step_lds(prec, a);
         if (a.ev_limit > 0) {
             events = true;
@@ -637,11 +630,16 @@ template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const Str
         if (prepared != hipSuccess) return prepared;
         return launch(kernel, grid, block, lds, lc, b, sel);
     };
-    if constexpr (T::kEvents)
-        if (events) return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, true, false>);
-    if constexpr (!std::is_same<T, TraitsF32>::value)
-        if (wide) return go(k_conv3x3_mfma_rows<T, false, true>);
-    return wide ? hipErrorInvalidValue : go(k_conv3x3_mfma_rows<T, false, false>);
+    constexpr bool kF32 = std::is_same<T, TraitsF32>::value;
+    if (wide && (kF32 || events)) return hipErrorInvalidValue;
+    if constexpr (T::kEvents) {
+        if (events) return go(k_conv3x3_mfma_rows<T, true, false, false>);
+    } else if (pad) {
+        // (a kernel of its own: where the kernel below had a few instructions for it -- a branch, a comparison per K-step, or
+        // unused loops beside the others -- nets without such layers took 1 to 2 % longer, float32 283 -> 288 us per image)
+        return wide ? go(k_conv3x3_mfma_rows<T, false, !kF32, true>) : go(k_conv3x3_mfma_rows<T, false, false, true>);
+    }
+    return wide ? go(k_conv3x3_mfma_rows<T, false, !kF32, false>) : go(k_conv3x3_mfma_rows<T, false, false, false>);
 }
 
 }  // namespace
@@ -684,7 +682,7 @@ void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, bool narrow, Row
     auto waves_log = [&](int tiles) { return tiles >= 4 ? 2 : tiles >= 2 ? 1 : 0; };
     a.wc_log = waves_log(wide ? n_ct / 2 : n_ct);
     // a stretch short enough for two workgroups to share a CU's LDS, where channels can take the waves instead of positions
-    while (a.wc_log < 2 && (((wide ? 128 : 64) >> a.wc_log) + 2) * cell_stride(std::max(a.cells, 1)) * 4 * 16 > 76 * 1024) ++a.wc_log;
+    while (a.wc_log < 2 && (((wide ? 128 : 64) >> a.wc_log) + 2) * position_stride(prec, std::max(a.cells, 1)) * 4 * 16 > 76 * 1024) ++a.wc_log;
     a.form = wide ? kRowWide2 : a.n_rows >= 2 ? kRowSmall2 : kRowSmall1;
     const int mc = a.form == kRowWide2 ? 2 : 1, xt = (16 * form_np(a.form) * kWaves) >> a.wc_log;
     auto rcp32 = [](int n) { return n > 1 ? (unsigned)((0x100000000ull + n - 1) / n) : 0u; };
