@@ -87,8 +87,9 @@ constexpr int kEvCap = 512;                      // events (stretch and halo) of
 // sums it hands to the accumulators, and the tile's share of the layer's weights.
 constexpr size_t event_lds_bytes(int rows, int xt, int nc, int c_in) { return (size_t)(2 * (xt + 4) + kEvCap + rows * xt * nc + 3 * c_in * nc) * 4; }
 
-// MC tiles of 16 channels x NP tiles of 16 positions x NR output rows per wave.  PAD: positions may be padded (see pad_cells).
-template <class T, int MC, int NP, int NR, bool EV, bool PAD>
+// MC tiles of 16 channels x NP tiles of 16 positions x NR output rows per wave.  TAIL: windows may end within a K-step,
+// in a float net: the weights behind are zero, but zero times infinity is not, so that what is read there has to be zero too.
+template <class T, int MC, int NP, int NR, bool EV, bool TAIL>
 __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, const int tile, const int si)
 {
     using acc_t = typename T::acc_t; using st_t = typename T::st_t; using ev_t = typename T::ev_t;
@@ -138,7 +139,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     // few channels: the stretch is kept as the windows the positions see, [row][position][3 * C_in values, padded to cells]
     const int wcells = small_c ? window_cells(C_in, VL, kFloat) : 0;
     const int wstride = cell_stride(wcells) * 16;
-    const int cells = a.cells, pad = PAD ? pad_cells(cells) : 0, stride = cell_stride(cells + pad) * 16;      // 16-byte cells per position; bytes from one position to the next
+    const int cells = a.cells, stride = cell_stride(cells) * 16;      // 16-byte cells per position; bytes from one position to the next
     const bool edge = x0 == 0 || x0 + XT >= W;
     auto cell_of = [&](int i, int &p, int &c) IDF_INLINE {
         p = (int)(((unsigned)i * a.cells_rcp) >> 16);
@@ -216,9 +217,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             }
         }
         if (lane == 0) occ[wave] = mask;
-        if (PAD && pad && wave < R)
-            for (int p = lane; p < XT + 2; p += 64)
-                for (int c = 0; c < pad; ++c) *reinterpret_cast<i32x4 *>(row + p * stride + (cells + c) * 16) = i32x4{0, 0, 0, 0};
+        // a cell of zeros in the row's next position (there is one: 64 divides no such stretch)
+        if (TAIL && (cells & 3) && wave < R && lane == 0) *reinterpret_cast<i32x4 *>(row + (XT + 2) * stride) = i32x4{0, 0, 0, 0};
     } else {
         // a lane gathers whole windows: three times C_in values next to each other in the row
         if (active) fetch_w(wa);
@@ -419,7 +419,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         }
     } else if (active) {
         // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column.  Past the end the
-        // weights are zero: the last one again, or the zeros behind it.
+        // weights are zero: the last one again, or (TAIL) a cell of zeros.
         unsigned long long mask = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w)
@@ -434,21 +434,24 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             if (--col_left == 0) { left = mask; col_left = cells >> 2; }
         };
         const uint32_t row_pitch = (uint32_t)(a.row_pos * stride), pos = (uint32_t)((wp * 16 * NP + m) * stride);
+        auto past = [&](int st) IDF_INLINE { return TAIL && 4 * st + g >= 3 * cells; };
         auto at = [&](int st) IDF_INLINE {
             int q = 4 * st + g;
-            if (!PAD) q = q < 3 * cells ? q : 3 * cells - 1;
+            q = q < 3 * cells ? q : 3 * cells - 1;
             const int kx = (q >= cells) + (q >= 2 * cells);
-            return pos + (uint32_t)(kx * stride + (q - kx * cells) * 16);
+            const uint32_t off = pos + (uint32_t)(kx * stride + (q - kx * cells) * 16);
+            return past(st) ? (uint32_t)((XT + 2) * stride) : off;
         };
+        auto next_tile = [&](int st) IDF_INLINE { return past(st) ? 0 : 16 * stride; };
         if (mask)
 #pragma unroll 1
             for (int st = 0; st < n_ksteps; st += 2) {
                 fetch_w(wb); advance_w();
-                if (live()) kstep(wa, smem, at(st), row_pitch, 16 * stride);
+                if (live()) kstep(wa, smem, at(st), row_pitch, next_tile(st));
                 __builtin_amdgcn_sched_barrier(0); // K-steps stay apart: nothing of a later one is held in registers early
                 next();
                 fetch_w(wa); advance_w();
-                if (live() && st + 1 < n_ksteps) kstep(wb, smem, at(st + 1), row_pitch, 16 * stride);
+                if (live() && st + 1 < n_ksteps) kstep(wb, smem, at(st + 1), row_pitch, next_tile(st + 1));
                 __builtin_amdgcn_sched_barrier(0);
                 next();
             }
@@ -574,7 +577,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 // steps with the deepest (longest) first.  Consecutive workgroups go to the eight XCDs in turn: with a
 // multiple of eight streams a stream always meets the same XCD, so its rows stay in one L2 from the layer
 // that emits them to the layer that reads them.
-template <class T, bool EV, bool WIDE, bool PAD>
+template <class T, bool EV, bool WIDE, bool TAIL>
 __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatch b, const StreamSel sel)
 {
     (void)b;                                      // the first argument: it begins the segment
@@ -586,9 +589,9 @@ __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatc
     if (tile >= a.tiles) return;
     switch (a.form) {
     case kRowTake: take_row<T>(a, sel, tile, si); break;
-    case kRowSmall1: conv_rows<T, 1, 1, 1, EV, PAD>(a, sel, tile, si); break;
-    case kRowSmall2: conv_rows<T, 1, 1, 2, EV, PAD>(a, sel, tile, si); break;
-    case kRowWide2: if constexpr (WIDE) conv_rows<T, 2, 2, 2, false, PAD>(a, sel, tile, si); break;
+    case kRowSmall1: conv_rows<T, 1, 1, 1, EV, TAIL>(a, sel, tile, si); break;
+    case kRowSmall2: conv_rows<T, 1, 1, 2, EV, TAIL>(a, sel, tile, si); break;
+    case kRowWide2: if constexpr (WIDE) conv_rows<T, 2, 2, 2, false, TAIL>(a, sel, tile, si); break;
     default: break;
     }
 }
@@ -596,26 +599,24 @@ __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatc
 int form_np(int form) { return form == kRowWide2 ? 2 : 1; }
 int form_rows(int form) { return form == kRowSmall1 ? 1 : 2; }
 
-int position_stride(int prec, int cells) { return cell_stride(cells + (prec != IDF_PREC_I8 ? pad_cells(cells) : 0)); }
-
 size_t step_lds(int prec, const RowStep &a)
 {
     if (a.form == kRowTake) return 0;
     const int xt = (16 * form_np(a.form) * kWaves) >> a.wc_log, rows = form_rows(a.form) + 2;
     if (a.cells == 0) return (size_t)rows * xt * cell_stride(window_cells(a.c_in, conv3x3_mfma_vl(prec), prec != IDF_PREC_I8)) * 16;
-    return (size_t)rows * a.row_pos * position_stride(prec, a.cells) * 16;
+    return (size_t)rows * a.row_pos * cell_stride(a.cells) * 16;
 }
 
 template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc)
 {
     size_t lds = 0;
     int tiles = 0;
-    bool events = false, wide = false, pad = false;
+    bool events = false, wide = false, tail = false;
     for (int k = 0; k < b.n; ++k) {
         const RowStep &a = b.st[k];
         tiles = std::max(tiles, a.tiles);
         wide = wide || a.form == kRowWide2;
-        pad = pad || (prec != IDF_PREC_I8 && a.form != kRowTake && (a.cells & 3));
+        tail = tail || (prec != IDF_PREC_I8 && a.form != kRowTake && (a.cells & 3));
         size_t need = step_lds(prec, a);
         if (a.ev_limit > 0) {
             events = true;
@@ -634,7 +635,7 @@ template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const Str
     if (wide && (kF32 || events)) return hipErrorInvalidValue;
     if constexpr (T::kEvents) {
         if (events) return go(k_conv3x3_mfma_rows<T, true, false, false>);
-    } else if (pad) {
+    } else if (tail) {
         // (a kernel of its own: where the kernel below had a few instructions for it -- a branch, a comparison per K-step, or
         // unused loops beside the others -- nets without such layers took 1 to 2 % longer, float32 283 -> 288 us per image)
         return wide ? go(k_conv3x3_mfma_rows<T, false, !kF32, true>) : go(k_conv3x3_mfma_rows<T, false, false, true>);
@@ -682,7 +683,7 @@ void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, bool narrow, Row
     auto waves_log = [&](int tiles) { return tiles >= 4 ? 2 : tiles >= 2 ? 1 : 0; };
     a.wc_log = waves_log(wide ? n_ct / 2 : n_ct);
     // a stretch short enough for two workgroups to share a CU's LDS, where channels can take the waves instead of positions
-    while (a.wc_log < 2 && (((wide ? 128 : 64) >> a.wc_log) + 2) * position_stride(prec, std::max(a.cells, 1)) * 4 * 16 > 76 * 1024) ++a.wc_log;
+    while (a.wc_log < 2 && (((wide ? 128 : 64) >> a.wc_log) + 2) * cell_stride(std::max(a.cells, 1)) * 4 * 16 > 76 * 1024) ++a.wc_log;
     a.form = wide ? kRowWide2 : a.n_rows >= 2 ? kRowSmall2 : kRowSmall1;
     const int mc = a.form == kRowWide2 ? 2 : 1, xt = (16 * form_np(a.form) * kWaves) >> a.wc_log;
     auto rcp32 = [](int n) { return n > 1 ? (unsigned)((0x100000000ull + n - 1) / n) : 0u; };

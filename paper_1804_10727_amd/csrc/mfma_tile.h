@@ -147,10 +147,8 @@ __device__ __forceinline__ int taps_of(int v, int n) { return 3 - (v == 0) - (v 
 // 123 at 9, 63 at 8).
 __host__ __device__ inline int cell_stride(int cells) { return cells == 1 ? 1 : (cells + 1) / 4 * 4 + 2; }
 
-// A K-step takes four cells.  Where the cells of a window do not come out even, the weights behind its end are zero, but zero times
-// infinity is not: float nets keep as many cells of zeros behind every position as the last K-step reads too far.
-__host__ __device__ inline int pad_cells(int cells) { return -3 * cells & 3; }
-// Cells of a window of 3 * c_in values, for layers of a few channels.
+// Cells of a window of 3 * c_in values, for layers of a few channels.  A K-step takes four cells: behind the window the weights are
+// zero, but zero times infinity is not, so that float nets keep zeros there.
 __host__ __device__ inline int window_cells(int c_in, int vl, bool is_float) { return is_float ? 4 : (3 * c_in + vl - 1) / vl; }
 
 }  // namespace
