@@ -223,7 +223,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         // a lane gathers whole windows: three times C_in values next to each other in the row
         if (active) fetch_w(wa);
         auto windows = [&](auto n_tag) IDF_INLINE {
-            constexpr int C = decltype(n_tag)::value, WC = kFloat ? 4 : (3 * C + VL - 1) / VL;
+            constexpr int C = decltype(n_tag)::value, WC = window_cells(C, VL, kFloat);
             if (wave >= R) return;
             for (int p = lane; p < XT; p += 64) {
                 ev_t val[WC * VL];

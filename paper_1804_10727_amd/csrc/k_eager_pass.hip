@@ -34,6 +34,10 @@ typedef const __attribute__((address_space(4))) EagerPass PassArgs;
 constexpr int kPassWaves = 16, kPassThreads = 64 * kPassWaves;
 constexpr int kQueue = 3;                        // K-steps whose weights are on their way
 
+// Zero times infinity is not zero: in a float net the first layer's positions carry as many cells of zeros as the last K-step of
+// their windows reads too far.  (Layers behind it have a multiple of 16 channels: their windows are whole K-steps.)
+__host__ __device__ inline int pad_cells(bool is_float, int cells) { return is_float ? -3 * cells & 3 : 0; }
+
 extern __shared__ __attribute__((aligned(16))) unsigned char pass_smem[];
 
 // ---- the pushed rows: announced values, events, and the first layer's delta band ---------------------
@@ -55,18 +59,18 @@ template <class T> __device__ __forceinline__ void pass_input(PassArgs &a, PassS
         }
         slot = slot + 1 == a.ann0_rows ? 0 : slot + 1;
     }
-    if (L.cells > 0) {                             // whole cells: [row][position, one of halo in front][channel]
-        const int cells = L.cells, n = XP * cells;
+    if (L.cells > 0) {                             // whole cells: [row][position, one of halo in front][channel], padded (pad_cells)
+        const int cells = L.cells, all = cells + pad_cells(T::EB == 4, cells), n = XP * all;
         for (int r = 0; r < n_rows; ++r)
             for (int i = tid; i < n; i += kPassThreads) {
-                const int p = i / cells, c = i - p * cells, x = p - 1;
+                const int p = i / all, c = i - p * all, x = p - 1;
                 i32x4 v = {0, 0, 0, 0};
-                if (x >= 0 && x < W) v = reinterpret_cast<const i32x4 *>(src)[(r * W + x) * cells + c];
+                if (x >= 0 && x < W && c < cells) v = reinterpret_cast<const i32x4 *>(src)[(r * W + x) * cells + c];
                 *reinterpret_cast<i32x4 *>(out + r * L.in_pitch + p * L.in_stride + c * 16) = v;
             }
     } else {                                       // few channels: the windows the positions see, 3 * C values padded to cells
         auto windows = [&](auto n_tag) IDF_INLINE {
-            constexpr int NC = decltype(n_tag)::value, WC = (3 * NC + T::VL - 1) / T::VL;
+            constexpr int NC = decltype(n_tag)::value, WC = window_cells(NC, T::VL, T::EB == 4);
             const int XT = 16 * L.n_xt;
             // (a wave takes whole rows: the waves are many and a row is short)
             for (int r = tid >> 6; r < n_rows; r += kPassWaves)
@@ -209,12 +213,13 @@ template <class T> __device__ __forceinline__ void pass_conv(PassStep &L, int st
                             if (r - ky >= 0 && r - ky < 4) acc[r - ky] = T::mfma(w[ky], xv[r], acc[r - ky], e);
                 }
             };
-            // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column (past the end the
-            // last one again: the weights there are zero); few channels: the cells of the gathered window
+            // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column (past the end, where
+            // the weights are zero, the padding of the last position; int8: the last one again); few channels: the cells of the
+            // gathered window
             auto at = [&](int st) IDF_INLINE {
                 int q = 4 * st + g;
                 if (cells == 0) return (uint32_t)(q < win_cells ? q : win_cells - 1) * 16;
-                q = q < 3 * cells ? q : 3 * cells - 1;
+                if (T::EB == 1) q = q < 3 * cells ? q : 3 * cells - 1;
                 const int kx = (q >= cells) + (q >= 2 * cells);
                 return (uint32_t)(kx * in_stride + (q - kx * cells) * 16);
             };
@@ -342,9 +347,9 @@ bool eager_pass_shape(int prec, EagerPass &a)
         L.n_ct = L.c_out == 16 ? 1 : 2 * ((L.c_out + 31) / 32);
         L.xt_rcp = rcp32(L.n_xt); L.ct_rcp = rcp32(L.n_ct);
         L.cells = L.c_in % vl == 0 ? L.c_in / vl : 0;
-        L.win_cells = L.cells ? 0 : (3 * L.c_in + vl - 1) / vl;
+        L.win_cells = L.cells ? 0 : window_cells(L.c_in, vl, eb == 4);
         L.n_ksteps = L.cells ? (3 * L.cells + 3) / 4 : 1;
-        L.in_stride = cell_stride(L.cells ? L.c_in * eb / 16 : L.win_cells) * 16;
+        L.in_stride = cell_stride(L.cells ? L.cells + pad_cells(eb == 4, L.cells) : L.win_cells) * 16;
         L.in_pitch = (16 * L.n_xt + 2) * L.in_stride;
         size[k] = (size_t)L.n_in * L.in_pitch;
         if (k > 0) { a.st[k - 1].out_stride = L.in_stride; a.st[k - 1].out_pitch = L.in_pitch; a.st[k - 1].out_rows = L.n_in; }

@@ -149,7 +149,7 @@ __host__ __device__ inline int cell_stride(int cells) { return cells == 1 ? 1 : 
 
 // Cells of a window of 3 * c_in values, for layers of a few channels.  A K-step takes four cells: behind the window the weights are
 // zero, but zero times infinity is not, so that float nets keep zeros there.
-__host__ __device__ inline int window_cells(int c_in, int vl, bool is_float) { return is_float ? 4 : (3 * c_in + vl - 1) / vl; }
+__host__ __device__ constexpr int window_cells(int c_in, int vl, bool is_float) { return is_float ? 4 : (3 * c_in + vl - 1) / vl; }
 
 }  // namespace
 

@@ -62,3 +62,26 @@ def test_only_windows_that_hold_it_are_reached(prec, c_in, c_out, W, streams, se
     assert st.layer_kernels() == ["conv3x3_mfma"]
     st.close(); net.destroy()
     check(wl, out)
+
+
+@pytest.mark.parametrize("c_in,c_out,W,seg", [(1, 16, 35, 1), (2, 32, 50, 2), (3, 32, 66, 1), (4, 48, 33, 3), (8, 32, 50, 1), (12, 64, 34, 4), (20, 16, 70, 2), (16, 32, 35, 1)])
+def test_only_windows_that_hold_it_are_reached_in_eager_emission(c_in, c_out, W, seg):
+    import torch
+    import paper_1804_10727_amd as idf
+    from paper_1804_10727_amd.binding import input_tensor
+    wl = one_layer("f32", 8, W, c_in, c_out, 24, seg)
+    for b, (y, x, c) in enumerate(places(wl)):
+        wl["x"][b, y, x, c] = np.inf
+    net = idf.net_from_workload(wl)
+    st = idf.Streams(net, wl["streams"], max_seg_rows=seg)
+    st.enable_eager()
+    x = input_tensor(wl)
+    st.profile_begin()
+    for r in range(0, 8, seg):
+        st.push_segment(x[:, r:r + seg].contiguous())
+    prof = st.profile_end()
+    out = st.read_announced(1, (8, W, c_out))
+    torch.cuda.synchronize()
+    assert [(p["name"], p["launches"]) for p in prof] == [("eager@0", -(-8 // seg))]      # a launch per push
+    check(wl, out.cpu().numpy())
+    st.close(); net.destroy()
