@@ -74,6 +74,9 @@ int conv3x3_mfma_event_cap();
 // Fills in how the workgroups of a step of a.n_rows rows lie (a.n_rows and a.ev_limit are set).  narrow: the step may share a
 // launch with one that takes the event path.
 void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, bool narrow, RowStep &a);
+// Tiles per stream and step that a launch takes; a step of more is cut after as many rows as fit (false: not even two do).
+constexpr int kRowTilesMax = 65535;
+bool conv3x3_mfma_split(RowStep &first, RowStep &rest);
 hipError_t launch_conv3x3_mfma_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc);
 
 // Matrix-core kernel that gathers its windows from memory: any kernel size, strides 1, 2, 4 .., any padding.

@@ -605,6 +605,19 @@ void take_step(idf_streams *s, int k, int64_t at, int64_t n, const void *dev_row
 int launch_rows(idf_streams *s, const RowBatch &b, const StreamSel &sel, double bytes, int layer)
 {
     if (b.n == 0) return IDF_OK;
+    bool fits = true;
+    for (int k = 0; k < b.n; ++k) fits = fits && b.st[k].tiles <= kRowTilesMax;
+    if (!fits) {
+        // a step of more tiles than a launch takes: its first rows, then the others (no step of a batch writes what one reads)
+        RowBatch first = b, rest;
+        rest.n = 0;
+        for (int k = 0; k < b.n; ++k)
+            if (b.st[k].tiles > kRowTilesMax && conv3x3_mfma_split(first.st[k], rest.st[rest.n])) ++rest.n;
+        if (rest.n > 0) {
+            int rc = launch_rows(s, first, sel, bytes, layer);
+            return rc != IDF_OK ? rc : launch_rows(s, rest, sel, 0, layer);
+        }
+    }
     hipError_t e = launch_conv3x3_mfma_rows(s->net->precision, b, sel, launch_ctx(s, kKindConvMfma, bytes, layer));
     return e == hipSuccess ? IDF_OK : dev_fail(e, "mfma conv launch");
 }

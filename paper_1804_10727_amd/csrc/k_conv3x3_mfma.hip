@@ -624,7 +624,7 @@ template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const Str
         }
         lds = std::max(lds, need);
     }
-    if (b.n < 1 || tiles < 1 || tiles > 65535 || lds > 160 * 1024 - 256) return hipErrorInvalidValue;      // tiles are the grid's y extent
+    if (b.n < 1 || tiles < 1 || tiles > kRowTilesMax || lds > 160 * 1024 - 256) return hipErrorInvalidValue;      // tiles are the grid's y extent
     const dim3 grid(sel.n, tiles, b.n), block(kThreads);
     auto go = [&](auto kernel) {
         static hipError_t prepared = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
@@ -695,6 +695,21 @@ void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, bool narrow, Row
     a.nb = ((xt + 2) * cells + 63) / 64;
     a.row_pos = (a.nb * 64 + cells - 1) / cells;
     a.cells_rcp = (unsigned)((65536 + cells - 1) / cells);
+}
+
+bool conv3x3_mfma_split(RowStep &first, RowStep &rest)
+{
+    const int pairs = first.form == kRowTake ? 1 : form_rows(first.form), per = first.form == kRowTake ? 1 : first.n_xt * first.n_cg;
+    const int n = kRowTilesMax / per * pairs;
+    if (n < 1 || n >= first.n_rows) return false;
+    rest = first;
+    first.n_rows = n;
+    first.tiles = n / pairs * per;
+    rest.n_rows -= n; rest.y0 += n;
+    rest.tiles = (rest.n_rows + pairs - 1) / pairs * per;
+    rest.slot0 = (rest.slot0 + n) % rest.ring_rows;
+    if (first.form != kRowTake) rest.dst_slot0 = (rest.dst_slot0 + (first.pool ? n / 2 : n)) % rest.dst_rows;
+    return true;
 }
 
 // Weights [k_h][k_w][c_in][c_out] -> fragment order, zero padded to whole K-steps and channel pairs:

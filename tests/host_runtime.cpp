@@ -42,6 +42,13 @@ void rows_launch(const RowBatch &b, const StreamSel &sel, const Dim3 &grid, size
     if ((long)lds > g_lds_limit) return error("LDS of " + str(lds));
     std::vector<std::pair<uintptr_t, Row>> writes;
     std::map<uintptr_t, int> reads;
+    for (int k = 0; k < b.n; ++k) {                        // rows that a layer of another kind has put into a ring: here they are counted
+        const RowStep &a = b.st[k];
+        for (int i = 0; a.form == kRowTake && !a.in_new && i < sel.n; ++i)
+            for (int r = 0; r < a.n_rows; ++r)
+                g_rows[(uintptr_t)a.in_ring + (uintptr_t)((a.in_stride * (int64_t)sel_stream(sel, i) + (int64_t)((a.slot0 + r) % a.ring_rows) * a.w * a.c_in) * eb)] =
+                    Row{a.layer, a.y0 + r};
+    }
     for (int k = 0; k < b.n; ++k) {
         const RowStep &a = b.st[k];
         if (a.tiles < 1 || a.tiles > (int)grid.y) error("tiles of a step exceed the grid");

@@ -189,3 +189,28 @@ def test_two_samples_through_the_staged_layers():
         check_stream(wl, out1[i].cpu().numpy(), i)
         check_stream(wl, out2[i].cpu().numpy(), 2 + i)
     st.close(); net.destroy()
+
+
+@pytest.mark.parametrize("pool", [False, True])
+def test_a_push_of_more_rows_than_a_launch_has_tiles_for(pool):
+    """2201 rows of 3840 positions in one push, 66060 tiles, against pushes of 100 rows: bit for bit."""
+    import torch
+    import paper_1804_10727_amd as idf
+    rng = np.random.default_rng(8)
+    H, W = 2201, 3840
+    layers = [conv(1, 16, 3, 3, p_h=1, p_w=1)] + ([maxpool(16)] if pool else []) + [conv(16, 1, 1, 1, act="none")]
+    ws = [None if L["kind"] != "conv" else rng.normal(size=(L["c_out"], L["c_in"], L["k_h"], L["k_w"])).astype(np.float32) for L in layers]
+    x = torch.rand((1, H, W, 1), generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+    net = idf.Net("f32", H, W, 1, layers, ws)
+    outs = []
+    for seg in (100, H):
+        st = idf.Streams(net, 1, max_seg_rows=seg)
+        assert st.layer_kernels()[0] == "conv3x3_mfma" and st.layer_kernels()[-1] == "conv_generic", st.layer_kernels()
+        for r in range(0, H, seg):
+            st.push_segment(x[:, r:r + seg].contiguous())
+        out, _, n = st.read_outputs(int(st.sizes.out_h))
+        assert n[0] == st.sizes.out_h
+        outs.append(out)
+        st.close()
+    net.destroy()
+    assert torch.equal(outs[0], outs[1]) and float(outs[0].abs().max()) > 0

@@ -86,3 +86,46 @@ def failed_launch(rt, net_args, streams, seg, fail_at, apart):
 @pytest.mark.parametrize("apart", [False, True])
 def test_rows_go_in_once_when_a_launch_fails(runtime, fail_at, apart):
     host_runtime.run(runtime, "test_host_schedule", "failed_launch", ("f32", 64, 20, [3, 32, 32, 64, 64], (1,)), 3, 40, fail_at, apart)
+
+
+# ---- pushes of more rows than a launch has tiles for ---------------------------------------------------------------
+def mixed(prec, h, w, channels, pools=(), last_1x1=True):
+    """The same with a 1x1 layer behind, or in front: the layers go one after the other."""
+    import paper_1804_10727_amd as idf
+    from workloads import conv, maxpool
+    dt = {"f32": np.float32, "bf16": np.uint16}[prec]
+    layers, weights = [], []
+    for i, (a, b) in enumerate(zip(channels, channels[1:])):
+        k = 1 if i == (len(channels) - 2 if last_1x1 else 0) else 3
+        layers.append(conv(a, b, k, k, p_h=k // 2, p_w=k // 2))
+        weights.append(np.ones((b, a, k, k), dt))
+        if i in pools:
+            layers.append(maxpool(b))
+            weights.append(None)
+    return idf.Net(prec, h, w, channels[0], layers, weights)
+
+
+def long_push(rt, kind, net_args, seg):
+    net = (chain if kind == "chain" else mixed)(*net_args)
+    h = net_args[1]
+    st = host_runtime.Streams(net, 1, seg)
+    rt.host_begin()
+    for _ in range(2):
+        for r in range(0, h, seg):
+            st.push(min(seg, h - r))
+        st.read(h)
+    assert rt.host_error() == b"", rt.host_error()
+    st.close()
+
+
+@pytest.mark.parametrize("kind,net_args,seg", [
+    ("mixed", ("f32", 1080, 3840, [3, 64, 64, 16]), 1080),
+    ("mixed", ("f32", 1080, 3840, [3, 64, 64, 16], (0,)), 1080),
+    ("mixed", ("f32", 1081, 3840, [3, 64, 64, 16], (1,)), 700),
+    ("mixed", ("f32", 512, 1920, [3, 256, 256, 16]), 512),
+    ("mixed", ("f32", 70001, 40, [3, 16, 16]), 70001),                # (more rows taken than a launch has tiles)
+    ("mixed", ("bf16", 1080, 3840, [8, 64, 128, 16], (), False), 1080),
+    ("chain", ("f32", 64, 60000, [3, 256, 256], (0,)), 64),
+])
+def test_long_pushes_are_several_launches(runtime, kind, net_args, seg):
+    host_runtime.run(runtime, "test_host_schedule", "long_push", kind, net_args, seg)
