@@ -158,7 +158,7 @@ struct RowStep {
     int dst_slot0, dst_rows;           // slot of the first emitted row, slots of the destination
     int layer, pool_layer, next_layer, next_c_out, n_layers;     // next_layer: the layer whose events the emitted rows are (-1: it counts them itself)
     int ev_limit;                      // a row's stretch of 32 positions with at most this many events goes the event path (0: never; at most half the list's length)
-    int in_stride, new_stride;         // elements per stream of the ring / of the caller's buffer
+    int64_t in_stride, new_stride;     // elements per stream of the ring / of the caller's buffer
     const void *in_ring, *in_new;
     void *dst;
     int64_t dst_stride;

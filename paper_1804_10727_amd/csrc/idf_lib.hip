@@ -540,7 +540,7 @@ void row_step(idf_streams *s, int k, int64_t o, int64_t n, int n_streams, bool c
     a.layer = u.l; a.n_layers = nl;
     a.next_layer = -1;
     if (u.next >= 0) { a.next_layer = s->units[u.next].l; a.next_c_out = net.g[a.next_layer].c_out; }
-    a.in_ring = s->ws + u.ring_off; a.in_stride = (int)u.ring_stride;
+    a.in_ring = s->ws + u.ring_off; a.in_stride = u.ring_stride;
     a.to_output = u.last;
     if (u.last) {
         a.dst = s->ws + s->out_off; a.dst_stride = s->out_stride; a.dst_rows = (int)s->out_cap;
@@ -587,7 +587,7 @@ void take_step(idf_streams *s, int k, int64_t at, int64_t n, const void *dev_row
     a.cells = g.c_in % vl == 0 && g.c_in >= vl ? g.c_in / vl : 0;
     a.y0 = (int)(at % g.h_in); a.n_rows = (int)n;
     a.ring_rows = u.ring_rows; a.slot0 = mod_rows(at, u.ring_rows);
-    a.in_ring = s->ws + u.ring_off; a.in_stride = (int)u.ring_stride;
+    a.in_ring = s->ws + u.ring_off; a.in_stride = u.ring_stride;
     a.x_lo = 0; a.x_hi = g.w_in;
     a.layer = u.l; a.n_layers = (int)net.g.size();
     a.stats = (unsigned long long *)(s->ws + s->stats_off);
@@ -595,10 +595,10 @@ void take_step(idf_streams *s, int k, int64_t at, int64_t n, const void *dev_row
     a.in_new = dev_rows;
     a.y_new = a.y0 - row_of_buffer;
     a.y_save = a.y0 + (int)std::max<int64_t>(0, save_at - at);
-    a.new_stride = n_rows * net.in_w * net.in_c;
+    a.new_stride = (int64_t)n_rows * net.in_w * net.in_c;
     if (s->part.on) {                              // a pixel segment: one row's columns [x_lo, x_hi)
         a.x_lo = s->part.x_lo; a.x_hi = s->part.x_hi; a.y_save = a.y0; a.y_new = a.y0;
-        a.new_stride = (a.x_hi - a.x_lo) * net.in_c;
+        a.new_stride = (int64_t)(a.x_hi - a.x_lo) * net.in_c;
     }
 }
 
@@ -663,7 +663,7 @@ bool row_plan(idf_streams *s, RowProg &p, int n_streams, const void *dev_rows, i
         row_step(s, k, o, n, n_streams, (q.early >> k) & 1u, b.st[b.n], bytes);
         if (k == 0 && n_new > 0 && !part && p.in[0] / g.h_in == o / g.h_out) {      // (else the new rows are of the next sample)
             b.st[b.n].in_new = (const char *)dev_rows + (int64_t)row0 * net.in_w * net.in_c * ev_bytes(net.precision);
-            b.st[b.n].new_stride = n_rows * net.in_w * net.in_c;
+            b.st[b.n].new_stride = (int64_t)n_rows * net.in_w * net.in_c;
             b.st[b.n].y_new = (int)(p.in[0] % g.h_in);
         }
         ++b.n;
@@ -1066,7 +1066,7 @@ int enqueue_cascade(idf_streams *s, const StreamSel &sel, const void *dev_rows, 
             if (c_fin > c_lo && !part) {
                 RowStep &a = b.st[b.n++];
                 row_step(s, k, sample * g.h_out + c_lo, c_fin - c_lo, sel.n, (early >> k) & 1u, a, bytes);
-                if (own_rows) { a.in_new = dev_rows; a.new_stride = (int)in_stride; a.y_new = (int)y0; }
+                if (own_rows) { a.in_new = dev_rows; a.new_stride = in_stride; a.y_new = (int)y0; }
                 if (!u.last && u.next < 0) a.dst_slot0 = 0;
                 if (u.last) a.dst_slot0 = (int)out_slot0;
             }

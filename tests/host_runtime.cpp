@@ -59,6 +59,7 @@ void rows_launch(const RowBatch &b, const StreamSel &sel, const Dim3 &grid, size
             if ((int64_t)a.in_stride < (int64_t)a.ring_rows * a.w * a.c_in) error("ring stride of layer " + str(a.layer));
             if (a.form == kRowTake) {
                 if (a.tiles != a.n_rows) error("rows taken");
+                if (a.in_new && a.new_stride < (int64_t)a.n_rows * (a.x_hi - a.x_lo) * a.c_in) error("stride of the caller's rows");
                 for (int r = 0; r < a.n_rows; ++r)
                     if (a.in_new && a.y0 + r >= a.y_save) writes.push_back({ring + (size_t)((a.slot0 + r) % a.ring_rows) * row_bytes, Row{a.layer, a.y0 + r}});
                 continue;

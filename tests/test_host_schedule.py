@@ -126,6 +126,7 @@ def long_push(rt, kind, net_args, seg):
     ("mixed", ("f32", 70001, 40, [3, 16, 16]), 70001),                # (more rows taken than a launch has tiles)
     ("mixed", ("bf16", 1080, 3840, [8, 64, 128, 16], (), False), 1080),
     ("chain", ("f32", 64, 60000, [3, 256, 256], (0,)), 64),
+    ("mixed", ("bf16", 1200, 7680, [256, 256, 256, 16]), 1200),       # (streams 2^31 elements apart, in the rings and in the buffer)
 ])
 def test_long_pushes_are_several_launches(runtime, kind, net_args, seg):
     host_runtime.run(runtime, "test_host_schedule", "long_push", kind, net_args, seg)
