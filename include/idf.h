@@ -175,7 +175,10 @@ int idf_query_sizes(const idf_net *net, int n_streams, int max_seg_rows, int64_t
 /* Open n_streams streams, all at row 0 with zero state (Sec. 3 assumes the network starts
  * from all-zero state).  dev_workspace (device, 256-byte aligned, >= workspace_bytes) stays owned by
  * the caller.  hip_stream: a hipStream_t (NULL = the default stream).  Enqueues the upload of
- * the packed weights. */
+ * the packed weights.
+ * idf_query_sizes tells what the fastest layout takes.  In a smaller workspace the layers give way:
+ * fewer rows per launch, rings of fewer rows, layers one after the other, in the end kernels that
+ * keep rows of c only.  IDF_EINVAL (with the size in the message) if none of that fits. */
 int idf_open_streams(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
                      void *dev_workspace, size_t workspace_bytes, void *hip_stream,
                      idf_streams **out);
@@ -192,8 +195,8 @@ int idf_close_streams(idf_streams *s);
  *     streams left in it; this call clears every byte it lays out before anything reads it.
  *   - One set of streams per GPU can hold it at a time: IDF_ESTATE while another set opened this
  *     way on the same GPU has not been closed (two sets would race for the same bytes).
- *   - IDF_ENOMEM with the sizes in the message if idf_query_sizes(...).workspace_bytes exceeds
- *     IDF_STATIC_WORKSPACE_BYTES: nothing is opened.
+ *   - IDF_ENOMEM with the sizes in the message if not even the smallest layout (see
+ *     idf_open_streams) fits IDF_STATIC_WORKSPACE_BYTES: nothing is opened.
  * Everything else is as for idf_open_streams; close with idf_close_streams. */
 #define IDF_STATIC_WORKSPACE_BYTES (32u << 20)
 int idf_open_streams_static(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,

@@ -141,6 +141,8 @@ struct idf_streams {
     std::vector<GatherStep> gather;             // per unit: what a step of it holds whatever the rows
     // pushes of all streams in step that wait for their launch (idf_set_push_batching)
     int batch = 1, batch_rows = 0;              // pushes per launch; rows a launch takes at most as the rings lie now
+    int batch_room = 0;                         // and as they can lie at most
+    int launch_rows = 0;                        // rows that arrive with a launch of 3x3 layers at most
     int held = 0, held_rows = 0;                // waiting buffers, and the rows each of them brings
     const void *held_buf[kGatherSegs];
     // Layers on the matrix-core kernel.  Where it serves the whole net (stg2d) one launch per push holds a step
@@ -218,8 +220,20 @@ struct Layout {
     int64_t out_stride = 0;
     bool gather = false;             // the gathering kernel serves this net
     bool cascade1d = false;          // and it is 1-D
+    bool staged = false;             // the layers run side by side
+    int launch_rows = 0, batch_rows = 0;       // rows that arrive with a launch at most: 3x3 layers, held-back pushes of a 1-D net
     idf_sizes sizes{};
 };
+
+// What gives way where a workspace does not hold the layout that is fastest.
+struct Fit {
+    int batch = kGatherSegs;         // 1-D nets: pushes a launch takes at most
+    int launch_rows = kRowLaunchRows;          // 3x3 nets: rows that arrive with a launch at most
+    bool tight = false;              // 3x3 layers: rings of the fewest rows that still move on
+    bool by_kind = false;            // a net of several kinds of layers goes layer by layer (rows of c instead of twice the rows of a launch)
+    bool plain = false;              // every layer on the generic kernels, which keep rows of c only
+};
+const Fit kFits[] = {{}, {8}, {4}, {2}, {1}, {1, 8}, {1, 4}, {1, 2}, {1, 1}, {1, 1, true}, {1, kRowLaunchRows, false, true}, {1, 1, true, true}, {1, 1, true, true, true}};
 
 // Staged layers (one launch per push, layer l a launch behind layer l-1), rows pushed one at a time: a layer
 // takes its rows in pairs, so besides the K_h rows its output rows still need at most two rows wait for it
@@ -289,10 +303,9 @@ bool gather_net(const idf_net &net, int B, int max_seg)
     return true;
 }
 
-// by_kind: a net of several kinds of layers goes layer by layer, which takes less memory (rows of c instead of twice the rows a
-// launch brings).
-int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout &L, bool by_kind = false)
+int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout &L, const Fit &fit = Fit())
 {
+    L = Layout{};
     const int n = (int)net.g.size();
     const int eb = ev_bytes(net.precision);
     size_t off = 0;
@@ -300,20 +313,21 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     L.ring_off.assign(n, 0); L.held_off.assign(n, 0); L.transit_off.assign(n, 0);
     L.ring_stride.assign(n, 0); L.held_stride.assign(n, 0); L.transit_stride.assign(n, 0);
     L.transit_cap.assign(n, 0);
-    // rows a layer completes in one push at most, and in one launch of the staged mode (which takes
-    // kRowLaunchRows arriving rows at most)
+    // rows a layer completes in one push at most, and in one launch of the staged mode
     std::vector<int> launch_cap(n, 0);
+    L.launch_rows = std::min(max_seg, fit.launch_rows);
     {
-        int cap = max_seg, lcap = std::min(max_seg, kRowLaunchRows);
+        int cap = max_seg, lcap = L.launch_rows;
         for (int l = 0; l < n; ++l) {
             L.transit_cap[l] = cap = std::max(1, max_emit(net.g[l], cap));
             launch_cap[l] = lcap = std::max(1, max_emit(net.g[l], lcap));
         }
     }
-    L.cascade1d = cascade1d_eligible(net.precision, net.g.data(), n, max_seg);
-    const bool all_mfma = net_all_mfma(net);
-    L.gather = L.cascade1d || (!by_kind && gather_net(net, B, max_seg));
-    L.mfma = L.gather ? std::vector<int>(n, 0) : mfma_layers(net);
+    L.cascade1d = !fit.plain && cascade1d_eligible(net.precision, net.g.data(), n, max_seg);
+    L.gather = L.cascade1d || (!fit.by_kind && gather_net(net, B, max_seg));
+    L.mfma = L.gather || fit.plain ? std::vector<int>(n, 0) : mfma_layers(net);
+    const bool staged_rows = !fit.plain && net_all_mfma(net) && !strict_rows();
+    L.staged = L.gather || staged_rows;
     for (int l = 0; l < n; ++l) {
         if (net.g[l].kind != IDF_CONV) continue;
         L.w_off[l] = off; off = align_up(off + net.w_img[l].size());
@@ -323,7 +337,6 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     }
     L.sizes.weights_bytes = off;
     size_t state_per_stream = 0, transit_per_stream = 0, handover_per_stream = 0;
-    const bool staged_rows = all_mfma && !strict_rows();
     for (int l = 0; l < n; ++l) {
         const Geom &g = net.g[l];
         // The retained state of a layer is K_h rows: of c, or, on the matrix cores, of the events of its input that
@@ -342,8 +355,13 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
             u.l = l; u.pool = l + 1 < n && L.mfma[l + 1] == 2; u.lp = u.pool ? l + 1 : l; u.last = u.lp == n - 1;
             if (!u.last && L.mfma[u.lp + 1] == 1) u.next = (int)L.units.size() + 1;
             // rows arriving with a launch while the ones before them are being read, and the rows still needed
-            const int cap = l == 0 ? max_seg : L.transit_cap[l - 1], lcap = l == 0 ? std::min(max_seg, kRowLaunchRows) : launch_cap[l - 1];
+            const int cap = l == 0 ? max_seg : L.transit_cap[l - 1], lcap = l == 0 ? L.launch_rows : launch_cap[l - 1];
             u.ring_rows = l == 0 ? lcap + 6 : std::max(2 * lcap + 4, cap + 4);
+            // Layers side by side wait for room in the ring behind them: the fewest rows are the four of a pair's windows and, where
+            // rows come in pairs, one more (three may wait for the fourth).  Layer by layer all rows of a push have to fit, behind the
+            // two or (a pair in front of a pool not being complete) three still needed.
+            if (l > 0 && staged_rows && fit.launch_rows < kRowLaunchRows) u.ring_rows = 2 * lcap + 4;
+            if (fit.tight) u.ring_rows = l == 0 ? 4 : staged_rows ? 5 : cap + (u.pool ? 3 : 2);
             u.ring_stride = (int64_t)u.ring_rows * g.w_in * g.c_in;
             u.ring_off = off; off = align_up(off + (size_t)u.ring_stride * eb * B);
             if (l > 0) {
@@ -376,7 +394,7 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     L.head_off = off; off = align_up(off + (size_t)B * net.out_c * 2 * sizeof(double));   // sums, means
     if (L.gather) {
         // every layer's input lies in a ring, with room (1-D) for the rows of up to kGatherSegs pushes, where they are held back
-        int big = L.cascade1d ? std::min(kGatherSegs * max_seg, kBatchRows) : max_seg, small = max_seg;
+        int big = L.batch_rows = L.cascade1d ? std::min(fit.batch * max_seg, kBatchRows) : max_seg, small = max_seg;
         for (int l = 0; l < n; ++l) {
             const Geom &g = net.g[l];
             RowUnit u;
@@ -402,6 +420,19 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     L.sizes.transit_bytes_per_stream = transit_per_stream;
     L.sizes.output_bytes_per_stream = (size_t)L.out_stride * 4;
     L.sizes.out_w = net.out_w; L.sizes.out_c = net.out_c; L.sizes.out_h = net.out_h;
+    return IDF_OK;
+}
+
+// The fastest layout that `bytes` hold; `need`: what one takes (the smallest, where none fits).
+int fit_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, size_t bytes, Layout &L, size_t &need)
+{
+    need = SIZE_MAX;
+    for (const Fit &fit : kFits) {
+        int rc = make_layout(net, B, max_seg, out_cap, L, fit);
+        if (rc != IDF_OK) return rc;
+        need = std::min(need, L.total);
+        if (L.total <= bytes) break;
+    }
     return IDF_OK;
 }
 
@@ -694,7 +725,7 @@ int row_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *dev_ro
     for (int guard = 0;; ++guard) {
         double bytes = 0;
         RowProg q = p;                             // (p moves on once the launch is enqueued)
-        const int n_new = dev_rows ? (int)std::min<int64_t>({n_rows - done, kRowLaunchRows, s->net->in_h - p.in[0] % s->net->in_h}) : 0;
+        const int n_new = dev_rows ? (int)std::min<int64_t>({n_rows - done, s->launch_rows, s->net->in_h - p.in[0] % s->net->in_h}) : 0;
         if (dev_rows && done == n_rows) return IDF_OK;
         bool go = row_plan(s, q, sel.n, dev_rows, done, n_rows, n_new, !dev_rows, b, bytes);
         const bool took = go && n_new > 0;
@@ -839,7 +870,7 @@ int gather_flush(idf_streams *s)
 void gather_rings(idf_streams *s, int k)
 {
     for (const RowProg &p : s->prog) if ((s->prog_same ? s->prog_all : p).in[0] > 0) return;
-    int rows = s->batch_rows = std::min(k * s->max_seg, kBatchRows);
+    int rows = s->batch_rows = std::min(k * s->max_seg, s->batch_room);
     for (RowUnit &u : s->units) {
         const Geom &g = s->net->g[u.l];
         u.ring_rows = std::min(u.ring_room, 2 * rows + g.k_h + g.s_h);
@@ -1768,9 +1799,10 @@ int idf_open_streams(idf_net *net, int n_streams, int max_seg_rows, int64_t out_
     if (n_streams < 1 || max_seg_rows < 1) return fail(IDF_EINVAL, "n_streams and max_seg_rows must be >= 1");
     if (((uintptr_t)dev_workspace & 255) != 0) return fail(IDF_EINVAL, "workspace must be 256-byte aligned");
     Layout L;
-    int rc = make_layout(*net, n_streams, max_seg_rows, out_cap_rows, L);
+    size_t need = 0;
+    int rc = fit_layout(*net, n_streams, max_seg_rows, out_cap_rows, workspace_bytes, L, need);
     if (rc != IDF_OK) return rc;
-    if (workspace_bytes < L.total) return fail(IDF_EINVAL, "workspace of %zu bytes, %zu needed", workspace_bytes, L.total);
+    if (workspace_bytes < need) return fail(IDF_EINVAL, "workspace of %zu bytes, %zu needed", workspace_bytes, need);
     return open_on(net, n_streams, max_seg_rows, out_cap_rows, L, dev_workspace, workspace_bytes, hip_stream, out);
 }
 
@@ -1781,15 +1813,12 @@ int idf_open_streams_static(idf_net *net, int n_streams, int max_seg_rows, int64
     *out = nullptr;
     if (n_streams < 1 || max_seg_rows < 1) return fail(IDF_EINVAL, "n_streams and max_seg_rows must be >= 1");
     Layout L;
-    int rc = make_layout(*net, n_streams, max_seg_rows, out_cap_rows, L);
-    if (rc == IDF_OK && L.total > kStaticScratchBytes && L.gather && !L.cascade1d) {
-        L = Layout{};
-        rc = make_layout(*net, n_streams, max_seg_rows, out_cap_rows, L, true);
-    }
+    size_t need = 0;
+    int rc = fit_layout(*net, n_streams, max_seg_rows, out_cap_rows, kStaticScratchBytes, L, need);
     if (rc != IDF_OK) return rc;
-    if (L.total > kStaticScratchBytes)
+    if (need > kStaticScratchBytes)
         return fail(IDF_ENOMEM, "these streams need a workspace of %zu bytes, the static one holds %zu: fewer streams, "
-                                "or idf_open_streams with a workspace of the caller's", L.total, kStaticScratchBytes);
+                                "or idf_open_streams with a workspace of the caller's", need, kStaticScratchBytes);
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return dev_fail(e, "hipGetDevice");
@@ -1863,7 +1892,7 @@ int open_on(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
     s->mfma = L.mfma; s->units = L.units;
     s->unit_of.assign(net->g.size(), -1);
     for (size_t k = 0; k < s->units.size(); ++k) s->unit_of[s->units[k].l] = (int)k;
-    s->stg2d = L.gather || (!strict_rows() && net_all_mfma(*net));
+    s->stg2d = L.staged; s->launch_rows = L.launch_rows; s->batch_room = L.batch_rows;
     if (s->stg2d) s->prog.assign(n_streams, RowProg{});
     if (L.gather) {
         s->batch_rows = max_seg_rows;
@@ -2051,7 +2080,7 @@ int idf_push_pixels(idf_streams *s, const int32_t *stream_ids, int n_ids, const 
         return rc;
     }
     // layer 0 takes the columns into its rolling buffer; nothing can be final yet
-    if (s->use_gather) {
+    if (s->stg2d) {
         // the row that is begun needs a slot nobody reads any more
         bool room = true;
         for (const RowProg &q : s->prog) {

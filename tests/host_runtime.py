@@ -55,6 +55,14 @@ class Streams:
         self.check(self.L.idf_push_segment(self.h, None if a is None else a.ctypes.data, self.n if a is None else len(a),
                                            C.c_void_p(1 << 50), n_rows))
 
+    def push_pixels(self, x0, n, ids):
+        import numpy as np
+        a = np.ascontiguousarray(ids, dtype=np.int32)
+        self.check(self.L.idf_push_pixels(self.h, a.ctypes.data, len(a), C.c_void_p(1 << 50), x0, n))
+
+    def stats(self, i):
+        self.check(self.L.idf_get_stats(self.h, i, None, None, None))
+
     def read(self, max_rows):
         import numpy as np
         first, cnt = np.zeros(self.n, np.int64), np.zeros(self.n, np.int32)

@@ -130,3 +130,77 @@ def long_push(rt, kind, net_args, seg):
 ])
 def test_long_pushes_are_several_launches(runtime, kind, net_args, seg):
     host_runtime.run(runtime, "test_host_schedule", "long_push", kind, net_args, seg)
+
+
+# ---- workspaces that do not hold the fastest layout ----------------------------------------------------------------
+def small_workspace(rt, kind, net_args, streams, seg):
+    """From the workspace of idf_query_sizes down to the smallest that is accepted: every row still goes where it should."""
+    import random
+    from paper_1804_10727_amd import IdfError
+    h, w = net_args[1], net_args[2]
+    net = (chain if kind == "chain" else mixed)(*net_args)
+    size = net.query_sizes(streams, seg).workspace_bytes
+    opened = 0
+    while True:
+        try:
+            st = host_runtime.Streams(net, streams, seg, workspace_bytes=size)
+        except IdfError as e:
+            assert e.code == -1
+            break
+        opened += 1
+        for way in ("together", "apart", "pixels"):
+            rng = random.Random(way)
+            rt.host_begin()
+            st.check(st.L.idf_reset_streams(st.h, None, streams))
+            rows = [0] * streams                       # of two samples, one after the other
+            while min(rows) < 2 * h:
+                ids = list(range(streams)) if way == "together" else [rng.choice([i for i in range(streams) if rows[i] < 2 * h])]
+                n = min(rng.randint(1, seg), h - rows[ids[0]] % h)
+                if way == "pixels" and n == 1:
+                    cut = rng.randint(1, w - 1)
+                    st.push_pixels(0, cut, ids)
+                    st.push_pixels(cut, w - cut, ids)
+                else:
+                    st.push(n, ids)
+                for i in ids:
+                    rows[i] += n
+                if rng.random() < 0.1:
+                    st.stats(0)
+                if rows[ids[0]] % h == 0 or rng.random() < 0.1:
+                    st.read(h)
+            assert rt.host_error() == b"", (way, size, opened, rt.host_error())
+        st.close()
+        size -= max(256, size // 20)
+    assert opened >= 2
+    net.destroy()
+
+
+@pytest.mark.parametrize("kind,net_args,streams,seg", [
+    ("chain", ("f32", 32, 32, [3, 32, 32, 64, 64], (1,)), 3, 8),
+    ("chain", ("f32", 31, 32, [3, 32, 32, 64, 64], (1,)), 2, 16),
+    ("chain", ("bf16", 45, 33, [3, 64, 64, 128, 128, 64], (0, 2)), 2, 16),
+    ("chain", ("bf16", 38, 40, [64, 16, 64, 16], ()), 2, 1),
+    ("chain", ("i8", 50, 48, [1, 16, 16, 32, 32, 64, 64, 64, 64], (1, 3, 5)), 2, 20),
+    ("chain", ("f32", 43, 20, [3, 16, 16], (0, 1)), 2, 5),
+    ("mixed", ("f32", 33, 32, [3, 32, 64, 16], (0,)), 2, 8),
+    ("mixed", ("bf16", 34, 32, [8, 64, 32, 64], (1,), False), 2, 16),
+])
+def test_small_workspaces_hold_the_same_schedule(runtime, kind, net_args, streams, seg):
+    host_runtime.run(runtime, "test_host_schedule", "small_workspace", kind, net_args, streams, seg)
+
+
+def capacity(rt):
+    """Streams of a net whose layers keep rows of c and the rows of one push (four bytes and an event each) within the library's
+    own workspace: as many of them open as did when that was what layers kept."""
+    for net_args, seg, streams in [(("f32", 32, 32, [3, 32, 32, 64, 64], (1,)), 8, 160), (("f32", 32, 32, [3, 32, 32, 64, 64], (1,)), 16, 132),
+                                   (("f32", 48, 47, [3, 32, 32, 64, 64], (1,)), 8, 95), (("f32", 48, 47, [3, 32, 32, 64, 64], (1,)), 16, 80),
+                                   (("bf16", 112, 112, [3, 64, 64, 128, 128, 256, 256, 256], (1, 3)), 16, 12),
+                                   (("f32", 64, 64, [64, 16], ()), 1, 121)]:
+        net = chain(*net_args)
+        st = host_runtime.Streams(net, streams, seg, static=True)
+        st.close()
+        net.destroy()
+
+
+def test_as_many_streams_as_before_open_in_the_static_workspace(runtime):
+    host_runtime.run(runtime, "test_host_schedule", "capacity")

@@ -68,3 +68,35 @@ def test_static_workspace_refusals():
         idf.Streams(netb, 64, static_workspace=True)
     assert e.value.code == binding.IDF_ENOMEM and "static" in str(e.value)
     netb.destroy()
+
+
+@pytest.mark.parametrize("wl,seg,kernel", [
+    (wl_mod.make(3, streams=160, size=32), 8, "conv3x3_mfma"),           # fewer rows per launch
+    (wl_mod.make(3, streams=132, size=32), 16, "conv3x3_mfma"),
+    (wl_mod.make(5, streams=12, size=112), 16, "conv3x3_mfma"),
+    (dict(wl_mod.make(3, streams=121, size=64, channels=(16, 16, 16, 16)), narrow=True), 2, "conv_generic"),       # rows of c only
+])
+def test_streams_whose_fastest_layout_does_not_fit(wl, seg, kernel):
+    import torch
+    import paper_1804_10727_amd as idf
+    if wl.pop("narrow", False):                             # 64 channels to 16: rows of events are larger than rows of c
+        from workloads import conv
+        rng = np.random.default_rng(1)
+        x = rng.random((121, 64, 64, 64), dtype=np.float32)
+        x[rng.random(x.shape[:3]) < 0.5] = 0
+        wl = dict(wl, in_c=64, layers=[conv(64, 16, 3, 3, p_h=1, p_w=1)], biases=[None], x=x,
+                  weights=[rng.normal(0, 0.06, size=(16, 64, 3, 3)).astype(np.float32)])
+    net = idf.net_from_workload(wl)
+    assert net.query_sizes(wl["streams"], seg, 0).workspace_bytes > (32 << 20)
+    st = idf.Streams(net, wl["streams"], max_seg_rows=seg, static_workspace=True)
+    assert st.layer_kernels()[0] == kernel, st.layer_kernels()
+    st.close(); net.destroy()
+    want, want_stats = run(wl, seg, static=False)
+    got, got_stats = run(wl, seg, static=True)
+    if kernel == "conv3x3_mfma":                            # the same kernel: identical bits
+        assert np.array_equal(got, want)
+        for a, b in zip(got_stats, want_stats):
+            assert np.array_equal(a["events_in"], b["events_in"]) and np.array_equal(a["macs"], b["macs"])
+    else:
+        from helpers import TOL, rel_err
+        assert rel_err(got, want.astype(np.float64)) <= TOL["f32"]
