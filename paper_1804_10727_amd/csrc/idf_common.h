@@ -259,6 +259,18 @@ template <int NS> struct GatherBatch {
     GatherStep st[NS];
 };
 
+// The rings of a 1-D net are laid out anew, for other numbers of rows: the newest rows of streams [first, first + n) move.
+struct RingMove {
+    int first, n;
+    int n_units;
+    struct Unit {
+        void *ring;
+        int row_cells;           // 16-byte cells of a row
+        int keep;                // rows that move
+        int from_slot, from_rows, to_slot, to_rows;            // slot of the first of them, rows of the ring
+    } unit[kGatherMax - 1];
+};
+
 // Eager emission of a segment through a whole net in one launch (k_eager_pass.hip): its layers in order.
 constexpr int kPassMax = 16;     // conv layers at most
 constexpr int kPassGroups = 4;   // groups of four rows of a layer that a band reaches at most

@@ -88,6 +88,8 @@ size_t conv_gather_pack(int prec, const Geom &g, const void *w_khkwcico, void *o
 // chain: the steps one after the other (a workgroup per stream), else all side by side.
 hipError_t launch_conv_gather(int prec, const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc);
 
+hipError_t launch_ring_move(const RingMove &a, const LaunchCtx &lc);
+
 // Plain kernels that show what the machine delivers (copy, multiply-add chains, matrix-instruction
 // chains): bytes the compute kinds write for a launch of `blocks` workgroups, operations such a
 // launch performs, and the launch itself (copy: first half of buf to the second half).

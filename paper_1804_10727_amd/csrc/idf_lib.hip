@@ -866,21 +866,55 @@ int gather_flush(idf_streams *s)
     return rc;
 }
 
-// How many rows of the rings are in use: as many as k pushes per launch need.  Only while no row lies in them.
-void gather_rings(idf_streams *s, int k)
+// How many rows of the rings are in use: as many as k pushes per launch need.  Nothing is on its way: of a layer's rows at most the
+// K_h newest are still needed, and they move to where the rings then have them.
+int gather_rings(idf_streams *s, int k)
 {
-    for (const RowProg &p : s->prog) if ((s->prog_same ? s->prog_all : p).in[0] > 0) return;
-    int rows = s->batch_rows = std::min(k * s->max_seg, s->batch_room);
-    for (RowUnit &u : s->units) {
-        const Geom &g = s->net->g[u.l];
-        u.ring_rows = std::min(u.ring_room, 2 * rows + g.k_h + g.s_h);
-        u.ring_stride = (int64_t)u.ring_rows * u.row_elems;        // (close together: a few pages hold the rings of all streams)
+    const int nu = (int)s->units.size(), eb = ev_bytes(s->net->precision);
+    int rows = std::min(k * s->max_seg, s->batch_room);
+    if (rows == s->batch_rows) return IDF_OK;
+    const int batch_rows = rows;
+    std::vector<int> ring_rows(nu);
+    for (int i = 0; i < nu; ++i) {
+        const Geom &g = s->net->g[s->units[i].l];
+        ring_rows[i] = std::min(s->units[i].ring_room, gather_ring(g, rows));
         rows = std::max(1, max_emit(g, rows));
     }
-    for (size_t k = 0; k < s->units.size(); ++k) {
-        s->gather[k].ring_stride = s->units[k].ring_stride;
-        if (!s->units[k].last) s->gather[k].dst_stride = s->units[k + 1].ring_stride;
+    auto prog = [&](int id) -> const RowProg & { return s->prog_same ? s->prog_all : s->prog[id]; };
+    auto move = [&](int first, int n) {
+        const RowProg &p = prog(first);
+        RingMove a{};
+        a.first = first; a.n = n; a.n_units = nu;
+        for (int i = 0; i < nu; ++i) {
+            const RowUnit &u = s->units[i];
+            RingMove::Unit &v = a.unit[i];
+            v.ring = s->ws + u.ring_off; v.row_cells = u.row_elems * eb / 16;
+            v.keep = (int)std::min<int64_t>(p.in[i], s->net->g[u.l].k_h);
+            v.from_rows = u.ring_rows; v.to_rows = ring_rows[i];
+            v.from_slot = mod_rows(p.in[i] - v.keep, v.from_rows); v.to_slot = mod_rows(p.in[i] - v.keep, v.to_rows);
+        }
+        hipError_t e = p.in[0] == 0 ? hipSuccess : launch_ring_move(a, launch_ctx(s, kKindCascade1d, 0));
+        return e == hipSuccess ? (int)IDF_OK : dev_fail(e, "ring launch");
+    };
+    // streams that stand at the same place together, from the side the rings grow to (every ring grows, or none does)
+    const bool grow = batch_rows > s->batch_rows;
+    for (int done = 0; done < s->B;) {
+        const int last = grow ? s->B - 1 - done : done;
+        int n = 1;
+        while (done + n < s->B && (s->prog_same || prog(grow ? last - n : last + n).same(prog(last), nu))) ++n;
+        int rc = move(grow ? last - n + 1 : last, n);
+        if (rc != IDF_OK) return rc;
+        done += n;
     }
+    s->batch_rows = batch_rows;
+    for (int i = 0; i < nu; ++i) {
+        RowUnit &u = s->units[i];
+        u.ring_rows = ring_rows[i];
+        u.ring_stride = (int64_t)u.ring_rows * u.row_elems;        // (close together: a few pages hold the rings of all streams)
+        s->gather[i].ring_stride = u.ring_stride;
+        if (i > 0) s->gather[i - 1].dst_stride = u.ring_stride;
+    }
+    return IDF_OK;
 }
 
 void prog_split(idf_streams *s)
@@ -2285,8 +2319,9 @@ int idf_set_push_batching(idf_streams *s, int k)
     if (s->eager.on) return fail(IDF_EUNSUPPORTED, "eager emission delivers every segment at once");
     int rc = pipeline_drain(s);                  // what is held back was pushed under the old setting
     if (rc != IDF_OK) return rc;
+    rc = gather_rings(s, k);
+    if (rc != IDF_OK) return rc;
     s->batch = k;
-    gather_rings(s, k);
     return IDF_OK;
 }
 

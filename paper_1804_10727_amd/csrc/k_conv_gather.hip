@@ -412,6 +412,26 @@ __global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherB
     }
 }
 
+// A workgroup per layer, stream by stream: a stream's new place may lie on what streams on one side of it held, so they go from that
+// side, and a stream's rows are all read before one is written.
+constexpr int kMoveThreads = 256;
+__global__ void __launch_bounds__(kMoveThreads) k_ring_move(const RingMove a)
+{
+    const RingMove::Unit &u = a.unit[blockIdx.x];
+    const int t = threadIdx.x, r = t / u.row_cells, c = t - r * u.row_cells;
+    const bool mine = r < u.keep;
+    const int64_t from = (int64_t)u.from_rows * u.row_cells, to = (int64_t)u.to_rows * u.row_cells;
+    const int64_t src = (int64_t)((u.from_slot + r) % u.from_rows) * u.row_cells + c, dst = (int64_t)((u.to_slot + r) % u.to_rows) * u.row_cells + c;
+    i32x4 *ring = (i32x4 *)u.ring, v = {0, 0, 0, 0};
+    for (int i = 0; i < a.n; ++i) {
+        const int64_t stream = a.first + (to > from ? a.n - 1 - i : i);
+        if (mine) v = ring[stream * from + src];
+        __syncthreads();
+        if (mine) ring[stream * to + dst] = v;
+        __syncthreads();
+    }
+}
+
 // Positions of a step's tiles that belong to one stream.
 int streams_per_tile_log(int positions, bool first)
 {
@@ -549,6 +569,13 @@ size_t conv_gather_pack(int prec, const Geom &g, const void *w_khkwcico, void *o
                        src + (((size_t)tap * g.c_in + ci) * g.c_out + co) * eb, eb);
         }
     return bytes;
+}
+
+hipError_t launch_ring_move(const RingMove &a, const LaunchCtx &lc)
+{
+    for (int k = 0; k < a.n_units; ++k)
+        if (a.unit[k].keep * a.unit[k].row_cells > kMoveThreads) return hipErrorInvalidValue;      // (cascade1d_eligible: at most 9 rows of 16 cells)
+    return launch(k_ring_move, dim3(a.n_units), dim3(kMoveThreads), 0, lc, a);
 }
 
 hipError_t launch_conv_gather(int prec, const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc)

@@ -282,3 +282,55 @@ def test_single_stream_one_sample_per_push_held_back():
     outs, _ = _run(wl, 1, reads_at={0, 1, 2, 3, 10, 11, 100}, batch=16)
     check_stream(wl, outs[0], 0)
     assert _same_up_to_association(outs[0], ref[0])
+
+
+@pytest.mark.parametrize("bounded", [True, False])
+@pytest.mark.parametrize("streams,length,seg,channels", [(5, 700, 16, (8, 8, 16, 16, 32, 64)), (37, 400, 3, (32, 32, 64, 64, 64, 64)), (1, 300, 1, (8, 7, 5, 16, 16, 16))])
+def test_batching_switched_while_rows_are_in(streams, length, seg, channels, bounded):
+    """Held-back pushes may be switched on, off and over at any time: every value is that of a launch per push, bit for bit, with
+    streams in step and apart when the rings are laid out anew."""
+    import torch
+    import paper_1804_10727_amd as idf
+    from paper_1804_10727_amd.binding import input_tensor
+    wl = wl_mod.make(2, streams=streams, length=length, channels=channels)
+    net = idf.Net("f32", length if bounded else 0, 1, 1, wl["layers"], wl["weights"], wl["biases"])
+    x = input_tensor(wl)
+    segs = [x[:, r:r + seg].contiguous() for r in range(0, length, seg)]
+    samples = 2 if bounded else 1
+    outs = []
+    for switch in (False, True):
+        st = idf.Streams(net, streams, max_seg_rows=seg, out_cap_rows=0 if bounded else length)
+        rng = np.random.default_rng(11)
+        got = [[] for _ in range(streams)]
+
+        def read():
+            out, _, n = st.read_outputs(length)
+            for b in range(streams):
+                got[b].append(out[b, :n[b]].clone())
+        for _ in range(samples):
+            for i, rows in enumerate(segs):
+                if switch and i % 5 == 2:
+                    st.set_push_batching(int(rng.choice([1, 2, 7, 16])))
+                if streams > 1 and i % 11 in (4, 5):                  # apart for a while: stream 1 first, then the others
+                    if i % 11 == 4:
+                        first = [(rows[1:2].contiguous()), (segs[i + 1][1:2].contiguous() if i + 1 < len(segs) else None)]
+                        st.push_segment(first[0], stream_ids=np.array([1], np.int32))
+                        if first[1] is not None:
+                            st.push_segment(first[1], stream_ids=np.array([1], np.int32))
+                        if switch:
+                            st.set_push_batching(3)
+                    ids = np.array([b for b in range(streams) if b != 1], np.int32)
+                    st.push_segment(rows[torch.from_numpy(ids).long().cuda()].contiguous(), stream_ids=ids)
+                else:
+                    st.push_segment(rows)
+                if i % 13 == 7:
+                    read()
+            read()
+        outs.append([torch.cat(g) for g in got])
+        st.close()
+    net.destroy()
+    for b in range(streams):
+        assert outs[0][b].shape == outs[1][b].shape and torch.equal(outs[0][b], outs[1][b]), b
+        if bounded:
+            n = outs[0][b].shape[0] // 2
+            check_stream(wl, outs[1][b][:n].cpu().numpy(), b)

@@ -204,3 +204,24 @@ def capacity(rt):
 
 def test_as_many_streams_as_before_open_in_the_static_workspace(runtime):
     host_runtime.run(runtime, "test_host_schedule", "capacity")
+
+
+# ---- held-back pushes ------------------------------------------------------------------------------------------------
+def batching(rt, when):
+    from workloads import make
+    import paper_1804_10727_amd as idf
+    net = idf.net_from_workload(make(2, streams=4, length=1600))
+    st = host_runtime.Streams(net, 4, 16)
+    for _ in range(when):
+        st.push(16)
+    st.check(st.L.idf_set_push_batching(st.h, 16))
+    rt.host_begin()
+    for _ in range(32):
+        st.push(16)
+    assert rt.host_launches(b"k_conv_gather") == 2, rt.host_launches(b"k_conv_gather")
+    st.close()
+
+
+@pytest.mark.parametrize("when", [0, 1, 20])
+def test_pushes_are_held_back_from_whenever_it_is_asked_for(runtime, when):
+    host_runtime.run(runtime, "test_host_schedule", "batching", when)
