@@ -267,6 +267,19 @@ bool net_all_mfma(const idf_net &net)
     return units >= 1 && units <= kRowUnits;
 }
 
+// No weight is infinite or NaN.
+template <class U> bool all_finite(const std::vector<unsigned char> &img, U exponent)
+{
+    unsigned bad = 0;
+    U w[4096 / sizeof(U)];           // (of its own type and without an exit: the compiler makes vector instructions of the inner loop)
+    for (size_t at = 0; at < img.size(); at += sizeof(w)) {
+        const size_t n = std::min(sizeof(w), img.size() - at);
+        memcpy(w, &img[at], n);
+        for (size_t i = 0; i < n / sizeof(U); ++i) bad += (w[i] & exponent) == exponent;
+    }
+    return bad == 0;
+}
+
 // Which layers run on the matrix-core kernel: 1 = a convolution, 2 = a pool fused into the one before it.
 std::vector<int> mfma_layers(const idf_net &net)
 {
@@ -1687,13 +1700,6 @@ int idf_create_net(const idf_net_desc *d, const void *const *weights, const void
                 size_t d_idx = (((size_t)ky * L.k_w + kx) * L.c_in + ci) * L.c_out + co;
                 memcpy(&img[d_idx * wb], src + s_idx * wb, wb);
             }
-            auto not_finite = [&](size_t i) {
-                if (wb == 1) return false;
-                uint32_t v = 0;
-                memcpy((unsigned char *)&v + 4 - wb, &img[i * wb], wb);
-                return (v & 0x7f800000u) == 0x7f800000u;
-            };
-            for (size_t i = 0; i * wb < img.size() && net->finite; ++i) net->finite = !not_finite(i);
             if (conv3x3_mfma_eligible(d->precision, g)) {
                 net->wm_img.back().resize(conv3x3_mfma_pack(d->precision, g, nullptr, nullptr));
                 conv3x3_mfma_pack(d->precision, g, img.data(), net->wm_img.back().data());
@@ -1707,6 +1713,10 @@ int idf_create_net(const idf_net_desc *d, const void *const *weights, const void
     }
     if (rc != IDF_OK) { delete net; return rc; }
     net->out_h = h; net->out_w = w; net->out_c = c;
+    // (asked for by gather_net alone, which nets served throughout by the 3x3 kernel never come to)
+    if (net->wm_img[0].empty() && !net_all_mfma(*net))
+        for (const auto &img : net->w_img)
+            net->finite = net->finite && (d->precision == IDF_PREC_I8 || (d->precision == IDF_PREC_F32 ? all_finite<uint32_t>(img, 0x7f800000u) : all_finite<uint16_t>(img, 0x7f80u)));
     *out = net;
     return IDF_OK;
 }

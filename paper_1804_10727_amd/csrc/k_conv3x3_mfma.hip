@@ -30,6 +30,7 @@
 #include "mfma_tile.h"
 #include <algorithm>
 #include <cstddef>
+#include <cstring>
 #include <type_traits>
 
 namespace idf {
@@ -731,7 +732,7 @@ size_t conv3x3_mfma_pack(int prec, const Geom &g, const void *w_khkwcico, void *
     if (!out) return bytes;
     unsigned char *o = (unsigned char *)out;
     const unsigned char *src = (const unsigned char *)w_khkwcico;
-    for (size_t i = 0; i < bytes; ++i) o[i] = 0;
+    memset(o, 0, bytes);
     const int cells = g.c_in % vl == 0 && g.c_in >= vl ? g.c_in / vl : 0;
     for (int ky = 0; ky < 3; ++ky)
         for (int kx = 0; kx < 3; ++kx)
@@ -753,7 +754,9 @@ size_t conv3x3_mfma_pack(int prec, const Geom &g, const void *w_khkwcico, void *
                         const int in = co % 32, t = in % 8 / 4, m = in / 8 * 4 + in % 4;
                         d = step * per_step + (size_t)(co / 32) * 6144 + (size_t)(ky * 2 + t) * 1024 + (size_t)(grp * 16 + m) * 16;
                     }
-                    for (int b = 0; b < eb; ++b) o[d + (size_t)elem * eb + b] = src[s_idx * eb + b];
+                    if (eb == 4) memcpy(o + d + (size_t)elem * 4, src + s_idx * 4, 4);
+                    else if (eb == 2) memcpy(o + d + (size_t)elem * 2, src + s_idx * 2, 2);
+                    else o[d + (size_t)elem] = src[s_idx];
                     if (prec == IDF_PREC_I8) o[frag_bytes + (((size_t)kx * g.c_in + ci) * cop + co) * 4 + ky] = src[s_idx];
                 }
             }

@@ -225,3 +225,26 @@ def batching(rt, when):
 @pytest.mark.parametrize("when", [0, 1, 20])
 def test_pushes_are_held_back_from_whenever_it_is_asked_for(runtime, when):
     host_runtime.run(runtime, "test_host_schedule", "batching", when)
+
+
+# ---- which kernels serve a net -----------------------------------------------------------------------------------------
+def finite_weights(rt):
+    """A net of several kinds of layers goes through the gathering kernel, which multiplies zeros, if all its weights are finite."""
+    import paper_1804_10727_amd as idf
+    from workloads import conv
+    layers = [conv(3, 32, 5, 5, p_h=2, p_w=2), conv(32, 33, 3, 3, p_h=1, p_w=1)]
+    for prec, bad in (("f32", [np.inf, -np.inf, np.nan]), ("bf16", [0x7F80, 0xFF80, 0x7FC1, 0xFF81])):
+        dt = np.float32 if prec == "f32" else np.uint16
+        largest = np.finfo(np.float32).max if prec == "f32" else 0x7F7F
+        for value, at in [(largest, 0)] + [(v, i) for v in bad for i in (0, 1, 9503)]:
+            w = [np.full((L["c_out"], L["c_in"], L["k_h"], L["k_w"]), 1, dt) for L in layers]
+            w[1].reshape(-1)[at] = value
+            net = idf.Net(prec, 32, 32, 3, layers, w)
+            st = host_runtime.Streams(net, 2)
+            assert st.L.idf_layer_kernel(st.h, 1) == (b"conv_gather" if value == largest else b"conv_generic"), (prec, value, at)
+            st.close()
+            net.destroy()
+
+
+def test_infinite_weights_stay_off_the_gathering_kernel(runtime):
+    host_runtime.run(runtime, "test_host_schedule", "finite_weights")
