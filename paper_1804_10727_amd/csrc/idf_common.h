@@ -275,7 +275,7 @@ struct RingMove {
 constexpr int kPassMax = 16;     // conv layers at most
 constexpr int kPassGroups = 4;   // groups of four rows of a layer that a band reaches at most
 struct EagerPassStep {           // a conv layer and the 2x2 pool behind it, if there is one
-    int layer, n_layers;
+    int layer;
     int n_in;                    // delta rows that arrive
     int row0, n_groups;          // first row of the first group; groups
     int band0;                   // row row0 - 1, counted from the band's first
@@ -287,13 +287,14 @@ struct EagerPassStep {           // a conv layer and the 2x2 pool behind it, if 
     int out_first;               // place of row row0 (pool: of row row0 / 2) among the rows passed on (may be negative)
     int pool, out_w;             // out_w: positions of the rows passed on
     uint32_t pool_on;            // bit i: pooled row row0 / 2 + i is looked at
-    uint32_t c_off[4 * kPassGroups], pool_off[2 * kPassGroups];   // bytes from a stream's first row kept to the one that holds each row
-    int64_t c_stride, ann_stride, pool_ann_stride;     // elements per stream
-    void *c, *ann, *pool_ann;    // ann: kept whole, or null: whoever wants them takes f of the state
+    uint32_t c_off[4 * kPassGroups];           // bytes from a stream's first row kept to the one that holds each row
+    uint32_t pool_slots[kPassGroups];          // of the pooled rows, two to a word: among those kept, the one that holds each row
+    uint32_t c_stride, ann_stride;             // elements per stream
+    int n_ksteps;                // (set with the layout, as all that stands behind the pointers)
+    void *c, *ann;               // ann: of the pool; else of a level that is kept whole, or null: whoever wants them takes f of the state
     const void *w_frag;
-    // set with the layout
     unsigned ct_rcp, xt_rcp;
-    int n_xt, n_ct, cells, win_cells, n_ksteps;
+    int n_xt, n_ct, cells;
     int lds_in, lds_out, in_pitch, in_stride, out_pitch, out_stride, out_rows;
 };
 struct EagerPass {
@@ -306,6 +307,7 @@ struct EagerPass {
     unsigned long long *stats;
     EagerPassStep st[kPassMax];
 };
+static_assert(sizeof(EagerPass) + sizeof(StreamSel) <= 4096 && sizeof(GatherBatch<kGatherMax>) + sizeof(StreamSel) <= 4096, "likewise");
 
 // Averaging output units: rows [first_slot, first_slot + n_rows) of the output ring are added to
 // the per-channel sums of each selected stream.

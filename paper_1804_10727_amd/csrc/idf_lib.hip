@@ -113,7 +113,6 @@ struct ProfRec {
 
 struct idf_streams {
     int static_dev = -1;             // >= 0: the workspace is that device's static array (given back at close)
-    int cus = 0;                     // compute units of the device the streams were opened on
     int ev_per_step = 0;             // int8 event path (idf_set_event_path): events a tile may hold per K-step of its contraction and still go that way; 0: off
     bool use_gather = false;         // the layers are units of the gathering kernel
     bool use_cascade1d = false;      // such a net, 1-D
@@ -1377,7 +1376,7 @@ bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int
         if (P.n == kPassMax) return false;
         EagerPassStep &L = P.st[P.n++];
         L = EagerPassStep{};
-        L.layer = l; L.n_layers = n;
+        L.layer = l;
         L.n_in = (int)(hi[l] - lo[l]);
         L.row0 = (int)(lo[lv] & ~(int64_t)1);              // (no window of a pool lies in two groups)
         L.n_groups = (int)((hi[lv] - L.row0 + 3) / 4);
@@ -1385,7 +1384,9 @@ bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int
         L.band0 = L.row0 - 1 - (int)lo[l];
         L.w = g.w_out; L.c_in = g.c_in; L.c_out = g.c_out; L.act = g.act; L.shr = g.shr; L.clamp_hi = g.clamp_hi;
         const uint32_t row_bytes = (uint32_t)E.row_elems[lv] * 4;
-        L.c = E.ws + E.c_off[lv]; L.c_stride = (int64_t)E.cd_rows[lv] * E.row_elems[lv];
+        // (offsets within a stream's map are 32 bits, rows of a pool's ring 16)
+        if (std::max(E.cd_rows[lv], E.ann_rows[lv]) * E.row_elems[lv] * 4 > UINT32_MAX) return false;
+        L.c = E.ws + E.c_off[lv]; L.c_stride = (uint32_t)(E.cd_rows[lv] * E.row_elems[lv]);
         for (int i = 0; i < 4 * L.n_groups + 2; ++i) {
             const int y = L.row0 + i;
             if (y - 1 >= lo[l] && y - 1 < hi[l]) L.rows_in |= 1u << i;
@@ -1395,7 +1396,7 @@ bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int
             L.c_off[i] = (uint32_t)(y % E.cd_rows[lv]) * row_bytes;
         }
         L.ann = lv < n ? nullptr : E.ws + E.ann_off[lv];
-        L.ann_stride = (int64_t)E.ann_rows[lv] * E.row_elems[lv];
+        L.ann_stride = (uint32_t)(E.ann_rows[lv] * E.row_elems[lv]);
         L.w_frag = s->ws + s->wm_off[l];
         L.out_w = g.w_out;
         L.out_first = L.row0 - (int)lo[lv];
@@ -1404,12 +1405,13 @@ bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int
         if (l < n && net.g[l].kind == IDF_MAXPOOL) {
             const int pv = l + 1;
             L.pool = 1; L.out_w = net.g[l].w_out;
+            if (E.ann_rows[pv] > 1 << 16 || E.ann_rows[pv] * E.row_elems[pv] * 4 > UINT32_MAX) return false;
             L.out_first = L.row0 / 2 - (int)lo[pv];
-            L.pool_ann = E.ws + E.ann_off[pv]; L.pool_ann_stride = (int64_t)E.ann_rows[pv] * E.row_elems[pv];
+            L.ann = E.ws + E.ann_off[pv]; L.ann_stride = (uint32_t)(E.ann_rows[pv] * E.row_elems[pv]);
             for (int i = 0; i < 2 * L.n_groups; ++i) {
                 const int o = L.row0 / 2 + i;
                 if (o >= lo[pv] && o < hi[pv]) L.pool_on |= 1u << i;
-                L.pool_off[i] = (uint32_t)(o % E.ann_rows[pv]) * (uint32_t)E.row_elems[pv] * 4;
+                L.pool_slots[i / 2] |= (uint32_t)(o % E.ann_rows[pv]) << i % 2 * 16;
             }
             bytes += (double)(hi[pv] - lo[pv]) * E.row_elems[pv] * 4.0;
             ++l;
@@ -1929,10 +1931,6 @@ int open_on(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
     s->out_off = L.out_off; s->stats_off = L.stats_off; s->issued_off = L.issued_off; s->out_stride = L.out_stride; s->sizes = L.sizes;
     s->use_gather = L.gather; s->use_cascade1d = L.cascade1d;
     s->head_off = L.head_off;
-    {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) s->cus = 0;
-    }
     s->mfma = L.mfma; s->units = L.units;
     s->unit_of.assign(net->g.size(), -1);
     for (size_t k = 0; k < s->units.size(); ++k) s->unit_of[s->units[k].l] = (int)k;

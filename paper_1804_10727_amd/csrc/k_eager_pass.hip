@@ -127,7 +127,7 @@ template <class T> struct Activation {
     }
 };
 
-template <class T> __device__ __forceinline__ void pass_conv(PassStep &L, int stream, uint32_t *events)
+template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassStep &L, int stream, uint32_t *events)
 {
     using acc_t = typename T::acc_t; using st_t = typename T::st_t;
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6), m = lane & 15, g = lane >> 4;
@@ -189,7 +189,7 @@ template <class T> __device__ __forceinline__ void pass_conv(PassStep &L, int st
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = acc_t{0, 0, 0, 0};
         {
-            const int cells = L.cells, n_ksteps = L.n_ksteps, in_stride = L.in_stride, win_cells = L.win_cells;
+            const int cells = L.cells, n_ksteps = L.n_ksteps, in_stride = L.in_stride;
             const uint32_t rows_in = L.rows_in >> (4 * gi);    // bit r: row r - 1 of the four (-1 .. 4) is in the band
             // where the six rows lie (those outside the band: somewhere inside)
             const unsigned char *row[6];
@@ -218,7 +218,7 @@ template <class T> __device__ __forceinline__ void pass_conv(PassStep &L, int st
             // gathered window
             auto at = [&](int st) IDF_INLINE {
                 int q = 4 * st + g;
-                if (cells == 0) return (uint32_t)(q < win_cells ? q : win_cells - 1) * 16;
+                if (cells == 0) return T::EB == 1 ? 0u : (uint32_t)q * 16;      // (int8: one cell)
                 if (T::EB == 1) q = q < 3 * cells ? q : 3 * cells - 1;
                 const int kx = (q >= cells) + (q >= 2 * cells);
                 return (uint32_t)(kx * in_stride + (q - kx * cells) * 16);
@@ -248,7 +248,7 @@ template <class T> __device__ __forceinline__ void pass_conv(PassStep &L, int st
             if constexpr (T::EB == 1) *reinterpret_cast<uint32_t *>(to) = e[0];
             else *reinterpret_cast<i32x4 *>(to) = i32x4{(int)e[0], (int)e[1], (int)e[2], (int)e[3]};
         };
-        char *ann = L.ann ? (char *)L.ann + ((int64_t)stream * L.ann_stride + (int64_t)(L.row0 + 4 * gi) * W * C_out) * 4 : nullptr;
+        char *ann = L.ann && !L.pool ? (char *)L.ann + ((int64_t)stream * L.ann_stride + (int64_t)(L.row0 + 4 * gi) * W * C_out) * 4 : nullptr;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             acc_t h_new, h_old = {0, 0, 0, 0};
@@ -269,7 +269,7 @@ template <class T> __device__ __forceinline__ void pass_conv(PassStep &L, int st
                     *at4(reinterpret_cast<acc_t *>((char *)c_map + c_off[j]), cell) = acc[j];
                     if (ann) *at4(reinterpret_cast<acc_t *>(ann + (int64_t)(j * W * C_out) * 4), cell) = h_new;
                 }
-                if (L.layer + 1 < L.n_layers) count(d, ev);
+                if (L.layer + 1 < a.n_layers) count(d, ev);
                 if (!L.pool && out_ok) pass_on(d, out + (4 * gi + j) * L.out_pitch + (x + 1) * L.out_stride);
             }
             // rows that have not been reached announce zero (and have nothing in acc or old)
@@ -291,7 +291,7 @@ template <class T> __device__ __forceinline__ void pass_conv(PassStep &L, int st
                     d[i] = mine ? n[i] - (oo > ox ? oo : ox) : (st_t)0;
                 }
                 count(d, ev_pool);
-                if (mine) *at4(reinterpret_cast<acc_t *>((char *)L.pool_ann + (int64_t)stream * L.pool_ann_stride * 4 + L.pool_off[2 * gi + p]),
+                if (mine) *at4(reinterpret_cast<acc_t *>((char *)L.ann + (int64_t)stream * L.ann_stride * 4 + (int64_t)((L.pool_slots[gi] >> p * 16) & 0xffffu) * (L.out_w * C_out * 4)),
                                (uint32_t)((x >> 1) * C_out + co0) * 4) = n;
                 if (L.emit && mine) pass_on(d, out + (2 * gi + p) * L.out_pitch + ((x >> 1) + 1) * L.out_stride);
             }
@@ -320,7 +320,7 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_eager_pass(const EagerPass 
 #pragma unroll 1
     for (int k = 0; k < n; ++k) {
         PassStep &L = a.st[k];
-        pass_conv<T>(L, stream, &events[L.layer + 1]);
+        pass_conv<T>(a, L, stream, &events[L.layer + 1]);
     }
     lds_barrier();
     if (tid < a.n_layers && events[tid]) atomicAdd(a.stats + ((int64_t)stream * a.n_layers + tid) * 2, (unsigned long long)events[tid]);
@@ -347,9 +347,8 @@ bool eager_pass_shape(int prec, EagerPass &a)
         L.n_ct = L.c_out == 16 ? 1 : 2 * ((L.c_out + 31) / 32);
         L.xt_rcp = rcp32(L.n_xt); L.ct_rcp = rcp32(L.n_ct);
         L.cells = L.c_in % vl == 0 ? L.c_in / vl : 0;
-        L.win_cells = L.cells ? 0 : window_cells(L.c_in, vl, eb == 4);
         L.n_ksteps = L.cells ? (3 * L.cells + 3) / 4 : 1;
-        L.in_stride = cell_stride(L.cells ? L.cells + pad_cells(eb == 4, L.cells) : L.win_cells) * 16;
+        L.in_stride = cell_stride(L.cells ? L.cells + pad_cells(eb == 4, L.cells) : window_cells(L.c_in, vl, eb == 4)) * 16;
         L.in_pitch = (16 * L.n_xt + 2) * L.in_stride;
         size[k] = (size_t)L.n_in * L.in_pitch;
         if (k > 0) { a.st[k - 1].out_stride = L.in_stride; a.st[k - 1].out_pitch = L.in_pitch; a.st[k - 1].out_rows = L.n_in; }
