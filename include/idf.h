@@ -85,9 +85,8 @@ typedef struct {
     size_t state_bytes_per_stream;   /* of which, per stream: the retained state -- the rolling rows of
                                         c of every conv layer and the held row of every pool.  This is
                                         the footprint the paper bounds; it does not depend on in_h.
-                                        Layers on the matrix cores keep K_h rows of their input, as
-                                        events, instead (in rings that count as transit): for them the
-                                        larger of the two is stated.                                 */
+                                        (Layers on the matrix cores keep rows of their input instead;
+                                        the rings they lie in count as transit.)                     */
     size_t handover_bytes_per_stream;/* of which, per stream: rows a layer has completed that may wait, when a
                                         call returns, for the next layer's step in a later call.  Only the
                                         staged modes have such rows (the default for nets served throughout

@@ -129,7 +129,6 @@ struct idf_streams {
     std::vector<int> mfma;           // per layer: 1 = matrix-core conv kernel, 2 = pool fused into the conv before it
     std::vector<int64_t> ring_stride, held_stride, transit_stride;   // elements per stream
     std::vector<int> transit_cap;                                    // rows per stream
-    std::vector<size_t> state_bytes;                                 // per layer and stream, as idf_sizes states it
     size_t out_off = 0, stats_off = 0, issued_off = 0, head_off = 0;
     bool count_issued = false;       // the kernels add up what they issue (an atomic per wave: switched on for measurements)
     bool head_on = false;
@@ -214,7 +213,6 @@ struct Layout {
     std::vector<size_t> w_off, b_off, wm_off, wg_off, ring_off, held_off, transit_off;
     std::vector<int64_t> ring_stride, held_stride, transit_stride;
     std::vector<int> transit_cap;
-    std::vector<size_t> state_bytes;
     std::vector<int> mfma;           // per layer: 1 = matrix-core conv kernel, 2 = pool fused into the conv before it
     std::vector<RowUnit> units;
     size_t out_off = 0, stats_off = 0, issued_off = 0, head_off = 0, total = 0;
@@ -326,7 +324,7 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     L.w_off.assign(n, 0); L.b_off.assign(n, 0); L.wm_off.assign(n, 0); L.wg_off.assign(n, 0);
     L.ring_off.assign(n, 0); L.held_off.assign(n, 0); L.transit_off.assign(n, 0);
     L.ring_stride.assign(n, 0); L.held_stride.assign(n, 0); L.transit_stride.assign(n, 0);
-    L.transit_cap.assign(n, 0); L.state_bytes.assign(n, 0);
+    L.transit_cap.assign(n, 0);
     // rows a layer completes in one push at most, and in one launch of the staged mode
     std::vector<int> launch_cap(n, 0);
     L.launch_rows = std::min(max_seg, fit.launch_rows);
@@ -354,19 +352,16 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
     for (int l = 0; l < n; ++l) {
         const Geom &g = net.g[l];
         // The retained state of a layer is K_h rows: of c, or, on the matrix cores, of the events of its input that
-        // some row of c has yet to take in (they lie in the ring the layer before writes them to).  What is stated is the
-        // larger of the two there: the method's bound holds, except where a layer has more input than output.
+        // some row of c has yet to take in (they lie in the ring the layer before writes them to).
         if (g.kind == IDF_CONV) {
             L.ring_stride[l] = (int64_t)g.k_h * g.w_out * g.c_out;
             if (!L.mfma[l] && !L.gather) { L.ring_off[l] = off; off = align_up(off + (size_t)L.ring_stride[l] * 4 * B); }
-            const int vl = conv3x3_mfma_vl(net.precision), c_in = L.gather ? (g.c_in + vl - 1) / vl * vl : g.c_in;
-            L.state_bytes[l] = std::max((size_t)L.ring_stride[l] * 4, L.mfma[l] || L.gather ? (size_t)g.k_h * g.w_in * c_in * eb : 0);
+            state_per_stream += (size_t)L.ring_stride[l] * 4;
         } else {
             L.held_stride[l] = (int64_t)g.w_in * g.c_out;
             if (!L.mfma[l] && !L.gather) { L.held_off[l] = off; off = align_up(off + (size_t)L.held_stride[l] * eb * B); }
-            L.state_bytes[l] = (size_t)L.held_stride[l] * eb;
+            state_per_stream += (size_t)L.held_stride[l] * eb;
         }
-        state_per_stream += L.state_bytes[l];
         if (L.mfma[l] == 1) {
             RowUnit u;
             u.l = l; u.pool = l + 1 < n && L.mfma[l + 1] == 2; u.lp = u.pool ? l + 1 : l; u.last = u.lp == n - 1;
@@ -1932,7 +1927,7 @@ int open_on(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
     s->st = (hipStream_t)hip_stream; s->ws = (char *)dev_workspace; s->ws_bytes = workspace_bytes;
     s->w_off = L.w_off; s->b_off = L.b_off; s->wm_off = L.wm_off; s->wg_off = L.wg_off; s->ring_off = L.ring_off; s->held_off = L.held_off;
     s->transit_off = L.transit_off; s->ring_stride = L.ring_stride; s->held_stride = L.held_stride;
-    s->transit_stride = L.transit_stride; s->transit_cap = L.transit_cap; s->state_bytes = L.state_bytes;
+    s->transit_stride = L.transit_stride; s->transit_cap = L.transit_cap;
     s->out_off = L.out_off; s->stats_off = L.stats_off; s->issued_off = L.issued_off; s->out_stride = L.out_stride; s->sizes = L.sizes;
     s->use_gather = L.gather; s->use_cascade1d = L.cascade1d;
     s->head_off = L.head_off;
@@ -2268,10 +2263,12 @@ int idf_get_stats(idf_streams *s, int stream_id, uint64_t *events_in, uint64_t *
         e = hipMemcpy(buf.data(), s->ws + s->stats_off + (size_t)stream_id * n * 2 * sizeof(unsigned long long),
                       buf.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return dev_fail(e, "get_stats");
+    const int eb = ev_bytes(s->net->precision);
     for (int l = 0; l < n; ++l) {
         if (events_in) events_in[l] = buf[2 * l];
         if (macs_executed) macs_executed[l] = buf[2 * l + 1];
-        if (state_bytes) state_bytes[l] = s->state_bytes[l];
+        if (state_bytes)
+            state_bytes[l] = s->net->g[l].kind == IDF_CONV ? (uint64_t)s->ring_stride[l] * 4 : (uint64_t)s->held_stride[l] * eb;
     }
     return IDF_OK;
 }

@@ -232,17 +232,3 @@ def test_volume_net_description_and_sizes():
     assert e.value.code == binding.IDF_EUNSUPPORTED
     with pytest.raises(idf.IdfError):                       # missing weights
         VolumeNet("f32", 9, 10, 8, 2, L, [w[0], None])
-
-
-def test_state_of_layers_with_more_input_than_output():
-    """Layers on the matrix cores keep K_h rows of their input as events: what is stated covers those too."""
-    net = idf.Net("f32", 32, 24, 64, [conv(64, 16, 3, 3, p_h=1, p_w=1)], [np.zeros((16, 64, 3, 3), np.float32)])
-    s = net.query_sizes(1)
-    assert s.state_bytes_per_stream == s.retained_bytes_per_stream == 3 * 24 * 64 * 4       # (3 rows of c: a quarter of that)
-    net.destroy()
-    net = idf.Net("f32", 0, 1, 64, [conv(64, 8, 5, 1)], [np.zeros((8, 64, 5, 1), np.float32)])
-    assert net.query_sizes(1, 1, 16).state_bytes_per_stream == 5 * 64 * 4
-    net.destroy()
-    net = idf.Net("bf16", 32, 24, 16, [conv(16, 64, 3, 3, p_h=1, p_w=1)], [np.zeros((64, 16, 3, 3), np.uint16)])
-    assert net.query_sizes(1).state_bytes_per_stream == 3 * 24 * 64 * 4                     # (the rows of c are larger)
-    net.destroy()
