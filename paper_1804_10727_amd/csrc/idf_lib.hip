@@ -116,6 +116,7 @@ struct idf_streams {
     int ev_per_step = 0;             // int8 event path (idf_set_event_path): events a tile may hold per K-step of its contraction and still go that way; 0: off
     bool use_gather = false;         // the layers are units of the gathering kernel
     bool use_cascade1d = false;      // such a net, 1-D
+    bool depth_first = false;        // whose layers run one after the other within each call
     bool prof_on = false;
     std::vector<ProfRec> prof;
     std::vector<hipEvent_t> ev_pool;
@@ -846,7 +847,7 @@ int gather_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *con
         const Geom &g = net.g[s->units[k].l];
         most = std::max(most, (rows_ready(g, p.in[k]) - p.out[k]) * g.w_out);
     }
-    const bool chain = out && ((s->use_cascade1d && strict_cascade()) || most <= 32);
+    const bool chain = out && (s->depth_first || most <= 32);
     for (bool fresh = n_seg > 0; fresh || out;) {
         double bytes = 0;
         RowProg q = p;                             // (p moves on once the launch is enqueued)
@@ -873,7 +874,7 @@ int gather_flush(idf_streams *s)
     StreamSel all{};
     all.n = s->B; all.base = 0; all.pos0 = 0;
     const int64_t before = s->prog_all.in[0];
-    int rc = gather_run(s, all, s->prog_all, s->held_buf, s->held, s->held_rows, strict_cascade());
+    int rc = gather_run(s, all, s->prog_all, s->held_buf, s->held, s->held_rows, s->depth_first);
     if (s->prog_all.in[0] != before) s->held = 0;
     return rc;
 }
@@ -1929,7 +1930,7 @@ int open_on(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
     s->transit_off = L.transit_off; s->ring_stride = L.ring_stride; s->held_stride = L.held_stride;
     s->transit_stride = L.transit_stride; s->transit_cap = L.transit_cap;
     s->out_off = L.out_off; s->stats_off = L.stats_off; s->issued_off = L.issued_off; s->out_stride = L.out_stride; s->sizes = L.sizes;
-    s->use_gather = L.gather; s->use_cascade1d = L.cascade1d;
+    s->use_gather = L.gather; s->use_cascade1d = L.cascade1d; s->depth_first = L.cascade1d && strict_cascade();
     s->head_off = L.head_off;
     s->mfma = L.mfma; s->units = L.units;
     s->unit_of.assign(net->g.size(), -1);
@@ -2073,7 +2074,7 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
         } else {
             rc = gather_flush(s);
             if (rc != IDF_OK) return rc;
-            rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, strict_cascade()); });
+            rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, s->depth_first); });
         }
         if (rc != IDF_OK) return give_up(rc);
     } else if (s->use_gather) {

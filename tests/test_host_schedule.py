@@ -248,3 +248,24 @@ def finite_weights(rt):
 
 def test_infinite_weights_stay_off_the_gathering_kernel(runtime):
     host_runtime.run(runtime, "test_host_schedule", "finite_weights")
+
+
+def depth_first(rt):
+    """IDF_CASCADE_STAGES=1 counts when streams are opened: theirs are launches of all layers, one after the other."""
+    import os
+    from workloads import make
+    import paper_1804_10727_amd as idf
+    net = idf.net_from_workload(make(2, streams=4, length=1600))
+    for strict in (True, False):
+        os.environ["IDF_CASCADE_STAGES"] = "1" if strict else "2"
+        st = host_runtime.Streams(net, 4, 16)
+        os.environ["IDF_CASCADE_STAGES"] = "2" if strict else "1"
+        rt.host_begin()
+        for _ in range(10):
+            st.push(16)
+        assert (rt.host_launches(b"k_conv_gather_chain"), rt.host_launches(b"k_conv_gather_rows")) == ((10, 0) if strict else (0, 10))
+        st.close()
+
+
+def test_streams_keep_the_mode_they_were_opened_in(runtime):
+    host_runtime.run(runtime, "test_host_schedule", "depth_first")
