@@ -85,15 +85,17 @@ typedef struct {
     size_t state_bytes_per_stream;   /* of which, per stream: the retained state -- the rolling rows of
                                         c of every conv layer and the held row of every pool.  This is
                                         the footprint the paper bounds; it does not depend on in_h.
-                                        (Layers on the matrix cores keep rows of their input instead;
-                                        the rings they lie in count as transit.)                     */
+                                        Layers on the matrix cores keep K_h rows of their input, as
+                                        events, instead (in rings that count as transit).            */
     size_t handover_bytes_per_stream;/* of which, per stream: rows a layer has completed that may wait, when a
                                         call returns, for the next layer's step in a later call.  Only the
                                         staged modes have such rows (the default for nets served throughout
                                         by the matrix-core kernels: layer l then
                                         runs behind layer l-1 by one launch); 0 when the layers run strictly
                                         depth-first within every call (environment IDF_CASCADE_STAGES=1,
-                                        IDF_NO_ROW_STAGES=1).  Independent of in_h as well.              */
+                                        IDF_NO_ROW_STAGES=1).  Also what K_h rows of events take beyond
+                                        K_h rows of c, in layers on the matrix cores with more input than
+                                        output.  Independent of in_h as well.                            */
     size_t retained_bytes_per_stream;/* state_bytes_per_stream + handover_bytes_per_stream: everything of a
                                         stream that survives from one call to the next                  */
     size_t transit_bytes_per_stream; /* per stream: room for rows passed between layers (scratch during a

@@ -358,6 +358,11 @@ int make_layout(const idf_net &net, int B, int max_seg, int64_t out_cap, Layout 
             L.ring_stride[l] = (int64_t)g.k_h * g.w_out * g.c_out;
             if (!L.mfma[l] && !L.gather) { L.ring_off[l] = off; off = align_up(off + (size_t)L.ring_stride[l] * 4 * B); }
             state_per_stream += (size_t)L.ring_stride[l] * 4;
+            // (the method's bound; where a layer has more input than output its rows of events take more than rows of c: rows of the
+            // layer before that wait)
+            const int vl = conv3x3_mfma_vl(net.precision), c_in = L.gather ? (g.c_in + vl - 1) / vl * vl : g.c_in;
+            const size_t events = L.mfma[l] || L.gather ? (size_t)g.k_h * g.w_in * c_in * eb : 0, rows_c = (size_t)L.ring_stride[l] * 4;
+            handover_per_stream += events > rows_c ? events - rows_c : 0;
         } else {
             L.held_stride[l] = (int64_t)g.w_in * g.c_out;
             if (!L.mfma[l] && !L.gather) { L.held_off[l] = off; off = align_up(off + (size_t)L.held_stride[l] * eb * B); }

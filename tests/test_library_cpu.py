@@ -232,3 +232,17 @@ def test_volume_net_description_and_sizes():
     assert e.value.code == binding.IDF_EUNSUPPORTED
     with pytest.raises(idf.IdfError):                       # missing weights
         VolumeNet("f32", 9, 10, 8, 2, L, [w[0], None])
+
+
+def test_retained_bytes_of_layers_with_more_input_than_output():
+    """Layers on the matrix cores keep K_h rows of their input as events: what a stream retains covers those too."""
+    net = idf.Net("f32", 32, 24, 64, [conv(64, 16, 3, 3, p_h=1, p_w=1)], [np.zeros((16, 64, 3, 3), np.float32)])
+    s = net.query_sizes(1)
+    assert s.state_bytes_per_stream == 3 * 24 * 16 * 4 and s.retained_bytes_per_stream == 3 * 24 * 64 * 4
+    net.destroy()
+    net = idf.Net("f32", 0, 1, 62, [conv(62, 8, 5, 1)], [np.zeros((8, 62, 5, 1), np.float32)])
+    assert net.query_sizes(1, 1, 16).retained_bytes_per_stream == 5 * 64 * 4               # (channels padded to 16 bytes)
+    net.destroy()
+    net = idf.Net("bf16", 32, 24, 16, [conv(16, 64, 3, 3, p_h=1, p_w=1)], [np.zeros((64, 16, 3, 3), np.uint16)])
+    assert net.query_sizes(1).retained_bytes_per_stream == 3 * 24 * 64 * 4                 # (the rows of c are larger)
+    net.destroy()
