@@ -1,6 +1,7 @@
-"""Pushes of several rows on nets served throughout by the matrix-core kernel go through the layers
-two rows per launch, the rows between them kept in the accumulators: every value and counter must be
-that of one launch per row, bit for bit (the sums are formed in the same order)."""
+"""Nets served throughout by the matrix-core kernel form their rows in pairs, which share weights and two of
+four input rows, except where a read brings everything out after every row, and in launches that hold a step of
+every layer, except where the layers go one after the other: every value and counter must be the same, bit
+for bit (the sums are formed in the same order)."""
 import os
 
 import numpy as np
@@ -12,17 +13,18 @@ from helpers import check_stream
 pytestmark = pytest.mark.gpu
 
 
-def _run(wl, seg, pairs=True, reads_between=False):
+def _run(wl, seg, staged=True, reads_between=False, read_rows=False):
+    """read_rows: everything is brought out after every push; staged: the layers run side by side."""
     import torch
     import paper_1804_10727_amd as idf
     from paper_1804_10727_amd.binding import input_tensor
-    if not pairs:
-        os.environ["IDF_NO_ROW_PAIRS"] = "1"
+    if not staged:
+        os.environ["IDF_NO_ROW_STAGES"] = "1"
     try:
         net = idf.net_from_workload(wl)
         st = idf.Streams(net, wl["streams"], max_seg_rows=max(seg, 2))
     finally:
-        os.environ.pop("IDF_NO_ROW_PAIRS", None)
+        os.environ.pop("IDF_NO_ROW_STAGES", None)
     assert set(st.layer_kernels()) == {"conv3x3_mfma"}        # the path under test: a launch per arriving row (pair)
     x = input_tensor(wl, "cuda:0")
     H = wl["in_h"]
@@ -33,7 +35,7 @@ def _run(wl, seg, pairs=True, reads_between=False):
             n = min(seg, H - r)
             st.push_segment(x[:, r:r + n].contiguous())
             r += n
-            if reads_between and (r // seg) % 3 == 0:
+            if read_rows or (reads_between and (r // seg) % 3 == 0):
                 out, first, cnt = st.read_outputs(int(st.sizes.out_h))
                 o = out.cpu().numpy()
                 for b in range(wl["streams"]):
@@ -60,9 +62,9 @@ CASES = [
 @pytest.mark.parametrize("seg", [2, 3, 5])
 def test_two_rows_per_launch_equals_one(cfg, kw, seg):
     wl = wl_mod.make(cfg, **kw)
-    one, st_one = _run(wl, 1, pairs=True)               # pushes of one row never pair
-    two, st_two = _run(wl, seg, pairs=True, reads_between=(seg == 3))
-    off, _ = _run(wl, seg, pairs=False)
+    one, st_one = _run(wl, 1, read_rows=True)           # single rows, but in front of a pool
+    two, st_two = _run(wl, seg, reads_between=(seg == 3))
+    off, _ = _run(wl, seg, staged=False)
     for b in range(wl["streams"]):
         assert one[b].shape == two[b].shape == off[b].shape
         assert np.array_equal(one[b], two[b]), (b, np.abs(one[b].astype(np.float64) - two[b]).max())
