@@ -570,6 +570,10 @@ int64_t leaving_index(const idf_net &net, const RowUnit &u, int64_t o)
     return o / h * net.g[u.lp].h_out + o % h / 2;
 }
 
+// Layers of more input channels never take the event path: their share of the weights would crowd the LDS of every
+// workgroup of the launch for stretches too sparse to exist in practice.
+constexpr int kEventChannels = 16;
+
 // The step that forms rows [o, o + n) of c of unit k: everything but where rows that are new in this
 // launch lie (y_new) and, for a layer of another kind or the output area behind it, the destination.
 void row_step(idf_streams *s, int k, int64_t o, int64_t n, int n_streams, bool counted, RowStep &a, double &bytes)
@@ -605,9 +609,7 @@ void row_step(idf_streams *s, int k, int64_t o, int64_t n, int n_streams, bool c
         // elements of the contraction.
         a.w_ev = s->ws + s->wm_off[u.l] + ev_at;
         const int vl = conv3x3_mfma_vl(net.precision), steps = (3 * g.c_in + 2 * vl - 1) / (2 * vl);
-        // (layers of more than 16 input channels never take it: their share of the weights would crowd
-        // the LDS of every workgroup of the launch for stretches too sparse to exist in practice)
-        a.ev_limit = s->ev_per_step == 0 || g.c_in > 16 ? 0
+        a.ev_limit = s->ev_per_step == 0 || g.c_in > kEventChannels ? 0
                      : g.c_in < vl ? conv3x3_mfma_event_cap() : std::min(conv3x3_mfma_event_cap(), steps * s->ev_per_step);
     }
     a.bias = net.b_img[u.l].empty() ? nullptr : s->ws + s->b_off[u.l];
@@ -2296,7 +2298,10 @@ int idf_set_event_path(idf_streams *s, int events_per_kstep)
     if (s->eager.on) return fail(IDF_EUNSUPPORTED, "eager emission has one kernel per layer kind and no event-list variant");
     int rc = pipeline_drain(s);                 // what is on its way was pushed under the old setting
     if (rc != IDF_OK) return rc;
-    s->ev_per_step = std::min(events_per_kstep, 1 << 16);
+    // (nets without a layer that could take it run as they do without it)
+    bool any = false;
+    for (const RowUnit &u : s->units) any = any || s->net->g[u.l].c_in <= kEventChannels;
+    s->ev_per_step = any ? std::min(events_per_kstep, 1 << 16) : 0;
     return IDF_OK;
 }
 
