@@ -653,22 +653,26 @@ void take_step(idf_streams *s, int k, int64_t at, int64_t n, const void *dev_row
     }
 }
 
+int launch_rows(idf_streams *s, const RowBatch &b, const StreamSel &sel, double bytes, int layer);
+
+// Steps of more tiles than a launch takes: their first rows, then the others (no step of a batch writes what one reads).
+__attribute__((noinline)) int launch_rows_in_parts(idf_streams *s, const RowBatch &b, const StreamSel &sel, double bytes, int layer)
+{
+    RowBatch first = b, rest;
+    rest.n = 0;
+    for (int k = 0; k < b.n; ++k)
+        if (b.st[k].tiles > kRowTilesMax && conv3x3_mfma_split(first.st[k], rest.st[rest.n])) ++rest.n;
+    if (rest.n == 0) return fail(IDF_EUNSUPPORTED, "a row of more than %d tiles", kRowTilesMax);
+    int rc = launch_rows(s, first, sel, bytes, layer);
+    return rc != IDF_OK ? rc : launch_rows(s, rest, sel, 0, layer);
+}
+
 int launch_rows(idf_streams *s, const RowBatch &b, const StreamSel &sel, double bytes, int layer)
 {
     if (b.n == 0) return IDF_OK;
-    bool fits = true;
-    for (int k = 0; k < b.n; ++k) fits = fits && b.st[k].tiles <= kRowTilesMax;
-    if (!fits) {
-        // a step of more tiles than a launch takes: its first rows, then the others (no step of a batch writes what one reads)
-        RowBatch first = b, rest;
-        rest.n = 0;
-        for (int k = 0; k < b.n; ++k)
-            if (b.st[k].tiles > kRowTilesMax && conv3x3_mfma_split(first.st[k], rest.st[rest.n])) ++rest.n;
-        if (rest.n > 0) {
-            int rc = launch_rows(s, first, sel, bytes, layer);
-            return rc != IDF_OK ? rc : launch_rows(s, rest, sel, 0, layer);
-        }
-    }
+    int tiles = 0;
+    for (int k = 0; k < b.n; ++k) tiles = std::max(tiles, b.st[k].tiles);
+    if (tiles > kRowTilesMax) return launch_rows_in_parts(s, b, sel, bytes, layer);
     hipError_t e = launch_conv3x3_mfma_rows(s->net->precision, b, sel, launch_ctx(s, kKindConvMfma, bytes, layer));
     return e == hipSuccess ? IDF_OK : dev_fail(e, "mfma conv launch");
 }
@@ -676,14 +680,13 @@ int launch_rows(idf_streams *s, const RowBatch &b, const StreamSel &sel, double 
 // One launch for streams that all stand at p: every unit forms the rows it has the input for -- in pairs,
 // which share their weights and two of four input rows; a single row only where the sample ends or, with
 // flush, where a caller wants everything out -- the first unit from the n_new rows of the caller's buffer
-// too.  What a unit emits waits for the next unit's step in a later launch.  Returns false, with nothing
-// launched and p unchanged, when the ring of the first unit has no room for the new rows yet, or when
-// there is nothing to do.
-bool row_plan(idf_streams *s, RowProg &p, int n_streams, const void *dev_rows, int row0, int n_rows, int n_new, bool flush, RowBatch &b, double &bytes)
+// too.  What a unit emits waits for the next unit's step in a later launch.  q: where they stand behind the launch.
+// Returns false when the ring of the first unit has no room for the new rows yet, or when there is nothing to do.
+bool row_plan(idf_streams *s, const RowProg &p, RowProg &q, int n_streams, const void *dev_rows, int row0, int n_rows, int n_new, bool flush, RowBatch &b, double &bytes)
 {
     const idf_net &net = *s->net;
     const int nu = (int)s->units.size();
-    RowProg q = p;
+    q = p;
     b.n = 0;
     const bool part = s->part.on && n_new > 0;
     if (n_new > 0) b.n = 1;                        // place for the step that takes them
@@ -732,24 +735,22 @@ bool row_plan(idf_streams *s, RowProg &p, int n_streams, const void *dev_rows, i
         std::rotate(b.st, b.st + 1, b.st + b.n);
         bytes += (double)n_streams * n_new * net.in_w * net.in_c * ev_bytes(net.precision);
     }
-    if (b.n == 0) return false;
-    p = q;
-    return true;
+    return b.n > 0;
 }
 
 // Streams that stand at p receive n_rows rows (dev_rows), or (dev_rows null) everything on its way is brought through.
 int row_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *dev_rows, int n_rows)
 {
     RowBatch b;
+    RowProg q;                                     // (p moves on once a launch is enqueued)
     int done = 0;
     for (int guard = 0;; ++guard) {
         double bytes = 0;
-        RowProg q = p;                             // (p moves on once the launch is enqueued)
         const int n_new = dev_rows ? (int)std::min<int64_t>({n_rows - done, s->launch_rows, s->net->in_h - p.in[0] % s->net->in_h}) : 0;
         if (dev_rows && done == n_rows) return IDF_OK;
-        bool go = row_plan(s, q, sel.n, dev_rows, done, n_rows, n_new, !dev_rows, b, bytes);
+        bool go = row_plan(s, p, q, sel.n, dev_rows, done, n_rows, n_new, !dev_rows, b, bytes);
         const bool took = go && n_new > 0;
-        if (!go && dev_rows) go = row_plan(s, q, sel.n, nullptr, 0, 0, 0, guard > 64, b, bytes);
+        if (!go && dev_rows) go = row_plan(s, p, q, sel.n, nullptr, 0, 0, 0, guard > 64, b, bytes);
         if (!go) return dev_rows ? fail(IDF_ESTATE, "internal: rows between layers do not move on") : IDF_OK;
         int rc = launch_rows(s, b, sel, bytes, -1);
         if (rc != IDF_OK) return rc;
@@ -796,11 +797,11 @@ void gather_take(const idf_streams *s, int64_t at, int n, int x_lo, int x_hi, Ga
 
 // One launch for streams that all stand at p; as row_plan, without pairs.  chain: the layers one after the other, each on
 // what the ones before it emit in this launch.
-bool gather_plan(const idf_streams *s, RowProg &p, int n_streams, int n_new, bool chain, GatherHead &h, GatherStep *st, double &bytes)
+bool gather_plan(const idf_streams *s, const RowProg &p, RowProg &q, int n_streams, int n_new, bool chain, GatherHead &h, GatherStep *st, double &bytes)
 {
     const idf_net &net = *s->net;
     const int nu = (int)s->units.size();
-    RowProg q = p;
+    q = p;
     h.n = 0;
     auto take = [&]() {
         gather_take(s, p.in[0], n_new, s->part.on ? s->part.x_lo : 0, s->part.on ? s->part.x_hi : net.in_w, st[h.n++]);
@@ -829,9 +830,7 @@ bool gather_plan(const idf_streams *s, RowProg &p, int n_streams, int n_new, boo
         const int64_t keep = std::min(first_needed(net.g[0], q.out[0]), first_needed(net.g[0], p.out[0]));
         if (q.in[0] - keep > s->units[0].ring_rows) return false;
     }
-    if (h.n == 0) return false;
-    p = q;
-    return true;
+    return h.n > 0;
 }
 
 // Streams that stand at p receive the rows of n_seg buffers of seg_rows rows each (0: none), which belong to one sample;
@@ -841,6 +840,7 @@ int gather_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *con
     const idf_net &net = *s->net;
     GatherHead h;
     GatherStep st[kGatherMax];
+    RowProg q;                                     // (p moves on once a launch is enqueued)
     h.n_layers = (int)net.g.size();
     h.stats = (unsigned long long *)(s->ws + s->stats_off);
     h.issued = s->count_issued ? (unsigned long long *)(s->ws + s->issued_off) : nullptr;
@@ -857,11 +857,10 @@ int gather_run(idf_streams *s, const StreamSel &sel, RowProg &p, const void *con
     const bool chain = out && (s->depth_first || most <= 32);
     for (bool fresh = n_seg > 0; fresh || out;) {
         double bytes = 0;
-        RowProg q = p;                             // (p moves on once the launch is enqueued)
-        const bool took = fresh && gather_plan(s, q, sel.n, n_seg * seg_rows, chain, h, st, bytes);
+        const bool took = fresh && gather_plan(s, p, q, sel.n, n_seg * seg_rows, chain, h, st, bytes);
         if (!took) {
             bytes = 0;
-            if (!gather_plan(s, q, sel.n, 0, chain, h, st, bytes)) {
+            if (!gather_plan(s, p, q, sel.n, 0, chain, h, st, bytes)) {
                 if (fresh) return fail(IDF_ESTATE, "internal: rows between layers do not move on");
                 break;
             }
@@ -2000,6 +1999,32 @@ int open_on(idf_net *net, int n_streams, int max_seg_rows, int64_t out_cap_rows,
 
 }  // namespace
 
+namespace {
+
+// n rows have gone into a stream, which complete `fresh` output rows: the host's count moves on.
+inline void took_rows(const idf_streams *s, StreamHost &h, int n, int64_t fresh)
+{
+    const int in_h = s->net->in_h;
+    h.out_written += fresh;
+    if (h.early) h.early = early_after(s, h.early, h.r, h.r + n);          // (layer by layer only)
+    h.r += n;
+    h.x_next = 0;
+    if (in_h > 0 && h.r == in_h) { h.r = 0; ++h.sample; }      // next sample
+}
+
+// A launch of a push to push_members failed.  Layers side by side: what the launches before it took in has been taken in.
+__attribute__((noinline)) int push_gave_up(idf_streams *s, int rc)
+{
+    for (const auto &m : s->push_members) {
+        StreamHost &h = s->h[m.second];
+        const int64_t in = (s->prog_same ? s->prog_all : s->prog[m.second]).in[0] - (h.sample * s->net->in_h + h.r);
+        if (in > 0) took_rows(s, h, (int)in, output_rows_of_push(*s->net, h.r, (int)in));
+    }
+    return rc;
+}
+
+}  // namespace
+
 extern "C" {
 
 int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const void *dev_rows, int n_rows)
@@ -2043,25 +2068,6 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
         else if (key != key0) one_group = false;
         members.push_back({i, id});
     }
-    // rows of the push that a stream has taken in: the host's count moves on
-    auto account = [&](StreamHost &h, int n) {
-        if (h.r != memo_r) { memo_r = h.r; memo_fresh = output_rows_of_push(net, h.r, n); }
-        h.out_written += memo_fresh;
-        if (by_sample && h.early) h.early = early_after(s, h.early, h.r, h.r + n);
-        h.r += n;
-        h.x_next = 0;
-        if (net.in_h > 0 && h.r == net.in_h) { h.r = 0; ++h.sample; }      // next sample
-    };
-    // A launch failed.  Layers side by side: what the launches before it took in has been taken in.
-    auto give_up = [&](int rc) {
-        for (const auto &m : members) {
-            StreamHost &h = s->h[m.second];
-            const int64_t in = (s->prog_same ? s->prog_all : s->prog[m.second]).in[0] - (h.sample * net.in_h + h.r);
-            memo_r = -1;
-            if (in > 0) account(h, (int)in);
-        }
-        return rc;
-    };
     auto deliver = [&](const Key &key, const std::vector<std::pair<int, int>> &group) {
         return for_each_selection(group, [&](const StreamSel &sel) {
             return enqueue_cascade(s, sel, dev_rows, n_rows, std::get<0>(key), std::get<1>(key), std::get<2>(key), std::get<3>(key));
@@ -2083,13 +2089,13 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
             if (rc != IDF_OK) return rc;
             rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, s->depth_first); });
         }
-        if (rc != IDF_OK) return give_up(rc);
+        if (rc != IDF_OK) return push_gave_up(s, rc);
     } else if (s->use_gather) {
         rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, false); });
-        if (rc != IDF_OK) return give_up(rc);
+        if (rc != IDF_OK) return push_gave_up(s, rc);
     } else if (s->stg2d) {
         rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return row_run(s, sel, p, dev_rows, n_rows); });
-        if (rc != IDF_OK) return give_up(rc);
+        if (rc != IDF_OK) return push_gave_up(s, rc);
     } else if (one_group) {
         rc = deliver(key0, members);
         if (rc != IDF_OK) return rc;
@@ -2102,7 +2108,15 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
         }
     }
     memo_r = -1;
-    for (int i = 0; i < n_ids; ++i) account(s->h[stream_ids ? stream_ids[i] : i], n_rows);
+    for (int i = 0; i < n_ids; ++i) {
+        StreamHost &h = s->h[stream_ids ? stream_ids[i] : i];
+        if (h.r != memo_r) { memo_r = h.r; memo_fresh = output_rows_of_push(net, h.r, n_rows); }
+        h.out_written += memo_fresh;
+        if (by_sample && h.early) h.early = early_after(s, h.early, h.r, h.r + n_rows);
+        h.r += n_rows;
+        h.x_next = 0;
+        if (net.in_h > 0 && h.r == net.in_h) { h.r = 0; ++h.sample; }      // next sample
+    }
     return IDF_OK;
 }
 
