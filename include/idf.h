@@ -214,8 +214,8 @@ int idf_open_streams_static(idf_net *net, int n_streams, int max_seg_rows, int64
  *   1 <= n_rows <= max_seg_rows.
  * Zero values are not events: they cause no arithmetic (Sec. 1).  Completed rows of the last
  * layer are appended to the stream's output area.
- * For nets whose layers run side by side (1-D nets; 2-D nets served throughout by the matrix-core
- * kernels) a push is one launch for every group of streams that stand at the same place, and each
+ * For nets whose layers run side by side (2-D nets served throughout by the 3x3 kernel, and nets that
+ * go through the gathering kernel: 1-D nets, nets of several kinds of layers) a push is one launch for every group of streams that stand at the same place, and each
  * layer takes what was complete before the launch: the deeper layers of a segment may be enqueued
  * only with the next pushes.  A 3x3 layer forms its rows in pairs where it can.  idf_read_outputs,
  * idf_get_stats, idf_reset_streams, idf_close_streams and idf_profile_end first enqueue whatever
@@ -228,19 +228,18 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
                      int n_rows);
 
 /* Throughput mode for 1-D nets whose streams are pushed in step (idf_push_segment with all streams
- * at the same row): up to k such segments are held back and run by one launch.  A workgroup takes
- * its stream's held-back segments in order, consecutive ones together while their rows fit one
- * step of a layer (16 rows), with the rolling buffers staying on chip in between; every segment
- * still goes through everything it can influence before the next is looked at (Sec. 3 first
- * paragraph).  k = 1 (the default) launches with every push.
+ * at the same row): up to k such segments are held back and run by one launch, as if they were one
+ * segment.  k = 1 (the default) launches with every push.  Takes effect at once, whatever has been
+ * pushed before: the rows that are still needed move within the workspace (one more launch).
  *   - A held-back segment's dev_rows is read when its launch runs: keep it unchanged until k - 1
  *     further pushes in step or any of the calls below have been made AND the stream's work has run.
  *   - idf_read_outputs, idf_get_stats, idf_get_issued_macs, idf_reset_streams, idf_snapshot,
  *     idf_restore, idf_read_head*, idf_close_streams, idf_profile_end, this call, and any push that is
  *     not of all streams in step first launch what is held back: what they return never shows it.
- *   - Rows of segments taken together are added in one pass: the float32 sums are associated
- *     differently than with a launch per push, so results agree with k = 1 to rounding, not bit for bit.
- *   - A launch is also due as soon as a further segment could make some layer need more than 8 steps.
+ *   - The sums are formed in the same order as with a launch per push: results are the same bit for bit.
+ *   - A launch is also due before a segment of another number of rows, before the first segment of a
+ *     sample, and as soon as a further segment would make more than 256 rows, or more than the
+ *     workspace has room for where it is smaller than idf_query_sizes says.
  * 1 <= k <= 16.  IDF_EUNSUPPORTED for nets the 1-D cascade does not serve and under eager emission. */
 int idf_set_push_batching(idf_streams *s, int k);
 
@@ -283,10 +282,10 @@ int idf_get_stats(idf_streams *s, int stream_id, uint64_t *events_in, uint64_t *
  * compaction of events (Sec. 1: zero values cause no arithmetic) leaves over.  Counted only while
  * switched on with idf_count_issued_macs(s, 1) (off after open: the count costs an atomic per
  * wave), since open/reset.
- * The matrix-core kernel skips K-steps whose 32-position fragment holds no event and multiplies
- * the zeros inside the others (a first layer of 1-4 input channels has one or two K-steps and
- * visits them always); the 1-D cascade skips input channels without an event in the
- * segment and computes all rows of the others; layers served by the generic kernels, which test
+ * The 3x3 kernel skips K-steps (four 16-byte cells of channels) without an event in the stretch of
+ * positions and input rows of a workgroup and multiplies the zeros inside the others (a first layer
+ * of few channels has one K-step and visits it always); the gathering kernel skips those without an
+ * event in the windows of a tile of 16 positions; layers served by the generic kernels, which test
  * every value, report their executed count.  Counted from open/reset on it is always >=
  * macs_executed of idf_get_stats.  IDF_EUNSUPPORTED under eager emission.  idf_get_issued_macs
  * synchronises the stream. */

@@ -413,7 +413,8 @@ __global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherB
 }
 
 // A workgroup per layer, stream by stream: a stream's new place may lie on what streams on one side of it held, so they go from that
-// side, and a stream's rows are all read before one is written.
+// side, and a stream's rows are all read before one is written.  Once per change of the rows in use, not per push: a memory
+// round trip per stream, 4 us for one, 25 us for 64 audio streams, 180 us for 512.
 constexpr int kMoveThreads = 256;
 __global__ void __launch_bounds__(kMoveThreads) k_ring_move(const RingMove a)
 {
