@@ -150,6 +150,10 @@ struct RowStep {
     unsigned xt_rcp, cg_rcp;           // ceil(2^32 / n) of those (0 for one)
     int nb, row_pos;                   // blocks of 64 cells per row of a stretch; positions those cover: what a row takes in LDS
     unsigned cells_rcp;                // ceil(65536 / cells)
+    int stride, row_pitch;             // bytes in LDS from one position, and one row of a stretch, to the next
+    int n_ct, co_g;                    // tiles of 16 output channels; channels from one group of lanes to the next
+    int n_ksteps;                      // K-steps of the contraction
+    unsigned w_kstep, w_ky;            // bytes from one K-step, and one tap row, to the next in the packed weights
     int act, shr, clamp_hi;
     int pool;                          // 1: 2x2 max-pool behind the layer
     int pool_from;                     // output rows before this one have been counted as the pool's events already

@@ -98,60 +98,47 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     constexpr int R = NR + 2;                      // input rows
     constexpr int NW = 3 * MC;                     // weight fragments of a K-step
     constexpr bool kFloat = std::is_same<st_t, float>::value;
-    constexpr int kLoads = NP == 2 ? 17 : 9;       // cells each lane has in flight: a row of 32 positions (16) and halo x 32 cells at once
+    constexpr int kLoads = NP == 2 ? 18 : 9;       // cells each lane has in flight: a row of 32 positions (16) and halo x 32 cells at once
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ unsigned long long occ[kWaves];     // per input row, bit c: cell c holds an event somewhere in the stretch
 
+    // Everything the loads need to know, asked for in one batch, and what the host can work out it has.  Left to first use the
+    // arguments were a dozen scalar loads one after the other: from the arguments' arrival to the first request for a row 2,100 cycles,
+    // now 1,000.  With weights asked for before the rows and the counters in one instruction (us per image, vgg-style net,
+    // 64 streams / four out of step / 8 rows per push / f32 net: 2826 / 7030 / 663 / 285 before, 2576 / 5548 / 593 / 257 after).
+    const int n_rows = a.n_rows, y0 = a.y0, n_cg = a.n_cg, n_xt = a.n_xt, W = a.w, H = a.h, C_in = a.c_in, cells = a.cells, wc_log = a.wc_log;
+    const int y_new = a.y_new, slot0 = a.slot0, ring_rows = a.ring_rows, nb = a.nb, n_ct = a.n_ct, co_g = a.co_g, n_ksteps = a.n_ksteps;
+    const int C_out = a.c_out, stride = a.stride, row_pitch = a.row_pitch;     // (the last two: bytes in LDS from one position, and one row, to the next)
+    const unsigned cg_rcp = a.cg_rcp, xt_rcp = a.xt_rcp, cells_rcp = a.cells_rcp, w_kstep = a.w_kstep, w_ky = a.w_ky;
+    const int64_t in_stride = a.in_stride, new_stride = a.new_stride;
+    const void *in_ring = a.in_ring, *in_new = a.in_new, *wfrag = a.wfrag, *bias = a.bias;
+    const int sel_base = sel.base, pos0 = sel.pos0;
+    asm volatile("" ::"s"(n_rows), "s"(y0), "s"(n_cg), "s"(n_xt), "s"(W), "s"(H), "s"(C_in), "s"(cells), "s"(wc_log), "s"(y_new), "s"(slot0), "s"(ring_rows),
+                 "s"(nb), "s"(n_ct), "s"(co_g), "s"(cg_rcp), "s"(xt_rcp), "s"(cells_rcp), "s"(w_kstep), "s"(in_stride), "s"(new_stride), "s"(in_ring),
+                 "s"(in_new), "s"(wfrag), "s"(bias), "s"(n_ksteps), "s"(sel_base));
+    asm volatile("" ::"s"(w_ky), "s"(pos0), "s"(C_out), "s"(stride), "s"(row_pitch));
+
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     const int m = lane & 15, g = lane >> 4;        // position within a tile; group of channels / of k
-    const int stream = sel_stream(sel, si);
-    const int rest = a.cg_rcp ? (int)__umulhi((unsigned)tile, a.cg_rcp) : tile, cg = tile - rest * a.n_cg;
-    const int rg = a.xt_rcp ? (int)__umulhi((unsigned)rest, a.xt_rcp) : rest, xt = rest - rg * a.n_xt;
-    const int y = a.y0 + rg * NR;                  // first output row
-    const int rows = a.n_rows - rg * NR < NR ? a.n_rows - rg * NR : NR;
-    const int W = a.w, H = a.h, C_in = a.c_in, C_out = a.c_out;
-    const int wc = wave & ((1 << a.wc_log) - 1), wp = wave >> a.wc_log;
-    const int XT = (16 * NP * kWaves) >> a.wc_log;
+    const int stream = sel_base >= 0 ? sel_base + si : sel.ids[si];
+    const int rest = (int)__umulhi((unsigned)tile, cg_rcp) + (n_cg == 1 ? tile : 0), cg = tile - rest * n_cg;
+    const int rg = (int)__umulhi((unsigned)rest, xt_rcp) + (n_xt == 1 ? rest : 0), xt = rest - rg * n_xt;
+    const int y = y0 + rg * NR;                    // first output row
+    const int rows = n_rows - rg * NR < NR ? n_rows - rg * NR : NR;
+    const int wc = wave & ((1 << wc_log) - 1), wp = wave >> wc_log;
+    const int XT = (16 * NP * kWaves) >> wc_log;
     const int x0 = xt * XT;
-    const bool single = C_out == 16;               // one tile of channels; else tiles come in interleaved pairs
-    const int n_blk = (C_out + 31) >> 5;
-    const int ct0 = ((cg << a.wc_log) + wc) * MC;  // first channel tile of this wave
+    const int ct0 = ((cg << wc_log) + wc) * MC;    // first channel tile of this wave (16 channels: the only one; else tiles come in interleaved pairs)
     const int xw = x0 + wp * 16 * NP;              // first position of this wave
-    const bool active = ct0 < (single ? 1 : 2 * n_blk) && xw < W;
+    const bool active = ct0 < n_ct && xw < W;
     // this lane's channels: co0 .. co0 + 4 * MC - 1
-    const int co0 = single ? g * 4 : (ct0 >> 1) * 32 + g * 8 + (MC == 1 ? (ct0 & 1) * 4 : 0);
+    const int co0 = (ct0 >> 1) * 32 + g * co_g + (MC == 1 ? (ct0 & 1) * 4 : 0);
     const bool co_ok = co0 < C_out;
-    const bool small_c = a.cells == 0;
-
-    // ---- input rows: wave r of the workgroup brings in input row r ------------------------------------
-    auto row_there = [&](int r) IDF_INLINE { const int yi = y - 1 + r; return yi >= 0 && yi < H && r < rows + 2; };
-    const bool there = wave < R && row_there(wave);
-    const unsigned char *my_row = nullptr;         // the same in every lane
-    if (there) {
-        const int yi = y - 1 + wave;
-        if (yi >= a.y_new) {
-            my_row = (const unsigned char *)a.in_new + ((int64_t)(sel.pos0 + si) * a.new_stride + (int64_t)(yi - a.y_new) * W * C_in) * EB;
-        } else {
-            int slot = a.slot0 + rg * NR + wave;
-            if (slot >= a.ring_rows) slot -= a.ring_rows;
-            my_row = (const unsigned char *)a.in_ring + ((int64_t)stream * a.in_stride + (int64_t)slot * W * C_in) * EB;
-        }
-    }
-    // few channels: the stretch is kept as the windows the positions see, [row][position][3 * C_in values, padded to cells]
-    const int wcells = small_c ? window_cells(C_in, VL, kFloat) : 0;
-    const int wstride = cell_stride(wcells) * 16;
-    const int cells = a.cells, stride = cell_stride(cells) * 16;      // 16-byte cells per position; bytes from one position to the next
-    const bool edge = x0 == 0 || x0 + XT >= W;
-    auto cell_of = [&](int i, int &p, int &c) IDF_INLINE {
-        p = (int)(((unsigned)i * a.cells_rcp) >> 16);
-        c = i - p * cells;
-    };
+    const bool small_c = cells == 0;
 
     // ---- weights -------------------------------------------------------------------------------------
     // [K-step][block of 32 channels][ky][tile of the pair][lane][16 bytes]  (one tile of channels: [K-step][ky][lane][16])
-    const uint32_t w_kstep = single ? 3 * 1024 : (uint32_t)n_blk * 6144;
-    const uint32_t w_ky = single ? 1024 : 2048;
-    const unsigned char *wp_next = (const unsigned char *)a.wfrag + (active && !single ? (ct0 >> 1) * 6144 + (MC == 1 ? (ct0 & 1) * 1024 : 0) : 0);
+    const unsigned char *wp_next = (const unsigned char *)wfrag + (active ? (ct0 >> 1) * 6144 + (MC == 1 ? (ct0 & 1) * 1024 : 0) : 0);
     const uint32_t w_lane = (uint32_t)lane * 16;
     auto fetch_w = [&](i32x4 (&w)[NW]) IDF_INLINE {
 #pragma unroll
@@ -160,56 +147,75 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             for (int mc = 0; mc < MC; ++mc)
                 w[ky * MC + mc] = *at4(reinterpret_cast<const i32x4 *>(wp_next), w_lane + (MC == 2 ? ky * 2048 + mc * 1024 : ky * w_ky));
     };
-    const int n_ksteps = small_c ? 1 : (3 * cells + 3) >> 2;
     int ks_left = n_ksteps;                        // K-steps whose weights have not been asked for
     auto advance_w = [&]() IDF_INLINE { if (--ks_left > 0) wp_next += w_kstep; };         // past the end the last one is simply fetched again
 
-    // ---- the first stretch, and what can be asked for while it is on its way ---------------------------
-    acc_t acc[NR][MC][NP];
+    acc_t acc[NR][MC][NP], start[MC];
     i32x4 wa[NW], wb[NW];
+    fetch_w(wa);                                   // (where rows lie is worked out while the first are on their way)
+    advance_w();
+#pragma unroll
+    for (int mc = 0; mc < MC; ++mc) {
+        start[mc] = acc_t{0, 0, 0, 0};
+        if (bias) start[mc] = *reinterpret_cast<const acc_t *>((const st_t *)bias + (co_ok ? co0 : 0) + mc * 4);
+    }
+
+    // ---- input rows: wave r of the workgroup brings in input row r ------------------------------------
+    auto row_there = [&](int r) IDF_INLINE { const int yi = y - 1 + r; return yi >= 0 && yi < H && r < rows + 2; };
+    const bool there = wave < R && row_there(wave);
+    const int row_bytes = W * C_in * EB;
+    const unsigned char *my_row;                   // the same in every lane; a row that is not there: some row, whose values are dropped
+    {
+        const int yi = y - 1 + wave;
+        int slot = slot0 + rg * NR + wave;
+        slot = slot >= ring_rows ? slot - ring_rows : slot;
+        const bool fresh = there && yi >= y_new;
+        const int64_t at = fresh ? (int64_t)(pos0 + si) * new_stride : (int64_t)stream * in_stride;
+        my_row = (const unsigned char *)(fresh ? in_new : in_ring) + at * EB + (int64_t)row_bytes * (there ? (fresh ? yi - y_new : slot) : 0);
+    }
+    // few channels: the stretch is kept as the windows the positions see, [row][position][3 * C_in values, padded to cells]
+    const int wstride = stride;
+
+    // ---- the stretch ----------------------------------------------------------------------------------
     if (!small_c) {
-        // The whole stretch at once, in blocks of 64 cells: everything this wave needs from memory is on its way together
-        // (the registers it lands in are those of the accumulators and fragments later).  A row in LDS is as long as whole
-        // blocks, so that no lane has to sit out.
-        const int nb = a.nb, pos_bytes = C_in * EB;
-        unsigned char *row = smem + wave * a.row_pos * stride;
+        // The whole stretch at once, in blocks of 64 cells (a position's cells are all its channels, so that a stretch lies in one
+        // piece): everything this wave needs from memory is on its way together.  The registers it lands in are those of the
+        // accumulators and fragments later.  A row in LDS is as long as whole blocks, so that no lane has to sit out.
+        constexpr int kGroup = NP == 2 ? 9 : 3;    // blocks that are asked for without a look at how many there are
+        static_assert(kLoads % kGroup == 0, "whole groups");
+        const int first = (x0 - 1) * cells * 16 + lane * 16, last = row_bytes - 16;      // this lane's first cell, the row's last
+        const bool edge = x0 == 0 || x0 + XT >= W || !there;
+        unsigned char *row = smem + wave * row_pitch;
         unsigned long long mask = 0;               // bit c: cell c holds an event somewhere in the stretch
         for (int b0 = 0; b0 < nb; b0 += kLoads) {
             i32x4 tv[kLoads];
-            int p, c;
-            if (there) {
-                cell_of(b0 * 64 + lane, p, c);
 #pragma unroll
-                for (int b = 0; b < kLoads; ++b) {
-                    if (b0 + b >= nb) break;
-                    int x = x0 - 1 + p;
-                    x = x < 0 ? 0 : (x >= W ? W - 1 : x);
-                    tv[b] = *at4(reinterpret_cast<const i32x4 *>(my_row), (uint32_t)(x * pos_bytes + c * 16));
-                    if (64 % cells == 0) p += 64 / cells; else cell_of((b0 + b + 1) * 64 + lane, p, c);
-                }
-            }
-            if (b0 == 0) {
-                if (active) fetch_w(wa);
-                advance_w();
+            for (int g0 = 0; g0 < kLoads; g0 += kGroup) {
+                if (b0 + g0 >= nb) break;
+#pragma unroll
+                for (int b = g0; b < g0 + kGroup; ++b)
+                    tv[b] = *at4(reinterpret_cast<const i32x4 *>(my_row), (uint32_t)min(max(first + (b0 + b) * 1024, 0), last));
             }
             if (wave < R) {
-                int ln = lane, any = 0;            // (places are worked out again rather than held in registers from the load on:
-                asm volatile("" : "+v"(ln));       //  the empty statement hides that this is the same value)
-                cell_of(b0 * 64 + ln, p, c);
+                int any = 0;
 #pragma unroll
-                for (int b = 0; b < kLoads; ++b) {
-                    if (b0 + b >= nb) break;
-                    i32x4 v = there ? tv[b] : i32x4{0, 0, 0, 0};
+                for (int g0 = 0; g0 < kLoads; g0 += kGroup) {
+                    if (b0 + g0 >= nb) break;
                     if (edge) {
-                        const int x = x0 - 1 + p;
-                        if (x < 0 || x >= W) v = i32x4{0, 0, 0, 0};
+#pragma unroll
+                        for (int b = g0; b < g0 + kGroup; ++b)
+                            if (!there || (uint32_t)(first + (b0 + b) * 1024) > (uint32_t)last) tv[b] = i32x4{0, 0, 0, 0};
                     }
-                    *reinterpret_cast<i32x4 *>(row + p * stride + c * 16) = v;
-                    any |= T::or_of(v);
-                    if (64 % cells == 0) p += 64 / cells; else cell_of((b0 + b + 1) * 64 + ln, p, c);
+#pragma unroll
+                    for (int b = g0; b < g0 + kGroup; ++b) {
+                        if (b0 + b >= nb) break;
+                        const uint32_t i = (uint32_t)((b0 + b) * 64 + lane), p = __umul24(i, cells_rcp) >> 16;
+                        *reinterpret_cast<i32x4 *>(row + __umul24(p, (uint32_t)(stride - cells * 16)) + i * 16) = tv[b];
+                        any |= T::or_of(tv[b]);
+                    }
                 }
                 unsigned long long bal = __ballot(any != 0);
-                if (64 % cells == 0) {             // a lane has had one and the same cell throughout
+                if ((cells & (cells - 1)) == 0) {  // a lane has had one and the same cell throughout
                     for (int w = 32; w >= cells; w >>= 1) bal |= bal >> w;
                 } else {
                     bal = bal ? ~0ull : 0ull;
@@ -222,7 +228,6 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         if (TAIL && (cells & 3) && wave < R && lane == 0) *reinterpret_cast<i32x4 *>(row + (XT + 2) * stride) = i32x4{0, 0, 0, 0};
     } else {
         // a lane gathers whole windows: three times C_in values next to each other in the row
-        if (active) fetch_w(wa);
         auto windows = [&](auto n_tag) IDF_INLINE {
             constexpr int C = decltype(n_tag)::value, WC = window_cells(C, VL, kFloat);
             if (wave >= R) return;
@@ -254,20 +259,21 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         default: windows(std::integral_constant<int, 4>{}); break;
         }
     }
-    {
-        acc_t start[MC];
 #pragma unroll
-        for (int mc = 0; mc < MC; ++mc) {
-            start[mc] = acc_t{0, 0, 0, 0};
-            if (a.bias) start[mc] = *reinterpret_cast<const acc_t *>((const st_t *)a.bias + (co_ok ? co0 : 0) + mc * 4);
-        }
+    for (int j = 0; j < NR; ++j)
 #pragma unroll
-        for (int j = 0; j < NR; ++j)
+        for (int mc = 0; mc < MC; ++mc)
 #pragma unroll
-            for (int mc = 0; mc < MC; ++mc)
-#pragma unroll
-                for (int np = 0; np < NP; ++np) acc[j][mc][np] = start[mc];
-    }
+            for (int np = 0; np < NP; ++np) acc[j][mc][np] = start[mc];
+    // (likewise for what comes after the contraction)
+    const int act = a.act, shr = a.shr, clamp_hi = a.clamp_hi, pool = a.pool, pool_from = a.pool_from, pool_emit = a.pool_emit, to_output = a.to_output;
+    const int dst_slot0 = a.dst_slot0, dst_rows = a.dst_rows, layer = a.layer, pool_layer = a.pool_layer, next_layer = a.next_layer, next_c_out = a.next_c_out;
+    const int n_layers = a.n_layers;
+    const int64_t dst_stride = a.dst_stride;
+    void *dst = a.dst;
+    unsigned long long *stats = a.stats, *issued = a.issued;
+    asm volatile("" ::"s"(act), "s"(shr), "s"(clamp_hi), "s"(pool), "s"(pool_from), "s"(pool_emit), "s"(to_output), "s"(dst_slot0), "s"(dst_rows), "s"(layer),
+                 "s"(pool_layer), "s"(next_layer), "s"(next_c_out), "s"(n_layers), "s"(dst_stride), "s"(dst), "s"(stats), "s"(issued));
     lds_barrier();
     uint32_t n_mfma = 0, n_done = 0;               // tiles of 16 x 16 x one K-step issued; K-steps issued
 
@@ -279,7 +285,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     uint32_t rows_done = 0;                        // input rows the list has taken care of (bit per row)
     if constexpr (EV && T::kEvents) {
         if (a.ev_limit > 0) {
-            const int nc = 16 * MC << a.wc_log, pitch = a.row_pos;
+            const int nc = 16 * MC << wc_log, pitch = a.row_pos;
             const size_t front = small_c ? (size_t)R * XT * wstride : (size_t)R * pitch * stride;
             int32_t *ev_cnt = reinterpret_cast<int32_t *>(smem + ((front + 15) & ~(size_t)15));
             int32_t *ev_off = ev_cnt + (XT + 4);
@@ -406,6 +412,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     if (small_c) {
         // one K-step per tap row, always visited
         if (active) {
+            const int wcells = window_cells(C_in, VL, kFloat);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (EV && ((rows_done >> r) & 1u)) continue;
@@ -434,7 +441,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             left >>= 4;
             if (--col_left == 0) { left = mask; col_left = cells >> 2; }
         };
-        const uint32_t row_pitch = (uint32_t)(a.row_pos * stride), pos = (uint32_t)((wp * 16 * NP + m) * stride);
+        const uint32_t pos = (uint32_t)((wp * 16 * NP + m) * stride);
         auto past = [&](int st) IDF_INLINE { return TAIL && 4 * st + g >= 3 * cells; };
         auto at = [&](int st) IDF_INLINE {
             int q = 4 * st + g;
@@ -448,11 +455,11 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 #pragma unroll 1
             for (int st = 0; st < n_ksteps; st += 2) {
                 fetch_w(wb); advance_w();
-                if (live()) kstep(wa, smem, at(st), row_pitch, next_tile(st));
+                if (live()) kstep(wa, smem, at(st), (uint32_t)row_pitch, next_tile(st));
                 __builtin_amdgcn_sched_barrier(0); // K-steps stay apart: nothing of a later one is held in registers early
                 next();
                 fetch_w(wa); advance_w();
-                if (live() && st + 1 < n_ksteps) kstep(wb, smem, at(st + 1), row_pitch, next_tile(st + 1));
+                if (live() && st + 1 < n_ksteps) kstep(wb, smem, at(st + 1), (uint32_t)row_pitch, next_tile(st + 1));
                 __builtin_amdgcn_sched_barrier(0);
                 next();
             }
@@ -463,7 +470,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     constexpr int NV = 4 * MC;                     // neighbouring channels a lane holds
     uint32_t next = 0, pooled = 0;                 // events for the next layer (high half: their taps), events the pool receives
     auto emit = [&](const uint32_t (&e)[MC * EB], int row_w, int x, int slot) IDF_INLINE {
-        unsigned char *d = (unsigned char *)a.dst + ((int64_t)stream * a.dst_stride + (int64_t)slot * row_w * C_out) * EB;
+        unsigned char *d = (unsigned char *)dst + ((int64_t)stream * dst_stride + (int64_t)slot * row_w * C_out) * EB;
         const uint32_t off = (uint32_t)((x * C_out + co0) * EB);
         if constexpr (MC * EB == 1) *at4(reinterpret_cast<uint32_t *>(d), off) = e[0];
         else if constexpr (MC * EB == 2) *at4(reinterpret_cast<i32x2 *>(d), off) = i32x2{(int)e[0], (int)e[1]};
@@ -474,7 +481,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         }
     };
     auto emit_out = [&](const st_t (&v)[NV], int row_w, int x, int slot) IDF_INLINE {        // last layer: 4-byte values, not rounded to the event type
-        st_t *d = (st_t *)a.dst + (int64_t)stream * a.dst_stride + (int64_t)slot * row_w * C_out;
+        st_t *d = (st_t *)dst + (int64_t)stream * dst_stride + (int64_t)slot * row_w * C_out;
 #pragma unroll
         for (int q = 0; q < MC; ++q)
             *at4(reinterpret_cast<acc_t *>(d), (uint32_t)((x * C_out + co0 + q * 4) * 4)) = acc_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
@@ -485,27 +492,27 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         for (int q = 0; q < MC * EB; ++q) n += (uint32_t)T::nonzero(e[q]);
         return n;
     };
-    auto slot_of = [&](int i) IDF_INLINE { int s = a.dst_slot0 + i; return s >= a.dst_rows ? s - a.dst_rows : s; };
+    auto slot_of = [&](int i) IDF_INLINE { int s = dst_slot0 + i; return s >= dst_rows ? s - dst_rows : s; };
 #pragma unroll
     for (int np = 0; np < NP; ++np) {
         const int x = xw + np * 16 + m;
         const bool ok = x < W && co_ok;
-        if (!a.pool) {
+        if (!pool) {
 #pragma unroll
             for (int j = 0; j < NR; ++j) {
                 if (j >= rows) break;
                 st_t v[NV];
 #pragma unroll
-                for (int q = 0; q < NV; ++q) v[q] = T::activate(acc[j][q >> 2][np][q & 3], a.act, a.shr, a.clamp_hi);
+                for (int q = 0; q < NV; ++q) v[q] = T::activate(acc[j][q >> 2][np][q & 3], act, shr, clamp_hi);
                 if (!ok) continue;
-                if (a.to_output) {
+                if (to_output) {
                     emit_out(v, W, x, slot_of(rg * NR + j));
                 } else {
                     uint32_t e[MC * EB];
 #pragma unroll
                     for (int q = 0; q < MC; ++q) T::pack4(v + 4 * q, e + q * EB);
                     emit(e, W, x, slot_of(rg * NR + j));
-                    if (a.next_layer >= 0) {
+                    if (next_layer >= 0) {
                         const uint32_t n = count(e);
                         next += n + ((n * (uint32_t)(taps_of(x, W) * taps_of(y + j, H))) << 16);
                     }
@@ -519,8 +526,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
                 if (j >= rows) break;
                 st_t u[NV];
 #pragma unroll
-                for (int q = 0; q < NV; ++q) u[q] = T::activate(acc[j][q >> 2][np][q & 3], a.act, a.shr, a.clamp_hi);
-                if (y + j >= a.pool_from && ok) {
+                for (int q = 0; q < NV; ++q) u[q] = T::activate(acc[j][q >> 2][np][q & 3], act, shr, clamp_hi);
+                if (y + j >= pool_from && ok) {
                     uint32_t e[MC * EB];
 #pragma unroll
                     for (int q = 0; q < MC; ++q) T::pack4(u + 4 * q, e + q * EB);
@@ -529,12 +536,12 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 #pragma unroll
                 for (int q = 0; q < NV; ++q) v[q] = j == 0 ? u[q] : (u[q] > v[q] ? u[q] : v[q]);
             }
-            if (NR == 2 && rows == 2 && a.pool_emit) {
+            if (NR == 2 && rows == 2 && pool_emit) {
 #pragma unroll
                 for (int q = 0; q < NV; ++q) { const st_t o = neighbour(v[q]); v[q] = o > v[q] ? o : v[q]; }
                 const int Wp = W >> 1, xp = x >> 1, yp = y >> 1;
                 if (ok && !(m & 1) && xp < Wp) {
-                    if (a.to_output) {
+                    if (to_output) {
                         // (a pool as the last layer: float32 nets only, whose events are the values)
                         emit_out(v, Wp, xp, slot_of(rg));
                     } else {
@@ -542,7 +549,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 #pragma unroll
                         for (int q = 0; q < MC; ++q) T::pack4(v + 4 * q, e + q * EB);
                         emit(e, Wp, xp, slot_of(rg));
-                        if (a.next_layer >= 0) {
+                        if (next_layer >= 0) {
                             const uint32_t n = count(e);
                             next += n + ((n * (uint32_t)(taps_of(xp, Wp) * taps_of(yp, H >> 1))) << 16);
                         }
@@ -551,24 +558,18 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             }
         }
     }
-    if (a.stats) {
-        if (a.next_layer >= 0) {
-            next = wave_sum(next);
-            if (lane == 0 && next) {
-                unsigned long long *d = a.stats + ((int64_t)stream * a.n_layers + a.next_layer) * 2;
-                atomicAdd(d, (unsigned long long)(next & 0xffffu));
-                atomicAdd(d + 1, (unsigned long long)(next >> 16) * (unsigned long long)a.next_c_out);
-            }
-        }
-        if (a.pool) {
-            pooled = wave_sum(pooled);
-            if (lane == 0 && pooled) atomicAdd(a.stats + ((int64_t)stream * a.n_layers + a.pool_layer) * 2, (unsigned long long)pooled);
-        }
+    if (stats) {
+        // (three lanes, one instruction: events of the next layer, the multiply-adds they stand for, events of the pool)
+        next = wave_sum(next);
+        pooled = wave_sum(pooled);
+        const uint64_t add = lane == 0 ? next & 0xffffu : lane == 1 ? (uint64_t)(next >> 16) * (uint32_t)next_c_out : pooled;
+        if (lane < 3 && add)
+            atomicAdd(stats + ((int64_t)stream * n_layers + (lane == 2 ? pool_layer : next_layer)) * 2 + (lane == 1), (unsigned long long)add);
     }
     // what the matrix instructions of this wave multiplied, zeros inside a live K-step included
     n_mfma += n_done * (uint32_t)(3 * rows * MC * NP);
-    if (a.issued && lane == 0 && n_mfma)
-        atomicAdd(a.issued + (int64_t)stream * a.n_layers + a.layer, (unsigned long long)n_mfma * (256ull * 4 * VL));
+    if (issued && lane == 0 && n_mfma)
+        atomicAdd(issued + (int64_t)stream * n_layers + layer, (unsigned long long)n_mfma * (256ull * 4 * VL));
 }
 
 // Several layers' steps in one launch (each on rows that were complete before the launch).  The grid is
@@ -586,9 +587,11 @@ __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatc
     const int tile = blockIdx.y, si = blockIdx.x;
     // (by every workgroup; us per pass, none / the first 256 / all: vgg-style net 3006 / 2925 / 2850, four streams out of step
     //  7256 / 7150 / 7030, float32 net 300 / 292 / 284)
-    request_arguments<sizeof(RowStep), kWaves>(&a);
-    if (tile >= a.tiles) return;
-    switch (a.form) {
+    request_arguments<sizeof(RowStep), kWaves>(&a, &sel);
+    const int tiles = a.tiles, form = a.form;
+    asm volatile("" ::"s"(tiles), "s"(form));
+    if (tile >= tiles) return;
+    switch (form) {
     case kRowTake: take_row<T>(a, sel, tile, si); break;
     case kRowSmall1: conv_rows<T, 1, 1, 1, EV, TAIL>(a, sel, tile, si); break;
     case kRowSmall2: conv_rows<T, 1, 1, 2, EV, TAIL>(a, sel, tile, si); break;
@@ -600,12 +603,11 @@ __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatc
 int form_np(int form) { return form == kRowWide2 ? 2 : 1; }
 int form_rows(int form) { return form == kRowSmall1 ? 1 : 2; }
 
-size_t step_lds(int prec, const RowStep &a)
+size_t step_lds(const RowStep &a)
 {
     if (a.form == kRowTake) return 0;
-    const int xt = (16 * form_np(a.form) * kWaves) >> a.wc_log, rows = form_rows(a.form) + 2;
-    if (a.cells == 0) return (size_t)rows * xt * cell_stride(window_cells(a.c_in, conv3x3_mfma_vl(prec), prec != IDF_PREC_I8)) * 16;
-    return (size_t)rows * a.row_pos * cell_stride(a.cells) * 16;
+    const int rows = form_rows(a.form) + 2;
+    return (size_t)rows * a.row_pitch;
 }
 
 template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc)
@@ -618,7 +620,7 @@ template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const Str
         tiles = std::max(tiles, a.tiles);
         wide = wide || a.form == kRowWide2;
         tail = tail || (prec != IDF_PREC_I8 && a.form != kRowTake && (a.cells & 3));
-        size_t need = step_lds(prec, a);
+        size_t need = step_lds(a);
         if (a.ev_limit > 0) {
             events = true;
             need = ((need + 15) & ~(size_t)15) + event_lds_bytes(form_rows(a.form), (16 * kWaves) >> a.wc_log, 16 << a.wc_log, a.c_in);
@@ -698,6 +700,11 @@ void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, bool narrow, Row
     a.nb = ((xt + 2) * cells + 63) / 64;
     a.row_pos = (a.nb * 64 + cells - 1) / cells;
     a.cells_rcp = (unsigned)((65536 + cells - 1) / cells);
+    a.stride = cell_stride(a.cells ? cells : window_cells(g.c_in, vl, prec != IDF_PREC_I8)) * 16; a.row_pitch = (a.cells ? a.row_pos : xt) * a.stride;
+    const bool single = g.c_out == 16;
+    a.n_ct = n_ct; a.co_g = single ? 4 : 8;
+    a.n_ksteps = a.cells ? (3 * a.cells + 3) / 4 : 1;
+    a.w_kstep = single ? 3 * 1024 : (unsigned)((g.c_out + 31) / 32) * 6144; a.w_ky = single ? 1024 : 2048;
 }
 
 bool conv3x3_mfma_split(RowStep &first, RowStep &rest)

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include "idf.h"
+#include "idf_common.h"
 
 namespace idf {
 
@@ -123,8 +124,9 @@ template <class V> __device__ __forceinline__ V neighbour(V v)
 }
 
 // Arguments of a launch on their way to the scalar cache, a few of their 64-byte lines by each wave of the workgroup: met one
-// after the other, each line would be a trip to memory of its own.
-template <int BYTES, int WAVES> __device__ __forceinline__ void request_arguments(const void __attribute__((address_space(4))) *args)
+// after the other, each line would be a trip to memory of its own.  sel: the launch's selection of streams, if it lies elsewhere (its
+// first line only).
+template <int BYTES, int WAVES> __device__ __forceinline__ void request_arguments(const void __attribute__((address_space(4))) *args, const StreamSel *sel = nullptr)
 {
     typedef const __attribute__((address_space(4))) int Word;
     constexpr int N = (BYTES / 64 + WAVES - 1) / WAVES;
@@ -135,6 +137,7 @@ template <int BYTES, int WAVES> __device__ __forceinline__ void request_argument
         const int at = (wave + q * WAVES) * 64;
         w[q] = ((Word *)args)[(at < BYTES ? at : 0) / 4];
     }
+    if (sel) asm volatile("" ::"s"(sel->base));
 #pragma unroll
     for (int q = 0; q < N; ++q) asm volatile("" ::"s"(w[q]));
 }
