@@ -138,22 +138,30 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 
     // ---- weights -------------------------------------------------------------------------------------
     // [K-step][block of 32 channels][ky][tile of the pair][lane][16 bytes]  (one tile of channels: [K-step][ky][lane][16])
-    const unsigned char *wp_next = (const unsigned char *)wfrag + (active ? (ct0 >> 1) * 6144 + (MC == 1 ? (ct0 & 1) * 1024 : 0) : 0);
-    const uint32_t w_lane = (uint32_t)lane * 16;
+    constexpr int D = 3;                           // K-steps whose weights are on their way
+    constexpr int D0 = NP == 2 ? 1 : D;            // of those, the ones asked for before the rows (as registers allow)
+    const unsigned char *w_base[3];
+    {
+        const unsigned char *first = (const unsigned char *)wfrag + (active ? (ct0 >> 1) * 6144 + (MC == 1 ? (ct0 & 1) * 1024 : 0) : 0);
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) w_base[ky] = first + ky * w_ky;
+    }
+    uint32_t w_off = (uint32_t)lane * 16;
+    int ks_left = n_ksteps;                        // K-steps whose weights have not been asked for
     auto fetch_w = [&](i32x4 (&w)[NW]) IDF_INLINE {
 #pragma unroll
         for (int ky = 0; ky < 3; ++ky)
 #pragma unroll
-            for (int mc = 0; mc < MC; ++mc)
-                w[ky * MC + mc] = *at4(reinterpret_cast<const i32x4 *>(wp_next), w_lane + (MC == 2 ? ky * 2048 + mc * 1024 : ky * w_ky));
+            for (int mc = 0; mc < MC; ++mc) w[ky * MC + mc] = at4(reinterpret_cast<const i32x4 *>(w_base[ky]), w_off)[mc * 64];
+        w_off += --ks_left > 0 ? w_kstep : 0u;     // past the end the last one is simply fetched again
     };
-    int ks_left = n_ksteps;                        // K-steps whose weights have not been asked for
-    auto advance_w = [&]() IDF_INLINE { if (--ks_left > 0) wp_next += w_kstep; };         // past the end the last one is simply fetched again
-
     acc_t acc[NR][MC][NP], start[MC];
-    i32x4 wa[NW], wb[NW];
-    fetch_w(wa);                                   // (where rows lie is worked out while the first are on their way)
-    advance_w();
+    i32x4 w[D][NW];
+#pragma unroll
+    for (int d = 0; d < D0; ++d) {                 // (where rows lie is worked out while these are on their way)
+        if (d > 0 && small_c) break;
+        fetch_w(w[d]);
+    }
 #pragma unroll
     for (int mc = 0; mc < MC; ++mc) {
         start[mc] = acc_t{0, 0, 0, 0};
@@ -184,46 +192,50 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         constexpr int kGroup = NP == 2 ? 9 : 3;    // blocks that are asked for without a look at how many there are
         static_assert(kLoads % kGroup == 0, "whole groups");
         const int first = (x0 - 1) * cells * 16 + lane * 16, last = row_bytes - 16;      // this lane's first cell, the row's last
-        const bool edge = x0 == 0 || x0 + XT >= W || !there;
+        const bool edge = x0 == 0 || x0 + XT >= W;
         unsigned char *row = smem + wave * row_pitch;
         unsigned long long mask = 0;               // bit c: cell c holds an event somewhere in the stretch
-        for (int b0 = 0; b0 < nb; b0 += kLoads) {
-            i32x4 tv[kLoads];
-#pragma unroll
-            for (int g0 = 0; g0 < kLoads; g0 += kGroup) {
-                if (b0 + g0 >= nb) break;
-#pragma unroll
-                for (int b = g0; b < g0 + kGroup; ++b)
-                    tv[b] = *at4(reinterpret_cast<const i32x4 *>(my_row), (uint32_t)min(max(first + (b0 + b) * 1024, 0), last));
-            }
-            if (wave < R) {
-                int any = 0;
+        auto place = [&](int b) IDF_INLINE {       // of this lane's cell of block b
+            const uint32_t i = (uint32_t)(b * 64 + lane);
+            return reinterpret_cast<i32x4 *>(row + __umul24(__umul24(i, cells_rcp) >> 16, (uint32_t)(stride - cells * 16)) + i * 16);
+        };
+        if (there) {
+            int any = 0;
+            for (int b0 = 0; b0 < nb; b0 += kLoads) {
+                i32x4 v[kLoads];
 #pragma unroll
                 for (int g0 = 0; g0 < kLoads; g0 += kGroup) {
                     if (b0 + g0 >= nb) break;
-                    if (edge) {
 #pragma unroll
-                        for (int b = g0; b < g0 + kGroup; ++b)
-                            if (!there || (uint32_t)(first + (b0 + b) * 1024) > (uint32_t)last) tv[b] = i32x4{0, 0, 0, 0};
-                    }
+                    for (int b = g0; b < g0 + kGroup; ++b)
+                        v[b] = *at4(reinterpret_cast<const i32x4 *>(my_row), (uint32_t)min(max(first + (b0 + b) * 1024, 0), last));
+                }
 #pragma unroll
-                    for (int b = g0; b < g0 + kGroup; ++b) {
-                        if (b0 + b >= nb) break;
-                        const uint32_t i = (uint32_t)((b0 + b) * 64 + lane), p = __umul24(i, cells_rcp) >> 16;
-                        *reinterpret_cast<i32x4 *>(row + __umul24(p, (uint32_t)(stride - cells * 16)) + i * 16) = tv[b];
-                        any |= T::or_of(tv[b]);
-                    }
+                for (int b = 0; b < kLoads; ++b) {
+                    if (b0 + b >= nb) break;
+                    *place(b0 + b) = v[b];
+                    const int o = T::or_of(v[b]);
+                    any |= edge && (uint32_t)(first + (b0 + b) * 1024) > (uint32_t)last ? 0 : o;
                 }
-                unsigned long long bal = __ballot(any != 0);
-                if ((cells & (cells - 1)) == 0) {  // a lane has had one and the same cell throughout
-                    for (int w = 32; w >= cells; w >>= 1) bal |= bal >> w;
-                } else {
-                    bal = bal ? ~0ull : 0ull;
-                }
-                mask |= bal;
             }
+            mask = __ballot(any != 0);
+            if ((cells & (cells - 1)) == 0) {      // a lane has had one and the same cell throughout
+                for (int c = 32; c >= cells; c >>= 1) mask |= mask >> c;
+            } else {
+                mask = mask ? ~0ull : 0ull;
+            }
+            // positions outside the row
+            if (x0 == 0)
+                for (int c = lane; c < cells; c += 64) *reinterpret_cast<i32x4 *>(row + c * 16) = i32x4{0, 0, 0, 0};
+            if (x0 + XT >= W)
+                for (int b = ((W - x0 + 1) * cells) >> 6; b < nb; ++b)
+                    if (first + b * 1024 > last) *place(b) = i32x4{0, 0, 0, 0};
+        } else if (wave < R) {
+            for (int b = 0; b < nb; ++b) *place(b) = i32x4{0, 0, 0, 0};
         }
         if (lane == 0) occ[wave] = mask;
+#pragma unroll
+        for (int d = D0; d < D; ++d) fetch_w(w[d]);
         // a cell of zeros in the row's next position (there is one: 64 divides no such stretch)
         if (TAIL && (cells & 3) && wave < R && lane == 0) *reinterpret_cast<i32x4 *>(row + (XT + 2) * stride) = i32x4{0, 0, 0, 0};
     } else {
@@ -392,23 +404,6 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
             }
     };
 
-    // One K-step with its weights in w: row by row, a row's cells asked for while the row before is multiplied.
-    // off: this lane's cell of the step in the first input row.
-    auto kstep = [&](const i32x4 (&w)[NW], const unsigned char *buf, uint32_t off, uint32_t row_pitch, int np_pitch) IDF_INLINE {
-        i32x4 x[2][NP];
-#pragma unroll
-        for (int np = 0; np < NP; ++np) x[0][np] = *reinterpret_cast<const i32x4 *>(buf + off + np * np_pitch);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (r + 1 < R) {
-#pragma unroll
-                for (int np = 0; np < NP; ++np)
-                    x[(r + 1) & 1][np] = *reinterpret_cast<const i32x4 *>(buf + off + (r + 1) * row_pitch + np * np_pitch);
-            }
-            deliver(w, x[r & 1], r);
-        }
-        ++n_done;
-    };
     if (small_c) {
         // one K-step per tap row, always visited
         if (active) {
@@ -421,57 +416,116 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 #pragma unroll
                 for (int np = 0; np < NP; ++np)
                     x[np] = *reinterpret_cast<const i32x4 *>(smem + (r * XT + wp * 16 * NP + np * 16 + m) * wstride + (kFloat || g < wcells ? g : wcells - 1) * 16);
-                deliver(wa, x, r);
+                deliver(w[0], x, r);
                 n_mfma += (uint32_t)(((r <= 2) + (NR == 2 && r >= 1 && rows == 2)) * MC * NP);
             }
         }
-    } else if (active) {
-        // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column.  Past the end the
-        // weights are zero: the last one again, or (TAIL) a cell of zeros.
-        unsigned long long mask = 0;
+    }
+    // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column.  Past the end the
+    // weights are zero: the last one again, or (TAIL) a cell of zeros.
+    unsigned long long mask = 0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w)
-            if (w < R && !(EV && ((rows_done >> w) & 1u))) mask |= occ[w];
-        mask = (unsigned long long)(uint32_t)uni((int)(mask >> 32)) << 32 | (uint32_t)uni((int)mask);
-        const bool by_cells = (cells & 3) == 0;    // every K-step lies in one tap column: its four cells have bits of their own
-        unsigned long long left = mask;
-        int col_left = by_cells ? cells >> 2 : 1 << 30;       // K-steps to the end of the tap column
-        auto live = [&]() IDF_INLINE { return by_cells ? ((uint32_t)left & 0xfu) != 0 : mask != 0; };
-        auto next = [&]() IDF_INLINE {
-            left >>= 4;
-            if (--col_left == 0) { left = mask; col_left = cells >> 2; }
+    for (int w = 0; w < kWaves; ++w)
+        if (w < R && !(EV && ((rows_done >> w) & 1u))) mask |= occ[w];
+    mask = (unsigned long long)(uint32_t)uni((int)(mask >> 32)) << 32 | (uint32_t)uni((int)mask);
+    const bool by_cells = (cells & 3) == 0;    // every K-step lies in one tap column: its four cells have bits of their own
+    const uint32_t pos = (uint32_t)((wp * 16 * NP + m) * stride);
+    // With events in every K-step (bit 4 i of the mask's cells 4 i .. 4 i + 3) they go without a look at the mask: three K-steps' weights
+    // and one K-step's cells ahead, and as few instructions in between as possible, which is what bounds a single wave (75 between
+    // the six matrix instructions of a narrow K-step took 460 cycles, 35 take 210; wide tiles 885 -> 580, of which 384 are matrix
+    // instructions.  Deeper requests alone, with the instructions as they were, gave nothing).
+    // us per image before -> after: vgg-style net 2576 -> 2431, four streams out of step 5548 -> 5000, f32 net 257 -> 247.
+    const unsigned long long some = (mask | mask >> 1 | mask >> 2 | mask >> 3) & 0x1111111111111111ull;
+    const bool dense = by_cells && !small_c && (some << (64 - cells)) == 0x1111111111111111ull << (64 - cells);
+    // (three blocks one after the other, of which one runs.  As branches of one another each would hold the first weights for
+    // the others, 72 registers too many; the empty statement keeps them apart.)
+    int n_dense = active && dense ? n_ksteps : 0, n_sparse = active && !small_c && !dense && mask ? n_ksteps : 0;
+    asm volatile("" : "+s"(n_dense), "+s"(n_sparse));
+    if (n_dense > 0) {
+        i32x4 x[R][NP];
+        uint32_t at = pos + (uint32_t)g * 16;
+        auto read_row = [&](int r) IDF_INLINE {
+#pragma unroll
+            for (int np = 0; np < NP; ++np) x[r][np] = *reinterpret_cast<const i32x4 *>(smem + (at + (uint32_t)(r * row_pitch + np * 16 * stride)));
         };
-        const uint32_t pos = (uint32_t)((wp * 16 * NP + m) * stride);
-        auto past = [&](int st) IDF_INLINE { return TAIL && 4 * st + g >= 3 * cells; };
-        auto at = [&](int st) IDF_INLINE {
+#pragma unroll
+        for (int r = 0; r < R; ++r) read_row(r);
+        // A row's cells make room for those of the next K-step where they have been used.
+        int left = n_dense, col = cells >> 2;
+        const uint32_t over = (uint32_t)(stride - cells * 16);
+#pragma unroll 1
+        for (; left > 0; left -= D) {          // (three tap columns: whole rounds)
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                if (d < D - 1 || left > D) {       // (not past the end)
+                    at += 64u;
+                    if (--col == 0) { at += over; col = cells >> 2; }
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    deliver(w[d], x[r], r);
+                    read_row(r);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                fetch_w(w[d]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        n_done = n_dense;
+    }
+    if (n_sparse > 0) {
+        auto kstep = [&](const i32x4 (&wv)[NW], int st) IDF_INLINE {
             int q = 4 * st + g;
+            const bool past = TAIL && q >= 3 * cells;
             q = q < 3 * cells ? q : 3 * cells - 1;
             const int kx = (q >= cells) + (q >= 2 * cells);
-            const uint32_t off = pos + (uint32_t)(kx * stride + (q - kx * cells) * 16);
-            return past(st) ? (uint32_t)((XT + 2) * stride) : off;
+            const uint32_t off = past ? (uint32_t)((XT + 2) * stride) : pos + (uint32_t)(kx * stride + (q - kx * cells) * 16);
+            const uint32_t np_pitch = past ? 0u : (uint32_t)(16 * stride);
+            i32x4 x[R][NP];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int np = 0; np < NP; ++np) x[r][np] = *reinterpret_cast<const i32x4 *>(smem + off + r * row_pitch + np * np_pitch);
+#pragma unroll
+            for (int r = 0; r < R; ++r) deliver(wv, x[r], r);
+            ++n_done;
         };
-        auto next_tile = [&](int st) IDF_INLINE { return past(st) ? 0 : 16 * stride; };
-        if (mask)
+        unsigned long long rest = mask;
+        int col_left = by_cells ? cells >> 2 : 1 << 30;       // K-steps to the end of the tap column
+        auto live = [&]() IDF_INLINE { return by_cells ? ((uint32_t)rest & 0xfu) != 0 : true; };
+        auto next = [&]() IDF_INLINE {
+            rest >>= 4;
+            if (--col_left == 0) { rest = mask; col_left = cells >> 2; }
+        };
+        // (the first two have their weights; what the prologue asked for beyond them is asked for again)
+        if (D > 2) { ks_left = n_ksteps > 2 ? n_ksteps - 2 : 0; w_off = (uint32_t)lane * 16 + (uint32_t)(n_ksteps > 2 ? 2 : n_ksteps - 1) * w_kstep; }
 #pragma unroll 1
-            for (int st = 0; st < n_ksteps; st += 2) {
-                fetch_w(wb); advance_w();
-                if (live()) kstep(wa, smem, at(st), (uint32_t)row_pitch, next_tile(st));
-                __builtin_amdgcn_sched_barrier(0); // K-steps stay apart: nothing of a later one is held in registers early
-                next();
-                fetch_w(wa); advance_w();
-                if (live() && st + 1 < n_ksteps) kstep(wb, smem, at(st + 1), (uint32_t)row_pitch, next_tile(st + 1));
-                __builtin_amdgcn_sched_barrier(0);
-                next();
-            }
+        for (int st = 0;; st += 2) {
+            if (live()) kstep(w[0], st);
+            if (st + 1 >= n_ksteps) break;
+            fetch_w(w[0]);
+            next();
+            __builtin_amdgcn_sched_barrier(0);  // K-steps stay apart: nothing of a later one is held in registers early
+            if (live()) kstep(w[1], st + 1);
+            if (st + 2 >= n_ksteps) break;
+            fetch_w(w[1]);
+            next();
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     if (!active) return;
 
     // ---- the rows are final: activate, emit, count ---------------------------------------------------------
+    // (a lane's place is worked out again rather than held in registers through the contraction: the empty statement hides that it
+    // is the same value)
+    int id = tid;
+    asm volatile("" : "+v"(id));
+    const int me = id & 15, co1 = (ct0 >> 1) * 32 + (id >> 4 & 3) * co_g + (MC == 1 ? (ct0 & 1) * 4 : 0);
     constexpr int NV = 4 * MC;                     // neighbouring channels a lane holds
     uint32_t next = 0, pooled = 0;                 // events for the next layer (high half: their taps), events the pool receives
     auto emit = [&](const uint32_t (&e)[MC * EB], int row_w, int x, int slot) IDF_INLINE {
         unsigned char *d = (unsigned char *)dst + ((int64_t)stream * dst_stride + (int64_t)slot * row_w * C_out) * EB;
-        const uint32_t off = (uint32_t)((x * C_out + co0) * EB);
+        const uint32_t off = (uint32_t)((x * C_out + co1) * EB);
         if constexpr (MC * EB == 1) *at4(reinterpret_cast<uint32_t *>(d), off) = e[0];
         else if constexpr (MC * EB == 2) *at4(reinterpret_cast<i32x2 *>(d), off) = i32x2{(int)e[0], (int)e[1]};
         else {
@@ -484,7 +538,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         st_t *d = (st_t *)dst + (int64_t)stream * dst_stride + (int64_t)slot * row_w * C_out;
 #pragma unroll
         for (int q = 0; q < MC; ++q)
-            *at4(reinterpret_cast<acc_t *>(d), (uint32_t)((x * C_out + co0 + q * 4) * 4)) = acc_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+            *at4(reinterpret_cast<acc_t *>(d), (uint32_t)((x * C_out + co1 + q * 4) * 4)) = acc_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
     };
     auto count = [&](const uint32_t (&e)[MC * EB]) IDF_INLINE {
         uint32_t n = 0;
@@ -495,8 +549,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     auto slot_of = [&](int i) IDF_INLINE { int s = dst_slot0 + i; return s >= dst_rows ? s - dst_rows : s; };
 #pragma unroll
     for (int np = 0; np < NP; ++np) {
-        const int x = xw + np * 16 + m;
-        const bool ok = x < W && co_ok;
+        const int x = xw + np * 16 + me;
+        const bool ok = x < W && co1 < C_out;
         if (!pool) {
 #pragma unroll
             for (int j = 0; j < NR; ++j) {
@@ -540,7 +594,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 #pragma unroll
                 for (int q = 0; q < NV; ++q) { const st_t o = neighbour(v[q]); v[q] = o > v[q] ? o : v[q]; }
                 const int Wp = W >> 1, xp = x >> 1, yp = y >> 1;
-                if (ok && !(m & 1) && xp < Wp) {
+                if (ok && !(me & 1) && xp < Wp) {
                     if (to_output) {
                         // (a pool as the last layer: float32 nets only, whose events are the values)
                         emit_out(v, Wp, xp, slot_of(rg));
@@ -562,13 +616,13 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         // (three lanes, one instruction: events of the next layer, the multiply-adds they stand for, events of the pool)
         next = wave_sum(next);
         pooled = wave_sum(pooled);
-        const uint64_t add = lane == 0 ? next & 0xffffu : lane == 1 ? (uint64_t)(next >> 16) * (uint32_t)next_c_out : pooled;
-        if (lane < 3 && add)
-            atomicAdd(stats + ((int64_t)stream * n_layers + (lane == 2 ? pool_layer : next_layer)) * 2 + (lane == 1), (unsigned long long)add);
+        const uint64_t add = (id & 63) == 0 ? next & 0xffffu : (id & 63) == 1 ? (uint64_t)(next >> 16) * (uint32_t)next_c_out : pooled;
+        if ((id & 63) < 3 && add)
+            atomicAdd(stats + ((int64_t)stream * n_layers + ((id & 63) == 2 ? pool_layer : next_layer)) * 2 + ((id & 63) == 1), (unsigned long long)add);
     }
     // what the matrix instructions of this wave multiplied, zeros inside a live K-step included
     n_mfma += n_done * (uint32_t)(3 * rows * MC * NP);
-    if (issued && lane == 0 && n_mfma)
+    if (issued && (id & 63) == 0 && n_mfma)
         atomicAdd(issued + (int64_t)stream * n_layers + layer, (unsigned long long)n_mfma * (256ull * 4 * VL));
 }
 
