@@ -279,27 +279,36 @@ struct RingMove {
 constexpr int kPassMax = 16;     // conv layers at most
 constexpr int kPassGroups = 4;   // groups of four rows of a layer that a band reaches at most
 struct EagerPassStep {           // a conv layer and the 2x2 pool behind it, if there is one
-    int layer;
-    int n_in;                    // delta rows that arrive
-    int row0, n_groups;          // first row of the first group; groups
-    int band0;                   // row row0 - 1, counted from the band's first
-    uint32_t rows_in;            // bit i: row row0 - 1 + i is in the band
-    uint32_t rows_on, rows_old;  // bit i: row row0 + i of the layer is reached / has a state already
-    int w, c_in, c_out;
-    int act, shr, clamp_hi;
-    int emit;                    // differences are passed on
-    int out_first;               // place of row row0 (pool: of row row0 / 2) among the rows passed on (may be negative)
-    int pool, out_w;             // out_w: positions of the rows passed on
-    uint32_t pool_on;            // bit i: pooled row row0 / 2 + i is looked at
-    uint32_t c_off[4 * kPassGroups];           // bytes from a stream's first row kept to the one that holds each row
-    uint32_t pool_slots[kPassGroups];          // of the pooled rows, two to a word: among those kept, the one that holds each row
-    uint32_t c_stride, ann_stride;             // elements per stream
-    int n_ksteps;                // (set with the layout, as all that stands behind the pointers)
-    void *c, *ann;               // ann: of the pool; else of a level that is kept whole, or null: whoever wants them takes f of the state
-    const void *w_frag;
+    // (in the order a wave needs them, and as it needs them: every instruction of a layer is issued by all sixteen waves)
+    int tasks, n_ct, n_xt;       // tiles of 16 channels x 16 positions x 4 rows; of channels, of positions
     unsigned ct_rcp, xt_rcp;
-    int n_xt, n_ct, cells;
-    int lds_in, lds_out, in_pitch, in_stride, out_pitch, out_stride, out_rows;
+    int w, c_out, co_g;          // co_g: channels from one group of lanes to the next
+    int n_ksteps;
+    uint32_t w_kstep, w_ky;      // bytes from one K-step, and one tap row, to the next in the packed weights
+    uint32_t c_stride;           // elements per stream
+    void *c;
+    const void *w_frag;
+
+    uint32_t rows_in;            // bit i: row row0 - 1 + i is in the band that arrives
+    uint32_t rows_on, rows_old;  // bit i: row row0 + i of the layer is reached / has a state already
+    int band0;                   // row row0 - 1, counted from the band's first
+    int cells, lds_in, in_pitch, in_stride;
+    int layer, emit;             // emit: differences are passed on
+    int act_none, act_lo, act_hi, act_shr;     // float32: no activation; int8: one shift and two bounds serve all three kinds
+    int pool, out_w;             // out_w: positions of the rows passed on
+
+    int lds_out, out_first;      // out_first: place of row row0 (pool: of row row0 / 2) among the rows passed on (may be negative)
+    int out_pitch, out_stride, out_rows;
+    int out_done, out_end;       // bytes of a row passed on: from where on no lane of the tiles writes, and its length as far as it is read
+    uint32_t ann_stride;         // elements per stream
+    void *ann;                   // of the pool; else of a level that is kept whole, or null: whoever wants them takes f of the state
+    uint32_t row_bytes;          // of a row of state
+    uint32_t pool_on;            // bit i: pooled row row0 / 2 + i is looked at
+    int row0;                    // first row of the first group
+    int n_groups, n_in, c_in;    // groups of four rows; delta rows that arrive
+
+    uint16_t c_slot[4 * kPassGroups];          // of each row, among those kept
+    uint32_t pool_slots[kPassGroups];          // of the pooled rows, two to a word
 };
 struct EagerPass {
     int n, n_layers;

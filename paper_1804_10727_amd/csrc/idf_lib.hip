@@ -1389,10 +1389,12 @@ bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int
         L.n_groups = (int)((hi[lv] - L.row0 + 3) / 4);
         if (L.n_groups > kPassGroups) return false;
         L.band0 = L.row0 - 1 - (int)lo[l];
-        L.w = g.w_out; L.c_in = g.c_in; L.c_out = g.c_out; L.act = g.act; L.shr = g.shr; L.clamp_hi = g.clamp_hi;
-        const uint32_t row_bytes = (uint32_t)E.row_elems[lv] * 4;
-        // (offsets within a stream's map are 32 bits, rows of a pool's ring 16)
-        if (std::max(E.cd_rows[lv], E.ann_rows[lv]) * E.row_elems[lv] * 4 > UINT32_MAX) return false;
+        L.w = g.w_out; L.c_in = g.c_in; L.c_out = g.c_out;
+        const bool clamps = g.act == IDF_ACT_RELU_SHR_CLAMP;
+        L.act_none = g.act == IDF_ACT_NONE; L.act_lo = L.act_none ? INT32_MIN : 0; L.act_hi = clamps ? g.clamp_hi : INT32_MAX; L.act_shr = clamps ? g.shr : 0;
+        L.row_bytes = (uint32_t)E.row_elems[lv] * 4;
+        // (offsets within a stream's map are 32 bits, rows of a ring 16)
+        if (std::max(E.cd_rows[lv], E.ann_rows[lv]) * E.row_elems[lv] * 4 > UINT32_MAX || E.cd_rows[lv] > 1 << 16) return false;
         L.c = E.ws + E.c_off[lv]; L.c_stride = (uint32_t)(E.cd_rows[lv] * E.row_elems[lv]);
         for (int i = 0; i < 4 * L.n_groups + 2; ++i) {
             const int y = L.row0 + i;
@@ -1400,7 +1402,7 @@ bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int
             if (i == 4 * L.n_groups) { if (y >= lo[l] && y < hi[l]) L.rows_in |= 2u << i; break; }
             if (y >= lo[lv] && y < hi[lv]) L.rows_on |= 1u << i;
             if (y < std::min(seen_hi[lv], hi[lv])) L.rows_old |= 1u << i;
-            L.c_off[i] = (uint32_t)(y % E.cd_rows[lv]) * row_bytes;
+            L.c_slot[i] = (uint16_t)(y % E.cd_rows[lv]);
         }
         L.ann = lv < n ? nullptr : E.ws + E.ann_off[lv];
         L.ann_stride = (uint32_t)(E.ann_rows[lv] * E.row_elems[lv]);

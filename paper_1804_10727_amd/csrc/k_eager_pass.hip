@@ -15,7 +15,11 @@
 // instructions and about a hundred others per wave, one after the other.  Hence sixteen waves with small shares
 // (eight waves with all the rows of a band each took 1.3 times as long), one copy of the code for every layer,
 // which then stays in the instruction cache, and weights and state on their way before the barrier.
-// Measured per pushed row, layer by layer before: int8, 8 streams of 112 x 112, 37 us (170); float32, 256 streams of
+// With sixteen waves on four SIMDs an instruction of a wave takes its turn every 16 cycles or so, scalar ones included: a layer takes
+// as long as the instructions beside the matrix ones are many.  Hence one batch of arguments, worked out as far as the host can,
+// three-operand bounds, bytes packed and counted by the word, and rows that nothing reaches left out (int8 4173 -> 3866 us per
+// image of 112 x 112, eight streams; float32 unchanged).
+// Measured per pushed row, layer by layer before: int8, 8 streams of 112 x 112, 34.5 us (170); float32, 256 streams of
 // 32 x 32, 35 us (112), of which 18 us are matrix instructions.
 #include <algorithm>
 #include <type_traits>
@@ -105,123 +109,120 @@ template <class T> __device__ __forceinline__ void pass_input(PassArgs &a, PassS
 }
 
 // ---- one conv layer, and the 2x2 max-pool behind it ------------------------------------------------------
-template <class T> struct Activation {
-    using st_t = typename T::st_t;
-    st_t lo, hi;
-    int shr;
-    bool none;
-    __device__ __forceinline__ explicit Activation(PassStep &L)
-    {
-        none = L.act == IDF_ACT_NONE;
-        lo = 0; hi = 0; shr = 0;
-        if constexpr (T::EB == 1) {                // one shift and two bounds serve all three kinds
-            lo = none ? INT32_MIN : 0;
-            hi = L.act == IDF_ACT_RELU_SHR_CLAMP ? L.clamp_hi : INT32_MAX;
-            shr = L.act == IDF_ACT_RELU_SHR_CLAMP ? L.shr : 0;
-        }
-    }
-    __device__ __forceinline__ st_t operator()(st_t c) const
-    {
-        if constexpr (T::EB == 1) return min(max(c >> shr, lo), hi);
-        else return none ? c : fmaxf(c, 0.f);
-    }
-};
-
-template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassStep &L, int stream, uint32_t *events)
+template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassStep &L, int stream, uint32_t *all_events)
 {
     using acc_t = typename T::acc_t; using st_t = typename T::st_t;
+    constexpr bool kInt = T::EB == 1;
+    // All of the step in one batch (but for what depends on the group of rows): left to first use these were fifteen scalar loads one
+    // after the other, by each of sixteen waves.
+    const int tasks = L.tasks, n_ct = L.n_ct, n_xt = L.n_xt, W = L.w, C_out = L.c_out, co_g = L.co_g, n_ksteps = L.n_ksteps, band0 = L.band0;
+    const int cells = L.cells, lds_in = L.lds_in, in_pitch = L.in_pitch, in_stride = L.in_stride, layer = L.layer, emit = L.emit, pool = L.pool, out_w = L.out_w;
+    const int act_none = L.act_none, act_lo = L.act_lo, act_hi = L.act_hi, act_shr = L.act_shr, lds_out = L.lds_out, out_first = L.out_first;
+    const int out_pitch = L.out_pitch, out_stride = L.out_stride, out_rows = L.out_rows, out_done = L.out_done, out_end = L.out_end, row0 = L.row0, n_in = L.n_in;
+    const unsigned ct_rcp = L.ct_rcp, xt_rcp = L.xt_rcp;
+    const uint32_t w_kstep = L.w_kstep, w_ky = L.w_ky, c_stride = L.c_stride, rows_in = L.rows_in, rows_on = L.rows_on, rows_old = L.rows_old;
+    const uint32_t ann_stride = L.ann_stride, row_bytes = L.row_bytes, pool_on = L.pool_on;
+    void *c = L.c, *ann_map = L.ann;
+    const void *w_frag = L.w_frag;
+    asm volatile("" ::"s"(tasks), "s"(n_ct), "s"(n_xt), "s"(W), "s"(C_out), "s"(co_g), "s"(n_ksteps), "s"(band0), "s"(cells), "s"(lds_in), "s"(in_pitch),
+                 "s"(in_stride), "s"(layer), "s"(emit), "s"(pool), "s"(out_w), "s"(act_none), "s"(act_lo), "s"(act_hi), "s"(act_shr), "s"(ct_rcp), "s"(xt_rcp),
+                 "s"(w_kstep), "s"(w_ky), "s"(c_stride), "s"(rows_in), "s"(rows_on), "s"(rows_old));
+    asm volatile("" ::"s"(lds_out), "s"(out_first), "s"(out_pitch), "s"(out_stride), "s"(out_rows), "s"(out_done), "s"(out_end), "s"(row0), "s"(n_in), "s"(ann_stride),
+                 "s"(row_bytes), "s"(pool_on), "s"(c), "s"(ann_map), "s"(w_frag));
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6), m = lane & 15, g = lane >> 4;
-    const int W = L.w, C_out = L.c_out, n_ct = L.n_ct, n_xt = L.n_xt, tasks = n_ct * n_xt * L.n_groups;
-    const bool single = C_out == 16;
-    const uint32_t w_kstep = single ? 3 * 1024 : (uint32_t)((C_out + 31) >> 5) * 6144, w_ky = single ? 1024 : 2048;
-    st_t *c_map = (st_t *)L.c + (int64_t)stream * L.c_stride;
+    char *c_map = (char *)c + (int64_t)stream * c_stride * 4;
 
     acc_t old[4];                                  // states as they were
     i32x4 wq[kQueue][3];
-    const unsigned char *w_next = nullptr;
-    int ks_left = 0, xt = 0, gi = 0, x = 0, co0 = 0;
+    const unsigned char *w_base[3];
+    uint32_t w_off = 0;
+    int xt = 0, gi = 0, x = 0, co0 = 0;
     uint32_t cell = 0;                             // this lane's first channel, bytes into a row
-    uint32_t c_off[4];
+    uint32_t c_off[4];                             // bytes from a stream's first row kept to each row
     bool here = false;
     auto fetch_w = [&](i32x4 (&w)[3]) IDF_INLINE {
 #pragma unroll
-        for (int ky = 0; ky < 3; ++ky) w[ky] = *at4(reinterpret_cast<const i32x4 *>(w_next), (uint32_t)(lane * 16 + ky * w_ky));
-        if (--ks_left > 0) w_next += w_kstep;
+        for (int ky = 0; ky < 3; ++ky) w[ky] = *at4(reinterpret_cast<const i32x4 *>(w_base[ky]), w_off);
+        w_off += w_kstep;
     };
     // everything a task needs from memory is asked for before its cells are
     auto begin = [&](int t) IDF_INLINE {
-        const int rest = L.ct_rcp ? (int)__umulhi((unsigned)t, L.ct_rcp) : t, ct = t - rest * n_ct;
-        gi = L.xt_rcp ? (int)__umulhi((unsigned)rest, L.xt_rcp) : rest;
+        const int rest = (int)__umulhi((unsigned)t, ct_rcp) + (n_ct == 1 ? t : 0), ct = t - rest * n_ct;
+        gi = (int)__umulhi((unsigned)rest, xt_rcp) + (n_xt == 1 ? rest : 0);
         xt = rest - gi * n_xt;
+        const uint32_t s01 = ((const __attribute__((address_space(4))) uint32_t *)L.c_slot)[2 * gi], s23 = ((const __attribute__((address_space(4))) uint32_t *)L.c_slot)[2 * gi + 1];
+        const unsigned char *first = (const unsigned char *)w_frag + (ct >> 1) * 6144 + (ct & 1) * 1024;
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) w_base[ky] = first + ky * w_ky;
+        w_off = (uint32_t)lane * 16;
+#pragma unroll
+        for (int d = 0; d < kQueue; ++d)
+            if (d < n_ksteps) fetch_w(wq[d]);
         x = xt * 16 + m;
-        co0 = single ? g * 4 : (ct >> 1) * 32 + g * 8 + (ct & 1) * 4;
+        co0 = (ct >> 1) * 32 + (ct & 1) * 4 + g * co_g;
         here = x < W && co0 < C_out;
         cell = here ? (uint32_t)(x * C_out + co0) * 4 : 0;
-        w_next = (const unsigned char *)L.w_frag + (single ? 0 : (ct >> 1) * 6144 + (ct & 1) * 1024);
-        ks_left = L.n_ksteps;
-#pragma unroll
-        for (int d = 0; d < kQueue; ++d) fetch_w(wq[d]);        // past the end the last one again
+        c_off[0] = (s01 & 0xffffu) * row_bytes; c_off[1] = (s01 >> 16) * row_bytes;
+        c_off[2] = (s23 & 0xffffu) * row_bytes; c_off[3] = (s23 >> 16) * row_bytes;
         // (rows without a state are read like the others: their places exist)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            c_off[j] = L.c_off[gi * 4 + j];
-            old[j] = *at4(reinterpret_cast<const acc_t *>((const char *)c_map + c_off[j]), cell);
+        for (int j = 0; j < 4; ++j) old[j] = *at4(reinterpret_cast<const acc_t *>(c_map + c_off[j]), cell);
+    };
+    auto act = [&](st_t v) IDF_INLINE {
+        if constexpr (kInt) {                      // (the bounds are in order: one instruction)
+            int32_t r;
+            asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"((int32_t)v >> act_shr), "s"(act_lo), "v"(act_hi));
+            return (st_t)r;
+        } else {
+            return act_none ? v : fmaxf(v, 0.f);
         }
     };
     int t = wave;
     if (t < tasks) begin(t);
     lds_barrier();                                 // the band is there, and nobody reads what this layer overwrites any more
-    const Activation<T> act(L);
-    if (L.emit) {
+    if (emit) {
         // what is passed on has zeros in front of each row, and behind it as far as no lane of the tiles reaches
-        const int cells_out = L.out_stride >> 4, end = L.out_pitch / L.out_stride, done = L.pool ? L.out_w : 16 * n_xt;
-        for (int r = wave; r < L.out_rows; r += kPassWaves) {
-            unsigned char *row = pass_smem + L.lds_out + r * L.out_pitch;
-            for (int c = lane; c < cells_out; c += 64) {
-                *reinterpret_cast<i32x4 *>(row + c * 16) = i32x4{0, 0, 0, 0};
-                for (int p = done + 1; p < end; ++p) *reinterpret_cast<i32x4 *>(row + p * L.out_stride + c * 16) = i32x4{0, 0, 0, 0};
-            }
+        for (int r = wave; r < out_rows; r += kPassWaves) {
+            unsigned char *row = pass_smem + lds_out + r * out_pitch;
+            for (int o = lane * 16; o < out_stride; o += 1024) *reinterpret_cast<i32x4 *>(row + o) = i32x4{0, 0, 0, 0};
+            for (int o = out_done + lane * 16; o < out_end; o += 1024) *reinterpret_cast<i32x4 *>(row + o) = i32x4{0, 0, 0, 0};
         }
     }
-    uint32_t ev = 0, ev_pool = 0;
+    const bool counts = layer + 1 < a.n_layers;
+    uint32_t ev = 0, ev_pool = 0;                  // (int8: of this lane; float32: of the wave)
     for (; t < tasks;) {
         acc_t acc[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = acc_t{0, 0, 0, 0};
+        const uint32_t in = rows_in >> (4 * gi);   // bit r: row r - 1 of the four (-1 .. 4) is in the band
         {
-            const int cells = L.cells, n_ksteps = L.n_ksteps, in_stride = L.in_stride;
-            const uint32_t rows_in = L.rows_in >> (4 * gi);    // bit r: row r - 1 of the four (-1 .. 4) is in the band
-            // where the six rows lie (those outside the band: somewhere inside)
-            const unsigned char *row[6];
+            const uint32_t base = (uint32_t)(lds_in + (xt * 16 + m) * in_stride);
+            uint32_t row[6];                       // where the six rows lie (those outside the band: somewhere inside)
 #pragma unroll
-            for (int r = 0; r < 6; ++r) {
-                int b = L.band0 + 4 * gi + r;
-                b = b < 0 ? 0 : (b >= L.n_in ? L.n_in - 1 : b);
-                row[r] = pass_smem + L.lds_in + b * L.in_pitch + (xt * 16 + m) * in_stride;
-            }
+            for (int r = 0; r < 6; ++r) row[r] = (uint32_t)(min(max(band0 + 4 * gi + r, 0), n_in - 1) * in_pitch);
+            // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column (past the end, where
+            // the weights are zero, the padding of the last position; int8: the last one again); few channels: the cells of the
+            // gathered window
+            auto at = [&](int st) IDF_INLINE {
+                int q = 4 * st + g;
+                if (cells == 0) return kInt ? base : base + (uint32_t)q * 16;        // (int8: one cell)
+                if (kInt) q = q < 3 * cells ? q : 3 * cells - 1;
+                return base + (uint32_t)(((q >= cells) + (q >= 2 * cells)) * (in_stride - cells * 16) + q * 16);
+            };
             auto kstep = [&](const i32x4 (&w)[3], uint32_t off) IDF_INLINE {
                 i32x4 xv[6];
 #pragma unroll
-                for (int r = 0; r < 6; ++r) xv[r] = *reinterpret_cast<const i32x4 *>(row[r] + off);
+                for (int r = 0; r < 6; ++r)
+                    xv[r] = *reinterpret_cast<const i32x4 *>(pass_smem + (off + row[r]));
 #pragma unroll
                 for (int r = 0; r < 6; ++r) {
-                    if (!((rows_in >> r) & 1u)) continue;
+                    if (!((in >> r) & 1u)) continue;
 #pragma unroll
                     for (int e = 0; e < T::kInst; ++e)
 #pragma unroll
                         for (int ky = 0; ky < 3; ++ky)
                             if (r - ky >= 0 && r - ky < 4) acc[r - ky] = T::mfma(w[ky], xv[r], acc[r - ky], e);
                 }
-            };
-            // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column (past the end, where
-            // the weights are zero, the padding of the last position; int8: the last one again); few channels: the cells of the
-            // gathered window
-            auto at = [&](int st) IDF_INLINE {
-                int q = 4 * st + g;
-                if (cells == 0) return T::EB == 1 ? 0u : (uint32_t)q * 16;      // (int8: one cell)
-                if (T::EB == 1) q = q < 3 * cells ? q : 3 * cells - 1;
-                const int kx = (q >= cells) + (q >= 2 * cells);
-                return (uint32_t)(kx * in_stride + (q - kx * cells) * 16);
             };
 #pragma unroll 1
             for (int st = 0; st < n_ksteps; st += kQueue) {
@@ -235,73 +236,78 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassSt
             }
         }
         // the state moves on; what is announced is f of it, less f of what it was
-        const uint32_t on = L.rows_on >> (4 * gi), had = L.rows_old >> (4 * gi);
-        unsigned char *out = pass_smem + L.lds_out + L.out_first * L.out_pitch + co0 * T::EB;
-        const bool out_ok = L.emit && co0 < C_out;
-        auto count = [&](const st_t (&d)[4], uint32_t &n) IDF_INLINE {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) n += (uint32_t)__builtin_popcountll(__ballot(d[i] != 0));
-        };
-        auto pass_on = [&](const st_t (&d)[4], unsigned char *to) IDF_INLINE {
+        const uint32_t on = rows_on >> (4 * gi), had = rows_old >> (4 * gi);
+        const bool out_ok = emit && co0 < C_out;
+        unsigned char *out = pass_smem + lds_out + out_first * out_pitch + co0 * T::EB;
+        // the differences of four channels (zero beyond the row's end) are counted and passed on
+        auto deliver = [&](const acc_t &h_new, const acc_t &h_old, bool mine, bool count, uint32_t &n, unsigned char *to, bool pass) IDF_INLINE {
+            st_t d[4];
             uint32_t e[T::EB];
-            T::pack4(d, e);
-            if constexpr (T::EB == 1) *reinterpret_cast<uint32_t *>(to) = e[0];
-            else *reinterpret_cast<i32x4 *>(to) = i32x4{(int)e[0], (int)e[1], (int)e[2], (int)e[3]};
-        };
-        char *ann = L.ann && !L.pool ? (char *)L.ann + ((int64_t)stream * L.ann_stride + (int64_t)(L.row0 + 4 * gi) * W * C_out) * 4 : nullptr;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            acc_t h_new, h_old = {0, 0, 0, 0};
-            if ((had >> j) & 1u) {
+            for (int i = 0; i < 4; ++i) d[i] = h_new[i] - h_old[i];
+            if constexpr (kInt) {
+                T::pack4(d, e);
+                e[0] = mine ? e[0] : 0u;
+                if (count) n += (uint32_t)T::nonzero(e[0]);
+                if (pass) *reinterpret_cast<uint32_t *>(to) = e[0];
+            } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { acc[j][i] += old[j][i]; h_old[i] = act(old[j][i]); }
-            }
+                for (int i = 0; i < 4; ++i) d[i] = mine ? d[i] : (st_t)0;
+                if (count) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) h_new[i] = act(acc[j][i]);
-            if ((on >> j) & 1u) {
-                st_t d[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) d[i] = h_new[i] - h_old[i];
-                if (!here) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) d[i] = 0;
-                } else {
-                    *at4(reinterpret_cast<acc_t *>((char *)c_map + c_off[j]), cell) = acc[j];
-                    if (ann) *at4(reinterpret_cast<acc_t *>(ann + (int64_t)(j * W * C_out) * 4), cell) = h_new;
+                    for (int i = 0; i < 4; ++i) n += (uint32_t)__builtin_popcountll(__ballot(d[i] != 0));
                 }
-                if (L.layer + 1 < a.n_layers) count(d, ev);
-                if (!L.pool && out_ok) pass_on(d, out + (4 * gi + j) * L.out_pitch + (x + 1) * L.out_stride);
+                T::pack4(d, e);
+                if (pass) *reinterpret_cast<i32x4 *>(to) = i32x4{(int)e[0], (int)e[1], (int)e[2], (int)e[3]};
             }
-            // rows that have not been reached announce zero (and have nothing in acc or old)
-            acc[j] = h_new; old[j] = h_old;
-        }
-        if (L.pool) {
-            const bool mine = (x & 1) == 0 && (x >> 1) < L.out_w && co0 < C_out;
+        };
+        char *ann = ann_map && !pool ? (char *)ann_map + ((int64_t)stream * ann_stride + (int64_t)(row0 + 4 * gi) * W * C_out) * 4 : nullptr;
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                if (!((L.pool_on >> (2 * gi + p)) & 1u)) continue;
-                acc_t n;
-                st_t d[4];
+        for (int p = 0; p < 2; ++p) {
+            acc_t h_new[2], h_old[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int j = 2 * p + q;
+                h_new[q] = h_old[q] = acc_t{0, 0, 0, 0};       // (rows that have not been reached announce zero)
+                if (!(((on | (pool ? had : 0u)) >> j) & 1u)) continue;
+                if ((had >> j) & 1u) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { acc[j][i] += old[j][i]; h_old[q][i] = act(old[j][i]); }
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) h_new[q][i] = act(acc[j][i]);
+                if (!((on >> j) & 1u)) continue;
+                if (here) {
+                    *at4(reinterpret_cast<acc_t *>(c_map + c_off[j]), cell) = acc[j];
+                    if (ann) *at4(reinterpret_cast<acc_t *>(ann + (int64_t)(j * W * C_out) * 4), cell) = h_new[q];
+                }
+                deliver(h_new[q], h_old[q], here, counts, ev, out + (4 * gi + j) * out_pitch + (x + 1) * out_stride, !pool && out_ok);
+            }
+            if (pool && ((pool_on >> (2 * gi + p)) & 1u)) {
+                const bool mine = (x & 1) == 0 && (x >> 1) < out_w && co0 < C_out;
+                acc_t n, o;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const st_t nn = acc[2 * p][i] > acc[2 * p + 1][i] ? acc[2 * p][i] : acc[2 * p + 1][i];
-                    const st_t oo = old[2 * p][i] > old[2 * p + 1][i] ? old[2 * p][i] : old[2 * p + 1][i];
+                    const st_t nn = h_new[0][i] > h_new[1][i] ? h_new[0][i] : h_new[1][i], oo = h_old[0][i] > h_old[1][i] ? h_old[0][i] : h_old[1][i];
                     const st_t nx = neighbour(nn), ox = neighbour(oo);
                     n[i] = nn > nx ? nn : nx;
-                    d[i] = mine ? n[i] - (oo > ox ? oo : ox) : (st_t)0;
+                    o[i] = oo > ox ? oo : ox;
                 }
-                count(d, ev_pool);
-                if (mine) *at4(reinterpret_cast<acc_t *>((char *)L.ann + (int64_t)stream * L.ann_stride * 4 + (int64_t)((L.pool_slots[gi] >> p * 16) & 0xffffu) * (L.out_w * C_out * 4)),
+                if (mine) *at4(reinterpret_cast<acc_t *>((char *)ann_map + (int64_t)stream * ann_stride * 4 + (int64_t)((L.pool_slots[gi] >> p * 16) & 0xffffu) * (out_w * C_out * 4)),
                                (uint32_t)((x >> 1) * C_out + co0) * 4) = n;
-                if (L.emit && mine) pass_on(d, out + (2 * gi + p) * L.out_pitch + ((x >> 1) + 1) * L.out_stride);
+                deliver(n, o, mine, true, ev_pool, out + (2 * gi + p) * out_pitch + ((x >> 1) + 1) * out_stride, emit && mine);
             }
         }
         t += kPassWaves;
         if (t < tasks) begin(t);
     }
+    if constexpr (kInt) {
+        ev = wave_sum(ev);
+        if (pool) ev_pool = wave_sum(ev_pool);
+    }
     if (lane == 0) {
-        if (ev) atomicAdd(events, ev);
-        if (ev_pool) atomicAdd(events + 1, ev_pool);
+        if (ev) atomicAdd(all_events + layer + 1, ev);
+        if (ev_pool) atomicAdd(all_events + layer + 2, ev_pool);
     }
 }
 
@@ -320,7 +326,7 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_eager_pass(const EagerPass 
 #pragma unroll 1
     for (int k = 0; k < n; ++k) {
         PassStep &L = a.st[k];
-        pass_conv<T>(a, L, stream, &events[L.layer + 1]);
+        pass_conv<T>(a, L, stream, events);
     }
     lds_barrier();
     if (tid < a.n_layers && events[tid]) atomicAdd(a.stats + ((int64_t)stream * a.n_layers + tid) * 2, (unsigned long long)events[tid]);
@@ -343,15 +349,24 @@ bool eager_pass_shape(int prec, EagerPass &a)
     auto rcp32 = [](int n) { return n > 1 ? (unsigned)((0x100000000ull + n - 1) / n) : 0u; };
     for (int k = 0; k < a.n; ++k) {
         EagerPassStep &L = a.st[k];
+        const bool single = L.c_out == 16;
+        const int n_blk = (L.c_out + 31) / 32;
         L.n_xt = (L.w + 15) / 16;
-        L.n_ct = L.c_out == 16 ? 1 : 2 * ((L.c_out + 31) / 32);
+        L.n_ct = single ? 1 : 2 * n_blk;
+        L.tasks = L.n_ct * L.n_xt * L.n_groups;
+        L.co_g = single ? 4 : 8;
+        L.w_kstep = single ? 3 * 1024 : (uint32_t)n_blk * 6144; L.w_ky = single ? 1024 : 2048;
         L.xt_rcp = rcp32(L.n_xt); L.ct_rcp = rcp32(L.n_ct);
         L.cells = L.c_in % vl == 0 ? L.c_in / vl : 0;
         L.n_ksteps = L.cells ? (3 * L.cells + 3) / 4 : 1;
         L.in_stride = cell_stride(L.cells ? L.cells + pad_cells(eb == 4, L.cells) : window_cells(L.c_in, vl, eb == 4)) * 16;
         L.in_pitch = (16 * L.n_xt + 2) * L.in_stride;
         size[k] = (size_t)L.n_in * L.in_pitch;
-        if (k > 0) { a.st[k - 1].out_stride = L.in_stride; a.st[k - 1].out_pitch = L.in_pitch; a.st[k - 1].out_rows = L.n_in; }
+        if (k > 0) {
+            EagerPassStep &P = a.st[k - 1];
+            P.out_stride = L.in_stride; P.out_pitch = P.out_end = L.in_pitch; P.out_rows = L.n_in;
+            P.out_done = ((P.pool ? P.out_w : 16 * P.n_xt) + 1) * L.in_stride;
+        }
     }
     for (int k = 0; k < a.n; ++k) lds = std::max(lds, size[k] + size[k + 1]);
     if (lds > 160 * 1024 - 512) return false;

@@ -70,7 +70,7 @@ struct TraitsI8 {
     }
     static __device__ __forceinline__ void pack4(const st_t *v, uint32_t *out)
     {
-        out[0] = (uint32_t)(uint8_t)v[0] | (uint32_t)(uint8_t)v[1] << 8 | (uint32_t)(uint8_t)v[2] << 16 | (uint32_t)v[3] << 24;
+        out[0] = __builtin_amdgcn_perm((uint32_t)v[1], (uint32_t)v[0], 0x0c0c0400u) | __builtin_amdgcn_perm((uint32_t)v[3], (uint32_t)v[2], 0x04000c0cu);
     }
     static __device__ __forceinline__ bool ev_nonzero(ev_t v) { return v != 0; }
 };
