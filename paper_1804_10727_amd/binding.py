@@ -260,11 +260,16 @@ class Streams:
 
     def push_segment(self, rows, stream_ids=None, n_rows=None):
         """rows: device tensor [n_ids][n_rows][in_w][in_c] (float32 / bfloat16 / int8)."""
-        keep, ptr = _ids(stream_ids)
-        n_ids = rows.shape[0] if stream_ids is None else len(keep)
-        n_rows = rows.shape[1] if n_rows is None else n_rows
         assert rows.is_contiguous() and rows.is_cuda
-        _check(load_library().idf_push_segment(self._h, ptr, n_ids, C.c_void_p(rows.data_ptr()), n_rows))
+        shape = rows.shape
+        if stream_ids is None:
+            ids, n_ids = None, shape[0]
+        else:           # (as bytes: a numpy array's address takes a microsecond to ask for)
+            ids = np.ascontiguousarray(stream_ids, dtype=np.int32)
+            ids, n_ids = ids.tobytes(), len(ids)
+        rc = _LIB.idf_push_segment(self._h, ids, n_ids, rows.data_ptr(), shape[1] if n_rows is None else n_rows)
+        if rc != IDF_OK:
+            _check(rc)
 
     def set_push_batching(self, k):
         _check(load_library().idf_set_push_batching(self._h, int(k)))

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "idf_common.h"
 
 namespace idf {
@@ -15,12 +17,15 @@ struct LaunchCtx {
     hipEvent_t start = nullptr, stop = nullptr;
 };
 
-template <class K, class... A>
-inline hipError_t launch(K kernel, dim3 grid, dim3 block, size_t lds, const LaunchCtx &c, A... args)
+// (arguments by reference: by value a block of 3 KB was copied three times on its way)
+template <class... P>
+inline hipError_t launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, const LaunchCtx &c, const std::common_type_t<P> &...args)
 {
-    if (c.start) hipExtLaunchKernelGGL(kernel, grid, block, lds, c.st, c.start, c.stop, 0, args...);
-    else hipLaunchKernelGGL(kernel, grid, block, lds, c.st, args...);
-    return hipGetLastError();
+    void *list[] = {const_cast<void *>(static_cast<const void *>(&args))...};
+    const void *fn = reinterpret_cast<const void *>(kernel);
+    const hipError_t e = c.start ? hipExtLaunchKernel(fn, grid, block, list, lds, c.st, c.start, c.stop, 0) : hipLaunchKernel(fn, grid, block, list, lds, c.st);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
 }
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits until every global

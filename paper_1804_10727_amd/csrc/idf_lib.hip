@@ -539,27 +539,32 @@ double conv_step_bytes(const idf_net &net, const ConvStep &a, int n_streams)
     return per_stream * n_streams + weights;
 }
 
+// Quotient and remainder of counts that are nearly always small: the 64-bit instruction takes several times as long, and a push has
+// some sixty of them.
+inline int64_t quot(int64_t a, int64_t b) { return ((uint64_t)a | (uint64_t)b) >> 32 ? a / b : (int64_t)((uint32_t)a / (uint32_t)b); }
+inline int64_t rest_of(int64_t a, int64_t b) { return ((uint64_t)a | (uint64_t)b) >> 32 ? a % b : (int64_t)((uint32_t)a % (uint32_t)b); }
+
 // ---- layers on the matrix cores -------------------------------------------------------------------
 // Rows counted over samples: sample * rows per sample + row.
 
 // Rows of c of a layer that can be formed once `in` input rows have arrived.
 // (a signal without end is one sample)
-int64_t rows_ready(const Geom &g, int64_t in) { return g.h_in > 0 ? in / g.h_in * g.h_out + rows_final(g, in % g.h_in) : rows_final(g, in); }
-int64_t row_in_sample(const Geom &g, int64_t o) { return g.h_out > 0 ? o % g.h_out : o; }
-int64_t sample_end(const Geom &g, int64_t o) { return g.h_out > 0 ? (o / g.h_out + 1) * g.h_out : INT64_MAX; }
+int64_t rows_ready(const Geom &g, int64_t in) { return g.h_in > 0 ? quot(in, g.h_in) * g.h_out + rows_final(g, rest_of(in, g.h_in)) : rows_final(g, in); }
+int64_t row_in_sample(const Geom &g, int64_t o) { return g.h_out > 0 ? rest_of(o, g.h_out) : o; }
+int64_t sample_end(const Geom &g, int64_t o) { return g.h_out > 0 ? (quot(o, g.h_out) + 1) * g.h_out : INT64_MAX; }
 // First input row that row o of c needs.
 int64_t first_needed(const Geom &g, int64_t o)
 {
-    return (g.h_out > 0 ? o / g.h_out * g.h_in : 0) + std::max<int64_t>(0, row_in_sample(g, o) * g.s_h - g.p_h);
+    return (g.h_out > 0 ? quot(o, g.h_out) * g.h_in : 0) + std::max<int64_t>(0, row_in_sample(g, o) * g.s_h - g.p_h);
 }
-int mod_rows(int64_t y, int64_t n) { return (int)((y % n + n) % n); }
+int mod_rows(int64_t y, int64_t n) { return y >= 0 ? (int)rest_of(y, n) : (int)((y % n + n) % n); }
 
 // How many rows leave a unit that forms rows [o, o + n) of c (all of one sample).
 int64_t rows_leaving(const idf_net &net, const RowUnit &u, int64_t o, int64_t n)
 {
     if (!u.pool) return n;
     const int h = net.g[u.l].h_out, hp = net.g[u.lp].h_out;
-    const int64_t y = o % h;
+    const int64_t y = rest_of(o, h);
     return std::min<int64_t>((y + n) / 2, hp) - std::min<int64_t>(y / 2, hp);
 }
 // The first of them, counted over samples.
@@ -567,7 +572,7 @@ int64_t leaving_index(const idf_net &net, const RowUnit &u, int64_t o)
 {
     if (!u.pool) return o;
     const int h = net.g[u.l].h_out;
-    return o / h * net.g[u.lp].h_out + o % h / 2;
+    return quot(o, h) * net.g[u.lp].h_out + rest_of(o, h) / 2;
 }
 
 // Layers of more input channels never take the event path: their share of the weights would crowd the LDS of every
@@ -2017,6 +2022,7 @@ inline void took_rows(const idf_streams *s, StreamHost &h, int n, int64_t fresh)
 // A launch of a push to push_members failed.  Layers side by side: what the launches before it took in has been taken in.
 __attribute__((noinline)) int push_gave_up(idf_streams *s, int rc)
 {
+    if (s->push_members.empty()) s->push_members = all_members(s);
     for (const auto &m : s->push_members) {
         StreamHost &h = s->h[m.second];
         const int64_t in = (s->prog_same ? s->prog_all : s->prog[m.second]).in[0] - (h.sample * s->net->in_h + h.r);
@@ -2046,6 +2052,10 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
     // go together only if they stand in the same sample too)
     typedef std::tuple<int64_t, int64_t, int64_t, uint32_t> Key;
     const bool by_sample = !s->units.empty() && !s->stg2d;
+    // (layers side by side: progress is kept per stream; all streams, in step and in order, need no list)
+    const bool side_by_side = s->use_gather || s->stg2d;
+    bool whole = side_by_side && s->prog_same && n_ids == s->B;
+    for (int i = 0; whole && stream_ids && i < n_ids; ++i) whole = stream_ids[i] == i;
     Key key0{0, 0, 0, 0};
     bool one_group = true;
     int64_t memo_r = -1, memo_fresh = 0;
@@ -2065,21 +2075,26 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
         if (h.out_written - h.out_read + fresh > s->out_cap)
             return fail(IDF_ESTATE, "stream %d: output area full (%lld rows waiting, %lld more would complete, room for %lld)",
                         id, (long long)(h.out_written - h.out_read), (long long)fresh, (long long)s->out_cap);
+        if (!whole) members.push_back({i, id});
+        if (side_by_side) continue;
         const Key key = key_of(h);
         if (i == 0) key0 = key;
         else if (key != key0) one_group = false;
-        members.push_back({i, id});
     }
+    // every launch of streams at the same place
+    auto run = [&](auto &&f) {
+        if (!whole) return for_each_prog(s, members, f);
+        StreamSel all{};
+        all.n = s->B; all.base = 0; all.pos0 = 0;
+        return f(all, s->prog_all);
+    };
     auto deliver = [&](const Key &key, const std::vector<std::pair<int, int>> &group) {
         return for_each_selection(group, [&](const StreamSel &sel) {
             return enqueue_cascade(s, sel, dev_rows, n_rows, std::get<0>(key), std::get<1>(key), std::get<2>(key), std::get<3>(key));
         });
     };
     if (s->use_cascade1d) {
-        const bool in_step = s->prog_same && n_ids == s->B && (!stream_ids || members.back().second == s->B - 1);
-        bool straight = in_step;
-        for (int i = 0; straight && stream_ids && i < n_ids; ++i) straight = stream_ids[i] == i;
-        if (straight && s->batch > 1) {
+        if (whole && s->batch > 1) {
             // held back until there are enough of them; a launch takes buffers of one size and of one sample
             if (s->held > 0 && (s->held_rows != n_rows || s->h[0].r == 0 || (s->held + 1) * n_rows > s->batch_rows)) rc = gather_flush(s);
             if (rc != IDF_OK) return rc;
@@ -2089,14 +2104,14 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
         } else {
             rc = gather_flush(s);
             if (rc != IDF_OK) return rc;
-            rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, s->depth_first); });
+            rc = run([&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, s->depth_first); });
         }
         if (rc != IDF_OK) return push_gave_up(s, rc);
     } else if (s->use_gather) {
-        rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, false); });
+        rc = run([&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, false); });
         if (rc != IDF_OK) return push_gave_up(s, rc);
     } else if (s->stg2d) {
-        rc = for_each_prog(s, members, [&](const StreamSel &sel, RowProg &p) { return row_run(s, sel, p, dev_rows, n_rows); });
+        rc = run([&](const StreamSel &sel, RowProg &p) { return row_run(s, sel, p, dev_rows, n_rows); });
         if (rc != IDF_OK) return push_gave_up(s, rc);
     } else if (one_group) {
         rc = deliver(key0, members);
