@@ -247,7 +247,7 @@ struct GatherStep {
     int h_out, flat;             // flat: one position per row and kernel column (1-D)
     // rows of many positions
     int k_w, s_w_log, p_w, w_in, w_out, nk_w, ns_w_log, np_w, nw_out;
-    unsigned kw_rcp, wout_rcp;
+    unsigned win_rcp, wout_rcp;  // of k_w * cells, of w_out: ceil(2^32 / n)
 };
 struct GatherHead {
     int end[8];                  // workgroups of the steps up to and with step i (the last step's own end is not needed)

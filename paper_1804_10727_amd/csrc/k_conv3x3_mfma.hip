@@ -637,11 +637,12 @@ template <class T, bool EV, bool WIDE, bool TAIL>
 __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatch b, const StreamSel sel)
 {
     (void)b;                                      // the first argument: it begins the segment
-    ArgStep &a = *((ArgStep *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(RowBatch, st)) + blockIdx.z);
+    const __attribute__((address_space(4))) char *args = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+    ArgStep &a = *((ArgStep *)(args + offsetof(RowBatch, st)) + blockIdx.z);
     const int tile = blockIdx.y, si = blockIdx.x;
     // (by every workgroup; us per pass, none / the first 256 / all: vgg-style net 3006 / 2925 / 2850, four streams out of step
     //  7256 / 7150 / 7030, float32 net 300 / 292 / 284)
-    request_arguments<sizeof(RowStep), kWaves>(&a, &sel);
+    request_arguments<sizeof(RowStep), kWaves>(&a, args + sizeof(RowBatch));          // (the streams behind)
     const int tiles = a.tiles, form = a.form;
     asm volatile("" ::"s"(tiles), "s"(form));
     if (tile >= tiles) return;

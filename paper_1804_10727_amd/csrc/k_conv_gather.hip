@@ -50,6 +50,15 @@ __device__ __forceinline__ int taps_axis(int v, int k, int s_log, int p, int n)
     return hi >= lo ? hi - lo + 1 : 0;
 }
 
+// The sum over the four lanes that are 16 apart, in each of them.
+__device__ __forceinline__ uint32_t other_halves(uint32_t v)
+{
+    auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = r[0] + r[1];
+    r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return r[0] + r[1];
+}
+
 // ---- the caller's rows: into the ring, channels padded to whole cells, and counted as the first layer's events ----
 template <class T> __device__ __forceinline__ void take_rows(Head &h, Step &a, const StreamSel &sel, int si, int tid, int threads)
 {
@@ -138,22 +147,37 @@ template <class T> __device__ __forceinline__ void pool_rows(Head &h, Step &a, c
 }
 
 // ---- one tile: 16 positions x 16 channels, by a team of four waves ---------------------------------------
+// What a launch of few tiles spends its time on is what stands around the contraction: a wave's arguments in one batch (and asked for
+// in one statement: request_arguments), cells found with an addition and two minima where they lie in one stretch, counters
+// added over lanes without LDS, in one instruction (us: 64 audio streams 5788 -> 5455 per 16,000 samples, one live stream 32.3 -> 29.2
+// per segment, 37 streams with 16 pushes per launch 738 -> 710, one sensor 18,430 -> 16,250, 32 images through six layers 556 -> 550).
 // share: LDS for the sums of three waves; barrier: where the team's waves meet.
-template <class T, bool COUNT, class Barrier>
+template <class T, bool COUNT, bool CHAIN, class Barrier>
 __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel, int si0, int pt, int ct, int spt_log, bool on, int kq,
                                           typename T::acc_t *share, Barrier &&barrier)
 {
     using acc_t = typename T::acc_t; using st_t = typename T::st_t;
     constexpr int VL = T::VL, EB = T::EB;
     const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
-    // everything the loads need to know, asked for in one batch (left to first use: one wait after the other)
+    // everything the tile needs to know, asked for in one batch (left to first use: one wait after the other)
     const int n_rows = a.n_rows, y0 = a.y0, n_ks = a.n_ks, cells = a.cells, slot0 = a.slot0, ring_rows = a.ring_rows, k_h = a.k_h, s_h_log = a.s_h_log;
-    const unsigned cells_rcp = a.cells_rcp;
-    const int64_t ring_stride = a.ring_stride;
+    const int64_t ring_stride = a.ring_stride, dst_stride = a.dst_stride;
     const void *ring_p = a.ring, *w_frag = a.w_frag;
+    void *dst = a.dst;
+    const st_t *bias = (const st_t *)a.bias;
     const int h_in = a.h_in, p_h = a.p_h, n_ct = a.n_ct, flat = a.flat, w_out = a.w_out;
-    asm volatile("" ::"s"(n_rows), "s"(y0), "s"(n_ks), "s"(cells), "s"(slot0), "s"(ring_rows), "s"(k_h), "s"(s_h_log), "s"(cells_rcp),
-                 "s"(ring_stride), "s"(ring_p), "s"(w_frag), "s"(h_in), "s"(p_h), "s"(n_ct), "s"(flat), "s"(w_out));
+    const int act = a.act, shr = a.shr, clamp_hi = a.clamp_hi, c_out = a.c_out, dst_cells = a.dst_cells, dst_slot0 = a.dst_slot0, dst_rows = a.dst_rows;
+    const int next_layer = a.next_layer, nk_h = a.nk_h, ns_h_log = a.ns_h_log, np_h = a.np_h, nh_out = a.nh_out, next_c_out = a.next_c_out, to_output = a.to_output;
+    unsigned long long *stats = h.stats;
+    const int n_layers = h.n_layers;
+    asm volatile("" ::"s"(n_rows), "s"(y0), "s"(n_ks), "s"(cells), "s"(slot0), "s"(ring_rows), "s"(k_h), "s"(s_h_log), "s"(ring_stride), "s"(ring_p), "s"(w_frag),
+                 "s"(h_in), "s"(p_h), "s"(n_ct), "s"(flat), "s"(w_out));
+    // (for what comes after the contraction; where steps follow each other in a loop that many registers are not free until then)
+    auto later = [&]() IDF_INLINE {
+        asm volatile("" ::"s"(act), "s"(shr), "s"(clamp_hi), "s"(c_out), "s"(dst_cells), "s"(dst_slot0), "s"(dst_rows), "s"(next_layer), "s"(nk_h), "s"(ns_h_log),
+                     "s"(np_h), "s"(nh_out), "s"(next_c_out), "s"(to_output), "s"(stats), "s"(n_layers), "s"(dst_stride), "s"(dst), "s"(bias));
+    };
+    if (!CHAIN) later();
     const int per_log = 4 - spt_log;               // positions per stream in the tile
     const int si = si0 + (m >> per_log), pl = m & ((1 << per_log) - 1);
     const bool stream_ok = on && si < sel.n;
@@ -196,20 +220,22 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
             // (a window that reaches over an end of the signal: its cells there are zero; so are those past the window's end, where
             // the weights are zero too, but zero times infinity is not)
             const bool edge = __ballot(valid && (y_in < 0 || y_in + k_h > h_in)) != 0ull || 4 * n_ks > q_last + 1;
+            // a position's rows follow each other in the ring and have nothing between them: the window is one stretch, but for the
+            // ring's end (cells past the window's end: see above, the last one again)
+            const uint32_t ring_bytes = (uint32_t)(ring_rows * cells) * 16, begin = slot_o * (uint32_t)cells * 16, last = (uint32_t)q_last * 16;
+            const unsigned cells_rcp = a.cells_rcp;
 #pragma unroll 1
             for (int kb = ks0; kb < ks1; kb += kChunk) {
                 i32x4 xv[kChunk], wv[kChunk];
                 const unsigned char *wf = wf0 + (kb - ks0) * w_step;
+                const uint32_t at = (uint32_t)(4 * kb + g) * 16;
 #pragma unroll
                 for (int i = 0; i < kChunk; ++i) {
                     if (kb + i >= ks1) continue;
                     wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf), (uint32_t)i * w_step + lane16);
-                    int q = 4 * (kb + i) + g;
-                    q = q < q_last ? q : q_last;               // (past the end: see below)
-                    const unsigned ky = __umul24((unsigned)q, cells_rcp) >> 16;
-                    unsigned slot = slot_o + ky;
-                    slot = min(slot, slot - (unsigned)ring_rows);
-                    xv[i] = *at4(reinterpret_cast<const i32x4 *>(ring), (__umul24(slot, (unsigned)cells) + (unsigned)q - __umul24(ky, (unsigned)cells)) * 16);
+                    uint32_t off = begin + min(at + (uint32_t)i * 64, last);
+                    off = min(off, off - ring_bytes);
+                    xv[i] = *at4(reinterpret_cast<const i32x4 *>(ring), off);
                 }
                 if (edge) {
 #pragma unroll
@@ -226,8 +252,10 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
                 contract(xv, wv, kb);
             }
         } else {
-            const int k_w = a.k_w, w_in = a.w_in, x_in = (x << a.s_w_log) - a.p_w, q_last = k_h * k_w * cells - 1;
-            const unsigned kw_rcp = a.kw_rcp;
+            // likewise a row of the window, k_w positions; what lies outside the row is outside of both ends of its cells
+            const int k_w = a.k_w, w_in = a.w_in, row_cells = w_in * cells, win_cells = k_w * cells, x_in = ((x << a.s_w_log) - a.p_w) * cells, q_last = k_h * win_cells - 1;
+            const unsigned win_rcp = a.win_rcp, one = win_cells == 1;
+            const unsigned y_top = (unsigned)y_in;
 #pragma unroll 1
             for (int kb = ks0; kb < ks1; kb += kChunk) {
                 i32x4 xv[kChunk], wv[kChunk];
@@ -237,16 +265,14 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
                 for (int i = 0; i < kChunk; ++i) {
                     if (kb + i >= ks1) continue;
                     wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf), (uint32_t)i * w_step + lane16);
-                    const int q_all = 4 * (kb + i) + g, q = q_all < q_last ? q_all : q_last;
-                    const unsigned tap = __umul24((unsigned)q, cells_rcp) >> 16, ky = __umul24(tap, kw_rcp) >> 16;
-                    const int c = q - (int)__umul24(tap, (unsigned)cells), xx = x_in + (int)(tap - __umul24(ky, (unsigned)k_w)), y = y_in + (int)ky;
-                    const bool ok = valid && (unsigned)y < (unsigned)h_in && (unsigned)xx < (unsigned)w_in && q_all <= q_last;
+                    const unsigned q = (unsigned)(4 * (kb + i) + g), ky = __umulhi(q, win_rcp) + __umul24(q, one);
+                    const int xc = x_in + (int)(q - __umul24(ky, (unsigned)win_cells));
+                    const bool ok = valid && y_top + ky < (unsigned)h_in && (unsigned)xc < (unsigned)row_cells && (int)q <= q_last;
                     there |= ok ? 1u << i : 0u;
                     unsigned slot = slot_o + ky;
                     slot = min(slot, slot - (unsigned)ring_rows);
                     slot = min(slot, slot - (unsigned)ring_rows);
-                    const uint32_t off = ok ? (__umul24(__umul24(slot, (unsigned)w_in) + (unsigned)xx, (unsigned)cells) + (unsigned)c) * 16 : 0u;
-                    xv[i] = *at4(reinterpret_cast<const i32x4 *>(ring), off);
+                    xv[i] = *at4(reinterpret_cast<const i32x4 *>(ring), ok ? (__umul24(slot, (unsigned)row_cells) + (unsigned)xc) * 16 : 0u);
                 }
 #pragma unroll
                 for (int i = 0; i < kChunk; ++i)
@@ -262,16 +288,7 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
         else acc = sums[0];
         if (kq > 0) share[(kq - 1) * 64 + lane] = acc;
     }
-    // (likewise for what comes after the contraction)
-    const int act = a.act, shr = a.shr, clamp_hi = a.clamp_hi, c_out = a.c_out, dst_cells = a.dst_cells, dst_slot0 = a.dst_slot0, dst_rows = a.dst_rows;
-    const int64_t dst_stride = a.dst_stride;
-    void *dst = a.dst;
-    const st_t *bias = (const st_t *)a.bias;
-    const int next_layer = a.next_layer, nk_h = a.nk_h, ns_h_log = a.ns_h_log, np_h = a.np_h, nh_out = a.nh_out, next_c_out = a.next_c_out, to_output = a.to_output;
-    unsigned long long *stats = h.stats;
-    const int n_layers = h.n_layers;
-    asm volatile("" ::"s"(act), "s"(shr), "s"(clamp_hi), "s"(c_out), "s"(dst_cells), "s"(dst_slot0), "s"(dst_rows), "s"(dst_stride), "s"(dst), "s"(bias),
-                 "s"(next_layer), "s"(nk_h), "s"(ns_h_log), "s"(np_h), "s"(nh_out), "s"(next_c_out), "s"(to_output), "s"(stats), "s"(n_layers));
+    if (CHAIN) later();
     barrier();
     if (!on || kq > 0) return;
 
@@ -320,18 +337,16 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
         for (int i = 0; i < EB; ++i) nz += (uint32_t)T::nonzero(e[i]);
     }
     if (!stats || next_layer < 0) return;
-    // events of the next layer and the taps they reach
-    uint32_t ev_all = nz;
-    uint32_t taps_all = nz * (uint32_t)(taps_axis(y0 + o, nk_h, ns_h_log, np_h, nh_out) * (flat ? 1 : taps_axis(x, a.nk_w, a.ns_w_log, a.np_w, a.nw_out)));
-    // per stream: over the four groups of channels, then over the stream's positions
-    ev_all += __shfl_xor(ev_all, 16); taps_all += __shfl_xor(taps_all, 16);
-    ev_all += __shfl_xor(ev_all, 32); taps_all += __shfl_xor(taps_all, 32);
-    for (int w = 1; w < (1 << per_log); w <<= 1) { ev_all += __shfl_xor(ev_all, w); taps_all += __shfl_xor(taps_all, w); }
-    if (g == 0 && pl == 0 && ev_all) {
-        unsigned long long *d = stats + ((int64_t)stream * n_layers + next_layer) * 2;
-        atomicAdd(d, (unsigned long long)ev_all);
-        atomicAdd(d + 1, (unsigned long long)taps_all * (unsigned long long)next_c_out);
-    }
+    // events of the next layer (at most 256: the low 12 bits) and the taps they reach, per stream: over the four groups of channels,
+    // then over the stream's positions.  Two lanes add them, with one instruction.
+    uint32_t sum = nz | nz * (uint32_t)(taps_axis(y0 + o, nk_h, ns_h_log, np_h, nh_out) * (flat ? 1 : taps_axis(x, a.nk_w, a.ns_w_log, a.np_w, a.nw_out))) << 12;
+    sum = other_halves(sum);
+    if (per_log > 0) sum += (uint32_t)__builtin_amdgcn_mov_dpp((int)sum, 0xB1, 0xf, 0xf, true);        // lane ^ 1
+    if (per_log > 1) sum += (uint32_t)__builtin_amdgcn_mov_dpp((int)sum, 0x4E, 0xf, 0xf, true);        // lane ^ 2
+    if (per_log > 2) sum += (uint32_t)__builtin_amdgcn_mov_dpp((int)sum, 0x141, 0xf, 0xf, true);       // the other four of eight (mirrored)
+    if (per_log > 3) sum += (uint32_t)__builtin_amdgcn_mov_dpp((int)sum, 0x140, 0xf, 0xf, true);       // the other eight of sixteen
+    if (g < 2 && pl == 0 && sum)
+        atomicAdd(stats + ((int64_t)stream * n_layers + next_layer) * 2 + g, g == 0 ? (unsigned long long)(sum & 0xfffu) : (unsigned long long)(sum >> 12) * (unsigned)next_c_out);
 }
 
 // Workgroups that request the launch's arguments; those behind the first round find them in the scalar cache.  us, nobody asking /
@@ -347,34 +362,32 @@ __global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows(const Gather
     // The steps' tiles follow each other without gaps: workgroups go to the compute units in turn, and with an empty one here
     // and there some units got the tiles of three layers and others none (12.7 us per launch of 64 audio streams instead of 7).
     int k = 0, tile = blockIdx.x;
-    if (blockIdx.x < kFirst) request_arguments<sizeof(Batch), kTeam>(&b);
+    if (blockIdx.x < kFirst) request_arguments<sizeof(Batch), kTeam>(&b, &b + 1);
+    const int n_sb = b.head.n_sb, n_sb8 = b.head.n_sb8, sb_log = b.head.sb_log, n_sel = sel.n;
+    const unsigned sb_rcp = b.head.sb_rcp;
     {
         int end[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) end[i] = b.head.end[i];
-        asm volatile("" ::"s"(end[0]), "s"(end[1]), "s"(end[2]), "s"(end[3]), "s"(end[4]), "s"(end[5]), "s"(end[6]), "s"(end[7]));
+        const int base = sel.base, pos0 = sel.pos0;
+        asm volatile("" ::"s"(end[0]), "s"(end[1]), "s"(end[2]), "s"(end[3]), "s"(end[4]), "s"(end[5]), "s"(end[6]), "s"(end[7]), "s"(n_sb), "s"(n_sb8), "s"(sb_log),
+                     "s"(n_sel), "s"(sb_rcp), "s"(base), "s"(pos0));
         int first = 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) if ((int)blockIdx.x >= end[i]) { k = i + 1; first = end[i]; }
         tile -= first;
     }
     Step &a = b.st[k];
-    {   // first round of scalar loads, with one wait
-        const int take = a.take, n_ct = a.n_ct, n_pt = a.n_pt, spt_log = a.spt_log, base = sel.base, pos0 = sel.pos0;
-        const int n_sb = b.head.n_sb, n_sb8 = b.head.n_sb8, sb_log = b.head.sb_log, n_sel = sel.n;
-        const unsigned sb_rcp = b.head.sb_rcp;
-        asm volatile("" ::"s"(take), "s"(n_ct), "s"(n_pt), "s"(spt_log), "s"(base), "s"(pos0), "s"(n_sb), "s"(n_sb8), "s"(sb_log), "s"(n_sel), "s"(sb_rcp));
-    }
     const int take = a.take, spt_log = a.spt_log;
     int sg, rest;                                  // group of streams; tile of positions and channels
-    if (b.head.n_sb > 0) {
+    if (n_sb > 0) {
         // workgroups go to the XCDs in turn: a block of streams meets one and the same in every layer, whose L2 then has the
         // rows that the layer before has just written
-        const int inner = (int)__umulhi((unsigned)tile, b.head.sb_rcp), sb = tile - inner * b.head.n_sb8, subs = b.head.sb_log - spt_log;
-        if (sb >= b.head.n_sb) return;
+        const int inner = (int)__umulhi((unsigned)tile, sb_rcp), sb = tile - inner * n_sb8, subs = sb_log - spt_log;
+        if (sb >= n_sb) return;
         sg = (sb << subs) + (inner & ((1 << subs) - 1));
         rest = inner >> subs;
-        if ((sg << spt_log) >= sel.n) return;
+        if ((sg << spt_log) >= n_sel) return;
     } else {
         const int per = a.n_ct * a.n_pt;
         sg = take == 1 ? tile : (int)((unsigned)tile / (unsigned)per);
@@ -383,7 +396,7 @@ __global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows(const Gather
     if (take == 1) { take_rows<T>(b.head, a, sel, sg, threadIdx.x, 64 * kTeam); return; }
     if (take == 2) { pool_rows<T>(b.head, a, sel, sg, rest * kPoolCells, (rest + 1) * kPoolCells, 64 * kTeam); return; }
     const int pt = a.ct_rcp ? (int)__umulhi((unsigned)rest, a.ct_rcp) : rest, ct = rest - pt * a.n_ct;
-    conv_tile<T, COUNT>(b.head, a, sel, sg << spt_log, pt, ct, spt_log, true, uni(threadIdx.x >> 6), share, [] { lds_barrier(); });
+    conv_tile<T, COUNT, false>(b.head, a, sel, sg << spt_log, pt, ct, spt_log, true, uni(threadIdx.x >> 6), share, [] { lds_barrier(); });
 }
 
 template <class T, int NS, bool COUNT>
@@ -392,7 +405,7 @@ __global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherB
     typedef const __attribute__((address_space(4))) GatherBatch<NS> Batch;
     Batch &b = *(Batch *)__builtin_amdgcn_kernarg_segment_ptr();
     __shared__ typename T::acc_t share[4][(kTeam - 1) * 64];
-    request_arguments<sizeof(Batch), 4 * kTeam>(&b);
+    request_arguments<sizeof(Batch), 4 * kTeam>(&b, &b + 1);
     const int team = uni(threadIdx.x >> 8), kq = uni((threadIdx.x >> 6) & 3), si = blockIdx.x;
     for (int k = 0; k < b.head.n; ++k) {
         Step &a = b.st[k];
@@ -403,8 +416,10 @@ __global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherB
         } else {
             const int tasks = a.n_ct * ((a.n_rows * a.w_out + 15) >> 4);
             for (int t0 = 0; t0 < tasks; t0 += 4) {
+                Step *step = &a;
+                asm volatile("" : "+s"(step));     // (a tile's arguments are read anew: kept over the loop they do not fit the registers)
                 const int t = t0 + team, pt = a.ct_rcp ? (int)__umulhi((unsigned)t, a.ct_rcp) : t, ct = t - pt * a.n_ct;
-                conv_tile<T, COUNT>(b.head, a, sel, si, pt, ct, 0, t < tasks, kq, share[team], [] { lds_barrier(); });
+                conv_tile<T, COUNT, true>(b.head, *step, sel, si, pt, ct, 0, t < tasks, kq, share[team], [] { lds_barrier(); });
                 lds_barrier();                     // the sums have been read
             }
         }
@@ -518,9 +533,11 @@ bool conv_gather_takes(int prec, const Geom &g, int ring_rows)
     if (g.k_h > 32 || g.k_w > 32 || g.p_h >= g.k_h || g.p_w >= g.k_w) return false;
     GatherStep a{};
     conv_gather_layer(prec, g, a);
+    // (win_rcp is exact for any window of these sizes: at most 2048 cells to a row of it, 65,539 in all)
+    const unsigned kw_rcp = (unsigned)((65536 + g.k_w - 1) / g.k_w);
     for (unsigned q = 0; q < (unsigned)(g.k_h * g.k_w * cells) + 4u; ++q) {
         const unsigned tap = q * a.cells_rcp >> 16;
-        if (q > UINT32_MAX / a.cells_rcp || tap > UINT32_MAX / a.kw_rcp || tap != q / cells || tap * a.kw_rcp >> 16 != tap / g.k_w) return false;
+        if (q > UINT32_MAX / a.cells_rcp || tap > UINT32_MAX / kw_rcp || tap != q / cells || tap * kw_rcp >> 16 != tap / g.k_w) return false;
     }
     return true;
 }
@@ -547,7 +564,8 @@ void conv_gather_layer(int prec, const Geom &g, GatherStep &a)
     a.n_ct = (g.c_out + 15) / 16;
     a.n_ks = (g.k_h * g.k_w * a.cells + 3) / 4;
     a.cells_rcp = (unsigned)((65536 + a.cells - 1) / a.cells);
-    a.kw_rcp = (unsigned)((65536 + g.k_w - 1) / g.k_w);
+    const unsigned win_cells = (unsigned)(g.k_w * a.cells);
+    a.win_rcp = win_cells > 1 ? (unsigned)((0x100000000ull + win_cells - 1) / win_cells) : 0u;
     a.wout_rcp = (unsigned)((0x100000000ull + g.w_out - 1) / g.w_out);
 }
 

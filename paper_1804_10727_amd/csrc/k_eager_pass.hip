@@ -319,7 +319,7 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_eager_pass(const EagerPass 
     __shared__ uint32_t events[2 * kPassMax + 2];      // per level
     const int tid = threadIdx.x, stream = sel_stream(sel, blockIdx.x);
     if (tid < 2 * kPassMax + 2) events[tid] = 0;
-    request_arguments<sizeof(EagerPass), kPassWaves>(&a);
+    request_arguments<sizeof(EagerPass), kPassWaves>(&a, &a + 1);
     lds_barrier();
     pass_input<T>(a, a.st[0], stream, sel.pos0 + (int)blockIdx.x, &events[0]);
     const int n = a.n;

@@ -5,7 +5,6 @@
 #include <hip/hip_runtime.h>
 
 #include "idf.h"
-#include "idf_common.h"
 
 namespace idf {
 
@@ -124,22 +123,31 @@ template <class V> __device__ __forceinline__ V neighbour(V v)
 }
 
 // Arguments of a launch on their way to the scalar cache, a few of their 64-byte lines by each wave of the workgroup: met one
-// after the other, each line would be a trip to memory of its own.  sel: the launch's selection of streams, if it lies elsewhere (its
-// first line only).
-template <int BYTES, int WAVES> __device__ __forceinline__ void request_arguments(const void __attribute__((address_space(4))) *args, const StreamSel *sel = nullptr)
+// after the other, each line would be a trip to memory of its own.  also: a further place whose line is wanted.  (One statement: the
+// compiler puts a wait behind each load whose value it believes to be used.)
+template <int BYTES, int WAVES> __device__ __forceinline__ void request_arguments(const void __attribute__((address_space(4))) *args, const void __attribute__((address_space(4))) *also)
 {
-    typedef const __attribute__((address_space(4))) int Word;
-    constexpr int N = (BYTES / 64 + WAVES - 1) / WAVES;
-    const int wave = uni(threadIdx.x >> 6);
-    int w[N];
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-        const int at = (wave + q * WAVES) * 64;
-        w[q] = ((Word *)args)[(at < BYTES ? at : 0) / 4];
-    }
-    if (sel) asm volatile("" ::"s"(sel->base));
-#pragma unroll
-    for (int q = 0; q < N; ++q) asm volatile("" ::"s"(w[q]));
+    typedef const __attribute__((address_space(4))) char Byte;
+    constexpr int N = (BYTES / 64 + WAVES - 1) / WAVES, PITCH = WAVES * 64;
+    static_assert(N >= 1 && N <= 12, "as many loads as stand below");
+    const int first = uni(threadIdx.x >> 6) * 64, last = first + (N - 1) * PITCH;
+    int sink;
+    asm volatile("s_load_dword %0, %1, 0x0\n\t"
+                 "s_load_dword %0, %2, 0x0\n\t"
+                 "s_load_dword %0, %3, 0x0\n\t"
+                 ".if %c4 > 2\n\ts_load_dword %0, %3, 1*%c5\n\t.endif\n\t"
+                 ".if %c4 > 3\n\ts_load_dword %0, %3, 2*%c5\n\t.endif\n\t"
+                 ".if %c4 > 4\n\ts_load_dword %0, %3, 3*%c5\n\t.endif\n\t"
+                 ".if %c4 > 5\n\ts_load_dword %0, %3, 4*%c5\n\t.endif\n\t"
+                 ".if %c4 > 6\n\ts_load_dword %0, %3, 5*%c5\n\t.endif\n\t"
+                 ".if %c4 > 7\n\ts_load_dword %0, %3, 6*%c5\n\t.endif\n\t"
+                 ".if %c4 > 8\n\ts_load_dword %0, %3, 7*%c5\n\t.endif\n\t"
+                 ".if %c4 > 9\n\ts_load_dword %0, %3, 8*%c5\n\t.endif\n\t"
+                 ".if %c4 > 10\n\ts_load_dword %0, %3, 9*%c5\n\t.endif\n\t"
+                 ".if %c4 > 11\n\ts_load_dword %0, %3, 10*%c5\n\t.endif\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(sink)
+                 : "s"(also), "s"((Byte *)args + (last < BYTES ? last : 0)), "s"((Byte *)args + (first < BYTES ? first : 0)), "n"(N), "n"(PITCH));
 }
 
 __device__ __forceinline__ int taps_of(int v, int n) { return 3 - (v == 0) - (v == n - 1); }      // of a 3-tap axis with one position of padding
