@@ -38,6 +38,7 @@ typedef const __attribute__((address_space(4))) GatherHead Head;
 
 constexpr int kTeam = 4;                         // waves that share a tile
 constexpr int kChunk = 9;                        // K-steps a wave has in flight
+constexpr int kStages = 2;                       // and a wave of a tile of two by two (with 3, or 5 at once: one wave per SIMD less, which costs more)
 constexpr int kPoolCells = 64 * kTeam;           // cells of a pool's rows per workgroup
 
 // Taps of an axis that position v lands on inside an output of n positions (n == 0: unbounded).
@@ -151,13 +152,15 @@ template <class T> __device__ __forceinline__ void pool_rows(Head &h, Step &a, c
 // in one statement: request_arguments), cells found with an addition and two minima where they lie in one stretch, counters
 // added over lanes without LDS, in one instruction (us: 64 audio streams 5788 -> 5455 per 16,000 samples, one live stream 32.3 -> 29.2
 // per segment, 37 streams with 16 pushes per launch 738 -> 710, one sensor 18,430 -> 16,250, 32 images through six layers 556 -> 550).
-// share: LDS for the sums of three waves; barrier: where the team's waves meet.
-template <class T, bool COUNT, bool CHAIN, class Barrier>
+// TW 2: two such tiles of channels x two of positions.  Their sums are those of single tiles, formed in the same order; each weight
+// and each cell that is fetched serves two tiles, and each wave brings one of the four to its end.
+// share: LDS for the waves' sums (three, or four per tile); barrier: where the team's waves meet.
+template <class T, bool COUNT, bool CHAIN, int TW, class Barrier>
 __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel, int si0, int pt, int ct, int spt_log, bool on, int kq,
                                           typename T::acc_t *share, Barrier &&barrier)
 {
     using acc_t = typename T::acc_t; using st_t = typename T::st_t;
-    constexpr int VL = T::VL, EB = T::EB;
+    constexpr int VL = T::VL, EB = T::EB, NT = TW * TW;
     const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
     // everything the tile needs to know, asked for in one batch (left to first use: one wait after the other)
     const int n_rows = a.n_rows, y0 = a.y0, n_ks = a.n_ks, cells = a.cells, slot0 = a.slot0, ring_rows = a.ring_rows, k_h = a.k_h, s_h_log = a.s_h_log;
@@ -186,118 +189,213 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
     const uint32_t lane16 = (uint32_t)lane * 16, w_step = (uint32_t)n_ct * 1024;
     // this wave's K-steps
     const int each = (n_ks + kTeam - 1) / kTeam, ks0 = kq * each, ks1 = ks0 + each < n_ks ? ks0 + each : n_ks;
-    const unsigned char *wf0 = (const unsigned char *)w_frag + ct * 1024 + ks0 * w_step;
-    const int p = (pt << per_log) + pl;
-    int o = p, x = 0;
-    if (!flat) { o = w_out == 1 ? p : (int)__umulhi((unsigned)p, a.wout_rcp); x = p - o * w_out; }
-    const bool valid = stream_ok && o < n_rows;
-    o = valid ? o : 0;
+    const unsigned char *wf0[TW];
+#pragma unroll
+    for (int tc = 0; tc < TW; ++tc) wf0[tc] = (const unsigned char *)w_frag + (TW == 1 || ct + tc < n_ct ? ct + tc : ct) * 1024 + ks0 * w_step;
+    // a lane's position in a tile: row and column of the output
+    auto place = [&](int tp, int &o, int &x) IDF_INLINE {
+        const int p = ((pt * TW + tp) << per_log) + pl;
+        o = p; x = 0;
+        if (!flat) { o = w_out == 1 ? p : (int)__umulhi((unsigned)p, a.wout_rcp); x = p - o * w_out; }
+        const bool valid = stream_ok && o < n_rows;
+        o = valid ? o : 0;
+        return valid;
+    };
+    int o = 0, x = 0;
+    bool valid = false;
     // A K-step's instructions have sums of their own: none waits for the one before, and the chains that round are a quarter as long.
-    acc_t sums[T::kInst] = {}, acc = {0, 0, 0, 0};
+    acc_t sums[T::kInst][NT] = {}, acc = {0, 0, 0, 0};
     if (on) {
-        const int y_in = ((y0 + o) << s_h_log) - p_h;          // the window's first row
-        unsigned slot_o = (unsigned)(slot0 + (o << s_h_log));
-        slot_o = min(slot_o, slot_o - (unsigned)ring_rows);
-        unsigned long long issued = 0;
-        auto contract = [&](const i32x4 (&xv)[kChunk], const i32x4 (&wv)[kChunk], int kb) IDF_INLINE {
+        bool there_is[TW];
+        int y_in[TW];                              // the window's first row
+        unsigned slot_o[TW];
+        int x_of[TW];
 #pragma unroll
-            for (int i = 0; i < kChunk; ++i) {
-                if (kb + i >= ks1) continue;
-                if (__ballot(T::or_of(xv[i]) != 0) == 0ull) continue;
+        for (int tp = 0; tp < TW; ++tp) {
+            there_is[tp] = place(tp, o, x);
+            x_of[tp] = x;
+            y_in[tp] = ((y0 + o) << s_h_log) - p_h;
+            slot_o[tp] = (unsigned)(slot0 + (o << s_h_log));
+            slot_o[tp] = min(slot_o[tp], slot_o[tp] - (unsigned)ring_rows);
+        }
+        valid = there_is[0];
+        if constexpr (TW > 1) {
+            // (tiles of one stream: a lane's place outside the map or the window is a place outside the ring, where nothing is read and
+            // zeros come back.  The next K-steps are on their way while one is multiplied; what bounds it is the L2, which every
+            // workgroup asks for all weights of its channels: without any contraction a launch of 37 audio streams with 16 pushes each
+            // takes 5.5 us, without its matrix instructions 16.5, in all 17.6; single tiles 22.6)
+            const int k_w = flat ? 1 : a.k_w, row_cells = flat ? cells : a.w_in * cells, win_cells = k_w * cells;
+            const unsigned win_rcp = a.win_rcp, one = win_cells == 1;
+            const uint32_t ring_bytes = (uint32_t)(ring_rows * row_cells) * 16;
+            unsigned char *first = (unsigned char *)const_cast<void *>(ring_p) + (int64_t)sel_stream(sel, si0) * ring_stride * EB;
+            const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(first, 0, (int)ring_bytes, 0x00027000);
+            uint32_t begin[TW], n_q[TW];           // flat: cells of the window inside the signal, from q_lo on
+            int q_lo[TW], xc0[TW];
 #pragma unroll
-                for (int e = 0; e < T::kInst; ++e) sums[e] = T::mfma(wv[i], xv[i], sums[e], e);
-                if (COUNT) {
-                    const int n_cells = k_h * (flat ? 1 : a.k_w) * cells;
-                    for (int u = 0; u < 4; ++u) {
-                        const int q = 4 * (kb + i) + u, c = q % cells;
-                        if (q < n_cells) issued += (a.c_in - c * VL < VL ? a.c_in - c * VL : VL);
+            for (int tp = 0; tp < TW; ++tp) {
+                q_lo[tp] = max(0, -y_in[tp]) * cells;
+                n_q[tp] = there_is[tp] ? (uint32_t)(min(k_h, h_in - y_in[tp]) * cells - q_lo[tp]) : 0u;
+                begin[tp] = slot_o[tp] * (uint32_t)cells * 16;
+                xc0[tp] = flat ? 0 : ((x_of[tp] << a.s_w_log) - a.p_w) * cells;
+            }
+            const int q_end = k_h * win_cells;
+            i32x4 xv[kStages][TW], wv[kStages][TW];
+            auto fetch = [&](i32x4 (&x_s)[TW], i32x4 (&w_s)[TW], int ks) IDF_INLINE {
+                ks = ks < ks1 ? ks : ks1 - 1;      // (past the end the last one again)
+#pragma unroll
+                for (int tc = 0; tc < TW; ++tc) w_s[tc] = *at4(reinterpret_cast<const i32x4 *>(wf0[tc] + (ks - ks0) * w_step), lane16);
+                const int q = 4 * ks + g;
+                const unsigned ky = flat ? 0u : __umulhi((unsigned)q, win_rcp) + __umul24((unsigned)q, one);
+#pragma unroll
+                for (int tp = 0; tp < TW; ++tp) {
+                    uint32_t off;
+                    bool ok;
+                    if (flat) {
+                        off = begin[tp] + (uint32_t)q * 16;
+                        off = min(off, off - ring_bytes);
+                        ok = (uint32_t)(q - q_lo[tp]) < n_q[tp];
+                    } else {
+                        const int xc = xc0[tp] + q - (int)__umul24(ky, (unsigned)win_cells);
+                        unsigned slot = slot_o[tp] + ky;
+                        slot = min(slot, slot - (unsigned)ring_rows);
+                        slot = min(slot, slot - (unsigned)ring_rows);
+                        off = (__umul24(slot, (unsigned)row_cells) + (unsigned)xc) * 16;
+                        ok = there_is[tp] && (unsigned)y_in[tp] + ky < (unsigned)h_in && (unsigned)xc < (unsigned)row_cells && q < q_end;
                     }
+                    x_s[tp] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, ok ? (int)off : INT32_MIN, 0, 0));
+                }
+            };
+            if (ks0 < ks1) {                       // (short windows leave a wave without a K-step)
+#pragma unroll
+                for (int i = 0; i < kStages; ++i) fetch(xv[i], wv[i], ks0 + i);
+            }
+#pragma unroll 1
+            for (int ks = ks0; ks < ks1; ks += kStages) {
+#pragma unroll
+                for (int i = 0; i < kStages; ++i) {
+#pragma unroll
+                    for (int tp = 0; tp < TW; ++tp) {
+                        if (ks + i >= ks1 || __ballot(T::or_of(xv[i][tp]) != 0) == 0ull) continue;
+#pragma unroll
+                        for (int e = 0; e < T::kInst; ++e)
+#pragma unroll
+                            for (int tc = 0; tc < TW; ++tc) sums[e][tp * TW + tc] = T::mfma(wv[i][tc], xv[i][tp], sums[e][tp * TW + tc], e);
+                    }
+                    fetch(xv[i], wv[i], ks + kStages + i);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
-        };
-        if (flat) {
-            const int q_last = k_h * cells - 1;
-            // (a window that reaches over an end of the signal: its cells there are zero; so are those past the window's end, where
-            // the weights are zero too, but zero times infinity is not)
-            const bool edge = __ballot(valid && (y_in < 0 || y_in + k_h > h_in)) != 0ull || 4 * n_ks > q_last + 1;
-            // a position's rows follow each other in the ring and have nothing between them: the window is one stretch, but for the
-            // ring's end (cells past the window's end: see above, the last one again)
-            const uint32_t ring_bytes = (uint32_t)(ring_rows * cells) * 16, begin = slot_o * (uint32_t)cells * 16, last = (uint32_t)q_last * 16;
-            const unsigned cells_rcp = a.cells_rcp;
-#pragma unroll 1
-            for (int kb = ks0; kb < ks1; kb += kChunk) {
-                i32x4 xv[kChunk], wv[kChunk];
-                const unsigned char *wf = wf0 + (kb - ks0) * w_step;
-                const uint32_t at = (uint32_t)(4 * kb + g) * 16;
+        } else {
+            unsigned long long issued = 0;
+            auto contract = [&](const i32x4 (&xv)[kChunk], const i32x4 (&wv)[kChunk], int kb) IDF_INLINE {
 #pragma unroll
                 for (int i = 0; i < kChunk; ++i) {
                     if (kb + i >= ks1) continue;
-                    wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf), (uint32_t)i * w_step + lane16);
-                    uint32_t off = begin + min(at + (uint32_t)i * 64, last);
-                    off = min(off, off - ring_bytes);
-                    xv[i] = *at4(reinterpret_cast<const i32x4 *>(ring), off);
+                    if (__ballot(T::or_of(xv[i]) != 0) == 0ull) continue;
+#pragma unroll
+                    for (int e = 0; e < T::kInst; ++e) sums[e][0] = T::mfma(wv[i], xv[i], sums[e][0], e);
+                    if (COUNT) {
+                        const int n_cells = k_h * (flat ? 1 : a.k_w) * cells;
+                        for (int u = 0; u < 4; ++u) {
+                            const int q = 4 * (kb + i) + u, c = q % cells;
+                            if (q < n_cells) issued += (a.c_in - c * VL < VL ? a.c_in - c * VL : VL);
+                        }
+                    }
                 }
-                if (edge) {
+            };
+            if (flat) {
+                const int q_last = k_h * cells - 1;
+                // (a window that reaches over an end of the signal: its cells there are zero; so are those past the window's end, where
+                // the weights are zero too, but zero times infinity is not)
+                const bool edge = __ballot(valid && (y_in[0] < 0 || y_in[0] + k_h > h_in)) != 0ull || 4 * n_ks > q_last + 1;
+                // a position's rows follow each other in the ring and have nothing between them: the window is one stretch, but for the
+                // ring's end (cells past the window's end: see above, the last one again)
+                const uint32_t ring_bytes = (uint32_t)(ring_rows * cells) * 16, begin = slot_o[0] * (uint32_t)cells * 16, last = (uint32_t)q_last * 16;
+                const unsigned cells_rcp = a.cells_rcp;
+#pragma unroll 1
+                for (int kb = ks0; kb < ks1; kb += kChunk) {
+                    i32x4 xv[kChunk], wv[kChunk];
+                    const unsigned char *wf = wf0[0] + (kb - ks0) * w_step;
+                    const uint32_t at = (uint32_t)(4 * kb + g) * 16;
 #pragma unroll
                     for (int i = 0; i < kChunk; ++i) {
                         if (kb + i >= ks1) continue;
-                        const int q = 4 * (kb + i) + g, y = y_in + (int)(__umul24((unsigned)q, cells_rcp) >> 16);
-                        if (y < 0 || y >= h_in || q > q_last) xv[i] = i32x4{0, 0, 0, 0};
+                        wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf), (uint32_t)i * w_step + lane16);
+                        uint32_t off = begin + min(at + (uint32_t)i * 64, last);
+                        off = min(off, off - ring_bytes);
+                        xv[i] = *at4(reinterpret_cast<const i32x4 *>(ring), off);
                     }
-                }
-                if (!valid) {
+                    if (edge) {
 #pragma unroll
-                    for (int i = 0; i < kChunk; ++i) if (kb + i < ks1) xv[i] = i32x4{0, 0, 0, 0};
+                        for (int i = 0; i < kChunk; ++i) {
+                            if (kb + i >= ks1) continue;
+                            const int q = 4 * (kb + i) + g, y = y_in[0] + (int)(__umul24((unsigned)q, cells_rcp) >> 16);
+                            if (y < 0 || y >= h_in || q > q_last) xv[i] = i32x4{0, 0, 0, 0};
+                        }
+                    }
+                    if (!valid) {
+#pragma unroll
+                        for (int i = 0; i < kChunk; ++i) if (kb + i < ks1) xv[i] = i32x4{0, 0, 0, 0};
+                    }
+                    contract(xv, wv, kb);
                 }
-                contract(xv, wv, kb);
-            }
-        } else {
-            // likewise a row of the window, k_w positions; what lies outside the row is outside of both ends of its cells
-            const int k_w = a.k_w, w_in = a.w_in, row_cells = w_in * cells, win_cells = k_w * cells, x_in = ((x << a.s_w_log) - a.p_w) * cells, q_last = k_h * win_cells - 1;
-            const unsigned win_rcp = a.win_rcp, one = win_cells == 1;
-            const unsigned y_top = (unsigned)y_in;
+            } else {
+                // likewise a row of the window, k_w positions; what lies outside the row is outside of both ends of its cells
+                const int k_w = a.k_w, w_in = a.w_in, row_cells = w_in * cells, win_cells = k_w * cells, x_in = ((x << a.s_w_log) - a.p_w) * cells, q_last = k_h * win_cells - 1;
+                const unsigned win_rcp = a.win_rcp, one = win_cells == 1;
 #pragma unroll 1
-            for (int kb = ks0; kb < ks1; kb += kChunk) {
-                i32x4 xv[kChunk], wv[kChunk];
-                const unsigned char *wf = wf0 + (kb - ks0) * w_step;
-                uint32_t there = 0;
+                for (int kb = ks0; kb < ks1; kb += kChunk) {
+                    i32x4 xv[kChunk], wv[kChunk];
+                    const unsigned char *wf = wf0[0] + (kb - ks0) * w_step;
+                    uint32_t there = 0;
 #pragma unroll
-                for (int i = 0; i < kChunk; ++i) {
-                    if (kb + i >= ks1) continue;
-                    wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf), (uint32_t)i * w_step + lane16);
-                    const unsigned q = (unsigned)(4 * (kb + i) + g), ky = __umulhi(q, win_rcp) + __umul24(q, one);
-                    const int xc = x_in + (int)(q - __umul24(ky, (unsigned)win_cells));
-                    const bool ok = valid && y_top + ky < (unsigned)h_in && (unsigned)xc < (unsigned)row_cells && (int)q <= q_last;
-                    there |= ok ? 1u << i : 0u;
-                    unsigned slot = slot_o + ky;
-                    slot = min(slot, slot - (unsigned)ring_rows);
-                    slot = min(slot, slot - (unsigned)ring_rows);
-                    xv[i] = *at4(reinterpret_cast<const i32x4 *>(ring), ok ? (__umul24(slot, (unsigned)row_cells) + (unsigned)xc) * 16 : 0u);
+                    for (int i = 0; i < kChunk; ++i) {
+                        if (kb + i >= ks1) continue;
+                        wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf), (uint32_t)i * w_step + lane16);
+                        const unsigned q = (unsigned)(4 * (kb + i) + g), ky = __umulhi(q, win_rcp) + __umul24(q, one);
+                        const int xc = x_in + (int)(q - __umul24(ky, (unsigned)win_cells));
+                        const bool ok = valid && (unsigned)y_in[0] + ky < (unsigned)h_in && (unsigned)xc < (unsigned)row_cells && (int)q <= q_last;
+                        there |= ok ? 1u << i : 0u;
+                        unsigned slot = slot_o[0] + ky;
+                        slot = min(slot, slot - (unsigned)ring_rows);
+                        slot = min(slot, slot - (unsigned)ring_rows);
+                        xv[i] = *at4(reinterpret_cast<const i32x4 *>(ring), ok ? (__umul24(slot, (unsigned)row_cells) + (unsigned)xc) * 16 : 0u);
+                    }
+#pragma unroll
+                    for (int i = 0; i < kChunk; ++i)
+                        if (kb + i < ks1 && !((there >> i) & 1u)) xv[i] = i32x4{0, 0, 0, 0};
+                    contract(xv, wv, kb);
                 }
-#pragma unroll
-                for (int i = 0; i < kChunk; ++i)
-                    if (kb + i < ks1 && !((there >> i) & 1u)) xv[i] = i32x4{0, 0, 0, 0};
-                contract(xv, wv, kb);
+            }
+            if (COUNT && h.issued && g == 0 && pl == 0 && si < sel.n && issued) {
+                const int co_n = a.c_out - ct * 16 < 16 ? a.c_out - ct * 16 : 16;
+                atomicAdd(h.issued + (int64_t)sel_stream(sel, si) * h.n_layers + a.layer, (issued * (unsigned long long)co_n) << per_log);
             }
         }
-        if (COUNT && h.issued && g == 0 && pl == 0 && si < sel.n && issued) {
-            const int co_n = a.c_out - ct * 16 < 16 ? a.c_out - ct * 16 : 16;
-            atomicAdd(h.issued + (int64_t)sel_stream(sel, si) * h.n_layers + a.layer, (issued * (unsigned long long)co_n) << per_log);
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            if constexpr (T::kInst == 4) acc = (sums[0][i] + sums[1][i]) + (sums[2][i] + sums[3][i]);
+            else acc = sums[0][i];
+            if (TW > 1) share[(i * kTeam + kq) * 64 + lane] = acc;
+            else if (kq > 0) share[(kq - 1) * 64 + lane] = acc;
         }
-        if constexpr (T::kInst == 4) acc = (sums[0] + sums[1]) + (sums[2] + sums[3]);
-        else acc = sums[0];
-        if (kq > 0) share[(kq - 1) * 64 + lane] = acc;
     }
     if (CHAIN) later();
     barrier();
-    if (!on || kq > 0) return;
+    if (!on || (TW == 1 && kq > 0)) return;
+    if (TW > 1) {                                  // this wave's tile
+        if (ct + (kq & 1) >= n_ct) return;
+        ct += kq & 1;
+        valid = place(kq >> 1, o, x);
+    }
 
     const int co0 = ct * 16 + g * 4;
     st_t hv[4];
     {
         acc_t part[kTeam - 1];
+        if (TW > 1) acc = share[kq * kTeam * 64 + lane];
 #pragma unroll
-        for (int w = 0; w < kTeam - 1; ++w) part[w] = share[w * 64 + lane];
+        for (int w = 0; w < kTeam - 1; ++w) part[w] = share[(TW > 1 ? kq * kTeam + 1 + w : w) * 64 + lane];
         st_t c[4] = {0, 0, 0, 0};
         if (bias) {
 #pragma unroll
@@ -353,12 +451,12 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
 // the first 256 / the first 512 / all: 64 audio streams 6090 / 5980 / 5785 / 5732; 37 streams with 16 pushes per launch 742 / 738 /
 // 738 / 762; 32 images through six layers 606 / 583 / 551 / 615; one live stream 36.3, asking 32.2.
 constexpr int kFirst = 512;
-template <class T, int NS, bool COUNT>
+template <class T, int NS, bool COUNT, bool WIDE>
 __global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows(const GatherBatch<NS> args, const StreamSel sel)
 {
     typedef const __attribute__((address_space(4))) GatherBatch<NS> Batch;
     Batch &b = *(Batch *)__builtin_amdgcn_kernarg_segment_ptr();
-    __shared__ typename T::acc_t share[(kTeam - 1) * 64];
+    __shared__ typename T::acc_t share[(WIDE ? 4 * kTeam : kTeam - 1) * 64];
     // The steps' tiles follow each other without gaps: workgroups go to the compute units in turn, and with an empty one here
     // and there some units got the tiles of three layers and others none (12.7 us per launch of 64 audio streams instead of 7).
     int k = 0, tile = blockIdx.x;
@@ -389,14 +487,15 @@ __global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows(const Gather
         rest = inner >> subs;
         if ((sg << spt_log) >= n_sel) return;
     } else {
-        const int per = a.n_ct * a.n_pt;
+        const int per = a.n_cg * a.n_pt;
         sg = take == 1 ? tile : (int)((unsigned)tile / (unsigned)per);
         rest = take == 1 ? 0 : tile - sg * per;
     }
     if (take == 1) { take_rows<T>(b.head, a, sel, sg, threadIdx.x, 64 * kTeam); return; }
     if (take == 2) { pool_rows<T>(b.head, a, sel, sg, rest * kPoolCells, (rest + 1) * kPoolCells, 64 * kTeam); return; }
-    const int pt = a.ct_rcp ? (int)__umulhi((unsigned)rest, a.ct_rcp) : rest, ct = rest - pt * a.n_ct;
-    conv_tile<T, COUNT, false>(b.head, a, sel, sg << spt_log, pt, ct, spt_log, true, uni(threadIdx.x >> 6), share, [] { lds_barrier(); });
+    const int n_cg = a.n_cg, pt = a.ct_rcp ? (int)__umulhi((unsigned)rest, a.ct_rcp) : rest, cg = rest - pt * n_cg;
+    if (WIDE && a.wide) conv_tile<T, COUNT, false, 2>(b.head, a, sel, sg, pt, 2 * cg, 0, true, uni(threadIdx.x >> 6), share, [] { lds_barrier(); });
+    else conv_tile<T, COUNT, false, 1>(b.head, a, sel, sg << spt_log, pt, cg, spt_log, true, uni(threadIdx.x >> 6), share, [] { lds_barrier(); });
 }
 
 template <class T, int NS, bool COUNT>
@@ -419,7 +518,7 @@ __global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherB
                 Step *step = &a;
                 asm volatile("" : "+s"(step));     // (a tile's arguments are read anew: kept over the loop they do not fit the registers)
                 const int t = t0 + team, pt = a.ct_rcp ? (int)__umulhi((unsigned)t, a.ct_rcp) : t, ct = t - pt * a.n_ct;
-                conv_tile<T, COUNT, true>(b.head, *step, sel, si, pt, ct, 0, t < tasks, kq, share[team], [] { lds_barrier(); });
+                conv_tile<T, COUNT, true, 1>(b.head, *step, sel, si, pt, ct, 0, t < tasks, kq, share[team], [] { lds_barrier(); });
                 lds_barrier();                     // the sums have been read
             }
         }
@@ -457,7 +556,15 @@ int streams_per_tile_log(int positions, bool first)
     return l;
 }
 
-template <class T, int NS> hipError_t launch_ns(const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc)
+// Tiles of a launch from which on they go two by two: a wave then fetches four operands for four products instead of eight, and
+// all four waves bring a tile to its end, but a quarter of the workgroups has to fill the chip.  GPU time per pass, single tiles against
+// two by two: audio net, 16 pushes per launch, 12 streams (1,536 tiles) 183 us against 184, 16 streams 213 : 191, 37 streams 374 : 299,
+// 64 streams 546 : 406, but 8 streams 151 : 170; six-layer net, 4 rows per push, 64 images of 79 x 79 (some 1,500 tiles) float32
+// 188 : 182, bfloat16 162 : 141, 15 images of 160 x 160 (700) 296 : 334 and 255 : 256.
+constexpr int kWideTiles = 1536;
+bool wide_step(const GatherStep &a) { return a.take == 0 && a.n_ct >= 2 && a.n_pt >= 2 && a.spt_log == 0; }
+
+template <class T, int NS, bool WIDE> hipError_t launch_ns(const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc)
 {
     GatherBatch<NS> b;
     b.head = h;
@@ -473,8 +580,12 @@ template <class T, int NS> hipError_t launch_ns(const GatherHead &h, const Gathe
     for (int k = 0; k < h.n; ++k) {
         b.st[k] = st[k];
         GatherStep &a = b.st[k];
+        if (WIDE && (a.wide = wide_step(a))) {
+            a.n_cg = (a.n_ct + 1) / 2; a.n_pt = (a.n_pt + 1) / 2;
+            a.ct_rcp = a.n_cg > 1 ? (unsigned)((0x100000000ull + a.n_cg - 1) / a.n_cg) : 0u;
+        }
         const int groups = b.head.n_sb > 0 ? b.head.n_sb8 << (b.head.sb_log - a.spt_log) : (sel.n + (1 << a.spt_log) - 1) >> a.spt_log;
-        a.tiles = groups * (a.take == 1 ? 1 : a.n_ct * a.n_pt);
+        a.tiles = groups * (a.take == 1 ? 1 : a.n_cg * a.n_pt);
         tiles += b.st[k].tiles;
         if (k < 8 && k + 1 < h.n) b.head.end[k] = (int)tiles;
     }
@@ -484,13 +595,18 @@ template <class T, int NS> hipError_t launch_ns(const GatherHead &h, const Gathe
     }
     if (tiles < 1 || tiles > INT32_MAX / (64 * kTeam)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles), block(64 * kTeam);
-    return h.issued ? launch(k_conv_gather_rows<T, NS, true>, grid, block, 0, lc, b, sel) : launch(k_conv_gather_rows<T, NS, false>, grid, block, 0, lc, b, sel);
+    if constexpr (WIDE) return launch(k_conv_gather_rows<T, NS, false, true>, grid, block, 0, lc, b, sel);
+    else return h.issued ? launch(k_conv_gather_rows<T, NS, true, false>, grid, block, 0, lc, b, sel) : launch(k_conv_gather_rows<T, NS, false, false>, grid, block, 0, lc, b, sel);
 }
 
 template <class T> hipError_t launch_t(const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc)
 {
+    // tiles of two by two where there are so many that the chip is full with a quarter of them
+    int64_t tiles = 0;
+    for (int k = 0; k < h.n; ++k) if (st[k].take == 0) tiles += (int64_t)((sel.n + (1 << st[k].spt_log) - 1) >> st[k].spt_log) * st[k].n_ct * st[k].n_pt;
+    if (!chain && !h.issued && tiles >= kWideTiles) return launch_ns<T, kGatherMax, true>(h, st, sel, false, lc);
     // (the short block for the usual few steps: a third of the bytes to hand over)
-    return h.n <= 4 ? launch_ns<T, 4>(h, st, sel, chain, lc) : launch_ns<T, kGatherMax>(h, st, sel, chain, lc);
+    return h.n <= 4 ? launch_ns<T, 4, false>(h, st, sel, chain, lc) : launch_ns<T, kGatherMax, false>(h, st, sel, chain, lc);
 }
 
 }  // namespace
@@ -499,11 +615,12 @@ template <class T> hipError_t launch_t(const GatherHead &h, const GatherStep *st
 void conv_gather_shape(bool first, GatherStep &a)
 {
     auto rcp32 = [](int n) { return n > 1 ? (unsigned)((0x100000000ull + n - 1) / n) : 0u; };
-    if (a.take == 1) { a.spt_log = 0; a.n_pt = 1; return; }
+    if (a.take == 1) { a.spt_log = 0; a.n_pt = a.n_cg = 1; return; }
     const int positions = a.n_rows * a.w_out;
-    if (a.take == 2) { a.spt_log = 0; a.n_ct = 1; a.n_pt = (positions * a.cells + kPoolCells - 1) / kPoolCells; a.ct_rcp = 0; return; }
+    if (a.take == 2) { a.spt_log = 0; a.n_ct = a.n_cg = 1; a.n_pt = (positions * a.cells + kPoolCells - 1) / kPoolCells; a.ct_rcp = 0; return; }
     a.spt_log = streams_per_tile_log(positions, first);
     a.n_pt = (positions + (16 >> a.spt_log) - 1) / (16 >> a.spt_log);
+    a.n_cg = a.n_ct;
     a.ct_rcp = rcp32(a.n_ct);
 }
 
