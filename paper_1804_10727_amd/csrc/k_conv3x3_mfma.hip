@@ -540,6 +540,10 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         for (int q = 0; q < MC; ++q)
             *at4(reinterpret_cast<acc_t *>(d), (uint32_t)((x * C_out + co1 + q * 4) * 4)) = acc_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
     };
+    auto activated = [&](st_t c) IDF_INLINE {
+        if constexpr (kFloat) return at_least(c, act == IDF_ACT_NONE ? __builtin_nanf("") : 0.f);
+        else return T::activate(c, act, shr, clamp_hi);
+    };
     auto count = [&](const uint32_t (&e)[MC * EB]) IDF_INLINE {
         uint32_t n = 0;
 #pragma unroll
@@ -557,7 +561,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
                 if (j >= rows) break;
                 st_t v[NV];
 #pragma unroll
-                for (int q = 0; q < NV; ++q) v[q] = T::activate(acc[j][q >> 2][np][q & 3], act, shr, clamp_hi);
+                for (int q = 0; q < NV; ++q) v[q] = activated(acc[j][q >> 2][np][q & 3]);
                 if (!ok) continue;
                 if (to_output) {
                     emit_out(v, W, x, slot_of(rg * NR + j));
@@ -580,7 +584,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
                 if (j >= rows) break;
                 st_t u[NV];
 #pragma unroll
-                for (int q = 0; q < NV; ++q) u[q] = T::activate(acc[j][q >> 2][np][q & 3], act, shr, clamp_hi);
+                for (int q = 0; q < NV; ++q) u[q] = activated(acc[j][q >> 2][np][q & 3]);
                 if (y + j >= pool_from && ok) {
                     uint32_t e[MC * EB];
 #pragma unroll

@@ -174,7 +174,7 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassSt
             asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"((int32_t)v >> act_shr), "s"(act_lo), "v"(act_hi));
             return (st_t)r;
         } else {
-            return act_none ? v : fmaxf(v, 0.f);
+            return at_least(v, act_none ? __builtin_nanf("") : 0.f);
         }
     };
     int t = wave;
