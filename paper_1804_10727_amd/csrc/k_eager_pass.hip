@@ -12,15 +12,18 @@
 //     maxima of two rows in registers and one exchange of lanes;
 //   * between layers there is one barrier over LDS; the stores of state and announced values are not waited for.
 // What bounds it is the chain: every layer is a memory round trip for its weights, a few dozen matrix
-// instructions and about a hundred others per wave, one after the other.  Hence sixteen waves with small shares
+// instructions and some five hundred others per wave, one after the other.  Hence sixteen waves with small shares
 // (eight waves with all the rows of a band each took 1.3 times as long), one copy of the code for every layer,
-// which then stays in the instruction cache, and weights and state on their way before the barrier.
+// which then stays in the instruction cache, weights asked for before the values of the layer before them are
+// worked out, and states before the barrier.
 // With sixteen waves on four SIMDs an instruction of a wave takes its turn every 16 cycles or so, scalar ones included: a layer takes
-// as long as the instructions beside the matrix ones are many.  Hence one batch of arguments, worked out as far as the host can,
-// three-operand bounds, bytes packed and counted by the word, and rows that nothing reaches left out (int8 4173 -> 3866 us per
-// image of 112 x 112, eight streams; float32 unchanged).
-// Measured per pushed row, layer by layer before: int8, 8 streams of 112 x 112, 34.5 us (170); float32, 256 streams of
-// 32 x 32, 35 us (112), of which 18 us are matrix instructions.
+// as long as the instructions beside the matrix ones are many.  Hence arguments that a wave keeps in the lanes of two registers, a step
+// ahead, and takes from there where it needs them (as scalar loads they were waited for, and of sixty values at once a third were put
+// aside and fetched back: 3975 instead of 3785 us, all else equal), worked out as far as the host can, three-operand bounds, bytes packed
+// and counted by the word, and rows that nothing reaches left out.
+// Measured per image of 112 x 112, int8, eight streams, 112 pushes: 4173 us, with fewer instructions 3860, waiting for weights and
+// states together 3727, as it is 3195; float32, 256 streams of 32 x 32, 32 pushes: 1130 -> 1034 us.  Per pushed row 28.5 us (layer by
+// layer 170) and 32 us (112), of which 18 us are matrix instructions.
 #include <algorithm>
 #include <type_traits>
 
@@ -36,7 +39,6 @@ typedef const __attribute__((address_space(4))) EagerPassStep PassStep;
 typedef const __attribute__((address_space(4))) EagerPass PassArgs;
 
 constexpr int kPassWaves = 16, kPassThreads = 64 * kPassWaves;
-constexpr int kQueue = 3;                        // K-steps whose weights are on their way
 
 // Zero times infinity is not zero: in a float net the first layer's positions carry as many cells of zeros as the last K-step of
 // their windows reads too far.  (Layers behind it have a multiple of 16 channels: their windows are whole K-steps.)
@@ -108,67 +110,87 @@ template <class T> __device__ __forceinline__ void pass_input(PassArgs &a, PassS
     if ((tid & 63) == 0 && ev) atomicAdd(events, ev);
 }
 
+// A step's arguments as a wave keeps them: lane i holds word i, and a value is taken from its lane where it is used.
+constexpr int kStepWords = sizeof(EagerPassStep) / 4;
+static_assert(kStepWords <= 64, "a word to each lane");
+__device__ __forceinline__ int step_words(PassStep *L)
+{
+    const int lane = threadIdx.x & 63;
+    return ((const __attribute__((address_space(4))) int *)L)[lane < kStepWords ? lane : kStepWords - 1];
+}
+template <class V> __device__ __forceinline__ V step_value(int words, int at)
+{
+    if constexpr (sizeof(V) == 8) return (V)(__attribute__((address_space(1))) void *)((uint64_t)(uint32_t)__builtin_amdgcn_readlane(words, at) | (uint64_t)(uint32_t)__builtin_amdgcn_readlane(words, at + 1) << 32);
+    else return (V)__builtin_amdgcn_readlane(words, at);
+}
+#define IDF_OF(words, field) step_value<decltype(EagerPassStep::field)>(words, (int)offsetof(EagerPassStep, field) / 4)
+
+// The weights a wave has on their way: of one K-step, the task's next or behind its last the first of the wave's next task, which as a
+// rule is of the next layer and has the time of all that stands between.  (Three K-steps on their way, asked for at every task whether
+// it has them or not: int8 3785 instead of 3310 us, float32 1074 instead of 1058.  Asked for where it has them, they would be out or
+// not: every wait then counts as if they were not.)
+template <class T> struct Weights {
+    i32x4 q[3];
+    const unsigned char *base[3];                  // of each tap row
+    int ct, rest;                                  // the task: its tile of channels, and what is left of its number
+    uint32_t step, off;                            // bytes from one K-step to the next; this lane's place in the one asked for next
+    __device__ __forceinline__ void aim(int words, int t)      // at task t of a step
+    {
+        const int n_ct = IDF_OF(words, n_ct);
+        rest = (int)__umulhi((unsigned)t, IDF_OF(words, ct_rcp)) + (n_ct == 1 ? t : 0);
+        ct = t - rest * n_ct;
+        const uint32_t w_ky = IDF_OF(words, w_ky);
+        const void *w_frag = IDF_OF(words, w_frag);
+        step = IDF_OF(words, w_kstep);
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) base[ky] = (const unsigned char *)w_frag + ((ct >> 1) * 6144 + (ct & 1) * 1024 + ky * w_ky);
+        off = (threadIdx.x & 63) * 16;
+    }
+    __device__ __forceinline__ void fetch()
+    {
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) q[ky] = *at4(reinterpret_cast<const i32x4 *>(base[ky]), off);
+        off += step;
+    }
+};
+
 // ---- one conv layer, and the 2x2 max-pool behind it ------------------------------------------------------
-template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassStep &L, int stream, uint32_t *all_events)
+template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, int words, int next, Weights<T> &wt, int stream, uint32_t *all_events)
 {
     using acc_t = typename T::acc_t; using st_t = typename T::st_t;
     constexpr bool kInt = T::EB == 1;
-    // All of the step in one batch (but for what depends on the group of rows): left to first use these were fifteen scalar loads one
-    // after the other, by each of sixteen waves.
-    const int tasks = L.tasks, n_ct = L.n_ct, n_xt = L.n_xt, W = L.w, C_out = L.c_out, co_g = L.co_g, n_ksteps = L.n_ksteps, band0 = L.band0;
-    const int cells = L.cells, lds_in = L.lds_in, in_pitch = L.in_pitch, in_stride = L.in_stride, layer = L.layer, emit = L.emit, pool = L.pool, out_w = L.out_w;
-    const int act_none = L.act_none, act_lo = L.act_lo, act_hi = L.act_hi, act_shr = L.act_shr, lds_out = L.lds_out, out_first = L.out_first;
-    const int out_pitch = L.out_pitch, out_stride = L.out_stride, out_rows = L.out_rows, out_done = L.out_done, out_end = L.out_end, row0 = L.row0, n_in = L.n_in;
-    const unsigned ct_rcp = L.ct_rcp, xt_rcp = L.xt_rcp;
-    const uint32_t w_kstep = L.w_kstep, w_ky = L.w_ky, c_stride = L.c_stride, rows_in = L.rows_in, rows_on = L.rows_on, rows_old = L.rows_old;
-    const uint32_t ann_stride = L.ann_stride, row_bytes = L.row_bytes, pool_on = L.pool_on;
-    void *c = L.c, *ann_map = L.ann;
-    const void *w_frag = L.w_frag;
-    asm volatile("" ::"s"(tasks), "s"(n_ct), "s"(n_xt), "s"(W), "s"(C_out), "s"(co_g), "s"(n_ksteps), "s"(band0), "s"(cells), "s"(lds_in), "s"(in_pitch),
-                 "s"(in_stride), "s"(layer), "s"(emit), "s"(pool), "s"(out_w), "s"(act_none), "s"(act_lo), "s"(act_hi), "s"(act_shr), "s"(ct_rcp), "s"(xt_rcp),
-                 "s"(w_kstep), "s"(w_ky), "s"(c_stride), "s"(rows_in), "s"(rows_on), "s"(rows_old));
-    asm volatile("" ::"s"(lds_out), "s"(out_first), "s"(out_pitch), "s"(out_stride), "s"(out_rows), "s"(out_done), "s"(out_end), "s"(row0), "s"(n_in), "s"(ann_stride),
-                 "s"(row_bytes), "s"(pool_on), "s"(c), "s"(ann_map), "s"(w_frag));
+#define STEP(field) IDF_OF(words, field)
+    const int tasks = STEP(tasks), n_ksteps = STEP(n_ksteps), layer = STEP(layer), emit = STEP(emit), pool = STEP(pool);
+    const int C_out = STEP(c_out), in_pitch = STEP(in_pitch), in_stride = STEP(in_stride), cells = STEP(cells);
+    const int out_pitch = STEP(out_pitch), out_stride = STEP(out_stride);
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6), m = lane & 15, g = lane >> 4;
-    char *c_map = (char *)c + (int64_t)stream * c_stride * 4;
+    char *c_map = (char *)STEP(c) + (uint64_t)(uint32_t)stream * STEP(c_stride) * 4;
 
     acc_t old[4];                                  // states as they were
-    i32x4 wq[kQueue][3];
-    const unsigned char *w_base[3];
-    uint32_t w_off = 0;
     int xt = 0, gi = 0, x = 0, co0 = 0;
     uint32_t cell = 0;                             // this lane's first channel, bytes into a row
     uint32_t c_off[4];                             // bytes from a stream's first row kept to each row
     bool here = false;
-    auto fetch_w = [&](i32x4 (&w)[3]) IDF_INLINE {
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky) w[ky] = *at4(reinterpret_cast<const i32x4 *>(w_base[ky]), w_off);
-        w_off += w_kstep;
-    };
-    // everything a task needs from memory is asked for before its cells are
-    auto begin = [&](int t) IDF_INLINE {
-        const int rest = (int)__umulhi((unsigned)t, ct_rcp) + (n_ct == 1 ? t : 0), ct = t - rest * n_ct;
-        gi = (int)__umulhi((unsigned)rest, xt_rcp) + (n_xt == 1 ? rest : 0);
+    // the states of a task are asked for before its cells are there
+    auto begin = [&]() IDF_INLINE {
+        const int n_xt = STEP(n_xt), rest = wt.rest, ct = wt.ct;
+        gi = (int)__umulhi((unsigned)rest, STEP(xt_rcp)) + (n_xt == 1 ? rest : 0);
         xt = rest - gi * n_xt;
-        const uint32_t s01 = ((const __attribute__((address_space(4))) uint32_t *)L.c_slot)[2 * gi], s23 = ((const __attribute__((address_space(4))) uint32_t *)L.c_slot)[2 * gi + 1];
-        __builtin_amdgcn_sched_barrier(0);         // (asked for before the weights)
-        const unsigned char *first = (const unsigned char *)w_frag + (ct >> 1) * 6144 + (ct & 1) * 1024;
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky) w_base[ky] = first + ky * w_ky;
-        w_off = (uint32_t)lane * 16;
-#pragma unroll
-        for (int d = 0; d < kQueue; ++d)
-            if (d < n_ksteps) fetch_w(wq[d]);
         x = xt * 16 + m;
-        co0 = (ct >> 1) * 32 + (ct & 1) * 4 + g * co_g;
-        here = x < W && co0 < C_out;
+        co0 = (ct >> 1) * 32 + (ct & 1) * 4 + g * STEP(co_g);
+        here = (int)(x < STEP(w)) & (int)(co0 < C_out);
         cell = here ? (uint32_t)(x * C_out + co0) * 4 : 0;
+        constexpr int kSlot = (int)offsetof(EagerPassStep, c_slot) / 4;
+        const uint32_t s01 = step_value<uint32_t>(words, kSlot + 2 * gi), s23 = step_value<uint32_t>(words, kSlot + 1 + 2 * gi), row_bytes = STEP(row_bytes);
         c_off[0] = (s01 & 0xffffu) * row_bytes; c_off[1] = (s01 >> 16) * row_bytes;
         c_off[2] = (s23 & 0xffffu) * row_bytes; c_off[3] = (s23 >> 16) * row_bytes;
         // (rows without a state are read like the others: their places exist)
 #pragma unroll
         for (int j = 0; j < 4; ++j) old[j] = *at4(reinterpret_cast<const acc_t *>(c_map + c_off[j]), cell);
     };
+    const int act_none = STEP(act_none), act_lo = STEP(act_lo), act_shr = STEP(act_shr);
+    int act_hi = STEP(act_hi);
+    asm("" : "+v"(act_hi));                        // (an instruction takes one scalar)
     auto act = [&](st_t v) IDF_INLINE {
         if constexpr (kInt) {                      // (the bounds are in order: one instruction)
             int32_t r;
@@ -178,35 +200,38 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassSt
             return at_least(v, act_none ? __builtin_nanf("") : 0.f);
         }
     };
-    const bool counts = layer + 1 < a.n_layers;
     uint32_t ev = 0, ev_pool = 0;                  // (int8: of this lane; float32: of the wave)
-    // Rounds of one way in and one way out, all a wave waits for behind it: where a loop was left from the middle, or a request was made
-    // on one of two ways, the compiler takes it to be out still, and had every layer wait for its weights before it asked for the states
-    // (int8 3860 -> 3727 us per image of 112 x 112, eight streams).
-    int rounds = (tasks + kPassWaves - 1) / kPassWaves, t = wave;
+    // the band is there, and nobody reads what this layer overwrites any more; what is passed on has zeros in front of each row, and
+    // behind it as far as no lane of the tiles reaches
+    auto enter = [&]() IDF_INLINE {
+        lds_barrier();
+        const int out_rows = STEP(out_rows), out_done = STEP(out_done), out_end = STEP(out_end);
+        if (emit) for (int r = wave; r < out_rows; r += kPassWaves) {
+            unsigned char *row = pass_smem + STEP(lds_out) + r * out_pitch;
+            for (int o = lane * 16; o < out_stride; o += 1024) *reinterpret_cast<i32x4 *>(row + o) = i32x4{0, 0, 0, 0};
+            for (int o = out_done + lane * 16; o < out_end; o += 1024) *reinterpret_cast<i32x4 *>(row + o) = i32x4{0, 0, 0, 0};
+        }
+    };
+    // Every wave takes the same way, one without a task too, and a state is known to be here before a round ends: a request made on one
+    // of two ways counts as out wherever they meet, and had the next layer wait for what it did not need yet.
+    int rounds = (int)((unsigned)(tasks + kPassWaves - 1) / kPassWaves), t = wave;
     asm volatile("" : "+s"(rounds));
 #pragma unroll 1
-    for (int i = 0; i < rounds; ++i, t += kPassWaves) {
-        if (t < tasks) begin(t);
-        if (i == 0) {
-            lds_barrier();                         // the band is there, and nobody reads what this layer overwrites any more
-            // what is passed on has zeros in front of each row, and behind it as far as no lane of the tiles reaches
-            if (emit) for (int r = wave; r < out_rows; r += kPassWaves) {
-                unsigned char *row = pass_smem + lds_out + r * out_pitch;
-                for (int o = lane * 16; o < out_stride; o += 1024) *reinterpret_cast<i32x4 *>(row + o) = i32x4{0, 0, 0, 0};
-                for (int o = out_done + lane * 16; o < out_end; o += 1024) *reinterpret_cast<i32x4 *>(row + o) = i32x4{0, 0, 0, 0};
-            }
-        }
-        if (t >= tasks) continue;
+    do {
+        --rounds;
+        const int n_mine = t < tasks ? n_ksteps : 0;           // (a wave without a task asks for its next weights like the others)
+        if (n_mine) begin();
+        if (t < kPassWaves) enter();
         acc_t acc[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = acc_t{0, 0, 0, 0};
-        const uint32_t in = rows_in >> (4 * gi);   // bit r: row r - 1 of the four (-1 .. 4) is in the band
+        const uint32_t in = STEP(rows_in) >> (4 * gi);   // bit r: row r - 1 of the four (-1 .. 4) is in the band
         {
-            const uint32_t base = (uint32_t)(lds_in + (xt * 16 + m) * in_stride);
-            uint32_t row[6];                       // where the six rows lie (those outside the band: somewhere inside)
+            const uint32_t base = (uint32_t)(STEP(lds_in) + (xt * 16 + m) * in_stride);
+            const uint32_t row0 = (uint32_t)((STEP(band0) + 4 * gi) * in_pitch);
+            uint32_t row[6];                       // where the six rows lie (those outside the band: its first)
 #pragma unroll
-            for (int r = 0; r < 6; ++r) row[r] = (uint32_t)(min(max(band0 + 4 * gi + r, 0), n_in - 1) * in_pitch);
+            for (int r = 0; r < 6; ++r) row[r] = (in >> r) & 1u ? row0 + (uint32_t)r * (uint32_t)in_pitch : 0u;
             // K-step st holds cells 4 st .. 4 st + 3 of the window's 3 * cells, counted tap column by tap column (past the end, where
             // the weights are zero, the padding of the last position; int8: the last one again); few channels: the cells of the
             // gathered window
@@ -216,7 +241,7 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassSt
                 if (kInt) q = q < 3 * cells ? q : 3 * cells - 1;
                 return base + (uint32_t)(((q >= cells) + (q >= 2 * cells)) * (in_stride - cells * 16) + q * 16);
             };
-            auto kstep = [&](const i32x4 (&w)[3], uint32_t off) IDF_INLINE {
+            auto kstep = [&](uint32_t off) IDF_INLINE {
                 i32x4 xv[6];
 #pragma unroll
                 for (int r = 0; r < 6; ++r)
@@ -228,27 +253,27 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassSt
                     for (int e = 0; e < T::kInst; ++e)
 #pragma unroll
                         for (int ky = 0; ky < 3; ++ky)
-                            if (r - ky >= 0 && r - ky < 4) acc[r - ky] = T::mfma(w[ky], xv[r], acc[r - ky], e);
+                            if (r - ky >= 0 && r - ky < 4) acc[r - ky] = T::mfma(wt.q[ky], xv[r], acc[r - ky], e);
                 }
             };
+            int st = 0;
 #pragma unroll 1
-            for (int st = 0; st < n_ksteps; st += kQueue) {
-#pragma unroll
-                for (int d = 0; d < kQueue; ++d) {
-                    if (st + d >= n_ksteps) continue;
-                    kstep(wq[d], at(st + d));
-                    if (st + d + kQueue < n_ksteps) fetch_w(wq[d]);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
+            do {
+                if (st + 1 >= n_mine) wt.aim(rounds ? words : next, rounds ? t + kPassWaves : wave);
+                if (n_mine) kstep(at(st));
+                wt.fetch();
+                __builtin_amdgcn_sched_barrier(0);
+            } while (++st < n_mine);
         }
-        __builtin_amdgcn_s_waitcnt(0xf70);         // vmcnt(0): weights and states are here, whichever way was taken
+        __builtin_amdgcn_s_waitcnt(0xf73);         // vmcnt(3): all but the weights asked for last are here
+        __builtin_amdgcn_sched_barrier(0);
+        if (n_mine) {
         // the state moves on; what is announced is f of it, less f of what it was
-        const uint32_t on = rows_on >> (4 * gi), had = rows_old >> (4 * gi);
+        const uint32_t on = STEP(rows_on) >> (4 * gi), had = STEP(rows_old) >> (4 * gi);
         const bool out_ok = emit && co0 < C_out;
-        unsigned char *out = pass_smem + lds_out + out_first * out_pitch + co0 * T::EB;
+        unsigned char *out = pass_smem + STEP(lds_out) + STEP(out_first) * out_pitch + co0 * T::EB;
         // the differences of four channels (zero beyond the row's end) are counted and passed on
-        auto deliver = [&](const acc_t &h_new, const acc_t &h_old, bool mine, bool count, uint32_t &n, unsigned char *to, bool pass) IDF_INLINE {
+        auto deliver = [&](const acc_t &h_new, const acc_t &h_old, bool mine, uint32_t &n, unsigned char *to, bool pass) IDF_INLINE {
             st_t d[4];
             uint32_t e[T::EB];
 #pragma unroll
@@ -256,20 +281,21 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassSt
             if constexpr (kInt) {
                 T::pack4(d, e);
                 e[0] = mine ? e[0] : 0u;
-                if (count) n += (uint32_t)T::nonzero(e[0]);
+                n += (uint32_t)T::nonzero(e[0]);
                 if (pass) *reinterpret_cast<uint32_t *>(to) = e[0];
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) d[i] = mine ? d[i] : (st_t)0;
-                if (count) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) n += (uint32_t)__builtin_popcountll(__ballot(d[i] != 0));
-                }
+                for (int i = 0; i < 4; ++i) n += (uint32_t)__builtin_popcountll(__ballot(d[i] != 0));
                 T::pack4(d, e);
                 if (pass) *reinterpret_cast<i32x4 *>(to) = i32x4{(int)e[0], (int)e[1], (int)e[2], (int)e[3]};
             }
         };
-        char *ann = ann_map && !pool ? (char *)ann_map + ((int64_t)stream * ann_stride + (int64_t)(row0 + 4 * gi) * W * C_out) * 4 : nullptr;
+        void *ann_map = STEP(ann);
+        const uint32_t ann_stride = STEP(ann_stride), pool_on = STEP(pool_on);
+        const int W = STEP(w), out_w = STEP(out_w);
+        char *ann = ann_map && !pool ? (char *)ann_map + ((int64_t)stream * ann_stride + (int64_t)(STEP(row0) + 4 * gi) * W * C_out) * 4 : nullptr;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             acc_t h_new[2], h_old[2];
@@ -289,7 +315,7 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassSt
                     *at4(reinterpret_cast<acc_t *>(c_map + c_off[j]), cell) = acc[j];
                     if (ann) *at4(reinterpret_cast<acc_t *>(ann + (int64_t)(j * W * C_out) * 4), cell) = h_new[q];
                 }
-                deliver(h_new[q], h_old[q], here, counts, ev, out + (4 * gi + j) * out_pitch + (x + 1) * out_stride, !pool && out_ok);
+                deliver(h_new[q], h_old[q], here, ev, out + (4 * gi + j) * out_pitch + (x + 1) * out_stride, !pool && out_ok);
             }
             if (pool && ((pool_on >> (2 * gi + p)) & 1u)) {
                 const bool mine = (x & 1) == 0 && (x >> 1) < out_w && co0 < C_out;
@@ -301,19 +327,23 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, PassSt
                     n[i] = nn > nx ? nn : nx;
                     o[i] = oo > ox ? oo : ox;
                 }
-                if (mine) *at4(reinterpret_cast<acc_t *>((char *)ann_map + (int64_t)stream * ann_stride * 4 + (int64_t)((L.pool_slots[gi] >> p * 16) & 0xffffu) * (out_w * C_out * 4)),
+                if (mine) *at4(reinterpret_cast<acc_t *>((char *)ann_map + (int64_t)stream * ann_stride * 4 + (int64_t)((step_value<uint32_t>(words, (int)offsetof(EagerPassStep, pool_slots) / 4 + gi) >> p * 16) & 0xffffu) * (out_w * C_out * 4)),
                                (uint32_t)((x >> 1) * C_out + co0) * 4) = n;
-                deliver(n, o, mine, true, ev_pool, out + (2 * gi + p) * out_pitch + ((x >> 1) + 1) * out_stride, emit && mine);
+                deliver(n, o, mine, ev_pool, out + (2 * gi + p) * out_pitch + ((x >> 1) + 1) * out_stride, emit && mine);
             }
         }
-    }
+        }
+        t += kPassWaves;
+    } while (rounds);
     if constexpr (kInt) {
         ev = wave_sum(ev);
         if (pool) ev_pool = wave_sum(ev_pool);
     }
+    // (an instruction each: an atomic of the language is prepared for lanes of many)
     if (lane == 0) {
-        if (ev) atomicAdd(all_events + layer + 1, ev);
-        if (ev_pool) atomicAdd(all_events + layer + 2, ev_pool);
+        const uint32_t level = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t *)(all_events + layer);
+        asm volatile("ds_add_u32 %0, %1 offset:4" ::"v"(level), "v"(ev) : "memory");         // (the last layer's are of no level: nobody looks at that place)
+        if (pool) asm volatile("ds_add_u32 %0, %1 offset:8" ::"v"(level), "v"(ev_pool) : "memory");
     }
 }
 
@@ -324,15 +354,23 @@ __global__ void __launch_bounds__(kPassThreads, 4) k_eager_pass(const EagerPass 
     PassArgs &a = *(PassArgs *)__builtin_amdgcn_kernarg_segment_ptr();
     __shared__ uint32_t events[2 * kPassMax + 2];      // per level
     const int tid = threadIdx.x, stream = sel_stream(sel, blockIdx.x);
+    const int n = a.n;
+    int words = step_words(&a.st[0]), next = step_words(&a.st[n > 1 ? 1 : 0]);
     if (tid < 2 * kPassMax + 2) events[tid] = 0;
     request_arguments<sizeof(EagerPass), kPassWaves>(&a, &a + 1);
+    Weights<T> wt;
+    wt.aim(words, uni(tid >> 6));
+    wt.fetch();
+    asm volatile("" : "+v"(next));
     lds_barrier();
     pass_input<T>(a, a.st[0], stream, sel.pos0 + (int)blockIdx.x, &events[0]);
-    const int n = a.n;
 #pragma unroll 1
     for (int k = 0; k < n; ++k) {
-        PassStep &L = a.st[k];
-        pass_conv<T>(a, L, stream, events);
+        asm volatile("" : "+v"(next));             // (it is here)
+        const int after = step_words(&a.st[k + 2 < n ? k + 2 : n - 1]);
+        pass_conv<T>(a, words, next, wt, stream, events);
+        words = next;
+        next = after;
     }
     lds_barrier();
     if (tid < a.n_layers && events[tid]) atomicAdd(a.stats + ((int64_t)stream * a.n_layers + tid) * 2, (unsigned long long)events[tid]);
