@@ -265,25 +265,34 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
                     x_s[tp] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, ok ? (int)off : INT32_MIN, 0, 0));
                 }
             };
+            auto contract = [&](const i32x4 (&x_s)[TW], const i32x4 (&w_s)[TW]) IDF_INLINE {
+#pragma unroll
+                for (int tp = 0; tp < TW; ++tp) {
+                    if (__ballot(T::or_of(x_s[tp]) != 0) == 0ull) continue;
+#pragma unroll
+                    for (int e = 0; e < T::kInst; ++e)
+#pragma unroll
+                        for (int tc = 0; tc < TW; ++tc) sums[e][tp * TW + tc] = T::mfma(w_s[tc], x_s[tp], sums[e][tp * TW + tc], e);
+                }
+            };
             if (ks0 < ks1) {                       // (short windows leave a wave without a K-step)
 #pragma unroll
                 for (int i = 0; i < kStages; ++i) fetch(xv[i], wv[i], ks0 + i);
-            }
+                int ks = ks0;
 #pragma unroll 1
-            for (int ks = ks0; ks < ks1; ks += kStages) {
+                for (; ks + kStages < ks1; ks += kStages) {
 #pragma unroll
-                for (int i = 0; i < kStages; ++i) {
-#pragma unroll
-                    for (int tp = 0; tp < TW; ++tp) {
-                        if (ks + i >= ks1 || __ballot(T::or_of(xv[i][tp]) != 0) == 0ull) continue;
-#pragma unroll
-                        for (int e = 0; e < T::kInst; ++e)
-#pragma unroll
-                            for (int tc = 0; tc < TW; ++tc) sums[e][tp * TW + tc] = T::mfma(wv[i][tc], xv[i][tp], sums[e][tp * TW + tc], e);
+                    for (int i = 0; i < kStages; ++i) {
+                        contract(xv[i], wv[i]);
+                        fetch(xv[i], wv[i], ks + kStages + i);
+                        __builtin_amdgcn_sched_barrier(0);
                     }
-                    fetch(xv[i], wv[i], ks + kStages + i);
-                    __builtin_amdgcn_sched_barrier(0);
                 }
+                // (the last ones stand behind the loop: nothing is asked for that no K-step is left for.  Three requests of twelve in a wave
+                // with nine K-steps were; a launch of 37 audio streams with 16 pushes each 13.4 -> 12.5 us, of 64 18.5 -> 17.1)
+#pragma unroll
+                for (int i = 0; i < kStages; ++i)
+                    if (ks + i < ks1) contract(xv[i], wv[i]);
             }
         } else {
             unsigned long long issued = 0;
