@@ -7,7 +7,7 @@
 // were complete before it, and one that puts the caller's new rows into the first ring.
 //
 // Max-pools, in nets that have them, are steps of the same launch.  Measured per image of 112 x 112, 32 streams, float32,
-// six layers (5x5 and 3x3 with stride 2, 3x3, 1x1, a pool): 551 us, 4.9 per row; a launch per layer, the layers that are not
+// six layers (5x5 and 3x3 with stride 2, 3x3, 1x1, a pool): 545 us, 4.9 per row; a launch per layer, the layers that are not
 // 3x3 with stride 1 on the vector units: 4360, 39 per row.
 //
 // The work is a matrix product: the columns of the instruction are output positions -- of one stream, or, where
@@ -223,7 +223,7 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
             // (tiles of one stream: a lane's place outside the map or the window is a place outside the ring, where nothing is read and
             // zeros come back.  The next K-steps are on their way while one is multiplied; what bounds it is the L2, which every
             // workgroup asks for all weights of its channels: without any contraction a launch of 37 audio streams with 16 pushes each
-            // takes 5.5 us, without its matrix instructions 16.5, in all 17.6; single tiles 22.6)
+            // takes 5.5 us under the profiler, without its matrix instructions 16.5, in all 17.6; single tiles 22.6)
             const int k_w = flat ? 1 : a.k_w, row_cells = flat ? cells : a.w_in * cells, win_cells = k_w * cells;
             const unsigned win_rcp = a.win_rcp, one = win_cells == 1;
             const uint32_t ring_bytes = (uint32_t)(ring_rows * row_cells) * 16;
@@ -417,6 +417,10 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
             hv[i] = co0 + i < c_out ? T::activate(c[i], act, shr, clamp_hi) : (st_t)0;
         }
     }
+    // steps one after the other: this one's rows are there before the wave goes on.  (Its counters need not be.)
+    auto settle = [&]() IDF_INLINE {
+        if constexpr (CHAIN) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
     int slot = dst_slot0 + o;
     slot = slot >= dst_rows ? slot - dst_rows : slot;
     const int at = flat ? slot : slot * w_out + x;
@@ -431,6 +435,7 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
                     if (co0 + i < c_out) d[i] = hv[i];
             }
         }
+        settle();
         return;
     }
     uint32_t e[EB], nz = 0;
@@ -443,7 +448,10 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
 #pragma unroll
         for (int i = 0; i < EB; ++i) nz += (uint32_t)T::nonzero(e[i]);
     }
-    if (!stats || next_layer < 0) return;
+    if (!stats || next_layer < 0) {
+        settle();
+        return;
+    }
     // events of the next layer (at most 256: the low 12 bits) and the taps they reach, per stream: over the four groups of channels,
     // then over the stream's positions.  Two lanes add them, with one instruction.
     uint32_t sum = nz | nz * (uint32_t)(taps_axis(y0 + o, nk_h, ns_h_log, np_h, nh_out) * (flat ? 1 : taps_axis(x, a.nk_w, a.ns_w_log, a.np_w, a.nw_out))) << 12;
@@ -452,6 +460,7 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
     if (per_log > 1) sum += (uint32_t)__builtin_amdgcn_mov_dpp((int)sum, 0x4E, 0xf, 0xf, true);        // lane ^ 2
     if (per_log > 2) sum += (uint32_t)__builtin_amdgcn_mov_dpp((int)sum, 0x141, 0xf, 0xf, true);       // the other four of eight (mirrored)
     if (per_log > 3) sum += (uint32_t)__builtin_amdgcn_mov_dpp((int)sum, 0x140, 0xf, 0xf, true);       // the other eight of sixteen
+    settle();
     if (g < 2 && pl == 0 && sum)
         atomicAdd(stats + ((int64_t)stream * n_layers + next_layer) * 2 + g, g == 0 ? (unsigned long long)(sum & 0xfffu) : (unsigned long long)(sum >> 12) * (unsigned)next_c_out);
 }
@@ -519,8 +528,10 @@ __global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherB
         Step &a = b.st[k];
         if (a.take == 1) {
             take_rows<T>(b.head, a, sel, si, threadIdx.x, 256 * kTeam);
+            __syncthreads();                       // what this step stored is there for the next
         } else if (a.take == 2) {
             pool_rows<T>(b.head, a, sel, si, 0, INT32_MAX, 256 * kTeam);
+            __syncthreads();
         } else {
             const int tasks = a.n_ct * ((a.n_rows * a.w_out + 15) >> 4);
             for (int t0 = 0; t0 < tasks; t0 += 4) {
@@ -528,10 +539,9 @@ __global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherB
                 asm volatile("" : "+s"(step));     // (a tile's arguments are read anew: kept over the loop they do not fit the registers)
                 const int t = t0 + team, pt = a.ct_rcp ? (int)__umulhi((unsigned)t, a.ct_rcp) : t, ct = t - pt * a.n_ct;
                 conv_tile<T, COUNT, true, 1>(b.head, *step, sel, si, pt, ct, 0, t < tasks, kq, share[team], [] { lds_barrier(); });
-                lds_barrier();                     // the sums have been read
+                lds_barrier();                     // the sums have been read, and every wave's rows are there for the next step
             }
         }
-        __syncthreads();                           // what this step stored is there for the next
     }
 }
 
