@@ -42,6 +42,12 @@ namespace {
 typedef const __attribute__((address_space(4))) RowStep ArgStep;
 
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
+// Streams from which on a launch's waves add to the counters by themselves; with fewer the waves of a workgroup add up first, which
+// takes a trip to LDS.  Additions to one place in memory go one after the other, and of few streams many waves add to the same place
+// (us per image of the bfloat16 net, by wave : by workgroup: 4 streams, 8 rows per push 484 : 333, 8 streams 1385 : 1233, 16 streams
+// 1455 : 1344, 24 streams 868 : 845 and, 8 rows per push, 556 : 559, 64 streams 2480 : 2510).
+// (Kernels of their own: the branch alone, not taken, cost 256 small images 244 -> 248 us.)
+constexpr int kTallyStreams = 24;
 
 // ---- rows of the caller: into the ring, and counted as the first layer's events --------------------
 template <class T> __device__ __forceinline__ void take_row(ArgStep &a, const StreamSel &sel, const int tile, const int si)
@@ -90,7 +96,7 @@ constexpr size_t event_lds_bytes(int rows, int xt, int nc, int c_in) { return (s
 
 // MC tiles of 16 channels x NP tiles of 16 positions x NR output rows per wave.  TAIL: windows may end within a K-step,
 // in a float net: the weights behind are zero, but zero times infinity is not, so that what is read there has to be zero too.
-template <class T, int MC, int NP, int NR, bool EV, bool TAIL>
+template <class T, int MC, int NP, int NR, bool EV, bool TAIL, bool TALLY>
 __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, const int tile, const int si)
 {
     using acc_t = typename T::acc_t; using st_t = typename T::st_t; using ev_t = typename T::ev_t;
@@ -100,6 +106,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     constexpr bool kFloat = std::is_same<st_t, float>::value;
     constexpr int kLoads = NP == 2 ? 18 : 9;       // cells each lane has in flight: a row of 32 positions (16) and halo x 32 cells at once
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ unsigned long long tally;           // what the waves have counted, and how many of them have
     __shared__ unsigned long long occ[kWaves];     // per input row, bit c: cell c holds an event somewhere in the stretch
 
     // Everything the loads need to know, asked for in one batch, and what the host can work out it has.  Left to first use the
@@ -286,6 +293,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     unsigned long long *stats = a.stats, *issued = a.issued;
     asm volatile("" ::"s"(act), "s"(shr), "s"(clamp_hi), "s"(pool), "s"(pool_from), "s"(pool_emit), "s"(to_output), "s"(dst_slot0), "s"(dst_rows), "s"(layer),
                  "s"(pool_layer), "s"(next_layer), "s"(next_c_out), "s"(n_layers), "s"(dst_stride), "s"(dst), "s"(stats), "s"(issued));
+    if (TALLY && tid == 0) tally = 0;
     lds_barrier();
     uint32_t n_mfma = 0, n_done = 0;               // tiles of 16 x 16 x one K-step issued; K-steps issued
 
@@ -633,8 +641,21 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         // (three lanes, one instruction: events of the next layer, the multiply-adds they stand for, events of the pool)
         next = wave_sum(next);
         pooled = wave_sum(pooled);
-        const uint64_t add = (id & 63) == 0 ? next & 0xffffu : (id & 63) == 1 ? (uint64_t)(next >> 16) * (uint32_t)next_c_out : pooled;
-        if ((id & 63) < 3 && add)
+        uint32_t events = next & 0xffffu, taps = next >> 16;
+        bool last = true;
+        if constexpr (TALLY) {                     // the last of the workgroup's waves adds for all
+            const int n_wc = min(1 << wc_log, (n_ct - (cg << wc_log) * MC + MC - 1) / MC), n_wp = min(kWaves >> wc_log, (W - x0 + 16 * NP - 1) / (16 * NP));
+            const uint64_t mine = (uint64_t)events | (uint64_t)taps << 14 | (uint64_t)pooled << 31 | 1ull << 45;     // (at most 8,192 events, nine taps each)
+            uint64_t before = 0;
+            if ((id & 63) == 0)
+                asm volatile("ds_add_rtn_u64 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)"
+                             : "=v"(before) : "v"((uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned long long *)&tally), "v"(mine) : "memory");
+            const uint64_t all = mine + ((uint64_t)(uint32_t)uni((int)(before >> 32)) << 32 | (uint32_t)uni((int)before));
+            last = (int)(all >> 45) == n_wc * n_wp;
+            events = (uint32_t)all & 0x3fffu; taps = (uint32_t)(all >> 14) & 0x1ffffu; pooled = (uint32_t)(all >> 31) & 0x3fffu;
+        }
+        const uint64_t add = (id & 63) == 0 ? events : (id & 63) == 1 ? (uint64_t)taps * (uint32_t)next_c_out : pooled;
+        if (last && (id & 63) < 3 && add)
             atomicAdd(stats + ((int64_t)stream * n_layers + ((id & 63) == 2 ? pool_layer : next_layer)) * 2 + ((id & 63) == 1), (unsigned long long)add);
     }
     // what the matrix instructions of this wave multiplied, zeros inside a live K-step included
@@ -650,7 +671,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 // steps with the deepest (longest) first.  Consecutive workgroups go to the eight XCDs in turn: with a
 // multiple of eight streams a stream always meets the same XCD, so its rows stay in one L2 from the layer
 // that emits them to the layer that reads them.
-template <class T, bool EV, bool WIDE, bool TAIL>
+template <class T, bool EV, bool WIDE, bool TAIL, bool TALLY>
 __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatch b, const StreamSel sel)
 {
     (void)b;                                      // the first argument: it begins the segment
@@ -665,9 +686,9 @@ __global__ void __launch_bounds__(kThreads, 3) k_conv3x3_mfma_rows(const RowBatc
     if (tile >= tiles) return;
     switch (form) {
     case kRowTake: take_row<T>(a, sel, tile, si); break;
-    case kRowSmall1: conv_rows<T, 1, 1, 1, EV, TAIL>(a, sel, tile, si); break;
-    case kRowSmall2: conv_rows<T, 1, 1, 2, EV, TAIL>(a, sel, tile, si); break;
-    case kRowWide2: if constexpr (WIDE) conv_rows<T, 2, 2, 2, false, TAIL>(a, sel, tile, si); break;
+    case kRowSmall1: conv_rows<T, 1, 1, 1, EV, TAIL, TALLY>(a, sel, tile, si); break;
+    case kRowSmall2: conv_rows<T, 1, 1, 2, EV, TAIL, TALLY>(a, sel, tile, si); break;
+    case kRowWide2: if constexpr (WIDE) conv_rows<T, 2, 2, 2, false, TAIL, TALLY>(a, sel, tile, si); break;
     default: break;
     }
 }
@@ -708,14 +729,18 @@ template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const Str
     };
     constexpr bool kF32 = std::is_same<T, TraitsF32>::value;
     if (wide && (kF32 || events)) return hipErrorInvalidValue;
-    if constexpr (T::kEvents) {
-        if (events) return go(k_conv3x3_mfma_rows<T, true, false, false>);
-    } else if (tail) {
-        // (a kernel of its own: where the kernel below had a few instructions for it -- a branch, a comparison per K-step, or
-        // unused loops beside the others -- nets without such layers took 1 to 2 % longer, float32 283 -> 288 us per image)
-        return wide ? go(k_conv3x3_mfma_rows<T, false, !kF32, true>) : go(k_conv3x3_mfma_rows<T, false, false, true>);
-    }
-    return wide ? go(k_conv3x3_mfma_rows<T, false, !kF32, false>) : go(k_conv3x3_mfma_rows<T, false, false, false>);
+    auto pick = [&](auto tally_tag) {
+        constexpr bool TALLY = decltype(tally_tag)::value;
+        if constexpr (T::kEvents) {
+            if (events) return go(k_conv3x3_mfma_rows<T, true, false, false, TALLY>);
+        } else if (tail) {
+            // (a kernel of its own: where the kernel below had a few instructions for it -- a branch, a comparison per K-step, or
+            // unused loops beside the others -- nets without such layers took 1 to 2 % longer, float32 283 -> 288 us per image)
+            return wide ? go(k_conv3x3_mfma_rows<T, false, !kF32, true, TALLY>) : go(k_conv3x3_mfma_rows<T, false, false, true, TALLY>);
+        }
+        return wide ? go(k_conv3x3_mfma_rows<T, false, !kF32, false, TALLY>) : go(k_conv3x3_mfma_rows<T, false, false, false, TALLY>);
+    };
+    return sel.n < kTallyStreams ? pick(std::true_type{}) : pick(std::false_type{});
 }
 
 }  // namespace
