@@ -561,8 +561,9 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         for (int q = 0; q < MC; ++q)
             *at4(reinterpret_cast<acc_t *>(d), (uint32_t)((x * C_out + co1 + q * 4) * 4)) = acc_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
     };
+    const FloatBounds bounds(act == IDF_ACT_NONE);
     auto activated = [&](st_t c) IDF_INLINE {
-        if constexpr (kFloat) return at_least(c, act == IDF_ACT_NONE ? __builtin_nanf("") : 0.f);
+        if constexpr (kFloat) return bounds(c);
         else return T::activate(c, act, shr, clamp_hi);
     };
     auto count = [&](const uint32_t (&e)[MC * EB]) IDF_INLINE {

@@ -191,14 +191,10 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, int wo
     const int act_none = STEP(act_none), act_lo = STEP(act_lo), act_shr = STEP(act_shr);
     int act_hi = STEP(act_hi);
     asm("" : "+v"(act_hi));                        // (an instruction takes one scalar)
+    const FloatBounds bounds(act_none);
     auto act = [&](st_t v) IDF_INLINE {
-        if constexpr (kInt) {                      // (the bounds are in order: one instruction)
-            int32_t r;
-            asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"((int32_t)v >> act_shr), "s"(act_lo), "v"(act_hi));
-            return (st_t)r;
-        } else {
-            return at_least(v, act_none ? __builtin_nanf("") : 0.f);
-        }
+        if constexpr (kInt) return (st_t)between((int32_t)v >> act_shr, act_lo, act_hi);
+        else return bounds(v);
     };
     uint32_t ev = 0, ev_pool = 0;                  // (int8: of this lane; float32: of the wave)
     // the band is there, and nobody reads what this layer overwrites any more; what is passed on has zeros in front of each row, and

@@ -18,15 +18,20 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(2))) int i32x2;
 
-// The larger of c and a bound all lanes share, which stands aside where it is NaN: an activation or none in one instruction (by
-// fmaxf and a choice it is three, one of them for signalling NaNs).  us per image, vgg-style net 2563 -> 2527, float32 net under
-// eager emission 1131 -> 1108; not in the gathering kernel, whose tiles end in few of them (64 audio streams 5556 -> 5636).
-__device__ __forceinline__ float at_least(float c, float lo)
-{
-    float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "s"(lo), "v"(c));
-    return r;
-}
+// An activation or none in one instruction: the median of a sum and two bounds -- zero and infinity, or NaN both, which stand aside; a
+// NaN sum stays NaN without an activation and is zero with one.  By fmaxf and a choice it is three instructions, one of them for
+// signalling NaNs (us per image, vgg-style net 2563 -> 2527, float32 net under eager emission 1131 -> 1108; not in the gathering
+// kernel, whose tiles end in few of them: 64 audio streams 5556 -> 5636).  An instruction that the compiler knows, and not inline
+// assembly, which took the same time (2420 : 2423, 1027 : 1022): it reads what matrix instructions have written, and the compiler keeps
+// the distance that such a read needs for its own instructions only.  The upper bound is in a vector register, since an instruction
+// takes one scalar, and hidden, since of bounds that it knows the compiler makes the three instructions again.
+struct FloatBounds {
+    float lo, hi;
+    __device__ __forceinline__ explicit FloatBounds(bool none) : lo(none ? __builtin_nanf("") : 0.f), hi(none ? __builtin_nanf("") : __builtin_inff()) { asm("" : "+v"(hi)); }
+    __device__ __forceinline__ float operator()(float c) const { return __builtin_amdgcn_fmed3f(c, lo, hi); }
+};
+// v between two bounds that are in order: the form of the median that the compiler knows as one instruction.
+__device__ __forceinline__ int32_t between(int32_t v, int32_t lo, int32_t hi) { return max(min(v, lo), min(max(v, lo), hi)); }
 // Per event type: VL elements per 16-byte cell, EB bytes per element, kInst matrix instructions of
 // 16 x 16 per K-step of four cells, pack4: four activated sums as EB words of events.
 struct TraitsBf16 {

@@ -1,0 +1,18 @@
+"""What the kernels' sources must not hold, because nothing at run time would show it reliably."""
+import glob
+import os
+import re
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1804_10727_amd", "csrc")
+
+
+@pytest.mark.parametrize("path", sorted(glob.glob(os.path.join(CSRC, "*.h*"))), ids=os.path.basename)
+def test_no_vector_instruction_in_inline_assembly(path):
+    """The compiler keeps the distance that a read of a matrix instruction's result, a lane exchange or a scalar written by a
+    vector instruction needs for its own instructions only.  Memory instructions and waits hold no such operands."""
+    text = re.sub(r"//[^\n]*", "", open(path).read())
+    for m in re.finditer(r"\basm\b(?:\s+volatile)?\s*\(", text):
+        template = re.match(r'\s*((?:"(?:[^"\\]|\\.)*"\s*)*)', text[m.end():]).group(1)
+        assert not re.search(r'(?:"|\\n|\\t|\s|;)v_[a-z0-9_]+', template), f"{os.path.basename(path)}: {template.strip()}"
