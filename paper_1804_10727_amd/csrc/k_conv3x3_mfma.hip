@@ -42,12 +42,20 @@ namespace {
 typedef const __attribute__((address_space(4))) RowStep ArgStep;
 
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
-// Streams from which on a launch's waves add to the counters by themselves; with fewer the waves of a workgroup add up first, which
-// takes a trip to LDS.  Additions to one place in memory go one after the other, and of few streams many waves add to the same place
-// (us per image of the bfloat16 net, by wave : by workgroup: 4 streams, 8 rows per push 484 : 333, 8 streams 1385 : 1233, 16 streams
-// 1455 : 1344, 24 streams 868 : 845 and, 8 rows per push, 556 : 559, 64 streams 2480 : 2510).
+// Where the waves of a workgroup add up their counters in LDS before one of them adds for all, and where each adds by itself.
+// Additions to one place in memory go one after the other, and all waves of a step add to the same place per stream: what counts is how
+// many workgroups a step has per stream -- with few there is little to wait for, and the trip to LDS costs more -- and whether other
+// work covers the wait: with many streams, and earlier where tiles are wide and their waves four times as long, or events are few.
+// us per image of 64 rows (int8: 112), by wave : by workgroup; in brackets the largest step's workgroups per stream.
+//   bfloat16, 64 to 256 channels: 4 streams (14) 366 : 343 and, 8 rows per push (56), 157 : 107; (6) 355 : 348, (4) 342 : 333;
+//     16 streams (14) 432 : 399, (6) 371 : 358, (4) 353 : 359; 24 streams (14) 485 : 476, 40 streams 511 : 510, 48 streams 564 : 570;
+//     wide tiles (14 and 28) 16 streams 200 : 196, 20 streams 235 : 234, 24 streams 241 : 243, 64 streams 498 : 501
+//   float32, 32 and 64 channels: (7) 8 streams 411 : 398, 32 streams 494 : 478, 48 streams 632 : 641; (2) 8 streams 384 : 392
+//   int8, every other value an event, 64 and 128 channels: (14) 4 streams 547 : 543 and, two rows per push, 348 : 288; 16 streams 606 : 524;
+//     32 to 128 channels, 8 rows per push (28), 24 streams 189 : 181; sparse events, 16 to 64 channels: (4) 16 streams 454 : 468;
+//     8 rows per push (16), 3 streams 99 : 98, 24 streams 128 : 130
 // (Kernels of their own: the branch alone, not taken, cost 256 small images 244 -> 248 us.)
-constexpr int kTallyStreams = 24;
+constexpr int kTallyTiles = 5, kTallyStreams = 40, kTallyStreamsInt8 = 24, kTallyStreamsWide = 22;
 
 // ---- rows of the caller: into the ring, and counted as the first layer's events --------------------
 template <class T> __device__ __forceinline__ void take_row(ArgStep &a, const StreamSel &sel, const int tile, const int si)
@@ -707,11 +715,12 @@ size_t step_lds(const RowStep &a)
 template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc)
 {
     size_t lds = 0;
-    int tiles = 0;
+    int tiles = 0, counting = 0;                   // workgroups per stream: of the largest step, and of the largest whose waves count
     bool events = false, wide = false, tail = false;
     for (int k = 0; k < b.n; ++k) {
         const RowStep &a = b.st[k];
         tiles = std::max(tiles, a.tiles);
+        if (a.form != kRowTake && (a.pool || a.next_layer >= 0)) counting = std::max(counting, a.tiles);
         wide = wide || a.form == kRowWide2;
         tail = tail || (prec != IDF_PREC_I8 && a.form != kRowTake && (a.cells & 3));
         size_t need = step_lds(a);
@@ -741,7 +750,8 @@ template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const Str
         }
         return wide ? go(k_conv3x3_mfma_rows<T, false, !kF32, false, TALLY>) : go(k_conv3x3_mfma_rows<T, false, false, false, TALLY>);
     };
-    return sel.n < kTallyStreams ? pick(std::true_type{}) : pick(std::false_type{});
+    const bool by_group = counting >= kTallyTiles && sel.n < (wide ? kTallyStreamsWide : T::kEvents ? kTallyStreamsInt8 : kTallyStreams);
+    return by_group ? pick(std::true_type{}) : pick(std::false_type{});
 }
 
 }  // namespace
