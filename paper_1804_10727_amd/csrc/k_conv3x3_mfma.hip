@@ -120,7 +120,9 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
     // Everything the loads need to know, asked for in one batch, and what the host can work out it has.  Left to first use the
     // arguments were a dozen scalar loads one after the other: from the arguments' arrival to the first request for a row 2,100 cycles,
     // now 1,000.  With weights asked for before the rows and the counters in one instruction (us per image, vgg-style net,
-    // 64 streams / four out of step / 8 rows per push / f32 net: 2826 / 7030 / 663 / 285 before, 2576 / 5548 / 593 / 257 after).
+    // 64 streams / four out of step / 24 with 8 rows per push / f32 net: 2826 / 7030 / 663 / 285 before, 2576 / 5548 / 593 / 257 after).
+    // What each is worth in the code as it stands, by taking it out: the batch nothing, now that little follows from the arguments
+    // (2411 / 4587 / 539 / 250 -> 2427 / 4558 / 542 / 250), weights first 2466 / 4668 / 541 / 254, one instruction 2453 / 4666 / 567 / 252.
     const int n_rows = a.n_rows, y0 = a.y0, n_cg = a.n_cg, n_xt = a.n_xt, W = a.w, H = a.h, C_in = a.c_in, cells = a.cells, wc_log = a.wc_log;
     const int y_new = a.y_new, slot0 = a.slot0, ring_rows = a.ring_rows, nb = a.nb, n_ct = a.n_ct, co_g = a.co_g, n_ksteps = a.n_ksteps;
     const int C_out = a.c_out, stride = a.stride, row_pitch = a.row_pitch;     // (the last two: bytes in LDS from one position, and one row, to the next)

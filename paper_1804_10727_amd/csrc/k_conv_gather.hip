@@ -7,7 +7,7 @@
 // were complete before it, and one that puts the caller's new rows into the first ring.
 //
 // Max-pools, in nets that have them, are steps of the same launch.  Measured per image of 112 x 112, 32 streams, float32,
-// six layers (5x5 and 3x3 with stride 2, 3x3, 1x1, a pool): 545 us, 4.9 per row; a launch per layer, the layers that are not
+// six layers (5x5 and 3x3 with stride 2, 3x3, 1x1, a pool): 532 to 576 us, 4.9 per row; a launch per layer, the layers that are not
 // 3x3 with stride 1 on the vector units: 4360, 39 per row.
 //
 // The work is a matrix product: the columns of the instruction are output positions -- of one stream, or, where
@@ -150,8 +150,10 @@ template <class T> __device__ __forceinline__ void pool_rows(Head &h, Step &a, c
 // ---- one tile: 16 positions x 16 channels, by a team of four waves ---------------------------------------
 // What a launch of few tiles spends its time on is what stands around the contraction: a wave's arguments in one batch (and asked for
 // in one statement: request_arguments), cells found with an addition and two minima where they lie in one stretch, counters
-// added over lanes without LDS, in one instruction (us: 64 audio streams 5788 -> 5455 per 16,000 samples, one live stream 32.3 -> 29.2
-// per segment, 37 streams with 16 pushes per launch 738 -> 710, one sensor 18,430 -> 16,250, 32 images through six layers 556 -> 550).
+// added over lanes without LDS, in one instruction (us: 64 audio streams 5898 -> 5548 per 16,000 samples, one live stream 32.2 -> 29.2
+// per segment, 37 streams with 16 pushes per launch 741 -> 713, 32 images through six layers 565 -> 532; one sensor, whose pushes wait
+// for the host, the same).  Taken out again one by one: counters by exchanges through LDS 5643 -> 5832 and 29.5 -> 30.3; a statement per
+// requested line 5683 and 29.6, no batch 5589 and 29.6, which is nothing: what is left is the way to the cells.
 // TW 2: two such tiles of channels x two of positions.  Their sums are those of single tiles, formed in the same order; each weight
 // and each cell that is fetched serves two tiles, and each wave brings one of the four to its end.
 // share: LDS for the waves' sums (three, or four per tile); barrier: where the team's waves meet.

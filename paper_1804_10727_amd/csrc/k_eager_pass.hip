@@ -23,7 +23,7 @@
 // and counted by the word, and rows that nothing reaches left out.
 // Measured per image of 112 x 112, int8, eight streams, 112 pushes: 4173 us, with fewer instructions 3860, waiting for weights and
 // states together 3727, as it is 3195; float32, 256 streams of 32 x 32, 32 pushes: 1130 -> 1034 us.  Per pushed row 28.5 us (layer by
-// layer 170) and 32 us (112), of which 18 us are matrix instructions.
+// layer 170) and 32 us (112), of which 14 us are matrix instructions (4,300 of 32 cycles, even over four SIMDs).
 #include <algorithm>
 #include <type_traits>
 
