@@ -28,6 +28,15 @@ inline hipError_t launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds
     return e;
 }
 
+// A kernel as a type, and the one call that lets its launches have so much LDS: kernels of the same arguments have pointers of one
+// type, so that a flag kept per type would be set for the first of them only.
+template <auto K> struct Kernel { static constexpr auto entry = K; };
+template <int BYTES, auto K> inline hipError_t allow_lds(Kernel<K>)
+{
+    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(K), hipFuncAttributeMaxDynamicSharedMemorySize, BYTES);
+    return e;
+}
+
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits until every global
 // store and atomic of the wave has been acknowledged (a release fence over all address spaces),
 // a memory round trip that the kernels here do not need at their internal barriers: what the

@@ -714,6 +714,8 @@ size_t step_lds(const RowStep &a)
     return (size_t)rows * a.row_pitch;
 }
 
+constexpr int kRowLds = 160 * 1024 - 256;         // of a workgroup at most, beside what the kernel declares
+
 template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const StreamSel &sel, const LaunchCtx &lc)
 {
     size_t lds = 0;
@@ -732,25 +734,24 @@ template <class T> hipError_t launch_rows(int prec, const RowBatch &b, const Str
         }
         lds = std::max(lds, need);
     }
-    if (b.n < 1 || tiles < 1 || tiles > kRowTilesMax || lds > 160 * 1024 - 256) return hipErrorInvalidValue;      // tiles are the grid's y extent
+    if (b.n < 1 || tiles < 1 || tiles > kRowTilesMax || lds > kRowLds) return hipErrorInvalidValue;      // tiles are the grid's y extent
     const dim3 grid(sel.n, tiles, b.n), block(kThreads);
     auto go = [&](auto kernel) {
-        static hipError_t prepared = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
-        if (prepared != hipSuccess) return prepared;
-        return launch(kernel, grid, block, lds, lc, b, sel);
+        const hipError_t e = allow_lds<kRowLds>(kernel);
+        return e != hipSuccess ? e : launch(kernel.entry, grid, block, lds, lc, b, sel);
     };
     constexpr bool kF32 = std::is_same<T, TraitsF32>::value;
     if (wide && (kF32 || events)) return hipErrorInvalidValue;
     auto pick = [&](auto tally_tag) {
         constexpr bool TALLY = decltype(tally_tag)::value;
         if constexpr (T::kEvents) {
-            if (events) return go(k_conv3x3_mfma_rows<T, true, false, false, TALLY>);
+            if (events) return go(Kernel<k_conv3x3_mfma_rows<T, true, false, false, TALLY>>{});
         } else if (tail) {
             // (a kernel of its own: where the kernel below had a few instructions for it -- a branch, a comparison per K-step, or
             // unused loops beside the others -- nets without such layers took 1 to 2 % longer, float32 283 -> 288 us per image)
-            return wide ? go(k_conv3x3_mfma_rows<T, false, !kF32, true, TALLY>) : go(k_conv3x3_mfma_rows<T, false, false, true, TALLY>);
+            return wide ? go(Kernel<k_conv3x3_mfma_rows<T, false, !kF32, true, TALLY>>{}) : go(Kernel<k_conv3x3_mfma_rows<T, false, false, true, TALLY>>{});
         }
-        return wide ? go(k_conv3x3_mfma_rows<T, false, !kF32, false, TALLY>) : go(k_conv3x3_mfma_rows<T, false, false, false, TALLY>);
+        return wide ? go(Kernel<k_conv3x3_mfma_rows<T, false, !kF32, false, TALLY>>{}) : go(Kernel<k_conv3x3_mfma_rows<T, false, false, false, TALLY>>{});
     };
     const bool by_group = counting >= kTallyTiles && sel.n < (wide ? kTallyStreamsWide : T::kEvents ? kTallyStreamsInt8 : kTallyStreams);
     return by_group ? pick(std::true_type{}) : pick(std::false_type{});

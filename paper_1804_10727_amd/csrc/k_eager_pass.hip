@@ -38,7 +38,7 @@ namespace {
 typedef const __attribute__((address_space(4))) EagerPassStep PassStep;
 typedef const __attribute__((address_space(4))) EagerPass PassArgs;
 
-constexpr int kPassWaves = 16, kPassThreads = 64 * kPassWaves;
+constexpr int kPassWaves = 16, kPassThreads = 64 * kPassWaves, kPassLds = 160 * 1024 - 512;
 
 // Zero times infinity is not zero: in a float net the first layer's positions carry as many cells of zeros as the last K-step of
 // their windows reads too far.  (Layers behind it have a multiple of 16 channels: their windows are whole K-steps.)
@@ -409,7 +409,7 @@ bool eager_pass_shape(int prec, EagerPass &a)
         }
     }
     for (int k = 0; k < a.n; ++k) lds = std::max(lds, size[k] + size[k + 1]);
-    if (lds > 160 * 1024 - 512) return false;
+    if (lds > kPassLds) return false;
     for (int k = 0; k < a.n; ++k) {                // bands lie alternately at the bottom and at the top
         a.st[k].lds_in = k & 1 ? (int)(lds - size[k]) : 0;
         a.st[k].lds_out = k & 1 ? 0 : (int)(lds - size[k + 1]);
@@ -421,11 +421,10 @@ bool eager_pass_shape(int prec, EagerPass &a)
 hipError_t launch_eager_pass(int prec, const EagerPass &a, const StreamSel &sel, const LaunchCtx &lc)
 {
     auto go = [&](auto kernel) {
-        static hipError_t prepared = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 512);
-        if (prepared != hipSuccess) return prepared;
-        return launch(kernel, dim3(sel.n), dim3(kPassThreads), (size_t)a.lds, lc, a, sel);
+        const hipError_t e = allow_lds<kPassLds>(kernel);
+        return e != hipSuccess ? e : launch(kernel.entry, dim3(sel.n), dim3(kPassThreads), (size_t)a.lds, lc, a, sel);
     };
-    return prec == IDF_PREC_I8 ? go(k_eager_pass<TraitsI8>) : go(k_eager_pass<TraitsF32>);
+    return prec == IDF_PREC_I8 ? go(Kernel<k_eager_pass<TraitsI8>>{}) : go(Kernel<k_eager_pass<TraitsF32>>{});
 }
 
 hipError_t launch_eager_announced(int prec, const Geom &g, const void *c, int c_rows, int64_t first, int n, void *out, hipStream_t st)

@@ -22,6 +22,8 @@ namespace {
 
 struct Dim3 { uint32_t x, y, z; };
 std::map<const void *, std::string> g_names;
+std::map<const void *, long> g_dynamic_lds;           // what a kernel has been allowed
+std::map<const void *, long> g_large;                  // launches with more than 64 KB of it
 std::string g_error;
 long g_launches = 0, g_fail_at = -1, g_lds_limit = 160 * 1024 - 256;
 int g_last = 0;
@@ -100,6 +102,8 @@ int launch(const void *fn, Dim3 grid, void **args, size_t lds)
     if (at == g_fail_at) return g_last = 98;           // (a launch failure)
     const std::string &name = g_names[fn];
     if (grid.x < 1 || grid.y < 1 || grid.z < 1 || grid.y > 65535 || grid.z > 65535) error("grid of " + name);
+    if (lds > 64 * 1024) ++g_large[fn];
+    if (lds > 64 * 1024 && (long)lds > g_dynamic_lds[fn]) error("LDS of " + str(lds) + " that was not asked for: " + name);
     bool found = false;
     for (auto &c : g_count) if (c.first == name) { ++c.second; found = true; }
     if (!found) g_count.push_back({name, 1});
@@ -120,9 +124,10 @@ long host_launches(const char *part)
     for (auto &c : g_count) if (!part || c.first.find(part) != std::string::npos) n += c.second;
     return n;
 }
+long host_large_kernels() { return (long)g_large.size(); }
 const char *host_error() { return g_error.c_str(); }
 void host_fail_in(long n) { g_fail_at = n < 0 ? -1 : g_launches + n; }
-void host_begin() { g_rows.clear(); g_next.clear(); g_error.clear(); g_count.clear(); g_fail_at = -1; }
+void host_begin() { g_rows.clear(); g_next.clear(); g_error.clear(); g_count.clear(); g_large.clear(); g_fail_at = -1; }
 
 // ---- the runtime ----
 void **__hipRegisterFatBinary(const void *) { static void *handle[1]; return handle; }
@@ -139,7 +144,11 @@ int hipLaunchKernel(const void *fn, Dim3 grid, Dim3, void **args, size_t lds, vo
 int hipExtLaunchKernel(const void *fn, Dim3 grid, Dim3, void **args, size_t lds, void *, void *, void *, int) { return launch(fn, grid, args, lds); }
 int hipGetLastError() { const int e = g_last; g_last = 0; return e; }
 const char *hipGetErrorString(int e) { return e == 98 ? "a launch failure" : "an error"; }
-int hipFuncSetAttribute(const void *, int, int) { return 0; }
+int hipFuncSetAttribute(const void *fn, int attribute, int value)
+{
+    if (attribute == 8) g_dynamic_lds[fn] = value;     // hipFuncAttributeMaxDynamicSharedMemorySize
+    return 0;
+}
 int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
 int hipGetSymbolAddress(void **p, const void *) { *p = (void *)(uintptr_t)0x200000000ull; return 0; }

@@ -269,3 +269,34 @@ def depth_first(rt):
 
 def test_streams_keep_the_mode_they_were_opened_in(runtime):
     host_runtime.run(runtime, "test_host_schedule", "depth_first")
+
+
+# ---- dynamic LDS beyond 64 KB ------------------------------------------------------------------------------------------
+def large_lds(rt, kind, precs, kernels):
+    """One process launches the variants of a kernel one after the other: each has asked for its LDS itself."""
+    import ctypes as C
+    rt.host_begin()
+    for prec in precs:
+        if kind == "eager":
+            cases = [(64, 2, w, [16, 64, 64]) for w in (62, 130, 200)]
+        else:                                      # (whole K-steps and not; of few streams and of many; narrow tiles and wide ones)
+            c = {"f32": 132, "bf16": 248, "i8": 512}[prec]
+            cases = [(streams, seg, 400, channels) for channels in ([c, 16, 16], [256, 64, 64]) for streams in (2, 64) for seg in (1, 8)]
+        for streams, seg, w, channels in cases:
+            net = chain(prec, 16, w, channels)
+            st = host_runtime.Streams(net, streams, seg)
+            if kind == "eager":
+                nb = C.c_size_t()
+                st.check(st.L.idf_query_eager_bytes(net._h, streams, seg, C.byref(nb)))
+                st.check(st.L.idf_enable_eager(st.h, C.c_void_p(1 << 42), nb))
+            for r in range(0, 16, seg):
+                st.push(min(seg, 16 - r))
+            st.close()
+            net.destroy()
+    assert rt.host_error() == b"", rt.host_error()
+    assert rt.host_large_kernels() >= kernels, rt.host_large_kernels()
+
+
+@pytest.mark.parametrize("kind,precs,kernels", [("rows", ("f32",), 2), ("rows", ("bf16",), 3), ("rows", ("i8",), 2), ("eager", ("f32", "i8"), 2)])
+def test_every_kernel_asks_for_its_lds(runtime, kind, precs, kernels):
+    host_runtime.run(runtime, "test_host_schedule", "large_lds", kind, precs, kernels)
