@@ -582,7 +582,12 @@ int streams_per_tile_log(int positions, bool first)
 // two by two: audio net, 16 pushes per launch, 12 streams (1,536 tiles) 183 us against 184, 16 streams 213 : 191, 37 streams 374 : 299,
 // 64 streams 546 : 406, but 8 streams 151 : 170; six-layer net, 4 rows per push, 64 images of 79 x 79 (some 1,500 tiles) float32
 // 188 : 182, bfloat16 162 : 141, 15 images of 160 x 160 (700) 296 : 334 and 255 : 256.
-constexpr int kWideTiles = 1536;
+// And where a sixteenth of them and more can: those of steps of 16 channels or few positions stay single, in a kernel that holds more LDS
+// and a longer block of arguments.  Likewise, by the share that can: none, three 8-channel layers, 64 streams with 16 pushes per launch
+// 315 : 325, four layers over images 79 wide, 4 rows per push, 128 images 292 : 298, bfloat16 260 : 264; 8 %, 64 and 128 images 240 : 237,
+// 399 : 396 and 209 : 212, 335 : 327; 13 %, 184 : 185, 273 : 268 and 171 : 173, 243 : 238; a quarter, 50 images (400 of 1,650 tiles)
+// 190 : 190 and 171 : 155.
+constexpr int kWideTiles = 1536, kWideShare = 16;
 bool wide_step(const GatherStep &a) { return a.take == 0 && a.n_ct >= 2 && a.n_pt >= 2 && a.spt_log == 0; }
 
 template <class T, int NS, bool WIDE> hipError_t launch_ns(const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc)
@@ -623,9 +628,14 @@ template <class T, int NS, bool WIDE> hipError_t launch_ns(const GatherHead &h, 
 template <class T> hipError_t launch_t(const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc)
 {
     // tiles of two by two where there are so many that the chip is full with a quarter of them
-    int64_t tiles = 0;
-    for (int k = 0; k < h.n; ++k) if (st[k].take == 0) tiles += (int64_t)((sel.n + (1 << st[k].spt_log) - 1) >> st[k].spt_log) * st[k].n_ct * st[k].n_pt;
-    if (!chain && !h.issued && tiles >= kWideTiles) return launch_ns<T, kGatherMax, true>(h, st, sel, false, lc);
+    int64_t tiles = 0, paired = 0;
+    for (int k = 0; k < h.n; ++k) {
+        if (st[k].take != 0) continue;
+        const int64_t n = (int64_t)((sel.n + (1 << st[k].spt_log) - 1) >> st[k].spt_log) * st[k].n_ct * st[k].n_pt;
+        tiles += n;
+        if (wide_step(st[k])) paired += n;
+    }
+    if (!chain && !h.issued && tiles >= kWideTiles && paired * kWideShare >= tiles) return launch_ns<T, kGatherMax, true>(h, st, sel, false, lc);
     // (the short block for the usual few steps: a third of the bytes to hand over)
     return h.n <= 4 ? launch_ns<T, 4, false>(h, st, sel, chain, lc) : launch_ns<T, kGatherMax, false>(h, st, sel, chain, lc);
 }

@@ -300,3 +300,39 @@ def large_lds(rt, kind, precs, kernels):
 @pytest.mark.parametrize("kind,precs,kernels", [("rows", ("f32",), 2), ("rows", ("bf16",), 3), ("rows", ("i8",), 2), ("eager", ("f32", "i8"), 2)])
 def test_every_kernel_asks_for_its_lds(runtime, kind, precs, kernels):
     host_runtime.run(runtime, "test_host_schedule", "large_lds", kind, precs, kernels)
+
+
+# ---- tiles of the gathering kernel ----------------------------------------------------------------------------------------
+def wide_tiles(rt, channels, streams, wide, strides=()):
+    """Held-back pushes of 256 rows in all: single tiles or two by two."""
+    import paper_1804_10727_amd as idf
+    from workloads import conv
+    layers = [conv(a, b, 9, 1, s=2 if i in strides else 1) for i, (a, b) in enumerate(zip(channels, channels[1:]))]
+    net = idf.Net("f32", 4096, 1, 1, layers, [np.ones((L["c_out"], L["c_in"], 9, 1), np.float32) for L in layers])
+    st = host_runtime.Streams(net, streams, 16)
+    st.check(st.L.idf_set_push_batching(st.h, 16))
+    rt.host_begin()
+    for _ in range(256):
+        st.push(16)
+    assert rt.host_launches(b"k_conv_gather_rows") == 16
+    assert (rt.host_launches(b"k_conv_gather_rowsINS0_9TraitsF32ELi9ELb0ELb1EE") > 0) == wide
+    st.close()
+
+
+@pytest.mark.parametrize("channels,streams,wide", [
+    ((1, 8, 8, 8), 64, False), ((1, 16, 16, 16, 16), 64, False),                       # 3,072 and 4,096 tiles, none that could go two by two
+    ((1, 16, 16, 16, 16, 32), 15, False), ((1, 16, 16, 16, 16, 32), 16, True),         # 96 tiles per stream, 32 of them could
+    ((1, 16, 16, 16, 16, 16, 16, 32), 11, False), ((1, 16, 16, 16, 16, 16, 16, 32), 12, True),     # 128 and 32
+    ((1, 32, 64, 64), 9, False), ((1, 32, 64, 64), 10, True),                          # 160, all
+])
+def test_tiles_go_two_by_two_where_many_can(runtime, channels, streams, wide):
+    host_runtime.run(runtime, "test_host_schedule", "wide_tiles", channels, streams, wide)
+
+
+@pytest.mark.parametrize("channels,strides,wide", [
+    ((1, 16, 16, 16, 16, 32, 16), (4,), True),                  # 16 of 88 tiles per stream
+    ((1, 16, 16, 16, 16, 16, 16, 32), (5, 6), True),            # 8 of 96
+    ((1, 16, 16, 16, 16, 16, 16, 32), (4, 5, 6), False),        # 4 of 80
+])
+def test_tiles_stay_single_where_few_can_go_two_by_two(runtime, channels, strides, wide):
+    host_runtime.run(runtime, "test_host_schedule", "wide_tiles", channels, 64, wide, strides)
