@@ -679,14 +679,11 @@ bool conv_gather_takes(int prec, const Geom &g, int ring_rows)
     auto shift = [](int s) { return s == 1 || s == 2 || s == 4; };
     if (!shift(g.s_h) || !shift(g.s_w) || g.k_h < g.s_h) return false;
     if (g.k_h > 32 || g.k_w > 32 || g.p_h >= g.k_h || g.p_w >= g.k_w) return false;
+    // (rows of many positions: win_rcp is exact for any window of these sizes, at most 2,048 cells to a row of it and 65,539 in all)
     GatherStep a{};
     conv_gather_layer(prec, g, a);
-    // (win_rcp is exact for any window of these sizes: at most 2048 cells to a row of it, 65,539 in all)
-    const unsigned kw_rcp = (unsigned)((65536 + g.k_w - 1) / g.k_w);
-    for (unsigned q = 0; q < (unsigned)(g.k_h * g.k_w * cells) + 4u; ++q) {
-        const unsigned tap = q * a.cells_rcp >> 16;
-        if (q > UINT32_MAX / a.cells_rcp || tap > UINT32_MAX / kw_rcp || tap != q / cells || tap * kw_rcp >> 16 != tap / g.k_w) return false;
-    }
+    for (unsigned q = 0; a.flat && q < (unsigned)(g.k_h * cells); ++q)
+        if (q * a.cells_rcp >> 16 != q / cells) return false;
     return true;
 }
 

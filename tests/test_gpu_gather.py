@@ -187,3 +187,33 @@ def test_a_static_workspace_too_small_for_the_rings_still_holds_the_streams():
     for o in outs:
         for b in (0, streams - 1):
             assert rel_err(o[b], oracle_dense(wl, b)) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("streams,seg,h,w,c0,layers", [
+    (3, 2, 12, 11, 192, [conv(192, 20, 7, 7, p_h=3, p_w=3), conv(20, 5, 1, 1)]),
+    (2, 1, 11, 3, 248, [conv(248, 17, 9, 2, p_h=1, p_w=1), conv(17, 16, 2, 2)]),       # a window of 1,116 cells
+    (17, 3, 26, 2, 250, [conv(250, 5, 23, 1, p_h=2)]),
+    (2, 4, 34, 33, 201, [conv(201, 16, 32, 32, p_h=1)]),
+    (2, 1, 60, 1, 250, [conv(250, 7, 22, 1, p_h=2)]),                                  # one position per row
+])
+def test_large_windows(streams, seg, h, w, c0, layers):
+    """float32: 200 input channels and more, windows of a thousand cells and more."""
+    import paper_1804_10727_amd as idf
+    from paper_1804_10727_amd.binding import input_tensor
+    import oracle
+    layers, weights, biases, x = _image("f32", streams, h, w, c0, layers, seed=c0)
+    x[0, :, w // 2:] = 0
+    wl = wl_mod._finish("gather2d", "f32", h, w, c0, layers, weights, biases, x, 1)
+    net = idf.net_from_workload(wl)
+    st = idf.Streams(net, streams, max_seg_rows=seg)
+    assert set(st.layer_kernels()) == {"conv_gather"}
+    xd = input_tensor(wl)
+    for r in range(0, h, seg):
+        st.push_segment(xd[:, r:r + seg].contiguous())
+    ev = [st.get_stats(b) for b in range(streams)]
+    o = st.read_outputs(int(st.sizes.out_h))[0].cpu().numpy()
+    for b in range(streams):
+        assert rel_err(o[b], oracle.dense(layers, wl["x"][b], wl["weights"], wl["biases"])) <= TOL["f32"], b
+        _, e = oracle.stream_run(layers, wl["x"][b], wl["weights"], wl["biases"], seg_rows=1)
+        assert ev[b]["events_in"].tolist() == e["events_in"].tolist() and ev[b]["macs"].tolist() == e["macs"].tolist(), b
+    st.close(); net.destroy()

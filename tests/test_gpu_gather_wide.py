@@ -70,3 +70,9 @@ def test_images_two_by_two(prec, n, h, w, c0, layers):
     x[1, :, w // 3:] = 0
     wl = wl_mod._finish("gather2d", prec, h, w, c0, layers, weights, biases, x, 1)
     _compare(wl, n, 16, emulate="bf16" if prec == "bf16" else None)
+
+
+def test_large_windows_two_by_two():
+    """float32, 1,550 cells."""
+    layers, weights, biases, x = _image("f32", 40, 16, 31, 248, [conv(248, 33, 5, 5, p_h=2, p_w=2)], seed=1)
+    _compare(wl_mod._finish("gather2d", "f32", 16, 31, 248, layers, weights, biases, x, 1), 40, 8)

@@ -336,3 +336,30 @@ def test_tiles_go_two_by_two_where_many_can(runtime, channels, streams, wide):
 ])
 def test_tiles_stay_single_where_few_can_go_two_by_two(runtime, channels, strides, wide):
     host_runtime.run(runtime, "test_host_schedule", "wide_tiles", channels, 64, wide, strides)
+
+
+# ---- windows of many cells ----------------------------------------------------------------------------------------------
+def large_windows(rt):
+    """The gathering kernel counts a window's cells in 32 bits; only where a row is one position it divides by a multiplication of 16."""
+    import paper_1804_10727_amd as idf
+    from workloads import conv
+    for w, c_in, k_h, k_w, kernel in [(32, 192, 7, 7, b"conv_gather"), (32, 248, 9, 2, b"conv_gather"), (32, 256, 32, 32, b"conv_gather"), (32, 201, 32, 31, b"conv_gather"),
+                                      (32, 257, 7, 7, b"conv_generic"), (33, 16, 33, 1, b"conv_generic"),
+                                      (2, 248, 18, 1, b"conv_gather"), (1, 248, 17, 1, b"conv_gather"), (1, 248, 18, 1, b"conv_generic")]:
+        net = idf.Net("f32", 40, w, c_in, [conv(c_in, 16, k_h, k_w)], [np.ones((16, c_in, k_h, k_w), np.float32)])
+        st = host_runtime.Streams(net, 1)
+        assert st.L.idf_layer_kernel(st.h, 0) == kernel, (w, c_in, k_h, k_w)
+        st.close()
+        net.destroy()
+
+
+def test_which_windows_the_gathering_kernel_takes(runtime):
+    host_runtime.run(runtime, "test_host_schedule", "large_windows")
+
+
+def test_division_of_a_window_into_rows_is_exact():
+    """ceil(2^32 / n) for windows of up to 32 x 32 positions of 64 cells, and the cells that the last K-step reads too far."""
+    q = np.arange(32 * 2048 + 4, dtype=np.uint64)
+    for n in sorted({k_w * cells for k_w in range(1, 33) for cells in range(1, 65)} - {1}):
+        few = q[:32 * n + 4]
+        assert np.array_equal(few * np.uint64(-(-2**32 // n)) >> np.uint64(32), few // np.uint64(n)), n
