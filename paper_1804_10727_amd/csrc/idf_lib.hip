@@ -539,8 +539,8 @@ double conv_step_bytes(const idf_net &net, const ConvStep &a, int n_streams)
     return per_stream * n_streams + weights;
 }
 
-// Quotient and remainder of counts that are nearly always small: the 64-bit instruction takes several times as long, and a push has
-// some sixty of them.
+// Quotient and remainder of counts that are nearly always small, of which a push has some sixty: by the 64-bit instruction throughout a
+// push takes 0.02 us longer (us per image, four streams out of step 4516 instead of 4498).
 inline int64_t quot(int64_t a, int64_t b) { return ((uint64_t)a | (uint64_t)b) >> 32 ? a / b : (int64_t)((uint32_t)a / (uint32_t)b); }
 inline int64_t rest_of(int64_t a, int64_t b) { return ((uint64_t)a | (uint64_t)b) >> 32 ? a % b : (int64_t)((uint32_t)a % (uint32_t)b); }
 
@@ -2052,7 +2052,8 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
     // go together only if they stand in the same sample too)
     typedef std::tuple<int64_t, int64_t, int64_t, uint32_t> Key;
     const bool by_sample = !s->units.empty() && !s->stg2d;
-    // (layers side by side: progress is kept per stream; all streams, in step and in order, need no list)
+    // (layers side by side: progress is kept per stream; all streams, in step and in order, need no list: 0.02 us of a push of one
+    // stream, 0.07 of 64, 0.14 of 256)
     const bool side_by_side = s->use_gather || s->stg2d;
     bool whole = side_by_side && s->prog_same && n_ids == s->B;
     for (int i = 0; whole && stream_ids && i < n_ids; ++i) whole = stream_ids[i] == i;
