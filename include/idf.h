@@ -330,6 +330,8 @@ int idf_rows_pushed(const idf_streams *s, int stream_id, int64_t *rows);
  *     to dev_out [n_ids][max_rows][W][C] and reports per stream the index of the first and how many
  *     (at most max_rows).  Rows before them are final and forgotten, rows after them still all zero.
  * idf_get_stats then counts, per layer, the non-zero changes delivered to it.
+ *   Segments pushed one after the other may be on their way through the layers when a push returns; every call that
+ * shows results lets them finish first, and after a whole sample nothing is on its way.
  * idf_eager_state_bytes: state c and announced values retained per stream (without the output map);
  * rows_kept (host, n_layers + 1 entries, may be NULL): rows kept per level. */
 int idf_query_eager_bytes(const idf_net *net, int n_streams, int max_seg_rows, size_t *bytes);

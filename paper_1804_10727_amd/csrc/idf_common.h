@@ -278,6 +278,7 @@ struct RingMove {
 
 // Eager emission of a segment through a whole net in one launch (k_eager_pass.hip): its layers in order.
 constexpr int kPassMax = 16;     // conv layers at most
+constexpr int kPassStages = 8;   // stages at most: a launch takes the newest push through the first, the one before it through the second, ..
 constexpr int kPassGroups = 4;   // groups of four rows of a layer that a band reaches at most
 struct EagerPassStep {           // a conv layer and the 2x2 pool behind it, if there is one
     // (in the order a wave needs them, and as it needs them: every instruction of a layer is issued by all sixteen waves)
@@ -319,6 +320,10 @@ struct EagerPass {
     int64_t in_stride, ann0_stride;
     void *ann0;
     unsigned long long *stats;
+    void *hand;                  // the bands from stage to stage lie at these places behind it, in units of 256 bytes
+    uint32_t hand_in[kPassStages], hand_out[kPassStages];
+    int stage0;                  // first stage of the launch; per stage its layers (none: first == end)
+    uint8_t first[kPassStages], end[kPassStages];
     EagerPassStep st[kPassMax];
 };
 static_assert(sizeof(EagerPass) + sizeof(StreamSel) <= 4096 && sizeof(GatherBatch<kGatherMax>) + sizeof(StreamSel) <= 4096, "likewise");

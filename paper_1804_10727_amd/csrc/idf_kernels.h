@@ -65,7 +65,7 @@ hipError_t launch_eager(int prec, int what, const EagerStep &a, const StreamSel 
 // A segment through a whole net of 3x3 conv layers and 2x2 pools in one launch: fills in how its bands lie (false: they
 // are too large for it), and the launch.
 bool eager_pass_shape(int prec, EagerPass &a);
-hipError_t launch_eager_pass(int prec, const EagerPass &a, const StreamSel &sel, const LaunchCtx &lc);
+hipError_t launch_eager_pass(int prec, const EagerPass &a, int stages, bool small, const StreamSel &sel, const LaunchCtx &lc);
 // Announced values of rows [first, first + n) of a conv layer from its ring of c_rows rows of state.
 hipError_t launch_eager_announced(int prec, const Geom &g, const void *c, int c_rows, int64_t first, int n, void *out, hipStream_t st);
 // Clears bytes (a multiple of 4, 4-byte aligned) with a kernel on stream st.

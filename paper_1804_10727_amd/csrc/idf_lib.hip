@@ -166,6 +166,18 @@ struct idf_streams {
         std::vector<int> rows;                    // per level: rows the level has (H)
         std::vector<int> ann_rows, cd_rows;       // per level: rows kept of the announced values / of state and deltas
         std::vector<size_t> ann_off, c_off, dlt_off;   // per level (c: conv layers only)
+        // Stages (eager_stages): pushes that follow one another go through the net in step, each a stage behind the next.
+        // Launch number `launch` takes the push that came with launch k through stage launch - k.
+        int stages = 1;
+        bool small = false;                       // workgroups of half as many waves
+        int first[kPassStages + 1] = {};          // per stage its first layer
+        size_t hand[kPassStages][2] = {};         // per stage where its band waits: of even and of odd launches
+        int64_t launch = 0;
+        bool on_way[kPassStages] = {};            // the push of launch k, at k mod stages, has not gone through all of them
+        std::vector<EagerPass> plan;              // and what each of them does
+        int since_read = 0;                       // pushes since results were last asked for
+        bool read_each = false;                   // results were asked for after a single push
+        std::vector<int64_t> lo, hi, seen_lo, seen_hi;
     } eager;
     // a pixel segment being pushed: columns [x_lo, x_hi) of the current row of layer 0 (else the whole row)
     struct Part { bool on = false; int x_lo = 0, x_hi = 0; bool first = true, last = true; } part;
@@ -1102,11 +1114,14 @@ int count_waiting_rows(idf_streams *s)
     return IDF_OK;
 }
 
+int eager_flush(idf_streams *s);
+
 // Everything still between stages or layers is enqueued: afterwards the work in the stream is
 // that of every pushed row having gone through every layer it can influence.
 int pipeline_drain(idf_streams *s)
 {
-    int rc = gather_flush(s);
+    int rc = eager_flush(s);
+    if (rc == IDF_OK) rc = gather_flush(s);
     return rc != IDF_OK ? rc : stg_drain(s);
 }
 
@@ -1381,6 +1396,7 @@ bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int
     P.ann0 = E.ws + E.ann_off[0]; P.ann0_rows = E.ann_rows[0]; P.ann0_slot = (int)(a % E.ann_rows[0]);
     P.ann0_stride = (int64_t)E.ann_rows[0] * E.row_elems[0];
     P.stats = (unsigned long long *)(s->ws + s->stats_off);
+    P.hand = E.ws;
     bytes = 0;
     for (int l = 0; l < n && hi[l] > lo[l] && hi[l + 1] > lo[l + 1];) {
         const Geom &g = net.g[l];
@@ -1439,8 +1455,9 @@ bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int
 // behind any of them; no biases (rings, every row starts from zero); differences that fit the operands -- a bfloat16
 // net's do not, and an int8 net must clamp what it passes on.  The switches that choose between the kernels for single
 // layers choose those.
-bool eager_one_launch(const idf_streams *s)
+bool eager_one_launch(const idf_streams *s, std::vector<double> &most)
 {
+    most.clear();
     const idf_net &net = *s->net;
     const bool ring = s->eager.ring;
     const int n = (int)net.g.size();
@@ -1470,10 +1487,122 @@ bool eager_one_launch(const idf_streams *s)
         // 64 positions, 108 against 73 at 128; with 64 streams the two are even there).  The quantised nets are ahead
         // at any size that fits (one stream of 224 positions: 62 us against 158).
         double macs = 0;
-        for (int k = 0; k < P.n; ++k) macs += 9.0 * P.st[k].n_in * 16 * P.st[k].n_xt * P.st[k].c_in * P.st[k].c_out;
+        most.resize(std::max<size_t>(most.size(), P.n), 0.0);
+        for (int k = 0; k < P.n; ++k) {
+            const double m = 9.0 * P.st[k].n_in * 16 * P.st[k].n_xt * P.st[k].c_in * P.st[k].c_out;
+            macs += m;
+            most[k] = std::max(most[k], m);
+        }
         if (net.precision == IDF_PREC_F32 && s->B < 64 && macs > 160e3 * 14 * n) return false;
     }
     return true;
+}
+
+// How a net goes through in stages, given the multiply-adds of each of its layers in a segment and stream.  One workgroup per stream
+// that takes a segment through all layers is a chain of some 3.5 us per layer on one compute unit; in stages the chain of a launch is
+// as long as the longest stage, and the other compute units have work.  So there are as many stages as layers, or as compute
+// units have room for a workgroup each; with more than half as many streams as compute units two stages, of workgroups of eight waves,
+// two of which share a compute unit.  A stage's band waits for the next launch in memory of the workspace that layer by layer only
+// needs: the announced values and differences of the level in front of it, each large enough for a band.
+// Measured, us per image, one stage : two : three : four (eight) of sixteen waves; two of eight waves: int8, 8 streams of 112 x 112,
+// 3195 : 2117 : 1754 : 1345 (1126); 2466.  float32, 32 x 32, 64 streams 975 : 606 : 595 : 598; 597.  100 streams 994 : 631 : 851 : 871; 629.
+// 128 streams 1003 : 641 : 856 : 879; 634.  200 streams 1024 : 1101 : 1181 : 1264; 943.  256 streams 1028 : 1125 : 1220 : 1319; 952.
+constexpr int kComputeUnits = 256;
+void eager_stages(idf_streams *s, const std::vector<double> &macs)
+{
+    const idf_net &net = *s->net;
+    idf_streams::Eager &E = s->eager;
+    const int n = (int)macs.size();
+    E.stages = 1; E.small = false;
+    if (strict_rows()) return;
+    int S = std::min({n, kPassStages, kComputeUnits / s->B});
+    if (S < 2 && n > 1 && 2 * s->B <= 2 * kComputeUnits) { S = 2; E.small = true; }
+    if (S < 2) return;
+    // the division of the layers whose longest stage is shortest
+    std::vector<double> sum(n + 1, 0);
+    for (int k = 0; k < n; ++k) sum[k + 1] = sum[k] + 3.0 + macs[k] / (net.precision == IDF_PREC_F32 ? 350e3 : 2000e3);
+    std::vector<std::vector<double>> best(S + 1, std::vector<double>(n + 1, 1e300));
+    std::vector<std::vector<int>> from(S + 1, std::vector<int>(n + 1, 0));
+    best[0][0] = 0;
+    for (int k = 1; k <= S; ++k)
+        for (int j = k; j <= n; ++j)
+            for (int i = k - 1; i < j; ++i) {
+                const double c = std::max(best[k - 1][i], sum[j] - sum[i]);
+                if (c < best[k][j]) { best[k][j] = c; from[k][j] = i; }
+            }
+    for (int k = S, j = n; k >= 0; --k) { E.first[k] = j; j = from[k][j]; }
+    std::vector<int> level;                                        // of each convolution
+    for (size_t l = 0; l < net.g.size(); ++l)
+        if (net.g[l].kind == IDF_CONV) level.push_back((int)l + 1);
+    for (int k = 1; k < S; ++k) {
+        const int lv = level[E.first[k] - 1];
+        E.hand[k][0] = E.ann_off[lv]; E.hand[k][1] = E.dlt_off[lv];
+        if (std::max(E.hand[k][0], E.hand[k][1]) / 256 > UINT32_MAX) return;
+    }
+    E.stages = S;
+    E.plan.resize(S);
+    E.launch = 0;
+    std::fill(E.on_way, E.on_way + kPassStages, false);
+}
+
+// The next launch of a net in stages: every push on its way goes through its next one, and a new push (planned at launch mod
+// stages already) through the first.
+int eager_advance(idf_streams *s, bool fresh, double bytes)
+{
+    idf_streams::Eager &E = s->eager;
+    const int S = E.stages;
+    int lo = S, hi = -1;
+    EagerPass A;
+    A.lds = 0;
+    for (int k = 0; k < S && k <= E.launch; ++k) {
+        const int64_t came = E.launch - k;
+        if (k == 0 ? !fresh : !E.on_way[came % S]) continue;
+        const EagerPass &P = E.plan[came % S];
+        if (hi < 0) {                                              // (all but the caller's rows is the same for all pushes, and those are the first one's)
+            memcpy((void *)&A, (const void *)&P, offsetof(EagerPass, st));
+            memset(A.first, 0, sizeof(A.first)); memset(A.end, 0, sizeof(A.end));
+            A.lds = 0; A.stage0 = lo = k;
+        }
+        hi = k;
+        const int a = E.first[k], b = std::max(a, std::min(P.n, E.first[k + 1]));
+        A.first[k] = (uint8_t)a; A.end[k] = (uint8_t)b;
+        A.hand_in[k] = (uint32_t)(E.hand[k][came & 1] / 256);
+        A.hand_out[k] = k + 1 < S ? (uint32_t)(E.hand[k + 1][came & 1] / 256) : 0u;
+        A.lds = std::max(A.lds, P.lds);
+        memcpy((void *)&A.st[a], (const void *)&P.st[a], sizeof(EagerPassStep) * (size_t)(b - a));
+    }
+    if (hi >= 0) {
+        StreamSel all{};
+        all.n = s->B; all.base = 0; all.pos0 = 0;
+        hipError_t e = launch_eager_pass(s->net->precision, A, hi - lo + 1, E.small, all, launch_ctx(s, kKindEager, bytes, 0));
+        if (e != hipSuccess) return dev_fail(e, "eager launch");
+    }
+    E.on_way[E.launch % S] = fresh;
+    ++E.launch;
+    return IDF_OK;
+}
+
+// Every push on its way goes through the stages that are left.
+int eager_flush(idf_streams *s)
+{
+    idf_streams::Eager &E = s->eager;
+    if (E.stages < 2) return IDF_OK;
+    auto pending = [&]() {
+        for (int k = 1; k < E.stages && k <= E.launch; ++k)
+            if (E.on_way[(E.launch - k) % E.stages]) return true;
+        return false;
+    };
+    while (pending())
+        if (int rc = eager_advance(s, false, 0)) return rc;
+    return IDF_OK;
+}
+
+// Results are asked for.
+int eager_settle(idf_streams *s)
+{
+    idf_streams::Eager &E = s->eager;
+    if (E.since_read > 0) { E.read_each = E.since_read == 1; E.since_read = 0; }
+    return eager_flush(s);
 }
 
 // One pass of eager emission for a selection of streams: the input rows [a, b) (pushed rows, or
@@ -1484,7 +1613,7 @@ int eager_pass(idf_streams *s, const StreamSel &sel, const void *dev_rows, int n
     const int n = (int)net.g.size();
     idf_streams::Eager &E = s->eager;
     unsigned long long *stats = (unsigned long long *)(s->ws + s->stats_off);
-    std::vector<int64_t> lo, hi, seen_lo, seen_hi;
+    std::vector<int64_t> &lo = E.lo, &hi = E.hi, &seen_lo = E.seen_lo, &seen_hi = E.seen_hi;
     eager_bands(net, a, b, init_bias, lo, hi);
     eager_bands(net, 0, a, false, seen_lo, seen_hi);          // seen_hi[lv]: rows of level lv reached before this pass
     const int round_bf16 = net.precision == IDF_PREC_BF16;
@@ -1492,7 +1621,7 @@ int eager_pass(idf_streams *s, const StreamSel &sel, const void *dev_rows, int n
         EagerPass P;
         double bytes = 0;
         if (!eager_pass_plan(s, dev_rows, n_rows, a, lo, hi, seen_hi, P, bytes)) return fail(IDF_ESTATE, "internal: a segment does not fit one launch");
-        hipError_t e = launch_eager_pass(net.precision, P, sel, launch_ctx(s, kKindEager, bytes * sel.n, 0));
+        hipError_t e = launch_eager_pass(net.precision, P, 0, false, sel, launch_ctx(s, kKindEager, bytes * sel.n, 0));
         return e == hipSuccess ? (int)IDF_OK : dev_fail(e, "eager launch");
     }
     auto fresh_from = [&](int lv) { return E.ring ? (int)seen_hi[lv] : (int)E.rows[lv]; };    // whole maps are cleared when a sample begins
@@ -1537,11 +1666,27 @@ int eager_pass(idf_streams *s, const StreamSel &sel, const void *dev_rows, int n
     return IDF_OK;
 }
 
+// A push in stages: all streams, in step and in order.  Not where results have been asked for push by push (a push then goes through all
+// layers at once: the stages would be as many launches), not while launches are timed (each is then the work of one push), and not into a graph that is being recorded, which may be replayed without
+// the launches that would follow.
+bool eager_staged(const idf_streams *s, const int32_t *stream_ids, int n_ids)
+{
+    const idf_streams::Eager &E = s->eager;
+    if (E.stages < 2 || n_ids != s->B || s->prof_on || (E.read_each && E.since_read == 0)) return false;
+    for (int i = 0; i < n_ids; ++i)
+        if ((stream_ids && stream_ids[i] != i) || s->h[i].r != s->h[0].r) return false;
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s->st, &c) == hipSuccess) return c == hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 int eager_push(idf_streams *s, const int32_t *stream_ids, int n_ids, const void *dev_rows, int n_rows)
 {
     const idf_net &net = *s->net;
     const int n = (int)net.g.size();
     idf_streams::Eager &E = s->eager;
+    const bool staged = eager_staged(s, stream_ids, n_ids);
     std::map<int64_t, std::vector<std::pair<int, int>>> groups;
     for (int i = 0; i < n_ids; ++i) {
         const int id = stream_ids ? stream_ids[i] : i;
@@ -1549,7 +1694,22 @@ int eager_push(idf_streams *s, const int32_t *stream_ids, int n_ids, const void 
         if (h.r + n_rows > net.in_h)
             return fail(IDF_ESTATE, "stream %d: rows %lld..%lld run past the sample of %d rows", id, (long long)h.r,
                         (long long)(h.r + n_rows - 1), net.in_h);
-        groups[h.r].push_back({i, id});
+        if (!staged) groups[h.r].push_back({i, id});
+    }
+    const int64_t r0 = s->h[0].r;
+    if (!staged || r0 == 0)
+        if (int rc = eager_flush(s)) return rc;
+    if (staged) {
+        if (r0 == 0) {                             // a sample begins: the output, which is kept whole, is zero
+            hipError_t e = launch_fill_zero(E.ws + E.ann_off[n], (size_t)E.ann_rows[n] * E.row_elems[n] * 4 * s->B, s->st);
+            if (e != hipSuccess) return dev_fail(e, "eager reset");
+        }
+        eager_bands(net, r0, r0 + n_rows, false, E.lo, E.hi);
+        eager_bands(net, 0, r0, false, E.seen_lo, E.seen_hi);
+        double bytes = 0;
+        if (!eager_pass_plan(s, dev_rows, n_rows, r0, E.lo, E.hi, E.seen_hi, E.plan[E.launch % E.stages], bytes))
+            return fail(IDF_ESTATE, "internal: a segment does not fit one launch");
+        if (int rc = eager_advance(s, true, bytes * s->B)) return rc;
     }
     bool any_bias = false;
     for (int l = 0; l < n; ++l) any_bias |= !net.b_img[l].empty();
@@ -1596,6 +1756,9 @@ int eager_push(idf_streams *s, const int32_t *stream_ids, int n_ids, const void 
         h.eager_rows = h.r;                      // rows of the current sample the levels have seen
         if (h.r == net.in_h) h.r = 0;
     }
+    ++E.since_read;
+    // a whole sample waits for nothing (a launch that fails here is made again when results are asked for)
+    if (staged && s->h[0].r == 0) (void)eager_flush(s);
     return IDF_OK;
 }
 
@@ -2473,7 +2636,9 @@ int idf_enable_eager(idf_streams *s, void *dev_workspace, size_t workspace_bytes
         if (h.r != 0 || h.out_written != 0 || h.x_next != 0) return fail(IDF_ESTATE, "eager emission must be enabled before the first push");
     eager_layout(*s->net, s->B, s->max_seg, &s->eager);
     s->eager.ws = (char *)dev_workspace;
-    s->eager.one_launch = eager_one_launch(s);
+    std::vector<double> macs;
+    s->eager.one_launch = eager_one_launch(s, macs);
+    if (s->eager.one_launch) eager_stages(s, macs);
     s->eager.on = true;
     return IDF_OK;
 }
@@ -2506,6 +2671,8 @@ int idf_read_announced(idf_streams *s, int level, const int32_t *stream_ids, int
                     s->eager.ann_rows[level]);
     int rc = check_ids(s, stream_ids, n_ids);
     if (rc != IDF_OK) return rc;
+    rc = eager_settle(s);
+    if (rc != IDF_OK) return rc;
     const size_t bytes = (size_t)s->eager.rows[level] * s->eager.row_elems[level] * 4;
     // streams lie side by side, as they do in the output: one copy per run of ids
     for (int i = 0, run; i < n_ids; i += run) {
@@ -2528,6 +2695,8 @@ int idf_read_announced_rows(idf_streams *s, int level, const int32_t *stream_ids
     if (level < 0 || level > n) return fail(IDF_EINVAL, "level %d outside [0, %d]", level, n);
     if (max_rows < 1) return fail(IDF_EINVAL, "max_rows must be >= 1");
     int rc = check_ids(s, stream_ids, n_ids);
+    if (rc != IDF_OK) return rc;
+    rc = eager_settle(s);
     if (rc != IDF_OK) return rc;
     const size_t row_bytes = (size_t)E.row_elems[level] * 4;
     std::vector<int64_t> lo, hi;
@@ -2692,6 +2861,7 @@ int idf_profile_begin(idf_streams *s)
 {
     if (!s) return fail(IDF_EINVAL, "null argument");
     if (s->prof_on) return fail(IDF_ESTATE, "profiling already on");
+    if (int rc = eager_flush(s)) return rc;
     s->prof_on = true;
     return IDF_OK;
 }

@@ -1,5 +1,8 @@
 // Eager emission of one segment through a whole net of 3x3 / stride 1 / same-padded conv layers and 2x2
-// max-pools in one launch: a workgroup takes one stream from the pushed rows to the output.
+// max-pools in one launch: a workgroup takes one stream from the pushed rows to the output, or, where pushes follow one another
+// without a read, through one stage of a few layers while others take the pushes before it through the stages behind (eager_stages in
+// idf_lib.hip has the rule and both sides of it; int8, eight streams of 112 x 112: 3195 -> 1126 us per image, float32, 256 streams of
+// 32 x 32: 1028 -> 952).
 //
 // A segment's events are a band of a few rows per layer, so layer by layer the work is small and the time
 // went into launches, into memory round trips between them and into finding the events: the 8 conv layers
@@ -21,7 +24,7 @@
 // ahead, and takes from there where it needs them (as scalar loads they were waited for, and of sixty values at once a third were put
 // aside and fetched back: 3975 instead of 3785 us, all else equal), worked out as far as the host can, three-operand bounds, bytes packed
 // and counted by the word, and rows that nothing reaches left out.
-// Measured per image of 112 x 112, int8, eight streams, 112 pushes: 4173 us, with fewer instructions 3860, waiting for weights and
+// Measured in one stage, per image of 112 x 112, int8, eight streams, 112 pushes: 4173 us, with fewer instructions 3860, waiting for weights and
 // states together 3727, as it is 3195; float32, 256 streams of 32 x 32, 32 pushes: 1130 -> 1034 us.  Per pushed row 28.5 us (layer by
 // layer 170) and 32 us (112), of which 14 us are matrix instructions (4,300 of 32 cycles, even over four SIMDs).
 #include <algorithm>
@@ -38,7 +41,7 @@ namespace {
 typedef const __attribute__((address_space(4))) EagerPassStep PassStep;
 typedef const __attribute__((address_space(4))) EagerPass PassArgs;
 
-constexpr int kPassWaves = 16, kPassThreads = 64 * kPassWaves, kPassLds = 160 * 1024 - 512;
+constexpr int kPassLds = 160 * 1024 - 512;
 
 // Zero times infinity is not zero: in a float net the first layer's positions carry as many cells of zeros as the last K-step of
 // their windows reads too far.  (Layers behind it have a multiple of 16 channels: their windows are whole K-steps.)
@@ -47,8 +50,9 @@ __host__ __device__ inline int pad_cells(bool is_float, int cells) { return is_f
 extern __shared__ __attribute__((aligned(16))) unsigned char pass_smem[];
 
 // ---- the pushed rows: announced values, events, and the first layer's delta band ---------------------
-template <class T> __device__ __forceinline__ void pass_input(PassArgs &a, PassStep &L, int stream, int pos, uint32_t *events)
+template <class T, int WAVES> __device__ __forceinline__ void pass_input(PassArgs &a, PassStep &L, int stream, int pos, uint32_t *events)
 {
+    constexpr int kThreads = 64 * WAVES;
     using ev_t = typename T::ev_t; using st_t = typename T::st_t;
     const int tid = threadIdx.x, W = L.w, C = L.c_in, n_rows = L.n_in, row_elems = W * C;
     const ev_t *src = (const ev_t *)a.in + (int64_t)pos * a.in_stride;
@@ -58,7 +62,7 @@ template <class T> __device__ __forceinline__ void pass_input(PassArgs &a, PassS
     uint32_t ev = 0;
     int slot = a.ann0_slot;
     for (int r = 0; r < n_rows; ++r) {
-        for (int i = tid; i < row_elems; i += kPassThreads) {
+        for (int i = tid; i < row_elems; i += kThreads) {
             const ev_t v = src[r * row_elems + i];
             ann[(int64_t)slot * row_elems + i] = (st_t)v;
             ev += T::ev_nonzero(v);
@@ -68,7 +72,7 @@ template <class T> __device__ __forceinline__ void pass_input(PassArgs &a, PassS
     if (L.cells > 0) {                             // whole cells: [row][position, one of halo in front][channel], padded (pad_cells)
         const int cells = L.cells, all = cells + pad_cells(T::EB == 4, cells), n = XP * all;
         for (int r = 0; r < n_rows; ++r)
-            for (int i = tid; i < n; i += kPassThreads) {
+            for (int i = tid; i < n; i += kThreads) {
                 const int p = i / all, c = i - p * all, x = p - 1;
                 i32x4 v = {0, 0, 0, 0};
                 if (x >= 0 && x < W && c < cells) v = reinterpret_cast<const i32x4 *>(src)[(r * W + x) * cells + c];
@@ -79,7 +83,7 @@ template <class T> __device__ __forceinline__ void pass_input(PassArgs &a, PassS
             constexpr int NC = decltype(n_tag)::value, WC = window_cells(NC, T::VL, T::EB == 4);
             const int XT = 16 * L.n_xt;
             // (a wave takes whole rows: the waves are many and a row is short)
-            for (int r = tid >> 6; r < n_rows; r += kPassWaves)
+            for (int r = tid >> 6; r < n_rows; r += WAVES)
               for (int p = tid & 63; p < XT; p += 64) {
                 ev_t val[WC * T::VL];
 #pragma unroll
@@ -155,7 +159,7 @@ template <class T> struct Weights {
 };
 
 // ---- one conv layer, and the 2x2 max-pool behind it ------------------------------------------------------
-template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, int words, int next, Weights<T> &wt, int stream, uint32_t *all_events)
+template <class T, int WAVES> __device__ __forceinline__ void pass_conv(PassArgs &a, int words, int next, Weights<T> &wt, int stream, uint32_t *all_events)
 {
     using acc_t = typename T::acc_t; using st_t = typename T::st_t;
     constexpr bool kInt = T::EB == 1;
@@ -202,7 +206,7 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, int wo
     auto enter = [&]() IDF_INLINE {
         lds_barrier();
         const int out_rows = STEP(out_rows), out_done = STEP(out_done), out_end = STEP(out_end);
-        if (emit) for (int r = wave; r < out_rows; r += kPassWaves) {
+        if (emit) for (int r = wave; r < out_rows; r += WAVES) {
             unsigned char *row = pass_smem + STEP(lds_out) + r * out_pitch;
             for (int o = lane * 16; o < out_stride; o += 1024) *reinterpret_cast<i32x4 *>(row + o) = i32x4{0, 0, 0, 0};
             for (int o = out_done + lane * 16; o < out_end; o += 1024) *reinterpret_cast<i32x4 *>(row + o) = i32x4{0, 0, 0, 0};
@@ -210,14 +214,14 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, int wo
     };
     // Every wave takes the same way, one without a task too, and a state is known to be here before a round ends: a request made on one
     // of two ways counts as out wherever they meet, and had the next layer wait for what it did not need yet.
-    int rounds = (int)((unsigned)(tasks + kPassWaves - 1) / kPassWaves), t = wave;
+    int rounds = (int)((unsigned)(tasks + WAVES - 1) / WAVES), t = wave;
     asm volatile("" : "+s"(rounds));
 #pragma unroll 1
     do {
         --rounds;
         const int n_mine = t < tasks ? n_ksteps : 0;           // (a wave without a task asks for its next weights like the others)
         if (n_mine) begin();
-        if (t < kPassWaves) enter();
+        if (t < WAVES) enter();
         acc_t acc[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = acc_t{0, 0, 0, 0};
@@ -255,7 +259,7 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, int wo
             int st = 0;
 #pragma unroll 1
             do {
-                if (st + 1 >= n_mine) wt.aim(rounds ? words : next, rounds ? t + kPassWaves : wave);
+                if (st + 1 >= n_mine) wt.aim(rounds ? words : next, rounds ? t + WAVES : wave);
                 if (n_mine) kstep(at(st));
                 wt.fetch();
                 __builtin_amdgcn_sched_barrier(0);
@@ -329,7 +333,7 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, int wo
             }
         }
         }
-        t += kPassWaves;
+        t += WAVES;
     } while (rounds);
     if constexpr (kInt) {
         ev = wave_sum(ev);
@@ -343,32 +347,78 @@ template <class T> __device__ __forceinline__ void pass_conv(PassArgs &a, int wo
     }
 }
 
-template <class T>
-__global__ void __launch_bounds__(kPassThreads, 4) k_eager_pass(const EagerPass args, const StreamSel sel)
+// ---- from stage to stage: the delta band as rows of whole cells, [row][position][cell], stream after stream ---------------
+// (four requests of a thread at once: one by one, each would be a trip to memory of its own)
+template <int WAVES> __device__ __forceinline__ void pass_hand_in(PassStep &L, const void *hand, int stream)
+{
+    constexpr int kThreads = 64 * WAVES, N = 4;
+    const int tid = threadIdx.x, W = L.w, cells = L.cells, per_row = (16 * L.n_xt + 2) * cells, n = L.n_in * per_row;
+    const i32x4 *src = reinterpret_cast<const i32x4 *>(hand) + (int64_t)stream * (L.n_in * W * cells);
+    const unsigned row_rcp = uni((int)(0xffffffffu / (unsigned)per_row + 1)), cell_rcp = uni((int)(0xffffffffu / (unsigned)cells + 1));
+    unsigned char *out = pass_smem + L.lds_in;
+    for (int i0 = tid; i0 < n; i0 += N * kThreads) {
+        i32x4 v[N];
+        int to[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const int i = i0 + k * kThreads;
+            const int r = (int)__umulhi((unsigned)i, row_rcp), in_row = i - r * per_row;
+            const int p = cells == 1 ? in_row : (int)__umulhi((unsigned)in_row, cell_rcp), c = in_row - p * cells;
+            const bool there = i < n && p >= 1 && p <= W;
+            to[k] = r * L.in_pitch + p * L.in_stride + c * 16;
+            v[k] = i32x4{0, 0, 0, 0};
+            if (there) v[k] = src[(r * W + p - 1) * cells + c];
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            if (i0 + k * kThreads < n) *reinterpret_cast<i32x4 *>(out + to[k]) = v[k];
+    }
+}
+template <int EB, int WAVES> __device__ __forceinline__ void pass_hand_on(PassStep &L, void *hand, int stream)
+{
+    constexpr int kThreads = 64 * WAVES;
+    const int tid = threadIdx.x, cells = L.c_out * EB / 16, per_row = L.out_w * cells, n = L.out_rows * per_row;
+    i32x4 *dst = reinterpret_cast<i32x4 *>(hand) + (int64_t)stream * n;
+    const unsigned row_rcp = uni((int)(0xffffffffu / (unsigned)per_row + 1)), cell_rcp = uni((int)(0xffffffffu / (unsigned)cells + 1));
+    const unsigned char *in = pass_smem + L.lds_out;
+    for (int i = tid; i < n; i += kThreads) {
+        const int r = per_row == 1 ? i : (int)__umulhi((unsigned)i, row_rcp), in_row = i - r * per_row;
+        const int p = cells == 1 ? in_row : (int)__umulhi((unsigned)in_row, cell_rcp), c = in_row - p * cells;
+        dst[i] = *reinterpret_cast<const i32x4 *>(in + r * L.out_pitch + (p + 1) * L.out_stride + c * 16);
+    }
+}
+
+// A workgroup takes one stream through the whole net or, STAGED, through one stage of it (gridDim.y of them, from a.stage0 on): layers
+// first[stage] .. end[stage] - 1.  (Kernels of their own: which layers they are is a trip to memory, 1.5 % of a pass of eight.)
+template <class T, int WAVES, bool STAGED>
+__global__ void __launch_bounds__(64 * WAVES, 4) k_eager_pass(const EagerPass args, const StreamSel sel)
 {
     // the arguments are read where the launch put them, a step at a time (by value they would be copied to scratch memory)
     PassArgs &a = *(PassArgs *)__builtin_amdgcn_kernarg_segment_ptr();
     __shared__ uint32_t events[2 * kPassMax + 2];      // per level
-    const int tid = threadIdx.x, stream = sel_stream(sel, blockIdx.x);
-    const int n = a.n;
-    int words = step_words(&a.st[0]), next = step_words(&a.st[n > 1 ? 1 : 0]);
+    const int tid = threadIdx.x, stream = sel_stream(sel, blockIdx.x), stage = STAGED ? a.stage0 + (int)blockIdx.y : 0;
+    const int k0 = STAGED ? a.first[stage] : 0, n = STAGED ? a.end[stage] : a.n;
+    if (STAGED && k0 >= n) return;
+    int words = step_words(&a.st[k0]), next = step_words(&a.st[k0 + 1 < n ? k0 + 1 : k0]);
     if (tid < 2 * kPassMax + 2) events[tid] = 0;
-    request_arguments<sizeof(EagerPass), kPassWaves>(&a, &a + 1);
+    request_arguments<sizeof(EagerPass), WAVES>(&a, &a + 1);
     Weights<T> wt;
     wt.aim(words, uni(tid >> 6));
     wt.fetch();
     asm volatile("" : "+v"(next));
     lds_barrier();
-    pass_input<T>(a, a.st[0], stream, sel.pos0 + (int)blockIdx.x, &events[0]);
+    if (STAGED && k0 > 0) pass_hand_in<WAVES>(a.st[k0], (const char *)a.hand + (uint64_t)a.hand_in[stage] * 256, stream);
+    else pass_input<T, WAVES>(a, a.st[0], stream, sel.pos0 + (int)blockIdx.x, &events[0]);
 #pragma unroll 1
-    for (int k = 0; k < n; ++k) {
+    for (int k = k0; k < n; ++k) {
         asm volatile("" : "+v"(next));             // (it is here)
         const int after = step_words(&a.st[k + 2 < n ? k + 2 : n - 1]);
-        pass_conv<T>(a, words, next, wt, stream, events);
+        pass_conv<T, WAVES>(a, words, next, wt, stream, events);
         words = next;
         next = after;
     }
     lds_barrier();
+    if (STAGED && a.st[n - 1].emit) pass_hand_on<T::EB, WAVES>(a.st[n - 1], (char *)a.hand + (uint64_t)a.hand_out[stage] * 256, stream);
     if (tid < a.n_layers && events[tid]) atomicAdd(a.stats + ((int64_t)stream * a.n_layers + tid) * 2, (unsigned long long)events[tid]);
 }
 
@@ -418,13 +468,18 @@ bool eager_pass_shape(int prec, EagerPass &a)
     return true;
 }
 
-hipError_t launch_eager_pass(int prec, const EagerPass &a, const StreamSel &sel, const LaunchCtx &lc)
+hipError_t launch_eager_pass(int prec, const EagerPass &a, int stages, bool small, const StreamSel &sel, const LaunchCtx &lc)
 {
-    auto go = [&](auto kernel) {
+    auto go = [&](auto kernel, int waves) {
         const hipError_t e = allow_lds<kPassLds>(kernel);
-        return e != hipSuccess ? e : launch(kernel.entry, dim3(sel.n), dim3(kPassThreads), (size_t)a.lds, lc, a, sel);
+        return e != hipSuccess ? e : launch(kernel.entry, dim3(sel.n, std::max(1, stages)), dim3(64 * waves), (size_t)a.lds, lc, a, sel);
     };
-    return prec == IDF_PREC_I8 ? go(Kernel<k_eager_pass<TraitsI8>>{}) : go(Kernel<k_eager_pass<TraitsF32>>{});
+    auto of = [&](auto t) {
+        using T = decltype(t);
+        if (stages == 0) return go(Kernel<k_eager_pass<T, 16, false>>{}, 16);
+        return small ? go(Kernel<k_eager_pass<T, 8, true>>{}, 8) : go(Kernel<k_eager_pass<T, 16, true>>{}, 16);
+    };
+    return prec == IDF_PREC_I8 ? of(TraitsI8{}) : of(TraitsF32{});
 }
 
 hipError_t launch_eager_announced(int prec, const Geom &g, const void *c, int c_rows, int64_t first, int n, void *out, hipStream_t st)
