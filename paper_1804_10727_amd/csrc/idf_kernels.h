@@ -86,8 +86,10 @@ size_t conv3x3_mfma_pack(int prec, const Geom &g, const void *w_khkwcico, void *
 size_t conv3x3_mfma_event_weights(int prec, const Geom &g);
 int conv3x3_mfma_event_cap();
 // Fills in how the workgroups of a step of a.n_rows rows lie (a.n_rows and a.ev_limit are set).  narrow: the step may share a
-// launch with one that takes the event path.
-void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, bool narrow, RowStep &a);
+// launch with one that takes the event path.  launch_waves: conv3x3_mfma_wide_waves of all steps of the launch, which count from kWideLaunch on.
+constexpr int kWideLaunch = 1400;
+int64_t conv3x3_mfma_wide_waves(int prec, const Geom &g, int n_streams, const RowStep &a);
+void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, bool narrow, int64_t launch_waves, RowStep &a);
 // Tiles per stream and step that a launch takes; a step of more is cut after as many rows as fit (false: not even two do).
 constexpr int kRowTilesMax = 65535;
 bool conv3x3_mfma_split(RowStep &first, RowStep &rest);

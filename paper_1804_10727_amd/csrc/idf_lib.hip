@@ -632,7 +632,7 @@ void row_step(idf_streams *s, int k, int64_t o, int64_t n, int n_streams, bool c
     a.bias = net.b_img[u.l].empty() ? nullptr : s->ws + s->b_off[u.l];
     a.stats = (unsigned long long *)(s->ws + s->stats_off);
     a.issued = s->count_issued ? (unsigned long long *)(s->ws + s->issued_off) : nullptr;
-    conv3x3_mfma_shape(net.precision, g, n_streams, s->ev_per_step > 0, a);
+    conv3x3_mfma_shape(net.precision, g, n_streams, s->ev_per_step > 0, 0, a);
     // Bytes the step has to move: the input rows the rows of c need (their events), the rows that leave, weights once.
     // Rows handed from layer to layer on their way out are not counted: the method does not require them to leave the chip.
     const int64_t i_lo = std::max<int64_t>(0, a.y0 - g.p_h), i_hi = std::min<int64_t>(g.h_in, a.y0 + n - g.p_h + g.k_h - 1);
@@ -741,6 +741,12 @@ bool row_plan(idf_streams *s, const RowProg &p, RowProg &q, int n_streams, const
         q.early &= ~(1u << k);
         q.out[k] = o + n;
         if (u.next >= 0) q.in[u.next] += rows_leaving(net, u, o, n);
+    }
+    if (s->ev_per_step == 0) {                     // which tiles a step takes goes by the launch, too
+        int64_t waves = 0;
+        for (int i = n_new > 0; i < b.n; ++i) waves += conv3x3_mfma_wide_waves(net.precision, net.g[b.st[i].layer], n_streams, b.st[i]);
+        for (int i = n_new > 0; i < b.n && waves >= kWideLaunch; ++i)
+            conv3x3_mfma_shape(net.precision, net.g[b.st[i].layer], n_streams, false, waves, b.st[i]);
     }
     if (n_new > 0) {
         q.in[0] += n_new;

@@ -793,18 +793,35 @@ static int row_ksteps(int prec, const Geom &g)
     return (3 * (g.c_in / vl) + 3) / 4;
 }
 
+// Waves of a step in tiles of 32 positions x 32 channels (0: it cannot have such).  float32 stays narrow, its matrix instructions being
+// sixteen times longer.  So do all steps next to one on the event path: one kernel with both wants more registers than three waves per
+// SIMD leave (20 bytes of scratch).
+int64_t conv3x3_mfma_wide_waves(int prec, const Geom &g, int n_streams, const RowStep &a)
+{
+    if (prec == IDF_PREC_F32 || a.ev_limit != 0 || a.n_rows < 2 || g.c_out <= 16) return 0;
+    return (int64_t)n_streams * ((g.w_out + 31) / 32) * ((g.c_out + 31) / 32) * ((a.n_rows + 1) / 2);
+}
+
+// Wide tiles use each weight fragment and each cell twice as often.  A step of its own has them where they give every SIMD most of a
+// wave; any but the smallest where the launch's steps together fill the chip with them, since weights on their way to the registers are
+// what bounds narrow ones then (42 bytes per clock and CU).  us per image, bfloat16, 64 to 256 channels, by step alone : with the launch
+// counted; streams of 96 x 224, rows per push:
+//   24 of 1 row 720 : 723, 32 798 : 778, 40 954 : 927, 48 957 : 911; 24 of 2 rows 554 : 513, 32 679 : 552; 12 of 4 296 : 295, 16 355 : 330,
+//   24 441 : 360; 8 of 8 195 : 185, 12 259 : 232, 16 301 : 260, 24 332 : 310; 60 of 96 x 100, 1 and 2 rows 792 : 780, 655 : 558.
+//   From 1,280 waves on in place of 1,400: 64 of 96 x 64, 2 rows, 433 : 436 : 478.  From 1,152 on: 12 of 4 rows 282 : 298.  From 1,792 on:
+//   24 of 2 rows 524 : 523, 40 of 1 row 910 : 889.  All steps of 192 and more, whatever the launch: 16 of 2 rows 402 : 474, 24 of 1 705 : 771.
+//   Steps of 256 and more in place of 192: 12 of 4 rows 303.  int8 the same either way (64 of 96 x 150, 4 rows, 197 : 195).
+constexpr int kWideAlone = 768, kWideLeast = 192;
+
 // Shape of a step of n_rows output rows for n_streams streams: which tiles a wave takes, how the waves of a
 // workgroup lie, and the numbers that follow from that.
-void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, bool narrow, RowStep &a)
+void conv3x3_mfma_shape(int prec, const Geom &g, int n_streams, bool narrow, int64_t launch_waves, RowStep &a)
 {
     const int vl = conv3x3_mfma_vl(prec);
     a.cells = g.c_in % vl == 0 && g.c_in >= vl ? g.c_in / vl : 0;
     const int n_ct = g.c_out == 16 ? 1 : 2 * ((g.c_out + 31) / 32);
-    const int pairs = a.n_rows >= 2 ? (a.n_rows + 1) / 2 : 1;
-    // Wide tiles use each weight fragment and each cell twice as often and pay where they still give
-    // every SIMD most of a wave; float32 stays narrow, its matrix instructions being sixteen times longer.  So do all steps next
-    // to one on the event path: one kernel with both wants more registers than three waves per SIMD leave (20 bytes of scratch).
-    const bool wide = prec != IDF_PREC_F32 && !narrow && a.ev_limit == 0 && a.n_rows >= 2 && g.c_out > 16 && (long)n_streams * ((g.w_out + 31) / 32) * (n_ct / 2) * pairs >= 768;
+    const int64_t waves = narrow ? 0 : conv3x3_mfma_wide_waves(prec, g, n_streams, a);
+    const bool wide = waves >= kWideAlone || (waves >= kWideLeast && launch_waves >= kWideLaunch);
     auto waves_log = [&](int tiles) { return tiles >= 4 ? 2 : tiles >= 2 ? 1 : 0; };
     a.wc_log = waves_log(wide ? n_ct / 2 : n_ct);
     // A stretch short enough for two workgroups to share a CU's LDS.  The waves it does not need for positions take channels; where
