@@ -8,6 +8,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
+_push = None                 # idf_push_segment on a tensor (csrc/push.cpp)
 
 IDF_OK, IDF_EINVAL, IDF_ENOMEM, IDF_ESTATE, IDF_EDEVICE, IDF_EUNSUPPORTED = 0, -1, -2, -3, -4, -5
 PREC = {"f32": 0, "bf16": 1, "i8": 2}
@@ -66,10 +67,10 @@ def lib_path() -> str:
 def load_library():
     """Load libidf.so, building it first only if it is not there.  No fallback: without the
     HIP library nothing in this package works."""
-    global _LIB
+    global _LIB, _push
     if _LIB is not None:
         return _LIB
-    if not os.path.exists(lib_path()):
+    if not os.path.exists(lib_path()) or not os.path.exists(os.path.join(_HERE, "_push.so")):
         from . import build as _build
         _build.build()
     # PyTorch ships its own copy of the HIP runtime (same soname).  Device pointers and streams
@@ -119,6 +120,9 @@ def load_library():
     L.idf_measure_peak.argtypes = [C.c_int, C.c_void_p, C.c_size_t, C.c_void_p, C.POINTER(C.c_double)]
     L.idf_profile_begin.argtypes = [C.c_void_p]
     L.idf_profile_end.argtypes = [C.c_void_p, C.c_int, C.POINTER(KernelProfile), C.POINTER(C.c_int)]
+    from . import _push as native
+    native.bind(C.cast(L.idf_push_segment, C.c_void_p).value)
+    _push = native.push
     _LIB = L
     return L
 
@@ -246,7 +250,7 @@ class Streams:
                 self.workspace = None
                 _check(load_library().idf_open_streams_static(net._h, n_streams, max_seg_rows, out_cap_rows,
                                                               C.c_void_p(self.stream.cuda_stream), C.byref(h)))
-                self._h = h
+                self._h, self._address = h, h.value
                 self.out_dtype = torch.int32 if net.precision == "i8" else torch.float32
                 return
             self.workspace = torch.empty(self.sizes.workspace_bytes + 256, dtype=torch.uint8, device=self.device)
@@ -255,21 +259,26 @@ class Streams:
             _check(load_library().idf_open_streams(net._h, n_streams, max_seg_rows, out_cap_rows,
                                                    C.c_void_p(self._ws_ptr), self.sizes.workspace_bytes,
                                                    C.c_void_p(self.stream.cuda_stream), C.byref(h)))
-        self._h = h
+        self._h, self._address = h, h.value
         self.out_dtype = torch.int32 if net.precision == "i8" else torch.float32
 
     def push_segment(self, rows, stream_ids=None, n_rows=None):
         """rows: device tensor [n_ids][n_rows][in_w][in_c] (float32 / bfloat16 / int8)."""
+        rc = _push(self._address, rows, stream_ids, n_rows)
+        if rc is None:
+            rc = self._push_converted(rows, stream_ids, n_rows)
+        if rc != IDF_OK:
+            _check(rc)
+
+    def _push_converted(self, rows, stream_ids, n_rows):
         assert rows.is_contiguous() and rows.is_cuda
         shape = rows.shape
         if stream_ids is None:
             ids, n_ids = None, shape[0]
-        else:           # (as bytes: a numpy array's address takes 0.9 us to ask for)
+        else:
             ids = np.ascontiguousarray(stream_ids, dtype=np.int32)
             ids, n_ids = ids.tobytes(), len(ids)
-        rc = _LIB.idf_push_segment(self._h, ids, n_ids, rows.data_ptr(), shape[1] if n_rows is None else n_rows)
-        if rc != IDF_OK:
-            _check(rc)
+        return _LIB.idf_push_segment(self._h, ids, n_ids, rows.data_ptr(), shape[1] if n_rows is None else n_rows)
 
     def set_push_batching(self, k):
         _check(load_library().idf_set_push_batching(self._h, int(k)))
@@ -425,7 +434,7 @@ class Streams:
     def close(self):
         if self._h:
             _check(load_library().idf_close_streams(self._h))
-            self._h = None
+            self._h, self._address = None, 0
 
 
 def create_net(precision, in_h, in_w, in_c, layers, weights, biases=None) -> Net:

@@ -1,16 +1,19 @@
-"""Builds the HIP library (libidf.so) for gfx950 with hipcc, in-tree."""
+"""Builds the HIP library (libidf.so) for gfx950 with hipcc, and the way into it from Python (_push.so), in-tree."""
 from __future__ import annotations
 
 import glob
 import os
 import shlex
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libidf.so")
+PUSH = os.path.join(HERE, "_push.so")
+PUSH_SRC = os.path.join(CSRC, "push.cpp")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -29,15 +32,25 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def push_command():
+    """The extension module is host code against torch's own headers and libraries, which are in the process before it is loaded."""
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    return ([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-o", PUSH, PUSH_SRC,
+             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}"] +
+            [a for d in [sysconfig.get_paths()["include"]] + include_paths() for a in ("-isystem", d)] +
+            ["-L" + d for d in library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-lc10"])
+
+
 def up_to_date() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(PUSH) or os.path.getmtime(PUSH) < os.path.getmtime(PUSH_SRC):
         return False
     deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
     return all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in deps)
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile every kernel and the host side into paper_1804_10727_amd/libidf.so."""
+    """Compile every kernel and the host side into paper_1804_10727_amd/libidf.so, and push.cpp into _push.so."""
     if not force and up_to_date():
         return LIB
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -58,8 +71,10 @@ def build(force: bool = True, verbose: bool = False) -> str:
 
     # one translation unit per kernel file, compiled side by side, then linked
     objs = [os.path.join(objdir, os.path.basename(f)[:-4] + ".o") for f in sources()]
-    with ThreadPoolExecutor(max_workers=min(8, len(objs))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(objs) + 1)) as ex:
+        push = ex.submit(run, push_command())
         list(ex.map(lambda fo: run([hipcc] + HIPCC_FLAGS + extra_flags() + ["-c", "-o", fo[1], fo[0]]), zip(sources(), objs)))
+        push.result()
     run([hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB] + objs)
     return LIB
 
