@@ -67,7 +67,7 @@ def lib_path() -> str:
 def load_library():
     """Load libidf.so, building it first only if it is not there.  No fallback: without the
     HIP library nothing in this package works."""
-    global _LIB, _push
+    global _LIB
     if _LIB is not None:
         return _LIB
     if not os.path.exists(lib_path()) or not os.path.exists(os.path.join(_HERE, "_push.so")):
@@ -120,11 +120,19 @@ def load_library():
     L.idf_measure_peak.argtypes = [C.c_int, C.c_void_p, C.c_size_t, C.c_void_p, C.POINTER(C.c_double)]
     L.idf_profile_begin.argtypes = [C.c_void_p]
     L.idf_profile_end.argtypes = [C.c_void_p, C.c_int, C.POINTER(KernelProfile), C.POINTER(C.c_int)]
-    from . import _push as native
-    native.bind(C.cast(L.idf_push_segment, C.c_void_p).value)
-    _push = native.push
     _LIB = L
     return L
+
+
+def load_push():
+    """Load _push.so, which needs torch's libraries in the process: with the first streams, whose pushes go through it."""
+    global _push
+    if _push is None:
+        L = load_library()
+        from . import _push as native
+        native.bind(C.cast(L.idf_push_segment, C.c_void_p).value)
+        _push = native.push
+    return _push
 
 
 PEAK_KINDS = {"copy": 0, "fma_f32": 1, "mfma_f32": 2, "mfma_bf16": 3, "mfma_i8": 4}
@@ -238,6 +246,7 @@ class Streams:
     def __init__(self, net: Net, n_streams, max_seg_rows=1, out_cap_rows=0, device="cuda:0", stream=None,
                  static_workspace=False):
         import torch
+        load_push()
         self.net = net
         self.n_streams = n_streams
         self.max_seg_rows = max_seg_rows

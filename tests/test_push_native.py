@@ -16,7 +16,7 @@ class Recorder:
     """Stands in for the library: takes down the call."""
 
     def __init__(self, monkeypatch):
-        idf.load_library()
+        binding.load_push()
         from paper_1804_10727_amd import _push as native
         self.calls = []
 
@@ -46,6 +46,7 @@ def recorder(monkeypatch):
 
 
 def _streams():
+    binding.load_push()
     s = object.__new__(idf.Streams)
     s._h, s._address = C.c_void_p(4096), 4096
     return s
@@ -91,7 +92,7 @@ def test_tensors_without_contiguous_memory_are_refused():
 
 
 def test_what_is_no_plain_tensor_goes_the_long_way():
-    idf.load_library()
+    binding.load_push()
     s = _streams()
     with pytest.raises(AssertionError):
         s.push_segment(torch.zeros((1, 1, 1, 1)))
