@@ -322,6 +322,7 @@ struct EagerPass {
     unsigned long long *stats;
     void *hand;                  // the bands from stage to stage lie at these places behind it, in units of 256 bytes
     uint32_t hand_in[kPassStages], hand_out[kPassStages];
+    int parts;                   // workgroups that share a stage of one layer
     int stage0;                  // first stage of the launch; per stage its layers (none: first == end)
     uint8_t first[kPassStages], end[kPassStages];
     EagerPassStep st[kPassMax];

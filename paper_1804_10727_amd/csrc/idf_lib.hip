@@ -169,6 +169,7 @@ struct idf_streams {
         // Stages (eager_stages): pushes that follow one another go through the net in step, each a stage behind the next.
         // Launch number `launch` takes the push that came with launch k through stage launch - k.
         int stages = 1;
+        int parts = 0;                            // workgroups of four waves that share a stage of one layer (0: a workgroup per stage)
         bool small = false;                       // workgroups of half as many waves
         int first[kPassStages + 1] = {};          // per stage its first layer
         size_t hand[kPassStages][2] = {};         // per stage where its band waits: of even and of odd launches
@@ -1398,6 +1399,7 @@ bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int
     const idf_streams::Eager &E = s->eager;
     P.n = 0;
     P.n_layers = n;
+    P.parts = 0;
     P.in = dev_rows; P.in_stride = (int64_t)n_rows * net.in_w * net.in_c;
     P.ann0 = E.ws + E.ann_off[0]; P.ann0_rows = E.ann_rows[0]; P.ann0_slot = (int)(a % E.ann_rows[0]);
     P.ann0_stride = (int64_t)E.ann_rows[0] * E.row_elems[0];
@@ -1513,13 +1515,19 @@ bool eager_one_launch(const idf_streams *s, std::vector<double> &most)
 // Measured, us per image, one stage : two : three : four (eight) of sixteen waves; two of eight waves: int8, 8 streams of 112 x 112,
 // 3195 : 2117 : 1754 : 1345 (1126); 2466.  float32, 32 x 32, 64 streams 975 : 606 : 595 : 598; 597.  100 streams 994 : 631 : 851 : 871; 629.
 // 128 streams 1003 : 641 : 856 : 879; 634.  200 streams 1024 : 1101 : 1181 : 1264; 943.  256 streams 1028 : 1125 : 1220 : 1319; 952.
-constexpr int kComputeUnits = 256;
+// A stage of one layer is shared by workgroups of four waves, up to eight of them and up to four to a compute unit: its waves then have
+// SIMDs to themselves, and each lane hands its differences to the next stage where the others waited for all of them in LDS first.
+// us per image, one workgroup of sixteen waves : so; int8, one stream of 112 x 112 1059 : 728, eight 1128 : 776, 12 of 80 x 80 758 : 594,
+// 16 of 60 x 60 492 : 428, 32 of 50 x 62 440 : 411; float32, 32 x 32, one stream 541 : 448, 16 568 : 464, 48 589 : 534, 56 and 64 593 : 601 and
+// 597 : 606, 60 of 24 x 48 710 : 649.  Up to one per compute unit only: eight streams of 112 x 112 825, 12 of 80 x 80 758.  Of more streams,
+// with one such workgroup to a layer: float32, 100 streams 630 : 823, 256 streams 961 : 1013.
+constexpr int kComputeUnits = 256, kPassParts = 8, kPartsPerUnit = 4;
 void eager_stages(idf_streams *s, const std::vector<double> &macs)
 {
     const idf_net &net = *s->net;
     idf_streams::Eager &E = s->eager;
     const int n = (int)macs.size();
-    E.stages = 1; E.small = false;
+    E.stages = 1; E.small = false; E.parts = 0;
     if (strict_rows()) return;
     int S = std::min({n, kPassStages, kComputeUnits / s->B});
     if (S < 2 && n > 1 && 2 * s->B <= 2 * kComputeUnits) { S = 2; E.small = true; }
@@ -1546,6 +1554,7 @@ void eager_stages(idf_streams *s, const std::vector<double> &macs)
         if (std::max(E.hand[k][0], E.hand[k][1]) / 256 > UINT32_MAX) return;
     }
     E.stages = S;
+    if (S == n && !E.small) E.parts = std::min(kPassParts, kPartsPerUnit * kComputeUnits / (S * s->B));
     E.plan.resize(S);
     E.launch = 0;
     std::fill(E.on_way, E.on_way + kPassStages, false);
@@ -1567,7 +1576,7 @@ int eager_advance(idf_streams *s, bool fresh, double bytes)
         if (hi < 0) {                                              // (all but the caller's rows is the same for all pushes, and those are the first one's)
             memcpy((void *)&A, (const void *)&P, offsetof(EagerPass, st));
             memset(A.first, 0, sizeof(A.first)); memset(A.end, 0, sizeof(A.end));
-            A.lds = 0; A.stage0 = lo = k;
+            A.lds = 0; A.stage0 = lo = k; A.parts = E.parts;
         }
         hi = k;
         const int a = E.first[k], b = std::max(a, std::min(P.n, E.first[k + 1]));

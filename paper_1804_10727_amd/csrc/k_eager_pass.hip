@@ -1,8 +1,8 @@
 // Eager emission of one segment through a whole net of 3x3 / stride 1 / same-padded conv layers and 2x2
 // max-pools in one launch: a workgroup takes one stream from the pushed rows to the output, or, where pushes follow one another
 // without a read, through one stage of a few layers while others take the pushes before it through the stages behind (eager_stages in
-// idf_lib.hip has the rule and both sides of it; int8, eight streams of 112 x 112: 3195 -> 1126 us per image, float32, 256 streams of
-// 32 x 32: 1028 -> 952).
+// idf_lib.hip has the rule and both sides of it; int8, eight streams of 112 x 112: 3195 -> 1126 us per image, and with several workgroups
+// to a stage 776; float32, 256 streams of 32 x 32: 1028 -> 952).
 //
 // A segment's events are a band of a few rows per layer, so layer by layer the work is small and the time
 // went into launches, into memory round trips between them and into finding the events: the 8 conv layers
@@ -50,7 +50,7 @@ __host__ __device__ inline int pad_cells(bool is_float, int cells) { return is_f
 extern __shared__ __attribute__((aligned(16))) unsigned char pass_smem[];
 
 // ---- the pushed rows: announced values, events, and the first layer's delta band ---------------------
-template <class T, int WAVES> __device__ __forceinline__ void pass_input(PassArgs &a, PassStep &L, int stream, int pos, uint32_t *events)
+template <class T, int WAVES> __device__ __forceinline__ void pass_input(PassArgs &a, PassStep &L, int stream, int pos, bool announces, uint32_t *events)
 {
     constexpr int kThreads = 64 * WAVES;
     using ev_t = typename T::ev_t; using st_t = typename T::st_t;
@@ -61,7 +61,7 @@ template <class T, int WAVES> __device__ __forceinline__ void pass_input(PassArg
     const int XP = 16 * L.n_xt + 2;
     uint32_t ev = 0;
     int slot = a.ann0_slot;
-    for (int r = 0; r < n_rows; ++r) {
+    if (announces) for (int r = 0; r < n_rows; ++r) {
         for (int i = tid; i < row_elems; i += kThreads) {
             const ev_t v = src[r * row_elems + i];
             ann[(int64_t)slot * row_elems + i] = (st_t)v;
@@ -159,7 +159,9 @@ template <class T> struct Weights {
 };
 
 // ---- one conv layer, and the 2x2 max-pool behind it ------------------------------------------------------
-template <class T, int WAVES> __device__ __forceinline__ void pass_conv(PassArgs &a, int words, int next, Weights<T> &wt, int stream, uint32_t *all_events)
+// SPLIT: the only layer of its stage, whose tasks `parts` workgroups share; differences go to memory (hand) from the lanes that have them.
+template <class T, int WAVES, bool SPLIT> __device__ __forceinline__ void pass_conv(PassArgs &a, int words, int next, Weights<T> &wt, int stream, int part, int parts,
+                                                                                    unsigned char *hand, uint32_t *all_events)
 {
     using acc_t = typename T::acc_t; using st_t = typename T::st_t;
     constexpr bool kInt = T::EB == 1;
@@ -206,7 +208,7 @@ template <class T, int WAVES> __device__ __forceinline__ void pass_conv(PassArgs
     auto enter = [&]() IDF_INLINE {
         lds_barrier();
         const int out_rows = STEP(out_rows), out_done = STEP(out_done), out_end = STEP(out_end);
-        if (emit) for (int r = wave; r < out_rows; r += WAVES) {
+        if (!SPLIT && emit) for (int r = wave; r < out_rows; r += WAVES) {
             unsigned char *row = pass_smem + STEP(lds_out) + r * out_pitch;
             for (int o = lane * 16; o < out_stride; o += 1024) *reinterpret_cast<i32x4 *>(row + o) = i32x4{0, 0, 0, 0};
             for (int o = out_done + lane * 16; o < out_end; o += 1024) *reinterpret_cast<i32x4 *>(row + o) = i32x4{0, 0, 0, 0};
@@ -214,14 +216,16 @@ template <class T, int WAVES> __device__ __forceinline__ void pass_conv(PassArgs
     };
     // Every wave takes the same way, one without a task too, and a state is known to be here before a round ends: a request made on one
     // of two ways counts as out wherever they meet, and had the next layer wait for what it did not need yet.
-    int rounds = (int)((unsigned)(tasks + WAVES - 1) / WAVES), t = wave;
+    const int all = SPLIT ? WAVES * parts : WAVES;             // waves that share the tasks
+    int rounds = SPLIT ? 1 : (int)((unsigned)(tasks + WAVES - 1) / WAVES), t = SPLIT ? part * WAVES + wave : wave;
+    if (SPLIT) for (int i = all; i < tasks; i += all) ++rounds;
     asm volatile("" : "+s"(rounds));
 #pragma unroll 1
     do {
         --rounds;
         const int n_mine = t < tasks ? n_ksteps : 0;           // (a wave without a task asks for its next weights like the others)
         if (n_mine) begin();
-        if (t < WAVES) enter();
+        if (t < all) enter();
         acc_t acc[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = acc_t{0, 0, 0, 0};
@@ -259,7 +263,7 @@ template <class T, int WAVES> __device__ __forceinline__ void pass_conv(PassArgs
             int st = 0;
 #pragma unroll 1
             do {
-                if (st + 1 >= n_mine) wt.aim(rounds ? words : next, rounds ? t + WAVES : wave);
+                if (st + 1 >= n_mine) wt.aim(rounds ? words : next, rounds ? t + all : wave);
                 if (n_mine) kstep(at(st));
                 wt.fetch();
                 __builtin_amdgcn_sched_barrier(0);
@@ -272,6 +276,8 @@ template <class T, int WAVES> __device__ __forceinline__ void pass_conv(PassArgs
         const uint32_t on = STEP(rows_on) >> (4 * gi), had = STEP(rows_old) >> (4 * gi);
         const bool out_ok = emit && co0 < C_out;
         unsigned char *out = pass_smem + STEP(lds_out) + STEP(out_first) * out_pitch + co0 * T::EB;
+        const int hand_pos = C_out * T::EB, hand_row = STEP(out_w) * hand_pos;
+        unsigned char *to_next = SPLIT ? hand + ((int64_t)stream * STEP(out_rows) + STEP(out_first)) * hand_row + co0 * T::EB : nullptr;
         // the differences of four channels (zero beyond the row's end) are counted and passed on
         auto deliver = [&](const acc_t &h_new, const acc_t &h_old, bool mine, uint32_t &n, unsigned char *to, bool pass) IDF_INLINE {
             st_t d[4];
@@ -315,7 +321,8 @@ template <class T, int WAVES> __device__ __forceinline__ void pass_conv(PassArgs
                     *at4(reinterpret_cast<acc_t *>(c_map + c_off[j]), cell) = acc[j];
                     if (ann) *at4(reinterpret_cast<acc_t *>(ann + (int64_t)(j * W * C_out) * 4), cell) = h_new[q];
                 }
-                deliver(h_new[q], h_old[q], here, ev, out + (4 * gi + j) * out_pitch + (x + 1) * out_stride, !pool && out_ok);
+                deliver(h_new[q], h_old[q], here, ev, SPLIT ? to_next + (4 * gi + j) * hand_row + x * hand_pos : out + (4 * gi + j) * out_pitch + (x + 1) * out_stride,
+                        !pool && out_ok && (!SPLIT || here));
             }
             if (pool && ((pool_on >> (2 * gi + p)) & 1u)) {
                 const bool mine = (x & 1) == 0 && (x >> 1) < out_w && co0 < C_out;
@@ -329,11 +336,11 @@ template <class T, int WAVES> __device__ __forceinline__ void pass_conv(PassArgs
                 }
                 if (mine) *at4(reinterpret_cast<acc_t *>((char *)ann_map + (int64_t)stream * ann_stride * 4 + (int64_t)((step_value<uint32_t>(words, (int)offsetof(EagerPassStep, pool_slots) / 4 + gi) >> p * 16) & 0xffffu) * (out_w * C_out * 4)),
                                (uint32_t)((x >> 1) * C_out + co0) * 4) = n;
-                deliver(n, o, mine, ev_pool, out + (2 * gi + p) * out_pitch + ((x >> 1) + 1) * out_stride, emit && mine);
+                deliver(n, o, mine, ev_pool, SPLIT ? to_next + (2 * gi + p) * hand_row + (x >> 1) * hand_pos : out + (2 * gi + p) * out_pitch + ((x >> 1) + 1) * out_stride, emit && mine);
             }
         }
         }
-        t += WAVES;
+        t += all;
     } while (rounds);
     if constexpr (kInt) {
         ev = wave_sum(ev);
@@ -389,36 +396,38 @@ template <int EB, int WAVES> __device__ __forceinline__ void pass_hand_on(PassSt
 }
 
 // A workgroup takes one stream through the whole net or, STAGED, through one stage of it (gridDim.y of them, from a.stage0 on): layers
-// first[stage] .. end[stage] - 1.  (Kernels of their own: which layers they are is a trip to memory, 1.5 % of a pass of eight.)
-template <class T, int WAVES, bool STAGED>
+// first[stage] .. end[stage] - 1.  SPLIT: stages are of one layer, whose tiles gridDim.z workgroups share (a.parts; the rule stands at eager_stages).  (Kernels of their own: which layers they are is a trip to memory, 1.5 % of a pass of eight.)
+template <class T, int WAVES, bool STAGED, bool SPLIT>
 __global__ void __launch_bounds__(64 * WAVES, 4) k_eager_pass(const EagerPass args, const StreamSel sel)
 {
     // the arguments are read where the launch put them, a step at a time (by value they would be copied to scratch memory)
     PassArgs &a = *(PassArgs *)__builtin_amdgcn_kernarg_segment_ptr();
     __shared__ uint32_t events[2 * kPassMax + 2];      // per level
     const int tid = threadIdx.x, stream = sel_stream(sel, blockIdx.x), stage = STAGED ? a.stage0 + (int)blockIdx.y : 0;
-    const int k0 = STAGED ? a.first[stage] : 0, n = STAGED ? a.end[stage] : a.n;
+    const int k0 = STAGED ? a.first[stage] : 0, n = STAGED ? a.end[stage] : a.n, part = SPLIT ? (int)blockIdx.z : 0, parts = SPLIT ? a.parts : 1;
     if (STAGED && k0 >= n) return;
     int words = step_words(&a.st[k0]), next = step_words(&a.st[k0 + 1 < n ? k0 + 1 : k0]);
     if (tid < 2 * kPassMax + 2) events[tid] = 0;
-    request_arguments<sizeof(EagerPass), WAVES>(&a, &a + 1);
+    if constexpr (SPLIT) request_arguments<sizeof(EagerPassStep), WAVES>(&a.st[k0], &a + 1);
+    else request_arguments<sizeof(EagerPass), WAVES>(&a, &a + 1);
+    if (SPLIT && part * WAVES >= IDF_OF(words, tasks) && part > 0) return;
     Weights<T> wt;
-    wt.aim(words, uni(tid >> 6));
+    wt.aim(words, part * WAVES + uni(tid >> 6));
     wt.fetch();
     asm volatile("" : "+v"(next));
     lds_barrier();
     if (STAGED && k0 > 0) pass_hand_in<WAVES>(a.st[k0], (const char *)a.hand + (uint64_t)a.hand_in[stage] * 256, stream);
-    else pass_input<T, WAVES>(a, a.st[0], stream, sel.pos0 + (int)blockIdx.x, &events[0]);
+    else pass_input<T, WAVES>(a, a.st[0], stream, sel.pos0 + (int)blockIdx.x, part == 0, &events[0]);
 #pragma unroll 1
     for (int k = k0; k < n; ++k) {
         asm volatile("" : "+v"(next));             // (it is here)
         const int after = step_words(&a.st[k + 2 < n ? k + 2 : n - 1]);
-        pass_conv<T, WAVES>(a, words, next, wt, stream, events);
+        pass_conv<T, WAVES, SPLIT>(a, words, next, wt, stream, part, parts, SPLIT ? (unsigned char *)a.hand + (uint64_t)a.hand_out[stage] * 256 : nullptr, events);
         words = next;
         next = after;
     }
     lds_barrier();
-    if (STAGED && a.st[n - 1].emit) pass_hand_on<T::EB, WAVES>(a.st[n - 1], (char *)a.hand + (uint64_t)a.hand_out[stage] * 256, stream);
+    if (STAGED && !SPLIT && a.st[n - 1].emit) pass_hand_on<T::EB, WAVES>(a.st[n - 1], (char *)a.hand + (uint64_t)a.hand_out[stage] * 256, stream);
     if (tid < a.n_layers && events[tid]) atomicAdd(a.stats + ((int64_t)stream * a.n_layers + tid) * 2, (unsigned long long)events[tid]);
 }
 
@@ -472,12 +481,13 @@ hipError_t launch_eager_pass(int prec, const EagerPass &a, int stages, bool smal
 {
     auto go = [&](auto kernel, int waves) {
         const hipError_t e = allow_lds<kPassLds>(kernel);
-        return e != hipSuccess ? e : launch(kernel.entry, dim3(sel.n, std::max(1, stages)), dim3(64 * waves), (size_t)a.lds, lc, a, sel);
+        return e != hipSuccess ? e : launch(kernel.entry, dim3(sel.n, std::max(1, stages), std::max(1, a.parts)), dim3(64 * waves), (size_t)a.lds, lc, a, sel);
     };
     auto of = [&](auto t) {
         using T = decltype(t);
-        if (stages == 0) return go(Kernel<k_eager_pass<T, 16, false>>{}, 16);
-        return small ? go(Kernel<k_eager_pass<T, 8, true>>{}, 8) : go(Kernel<k_eager_pass<T, 16, true>>{}, 16);
+        if (stages == 0) return go(Kernel<k_eager_pass<T, 16, false, false>>{}, 16);
+        if (a.parts > 0) return go(Kernel<k_eager_pass<T, 4, true, true>>{}, 4);
+        return small ? go(Kernel<k_eager_pass<T, 8, true, false>>{}, 8) : go(Kernel<k_eager_pass<T, 16, true, false>>{}, 16);
     };
     return prec == IDF_PREC_I8 ? of(TraitsI8{}) : of(TraitsF32{});
 }
