@@ -142,6 +142,8 @@ struct idf_streams {
     // pushes of all streams in step that wait for their launch (idf_set_push_batching)
     int batch = 1, batch_rows = 0;              // pushes per launch; rows a launch takes at most as the rings lie now
     int batch_room = 0;                         // and as they can lie at most
+    int since_read = 0;                         // 1-D nets: pushes since outputs were last read
+    bool read_each = false;                     // and whether that was after a single one
     int launch_rows = 0;                        // rows that arrive with a launch of 3x3 layers at most
     int held = 0, held_rows = 0;                // waiting buffers, and the rows each of them brings
     const void *held_buf[kGatherSegs];
@@ -2283,7 +2285,10 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
         } else {
             rc = gather_flush(s);
             if (rc != IDF_OK) return rc;
-            rc = run([&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, s->depth_first); });
+            // A signal that is read push by push goes through all layers with the push: what the read would bring out is out already.
+            // (us per push and read, audio net, one stream with 16 samples 29.4 -> 27.7, 4 samples 28.0 -> 26.3, 64 streams 31.8 -> 29.9)
+            const bool out = s->depth_first || (s->read_each && s->since_read == 0);
+            rc = run([&](const StreamSel &sel, RowProg &p) { return gather_run(s, sel, p, &dev_rows, 1, n_rows, out); });
         }
         if (rc != IDF_OK) return push_gave_up(s, rc);
     } else if (s->use_gather) {
@@ -2303,6 +2308,7 @@ int idf_push_segment(idf_streams *s, const int32_t *stream_ids, int n_ids, const
             if (rc != IDF_OK) return rc;
         }
     }
+    ++s->since_read;
     memo_r = -1;
     for (int i = 0; i < n_ids; ++i) {
         StreamHost &h = s->h[stream_ids ? stream_ids[i] : i];
@@ -2413,6 +2419,7 @@ int idf_read_outputs(idf_streams *s, const int32_t *stream_ids, int n_ids, void 
     if (rc != IDF_OK) return rc;
     if (max_rows < 1) return fail(IDF_EINVAL, "max_rows must be >= 1");
     if (s->eager.on) return fail(IDF_ESTATE, "eager emission: the output is read with idf_read_announced");
+    if (s->since_read > 0) { s->read_each = s->since_read == 1; s->since_read = 0; }
     rc = pipeline_drain(s);                // rows still between stages belong to what was pushed
     if (rc != IDF_OK) return rc;
     rc = head_catch_up(s, stream_ids, n_ids);
