@@ -227,7 +227,7 @@ struct GatherStep {
     // (in the order a workgroup needs them: a scalar load brings 64 bytes)
     int tiles, take;             // workgroups (set by the launcher); 1: the caller's rows are taken in, 2: a max-pool
     int n_ct, n_pt, spt_log;     // tiles of channels; of positions per stream or group of streams; streams per tile (log2)
-    int wide, n_cg;              // (set by the launcher) tiles are two by two; of channels then
+    int wide, n_cg;              // (set by the launcher) tiles are two by two, or their windows go through LDS; of channels then
     unsigned ct_rcp;
     int n_rows, y0;              // output rows (take: input rows): how many, first within its sample
     int n_ks, cells;             // K-steps; cells of 16 bytes per position (channels padded)

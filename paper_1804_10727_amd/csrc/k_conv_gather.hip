@@ -19,11 +19,12 @@
 // K-steps at a time) before they use any of it; their sums are added in a fixed order.  Results do not depend
 // on how rows or streams were grouped.  K-steps whose 16 positions hold no event are skipped.
 //
-//   k_conv_gather_rows    a workgroup per tile, all steps side by side;
+//   k_conv_gather_rows    a workgroup per tile, all steps side by side (_staged: some steps' windows by way of LDS);
 //   k_conv_gather_chain   a workgroup of four such teams per stream, the steps one after the other: rows that
 //                         are to come out at once go through all layers in one launch.
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "idf.h"
 #include "idf_kernels.h"
@@ -40,6 +41,15 @@ constexpr int kTeam = 4;                         // waves that share a tile
 constexpr int kChunk = 9;                        // K-steps a wave has in flight
 constexpr int kStages = 2;                       // and a wave of a tile of two by two (with 3, or 5 at once: one wave per SIMD less, which costs more)
 constexpr int kPoolCells = 64 * kTeam;           // cells of a pool's rows per workgroup
+constexpr int kStageCells = 1280, kStageLoads = 4;   // cells of windows in LDS; loads of a lane that bring them
+
+// Cells in LDS from one stream's rows to the next's.  The positions of two streams (four each; or eight of one) are served together:
+// they lie on banks of their own where all their distances are even and none the same (cells mod 16).
+__host__ __device__ inline int stage_block(int rows, int pitch, int s_h_log)
+{
+    const int n = rows * pitch, want = s_h_log == 0 ? 8 : 2;
+    return n + ((want - n) & 15);
+}
 
 // Taps of an axis that position v lands on inside an output of n positions (n == 0: unbounded).
 __device__ __forceinline__ int taps_axis(int v, int k, int s_log, int p, int n)
@@ -157,9 +167,9 @@ template <class T> __device__ __forceinline__ void pool_rows(Head &h, Step &a, c
 // TW 2: two such tiles of channels x two of positions.  Their sums are those of single tiles, formed in the same order; each weight
 // and each cell that is fetched serves two tiles, and each wave brings one of the four to its end.
 // share: LDS for the waves' sums (three, or four per tile); barrier: where the team's waves meet.
-template <class T, bool COUNT, bool CHAIN, int TW, class Barrier>
+template <class T, bool COUNT, bool CHAIN, int TW, bool STAGE, class Barrier>
 __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel, int si0, int pt, int ct, int spt_log, bool on, int kq,
-                                          typename T::acc_t *share, Barrier &&barrier)
+                                          typename T::acc_t *share, i32x4 *cells_at, Barrier &&barrier)
 {
     using acc_t = typename T::acc_t; using st_t = typename T::st_t;
     constexpr int VL = T::VL, EB = T::EB, NT = TW * TW;
@@ -314,7 +324,56 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
                     }
                 }
             };
-            if (flat) {
+            if constexpr (STAGE) {
+                // The rows that the tile's windows lie in go to LDS once, those of each stream by 4 / streams waves: windows that follow one
+                // another share all but their first rows, and loads of single cells are what bounds a launch of many tiles.
+                const int streams_log = 4 - per_log, cells_log = 31 - __builtin_clz(cells), P = 1 << per_log;
+                const int rows = ((P - 1) << s_h_log) + k_h, pitch = cells + 2, block = stage_block(rows, pitch, s_h_log);
+                const int own = kq >> (2 - streams_log), n = rows << cells_log;
+                const int y_first = ((y0 + (pt << per_log)) << s_h_log) - p_h;
+                const bool there = si0 + own < sel.n;
+                const unsigned char *from = (const unsigned char *)ring_p + (int64_t)sel_stream(sel, there ? si0 + own : 0) * ring_stride * EB;
+                i32x4 wv[kChunk], cv[kStageLoads];
+                const unsigned char *wf = wf0[0];
+#pragma unroll
+                for (int i = 0; i < kChunk; ++i)
+                    if (ks0 + i < ks1) wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf), (uint32_t)i * w_step + lane16);
+                const int i0 = (kq & ((4 >> streams_log) - 1)) * 64 + lane, step = 256 >> streams_log;
+#pragma unroll
+                for (int j = 0; j < kStageLoads; ++j) {
+                    const int i = i0 + j * step, r = i >> cells_log;
+                    unsigned slot = (unsigned)(slot0 + (((pt << per_log)) << s_h_log) + r);
+                    slot = min(slot, slot - (unsigned)ring_rows);
+                    slot = min(slot, slot - (unsigned)ring_rows);
+                    const bool ok = i < n && there && (unsigned)(y_first + r) < (unsigned)h_in;
+                    cv[j] = i32x4{0, 0, 0, 0};
+                    if (ok) cv[j] = *at4(reinterpret_cast<const i32x4 *>(from), (slot << cells_log | (unsigned)(i & (cells - 1))) * 16);
+                }
+#pragma unroll
+                for (int j = 0; j < kStageLoads; ++j) {
+                    const int i = i0 + j * step;
+                    if (i < n) cells_at[own * block + (i >> cells_log) * pitch + (i & (cells - 1))] = cv[j];
+                }
+                lds_barrier();
+                const i32x4 *mine = cells_at + (m >> per_log) * block + (pl << s_h_log) * pitch + g;
+#pragma unroll 1
+                for (int kb = ks0; kb < ks1; kb += kChunk) {
+                    i32x4 xv[kChunk];
+                    if (kb > ks0) {
+#pragma unroll
+                        for (int i = 0; i < kChunk; ++i)
+                            if (kb + i < ks1) wv[i] = *at4(reinterpret_cast<const i32x4 *>(wf0[0] + (kb - ks0) * w_step), (uint32_t)i * w_step + lane16);
+                    }
+#pragma unroll
+                    for (int i = 0; i < kChunk; ++i) {
+                        if (kb + i >= ks1) continue;
+                        const int q = 4 * (kb + i);
+                        xv[i] = mine[(q >> cells_log) * pitch + (q & (cells - 1))];
+                        if (!valid) xv[i] = i32x4{0, 0, 0, 0};
+                    }
+                    contract(xv, wv, kb);
+                }
+            } else if (flat) {
                 const int q_last = k_h * cells - 1;
                 // (a window that reaches over an end of the signal: its cells there are zero; so are those past the window's end, where
                 // the weights are zero too, but zero times infinity is not)
@@ -471,12 +530,12 @@ __device__ __forceinline__ void conv_tile(Head &h, Step &a, const StreamSel &sel
 // the first 256 / the first 512 / all: 64 audio streams 6090 / 5980 / 5785 / 5732; 37 streams with 16 pushes per launch 742 / 738 /
 // 738 / 762; 32 images through six layers 606 / 583 / 551 / 615; one live stream 36.3, asking 32.2.
 constexpr int kFirst = 512;
-template <class T, int NS, bool COUNT, bool WIDE>
-__global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows(const GatherBatch<NS> args, const StreamSel sel)
+template <class T, int NS, bool COUNT, bool WIDE, bool STAGE> __device__ __forceinline__ void gather_rows(const StreamSel &sel)
 {
     typedef const __attribute__((address_space(4))) GatherBatch<NS> Batch;
     Batch &b = *(Batch *)__builtin_amdgcn_kernarg_segment_ptr();
     __shared__ typename T::acc_t share[(WIDE ? 4 * kTeam : kTeam - 1) * 64];
+    __shared__ i32x4 cells_at[STAGE ? kStageCells : 1];
     // The steps' tiles follow each other without gaps: workgroups go to the compute units in turn, and with an empty one here
     // and there some units got the tiles of three layers and others none (12.7 us per launch of 64 audio streams instead of 7).
     int k = 0, tile = blockIdx.x;
@@ -514,9 +573,16 @@ __global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows(const Gather
     if (take == 1) { take_rows<T>(b.head, a, sel, sg, threadIdx.x, 64 * kTeam); return; }
     if (take == 2) { pool_rows<T>(b.head, a, sel, sg, rest * kPoolCells, (rest + 1) * kPoolCells, 64 * kTeam); return; }
     const int n_cg = a.n_cg, pt = a.ct_rcp ? (int)__umulhi((unsigned)rest, a.ct_rcp) : rest, cg = rest - pt * n_cg;
-    if (WIDE && a.wide) conv_tile<T, COUNT, false, 2>(b.head, a, sel, sg, pt, 2 * cg, 0, true, uni(threadIdx.x >> 6), share, [] { lds_barrier(); });
-    else conv_tile<T, COUNT, false, 1>(b.head, a, sel, sg << spt_log, pt, cg, spt_log, true, uni(threadIdx.x >> 6), share, [] { lds_barrier(); });
+    const int wave = uni(threadIdx.x >> 6);
+    if (WIDE && a.wide) conv_tile<T, COUNT, false, 2, false>(b.head, a, sel, sg, pt, 2 * cg, 0, true, wave, share, nullptr, [] { lds_barrier(); });
+    else if (STAGE && a.wide) conv_tile<T, COUNT, false, 1, STAGE>(b.head, a, sel, sg << spt_log, pt, cg, spt_log, true, wave, share, cells_at, [] { lds_barrier(); });
+    else conv_tile<T, COUNT, false, 1, false>(b.head, a, sel, sg << spt_log, pt, cg, spt_log, true, wave, share, nullptr, [] { lds_barrier(); });
 }
+
+template <class T, int NS, bool COUNT, bool WIDE>
+__global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows(const GatherBatch<NS> args, const StreamSel sel) { gather_rows<T, NS, COUNT, WIDE, false>(sel); }
+template <class T, int NS>
+__global__ void __launch_bounds__(64 * kTeam, 4) k_conv_gather_rows_staged(const GatherBatch<NS> args, const StreamSel sel) { gather_rows<T, NS, false, false, true>(sel); }
 
 template <class T, int NS, bool COUNT>
 __global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherBatch<NS> args, const StreamSel sel)
@@ -540,7 +606,7 @@ __global__ void __launch_bounds__(256 * kTeam) k_conv_gather_chain(const GatherB
                 Step *step = &a;
                 asm volatile("" : "+s"(step));     // (a tile's arguments are read anew: kept over the loop they do not fit the registers)
                 const int t = t0 + team, pt = a.ct_rcp ? (int)__umulhi((unsigned)t, a.ct_rcp) : t, ct = t - pt * a.n_ct;
-                conv_tile<T, COUNT, true, 1>(b.head, *step, sel, si, pt, ct, 0, t < tasks, kq, share[team], [] { lds_barrier(); });
+                conv_tile<T, COUNT, true, 1, false>(b.head, *step, sel, si, pt, ct, 0, t < tasks, kq, share[team], nullptr, [] { lds_barrier(); });
                 lds_barrier();                     // the sums have been read, and every wave's rows are there for the next step
             }
         }
@@ -590,7 +656,19 @@ int streams_per_tile_log(int positions, bool first)
 constexpr int kWideTiles = 1536, kWideShare = 16;
 bool wide_step(const GatherStep &a) { return a.take == 0 && a.n_ct >= 2 && a.n_pt >= 2 && a.spt_log == 0; }
 
-template <class T, int NS, bool WIDE> hipError_t launch_ns(const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc)
+// A step whose windows go through LDS: many K-steps, whole K-steps to a row, one to four streams per tile; and launches that have them
+// do so from as many tiles on as there are compute units: with fewer it makes no difference.  us per pass, cell by cell : through LDS, audio
+// net, 16 samples per push, 64 streams of 16,000 samples 5637 : 5323, of 8,000, 48 streams 2994 : 2818, 32 2584 : 2528, 16 (144 tiles)
+// 2739 : 2733; 16 pushes per launch, 12 streams 302 : 298.  (Without any loads of cells the first would take 4888, without weights' 5455.)
+bool stage_step(const GatherStep &a)
+{
+    if (a.take != 0 || !a.flat || a.spt_log > 2 || a.n_ks < 9 || a.cells < 4 || (a.cells & (a.cells - 1))) return false;
+    const int P = 16 >> a.spt_log, rows = ((P - 1) << a.s_h_log) + a.k_h;
+    return rows * a.cells <= kStageLoads * (256 >> a.spt_log) && stage_block(rows, a.cells + 2, a.s_h_log) << a.spt_log <= kStageCells && (P << a.s_h_log) + a.k_h <= a.ring_rows;
+}
+constexpr int kStageTiles = 256;
+
+template <class T, int NS, bool WIDE, bool STAGE> hipError_t launch_ns(const GatherHead &h, const GatherStep *st, const StreamSel &sel, bool chain, const LaunchCtx &lc)
 {
     GatherBatch<NS> b;
     b.head = h;
@@ -606,6 +684,7 @@ template <class T, int NS, bool WIDE> hipError_t launch_ns(const GatherHead &h, 
     for (int k = 0; k < h.n; ++k) {
         b.st[k] = st[k];
         GatherStep &a = b.st[k];
+        if (STAGE) a.wide = stage_step(a);
         if (WIDE && (a.wide = wide_step(a))) {
             a.n_cg = (a.n_ct + 1) / 2; a.n_pt = (a.n_pt + 1) / 2;
             a.ct_rcp = a.n_cg > 1 ? (unsigned)((0x100000000ull + a.n_cg - 1) / a.n_cg) : 0u;
@@ -621,7 +700,8 @@ template <class T, int NS, bool WIDE> hipError_t launch_ns(const GatherHead &h, 
     }
     if (tiles < 1 || tiles > INT32_MAX / (64 * kTeam)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles), block(64 * kTeam);
-    if constexpr (WIDE) return launch(k_conv_gather_rows<T, NS, false, true>, grid, block, 0, lc, b, sel);
+    if constexpr (STAGE) return launch(k_conv_gather_rows_staged<T, NS>, grid, block, 0, lc, b, sel);
+    else if constexpr (WIDE) return launch(k_conv_gather_rows<T, NS, false, true>, grid, block, 0, lc, b, sel);
     else return h.issued ? launch(k_conv_gather_rows<T, NS, true, false>, grid, block, 0, lc, b, sel) : launch(k_conv_gather_rows<T, NS, false, false>, grid, block, 0, lc, b, sel);
 }
 
@@ -635,9 +715,15 @@ template <class T> hipError_t launch_t(const GatherHead &h, const GatherStep *st
         tiles += n;
         if (wide_step(st[k])) paired += n;
     }
-    if (!chain && !h.issued && tiles >= kWideTiles && paired * kWideShare >= tiles) return launch_ns<T, kGatherMax, true>(h, st, sel, false, lc);
+    if (!chain && !h.issued && tiles >= kWideTiles && paired * kWideShare >= tiles) return launch_ns<T, kGatherMax, true, false>(h, st, sel, false, lc);
     // (the short block for the usual few steps: a third of the bytes to hand over)
-    return h.n <= 4 ? launch_ns<T, 4, false>(h, st, sel, chain, lc) : launch_ns<T, kGatherMax, false>(h, st, sel, chain, lc);
+    if constexpr (std::is_same<T, TraitsF32>::value) {
+        bool any = false;
+        for (int k = 0; k < h.n; ++k) any = any || stage_step(st[k]);
+        if (!chain && !h.issued && any && tiles >= kStageTiles)
+            return h.n <= 4 ? launch_ns<T, 4, false, true>(h, st, sel, false, lc) : launch_ns<T, kGatherMax, false, true>(h, st, sel, false, lc);
+    }
+    return h.n <= 4 ? launch_ns<T, 4, false, false>(h, st, sel, chain, lc) : launch_ns<T, kGatherMax, false, false>(h, st, sel, chain, lc);
 }
 
 }  // namespace
