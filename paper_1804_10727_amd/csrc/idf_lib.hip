@@ -163,6 +163,7 @@ struct idf_streams {
         bool on = false;
         bool ring = false;
         bool one_launch = false;                  // a segment can go through the net in one launch (k_eager_pass.hip)
+        bool by_stage = false;                    // but is too much for one workgroup: a launch per stage where pushes are not in stages
         char *ws = nullptr;
         std::vector<int64_t> row_elems;           // per level: W*C of one row
         std::vector<int> rows;                    // per level: rows the level has (H)
@@ -1465,9 +1466,11 @@ bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int
 // behind any of them; no biases (rings, every row starts from zero); differences that fit the operands -- a bfloat16
 // net's do not, and an int8 net must clamp what it passes on.  The switches that choose between the kernels for single
 // layers choose those.
-bool eager_one_launch(const idf_streams *s, std::vector<double> &most)
+constexpr int kComputeUnits = 256, kPassParts = 8, kPartsPerUnit = 4;
+bool eager_one_launch(const idf_streams *s, std::vector<double> &most, bool &by_stage)
 {
     most.clear();
+    by_stage = false;
     const idf_net &net = *s->net;
     const bool ring = s->eager.ring;
     const int n = (int)net.g.size();
@@ -1495,7 +1498,10 @@ bool eager_one_launch(const idf_streams *s, std::vector<double> &most)
         // One workgroup per stream: at float32 it does 160 multiply-adds per ns, where a launch per layer takes some 14 us
         // for each layer as long as the streams are few (one stream of 32-32-64-64 channels: 57 us against about 70 at
         // 64 positions, 108 against 73 at 128; with 64 streams the two are even there).  The quantised nets are ahead
-        // at any size that fits (one stream of 224 positions: 62 us against 158).
+        // at any size that fits (one stream of 224 positions: 62 us against 158).  Beyond that line the nets whose layers have
+        // workgroups to themselves go through in stages, or, read push by push or apart, a stage after the other (us per image, layer by layer :
+        // in stages, 32-32-64-64 channels: 20 streams of 48 x 48, 2 rows per push, 1850 : 464, one stream of 48 x 128 3507 : 799, 60 of
+        // 48 x 40, 3 rows, 1369 : 540; read push by push 1901 : 1029, 3595 : 2114, 1492 : 785; the first apart 34,950 : 18,789).
         double macs = 0;
         most.resize(std::max<size_t>(most.size(), P.n), 0.0);
         for (int k = 0; k < P.n; ++k) {
@@ -1503,9 +1509,10 @@ bool eager_one_launch(const idf_streams *s, std::vector<double> &most)
             macs += m;
             most[k] = std::max(most[k], m);
         }
-        if (net.precision == IDF_PREC_F32 && s->B < 64 && macs > 160e3 * 14 * n) return false;
+        by_stage = by_stage || (net.precision == IDF_PREC_F32 && s->B < 64 && macs > 160e3 * 14 * n);
     }
-    return true;
+    const int stages = (int)most.size();
+    return !by_stage || (!strict_rows() && stages >= 2 && stages <= kPassStages && stages * s->B <= kComputeUnits);
 }
 
 // How a net goes through in stages, given the multiply-adds of each of its layers in a segment and stream.  One workgroup per stream
@@ -1523,7 +1530,6 @@ bool eager_one_launch(const idf_streams *s, std::vector<double> &most)
 // 16 of 60 x 60 492 : 428, 32 of 50 x 62 440 : 411; float32, 32 x 32, one stream 541 : 448, 16 568 : 464, 48 589 : 534, 56 and 64 593 : 601 and
 // 597 : 606, 60 of 24 x 48 710 : 649.  Up to one per compute unit only: eight streams of 112 x 112 825, 12 of 80 x 80 758.  Of more streams,
 // with one such workgroup to a layer: float32, 100 streams 630 : 823, 256 streams 961 : 1013.
-constexpr int kComputeUnits = 256, kPassParts = 8, kPartsPerUnit = 4;
 void eager_stages(idf_streams *s, const std::vector<double> &macs)
 {
     const idf_net &net = *s->net;
@@ -1638,7 +1644,14 @@ int eager_pass(idf_streams *s, const StreamSel &sel, const void *dev_rows, int n
         EagerPass P;
         double bytes = 0;
         if (!eager_pass_plan(s, dev_rows, n_rows, a, lo, hi, seen_hi, P, bytes)) return fail(IDF_ESTATE, "internal: a segment does not fit one launch");
-        hipError_t e = launch_eager_pass(net.precision, P, 0, false, sel, launch_ctx(s, kKindEager, bytes * sel.n, 0));
+        hipError_t e = hipSuccess;
+        if (!E.by_stage) e = launch_eager_pass(net.precision, P, 0, false, sel, launch_ctx(s, kKindEager, bytes * sel.n, 0));
+        P.parts = E.parts;
+        for (int k = 0; E.by_stage && k < P.n && e == hipSuccess; ++k) {
+            P.stage0 = k; P.first[k] = (uint8_t)k; P.end[k] = (uint8_t)(k + 1);
+            P.hand_in[k] = (uint32_t)(E.hand[k][0] / 256); P.hand_out[k] = k + 1 < E.stages ? (uint32_t)(E.hand[k + 1][0] / 256) : 0u;
+            e = launch_eager_pass(net.precision, P, 1, false, sel, launch_ctx(s, kKindEager, k == 0 ? bytes * sel.n : 0.0, 0));
+        }
         return e == hipSuccess ? (int)IDF_OK : dev_fail(e, "eager launch");
     }
     auto fresh_from = [&](int lv) { return E.ring ? (int)seen_hi[lv] : (int)E.rows[lv]; };    // whole maps are cleared when a sample begins
@@ -2659,8 +2672,9 @@ int idf_enable_eager(idf_streams *s, void *dev_workspace, size_t workspace_bytes
     eager_layout(*s->net, s->B, s->max_seg, &s->eager);
     s->eager.ws = (char *)dev_workspace;
     std::vector<double> macs;
-    s->eager.one_launch = eager_one_launch(s, macs);
+    s->eager.one_launch = eager_one_launch(s, macs, s->eager.by_stage);
     if (s->eager.one_launch) eager_stages(s, macs);
+    if (s->eager.by_stage && s->eager.parts == 0) s->eager.one_launch = s->eager.by_stage = false;
     s->eager.on = true;
     return IDF_OK;
 }
