@@ -310,8 +310,8 @@ int idf_rows_pushed(const idf_streams *s, int stream_id, int64_t *rows);
 
 /* Eager emission -- Sec. 3 taken literally: every neuron announces a change of f(c) at once, as an
  * event that the next layer takes in at once, so that after every pushed segment the announced
- * activations of every layer are those of the conventional network on the input seen so far (the
- * rest taken as zero; Sec. 4, Fig. 3).  State lives in a second caller-owned device workspace of
+ * activations of every layer, as the calls below read them, are those of the conventional network on the
+ * input seen so far (the rest taken as zero; Sec. 4, Fig. 3).  State lives in a second caller-owned device workspace of
  * idf_query_eager_bytes() bytes; bounded samples only (IDF_EUNSUPPORTED otherwise); all three
  * precisions (a bfloat16 net announces values rounded to bfloat16, the last layer unrounded, like
  * its row-complete counterpart).
@@ -332,6 +332,9 @@ int idf_rows_pushed(const idf_streams *s, int stream_id, int64_t *rows);
  * idf_get_stats then counts, per layer, the non-zero changes delivered to it.
  *   Segments pushed one after the other may be on their way through the layers when a push returns; every call that
  * shows results lets them finish first, and after a whole sample nothing is on its way.
+ *   Calls may be recorded into a graph anywhere in a sample.  What is on its way then is brought through by a replay or by the
+ * next call that is not recorded, whichever runs first.  From the first recorded call on nothing is on its way when a push returns:
+ * a recorded read shows, at every replay, what has been pushed by then.
  * idf_eager_state_bytes: state c and announced values retained per stream (without the output map);
  * rows_kept (host, n_layers + 1 entries, may be NULL): rows kept per level. */
 int idf_query_eager_bytes(const idf_net *net, int n_streams, int max_seg_rows, size_t *bytes);

@@ -68,8 +68,9 @@ bool eager_pass_shape(int prec, EagerPass &a);
 hipError_t launch_eager_pass(int prec, const EagerPass &a, int stages, bool small, const StreamSel &sel, const LaunchCtx &lc);
 // Announced values of rows [first, first + n) of a conv layer from its ring of c_rows rows of state.
 hipError_t launch_eager_announced(int prec, const Geom &g, const void *c, int c_rows, int64_t first, int n, void *out, hipStream_t st);
-// Clears bytes (a multiple of 4, 4-byte aligned) with a kernel on stream st.
-hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st);
+// Sets the 4-byte words of bytes (a multiple of 4, 4-byte aligned) with a kernel on stream st.
+hipError_t launch_fill(void *p, size_t bytes, uint32_t v, hipStream_t st);
+inline hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st) { return launch_fill(p, bytes, 0u, st); }
 hipError_t launch_copy_out(const CopyOut &a, const StreamSel &sel, int64_t first_slot, int n_rows,
                            const LaunchCtx &lc);
 

@@ -179,6 +179,11 @@ struct idf_streams {
         int64_t launch = 0;
         bool on_way[kPassStages] = {};            // the push of launch k, at k mod stages, has not gone through all of them
         std::vector<EagerPass> plan;              // and what each of them does
+        // Recorded into a graph (eager_flush), what is on its way may run with a replay, or not before the next call that is not recorded:
+        // whichever comes first finds `open` set and clears it.  Once anything has been recorded pushes go through all layers at once.
+        bool recorded = false, in_graph = false;  // a call on a recording stream; one with something on its way
+        unsigned long long graph = 0;             // the recording that has it
+        uint32_t *open = nullptr;
         int since_read = 0;                       // pushes since results were last asked for
         bool read_each = false;                   // results were asked for after a single push
         std::vector<int64_t> lo, hi, seen_lo, seen_hi;
@@ -1407,7 +1412,7 @@ bool eager_pass_plan(const idf_streams *s, const void *dev_rows, int n_rows, int
     P.ann0 = E.ws + E.ann_off[0]; P.ann0_rows = E.ann_rows[0]; P.ann0_slot = (int)(a % E.ann_rows[0]);
     P.ann0_stride = (int64_t)E.ann_rows[0] * E.row_elems[0];
     P.stats = (unsigned long long *)(s->ws + s->stats_off);
-    P.hand = E.ws;
+    P.hand = E.ws; P.open = nullptr;
     bytes = 0;
     for (int l = 0; l < n && hi[l] > lo[l] && hi[l + 1] > lo[l + 1];) {
         const Geom &g = net.g[l];
@@ -1561,6 +1566,7 @@ void eager_stages(idf_streams *s, const std::vector<double> &macs)
         E.hand[k][0] = E.ann_off[lv]; E.hand[k][1] = E.dlt_off[lv];
         if (std::max(E.hand[k][0], E.hand[k][1]) / 256 > UINT32_MAX) return;
     }
+    E.open = (uint32_t *)(E.ws + E.dlt_off[0]);                    // (the first stage's band is the caller's rows)
     E.stages = S;
     if (S == n && !E.small) E.parts = std::min(kPassParts, kPartsPerUnit * kComputeUnits / (S * s->B));
     E.plan.resize(S);
@@ -1584,7 +1590,7 @@ int eager_advance(idf_streams *s, bool fresh, double bytes)
         if (hi < 0) {                                              // (all but the caller's rows is the same for all pushes, and those are the first one's)
             memcpy((void *)&A, (const void *)&P, offsetof(EagerPass, st));
             memset(A.first, 0, sizeof(A.first)); memset(A.end, 0, sizeof(A.end));
-            A.lds = 0; A.stage0 = lo = k; A.parts = E.parts;
+            A.lds = 0; A.stage0 = lo = k; A.parts = E.parts; A.open = E.in_graph ? E.open : nullptr;
         }
         hi = k;
         const int a = E.first[k], b = std::max(a, std::min(P.n, E.first[k + 1]));
@@ -1605,19 +1611,49 @@ int eager_advance(idf_streams *s, bool fresh, double bytes)
     return IDF_OK;
 }
 
-// Every push on its way goes through the stages that are left.
+// 1: the stream is being recorded into a graph, as `id`; -1: it cannot be told.
+int eager_recording(idf_streams *s, unsigned long long *id = nullptr)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    unsigned long long n = 0;
+    if (hipStreamGetCaptureInfo(s->st, &c, &n) != hipSuccess) { (void)hipGetLastError(); return -1; }
+    if (c == hipStreamCaptureStatusNone) return 0;
+    s->eager.recorded = true;
+    if (id) *id = n;
+    return 1;
+}
+
+// Every push on its way goes through the stages that are left.  On a recording stream these launches are part of the graph, in front of what
+// else is recorded, and nothing has run when the call returns: the host keeps the pushes, and until it knows better every graph and the
+// next call that is not recorded bring them through.  The first that runs does it (EagerPass::open); the others find nothing left.
 int eager_flush(idf_streams *s)
 {
     idf_streams::Eager &E = s->eager;
     if (E.stages < 2) return IDF_OK;
+    unsigned long long graph = 0;
+    const bool recording = eager_recording(s, &graph) == 1;
     auto pending = [&]() {
         for (int k = 1; k < E.stages && k <= E.launch; ++k)
             if (E.on_way[(E.launch - k) % E.stages]) return true;
         return false;
     };
-    while (pending())
-        if (int rc = eager_advance(s, false, 0)) return rc;
-    return IDF_OK;
+    if (!pending() || (recording && E.in_graph && E.graph == graph)) return IDF_OK;
+    const int64_t launch = E.launch;
+    bool on_way[kPassStages];
+    std::copy(E.on_way, E.on_way + kPassStages, on_way);
+    E.in_graph = E.in_graph || recording;
+    int rc = IDF_OK;
+    while (rc == IDF_OK && pending()) rc = eager_advance(s, false, 0);
+    if (rc == IDF_OK && E.in_graph) {
+        hipError_t e = launch_fill_zero(E.open, 4, s->st);
+        if (e != hipSuccess) rc = dev_fail(e, "eager launch");
+    }
+    if (recording) {
+        E.launch = launch;
+        std::copy(on_way, on_way + kPassStages, E.on_way);
+        if (rc == IDF_OK) E.graph = graph;
+    }
+    return rc;
 }
 
 // Results are asked for.
@@ -1697,18 +1733,15 @@ int eager_pass(idf_streams *s, const StreamSel &sel, const void *dev_rows, int n
 }
 
 // A push in stages: all streams, in step and in order.  Not where results have been asked for push by push (a push then goes through all
-// layers at once: the stages would be as many launches), not while launches are timed (each is then the work of one push), and not into a graph that is being recorded, which may be replayed without
-// the launches that would follow.
-bool eager_staged(const idf_streams *s, const int32_t *stream_ids, int n_ids)
+// layers at once: the stages would be as many launches), not while launches are timed (each is then the work of one push), and not into a graph, which may be
+// replayed without the launches that would follow, nor behind one: a recorded read shows what has been pushed when it is replayed.
+bool eager_staged(idf_streams *s, const int32_t *stream_ids, int n_ids)
 {
     const idf_streams::Eager &E = s->eager;
-    if (E.stages < 2 || n_ids != s->B || s->prof_on || (E.read_each && E.since_read == 0)) return false;
+    if (E.stages < 2 || E.recorded || n_ids != s->B || s->prof_on || (E.read_each && E.since_read == 0)) return false;
     for (int i = 0; i < n_ids; ++i)
         if ((stream_ids && stream_ids[i] != i) || s->h[i].r != s->h[0].r) return false;
-    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s->st, &c) == hipSuccess) return c == hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return false;
+    return eager_recording(s) == 0;
 }
 
 int eager_push(idf_streams *s, const int32_t *stream_ids, int n_ids, const void *dev_rows, int n_rows)
@@ -2675,6 +2708,11 @@ int idf_enable_eager(idf_streams *s, void *dev_workspace, size_t workspace_bytes
     s->eager.one_launch = eager_one_launch(s, macs, s->eager.by_stage);
     if (s->eager.one_launch) eager_stages(s, macs);
     if (s->eager.by_stage && s->eager.parts == 0) s->eager.one_launch = s->eager.by_stage = false;
+    s->eager.recorded = eager_recording(s) != 0;
+    if (s->eager.stages > 1 && !s->eager.recorded) {
+        hipError_t e = launch_fill(s->eager.open, 4, 1u, s->st);
+        if (e != hipSuccess) return dev_fail(e, "enable_eager");
+    }
     s->eager.on = true;
     return IDF_OK;
 }

@@ -405,7 +405,7 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_eager_pass(const EagerPass ar
     __shared__ uint32_t events[2 * kPassMax + 2];      // per level
     const int tid = threadIdx.x, stream = sel_stream(sel, blockIdx.x), stage = STAGED ? a.stage0 + (int)blockIdx.y : 0;
     const int k0 = STAGED ? a.first[stage] : 0, n = STAGED ? a.end[stage] : a.n, part = SPLIT ? (int)blockIdx.z : 0, parts = SPLIT ? a.parts : 1;
-    if (STAGED && k0 >= n) return;
+    if (STAGED && (k0 >= n || (a.open && *a.open == 0))) return;
     int words = step_words(&a.st[k0]), next = step_words(&a.st[k0 + 1 < n ? k0 + 1 : k0]);
     if (tid < 2 * kPassMax + 2) events[tid] = 0;
     if constexpr (SPLIT) request_arguments<sizeof(EagerPassStep), WAVES>(&a.st[k0], &a + 1);
