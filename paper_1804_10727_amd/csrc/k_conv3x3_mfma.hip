@@ -560,8 +560,8 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         // bfloat16 rows go through the L2 to memory at once: left there they are written back behind the last workgroup, and the next launch
         // waits for it (us per image, vgg-style net, 64 streams / four out of step / 24 with 8 rows per push: 2382 -> 2314, 4565 -> 4426,
         // 528 -> 520; past both caches, `nt`, 2455, 4688, 560.  float32 rows, half of a line per store, 248 -> 250; rows of the output,
-        // which are larger, 2314 -> 2402; what the gathering kernel emits the same either way).  The s_nop: registers of a store of more than
-        // eight bytes may not be written by the next instruction, which the compiler sees to for its own stores only.
+        // which are larger, 2314 -> 2402; what the gathering kernel emits the same either way).  The s_nop: gfx950 wants two wait states between a
+        // store of more than eight bytes and a vector instruction that writes its registers, which the compiler sees to for its own stores only.
         if constexpr (MC * EB == 1) *at4(reinterpret_cast<uint32_t *>(d), off) = e[0];
         else if constexpr (MC * EB == 2) {
             const i32x2 v{(int)e[0], (int)e[1]};
@@ -571,7 +571,7 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
 #pragma unroll
             for (int q = 0; q < MC * EB / 4; ++q) {
                 const i32x4 v{(int)e[4 * q], (int)e[4 * q + 1], (int)e[4 * q + 2], (int)e[4 * q + 3]};
-                if constexpr (EB == 2) asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 0" ::"v"(off + q * 16), "v"(v), "s"(d) : "memory");
+                if constexpr (EB == 2) asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 1" ::"v"(off + q * 16), "v"(v), "s"(d) : "memory");
                 else *at4(reinterpret_cast<i32x4 *>(d), off + q * 16) = v;
             }
         }
