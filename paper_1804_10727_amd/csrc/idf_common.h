@@ -325,8 +325,8 @@ struct EagerPass {
     int parts;                   // workgroups that share a stage of one layer
     int stage0;                  // first stage of the launch; per stage its layers (none: first == end)
     uint8_t first[kPassStages], end[kPassStages];
-    const uint32_t *open;        // not null: a launch that is made where it finds something else than zero there
     EagerPassStep st[kPassMax];
+    const uint32_t *open;        // not null: the launch does nothing where this is zero
 };
 static_assert(sizeof(EagerPass) + sizeof(StreamSel) <= 4096 && sizeof(GatherBatch<kGatherMax>) + sizeof(StreamSel) <= 4096, "likewise");
 

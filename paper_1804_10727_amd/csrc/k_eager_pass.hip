@@ -396,8 +396,8 @@ template <int EB, int WAVES> __device__ __forceinline__ void pass_hand_on(PassSt
 }
 
 // A workgroup takes one stream through the whole net or, STAGED, through one stage of it (gridDim.y of them, from a.stage0 on): layers
-// first[stage] .. end[stage] - 1.  SPLIT: stages are of one layer, whose tiles gridDim.z workgroups share (a.parts; the rule stands at eager_stages).  (Kernels of their own: which layers they are is a trip to memory, 1.5 % of a pass of eight.)
-template <class T, int WAVES, bool STAGED, bool SPLIT>
+// first[stage] .. end[stage] - 1.  SPLIT: stages are of one layer, whose tiles gridDim.z workgroups share (a.parts; the rule stands at eager_stages).  (Kernels of their own: which layers they are is a trip to memory, 1.5 % of a pass of eight.  So are the launches of a recording that may find nothing left to do, OPEN: asked by every launch, 0.3 to 0.9 %.)
+template <class T, int WAVES, bool STAGED, bool SPLIT, bool OPEN = false>
 __global__ void __launch_bounds__(64 * WAVES, 4) k_eager_pass(const EagerPass args, const StreamSel sel)
 {
     // the arguments are read where the launch put them, a step at a time (by value they would be copied to scratch memory)
@@ -405,7 +405,8 @@ __global__ void __launch_bounds__(64 * WAVES, 4) k_eager_pass(const EagerPass ar
     __shared__ uint32_t events[2 * kPassMax + 2];      // per level
     const int tid = threadIdx.x, stream = sel_stream(sel, blockIdx.x), stage = STAGED ? a.stage0 + (int)blockIdx.y : 0;
     const int k0 = STAGED ? a.first[stage] : 0, n = STAGED ? a.end[stage] : a.n, part = SPLIT ? (int)blockIdx.z : 0, parts = SPLIT ? a.parts : 1;
-    if (STAGED && (k0 >= n || (a.open && *a.open == 0))) return;
+    if (STAGED && k0 >= n) return;
+    if (OPEN && *a.open == 0) return;
     int words = step_words(&a.st[k0]), next = step_words(&a.st[k0 + 1 < n ? k0 + 1 : k0]);
     if (tid < 2 * kPassMax + 2) events[tid] = 0;
     if constexpr (SPLIT) request_arguments<sizeof(EagerPassStep), WAVES>(&a.st[k0], &a + 1);
@@ -486,6 +487,10 @@ hipError_t launch_eager_pass(int prec, const EagerPass &a, int stages, bool smal
     auto of = [&](auto t) {
         using T = decltype(t);
         if (stages == 0) return go(Kernel<k_eager_pass<T, 16, false, false>>{}, 16);
+        if (a.open) {
+            if (a.parts > 0) return go(Kernel<k_eager_pass<T, 4, true, true, true>>{}, 4);
+            return small ? go(Kernel<k_eager_pass<T, 8, true, false, true>>{}, 8) : go(Kernel<k_eager_pass<T, 16, true, false, true>>{}, 16);
+        }
         if (a.parts > 0) return go(Kernel<k_eager_pass<T, 4, true, true>>{}, 4);
         return small ? go(Kernel<k_eager_pass<T, 8, true, false>>{}, 8) : go(Kernel<k_eager_pass<T, 16, true, false>>{}, 16);
     };
