@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -176,7 +177,7 @@ struct idf_streams {
         bool small = false;                       // workgroups of half as many waves
         int first[kPassStages + 1] = {};          // per stage its first layer
         size_t hand[kPassStages][2] = {};         // per stage where its band waits: of even and of odd launches
-        int64_t launch = 0;
+        int64_t launch = 0, newest = INT64_MIN / 2;       // newest: the last that brought a push
         bool on_way[kPassStages] = {};            // the push of launch k, at k mod stages, has not gone through all of them
         std::vector<EagerPass> plan;              // and what each of them does
         // Recorded into a graph (eager_flush), what is on its way may run with a replay, or not before the next call that is not recorded:
@@ -184,8 +185,8 @@ struct idf_streams {
         bool recorded = false, in_graph = false;  // a call on a recording stream; one with something on its way
         unsigned long long graph = 0;             // the recording that has it
         uint32_t *open = nullptr;
-        int since_read = 0;                       // pushes since results were last asked for
-        bool read_each = false;                   // results were asked for after a single push
+        int pays = 0;                             // pushes in a row that the stages pay for, with the launches that empty them
+        int since = 0, span[2] = {INT_MAX, INT_MAX};       // pushes since what was on its way last had to be brought through; before that, and before that
         std::vector<int64_t> lo, hi, seen_lo, seen_hi;
     } eager;
     // a pixel segment being pushed: columns [x_lo, x_hi) of the current row of layer 0 (else the whole row)
@@ -1129,13 +1130,13 @@ int count_waiting_rows(idf_streams *s)
     return IDF_OK;
 }
 
-int eager_flush(idf_streams *s);
+int eager_settle(idf_streams *s);
 
 // Everything still between stages or layers is enqueued: afterwards the work in the stream is
 // that of every pushed row having gone through every layer it can influence.
 int pipeline_drain(idf_streams *s)
 {
-    int rc = eager_flush(s);
+    int rc = eager_settle(s);
     if (rc == IDF_OK) rc = gather_flush(s);
     return rc != IDF_OK ? rc : stg_drain(s);
 }
@@ -1526,6 +1527,10 @@ bool eager_one_launch(const idf_streams *s, std::vector<double> &most, bool &by_
 // units have room for a workgroup each; with more than half as many streams as compute units two stages, of workgroups of eight waves,
 // two of which share a compute unit.  A stage's band waits for the next launch in memory of the workspace that layer by layer only
 // needs: the announced values and differences of the level in front of it, each large enough for a band.
+// Where two workgroups share a compute unit they share its SIMDs, too, and the longer stage has half the waves one workgroup would give it:
+// only where that stage has no more than three fifths of the chain, or the multiply-adds of all layers take no time (1 us) beside the trips.  us per push in one stage : two, 32-16-16-64-64 channels (0.66 to 0.70)
+// 140 streams of 24 positions 52.5 : 58.7, 200 of 40 77.3 : 86.2; 3-64-64 (0.80) 25.2 : 26.3; 3-16-32 (0.62) 200 of 40 12.3 : 12.8, (0.58)
+// 256 of 24 10.7 : 10.0; int8, 16-32-64 (0.58) 14.2 : 13.8, 1-16-32-32 (0.62, few multiply-adds) 11.7 : 10.0.
 // Measured, us per image, one stage : two : three : four (eight) of sixteen waves; two of eight waves: int8, 8 streams of 112 x 112,
 // 3195 : 2117 : 1754 : 1345 (1126); 2466.  float32, 32 x 32, 64 streams 975 : 606 : 595 : 598; 597.  100 streams 994 : 631 : 851 : 871; 629.
 // 128 streams 1003 : 641 : 856 : 879; 634.  200 streams 1024 : 1101 : 1181 : 1264; 943.  256 streams 1028 : 1125 : 1220 : 1319; 952.
@@ -1541,6 +1546,7 @@ void eager_stages(idf_streams *s, const std::vector<double> &macs)
     idf_streams::Eager &E = s->eager;
     const int n = (int)macs.size();
     E.stages = 1; E.small = false; E.parts = 0;
+    E.since = 0; E.span[0] = E.span[1] = INT_MAX;
     if (strict_rows()) return;
     int S = std::min({n, kPassStages, kComputeUnits / s->B});
     if (S < 2 && n > 1 && 2 * s->B <= 2 * kComputeUnits) { S = 2; E.small = true; }
@@ -1557,6 +1563,7 @@ void eager_stages(idf_streams *s, const std::vector<double> &macs)
                 const double c = std::max(best[k - 1][i], sum[j] - sum[i]);
                 if (c < best[k][j]) { best[k][j] = c; from[k][j] = i; }
             }
+    if (E.small && best[S][n] > 0.6 * sum[n] && sum[n] - 3.0 * n > 1.0) return;
     for (int k = S, j = n; k >= 0; --k) { E.first[k] = j; j = from[k][j]; }
     std::vector<int> level;                                        // of each convolution
     for (size_t l = 0; l < net.g.size(); ++l)
@@ -1568,9 +1575,17 @@ void eager_stages(idf_streams *s, const std::vector<double> &macs)
     }
     E.open = (uint32_t *)(E.ws + E.dlt_off[0]);                    // (the first stage's band is the caller's rows)
     E.stages = S;
+    // Pushes in a row for which S - 1 further launches, in which stages stand empty, are made up for: us per push in one stage : in stages, read every
+    // two, three, four, six, twelve pushes.  Stages of many multiply-adds: int8, 8 streams of 112 x 112 29.4 : 27.4, 29.1 : 20.7; float32, 32 x 32,
+    // 64 streams 31.4 : 27.9, 31.0 : 24.5, one stream 29.7 : 26.2.  Of few: int8, 16 of 60 x 60 22.6 : 27.5, 22.3 : 20.3, 4 of 30 x 30 20.8 : 27.0,
+    // 20.5 : 19.7; two stages, 4 streams of 20 positions, 7.8 : 8.8, 7.5 : 7.8, 7.3 : 7.1.  Two workgroups to a compute unit: float32, 256 of 32 x 32
+    // 35.3 : 36.8, 34.2 : 34.5, 33.6 : 33.1, 33.0 : 32.0; 140 of 24 x 40, two rows, 51.7 : 56.6, 51.1 : 53.7, 50.8 : 52.3, 50.3 : 50.8, 49.9 : 49.4;
+    // int8, 16-32-64 channels, 140 of 24, every four 13.2 : 14.2, six 12.2 : 12.8, twelve 11.2 : 11.2.
+    if (E.small) E.pays = net.precision == IDF_PREC_F32 && sum[n] <= 32.0 ? 6 : 12;
+    else E.pays = sum[n] >= 4.3 * S ? 2 : S == 2 ? 4 : 3;
     if (S == n && !E.small) E.parts = std::min(kPassParts, kPartsPerUnit * kComputeUnits / (S * s->B));
     E.plan.resize(S);
-    E.launch = 0;
+    E.launch = 0; E.newest = INT64_MIN / 2;
     std::fill(E.on_way, E.on_way + kPassStages, false);
 }
 
@@ -1607,6 +1622,7 @@ int eager_advance(idf_streams *s, bool fresh, double bytes)
         if (e != hipSuccess) return dev_fail(e, "eager launch");
     }
     E.on_way[E.launch % S] = fresh;
+    if (fresh) E.newest = E.launch;
     ++E.launch;
     return IDF_OK;
 }
@@ -1623,6 +1639,12 @@ int eager_recording(idf_streams *s, unsigned long long *id = nullptr)
     return 1;
 }
 
+bool eager_pending(const idf_streams *s)
+{
+    const idf_streams::Eager &E = s->eager;
+    return E.launch - E.newest < E.stages;
+}
+
 // Every push on its way goes through the stages that are left.  On a recording stream these launches are part of the graph, in front of what
 // else is recorded, and nothing has run when the call returns: the host keeps the pushes, and until it knows better every graph and the
 // next call that is not recorded bring them through.  The first that runs does it (EagerPass::open); the others find nothing left.
@@ -1632,18 +1654,13 @@ int eager_flush(idf_streams *s)
     if (E.stages < 2) return IDF_OK;
     unsigned long long graph = 0;
     const bool recording = eager_recording(s, &graph) == 1;
-    auto pending = [&]() {
-        for (int k = 1; k < E.stages && k <= E.launch; ++k)
-            if (E.on_way[(E.launch - k) % E.stages]) return true;
-        return false;
-    };
-    if (!pending() || (recording && E.in_graph && E.graph == graph)) return IDF_OK;
+    if (!eager_pending(s) || (recording && E.in_graph && E.graph == graph)) return IDF_OK;
     const int64_t launch = E.launch;
     bool on_way[kPassStages];
     std::copy(E.on_way, E.on_way + kPassStages, on_way);
     E.in_graph = E.in_graph || recording;
     int rc = IDF_OK;
-    while (rc == IDF_OK && pending()) rc = eager_advance(s, false, 0);
+    while (rc == IDF_OK && eager_pending(s)) rc = eager_advance(s, false, 0);
     if (rc == IDF_OK && E.in_graph) {
         hipError_t e = launch_fill_zero(E.open, 4, s->st);
         if (e != hipSuccess) rc = dev_fail(e, "eager launch");
@@ -1656,11 +1673,11 @@ int eager_flush(idf_streams *s)
     return rc;
 }
 
-// Results are asked for.
+// Something other than the next push of all streams in step, or the end of a sample: a read, counters, a reset, a push of some streams.
 int eager_settle(idf_streams *s)
 {
     idf_streams::Eager &E = s->eager;
-    if (E.since_read > 0) { E.read_each = E.since_read == 1; E.since_read = 0; }
+    if (E.since > 0) { E.span[1] = E.span[0]; E.span[0] = E.since; E.since = 0; }
     return eager_flush(s);
 }
 
@@ -1732,15 +1749,20 @@ int eager_pass(idf_streams *s, const StreamSel &sel, const void *dev_rows, int n
     return IDF_OK;
 }
 
-// A push in stages: all streams, in step and in order.  Not where results have been asked for push by push (a push then goes through all
-// layers at once: the stages would be as many launches), not while launches are timed (each is then the work of one push), and not into a graph, which may be
-// replayed without the launches that would follow, nor behind one: a recorded read shows what has been pushed when it is replayed.
-bool eager_staged(idf_streams *s, const int32_t *stream_ids, int n_ids)
+// Whether a push of all streams in step goes in stages.  Begun, they go on; they begin where as many pushes as they pay for are to be expected
+// before what is on its way has to be brought through: as many are left of the sample, and were made between the last two reads (the fewer of the
+// two, less those made since; a row of pushes twice as long as pays ends that expectation).  Not while launches are timed (each is then the work of
+// one push), and not into a graph, which may be replayed without the launches that would follow, nor behind one: a recorded read shows what
+// has been pushed when it is replayed.
+bool eager_staged(idf_streams *s, int n_rows)
 {
     const idf_streams::Eager &E = s->eager;
-    if (E.stages < 2 || E.recorded || n_ids != s->B || s->prof_on || (E.read_each && E.since_read == 0)) return false;
-    for (int i = 0; i < n_ids; ++i)
-        if ((stream_ids && stream_ids[i] != i) || s->h[i].r != s->h[0].r) return false;
+    if (E.stages < 2 || E.recorded || s->prof_on) return false;
+    if (!eager_pending(s)) {
+        const int left = (s->net->in_h - (int)s->h[0].r + n_rows - 1) / n_rows, span = std::min(E.span[0], E.span[1]);
+        const int expected = E.since < span ? span - E.since : E.since >= 2 * E.pays ? INT_MAX : 0;
+        if (std::min(left, expected) < E.pays) return false;
+    }
     return eager_recording(s) == 0;
 }
 
@@ -1749,7 +1771,9 @@ int eager_push(idf_streams *s, const int32_t *stream_ids, int n_ids, const void 
     const idf_net &net = *s->net;
     const int n = (int)net.g.size();
     idf_streams::Eager &E = s->eager;
-    const bool staged = eager_staged(s, stream_ids, n_ids);
+    bool in_step = n_ids == s->B;
+    for (int i = 0; in_step && i < n_ids; ++i) in_step = (!stream_ids || stream_ids[i] == i) && s->h[i].r == s->h[0].r;
+    const bool staged = in_step && eager_staged(s, n_rows);
     std::map<int64_t, std::vector<std::pair<int, int>>> groups;
     for (int i = 0; i < n_ids; ++i) {
         const int id = stream_ids ? stream_ids[i] : i;
@@ -1760,8 +1784,7 @@ int eager_push(idf_streams *s, const int32_t *stream_ids, int n_ids, const void 
         if (!staged) groups[h.r].push_back({i, id});
     }
     const int64_t r0 = s->h[0].r;
-    if (!staged || r0 == 0)
-        if (int rc = eager_flush(s)) return rc;
+    if (int rc = !in_step ? eager_settle(s) : !staged || r0 == 0 ? eager_flush(s) : (int)IDF_OK) return rc;
     if (staged) {
         if (r0 == 0) {                             // a sample begins: the output, which is kept whole, is zero
             hipError_t e = launch_fill_zero(E.ws + E.ann_off[n], (size_t)E.ann_rows[n] * E.row_elems[n] * 4 * s->B, s->st);
@@ -1819,7 +1842,7 @@ int eager_push(idf_streams *s, const int32_t *stream_ids, int n_ids, const void 
         h.eager_rows = h.r;                      // rows of the current sample the levels have seen
         if (h.r == net.in_h) h.r = 0;
     }
-    ++E.since_read;
+    if (in_step) ++E.since;
     // a whole sample waits for nothing (a launch that fails here is made again when results are asked for)
     if (staged && s->h[0].r == 0) (void)eager_flush(s);
     return IDF_OK;

@@ -155,6 +155,7 @@ int hipGetSymbolAddress(void **p, const void *) { *p = (void *)(uintptr_t)0x2000
 int hipMemcpy(void *dst, const void *, size_t n, int kind) { if (kind == 2) memset(dst, 0, n); return 0; }
 int hipMemcpyAsync(void *, const void *, size_t, int, void *) { return 0; }
 int hipStreamSynchronize(void *) { return 0; }
+int hipStreamGetCaptureInfo(void *, int *status, unsigned long long *id) { *status = 0; if (id) *id = 0; return 0; }
 int hipEventCreate(void **) { return 2; }
 int hipEventDestroy(void *) { return 0; }
 int hipEventElapsedTime(float *ms, void *, void *) { *ms = 0; return 0; }

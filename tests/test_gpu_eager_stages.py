@@ -80,6 +80,32 @@ def test_against_layers_one_after_the_other(prec, h, w, streams, n_conv, seg, mo
         assert np.array_equal(a, b)                # the same sums in the same order
 
 
+@pytest.mark.parametrize("prec,h,w,streams,n_conv,seg", [("i8", 26, 16, 256, 5, 1), ("f32", 23, 17, 130, 4, 1), ("f32", 17, 20, 201, 4, 1), ("i8", 25, 33, 140, 7, 2)])
+def test_two_workgroups_to_a_compute_unit(prec, h, w, streams, n_conv, seg, monkeypatch):
+    """Samples long enough for the stages to pay there, read once on the way and at the end."""
+    wl = workload(prec, h, w, streams, n_conv, h * w + streams)
+    some = sorted({0, streams // 2, streams - 1})
+    results = []
+    for plain in (False, True):
+        if plain:
+            monkeypatch.setenv("IDF_NO_ROW_STAGES", "1")
+        net, st, x, out = open_eager(wl, seg)
+        seen = []
+        for sample in range(3):
+            for r in range(0, h, seg):
+                st.push_segment(x[:, r:r + seg].contiguous())
+                if sample == 2 and r // seg == 6:
+                    seen.append(st.read_announced(*out).cpu().numpy())
+                    check(wl, seen[-1], r + seg, some)
+            seen.append(st.read_announced(*out).cpu().numpy())
+            check(wl, seen[-1], h, some)
+        results.append((seen, [st.get_stats(b)["events_in"].tolist() for b in some]))
+        st.close(); net.destroy()
+    assert results[0][1] == results[1][1]
+    for a, b in zip(results[0][0], results[1][0]):
+        assert np.array_equal(a, b)
+
+
 def test_streams_apart_reset_and_inner_levels():
     wl = workload("f32", 19, 18, 3, 4, 7)
     net, st, x, out = open_eager(wl, 1)

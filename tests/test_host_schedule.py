@@ -363,3 +363,91 @@ def test_division_of_a_window_into_rows_is_exact():
     for n in sorted({k_w * cells for k_w in range(1, 33) for cells in range(1, 65)} - {1}):
         few = q[:32 * n + 4]
         assert np.array_equal(few * np.uint64(-(-2**32 // n)) >> np.uint64(32), few // np.uint64(n)), n
+
+
+# ---- eager emission in stages -----------------------------------------------------------------------------------------------
+def enable_eager(st, net, streams, seg):
+    import ctypes as C
+    nb = C.c_size_t()
+    st.check(st.L.idf_query_eager_bytes(net._h, streams, seg, C.byref(nb)))
+    st.check(st.L.idf_enable_eager(st.h, C.c_void_p(1 << 42), nb))
+
+
+def eager_reads(rt, prec, h, w, channels, pools, streams, seg, every, staged):
+    """Reads after every so many pushes, or at the end of the sample (0): a launch per push, or more where the pushes go in stages."""
+    import ctypes as C
+    net = chain(prec, h, w, channels, pools)
+    n_layers = len(channels) - 1 + len(pools)
+    st = host_runtime.Streams(net, streams, seg)
+    enable_eager(st, net, streams, seg)
+    pushes = -(-h // seg)
+    for sample in range(4):                        # (the first reads are what later pushes go by)
+        rt.host_begin()
+        for i in range(pushes):
+            st.push(min(seg, h - i * seg))
+            if (every and (i + 1) % every == 0) or i + 1 == pushes:
+                st.check(st.L.idf_read_announced(st.h, n_layers, None, streams, C.c_void_p(1 << 51)))
+    assert (rt.host_launches(b"k_eager_pass") > pushes) == staged, (rt.host_launches(b"k_eager_pass"), pushes)
+    assert rt.host_error() == b"", rt.host_error()
+    st.close()
+    net.destroy()
+
+
+EVENTS, EVENTS_POOLS = [1, 16, 16, 32, 32, 64, 64, 64, 64], (1, 3, 5)
+SMALL = [3, 32, 32, 64, 64]
+
+
+@pytest.mark.parametrize("prec,h,w,channels,pools,streams,seg,every,staged", [
+    ("i8", 60, 60, EVENTS, EVENTS_POOLS, 16, 1, 1, False), ("i8", 60, 60, EVENTS, EVENTS_POOLS, 16, 1, 2, False),
+    ("i8", 60, 60, EVENTS, EVENTS_POOLS, 16, 1, 3, True), ("i8", 60, 60, EVENTS, EVENTS_POOLS, 16, 1, 0, True),
+    ("i8", 112, 112, EVENTS, EVENTS_POOLS, 8, 1, 2, True),                       # stages of many multiply-adds
+    ("f32", 32, 32, SMALL, (1,), 64, 1, 1, False), ("f32", 32, 32, SMALL, (1,), 64, 1, 2, True),
+    ("f32", 30, 20, [3, 16, 16], (), 4, 1, 3, False), ("f32", 30, 20, [3, 16, 16], (), 4, 1, 5, True),
+    ("f32", 32, 32, SMALL, (1,), 256, 1, 4, False), ("f32", 32, 32, SMALL, (1,), 256, 1, 8, True),          # two workgroups to a compute unit
+    ("f32", 15, 32, SMALL, (1,), 256, 3, 0, False), ("f32", 18, 32, SMALL, (1,), 256, 3, 0, True),          # samples of five and of six pushes
+    ("f32", 24, 40, SMALL, (1,), 140, 2, 6, False), ("f32", 24, 40, SMALL, (1,), 140, 2, 0, True),
+    ("f32", 48, 24, [3, 16, 16, 64, 64], (), 140, 1, 0, False),                  # one stage would have most of the work
+    ("i8", 48, 24, [1, 16, 32, 32], (), 200, 1, 0, True),                        # little work anywhere
+    ("i8", 26, 16, [2, 16, 32, 16, 48, 16], (0, 3), 256, 1, 0, True), ("f32", 23, 17, [2, 16, 32, 16, 48], (0,), 130, 1, 0, True),
+    ("f32", 17, 20, [2, 16, 32, 16, 48], (0,), 201, 1, 0, True), ("i8", 25, 33, [2, 16, 32, 16, 48, 16, 16, 32], (0, 3), 140, 2, 0, True),
+])
+def test_pushes_go_in_stages_where_the_reads_leave_enough_of_them(runtime, prec, h, w, channels, pools, streams, seg, every, staged):
+    host_runtime.run(runtime, "test_host_schedule", "eager_reads", prec, h, w, channels, pools, streams, seg, every, staged)
+
+
+def eager_history(rt):
+    """What was read push by push before is in stages again after a row of pushes, and at once after two; counters and pushes of some
+    streams count as reads do."""
+    import ctypes as C
+    net = chain("i8", 112, 30, EVENTS, EVENTS_POOLS)
+    st = host_runtime.Streams(net, 3)
+    enable_eager(st, net, 3, 1)
+
+    def read():
+        st.check(st.L.idf_read_announced(st.h, len(EVENTS) + 2, None, 3, C.c_void_p(1 << 51)))
+
+    def launches(n, after):                        # of n pushes and whatever comes after them
+        rt.host_begin()
+        for _ in range(n):
+            st.push(1)
+        after()
+        return rt.host_launches(b"k_eager_pass")
+    assert launches(1, read) == 8 and launches(1, read) == launches(1, read) == 1
+    assert launches(20, read) == 6 + 14 + 7        # six by themselves, the others in stages
+    assert launches(20, read) == 1 + 5 + 14 + 7    # (one of the last two reads came after a single push)
+    assert launches(20, read) == 20 + 7
+    for _ in range(2):
+        launches(1, lambda: st.stats(0))
+    assert launches(1, lambda: st.stats(0)) == 1
+    st.check(st.L.idf_reset_streams(st.h, None, 3))
+    for _ in range(2):
+        launches(6, read)
+    for _ in range(2):                             # pushes of some streams and of all in turn
+        launches(1, lambda: [st.push(1, [i]) for i in range(3)])
+    assert launches(1, lambda: [st.push(1, [i]) for i in range(3)]) == 1 + 3
+    st.close()
+    net.destroy()
+
+
+def test_what_pushes_in_stages_go_by(runtime):
+    host_runtime.run(runtime, "test_host_schedule", "eager_history")
