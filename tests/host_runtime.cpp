@@ -29,6 +29,7 @@ long g_launches = 0, g_fail_at = -1, g_lds_limit = 160 * 1024 - 256;
 int g_last = 0;
 struct Config { Dim3 grid, block; size_t lds; void *stream; } g_config;
 std::vector<std::pair<std::string, long>> g_count;
+long g_max_lds = 0;                                    // dynamic LDS of any launch
 
 struct Row { int layer, y; };
 std::map<uintptr_t, Row> g_rows;                       // address of a row in a ring -> what lies there
@@ -102,6 +103,7 @@ int launch(const void *fn, Dim3 grid, void **args, size_t lds)
     if (at == g_fail_at) return g_last = 98;           // (a launch failure)
     const std::string &name = g_names[fn];
     if (grid.x < 1 || grid.y < 1 || grid.z < 1 || grid.y > 65535 || grid.z > 65535) error("grid of " + name);
+    g_max_lds = (long)lds > g_max_lds ? (long)lds : g_max_lds;
     if (lds > 64 * 1024) ++g_large[fn];
     if (lds > 64 * 1024 && (long)lds > g_dynamic_lds[fn]) error("LDS of " + str(lds) + " that was not asked for: " + name);
     bool found = false;
@@ -124,10 +126,11 @@ long host_launches(const char *part)
     for (auto &c : g_count) if (!part || c.first.find(part) != std::string::npos) n += c.second;
     return n;
 }
+long host_max_lds() { return g_max_lds; }
 long host_large_kernels() { return (long)g_large.size(); }
 const char *host_error() { return g_error.c_str(); }
 void host_fail_in(long n) { g_fail_at = n < 0 ? -1 : g_launches + n; }
-void host_begin() { g_rows.clear(); g_next.clear(); g_error.clear(); g_count.clear(); g_large.clear(); g_fail_at = -1; }
+void host_begin() { g_rows.clear(); g_next.clear(); g_error.clear(); g_count.clear(); g_large.clear(); g_fail_at = -1; g_max_lds = 0; }
 
 // ---- the runtime ----
 void **__hipRegisterFatBinary(const void *) { static void *handle[1]; return handle; }

@@ -28,7 +28,7 @@ def run(so, script, function, *args):
 def start(so):
     rt = C.CDLL(so, mode=C.RTLD_GLOBAL)         # in front of the real runtime for whatever is loaded from here on
     rt.host_error.restype = C.c_char_p
-    rt.host_launches.restype = C.c_long
+    rt.host_launches.restype = rt.host_max_lds.restype = C.c_long
     rt.host_launches.argtypes = [C.c_char_p]
     rt.host_fail_in.argtypes = [C.c_long]
     sys.modules["torch"] = types.ModuleType("torch")      # (the binding loads it for its runtime; not wanted here)

@@ -451,3 +451,29 @@ def eager_history(rt):
 
 def test_what_pushes_in_stages_go_by(runtime):
     host_runtime.run(runtime, "test_host_schedule", "eager_history")
+
+
+def eager_lds(rt, prec, h, w, channels, pools, streams, seg):
+    """The largest LDS of a launch: stages of one layer that several workgroups share, and the whole net in one workgroup."""
+    import os
+    lds = []
+    for plain in (False, True):
+        if plain:
+            os.environ["IDF_NO_ROW_STAGES"] = "1"
+        net = chain(prec, h, w, channels, pools)
+        st = host_runtime.Streams(net, streams, seg)
+        enable_eager(st, net, streams, seg)
+        rt.host_begin()
+        for r in range(0, h, seg):
+            st.push(min(seg, h - r))
+        assert rt.host_error() == b"", rt.host_error()
+        assert rt.host_launches(b"k_eager_pass") > 0
+        lds.append(rt.host_max_lds())
+        st.close()
+        net.destroy()
+    assert lds[0] <= 0.8 * lds[1], lds                 # a band, and not the band in front and the one behind
+
+
+@pytest.mark.parametrize("prec,h,w,channels,pools,streams,seg", [("i8", 40, 112, EVENTS, EVENTS_POOLS, 8, 1), ("f32", 20, 60, SMALL, (1,), 64, 1)])
+def test_a_shared_stage_asks_for_its_band_only(runtime, prec, h, w, channels, pools, streams, seg):
+    host_runtime.run(runtime, "test_host_schedule", "eager_lds", prec, h, w, channels, pools, streams, seg)
