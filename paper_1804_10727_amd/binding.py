@@ -70,9 +70,9 @@ def load_library():
     global _LIB
     if _LIB is not None:
         return _LIB
-    if not os.path.exists(lib_path()) or not os.path.exists(os.path.join(_HERE, "_push.so")):
+    if not os.path.exists(lib_path()):
         from . import build as _build
-        _build.build()
+        _build.build_library()
     # PyTorch ships its own copy of the HIP runtime (same soname).  Device pointers and streams
     # are only meaningful inside the runtime instance that made them, so that copy must be the
     # one this library binds to: import torch first, then the loader resolves our dependency
@@ -125,11 +125,21 @@ def load_library():
 
 
 def load_push():
-    """Load _push.so, which needs torch's libraries in the process: with the first streams, whose pushes go through it."""
+    """Load the extension module of push.cpp, which needs torch's libraries in the process: with the first streams, whose pushes go through
+    it.  Built first, it alone, if this interpreter's and this torch's is not there."""
     global _push
     if _push is None:
         L = load_library()
-        from . import _push as native
+        import importlib.util
+        import sys
+        from . import build as _build
+        path, name = _build.push_path(), __package__ + "._push"
+        if not os.path.exists(path):
+            _build.build_push()
+        spec = importlib.util.spec_from_file_location(name, path)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
+        sys.modules[name] = sys.modules[__package__]._push = native
         native.bind(C.cast(L.idf_push_segment, C.c_void_p).value)
         _push = native.push
     return _push

@@ -1,6 +1,7 @@
 """Pushes go into the library by csrc/push.cpp: what it hands over is what the conversion by ctypes hands over, for every form of the
 arguments; what it does not take goes that way, and raises what it raised."""
 import ctypes as C
+import os
 
 import numpy as np
 import pytest
@@ -101,3 +102,38 @@ def test_what_is_no_plain_tensor_goes_the_long_way():
     assert binding._push(0, None, None, None) is None
     with pytest.raises(TypeError):
         binding._push(0, None)
+
+
+def test_the_module_is_of_this_interpreter_and_torch(monkeypatch):
+    """Another torch's or interpreter's module has another name; where this one's is absent it is built, and nothing else."""
+    import shutil
+    import sys
+    import sysconfig
+    from paper_1804_10727_amd import build
+    binding.load_push()
+    from paper_1804_10727_amd import _push as native
+    monkeypatch.setitem(sys.modules, native.__name__, native)          # (both are as they were behind this test)
+    monkeypatch.setattr(idf, "_push", native)
+    path = build.push_path()
+    assert path.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and torch.__version__ in path
+    monkeypatch.setattr(torch, "__version__", "0.0.0+another")
+    other = build.push_path()
+    assert other != path and not build.up_to_date()
+    built = []
+
+    def build_push():
+        built.append(build.push_path())
+        shutil.copy(path, other)                   # (this torch's, in place of one that cannot be built here)
+    monkeypatch.setattr(build, "build_push", build_push)
+    for name in ("build", "build_library"):
+        monkeypatch.setattr(build, name, lambda *a, **k: pytest.fail("the library is there"))
+    monkeypatch.setattr(binding, "_push", None)
+    try:
+        monkeypatch.setattr(binding, "_LIB", None)
+        binding.load_library()                     # the library alone asks for no module
+        assert not built
+        binding.load_push()
+        assert built == [other]
+    finally:
+        if os.path.exists(other):
+            os.remove(other)
