@@ -149,6 +149,10 @@ def trace_summary(stats_csv, bench_log):
             dom = r
     assert dom, f"no {sym} kernel in the trace"
     avg_s = float(dom["AverageNs"]) * 1e-9
+    if eager:                   # the passes in stages, of which the bench line knows the bytes only
+        per_step = int(dom["Calls"]) / (bench["steps"] + bench["warmup"])
+        rf = dict(rf, launches_per_step=round(per_step, 2), algorithmic_bytes_per_launch=rf["algorithmic_bytes_per_step"] / per_step,
+                  executed_flops_per_launch=rf["executed_flops_per_step"] / per_step)
     if rf["bound"] == "hbm":
         ach = rf["algorithmic_bytes_per_launch"] / avg_s / 1e9
     else:
@@ -344,6 +348,13 @@ def run_workload(config, steps_arg=None, warmup_arg=None, eager=False, push_batc
                  "algorithmic_bytes_per_launch": bytes_per_launch, "executed_flops_per_launch": flops_per_launch,
                  "kernel_time_share": dom["total_ms"] / sum(p["total_ms"] for p in prof),
                  "gpu_busy_ms_per_step": sum(p["total_ms"] for p in prof)})
+    if eager:
+        # Launches are bracketed one push at a time; the timed passes go in stages, launches of another kind and number.  What holds for
+        # them is the whole pass: its bytes, and its time.
+        roof = {"bound": "hbm", "kernel": dom["name"], "achieved": dom["algorithmic_bytes"] / (dt / steps) / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
+                "frac": dom["algorithmic_bytes"] / (dt / steps) / PEAK_HBM, "traffic": None, "algorithmic_bytes_per_step": dom["algorithmic_bytes"],
+                "executed_flops_per_step": 2.0 * macs_exec,
+                "a_push_by_itself": {"launches_per_step": dom["launches"], "avg_launch_us": avg_s * 1e6, "gpu_busy_ms_per_step": roof["gpu_busy_ms_per_step"]}}
 
     res = {
         "metric": "input_pixels_per_s", "value": value, "unit": "pixels/s", "n_gpus": 1, "steps": steps,

@@ -395,7 +395,8 @@ const char *idf_layer_kernel(const idf_streams *s, int layer);
  * kernel's own start and end.  idf_profile_end synchronises the stream and returns, per kernel
  * family and layer (name "family@layer"; families that span the whole net have no "@layer"), the
  * number of launches, the summed execution time and the summed algorithmic bytes (network input
- * read, retained state read and written, weights once per launch, output rows written).
+ * read, retained state read and written, weights once per launch, output rows written).  Under eager
+ * emission every push then goes through all layers by itself, without the ones before and behind it on their way.
  * out: host array of max_kinds entries; *n_kinds receives how many were filled. */
 typedef struct {
     char name[32];
