@@ -1,6 +1,7 @@
 """1-D layers whose windows go through LDS, which they do in launches of many tiles: one, two and four streams per tile, a stream that
 fills no tile, windows over the ring's end and the signal's ends, strides, channels of one K-step and several to a row; bit for bit what
-a launch of few streams gives, and the oracle's values."""
+a launch of few streams gives, and the oracle's values.  (That these launches go that way, and those of few streams do not, is checked
+without a GPU: test_host_schedule.)"""
 import numpy as np
 import pytest
 
@@ -10,13 +11,16 @@ from workloads import conv
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("chans,k,strides,pad,seg,streams", [
+CASES = [
     ((1, 32, 32, 64, 64, 64, 64), 9, (1, 2, 1, 2, 1, 1), 0, 16, 61),       # four streams per tile behind the second stride, two before
     ((1, 64, 64, 64), 9, (1, 1, 1), 4, 16, 45),                            # one stream per tile; rows outside the signal
     ((1, 64, 64, 48), 9, (1, 1, 2), 0, 5, 130),                            # two, five of eight positions; channels that fill no tile
     ((1, 16, 32, 16), 9, (1, 1, 1), 0, 13, 200),                           # one K-step to a row
-    ((4, 64, 64), 5, (2, 2), 2, 8, 150),
-])
+    ((4, 64, 64), 5, (2, 2), 2, 16, 150),                                  # windows of every second row, over the signal's ends
+]
+
+
+@pytest.mark.parametrize("chans,k,strides,pad,seg,streams", CASES)
 def test_windows_through_lds(chans, k, strides, pad, seg, streams):
     rng = np.random.default_rng(streams)
     n, h = len(strides), 150

@@ -477,3 +477,26 @@ def eager_lds(rt, prec, h, w, channels, pools, streams, seg):
 @pytest.mark.parametrize("prec,h,w,channels,pools,streams,seg", [("i8", 40, 112, EVENTS, EVENTS_POOLS, 8, 1), ("f32", 20, 60, SMALL, (1,), 64, 1)])
 def test_a_shared_stage_asks_for_its_band_only(runtime, prec, h, w, channels, pools, streams, seg):
     host_runtime.run(runtime, "test_host_schedule", "eager_lds", prec, h, w, channels, pools, streams, seg)
+
+
+# ---- windows by way of LDS --------------------------------------------------------------------------------------------------
+def staged_windows(rt, chans, k, strides, pad, seg, streams):
+    import paper_1804_10727_amd as idf
+    from workloads import conv
+    h, n = 150, len(strides)
+    layers = [conv(chans[i], chans[i + 1], k, 1, s=strides[i], p_h=pad) for i in range(n)]
+    net = idf.Net("f32", h, 1, chans[0], layers, [np.ones((L["c_out"], L["c_in"], k, 1), np.float32) for L in layers])
+    for b in (streams, 3):
+        st = host_runtime.Streams(net, b, seg)
+        rt.host_begin()
+        for r in range(0, h, seg):
+            st.push(min(seg, h - r))
+        assert (rt.host_launches(b"k_conv_gather_rows_staged") >= 3) == (b == streams), (b, rt.host_launches(b"k_conv_gather_rows_staged"))
+        st.close()
+    net.destroy()
+
+
+def test_windows_go_through_lds_where_tiles_are_many(runtime):
+    from test_gpu_gather_lds import CASES
+    for case in CASES:
+        host_runtime.run(runtime, "test_host_schedule", "staged_windows", *case)
