@@ -47,6 +47,35 @@ def test_reads_in_between(h, w, streams, seg, reads, monkeypatch):
     assert stats[0] == stats[1] == [2 * np.count_nonzero(wl["x"][b]) for b in some]
 
 
+@pytest.mark.parametrize("h,w,streams,seg,reads", [(14, 97, 3, 2, ()), (14, 97, 3, 2, tuple(range(7))), (13, 64, 60, 3, (1, 2)), (11, 128, 1, 3, (0, 1, 3))])
+def test_counters_of_every_layer(h, w, streams, seg, reads, monkeypatch):
+    """Whole numbers with few weights per channel: every sum is exact (eight taps per channel, below 8^4), whatever its order, and so is
+    which differences are zero."""
+    wl = workload(h, w, streams, h + w)
+    rng = np.random.default_rng(h)
+    for i, L in enumerate(wl["layers"]):
+        if L["kind"] != "conv":
+            continue
+        k = np.zeros((L["c_out"], 9 * L["c_in"]), np.float32)
+        for o in range(L["c_out"]):
+            k[o, rng.choice(9 * L["c_in"], 8, replace=False)] = rng.choice([-1, 1], 8)
+        wl["weights"][i] = k.reshape(L["c_out"], L["c_in"], 3, 3)
+    wl["x"] = (rng.random(wl["x"].shape) < 0.5).astype(np.float32)
+    results = []
+    for plain in (False, True):
+        if plain:
+            monkeypatch.setenv("IDF_NO_ROW_STAGES", "1")
+        net, st, x, out = open_eager(wl, seg)
+        for i, r in enumerate(range(0, h, seg)):
+            st.push_segment(x[:, r:r + seg].contiguous())
+            if i in reads:
+                st.read_announced(*out)
+        results.append((st.read_announced(*out).cpu().numpy(), [st.get_stats(b)["events_in"].tolist() for b in range(streams)]))
+        st.close(); net.destroy()
+    assert all(min(e) > 0 for e in results[0][1]) and results[0][1] == results[1][1]
+    assert np.array_equal(results[0][0], results[1][0])
+
+
 def test_streams_apart():
     wl = workload(12, 100, 4, 5)
     net, st, x, out = open_eager(wl, 2)
