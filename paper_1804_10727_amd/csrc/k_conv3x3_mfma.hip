@@ -560,8 +560,13 @@ __device__ __forceinline__ void conv_rows(ArgStep &a, const StreamSel &sel, cons
         // bfloat16 rows go through the L2 to memory at once: left there they are written back behind the last workgroup, and the next launch
         // waits for it (us per image, vgg-style net, 64 streams / four out of step / 24 with 8 rows per push: 2382 -> 2314, 4565 -> 4426,
         // 528 -> 520; past both caches, `nt`, 2455, 4688, 560.  float32 rows, half of a line per store, 248 -> 250; rows of the output,
-        // which are larger, 2314 -> 2402; what the gathering kernel emits the same either way).  The s_nop: gfx950 wants two wait states between a
-        // store of more than eight bytes and a vector instruction that writes its registers, which the compiler sees to for its own stores only.
+        // which are larger, 2314 -> 2402; what the gathering kernel emits the same either way).  In launches of 2,500 to 7,500 positions either
+        // way is ahead by up to 1 %, with no order in width or streams: 29 streams of 57 x 130 406 -> 410, 24 of 48 x 200 357 -> 361, 28 of 48 x 224
+        // 388 -> 384, 43 of 73 x 176 683 -> 678; below and above it is this one, 12 of 48 x 224 292 -> 290, 56 of 48 x 224 497 -> 483.  Asking whether a
+        // launch of narrow tiles has 3,600 positions or fewer costs what it gains: 24 of 48 x 200 1.004 of the time without -> 0.997, 28 of 48 x 224
+        // 0.985 -> 0.998, 32 of 48 x 128 with two rows 0.992 -> 1.013.
+        // The s_nop: gfx950 wants two wait states between a store of more than eight bytes and a vector instruction that writes its registers,
+        // which the compiler sees to for its own stores only.
         if constexpr (MC * EB == 1) *at4(reinterpret_cast<uint32_t *>(d), off) = e[0];
         else if constexpr (MC * EB == 2) {
             const i32x2 v{(int)e[0], (int)e[1]};
