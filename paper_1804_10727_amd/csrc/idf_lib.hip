@@ -186,7 +186,8 @@ struct idf_streams {
         unsigned long long graph = 0;             // the recording that has it
         uint32_t *open = nullptr;
         int pays = 0;                             // pushes in a row that the stages pay for, with the launches that empty them
-        int since = 0, span[2] = {INT_MAX, INT_MAX};       // pushes since what was on its way last had to be brought through; before that, and before that
+        int since = 0;                            // pushes since something other than pushes of all streams in step came last (eager_settle)
+        int span[2] = {INT_MAX, INT_MAX};         // and how many there were before that, and before that
         std::vector<int64_t> lo, hi, seen_lo, seen_hi;
     } eager;
     // a pixel segment being pushed: columns [x_lo, x_hi) of the current row of layer 0 (else the whole row)
@@ -1528,9 +1529,10 @@ bool eager_one_launch(const idf_streams *s, std::vector<double> &most, bool &by_
 // two of which share a compute unit.  A stage's band waits for the next launch in memory of the workspace that layer by layer only
 // needs: the announced values and differences of the level in front of it, each large enough for a band.
 // Where two workgroups share a compute unit they share its SIMDs, too, and the longer stage has half the waves one workgroup would give it:
-// only where that stage has no more than three fifths of the chain, or the multiply-adds of all layers take no time (1 us) beside the trips.  us per push in one stage : two, 32-16-16-64-64 channels (0.66 to 0.70)
-// 140 streams of 24 positions 52.5 : 58.7, 200 of 40 77.3 : 86.2; 3-64-64 (0.80) 25.2 : 26.3; 3-16-32 (0.62) 200 of 40 12.3 : 12.8, (0.58)
-// 256 of 24 10.7 : 10.0; int8, 16-32-64 (0.58) 14.2 : 13.8, 1-16-32-32 (0.62, few multiply-adds) 11.7 : 10.0.
+// only where that stage has no more than three fifths of the chain, or the multiply-adds of all layers take no time (1 us) beside the trips.
+// us per push in one stage : two, 3-16-16-64-64 channels (0.66 to 0.70) 140 streams of 24 positions 52.5 : 58.7, 200 of 40 77.3 : 86.2; 3-64-64
+// (0.80) 25.2 : 26.3; 3-16-32 (0.62) 200 of 40 12.3 : 12.8, (0.58) 256 of 24 10.7 : 10.0; int8, 16-32-64 (0.58) 14.2 : 13.8, 1-16-32-32 (0.62, few
+// multiply-adds) 11.7 : 10.0.
 // Measured, us per image, one stage : two : three : four (eight) of sixteen waves; two of eight waves: int8, 8 streams of 112 x 112,
 // 3195 : 2117 : 1754 : 1345 (1126); 2466.  float32, 32 x 32, 64 streams 975 : 606 : 595 : 598; 597.  100 streams 994 : 631 : 851 : 871; 629.
 // 128 streams 1003 : 641 : 856 : 879; 634.  200 streams 1024 : 1101 : 1181 : 1264; 943.  256 streams 1028 : 1125 : 1220 : 1319; 952.

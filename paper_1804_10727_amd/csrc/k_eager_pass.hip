@@ -396,7 +396,9 @@ template <int EB, int WAVES> __device__ __forceinline__ void pass_hand_on(PassSt
 }
 
 // A workgroup takes one stream through the whole net or, STAGED, through one stage of it (gridDim.y of them, from a.stage0 on): layers
-// first[stage] .. end[stage] - 1.  SPLIT: stages are of one layer, whose tiles gridDim.z workgroups share (a.parts; the rule stands at eager_stages).  (Kernels of their own: which layers they are is a trip to memory, 1.5 % of a pass of eight.  So are the launches of a recording that may find nothing left to do, OPEN: asked by every launch, 0.3 to 0.9 %.)
+// first[stage] .. end[stage] - 1.  SPLIT: stages are of one layer, whose tiles gridDim.z workgroups share (a.parts; the rule stands at eager_stages).  (Kernels
+// of their own: which layers they are is a trip to memory, 1.5 % of a pass of eight.  So are the launches of a recording that may find nothing
+// left to do, OPEN: asked by every launch, 0.3 to 0.9 %.)
 template <class T, int WAVES, bool STAGED, bool SPLIT, bool OPEN = false>
 __global__ void __launch_bounds__(64 * WAVES, 4) k_eager_pass(const EagerPass args, const StreamSel sel)
 {

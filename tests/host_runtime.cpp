@@ -29,6 +29,7 @@ long g_launches = 0, g_fail_at = -1, g_lds_limit = 160 * 1024 - 256;
 int g_last = 0;
 struct Config { Dim3 grid, block; size_t lds; void *stream; } g_config;
 std::vector<std::pair<std::string, long>> g_count;
+unsigned long long g_recording = 0;
 long g_max_lds = 0;                                    // dynamic LDS of any launch
 
 struct Row { int layer, y; };
@@ -126,6 +127,7 @@ long host_launches(const char *part)
     for (auto &c : g_count) if (!part || c.first.find(part) != std::string::npos) n += c.second;
     return n;
 }
+void host_record(unsigned long long id) { g_recording = id; }      // (0: the stream is not being recorded)
 long host_max_lds() { return g_max_lds; }
 long host_large_kernels() { return (long)g_large.size(); }
 const char *host_error() { return g_error.c_str(); }
@@ -158,7 +160,7 @@ int hipGetSymbolAddress(void **p, const void *) { *p = (void *)(uintptr_t)0x2000
 int hipMemcpy(void *dst, const void *, size_t n, int kind) { if (kind == 2) memset(dst, 0, n); return 0; }
 int hipMemcpyAsync(void *, const void *, size_t, int, void *) { return 0; }
 int hipStreamSynchronize(void *) { return 0; }
-int hipStreamGetCaptureInfo(void *, int *status, unsigned long long *id) { *status = 0; if (id) *id = 0; return 0; }
+int hipStreamGetCaptureInfo(void *, int *status, unsigned long long *id) { *status = g_recording != 0; if (id) *id = g_recording; return 0; }
 int hipEventCreate(void **) { return 2; }
 int hipEventDestroy(void *) { return 0; }
 int hipEventElapsedTime(float *ms, void *, void *) { *ms = 0; return 0; }

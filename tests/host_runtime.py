@@ -31,6 +31,7 @@ def start(so):
     rt.host_launches.restype = rt.host_max_lds.restype = C.c_long
     rt.host_launches.argtypes = [C.c_char_p]
     rt.host_fail_in.argtypes = [C.c_long]
+    rt.host_record.argtypes = [C.c_ulonglong]
     sys.modules["torch"] = types.ModuleType("torch")      # (the binding loads it for its runtime; not wanted here)
     return rt
 

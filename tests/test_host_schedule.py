@@ -500,3 +500,39 @@ def test_windows_go_through_lds_where_tiles_are_many(runtime):
     from test_gpu_gather_lds import CASES
     for case in CASES:
         host_runtime.run(runtime, "test_host_schedule", "staged_windows", *case)
+
+
+# ---- eager emission recorded into a graph -----------------------------------------------------------------------------------
+def eager_recorded(rt):
+    """What is on its way goes into every graph once, by launches that look whether it is still to be done, and through once more, by the
+    same kind, with the next call that is not recorded.  Pushes go through all layers at once from then on."""
+    import ctypes as C
+    net = chain("i8", 112, 30, EVENTS, EVENTS_POOLS)
+    st = host_runtime.Streams(net, 3)
+    enable_eager(st, net, 3, 1)
+
+    def read():
+        st.check(st.L.idf_read_announced(st.h, len(EVENTS) + 2, None, 3, C.c_void_p(1 << 51)))
+
+    def launches(*calls):
+        rt.host_begin()
+        for f in calls:
+            f()
+        return rt.host_launches(b"k_eager_passINS0_8TraitsI8ELi4ELb1ELb1ELb1EE"), rt.host_launches(b"k_eager_pass"), rt.host_launches(b"k_fill")
+
+    def push():
+        st.push(1)
+    assert launches(*[push] * 10)[:2] == (0, 10)
+    for graph in (7, 8):
+        rt.host_record(graph)
+        assert launches(push, push, read, push) == (7, 7 + 3, 1)
+    rt.host_record(0)
+    assert launches(read) == (7, 7, 1)
+    assert launches(read) == (0, 0, 0)
+    assert launches(*[push] * 20, read) == (0, 20, 0)
+    st.close()
+    net.destroy()
+
+
+def test_recorded_calls_bring_through_what_is_on_its_way(runtime):
+    host_runtime.run(runtime, "test_host_schedule", "eager_recorded")
